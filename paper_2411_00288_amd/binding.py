@@ -1,8 +1,13 @@
-"""ctypes binding over the C ABI declared in include/ss.h.
+"""Binding over the C ABI declared in include/ss.h.
 
 Argument marshalling only: every step of the path (compression, convolution, epilogue) runs in
 the HIP library.  PyTorch provides device memory and the stream.  There is no fallback: if the
 library has not been built, importing fails with an instruction to build it.
+
+A plain good call goes through the extension module ``_native`` (csrc/ss_python.cpp): it checks, allocates
+and enqueues in compiled code.  Where that declines (returns None: something is wrong with the arguments, or an option it
+does not handle, such as an explicit stream), the checks below find the reason and report it, or make the call through
+ctypes.
 """
 from __future__ import annotations
 
@@ -85,6 +90,7 @@ def _load() -> ctypes.CDLL:
 
 
 _lib = _load()
+from . import _native  # noqa: E402  (links against the library loaded above)
 
 
 def status_string(status: int) -> str:
@@ -143,9 +149,20 @@ def ss_dense_bytes(desc: ss_weight_desc) -> int:
     return int(out.value)
 
 
+def _packed_or_raise(r, what):
+    """The packed buffer, or the SSError for the (status, row, block) of an invalid mask."""
+    if type(r) is tuple:
+        raise SSError(r[0], what, detail=(r[1], r[2]))
+    return r
+
+
 def ss_mask_compress(desc: ss_weight_desc, W: torch.Tensor, M: torch.Tensor, packed: torch.Tensor | None = None,
                      stream=None) -> torch.Tensor:
     """W [cout, K] 16-bit, M [cout, K] uint8 (device) -> packed uint8 buffer (device)."""
+    if stream is None:
+        r = _native.pack(0, desc, W, None, M, packed)
+        if r is not None:
+            return _packed_or_raise(r, "ss_mask_compress")
     K = desc.cin * desc.kh * desc.kw
     if W is not None and W.numel() != desc.cout * K or M is not None and M.numel() != desc.cout * K:
         raise SSError(SS_ERR_INVALID_ARG, "ss_mask_compress: W/M size does not match the descriptor")
@@ -164,6 +181,10 @@ def ss_mask_compress(desc: ss_weight_desc, W: torch.Tensor, M: torch.Tensor, pac
 def ss_mask_update_compress(desc: ss_weight_desc, W: torch.Tensor, U: torch.Tensor, M: torch.Tensor,
                             packed: torch.Tensor | None = None, stream=None) -> torch.Tensor:
     """W <- round16(W + U) in place, and packed <- compress(W, M): re-packing after a weight update."""
+    if stream is None:
+        r = _native.pack(1, desc, W, U, M, packed)
+        if r is not None:
+            return _packed_or_raise(r, "ss_mask_update_compress")
     K = desc.cin * desc.kh * desc.kw
     if W is None or U is None or M is None or W.numel() != desc.cout * K or U.numel() != desc.cout * K or \
             M.numel() != desc.cout * K or U.dtype != W.dtype:
@@ -195,6 +216,10 @@ def ss_mask_decompress(desc: ss_weight_desc, packed: torch.Tensor, out: torch.Te
 
 def ss_dense_pack(desc: ss_weight_desc, W: torch.Tensor, M: torch.Tensor | None, dense: torch.Tensor | None = None,
                   stream=None) -> torch.Tensor:
+    if stream is None:
+        r = _native.pack(2, desc, W, None, M, dense)
+        if r is not None:
+            return r
     K = desc.cin * desc.kh * desc.kw
     if W.numel() != desc.cout * K or (M is not None and M.numel() != desc.cout * K):
         raise SSError(SS_ERR_INVALID_ARG, "ss_dense_pack: W/M size does not match the descriptor")
@@ -324,6 +349,15 @@ def _conv(fn, what, desc, x, wbuf, bias, stride, pad, act, y, workspace, stream,
     return y
 
 
+def _launch(what, kind, desc1, desc2, x, w1, w2, scale, bias1, bias2, residual, y, workspace, nhw, stride, pad, act1, act2=0, pool=None):
+    """The callable that enqueues a marshalled call on torch's current stream (arguments checked by the caller)."""
+    def failed(st):
+        raise SSError(st, what)
+    tensors = (x, w1, w2, scale, bias1, bias2, residual, y, workspace)
+    return _native.launch(kind, desc1, desc2, tuple(None if t is None else t.data_ptr() for t in tensors), _nbytes(workspace),
+                          tuple(nhw), (stride[0], stride[1], pad[0], pad[1]), int(act1), int(act2), pool, tensors, failed)
+
+
 def prepare_conv2d(desc, x, wbuf, bias=None, stride=(1, 1), pad=(0, 0), act=SS_ACT_NONE, y=None, workspace=None,
                    sparse=True, residual=None):
     """Marshal the arguments of ss_conv2d_fwd / ss_conv2d_dense_fwd (ss_conv2d_res_fwd / ss_conv2d_dense_res_fwd
@@ -334,20 +368,17 @@ def prepare_conv2d(desc, x, wbuf, bias=None, stride=(1, 1), pad=(0, 0), act=SS_A
     with_res = residual is not None
     what = ("ss_conv2d_res_fwd" if sparse else "ss_conv2d_dense_res_fwd") if with_res else \
            ("ss_conv2d_fwd" if sparse else "ss_conv2d_dense_fwd")
-    fn = getattr(_lib, what)
-    args, y, ws = _conv_args(what, desc, x, wbuf, bias, stride, pad, act, y, workspace, None, residual, with_res)
-    keep = (desc, x, wbuf, bias, y, ws, residual)
-
-    def launch(_keep=keep):
-        st = fn(*args, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
-        if st != SS_OK:
-            raise SSError(st, what)
-    return launch, y
+    _args, y, ws = _conv_args(what, desc, x, wbuf, bias, stride, pad, act, y, workspace, None, residual, with_res)
+    return _launch(what, 0 if sparse else 1, desc, None, x, wbuf, None, None, bias, None, residual, y, ws, x.shape[:3], stride, pad, act), y
 
 
 def ss_conv2d_fwd(desc, x, packed, bias=None, stride=(1, 1), pad=(0, 0), act=SS_ACT_NONE, y=None, workspace=None,
                   stream=None) -> torch.Tensor:
     """2:4-sparse convolution: x NHWC [N,H,W,cin] -> y NHWC [N,Ho,Wo,cout] (same 16-bit dtype)."""
+    if stream is None:
+        r = _native.conv(0, desc, x, packed, None, bias, None, stride, pad, act, y, workspace)
+        if r is not None:
+            return r
     return _conv(_lib.ss_conv2d_fwd, "ss_conv2d_fwd", desc, x, packed, bias, stride, pad, act, y, workspace, stream)
 
 
@@ -378,6 +409,10 @@ def ss_conv2d_fwd_static_ws(desc, x, packed, bias=None, stride=(1, 1), pad=(0, 0
 def ss_conv2d_dense_fwd(desc, x, dense, bias=None, stride=(1, 1), pad=(0, 0), act=SS_ACT_NONE, y=None,
                         workspace=None, stream=None) -> torch.Tensor:
     """The dense-MFMA twin on the operand built by ss_dense_pack."""
+    if stream is None:
+        r = _native.conv(1, desc, x, dense, None, bias, None, stride, pad, act, y, workspace)
+        if r is not None:
+            return r
     return _conv(_lib.ss_conv2d_dense_fwd, "ss_conv2d_dense_fwd", desc, x, dense, bias, stride, pad, act, y,
                  workspace, stream)
 
@@ -385,6 +420,10 @@ def ss_conv2d_dense_fwd(desc, x, dense, bias=None, stride=(1, 1), pad=(0, 0), ac
 def ss_conv2d_res_fwd(desc, x, packed, bias=None, residual=None, stride=(1, 1), pad=(0, 0), act=SS_ACT_NONE, y=None,
                       workspace=None, stream=None) -> torch.Tensor:
     """2:4-sparse convolution closing a residual block: y = act(conv(x) + bias + residual), residual NHWC like y."""
+    if stream is None:
+        r = _native.conv(0, desc, x, packed, None, bias, residual, stride, pad, act, y, workspace)
+        if r is not None:
+            return r
     return _conv(_lib.ss_conv2d_res_fwd, "ss_conv2d_res_fwd", desc, x, packed, bias, stride, pad, act, y, workspace,
                  stream, residual, True)
 
@@ -392,6 +431,10 @@ def ss_conv2d_res_fwd(desc, x, packed, bias=None, residual=None, stride=(1, 1), 
 def ss_conv2d_dense_res_fwd(desc, x, dense, bias=None, residual=None, stride=(1, 1), pad=(0, 0), act=SS_ACT_NONE,
                             y=None, workspace=None, stream=None) -> torch.Tensor:
     """The dense-MFMA twin of ss_conv2d_res_fwd."""
+    if stream is None:
+        r = _native.conv(1, desc, x, dense, None, bias, residual, stride, pad, act, y, workspace)
+        if r is not None:
+            return r
     return _conv(_lib.ss_conv2d_dense_res_fwd, "ss_conv2d_dense_res_fwd", desc, x, dense, bias, stride, pad, act, y,
                  workspace, stream, residual, True)
 
@@ -427,21 +470,18 @@ def prepare_conv2d_q8(desc, x, wbuf, scale=None, bias=None, stride=(1, 1), pad=(
                       workspace=None, sparse=True):
     """prepare_conv2d for the 8-bit integer entry points: returns (launch, y)."""
     what = "ss_conv2d_q8_fwd" if sparse else "ss_conv2d_q8_dense_fwd"
-    fn = getattr(_lib, what)
-    args, y, ws = _q8_args(what, desc, x, wbuf, scale, bias, stride, pad, act, y, workspace)
-    keep = (desc, x, wbuf, scale, bias, y, ws)
-
-    def launch(_keep=keep):
-        st = fn(*args, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
-        if st != SS_OK:
-            raise SSError(st, what)
-    return launch, y
+    _args, y, ws = _q8_args(what, desc, x, wbuf, scale, bias, stride, pad, act, y, workspace)
+    return _launch(what, 2 if sparse else 3, desc, None, x, wbuf, None, scale, bias, None, None, y, ws, x.shape[:3], stride, pad, act), y
 
 
 def ss_conv2d_q8_fwd(desc, x, packed, scale=None, bias=None, stride=(1, 1), pad=(0, 0), act=SS_ACT_NONE, y=None,
                      workspace=None, stream=None) -> torch.Tensor:
     """2:4-sparse convolution on 8-bit operands (int8, or FP8 E4M3 bytes): x NHWC -> y NHWC float16 =
     act(scale * sum + bias)."""
+    if stream is None:
+        r = _native.conv(2, desc, x, packed, scale, bias, None, stride, pad, act, y, workspace)
+        if r is not None:
+            return r
     args, y, _ws = _q8_args("ss_conv2d_q8_fwd", desc, x, packed, scale, bias, stride, pad, act, y, workspace)
     st = _lib.ss_conv2d_q8_fwd(*args, _stream_ptr(stream))
     if st != SS_OK:
@@ -452,6 +492,10 @@ def ss_conv2d_q8_fwd(desc, x, packed, scale=None, bias=None, stride=(1, 1), pad=
 def ss_conv2d_q8_dense_fwd(desc, x, dense, scale=None, bias=None, stride=(1, 1), pad=(0, 0), act=SS_ACT_NONE, y=None,
                            workspace=None, stream=None) -> torch.Tensor:
     """The dense integer-MFMA twin of ss_conv2d_q8_fwd."""
+    if stream is None:
+        r = _native.conv(3, desc, x, dense, scale, bias, None, stride, pad, act, y, workspace)
+        if r is not None:
+            return r
     args, y, _ws = _q8_args("ss_conv2d_q8_dense_fwd", desc, x, dense, scale, bias, stride, pad, act, y, workspace)
     st = _lib.ss_conv2d_q8_dense_fwd(*args, _stream_ptr(stream))
     if st != SS_OK:
@@ -478,18 +522,13 @@ def prepare_conv2d_pw_fused(desc1, x, w1, bias1, stride, pad, act1, desc2, w2, b
         raise SSError(SS_ERR_INVALID_ARG, f"{what}: y must be {shp} {x.dtype}")
     if residual is not None and (tuple(residual.shape) != shp or residual.dtype != x.dtype or not residual.is_contiguous()):
         raise SSError(SS_ERR_INVALID_ARG, f"{what}: residual must be contiguous {shp} {x.dtype}")
-    fn = getattr(_lib, what)
-    args = (ctypes.byref(desc1), _dev_ptr(x, "x", (torch_dtype(desc1.dtype),)), N, H, W, _dev_ptr(w1, "weights 1"),
-            _dev_ptr(bias1, "bias1", (torch.float32,), allow_none=True), stride[0], stride[1], pad[0], pad[1], act1,
-            ctypes.byref(desc2), _dev_ptr(w2, "weights 2"), _dev_ptr(bias2, "bias2", (torch.float32,), allow_none=True),
-            _dev_ptr(residual, "residual", allow_none=True), act2, _dev_ptr(y, "y"))
-    keep = (desc1, desc2, x, w1, w2, bias1, bias2, residual, y)
-
-    def launch(_keep=keep):
-        st = fn(*args, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
-        if st != SS_OK:
-            raise SSError(st, what)
-    return launch, y
+    for t, name, dtypes in ((x, "x", (torch_dtype(desc1.dtype),)), (w1, "weights 1", None), (w2, "weights 2", None), (y, "y", None)):
+        _dev_ptr(t, name, dtypes)
+    for t, name in ((bias1, "bias1"), (bias2, "bias2")):
+        _dev_ptr(t, name, (torch.float32,), allow_none=True)
+    _dev_ptr(residual, "residual", allow_none=True)
+    return _launch(what, 4 if sparse else 5, desc1, desc2, x, w1, w2, None, bias1, bias2, residual, y, None, (N, H, W), stride, pad,
+                   act1, act2), y
 
 
 def ss_conv2d_pw_fused_query(desc1, stride, pad, desc2, sparse=True):
@@ -505,6 +544,9 @@ def ss_conv2d_pw_fused_query(desc1, stride, pad, desc2, sparse=True):
 def ss_conv2d_pw_fused_fwd(desc1, x, packed1, bias1, stride, pad, act1, desc2, packed2, bias2=None, residual=None,
                            act2=SS_ACT_NONE, y=None) -> torch.Tensor:
     """k x k masked convolution followed by a 1x1 masked convolution (+ residual), the intermediate kept on chip."""
+    r = _native.fused(1, desc1, x, packed1, bias1, stride, pad, act1, desc2, packed2, bias2, residual, act2, y)
+    if r is not None:
+        return r
     launch, y = prepare_conv2d_pw_fused(desc1, x, packed1, bias1, stride, pad, act1, desc2, packed2, bias2, residual,
                                         act2, y, sparse=True)
     launch()
@@ -514,6 +556,9 @@ def ss_conv2d_pw_fused_fwd(desc1, x, packed1, bias1, stride, pad, act1, desc2, p
 def ss_conv2d_pw_fused_dense_fwd(desc1, x, dense1, bias1, stride, pad, act1, desc2, dense2, bias2=None, residual=None,
                                  act2=SS_ACT_NONE, y=None) -> torch.Tensor:
     """The dense twin of ss_conv2d_pw_fused_fwd."""
+    r = _native.fused(0, desc1, x, dense1, bias1, stride, pad, act1, desc2, dense2, bias2, residual, act2, y)
+    if r is not None:
+        return r
     launch, y = prepare_conv2d_pw_fused(desc1, x, dense1, bias1, stride, pad, act1, desc2, dense2, bias2, residual,
                                         act2, y, sparse=False)
     launch()
@@ -523,6 +568,10 @@ def ss_conv2d_pw_fused_dense_fwd(desc1, x, dense1, bias1, stride, pad, act1, des
 def ss_maxpool2d(x: torch.Tensor, k: int = 3, stride: int = 2, pad: int = 1, y: torch.Tensor | None = None,
                  stream=None) -> torch.Tensor:
     """NHWC max pooling of a 16-bit tensor (positions outside the image do not take part)."""
+    if stream is None:
+        r = _native.maxpool(x, k, stride, pad, y)
+        if r is not None:
+            return r
     if x is None or x.dim() != 4 or x.dtype not in _T16 or stride <= 0:
         raise SSError(SS_ERR_INVALID_ARG, "ss_maxpool2d: x must be a 16-bit NHWC tensor")
     N, H, W, C = x.shape
@@ -538,9 +587,29 @@ def ss_maxpool2d(x: torch.Tensor, k: int = 3, stride: int = 2, pad: int = 1, y: 
     return y
 
 
+def prepare_maxpool2d(x, k=3, stride=2, pad=1, y=None):
+    """Marshal the arguments of ss_maxpool2d once; returns (launch, y), as prepare_conv2d does."""
+    if x is None or x.dim() != 4 or x.dtype not in _T16 or stride <= 0:
+        raise SSError(SS_ERR_INVALID_ARG, "ss_maxpool2d: x must be a 16-bit NHWC tensor")
+    N, H, W, C = x.shape
+    shp = (N, (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1, C)
+    if y is None:
+        y = torch.empty(shp, dtype=x.dtype, device=x.device)
+    elif tuple(y.shape) != shp or y.dtype != x.dtype:
+        raise SSError(SS_ERR_INVALID_ARG, f"ss_maxpool2d: y must be {shp} {x.dtype}")
+    _dev_ptr(x, "x")
+    _dev_ptr(y, "y")
+    return _launch("ss_maxpool2d", 6, None, None, x, None, None, None, None, None, None, y, None, (N, H, W), (stride, stride),
+                   (pad, pad), 0, 0, (C, SS_F16 if x.dtype == torch.float16 else SS_BF16, k)), y
+
+
 def ss_dwconv2d_fwd(x: torch.Tensor, w: torch.Tensor, bias: torch.Tensor | None = None, pad=(0, 0), act=SS_ACT_NONE,
                     y: torch.Tensor | None = None, stream=None) -> torch.Tensor:
     """Depthwise convolution, stride 1: x NHWC 16-bit, w [kh, kw, C] of the same dtype -> y NHWC."""
+    if stream is None:
+        r = _native.dwconv(x, w, bias, pad, act, y)
+        if r is not None:
+            return r
     if x is None or w is None or x.dim() != 4 or w.dim() != 3 or w.shape[2] != x.shape[3] or w.dtype != x.dtype or \
             x.dtype not in (torch.float16, torch.bfloat16):
         raise SSError(SS_ERR_INVALID_ARG, "ss_dwconv2d_fwd: x must be NHWC 16-bit and w [kh, kw, C] of the same dtype")

@@ -128,7 +128,10 @@ inline SplitPlan plan_split(const ss_weight_desc *d, long long P, int Ks, int nc
     if (n > nchunks) n = nchunks;
     if (n < 1) n = 1;
     pl.nsplit = n;
-    pl.ctr_bytes = (size_t)((pl.tiles * 4 + 255) / 256 * 256);
+    // Every plan the library makes by itself has at most 128 tiles (half of 256 compute units): their counters take the same
+    // 512 bytes, so that plans of different sizes can follow each other in one workspace without one's partial sums
+    // lying where the other expects its counters at zero.
+    pl.ctr_bytes = (size_t)((pl.tiles * 4 + 511) / 512 * 512);
     pl.part_bytes = (size_t)pl.tiles * n * pl.bm * pl.bn * 4;
     return pl;
 }

@@ -102,8 +102,7 @@ class Trunk:
         pos = {}                                            # op name -> index of its launch
         for op in self.ops:
             if op.kind == "pool":
-                x, y = self.bufs[op.src], self.bufs[op.dst]
-                self.launches.append(lambda x=x, y=y: ss.ss_maxpool2d(x, 3, 2, 1, y=y))
+                self.launches.append(ss.prepare_maxpool2d(self.bufs[op.src], 3, 2, 1, y=self.bufs[op.dst])[0])
                 continue
             L = op.layer
             desc, wbuf, bias, use_sparse = prepared[op.name]
