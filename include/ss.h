@@ -17,7 +17,8 @@
  *   - Every function returns an int status: SS_OK (0) or a negative SS_ERR_* code.  Nothing throws.
  *   - Unless a parameter is marked [host], every data pointer is a DEVICE pointer.  The caller
  *     owns every buffer; the library never allocates or frees device memory.  Its only state is a per-device
- *     record of which kernels have had their shared-memory limit raised (set once, at a kernel's first launch).
+ *     record of which kernels have had their shared-memory limit raised (set once, at a kernel's first launch) and,
+ *     for each device, a few words of pinned host memory and events with which the packing calls wait.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  The convolution
  *     calls only enqueue work on it and return; ss_mask_compress additionally waits for the
  *     stream once, because it reports the mask's validity.

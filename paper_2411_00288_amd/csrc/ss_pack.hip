@@ -1,43 +1,41 @@
 // Weight compressor, decompressor and dense-twin packer (Fig. 1; Sec. 3.1 Eq. 2; Sec. 3.3 Eq. 6).
 // Integer / bit work only: no floating-point instruction touches a weight.
 #include "ss_internal.h"
+#include <hip/hip_ext.h>
+#include <mutex>
+#include <vector>
 
 namespace ss {
 
 // ---------------------------------------------------------------------------------------------
-// header
+// header: its words travel as a kernel argument and are written by the packing kernel's first workgroup
 // ---------------------------------------------------------------------------------------------
-__global__ void write_header_kernel(uint32_t *hdr, uint32_t magic, int cout, int cin, int kh, int kw,
-                                    int dtype, int korder, int Mt, int Ks)
+constexpr int kHdrWords = kHdrFirstBad + 1;
+struct PackHeader {
+    uint32_t w[kHdrWords];
+};
+
+static PackHeader pack_header(uint32_t magic, const ss_weight_desc *d, const TileDims &t)
 {
-    int i = threadIdx.x;            // 64 threads, one word each
-    uint32_t v = 0;
-    switch (i) {
-        case 0: v = magic; break;
-        case 1: v = 1; break;
-        case 2: v = (uint32_t)cout; break;
-        case 3: v = (uint32_t)cin; break;
-        case 4: v = (uint32_t)kh; break;
-        case 5: v = (uint32_t)kw; break;
-        case 6: v = (uint32_t)dtype; break;
-        case 7: v = (uint32_t)korder; break;
-        case 8: v = (uint32_t)Mt; break;
-        case 9: v = (uint32_t)Ks; break;
-        case 10: v = kNoBadBlock; break;
-        default: break;
-    }
-    hdr[i] = v;
+    return {{magic, 1u, (uint32_t)d->cout, (uint32_t)d->cin, (uint32_t)d->kh, (uint32_t)d->kw, (uint32_t)d->dtype, (uint32_t)d->korder,
+             (uint32_t)t.Mt, (uint32_t)t.Ks, kNoBadBlock}};
 }
 
 // ---------------------------------------------------------------------------------------------
 // compressor
 //
-// One thread produces one lane of one value tile: 8 packed values (16 bytes) and the 16 index
-// bits that go with them.  Lane l of tile (mt, ks) owns row 32*mt + l%32 and the four blocks
-// 8*ks + {0,1,4,5} + 2*(l/32) of that row, i.e. the reduction indices 32*ks + 8*(l/32) + [0,8)
-// and 32*ks + 16 + 8*(l/32) + [0,8): this is where gfx950's 32x32x32 sparse MFMA expects the
-// A operand of a lane to come from, given that lane l of the B operand holds the 16 consecutive
-// reduction indices 32*ks + 16*(l/32) + [0,16).
+// Lane l of value tile (mt, ks) owns row 32*mt + l%32 and the four blocks 8*ks + {0,1,4,5} + 2*(l/32) of that row, i.e. the
+// reduction indices 32*ks + 8*(l/32) + [0,8) and 32*ks + 16 + 8*(l/32) + [0,8): this is where gfx950's 32x32x32 sparse MFMA
+// expects the A operand of a lane to come from, given that lane l of the B operand holds the 16 consecutive reduction
+// indices 32*ks + 16*(l/32) + [0,16).  (8-bit operands, integer or FP8 -- bytes are copied, never interpreted --: lane l owns
+// in slots 2j, 2j+1, j = 0..7, block 16*ks + 8*(j/4) + 4*(l/32) + j%4, because the 32x32x64 instructions pair slot s of
+// lane l with the bytes 16*(l/32) + 4*((s%8)/2) + [0,4) of the B lane of the same column in lane group s/8.)
+//
+// Memory-bound: (2 + 1 + 1.125) bytes per 16-bit weight, 8.125 with an update.  A workgroup packs 32 rows x 32 blocks (128
+// weights, kTilesX tiles): consecutive lanes read consecutive blocks of a row (8-byte weight and 4-byte mask loads, 256
+// contiguous bytes per row), the packed words cross LDS into tile order and leave as 16-byte stores.  Reading in tile
+// order instead (lanes down the rows, 16 contiguous bytes per row and load) touched four times the cache lines:
+// 512 x 4608 with an update took 10.5 us so, 6.4 us here (3 TB/s; 3.7 us at the rate of a large copy).
 // ---------------------------------------------------------------------------------------------
 // binary32 sum of two 16-bit values, rounded to nearest even back to the storage type
 template <int DT>
@@ -52,63 +50,115 @@ __device__ __forceinline__ uint32_t add16(uint32_t a, uint32_t b)
     }
 }
 
-// UPD: the weights are first moved to V = W + U (written back over W; every element belongs to exactly one
-// thread's blocks), then V is packed.
-template <int DT, bool UPD>
-__global__ __launch_bounds__(256) void compress_kernel(uint16_t *__restrict__ W, const uint16_t *__restrict__ U,
-                                                       const uint8_t *__restrict__ M, uint8_t *__restrict__ packed,
-                                                       int cout, int K, int Mt, int Ks, int Kp)
-{
-    int tid = blockIdx.x * 256 + threadIdx.x;
-    int total = Mt * Ks * 64;
-    if (tid >= total) return;
-    int lane = tid & 63;
-    int tile = tid >> 6;
-    int ks = tile % Ks;
-    int mt = tile / Ks;
-    int row = mt * 32 + (lane & 31);
-    int ga = lane >> 5;
-    int G = K >> 2;
+constexpr int kPackBlocks = 32;      // blocks of a row per workgroup
 
-    uint32_t v[4];
-    uint32_t nibbles = 0;
-    uint32_t *first_bad = reinterpret_cast<uint32_t *>(packed) + kHdrFirstBad;
+// A mask word with exactly two of its four bytes set to one?
+__device__ __forceinline__ bool mask_ok(uint32_t m)
+{
+    return (m & 0xFEFEFEFEu) == 0 && __popc(m) == 2;
+}
+
+// UPD: the weights are first moved to V = W + U (written back over W; every element belongs to exactly one
+// thread's blocks), then V is packed.  *any_bad (host memory) is set when a block's mask is invalid; its place is looked up
+// by find_bad_kernel then.
+template <int DT, bool UPD>
+__global__ __launch_bounds__(256) void compress_kernel(void *__restrict__ W, const void *__restrict__ U,
+                                                       const uint8_t *__restrict__ M, uint8_t *__restrict__ packed,
+                                                       int cout, int K, int Mt, int Ks, int Kp, PackHeader hdr, uint32_t *any_bad)
+{
+    constexpr bool BYTES = is_byte_type(DT);
+    constexpr int TB = BYTES ? 16 : 8;                    // blocks per row of a tile
+    constexpr int TX = kPackBlocks / TB;                  // tiles of the workgroup
+    constexpr int J = TB / 2;                             // blocks per lane of a tile
+    __shared__ __attribute__((aligned(16))) uint32_t vals[TX * 256];      // the tiles as they will be stored
+    __shared__ __attribute__((aligned(16))) uint8_t nibs[TX * 64 * J];    // one nibble per byte, in slot order
+    const int tid = threadIdx.x;
+    const int G = K >> 2, gx = (Ks + TX - 1) / TX;
+    const int mt = blockIdx.x / gx, ks0 = (blockIdx.x - mt * gx) * TX;
+    if (blockIdx.x == 0 && tid < 64) reinterpret_cast<uint32_t *>(packed)[tid] = tid < kHdrWords ? hdr.w[tid] : 0u;
+
+    const int col = tid & 31;                             // block of the row this thread packs
+    const int g = ks0 * TB + col;
+    uint32_t m[4];
+    uint64_t w[4], u[4];
 #pragma unroll
-    for (int j = 0; j < 4; j++) {
-        int g = 8 * ks + 4 * (j >> 1) + 2 * ga + (j & 1);
-        uint32_t pair = 0, nib = 0x4;
+    for (int i = 0; i < 4; i++) {
+        const int row = mt * 32 + (tid >> 5) + 8 * i;
+        m[i] = 0x00000101u;                               // padding: +0 values with the nibble of positions 0, 1
+        w[i] = u[i] = 0;
         if (row < cout && g < G) {
-            size_t e = (size_t)row * K + 4 * (size_t)g;
-            uint32_t m = *reinterpret_cast<const uint32_t *>(M + e);
-            uint2 w = *reinterpret_cast<const uint2 *>(W + e);
-            if constexpr (UPD) {
-                const uint2 u = *reinterpret_cast<const uint2 *>(U + e);
-                w.x = add16<DT>(w.x & 0xFFFFu, u.x & 0xFFFFu) | (add16<DT>(w.x >> 16, u.x >> 16) << 16);
-                w.y = add16<DT>(w.y & 0xFFFFu, u.y & 0xFFFFu) | (add16<DT>(w.y >> 16, u.y >> 16) << 16);
-                *reinterpret_cast<uint2 *>(W + e) = w;
-            }
-            bool ok = ((m & 0xFEFEFEFEu) == 0) && (__popc(m) == 2);
-            if (ok) {
-                int i0 = (__ffs(m) - 1) >> 3;
-                int i1 = (31 - __clz(m)) >> 3;
-                uint64_t w64 = ((uint64_t)w.y << 32) | w.x;
-                uint32_t v0 = (uint32_t)(w64 >> (16 * i0)) & 0xFFFFu;
-                uint32_t v1 = (uint32_t)(w64 >> (16 * i1)) & 0xFFFFu;
-                pair = v0 | (v1 << 16);
-                nib = (uint32_t)(i0 | (i1 << 2));
+            const size_t e = (size_t)row * G + g;         // in blocks
+            m[i] = reinterpret_cast<const uint32_t *>(M)[e];
+            if constexpr (BYTES) {
+                w[i] = static_cast<const uint32_t *>(W)[e];
             } else {
-                atomicMin(first_bad, (uint32_t)((size_t)row * G + g));
+                w[i] = static_cast<const uint64_t *>(W)[e];
+                if constexpr (UPD) u[i] = static_cast<const uint64_t *>(U)[e];
             }
         }
-        v[j] = pair;
-        nibbles |= nib << (4 * j);
     }
-    uint4 out = make_uint4(v[0], v[1], v[2], v[3]);
-    *reinterpret_cast<uint4 *>(packed + kHeaderBytes + ((size_t)tile * 64 + lane) * 16) = out;
-    uint16_t *meta = reinterpret_cast<uint16_t *>(packed + kHeaderBytes + (size_t)Mt * Ks * 1024);
-    size_t mi = (((size_t)mt * Kp + (ks >> 1)) * 64 + lane) * 2 + (ks & 1);
-    meta[mi] = (uint16_t)nibbles;
-    if ((Ks & 1) && ks == Ks - 1) meta[mi + 1] = 0x4444;   // unused upper half of the last pair
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const int r = (tid >> 5) + 8 * i, row = mt * 32 + r;
+        if constexpr (UPD) {
+            uint64_t v = 0;
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+                v |= (uint64_t)add16<DT>((uint32_t)(w[i] >> (16 * e)) & 0xFFFFu, (uint32_t)(u[i] >> (16 * e)) & 0xFFFFu) << (16 * e);
+            w[i] = v;
+            if (row < cout && g < G) static_cast<uint64_t *>(W)[(size_t)row * G + g] = v;
+        }
+        const bool ok = mask_ok(m[i]);
+        bad |= !ok;
+        const int i0 = ok ? (__ffs(m[i]) - 1) >> 3 : 0, i1 = ok ? (31 - __clz(m[i])) >> 3 : 1;
+        const int t = col / TB, gl = col % TB;
+        // block gl of the tile's row -> lane group and slot pair
+        const int ga = BYTES ? (gl >> 2) & 1 : (gl >> 1) & 1;
+        const int j = BYTES ? 4 * (gl >> 3) + (gl & 3) : 2 * (gl >> 2) + (gl & 1);
+        const int lane = 32 * ga + r;
+        if constexpr (BYTES) {
+            const uint32_t pair = ((uint32_t)(w[i] >> (8 * i0)) & 0xFFu) | (((uint32_t)(w[i] >> (8 * i1)) & 0xFFu) << 8);
+            reinterpret_cast<uint16_t *>(vals)[(t * 64 + lane) * 8 + j] = (uint16_t)pair;
+        } else {
+            vals[(t * 64 + lane) * 4 + j] = ((uint32_t)(w[i] >> (16 * i0)) & 0xFFFFu) | (((uint32_t)(w[i] >> (16 * i1)) & 0xFFFFu) << 16);
+        }
+        nibs[(t * 64 + lane) * J + j] = (uint8_t)(i0 | (i1 << 2));
+    }
+    if (bad) *any_bad = 1;
+    __syncthreads();
+    // values: one 16-byte vector per thread and 256-vector pass
+#pragma unroll
+    for (int v = tid; v < TX * 64; v += 256)
+        if (ks0 + (v >> 6) < Ks)
+            *reinterpret_cast<uint4 *>(packed + kHeaderBytes + (((size_t)mt * Ks + ks0) * 64 + v) * 16) = *reinterpret_cast<const uint4 *>(vals + v * 4);
+    // indices: one word per lane and tile (8-bit) or pair of tiles (16-bit; TX is even, so pairs do not straddle workgroups)
+    uint32_t *meta = reinterpret_cast<uint32_t *>(packed + kHeaderBytes + (size_t)Mt * Ks * 1024);
+    auto word = [&](int t, int lane) {                    // the nibbles of a lane of a tile
+        uint32_t out = 0;
+#pragma unroll
+        for (int q = 0; q < J / 4; q++) {
+            const uint32_t b = *reinterpret_cast<const uint32_t *>(nibs + (t * 64 + lane) * J + 4 * q);
+            out |= ((b & 0xFu) | ((b >> 4) & 0xF0u) | ((b >> 8) & 0xF00u) | ((b >> 12) & 0xF000u)) << (16 * q);
+        }
+        return out;
+    };
+    if (tid < 128) {
+        const int t = tid >> 6, lane = tid & 63;
+        if constexpr (BYTES) {
+            if (ks0 + t < Ks) meta[((size_t)mt * Ks + ks0 + t) * 64 + lane] = word(t, lane);
+        } else if ((ks0 >> 1) + t < Kp) {
+            // (the upper half of an odd last pair: blocks past the row's end, i.e. padding nibbles)
+            meta[((size_t)mt * Kp + (ks0 >> 1) + t) * 64 + lane] = word(2 * t, lane) | (word(2 * t + 1, lane) << 16);
+        }
+    }
+}
+
+// The first (row-major) block with an invalid mask, into the header.  Runs only after a compression found one.
+__global__ __launch_bounds__(256) void find_bad_kernel(const uint8_t *__restrict__ M, uint32_t *first_bad, uint32_t blocks)
+{
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+    if (i < blocks && !mask_ok(reinterpret_cast<const uint32_t *>(M)[i])) atomicMin(first_bad, i);
 }
 
 // thread per (row, block): inverse permutation, writes 4 elements (8 bytes)
@@ -136,85 +186,6 @@ __global__ __launch_bounds__(256) void decompress_kernel(const uint8_t *__restri
     *reinterpret_cast<uint2 *>(Wm + (size_t)row * K + 4 * (size_t)g) = make_uint2((uint32_t)w64, (uint32_t)(w64 >> 32));
 }
 
-// Dense twin operand: thread per (tile (mt, ks, h), lane); 8 elements k = 32*ks + 16*(l/32) + 8*h + s.
-__global__ __launch_bounds__(256) void dense_pack_kernel(const uint16_t *__restrict__ W, const uint8_t *__restrict__ M,
-                                                         uint8_t *__restrict__ dense, int cout, int K, int Mt, int Ks)
-{
-    int tid = blockIdx.x * 256 + threadIdx.x;
-    int total = Mt * Ks * 2 * 64;
-    if (tid >= total) return;
-    int lane = tid & 63;
-    int tile = tid >> 6;
-    int h = tile & 1;
-    int ks = (tile >> 1) % Ks;
-    int mt = (tile >> 1) / Ks;
-    int row = mt * 32 + (lane & 31);
-    int kbase = 32 * ks + 16 * (lane >> 5) + 8 * h;
-    uint32_t o[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (int s = 0; s < 8; s++) {
-        int k = kbase + s;
-        uint32_t val = 0;
-        if (row < cout && k < K) {
-            size_t e = (size_t)row * K + k;
-            bool keep = (M == nullptr) || (M[e] != 0);
-            val = keep ? (uint32_t)W[e] : 0u;
-        }
-        o[s >> 1] |= val << (16 * (s & 1));
-    }
-    *reinterpret_cast<uint4 *>(dense + kHeaderBytes + ((size_t)tile * 64 + lane) * 16) = make_uint4(o[0], o[1], o[2], o[3]);
-}
-
-// ---------------------------------------------------------------------------------------------
-// 8-bit operands (integer or FP8: bytes are copied, never interpreted).  One thread produces one lane of one value tile: 16 packed bytes and the 32 index
-// bits that go with them.  Lane l of tile (mt, ks) owns row 32*mt + l%32 and, in slots 2j, 2j+1 (j = 0..7),
-// block 16*ks + 8*(j/4) + 4*(l/32) + j%4: gfx950's 32x32x64 8-bit sparse MFMAs pair slot s of lane l with the
-// bytes 16*(l/32) + 4*((s%8)/2) + [0,4) of the B lane of the same column in lane group s/8, and B lane groups
-// hold the reduction indices 64*ks + 32*group + [0,32).
-// ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void compress8_kernel(const uint8_t *__restrict__ W, const uint8_t *__restrict__ M,
-                                                        uint8_t *__restrict__ packed, int cout, int K, int Mt, int Ks)
-{
-    int tid = blockIdx.x * 256 + threadIdx.x;
-    int total = Mt * Ks * 64;
-    if (tid >= total) return;
-    int lane = tid & 63;
-    int tile = tid >> 6;
-    int ks = tile % Ks;
-    int mt = tile / Ks;
-    int row = mt * 32 + (lane & 31);
-    int ga = lane >> 5;
-    int G = K >> 2;
-
-    uint32_t v[4] = {0, 0, 0, 0};
-    uint32_t nibbles = 0;
-    uint32_t *first_bad = reinterpret_cast<uint32_t *>(packed) + kHdrFirstBad;
-#pragma unroll
-    for (int j = 0; j < 8; j++) {
-        int g = 16 * ks + 8 * (j >> 2) + 4 * ga + (j & 3);
-        uint32_t pair = 0, nib = 0x4;
-        if (row < cout && g < G) {
-            size_t e = (size_t)row * K + 4 * (size_t)g;
-            uint32_t m = *reinterpret_cast<const uint32_t *>(M + e);
-            uint32_t w = *reinterpret_cast<const uint32_t *>(W + e);
-            bool ok = ((m & 0xFEFEFEFEu) == 0) && (__popc(m) == 2);
-            if (ok) {
-                int i0 = (__ffs(m) - 1) >> 3;
-                int i1 = (31 - __clz(m)) >> 3;
-                pair = ((w >> (8 * i0)) & 0xFFu) | (((w >> (8 * i1)) & 0xFFu) << 8);
-                nib = (uint32_t)(i0 | (i1 << 2));
-            } else {
-                atomicMin(first_bad, (uint32_t)((size_t)row * G + g));
-            }
-        }
-        v[j >> 1] |= pair << (16 * (j & 1));
-        nibbles |= nib << (4 * j);
-    }
-    *reinterpret_cast<uint4 *>(packed + kHeaderBytes + ((size_t)tile * 64 + lane) * 16) = make_uint4(v[0], v[1], v[2], v[3]);
-    uint32_t *meta = reinterpret_cast<uint32_t *>(packed + kHeaderBytes + (size_t)Mt * Ks * 1024);
-    meta[(size_t)tile * 64 + lane] = nibbles;
-}
-
 // thread per (row, block): inverse permutation, writes 4 bytes
 __global__ __launch_bounds__(256) void decompress8_kernel(const uint8_t *__restrict__ packed, uint8_t *__restrict__ Wm,
                                                           int cout, int K, int Mt, int Ks)
@@ -237,33 +208,42 @@ __global__ __launch_bounds__(256) void decompress8_kernel(const uint8_t *__restr
     *reinterpret_cast<uint32_t *>(Wm + (size_t)row * K + 4 * (size_t)g) = w;
 }
 
-// Dense twin operand: thread per (tile (mt, ks, h), lane); 16 bytes k = 64*ks + 32*(l/32) + 16*h + s.
-__global__ __launch_bounds__(256) void dense_pack8_kernel(const uint8_t *__restrict__ W, const uint8_t *__restrict__ M,
-                                                          uint8_t *__restrict__ dense, int cout, int K, int Mt, int Ks)
+// Dense twin operand.  16-bit: tile (mt, ks, h), lane l, slot s <-> k = 32*ks + 16*(l/32) + 8*h + s; 8-bit: slot s <->
+// k = 64*ks + 32*(l/32) + 16*h + s.  Either way a lane's slots are 16 contiguous bytes of a row, and the 32 rows x 256 bytes
+// of a workgroup are 4 reduction steps: consecutive lanes read consecutive pieces of a row, the masked values cross LDS into
+// tile order.  Rows are read in units of UB bytes, the largest of 16 .. 1 that divides a row (in elements with their mask
+// bytes; UB / element size of them).
+template <typename T, int UE>      // T: element; UE: elements per unit
+__global__ __launch_bounds__(256) void dense_pack_kernel(const T *__restrict__ W, const uint8_t *__restrict__ M,
+                                                         uint8_t *__restrict__ dense, int cout, int K, int Mt, int Ks, PackHeader hdr)
 {
-    int tid = blockIdx.x * 256 + threadIdx.x;
-    int total = Mt * Ks * 2 * 64;
-    if (tid >= total) return;
-    int lane = tid & 63;
-    int tile = tid >> 6;
-    int h = tile & 1;
-    int ks = (tile >> 1) % Ks;
-    int mt = (tile >> 1) / Ks;
-    int row = mt * 32 + (lane & 31);
-    int kbase = 64 * ks + 32 * (lane >> 5) + 16 * h;
-    uint32_t o[4] = {0, 0, 0, 0};
+    struct __attribute__((aligned(sizeof(T) * UE))) Unit { T e[UE]; };
+    struct __attribute__((aligned(UE))) Mask { uint8_t e[UE]; };
+    constexpr int STEP = 64 / (int)sizeof(T);             // reduction indices per step (64 bytes)
+    constexpr int UNITS = 256 / (int)sizeof(Unit);        // units per row and workgroup
+    __shared__ __attribute__((aligned(16))) uint8_t tile[32 * 256];
+    const int tid = threadIdx.x, gx = (Ks + 3) / 4;
+    const int mt = blockIdx.x / gx, ks0 = (blockIdx.x - mt * gx) * 4;
+    if (blockIdx.x == 0 && tid < 64) reinterpret_cast<uint32_t *>(dense)[tid] = tid < kHdrWords ? hdr.w[tid] : 0u;
+    for (int i = tid; i < 32 * UNITS; i += 256) {
+        const int r = i / UNITS, b = (i % UNITS) * (int)sizeof(Unit);      // row, byte inside the workgroup's 256
+        const int row = mt * 32 + r, k = ks0 * STEP + b / (int)sizeof(T);
+        Unit v{};
+        if (row < cout && k < K) {                        // (a row is a whole number of units)
+            v = *reinterpret_cast<const Unit *>(W + (size_t)row * K + k);
+            if (M != nullptr) {
+                const Mask m = *reinterpret_cast<const Mask *>(M + (size_t)row * K + k);
 #pragma unroll
-    for (int s = 0; s < 16; s++) {
-        int k = kbase + s;
-        uint32_t val = 0;
-        if (row < cout && k < K) {
-            size_t e = (size_t)row * K + k;
-            bool keep = (M == nullptr) || (M[e] != 0);
-            val = keep ? (uint32_t)W[e] : 0u;
+                for (int e = 0; e < UE; e++) v.e[e] = m.e[e] != 0 ? v.e[e] : (T)0;
+            }
         }
-        o[s >> 2] |= val << (8 * (s & 3));
+        // step b/64, lane group (b/32)%2, half (b/16)%2
+        *reinterpret_cast<Unit *>(tile + (b >> 6) * 2048 + ((b >> 4) & 1) * 1024 + (32 * ((b >> 5) & 1) + r) * 16 + (b & 15)) = v;
     }
-    *reinterpret_cast<uint4 *>(dense + kHeaderBytes + ((size_t)tile * 64 + lane) * 16) = make_uint4(o[0], o[1], o[2], o[3]);
+    __syncthreads();
+    for (int v = tid; v < 512; v += 256)
+        if (ks0 + (v >> 7) < Ks)
+            *reinterpret_cast<uint4 *>(dense + kHeaderBytes + (((size_t)mt * Ks + ks0) * 128 + v) * 16) = *reinterpret_cast<const uint4 *>(tile + v * 16);
 }
 
 }  // namespace ss
@@ -301,6 +281,82 @@ extern "C" int ss_dense_bytes(const ss_weight_desc *desc, size_t *dense_bytes)
     return SS_OK;
 }
 
+// What a compression waits with: a word of pinned host memory in which it reports an invalid mask (read after the wait, with
+// no copy from the device) and an event that completes with the kernel itself (given to the launch, so no marker follows
+// the kernel; polled: 9.4 us from launch to return for a small kernel, against 11.9 with hipStreamSynchronize and about 30 in
+// all with the header launch and the copy of the status word that this replaces).  Handed out one per call in flight and
+// kept for the next.
+namespace {
+struct Waiter {
+    volatile uint32_t *bad = nullptr;
+    hipEvent_t done = nullptr;
+    int device = -1;
+};
+constexpr size_t kKeptWaiters = 64;
+std::mutex waiter_mutex;
+std::vector<Waiter> &waiters()
+{
+    static auto *v = new std::vector<Waiter>;             // (not destroyed: no HIP calls while the process ends)
+    return *v;
+}
+
+bool take_waiter(Waiter *w)
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return false;
+    {
+        const std::lock_guard<std::mutex> lock(waiter_mutex);
+        auto &v = waiters();
+        for (size_t i = v.size(); i-- > 0;)
+            if (v[i].device == dev) {
+                *w = v[i];
+                v.erase(v.begin() + (long)i);
+                *w->bad = 0;
+                return true;
+            }
+    }
+    void *page = nullptr;
+    if (hipHostMalloc(&page, 64, hipHostMallocDefault) != hipSuccess) return false;
+    if (hipEventCreateWithFlags(&w->done, hipEventDisableTiming) != hipSuccess) {
+        (void)hipHostFree(page);
+        return false;
+    }
+    w->bad = static_cast<volatile uint32_t *>(page);
+    w->device = dev;
+    *w->bad = 0;
+    return true;
+}
+
+void give_waiter(const Waiter &w)
+{
+    {
+        const std::lock_guard<std::mutex> lock(waiter_mutex);
+        if (waiters().size() < kKeptWaiters) {
+            waiters().push_back(w);
+            return;
+        }
+    }
+    (void)hipEventDestroy(w.done);
+    (void)hipHostFree(const_cast<uint32_t *>(w.bad));
+}
+}  // namespace
+
+template <int DT, bool UPD>
+static int launch_compress(const ss_weight_desc *desc, const TileDims &t, void *W, const void *U, const uint8_t *M, uint8_t *packed,
+                           const Waiter &w, hipStream_t s)
+{
+    constexpr int steps = kPackBlocks / (is_byte_type(DT) ? 16 : 8);      // reduction steps per workgroup
+    const long long blocks = (long long)t.Mt * ((t.Ks + steps - 1) / steps);
+    if (blocks > 0x7FFFFFFFll) return SS_ERR_UNSUPPORTED;
+    hipExtLaunchKernelGGL((compress_kernel<DT, UPD>), dim3((unsigned)blocks), dim3(256), 0, s, nullptr, w.done, 0, W, U, M, packed,
+                          desc->cout, t.K, t.Mt, t.Ks, t.Kp, pack_header(kMagicSparse, desc, t), const_cast<uint32_t *>(w.bad));
+    if (hipGetLastError() != hipSuccess) return SS_ERR_HIP;
+    hipError_t e;
+    while ((e = hipEventQuery(w.done)) == hipErrorNotReady) {
+    }
+    return e == hipSuccess ? SS_OK : SS_ERR_HIP;
+}
+
 static int compress_entry(const ss_weight_desc *desc, void *W, const void *U, const uint8_t *M, void *packed,
                           int32_t *bad_row_group, void *stream)
 {
@@ -313,32 +369,29 @@ static int compress_entry(const ss_weight_desc *desc, void *W, const void *U, co
     TileDims t = tile_dims(desc);
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint8_t *p = static_cast<uint8_t *>(packed);
-    write_header_kernel<<<1, 64, 0, s>>>(reinterpret_cast<uint32_t *>(p), kMagicSparse, desc->cout, desc->cin,
-                                         desc->kh, desc->kw, desc->dtype, desc->korder, t.Mt, t.Ks);
-    int total = t.Mt * t.Ks * 64;
-    dim3 grid((total + 255) / 256), block(256);
-    uint16_t *w = static_cast<uint16_t *>(W);
-    const uint16_t *u = static_cast<const uint16_t *>(U);
-    if (i8)
-        compress8_kernel<<<grid, block, 0, s>>>(static_cast<const uint8_t *>(W), M, p, desc->cout, t.K, t.Mt, t.Ks);
-    else if (!U)
-        compress_kernel<SS_F16, false><<<grid, block, 0, s>>>(w, nullptr, M, p, desc->cout, t.K, t.Mt, t.Ks, t.Kp);
-    else if (desc->dtype == SS_F16)
-        compress_kernel<SS_F16, true><<<grid, block, 0, s>>>(w, u, M, p, desc->cout, t.K, t.Mt, t.Ks, t.Kp);
-    else
-        compress_kernel<SS_BF16, true><<<grid, block, 0, s>>>(w, u, M, p, desc->cout, t.K, t.Mt, t.Ks, t.Kp);
-    if (hipGetLastError() != hipSuccess) return SS_ERR_HIP;
+    Waiter wt;
+    if (!take_waiter(&wt)) return SS_ERR_HIP;
+    if (i8) st = launch_compress<SS_I8, false>(desc, t, W, nullptr, M, p, wt, s);
+    else if (!U) st = launch_compress<SS_F16, false>(desc, t, W, nullptr, M, p, wt, s);
+    else if (desc->dtype == SS_F16) st = launch_compress<SS_F16, true>(desc, t, W, U, M, p, wt, s);
+    else st = launch_compress<SS_BF16, true>(desc, t, W, U, M, p, wt, s);
+    if (st == SS_ERR_HIP) return st;                      // (the kernel may still run: the waiter is not handed out again)
+    const bool bad = *wt.bad != 0;
+    give_waiter(wt);
+    if (st != SS_OK || !bad) return st;
+    // an invalid mask: find its first block and leave it in the header
     uint32_t first_bad = 0;
-    if (hipMemcpyAsync(&first_bad, p + 4 * kHdrFirstBad, 4, hipMemcpyDeviceToHost, s) != hipSuccess) return SS_ERR_HIP;
+    uint32_t *word = reinterpret_cast<uint32_t *>(p) + kHdrFirstBad;
+    const uint32_t n = (uint32_t)desc->cout * (uint32_t)t.G;
+    find_bad_kernel<<<(n + 255) / 256, 256, 0, s>>>(M, word, n);
+    if (hipGetLastError() != hipSuccess) return SS_ERR_HIP;
+    if (hipMemcpyAsync(&first_bad, word, 4, hipMemcpyDeviceToHost, s) != hipSuccess) return SS_ERR_HIP;
     if (hipStreamSynchronize(s) != hipSuccess) return SS_ERR_HIP;
-    if (first_bad != kNoBadBlock) {
-        if (bad_row_group) {
-            bad_row_group[0] = (int32_t)(first_bad / (uint32_t)t.G);
-            bad_row_group[1] = (int32_t)(first_bad % (uint32_t)t.G);
-        }
-        return SS_ERR_BAD_MASK;
+    if (bad_row_group) {
+        bad_row_group[0] = (int32_t)(first_bad / (uint32_t)t.G);
+        bad_row_group[1] = (int32_t)(first_bad % (uint32_t)t.G);
     }
-    return SS_OK;
+    return SS_ERR_BAD_MASK;
 }
 
 extern "C" int ss_mask_compress(const ss_weight_desc *desc, const void *W, const uint8_t *M, void *packed,
@@ -401,14 +454,24 @@ extern "C" int ss_dense_pack(const ss_weight_desc *desc, const void *W, const ui
     TileDims t = tile_dims(desc);
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint8_t *p = static_cast<uint8_t *>(dense);
-    write_header_kernel<<<1, 64, 0, s>>>(reinterpret_cast<uint32_t *>(p), kMagicDense, desc->cout, desc->cin,
-                                         desc->kh, desc->kw, desc->dtype, desc->korder, t.Mt, t.Ks);
-    int total = t.Mt * t.Ks * 2 * 64;
-    if (is_byte_type(desc->dtype))
-        dense_pack8_kernel<<<(total + 255) / 256, 256, 0, s>>>(static_cast<const uint8_t *>(W), M, p, desc->cout, t.K,
-                                                               t.Mt, t.Ks);
-    else
-        dense_pack_kernel<<<(total + 255) / 256, 256, 0, s>>>(static_cast<const uint16_t *>(W), M, p, desc->cout, t.K,
-                                                              t.Mt, t.Ks);
+    const PackHeader hdr = pack_header(kMagicDense, desc, t);
+    const long long blocks = (long long)t.Mt * ((t.Ks + 3) / 4);
+    if (blocks > 0x7FFFFFFFll) return SS_ERR_UNSUPPORTED;
+    const dim3 grid((unsigned)blocks), block(256);
+    // elements per load: as many as divide a row and as W's and M's addresses allow
+    auto fits = [&](int elems, int esize) {
+        return t.K % elems == 0 && aligned(W, (size_t)elems * esize) && (!M || aligned(M, (size_t)elems));
+    };
+    if (is_byte_type(desc->dtype)) {
+        const uint8_t *w = static_cast<const uint8_t *>(W);
+        if (fits(16, 1)) dense_pack_kernel<uint8_t, 16><<<grid, block, 0, s>>>(w, M, p, desc->cout, t.K, t.Mt, t.Ks, hdr);
+        else if (fits(4, 1)) dense_pack_kernel<uint8_t, 4><<<grid, block, 0, s>>>(w, M, p, desc->cout, t.K, t.Mt, t.Ks, hdr);
+        else dense_pack_kernel<uint8_t, 1><<<grid, block, 0, s>>>(w, M, p, desc->cout, t.K, t.Mt, t.Ks, hdr);
+    } else {
+        const uint16_t *w = static_cast<const uint16_t *>(W);
+        if (fits(8, 2)) dense_pack_kernel<uint16_t, 8><<<grid, block, 0, s>>>(w, M, p, desc->cout, t.K, t.Mt, t.Ks, hdr);
+        else if (fits(4, 2)) dense_pack_kernel<uint16_t, 4><<<grid, block, 0, s>>>(w, M, p, desc->cout, t.K, t.Mt, t.Ks, hdr);
+        else dense_pack_kernel<uint16_t, 1><<<grid, block, 0, s>>>(w, M, p, desc->cout, t.K, t.Mt, t.Ks, hdr);
+    }
     return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP;
 }

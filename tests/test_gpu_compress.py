@@ -173,3 +173,16 @@ def test_update_compress_argument_and_mask_errors(ss):
     with pytest.raises(ss.SSError) as e:
         ss.ss_mask_update_compress(desc, W, U, torch.from_numpy(Mb).cuda())
     assert e.value.status == ss.SS_ERR_BAD_MASK and e.value.detail == (3, 1)
+
+
+@pytest.mark.parametrize("K,offset", [(8, 0), (12, 0), (147, 0), (264, 0), (264, 1), (260, 4), (516, 0)])
+def test_dense_pack_reads_rows_of_any_alignment(ss, K, offset):
+    """Rows of 16-, 8- and 2-byte units, and operands whose address allows less than the row length does; odd step counts."""
+    cout = 37
+    rng = np.random.Generator(np.random.PCG64(K + offset))
+    W = rng.integers(0, 1 << 16, size=cout * K + offset, dtype=np.uint16)
+    M = rng.integers(0, 2, size=cout * K + offset, dtype=np.uint8)
+    desc = ss.make_desc(cout, K, 1, 1, wl.F16)
+    got = ss.ss_dense_pack(desc, dev_bits(W, wl.F16)[offset:], torch.from_numpy(M).cuda()[offset:]).cpu().numpy()
+    Wm = np.where(M == 1, W, 0).astype(np.uint16)[offset:].reshape(cout, K)
+    assert np.array_equal(got, dl.tile_dense(Wm, cin=K, kh=1, kw=1, dtype=wl.F16, korder=wl.K_CRS))
