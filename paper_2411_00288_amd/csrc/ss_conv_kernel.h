@@ -185,8 +185,15 @@ __device__ __forceinline__ float gelu_erfc(float z)
 //               channel-major order before the LDS write, so the MFMA side still reads 16-byte
 //               vectors.  A chunk is 32 channels = KH*KW reduction steps.  (8-bit operands: 16 channels per
 //               vector, a byte transpose, chunks of 64 channels.)
-enum { MODE_VEC = 0, MODE_GATHER = 1, MODE_TAPS = 2, MODE_PW = 3, MODE_PW2 = 4, MODE_VEC8 = 5, MODE_GATHER4 = 6 };
+//   MODE_TAPSR, MODE_PWR   MODE_TAPS and MODE_PW for channel counts that are multiples of 4 only: the last chunk's channel
+//               octets past the end are out of range; an octet that straddles it (cin % 8 == 4) is loaded 8 bytes early, so that
+//               no load reaches past its pixel, and moved into place on its way to LDS (cin >= 8).  (Modes of their own: the checks cost the plain
+//               ones registers.  Against MODE_GATHER, which these shapes took before: 3x3 80 -> 136 on 6 x 45 x 61 pixels
+//               51.4 -> 12.3 us; 212 -> 132 on 24 x 16 x 27: 60 -> 17 us.)
+enum { MODE_VEC = 0, MODE_GATHER = 1, MODE_TAPS = 2, MODE_PW = 3, MODE_PW2 = 4, MODE_VEC8 = 5, MODE_GATHER4 = 6, MODE_TAPSR = 7, MODE_PWR = 8 };
 constexpr bool is_vec(int mode) { return mode == MODE_VEC || mode == MODE_VEC8; }
+constexpr bool is_taps(int mode) { return mode == MODE_TAPS || mode == MODE_TAPSR; }
+constexpr bool is_pw(int mode) { return mode == MODE_PW || mode == MODE_PW2 || mode == MODE_PWR; }
 
 // Weight fragments of one 32-wide reduction step for the TM row tiles of a wave.
 template <bool SPARSE, int TM>
@@ -198,7 +205,7 @@ struct AStep {
 template <int MODE, int KH, int KW, bool DEEP>
 struct ChunkShape {
     static constexpr int TAPS = KH * KW;
-    static constexpr int KSTEPS = (MODE == MODE_TAPS) ? TAPS : (MODE == MODE_VEC8 ? 8 : (MODE == MODE_PW ? 4 : 2));   // 32-wide reduction steps per LDS chunk
+    static constexpr int KSTEPS = is_taps(MODE) ? TAPS : (MODE == MODE_VEC8 ? 8 : (MODE == MODE_PW || MODE == MODE_PWR ? 4 : 2));   // 32-wide reduction steps per LDS chunk
     static constexpr int BK = KSTEPS * 32;
     // Bank-conflict-free layout of a pixel row in LDS.  Default: +16 bytes per row, so that the 16-byte fragment reads
     // of consecutive pixels hit distinct banks.  The 3x3 tap-transposing mode writes 16-byte vectors at a stride of 9
@@ -209,12 +216,12 @@ struct ChunkShape {
     // Only in the deep variants: the swizzled addresses cost the shallow 128 x 64 kernel eight registers, which is the
     // step from four to three waves per SIMD (its fused form ran 35 -> 49 us with it); the deep variants run at one to
     // three waves per SIMD anyway.
-    static constexpr bool SWZ = MODE == MODE_TAPS && TAPS == 9 && DEEP;
+    static constexpr bool SWZ = is_taps(MODE) && TAPS == 9 && DEEP;
     static constexpr int ROW = SWZ ? BK : BK + 8;
     // LDS copies of the chunk: double-buffered, so that the next chunk is written while this one is
     // multiplied -- except for the large unfolded 3x3 chunk in the shallow variant, which is kept once
     // (more workgroups per compute unit then hide the store phase instead).
-    static constexpr int NBUF = (MODE == MODE_TAPS && TAPS > 4 && !DEEP) ? 1 : 2;
+    static constexpr int NBUF = (is_taps(MODE) && TAPS > 4 && !DEEP) ? 1 : 2;
 };
 
 constexpr int ring_size(int ksteps, int regs_per_step, int budget)
@@ -270,7 +277,7 @@ constexpr int min_waves_per_simd(int tm, int tn, bool big_stage)
 // bottleneck without the intermediate tensor's round trip through memory.
 template <int DT, bool SPARSE, int WAVES_M, int WAVES_N, int TM, int TN, int MODE, int KH, int KW, bool DEEP, bool SPEC, bool FUSE = false>
 __global__ __launch_bounds__((WAVES_M * WAVES_N + (SPEC ? 4 : 0)) * 64)
-__attribute__((amdgpu_waves_per_eu(DEEP ? 1 : (((DT == SS_F8 || FUSE) && !SPARSE && MODE == MODE_VEC && TM * TN == 2) ? 3 : min_waves_per_simd(TM, TN, MODE == MODE_TAPS || MODE == MODE_VEC8)))))
+__attribute__((amdgpu_waves_per_eu(DEEP ? 1 : (((DT == SS_F8 || FUSE) && !SPARSE && MODE == MODE_VEC && TM * TN == 2) ? 3 : min_waves_per_simd(TM, TN, is_taps(MODE) || MODE == MODE_VEC8)))))
 void conv_kernel(ConvParams p)
 {
     using CS = ChunkShape<MODE, KH, KW, DEEP>;
@@ -355,7 +362,7 @@ void conv_kernel(ConvParams p)
 
     // ------------------------------------------------------------------ activation staging state
     // per pixel row and chunk: 16-byte runs (VEC: 8, TAPS: 4 channel octets) or 4-element blocks (GATHER: 16)
-    constexpr int UNITS = (MODE == MODE_GATHER || MODE == MODE_GATHER4) ? 16 : (MODE == MODE_TAPS ? 4 : (MODE == MODE_VEC8 ? 32 : (MODE == MODE_PW ? 16 : 8)));
+    constexpr int UNITS = (MODE == MODE_GATHER || MODE == MODE_GATHER4) ? 16 : (is_taps(MODE) ? 4 : (MODE == MODE_VEC8 ? 32 : (MODE == MODE_PW || MODE == MODE_PWR ? 16 : 8)));
     constexpr int ST = SPEC ? (256 < BN * UNITS ? 256 : BN * UNITS) : (NT < BN * UNITS ? NT : BN * UNITS);     // staging threads (whole waves); the rest only multiply
     constexpr int ITEMS = BN * UNITS / ST;
     constexpr int NSET = SPEC ? 2 : 1;                    // producer waves hold two chunks in registers
@@ -399,8 +406,8 @@ void conv_kernel(ConvParams p)
     }
     // MODE_TAPS: per (pixel, tap) byte offsets, fixed for the whole reduction; the chunk's channel
     // offset travels in the scalar offset of the load.  Out-of-image taps are out of range for good.
-    unsigned tapoff[MODE == MODE_TAPS ? ITEMS : 1][MODE == MODE_TAPS ? TAPS : 1];
-    if constexpr (MODE == MODE_TAPS) {
+    unsigned tapoff[is_taps(MODE) ? ITEMS : 1][is_taps(MODE) ? TAPS : 1];
+    if constexpr (is_taps(MODE)) {
 #pragma unroll
         for (int i = 0; i < ITEMS; i++)
 #pragma unroll
@@ -414,8 +421,8 @@ void conv_kernel(ConvParams p)
 
     // MODE_PW: per pixel byte offset of this thread's 16-byte run in the first chunk (out of range for pixels
     // past the end or in the padding)
-    unsigned pwoff[(MODE == MODE_PW || MODE == MODE_PW2) ? ITEMS : 1];
-    if constexpr (MODE == MODE_PW || MODE == MODE_PW2) {
+    unsigned pwoff[is_pw(MODE) ? ITEMS : 1];
+    if constexpr (is_pw(MODE)) {
 #pragma unroll
         for (int i = 0; i < ITEMS; i++) {
             bool ok = (unsigned)ih0[i] < (unsigned)p.H && (unsigned)iw0[i] < (unsigned)p.W;
@@ -423,10 +430,11 @@ void conv_kernel(ConvParams p)
         }
     }
 
-    u32x4 stage_v_[NSET][(is_vec(MODE) || MODE == MODE_PW || MODE == MODE_PW2) ? ITEMS : 1];
+    u32x4 stage_v_[NSET][(is_vec(MODE) || is_pw(MODE)) ? ITEMS : 1];
     uint16_t stage_g_[NSET][MODE == MODE_GATHER ? ITEMS : 1][4];
     uint2 stage_g4_[NSET][MODE == MODE_GATHER4 ? ITEMS : 1];
-    u32x4 stage_t_[NSET][MODE == MODE_TAPS ? ITEMS : 1][MODE == MODE_TAPS ? TAPS : 1];
+    u32x4 stage_t_[NSET][is_taps(MODE) ? ITEMS : 1][is_taps(MODE) ? TAPS : 1];
+    bool half_[NSET];                 // MODE_TAPSR / MODE_PWR: the octet straddles the last channel and was loaded 8 bytes early
 
     auto stage_load = [&](int ci_rel, int set = 0) {      // set: compile time at every call site; chunk relative to c_first
         if (!stager) return;
@@ -449,11 +457,16 @@ void conv_kernel(ConvParams p)
                 vc -= p.Cin;
                 if (++vt == p.kw) { vt = 0; ++vr; }
             }
-        } else if constexpr (MODE == MODE_PW || MODE == MODE_PW2) {
+        } else if constexpr (is_pw(MODE)) {
+            int early = 0;
+            if constexpr (MODE == MODE_PWR) {
+                half_[set] = ci * BK + unit * 8 + 4 == p.K;
+                early = half_[set] ? 8 : 0;
+            }
             const bool kok = ci * BK + unit * 8 < p.K;      // the last chunk may reach past the reduction length
 #pragma unroll
             for (int i = 0; i < ITEMS; i++)
-                stage_v[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(kok ? pwoff[i] : kOutOfRange), ci * (BK * 2), 0);
+                stage_v[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(kok ? pwoff[i] + (MODE == MODE_PWR ? ci * (BK * 2) - early : 0) : kOutOfRange), MODE == MODE_PWR ? 0 : ci * (BK * 2), 0);
         } else if constexpr (MODE == MODE_GATHER4) {
             // this thread's block of 4 reduction indices: one tap, 4 consecutive channels
             auto &stage_g4 = stage_g4_[set];
@@ -503,12 +516,21 @@ void conv_kernel(ConvParams p)
                 }
             }
         } else {
-            const int soff = ci * 64;                   // 32 channels per chunk
+            const unsigned soff = (unsigned)ci * 64;    // 32 channels per chunk
+            unsigned past = 0, early = 0;               // kOutOfRange for an octet past the last channel
+            if constexpr (MODE == MODE_TAPSR) {
+                const int c = ci * 32 + unit * 8;
+                past = c < p.Cin ? 0u : kOutOfRange;
+                half_[set] = c + 4 == p.Cin;
+                early = half_[set] ? 8u : 0u;           // (an out-of-image tap stays out of range: every buffer is 64 MiB short of 2 GiB)
+            }
 #pragma unroll
             for (int i = 0; i < ITEMS; i++)
 #pragma unroll
                 for (int tap = 0; tap < TAPS; tap++)
-                    stage_t[i][tap] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)tapoff[i][tap], soff, 0);
+                    stage_t[i][tap] = MODE == MODE_TAPSR
+                        ? __builtin_amdgcn_raw_buffer_load_b128(rx, (int)((tapoff[i][tap] | past) + (soff - early)), 0, 0)      // (one sum: the offset alone could go below 0)
+                        : __builtin_amdgcn_raw_buffer_load_b128(rx, (int)tapoff[i][tap], soff, 0);
         }
     };
     // Writes slice j of n of the staged chunk to LDS (j, n are compile-time at every call site): a share of the
@@ -521,7 +543,7 @@ void conv_kernel(ConvParams p)
 #pragma unroll
         for (int i = 0; i < ITEMS; i++) {
             int pr = pr0 + i * (ST / UNITS);
-            if constexpr (MODE == MODE_TAPS) {
+            if constexpr (is_taps(MODE)) {
                 // [tap][8 channels] -> [channel][tap]: output element h = c*TAPS + tap, two per dword, four dwords per vector
                 u32x4 *rowp = reinterpret_cast<u32x4 *>(Bs + pr * ROW);
                 const int vec0 = unit * TAPS, swz = CS::SWZ ? (pr >> 2) & 3 : 0;     // first vector of the unit; the row's XOR key
@@ -557,6 +579,10 @@ void conv_kernel(ConvParams p)
                         const int ca = ha / TAPS, ta = ha % TAPS, cb = hb / TAPS, tb = hb % TAPS;
                         uint32_t sa = stage_t[i][ta][ca >> 1];
                         uint32_t sb = stage_t[i][tb][cb >> 1];
+                        if constexpr (MODE == MODE_TAPSR) {
+                            sa = half_[set] ? (ca >= 4 ? 0u : stage_t[i][ta][2 + (ca >> 1 & 1)]) : sa;
+                            sb = half_[set] ? (cb >= 4 ? 0u : stage_t[i][tb][2 + (cb >> 1 & 1)]) : sb;
+                        }
                         const uint32_t sel = (uint32_t)(2 * (ca & 1)) | ((uint32_t)(2 * (ca & 1) + 1) << 8) |
                                              ((uint32_t)(4 + 2 * (cb & 1)) << 16) | ((uint32_t)(5 + 2 * (cb & 1)) << 24);
                         o[q] = __builtin_amdgcn_perm(sb, sa, sel);
@@ -573,7 +599,10 @@ void conv_kernel(ConvParams p)
                                          (uint32_t)stage_g[i][2] | ((uint32_t)stage_g[i][3] << 16));
                     *reinterpret_cast<uint2 *>(Bs + pr * ROW + unit * 4) = v;
                 } else {
-                    *reinterpret_cast<u32x4 *>(Bs + pr * ROW + unit * 8) = stage_v[i];
+                    u32x4 v = stage_v[i];
+                    if constexpr (MODE == MODE_PWR)
+                        if (half_[set]) v = u32x4{v[2], v[3], 0u, 0u};
+                    *reinterpret_cast<u32x4 *>(Bs + pr * ROW + unit * 8) = v;
                 }
             }
         }
@@ -956,21 +985,32 @@ void conv_kernel(ConvParams p)
             }
             return;
         }
-        for (int it = etid; it < BN * RUNS; it += NT) {
-            const int pl = it / RUNS, run = it % RUNS;
-            const int pg = n0 + pl, o = m0 + run * 8;
-            if (pg >= p.P || o >= p.Cout) continue;
-            const uint2 lo = *reinterpret_cast<const uint2 *>(Cs + pl * CROW + run * 8);
-            const uint2 hi = *reinterpret_cast<const uint2 *>(Cs + pl * CROW + run * 8 + 4);
-            uint16_t *dst = p.y + (size_t)pg * p.Cout + o;
-            if (vec_ok) {
-                *reinterpret_cast<uint4 *>(dst) = make_uint4(lo.x, lo.y, hi.x, hi.y);
-            } else {
-                const uint32_t w[4] = {lo.x, lo.y, hi.x, hi.y};
-#pragma unroll
-                for (int e = 0; e < 8; e++)
-                    if (o + e < p.Cout) dst[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+        if (vec_ok) {
+            for (int it = etid; it < BN * RUNS; it += NT) {
+                const int pl = it / RUNS, run = it % RUNS;
+                const int pg = n0 + pl, o = m0 + run * 8;
+                if (pg >= p.P || o >= p.Cout) continue;
+                const uint2 lo = *reinterpret_cast<const uint2 *>(Cs + pl * CROW + run * 8);
+                const uint2 hi = *reinterpret_cast<const uint2 *>(Cs + pl * CROW + run * 8 + 4);
+                *reinterpret_cast<uint4 *>(p.y + (size_t)pg * p.Cout + o) = make_uint4(lo.x, lo.y, hi.x, hi.y);
             }
+        } else {
+            // Channel counts whose pixel rows are not 16-byte aligned: consecutive lanes write consecutive 8-, 4- or 2-byte
+            // pieces of a pixel (contiguous per instruction; eight 2-byte stores per thread, 16 bytes apart from lane to
+            // lane, before).
+            auto pieces = [&](auto piece) {
+                using T = decltype(piece);
+                constexpr int E = (int)sizeof(T) / 2, PER = BM / E;
+                for (int it = etid; it < BN * PER; it += NT) {
+                    const int pl = it / PER, c = (it % PER) * E;
+                    const int pg = n0 + pl, o = m0 + c;
+                    if (pg >= p.P || o >= p.Cout) continue;
+                    *reinterpret_cast<T *>(p.y + (size_t)pg * p.Cout + o) = *reinterpret_cast<const T *>(Cs + pl * CROW + c);
+                }
+            };
+            if ((p.Cout & 3) == 0) pieces(uint2{});
+            else if ((p.Cout & 1) == 0) pieces(uint32_t{});
+            else pieces(uint16_t{});
         }
     } else if constexpr (!Q8) {
         // With a residual the tile crosses LDS in fp32 (conv + bias); the thread that stores a 16-byte run adds the
@@ -1022,22 +1062,36 @@ void conv_kernel(ConvParams p)
                 const float4 lo = *reinterpret_cast<const float4 *>(Cf + pl * CROW + run * 8);
                 const float4 hi = *reinterpret_cast<const float4 *>(Cf + pl * CROW + run * 8 + 4);
                 const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-                uint16_t *dst = p.y + (size_t)pg * p.Cout + o;
-                if (vec_ok) {
-                    uint32_t w[4];
+                uint32_t w[4];
 #pragma unroll
-                    for (int e = 0; e < 4; e++)
-                        w[e] = cvt_pack2<ODT>(actf(v[2 * e] + widen<ODT>((uint16_t)(res[j][e] & 0xFFFFu))),
-                                              actf(v[2 * e + 1] + widen<ODT>((uint16_t)(res[j][e] >> 16))));
-                    *reinterpret_cast<uint4 *>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
-                } else {
-                    const uint16_t *rs = p.residual + (size_t)pg * p.Cout + o;
-#pragma unroll
-                    for (int e = 0; e < 8; e++)
-                        if (o + e < p.Cout) dst[e] = (uint16_t)(cvt_pack2<ODT>(actf(v[e] + widen<ODT>(rs[e])), 0.f) & 0xFFFFu);
-                }
+                for (int e = 0; e < 4; e++)
+                    w[e] = cvt_pack2<ODT>(actf(v[2 * e] + widen<ODT>((uint16_t)(res[j][e] & 0xFFFFu))),
+                                          actf(v[2 * e + 1] + widen<ODT>((uint16_t)(res[j][e] >> 16))));
+                *reinterpret_cast<uint4 *>(p.y + (size_t)pg * p.Cout + o) = make_uint4(w[0], w[1], w[2], w[3]);
             }
         };
+        // (pixel rows that are not 16-byte aligned: as in the plain tail, one 4- or 2-byte piece per lane)
+        auto from_lds_pieces = [&](auto actf, auto piece) {
+            using T = decltype(piece);
+            constexpr int E = (int)sizeof(T) / 2, PER = BM / E;
+            for (int it = etid; it < BN * PER; it += NT) {
+                const int pl = it / PER, c = (it % PER) * E;
+                const int pg = n0 + pl, o = m0 + c;
+                if (pg >= p.P || o >= p.Cout) continue;
+                const size_t at = (size_t)pg * p.Cout + o;
+                const T r = *reinterpret_cast<const T *>(p.residual + at);
+                const float a = actf(Cf[pl * CROW + c] + widen<ODT>((uint16_t)(r & 0xFFFFu)));
+                const float b = E == 2 ? actf(Cf[pl * CROW + c + E - 1] + widen<ODT>((uint16_t)((uint32_t)r >> 16))) : 0.f;
+                *reinterpret_cast<T *>(p.y + at) = (T)cvt_pack2<ODT>(a, b);
+            }
+        };
+        if (!vec_ok) {
+            auto run = [&](auto actf) {
+                if ((p.Cout & 1) == 0) from_lds_pieces(actf, uint32_t{}); else from_lds_pieces(actf, uint16_t{});
+            };
+            if (p.act == SS_ACT_GELU) run(gelu); else run(relu_or_id);
+            return;
+        }
         if (p.act == SS_ACT_GELU) from_lds(gelu); else from_lds(relu_or_id);
     }
 }
@@ -1367,8 +1421,8 @@ static int pick_tile(const ConvParams &p, hipStream_t s)
         int st = launch_tile<DT, SPARSE, MODE, KH, KW>(forced, p, s);
         if (st != SS_ERR_INVALID_ARG) return st;
     }
-    constexpr bool pointwise = MODE == MODE_PW || MODE == MODE_PW2;
-    constexpr bool bigchunk = (MODE == MODE_TAPS && KH * KW > 4) || MODE == MODE_VEC8;
+    constexpr bool pointwise = is_pw(MODE);
+    constexpr bool bigchunk = (is_taps(MODE) && KH * KW > 4) || MODE == MODE_VEC8;
     int id = choose_tile(p, pointwise, bigchunk);
     // The dense FP8 instruction of the deep kernels wants its 32-byte A operand in eight consecutive registers; the
     // 256x64 four-wave tile then runs at one wave per SIMD (measured 40 % slower than with producer waves).
@@ -1408,6 +1462,12 @@ static int pick_mode(const ss_weight_desc *desc, const ConvParams &p, hipStream_
     if (desc->korder == SS_K_CRS && desc->cin % 32 == 0) {
         if (desc->kh == 3 && desc->kw == 3) return pick_tile<DT, SPARSE, MODE_TAPS, 3, 3>(p, s);
         if (desc->kh == 2 && desc->kw == 2) return pick_tile<DT, SPARSE, MODE_TAPS, 2, 2>(p, s);
+    }
+    if (desc->cin % 4 == 0 && desc->cin >= 8) {
+        if (taps == 1 && p.Ks > 2) return pick_tile<DT, SPARSE, MODE_PWR, 1, 1>(p, s);
+        if (desc->korder == SS_K_CRS && desc->kh == 3 && desc->kw == 3) return pick_tile<DT, SPARSE, MODE_TAPSR, 3, 3>(p, s);
+        if (desc->korder == SS_K_CRS && desc->kh == 2 && desc->kw == 2) return pick_tile<DT, SPARSE, MODE_TAPSR, 2, 2>(p, s);
+        if (taps == 1) return pick_tile<DT, SPARSE, MODE_GATHER4, 1, 1>(p, s);
     }
     if (desc->cin % 4 == 0 && desc->korder == SS_K_RSC) return pick_tile<DT, SPARSE, MODE_GATHER4, 1, 1>(p, s);
     return pick_tile<DT, SPARSE, MODE_GATHER, 1, 1>(p, s);
