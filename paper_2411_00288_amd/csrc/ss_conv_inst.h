@@ -4,6 +4,7 @@
 #include "ss_conv_stream.h"
 #include "ss_conv_image.h"
 #include "ss_conv_rows.h"
+#include "ss_conv_small.h"
 
 #define SS_CAT2(a, b) a##b
 #define SS_CAT(a, b) SS_CAT2(a, b)
@@ -12,6 +13,11 @@ namespace ss {
 
 int SS_CAT(conv_dispatch_, SS_INST_NAME)(const ss_weight_desc *desc, const ConvParams &p, hipStream_t s)
 {
+    // Few output pixels: the one-latency kernels (tile ids 20 to 22 when forced; a forced split means the tiled kernels)
+    if (forced_tile() < 0 ? forced_split() == 0 : forced_tile() >= 20 && forced_tile() <= 22) {
+        const int st = small_mode<SS_INST_DT, SS_INST_SPARSE>(desc, p, forced_tile() < 0 ? -1 : forced_tile() - 20, s);
+        if (st != SS_ERR_INVALID_ARG) return st;
+    }
     if constexpr (!is_byte_type(SS_INST_DT)) {
         if (p.nsplit <= 1 && stream_eligible(desc, p)) {
             int ncu = compute_units();

@@ -1,0 +1,459 @@
+// Convolution on few output pixels (small-batch inference, the late stages of a network): one memory latency deep.
+//
+// A layer with a few hundred output pixels gives the tiled kernels a handful of workgroups, each of which walks through
+// the whole reduction chunk by chunk: a chain of load -> LDS -> barrier -> multiply steps of about half a microsecond
+// each on a chip that is otherwise idle (ResNet-50 at one image: 5-10 us per layer).  Here the output is cut into
+// 32-channel x 32-pixel tiles, one per workgroup, and the workgroup's waves split the reduction: every wave issues all the loads
+// of its share at once, multiplies, and the partial sums meet once in LDS, where they are added in wave order (a fixed
+// order: the result does not depend on timing), rounded once and stored.  There is no barrier before that meeting.
+//   * 1x1 kernels and the channels-last flattening (DIRECT): a lane's activation fragment, 16 consecutive reduction
+//     indices of one pixel, is two aligned 16-byte runs in memory; it goes straight into the matrix instruction's
+//     registers, no LDS.
+//   * the paper's flattening with a KH x KW kernel: a wave takes whole chunks of 32 channels, transposes the taps in registers
+//     as the tiled kernels do (stage_taps) into LDS of its own and reads the fragments back.
+// The arithmetic is that of the tiled kernels up to the order of the fp32 additions.
+#ifndef SS_CONV_SMALL_H_
+#define SS_CONV_SMALL_H_
+#include "ss_conv_kernel.h"
+
+namespace ss {
+
+enum { SMALL_PW = 0, SMALL_RSC = 1, SMALL_TAPS = 2, SMALL_TAPSR = 3 };      // (TAPSR: cin % 32 != 0, as MODE_TAPSR)
+constexpr bool small_taps(int mode) { return mode == SMALL_TAPS || mode == SMALL_TAPSR; }
+
+// One 16-byte vector v of a tap-transposed unit: [tap][8 channels] -> [channel][tap] (8-bit operands: 16 channels), see MODE_TAPS.
+template <bool Q8, bool RAG, int TAPS>
+__device__ __forceinline__ u32x4 taps_vector(const u32x4 (&t)[TAPS], int v, bool half)
+{
+    u32x4 w;
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const int d = 4 * v + q;
+        if constexpr (Q8) {
+            uint32_t src[4], pick[4];
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const int h = 4 * d + e, c = h / TAPS, tp = h % TAPS;
+                src[e] = t[tp][c >> 2];
+                pick[e] = (uint32_t)(c & 3);
+            }
+            const uint32_t p01 = __builtin_amdgcn_perm(src[1], src[0], pick[0] | ((4u + pick[1]) << 8));
+            const uint32_t p23 = __builtin_amdgcn_perm(src[3], src[2], pick[2] | ((4u + pick[3]) << 8));
+            w[q] = __builtin_amdgcn_perm(p23, p01, 0x05040100u);
+        } else {
+            const int ha = 2 * d, hb = 2 * d + 1;
+            const int ca = ha / TAPS, ta = ha % TAPS, cb = hb / TAPS, tb = hb % TAPS;
+            uint32_t sa = t[ta][ca >> 1], sb = t[tb][cb >> 1];
+            if constexpr (RAG) {
+                sa = half ? (ca >= 4 ? 0u : t[ta][2 + (ca >> 1 & 1)]) : sa;
+                sb = half ? (cb >= 4 ? 0u : t[tb][2 + (cb >> 1 & 1)]) : sb;
+            }
+            const uint32_t sel = (uint32_t)(2 * (ca & 1)) | ((uint32_t)(2 * (ca & 1) + 1) << 8) |
+                                 ((uint32_t)(4 + 2 * (cb & 1)) << 16) | ((uint32_t)(5 + 2 * (cb & 1)) << 24);
+            w[q] = __builtin_amdgcn_perm(sb, sa, sel);
+        }
+    }
+    return w;
+}
+
+// Workgroups of a problem.
+static inline long long small_blocks(const ConvParams &p, int px, int tm)
+{
+    return (long long)((p.Mt + tm - 1) / tm) * (((long long)p.P + px - 1) / px);
+}
+
+// LDS of a wave: its staging area (taps), which later holds its partial sums
+template <int MODE, int TAPS, int PX, int TM>
+constexpr size_t small_wave_lds()
+{
+    const size_t stage = small_taps(MODE) ? (size_t)PX * TAPS * 64 : 0, part = (size_t)TM * 4096;
+    return stage > part ? stage : part;
+}
+
+// PX: pixels of a tile (32, or 16: half of the matrix instruction's columns stay empty, and twice as many workgroups share
+// the loads, which is what bounds a grid far below the chip's size).  NW: waves.
+template <int DT, bool SPARSE, int MODE, int KH, int KW, int PX, int TM, int NW>
+__global__ __launch_bounds__(NW * 64) void conv_small_kernel(ConvParams p)
+{
+    constexpr bool Q8 = is_byte_type(DT);
+    constexpr int ODT = out_type<DT>();
+    constexpr int TAPS = KH * KW;
+    constexpr int RING = NW > 8 ? 4 : 8;                  // direct: reduction steps in flight per wave (16 waves: 128 registers each)
+    constexpr bool SWZ = TAPS == 9;                       // LDS row layout of the tap modes (see ChunkShape::SWZ; 2x2 rows are 16 vectors, XOR-ed with the whole row number)
+    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 5, c = lane & 31;
+    // Row tiles fastest: workgroups are dealt to the 8 XCDs round-robin, so with a multiple of 8 row tiles every XCD's L2
+    // reads its own eighth of the weights only.
+    const int tile_n = fast_div(blockIdx.x, p.tm_mul, p.tm_sh);
+    const int mt = (blockIdx.x - tile_n * p.tiles_m) * TM;      // first row tile
+    const int n0 = tile_n * PX;
+    const int HoWo = p.Ho * p.Wo;
+
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.x), 0, (int)p.x_bytes, kRsrcFlags);
+    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.a_vals), 0, (int)p.a_bytes, kRsrcFlags);
+    const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.a_meta), 0, (int)p.meta_bytes, kRsrcFlags);
+    unsigned a_voff[TM], m_voff[TM];                      // (a row tile past the last one is clamped to it and not stored)
+#pragma unroll
+    for (int tm = 0; tm < TM; tm++) {
+        const int m = min(mt + tm, p.Mt - 1);
+        a_voff[tm] = (unsigned)(m * p.Ks * (SPARSE ? 1 : 2) * 64 + lane) * 16u;
+        m_voff[tm] = (unsigned)(m * p.Kp * 64 + lane) * 4u;
+    }
+    using A = AStep<SPARSE, TM>;
+    auto load_a = [&](A &a, int ks) {                     // (steps past the last one meet all-zero activations: any weights do)
+        ks = min(ks, p.Ks - 1);
+#pragma unroll
+        for (int tm = 0; tm < TM; tm++) {
+            if constexpr (SPARSE) {
+                a.v[0][tm] = __builtin_amdgcn_raw_buffer_load_b128(ra, (int)a_voff[tm], ks * 1024, 0);
+                a.idx[tm] = __builtin_amdgcn_raw_buffer_load_b32(rm, (int)m_voff[tm], (Q8 ? ks : (ks >> 1)) * 256, 0);
+            } else {
+                a.v[0][tm] = __builtin_amdgcn_raw_buffer_load_b128(ra, (int)a_voff[tm], ks * 2048, 0);
+                a.v[1][tm] = __builtin_amdgcn_raw_buffer_load_b128(ra, (int)a_voff[tm], ks * 2048 + 1024, 0);
+            }
+        }
+    };
+    Acc<DT> acc[TM];
+#pragma unroll
+    for (int tm = 0; tm < TM; tm++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) acc[tm][v] = 0;
+    auto multiply = [&](const A &a, const B32 &b, int ks) {
+        const int shift = Q8 ? 0 : (min(ks, p.Ks - 1) & 1) * 16;
+#pragma unroll
+        for (int tm = 0; tm < TM; tm++) {
+            if constexpr (SPARSE) {
+                acc[tm] = mma_sparse<DT>(a.v[0][tm], b, acc[tm], a.idx[tm] >> shift);
+            } else if constexpr (DT == SS_F8) {
+                acc[tm] = mma_dense_f8(a.v[0][tm], a.v[1][tm], b, acc[tm]);
+            } else {
+                acc[tm] = mma_dense<DT>(a.v[0][tm], b.lo, acc[tm]);
+                acc[tm] = mma_dense<DT>(a.v[1][tm], b.hi, acc[tm]);
+            }
+        }
+    };
+    // position of an output pixel's window
+    struct Pixel {
+        int ih, iw;
+        unsigned byte;
+    };
+    auto pixel = [&](int pg) {
+        Pixel q{-(1 << 28), -(1 << 28), 0u};              // past the last pixel: every bounds test fails
+        if (pg < p.P) {
+            const int n = fast_div(pg, p.howo_mul, p.howo_sh);
+            const int rem = pg - n * HoWo;
+            const int ho = fast_div(rem, p.wo_mul, p.wo_sh);
+            q.ih = ho * p.sh - p.ph;
+            q.iw = (rem - ho * p.Wo) * p.sw - p.pw;
+            q.byte = (unsigned)(((n * p.H + q.ih) * p.W + q.iw) * p.Cin * 2);
+        }
+        return q;
+    };
+
+    if constexpr (!small_taps(MODE)) {
+        // ------------------------------------------------------------ fragments straight from memory
+        const Pixel px = pixel(PX == 32 || c < PX ? n0 + c : p.P);
+        const bool in0 = (unsigned)px.ih < (unsigned)p.H && (unsigned)px.iw < (unsigned)p.W;
+        const int per = (p.Ks + NW - 1) / NW;             // steps of a wave
+        const int s0 = wave * per, s1 = min(s0 + per, p.Ks);
+        auto octet = [&](int k) -> u32x4 {                // 8 reduction indices from k
+            unsigned off = kOutOfRange;
+            if constexpr (MODE == SMALL_PW) {
+                if (in0 && k < p.K) off = px.byte + (unsigned)k * 2;
+            } else {
+                const int tap = fast_div(k, p.cin_mul, p.cin_sh);
+                const int r = fast_div(tap, p.kw_mul, p.kw_sh), t = tap - r * p.kw;
+                const bool ok = (unsigned)(px.ih + r) < (unsigned)p.H && (unsigned)(px.iw + t) < (unsigned)p.W && k < p.K;
+                if (ok) off = px.byte + (unsigned)(((r * p.W + t) * p.Cin + k - tap * p.Cin) * 2);
+            }
+            return __builtin_amdgcn_raw_buffer_load_b128(rx, (int)off, 0, 0);
+        };
+        A a[RING];
+        B32 b[RING];
+        auto load = [&](int j, int s) {
+            load_a(a[j], s);
+            const int k = s < s1 ? s * 32 + 16 * g : 1 << 30;      // (a share's end: zeros)
+            b[j].lo = octet(k);
+            b[j].hi = octet(k + 8);
+        };
+#pragma unroll
+        for (int j = 0; j < RING; j++) load(j, s0 + j);
+        for (int s = s0; s < s1; s += RING) {
+#pragma unroll
+            for (int j = 0; j < RING; j++) {
+                multiply(a[j], b[j], s + j);
+                if (s + RING < s1) load(j, s + RING + j);
+            }
+        }
+    } else {
+        // ------------------------------------------------------------ taps of whole channel chunks, transposed in the wave's own LDS
+        constexpr int VPR = TAPS * 4;                     // 16-byte vectors per pixel row of a chunk (TAPS steps of 64 bytes)
+        u32x4 *const mine = reinterpret_cast<u32x4 *>(smem) + wave * (PX * VPR);
+        const int unit = lane & 3, nchunks = (p.Ks + TAPS - 1) / TAPS;
+        constexpr int IT = PX / 16;                       // pixels per lane
+        unsigned tapoff[IT][TAPS];
+#pragma unroll
+        for (int i = 0; i < IT; i++) {
+            const Pixel px = pixel(n0 + (lane >> 2) + 16 * i);
+#pragma unroll
+            for (int tap = 0; tap < TAPS; tap++) {
+                const int r = tap / KW, t = tap % KW;
+                const bool ok = (unsigned)(px.ih + r) < (unsigned)p.H && (unsigned)(px.iw + t) < (unsigned)p.W;
+                tapoff[i][tap] = ok ? px.byte + (unsigned)(((r * p.W + t) * p.Cin + unit * 8) * 2) : kOutOfRange;
+            }
+        }
+        u32x4 x[IT][TAPS];
+        A a[TAPS];
+        bool half = false;
+        auto load_x = [&](int ci) {
+            const unsigned soff = (unsigned)ci * 64;
+            if constexpr (MODE == SMALL_TAPSR) {
+                const int ch = ci * 32 + unit * 8;
+                half = ch + 4 == p.Cin;
+                const unsigned past = ch < p.Cin ? 0u : kOutOfRange, early = half ? 8u : 0u;
+#pragma unroll
+                for (int i = 0; i < IT; i++)
+#pragma unroll
+                    for (int tap = 0; tap < TAPS; tap++)
+                        x[i][tap] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)((tapoff[i][tap] | past) + (soff - early)), 0, 0);
+            } else {
+#pragma unroll
+                for (int i = 0; i < IT; i++)
+#pragma unroll
+                    for (int tap = 0; tap < TAPS; tap++)
+                        x[i][tap] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)tapoff[i][tap], soff, 0);
+            }
+        };
+        if (wave < nchunks) load_x(wave);
+        for (int ci = wave; ci < nchunks; ci += NW) {
+#pragma unroll
+            for (int s = 0; s < TAPS; s++) load_a(a[s], ci * TAPS + s);
+#pragma unroll
+            for (int i = 0; i < IT; i++) {
+                const int pr = (lane >> 2) + 16 * i, key = SWZ ? (pr >> 2) & 3 : pr & 15;
+#pragma unroll
+                for (int v = 0; v < TAPS; v++) mine[pr * VPR + ((unit * TAPS + v) ^ key)] = taps_vector<Q8, MODE == SMALL_TAPSR, TAPS>(x[i], v, half);
+            }
+            if (ci + NW < nchunks) load_x(ci + NW);
+            __builtin_amdgcn_wave_barrier();              // (a wave's LDS operations execute in order: the reads below see the writes above)
+            const int cc = c & (PX - 1), key = SWZ ? (cc >> 2) & 3 : cc & 15;
+#pragma unroll
+            for (int s = 0; s < TAPS; s++) {
+                B32 b;
+                b.lo = mine[cc * VPR + ((s * 4 + 2 * g) ^ key)];
+                b.hi = mine[cc * VPR + ((s * 4 + 2 * g + 1) ^ key)];
+                multiply(a[s], b, ci * TAPS + s);
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+
+    // ---------------------------------------------------------------- partial sums meet in LDS, in register order [wave][quad][lane]
+    // (each wave's region lies inside its own staging area where there is one: no barrier before it)
+    constexpr int RSTRIDE = (int)(small_wave_lds<MODE, TAPS, PX, TM>() / 16), QUADS = PX * 8 * TM;       // 16-byte vectors from one wave's region to the next
+    u32x4 *const part = reinterpret_cast<u32x4 *>(smem);
+#pragma unroll
+    for (int tm = 0; tm < TM; tm++)
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            u32x4 w;
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const auto v = acc[tm][4 * q + e];
+                w[e] = __builtin_bit_cast(uint32_t, v);
+            }
+            part[wave * RSTRIDE + (tm * 4 + q) * 64 + lane] = w;
+        }
+    // (consecutive threads finish the tile's channels of a pixel)
+    const float floor = p.act == SS_ACT_RELU ? 0.f : -__builtin_inff();
+    const bool four = (p.Cout & 3) == 0;
+    struct Tail {                                         // what a finished quad needs from memory, fetched before the barrier
+        float bias[4], scale[4], res[4];
+    };
+    auto quad = [&](int t, int *pl, int *cq, int *pg, int *o) {
+        *pl = t / (8 * TM);                               // pixel, quad of channels: accumulators 4*(cq/2).. of lane group cq%2
+        *cq = t % (8 * TM);
+        *pg = n0 + *pl;
+        *o = mt * 32 + *cq * 4;
+        return *pg < p.P && *o < p.Cout;
+    };
+    auto fetch = [&](int t) {
+        Tail f;
+        int pl, cq, pg, o;
+        const bool in = t < QUADS && quad(t, &pl, &cq, &pg, &o);
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            const bool ine = in && o + e < p.Cout;
+            f.bias[e] = ine && p.bias != nullptr ? p.bias[o + e] : 0.f;
+            f.scale[e] = Q8 && ine && p.scale != nullptr ? p.scale[o + e] : 1.f;
+            f.res[e] = 0.f;
+        }
+        if constexpr (!Q8) {
+            if (p.residual != nullptr && in) {
+                const uint16_t *r = p.residual + (size_t)pg * p.Cout + o;
+                if (four) {
+                    const uint2 u = *reinterpret_cast<const uint2 *>(r);
+                    f.res[0] = widen<ODT>((uint16_t)u.x); f.res[1] = widen<ODT>((uint16_t)(u.x >> 16));
+                    f.res[2] = widen<ODT>((uint16_t)u.y); f.res[3] = widen<ODT>((uint16_t)(u.y >> 16));
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; e++)
+                        if (o + e < p.Cout) f.res[e] = widen<ODT>(r[e]);
+                }
+            }
+        }
+        return f;
+    };
+    auto finish = [&](int t, const Tail &f) {
+        int pl, cq, pg, o;
+        if (t >= QUADS || !quad(t, &pl, &cq, &pg, &o)) return;
+        float v[4];
+        const int from = (cq >> 1) * 64 + (cq & 1) * 32 + pl;
+        if constexpr (DT == SS_I8) {
+            int sum[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int w = 0; w < NW; w++) {
+                const u32x4 u = part[w * RSTRIDE + from];
+#pragma unroll
+                for (int e = 0; e < 4; e++) sum[e] += (int)u[e];
+            }
+#pragma unroll
+            for (int e = 0; e < 4; e++) v[e] = (float)sum[e];
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; e++) v[e] = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; w++) {
+                const f32x4 u = __builtin_bit_cast(f32x4, part[w * RSTRIDE + from]);
+#pragma unroll
+                for (int e = 0; e < 4; e++) v[e] += u[e];
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            const float z = (Q8 ? v[e] * f.scale[e] + f.bias[e] : v[e] + f.bias[e]) + f.res[e];
+            v[e] = p.act == SS_ACT_GELU ? gelu_erfc(z) : floor_at(z, floor);
+        }
+        uint16_t *y = p.y + (size_t)pg * p.Cout + o;
+        if (four) {
+            *reinterpret_cast<uint2 *>(y) = make_uint2(cvt_pack2<ODT>(v[0], v[1]), cvt_pack2<ODT>(v[2], v[3]));
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+                if (o + e < p.Cout) y[e] = (uint16_t)(cvt_pack2<ODT>(v[e], 0.f) & 0xFFFFu);
+        }
+    };
+    const Tail first = fetch(tid);
+    __syncthreads();
+    finish(tid, first);
+    for (int t = tid + NW * 64; t < QUADS; t += NW * 64) finish(t, fetch(t));
+}
+
+template <int DT, bool SPARSE, int MODE, int KH, int KW, int PX, int TM, int NW>
+static int launch_small_waves(ConvParams p, hipStream_t s)
+{
+    constexpr size_t smem = NW * small_wave_lds<MODE, KH * KW, PX, TM>();
+    static_assert(smem <= 160 * 1024, "LDS");
+    p.tiles_m = (p.Mt + TM - 1) / TM;
+    fast_div_setup((unsigned)p.tiles_m, &p.tm_mul, &p.tm_sh);
+    const long long blocks = small_blocks(p, PX, TM);
+    if (blocks <= 0 || blocks > 0x7FFFFFFFll) return SS_ERR_UNSUPPORTED;
+    auto kern = conv_small_kernel<DT, SPARSE, MODE, KH, KW, PX, TM, NW>;
+    if (smem > 64 * 1024) {
+        static std::atomic<unsigned long long> done_mask{0};      // as in launch(): once per device
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess) return SS_ERR_HIP;
+        const unsigned long long bit = 1ull << (dev & 63);
+        if (dev >= 64 || !(done_mask.load(std::memory_order_acquire) & bit)) {
+            if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess)
+                return SS_ERR_HIP;
+            if (dev < 64) done_mask.fetch_or(bit, std::memory_order_release);
+        }
+    }
+    kern<<<dim3((unsigned)blocks), dim3(NW * 64), smem, s>>>(p);
+    return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP;
+}
+
+// Waves per workgroup: one per chunk of 32 channels (taps: the kernel's tap count, 0 = direct) or per four steps (direct), at most eight
+// (sixteen with the 16-pixel tiles of the direct modes, whose fragments leave the registers for it).
+static inline int small_waves(const ConvParams &p, int taps, bool tile16)
+{
+    const int shares = taps ? (p.Ks + taps - 1) / taps : (p.Ks + 3) / 4;
+    return shares <= 2 ? 2 : (shares <= 4 ? 4 : (shares <= 8 || taps || !tile16 ? 8 : 16));
+}
+
+enum { SMALL_NONE = -1, SMALL_16 = 0, SMALL_32 = 1, SMALL_64X32 = 2 };      // 32 channels x 16 / x 32 pixels, 64 x 32
+
+// Which variant pays, from a sweep of all of them and the tiled kernels over the ResNet-50 layers at batches 1 to 32, both
+// flattenings, sparse and dense, 16- and 8-bit operands (profiles/small_grids.md):
+//   * 16-pixel tiles while one per compute unit holds them all, and with two waves (short reductions) up to eight waves
+//     per compute unit: 3x3 256 -> 256 on one 14x14 image 9.0 -> 4.4 us, 64 -> 64 on one 56x56 4.9 -> 3.7;
+//   * 32-pixel tiles under the same conditions (four waves up to eight waves per unit, 2x2 kernels two workgroups):
+//     the 256 -> 256 layer on four images 9.1 -> 5.4;
+//   * 64 x 32 tiles for long reductions while one per unit holds them: 512 -> 512 on sixteen 7x7 images 19 -> 9.6 us.  Not for the
+//     dense form of the tap modes (its fragments spill: 11.4 vs 9.8) nor for 8-bit direct loads (8.3 vs 6.6).
+//   * 1x1 reductions of one or two steps stay with the tiled kernels (3.5 vs 3.6 us).
+static inline int small_variant(const ConvParams &p, int taps, bool sparse, bool q8, int ncu)
+{
+    if (!taps && p.kh * p.kw == 1 && p.Ks <= 2) return SMALL_NONE;
+    const long long b16 = small_blocks(p, 16, 1), b32 = small_blocks(p, 32, 1), b64 = small_blocks(p, 32, 2);
+    const int nw = small_waves(p, taps, false);
+    if (b16 <= ncu || (taps && nw == 2 && b16 * nw <= 8ll * ncu)) return SMALL_16;
+    if (b32 <= ncu || (taps && nw == 4 && b32 * nw <= 8ll * ncu) || (taps == 4 && b32 <= 2ll * ncu)) return SMALL_32;
+    if (b64 <= ncu && (taps ? nw == 8 && sparse : p.Ks >= 36 && !q8)) return SMALL_64X32;
+    return SMALL_NONE;
+}
+
+template <int DT, bool SPARSE, int MODE, int KH, int KW>
+static int launch_small(const ConvParams &p, int variant, hipStream_t s)
+{
+    constexpr int taps = small_taps(MODE) ? KH * KW : 0;
+    if (variant < 0) {                                    // the library decides
+        const int ncu = compute_units();
+        if (ncu <= 0) return SS_ERR_HIP;
+        variant = small_variant(p, taps, SPARSE, is_byte_type(DT), ncu);
+        if (variant < 0) return SS_ERR_INVALID_ARG;
+    }
+    auto waves = [&](auto px, auto tm) -> int {
+        constexpr int PX = decltype(px)::value, TM = decltype(tm)::value;
+        switch (small_waves(p, taps, PX == 16)) {
+            case 2: return launch_small_waves<DT, SPARSE, MODE, KH, KW, PX, TM, 2>(p, s);
+            case 4: return launch_small_waves<DT, SPARSE, MODE, KH, KW, PX, TM, 4>(p, s);
+            case 8: return launch_small_waves<DT, SPARSE, MODE, KH, KW, PX, TM, 8>(p, s);
+            default: break;
+        }
+        if constexpr (PX == 16 && taps == 0) return launch_small_waves<DT, SPARSE, MODE, KH, KW, PX, TM, 16>(p, s);
+        return SS_ERR_INVALID_ARG;
+    };
+    using std::integral_constant;
+    if (variant == SMALL_16) return waves(integral_constant<int, 16>{}, integral_constant<int, 1>{});
+    if (variant == SMALL_32) return waves(integral_constant<int, 32>{}, integral_constant<int, 1>{});
+    return waves(integral_constant<int, 32>{}, integral_constant<int, 2>{});
+}
+
+// Returns SS_ERR_INVALID_ARG where no mode fits, or (variant < 0: the library decides) where the tiled kernels are the better choice.
+template <int DT, bool SPARSE>
+static int small_mode(const ss_weight_desc *desc, const ConvParams &p, int variant, hipStream_t s)
+{
+    const int taps = desc->kh * desc->kw;
+    if (taps == 1 && p.Cin % 8 == 0) return launch_small<DT, SPARSE, SMALL_PW, 1, 1>(p, variant, s);
+    if (desc->korder == SS_K_RSC && p.Cin % 8 == 0) return launch_small<DT, SPARSE, SMALL_RSC, 1, 1>(p, variant, s);
+    if (desc->korder == SS_K_CRS && p.Cin % 32 == 0) {
+        if (desc->kh == 3 && desc->kw == 3) return launch_small<DT, SPARSE, SMALL_TAPS, 3, 3>(p, variant, s);
+        if (desc->kh == 2 && desc->kw == 2) return launch_small<DT, SPARSE, SMALL_TAPS, 2, 2>(p, variant, s);
+    }
+    if constexpr (!is_byte_type(DT)) {
+        if (desc->korder == SS_K_CRS && p.Cin % 4 == 0 && p.Cin >= 8) {
+            if (desc->kh == 3 && desc->kw == 3) return launch_small<DT, SPARSE, SMALL_TAPSR, 3, 3>(p, variant, s);
+            if (desc->kh == 2 && desc->kw == 2) return launch_small<DT, SPARSE, SMALL_TAPSR, 2, 2>(p, variant, s);
+        }
+    }
+    return SS_ERR_INVALID_ARG;
+}
+
+}  // namespace ss
+
+#endif
