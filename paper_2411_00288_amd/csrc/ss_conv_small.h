@@ -454,6 +454,263 @@ static int small_mode(const ss_weight_desc *desc, const ConvParams &p, int varia
     return SS_ERR_INVALID_ARG;
 }
 
+// ---------------------------------------------------------------------------------------------
+// The fused pair (3x3 in the paper's flattening -> 1x1 + residual, see conv_kernel's FUSE) on few output pixels: a workgroup of eight
+// waves owns PX pixels through both layers.  All chunks of the first layer's unfolded input are staged in LDS at once (one
+// memory latency, the weights of both layers in flight with it); the waves then split rows x reduction of the first layer, the
+// partial sums meet in LDS, the finished 16-bit tile stays there, and the waves take the second layer's row tiles in turn.
+// Measured against the tiled fused kernel, whose 64-pixel workgroups are 49 and 13 on one image: 64 -> 64 -> 256 at 56x56
+// 9.2 -> 5.8 us, 128 -> 128 -> 512 at 28x28 11.5 -> 8.3 (bound by the weights each workgroup fetches: a ring of 18 instead of 9
+// steps in flight measured 8.6); past one workgroup per compute unit the tiled kernel shares them over more pixels and wins.
+// ---------------------------------------------------------------------------------------------
+constexpr int kPairWaves = 8;
+struct PairShape {                    // LDS map of a workgroup, in bytes
+    size_t stage, part, tile, total;  // [0, stage): staging, later the output slabs; then partial sums; then the 16-bit tile
+};
+static inline __host__ __device__ PairShape pair_shape(int px, int nchunks, int cout1)
+{
+    PairShape h;
+    h.stage = (size_t)nchunks * px * 576;
+    const size_t slabs = (size_t)kPairWaves * px * kFuseRow * 4;
+    if (h.stage < slabs) h.stage = slabs;
+    h.part = (size_t)kPairWaves * 4096;
+    h.tile = (size_t)px * (cout1 + 4) * 2;
+    h.total = h.stage + h.part + h.tile;
+    return h;
+}
+
+template <int DT, bool SPARSE, int PX>
+__global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams p)
+{
+    constexpr int TAPS = 9, VPR = 36, NT = kPairWaves * 64, RING = 9, KS2 = 8;
+    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 5, c = lane & 31, cc = c & (PX - 1);
+    const int n0 = blockIdx.x * PX;
+    const int HoWo = p.Ho * p.Wo;
+    const int nchunks = p.Ks / TAPS;                      // cin % 32 == 0
+    const PairShape sh = pair_shape(PX, nchunks, p.Cout);
+    u32x4 *const stage = reinterpret_cast<u32x4 *>(smem);
+    u32x4 *const part = reinterpret_cast<u32x4 *>(reinterpret_cast<char *>(smem) + sh.stage);
+    uint16_t *const tile = reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(smem) + sh.stage + sh.part);
+    const int TROW = p.Cout + 4;                          // 16-bit units per pixel row of the tile
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.x), 0, (int)p.x_bytes, kRsrcFlags);
+    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.a_vals), 0, (int)p.a_bytes, kRsrcFlags);
+    const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.a_meta), 0, (int)p.meta_bytes, kRsrcFlags);
+    const __amdgpu_buffer_rsrc_t ra2 = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.a2_vals), 0, (int)p.a2_bytes, kRsrcFlags);
+    const __amdgpu_buffer_rsrc_t rm2 = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.a2_meta), 0, (int)p.meta2_bytes, kRsrcFlags);
+
+    // ---- first layer: this wave's row tile and share of the reduction steps
+    const int groups = kPairWaves / p.Mt;                 // waves per row tile (Mt <= 8)
+    const int rt = wave % p.Mt, kg = wave / p.Mt;
+    const bool works = kg < groups;
+    const int s0 = works ? kg * p.Ks / groups : 0, s1 = works ? (kg + 1) * p.Ks / groups : 0;
+    using A = AStep<SPARSE, 1>;
+    auto load_w = [&](A &a, __amdgpu_buffer_rsrc_t rv, __amdgpu_buffer_rsrc_t ri, int mt, int Ks, int Kp, int ks) {
+        if constexpr (SPARSE) {
+            a.v[0][0] = __builtin_amdgcn_raw_buffer_load_b128(rv, lane * 16, (mt * Ks + ks) * 1024, 0);
+            a.idx[0] = __builtin_amdgcn_raw_buffer_load_b32(ri, lane * 4, (mt * Kp + (ks >> 1)) * 256, 0);
+        } else {
+            a.v[0][0] = __builtin_amdgcn_raw_buffer_load_b128(rv, lane * 16, (mt * Ks + ks) * 2048, 0);
+            a.v[1][0] = __builtin_amdgcn_raw_buffer_load_b128(rv, lane * 16, (mt * Ks + ks) * 2048 + 1024, 0);
+        }
+    };
+    auto mma = [&](const A &a, const B32 &b, f32x16 acc, int ks) {
+        if constexpr (SPARSE) return mma_sparse<DT>(a.v[0][0], b, acc, a.idx[0] >> ((ks & 1) * 16));
+        else return mma_dense<DT>(a.v[1][0], b.hi, mma_dense<DT>(a.v[0][0], b.lo, acc));
+    };
+    // ---- activations: item = (chunk, pixel, octet of channels), nine taps each
+    auto stage_item = [&](int it, u32x4 (&x)[TAPS]) {
+        const int unit = it & 3, pr = (it >> 2) & (PX - 1), ci = it / (PX * 4);
+        const int pg = n0 + pr;
+        int ih = -(1 << 28), iw = -(1 << 28);
+        unsigned byte = 0;
+        if (pg < p.P) {
+            const int n = fast_div(pg, p.howo_mul, p.howo_sh);
+            const int rem = pg - n * HoWo;
+            const int ho = fast_div(rem, p.wo_mul, p.wo_sh);
+            ih = ho * p.sh - p.ph;
+            iw = (rem - ho * p.Wo) * p.sw - p.pw;
+            byte = (unsigned)((((n * p.H + ih) * p.W + iw) * p.Cin + ci * 32 + unit * 8) * 2);
+        }
+#pragma unroll
+        for (int tap = 0; tap < TAPS; tap++) {
+            const int r = tap / 3, t = tap % 3;
+            const bool ok = (unsigned)(ih + r) < (unsigned)p.H && (unsigned)(iw + t) < (unsigned)p.W;
+            x[tap] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(ok ? byte + (unsigned)((r * p.W + t) * p.Cin * 2) : kOutOfRange), 0, 0);
+        }
+    };
+    auto store_item = [&](int it, const u32x4 (&x)[TAPS]) {
+        const int unit = it & 3, pr = (it >> 2) & (PX - 1), ci = it / (PX * 4), key = (pr >> 2) & 3;
+#pragma unroll
+        for (int v = 0; v < TAPS; v++) stage[(ci * PX + pr) * VPR + ((unit * TAPS + v) ^ key)] = taps_vector<false, false, TAPS>(x, v, false);
+    };
+    const int items = nchunks * PX * 4;
+    A a[RING];
+    {
+        u32x4 x[TAPS];
+        if (tid < items) stage_item(tid, x);
+#pragma unroll
+        for (int j = 0; j < RING; j++)
+            if (s0 + j < s1) load_w(a[j], ra, rm, rt, p.Ks, p.Kp, s0 + j);      // uniform
+        if (tid < items) store_item(tid, x);
+    }
+    for (int it = tid + NT; it < items; it += NT) {
+        u32x4 x[TAPS];
+        stage_item(it, x);
+        store_item(it, x);
+    }
+    struct Row2 {
+        A a[KS2];
+        float4 b[4];
+    };
+    auto load_row2 = [&](Row2 &r, int mt) {
+#pragma unroll
+        for (int s = 0; s < KS2; s++)
+            if (s < p.Ks2) load_w(r.a[s], ra2, rm2, mt, p.Ks2, p.Kp2, s);      // uniform
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+            r.b[q] = p.bias2 ? *reinterpret_cast<const float4 *>(p.bias2 + mt * 32 + 8 * q + 4 * g) : make_float4(0.f, 0.f, 0.f, 0.f);
+    };
+    Row2 r2;
+    if (wave < p.Mt2) load_row2(r2, wave);                // in flight while the first layer is multiplied
+    __syncthreads();
+    f32x16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; v++) acc[v] = 0.f;
+    {
+        const int key = (cc >> 2) & 3;
+        for (int s = s0; s < s1; s += RING) {
+#pragma unroll
+            for (int j = 0; j < RING; j++) {
+                if (s + j < s1) {                         // uniform
+                    const int ci = (s + j) * 7282 >> 16, st = s + j - ci * TAPS;      // chunk and step inside it (7282 = ceil(2^16 / 9), exact below 2^13)
+                    const u32x4 *row = stage + (ci * PX + cc) * VPR;
+                    B32 b;
+                    b.lo = row[(st * 4 + 2 * g) ^ key];
+                    b.hi = row[(st * 4 + 2 * g + 1) ^ key];
+                    acc = mma(a[j], b, acc, s + j);
+                    if (s + RING + j < s1) load_w(a[j], ra, rm, rt, p.Ks, p.Kp, s + RING + j);
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const f32x4 w = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+        part[wave * 256 + q * 64 + lane] = __builtin_bit_cast(u32x4, w);
+    }
+    __syncthreads();
+    const float floor1 = p.act == SS_ACT_RELU ? 0.f : -__builtin_inff();
+    for (int t = tid; t < PX * 8 * p.Mt; t += NT) {       // quads of channels, pixel fastest: (row tile, quad, pixel)
+        const int pl = t & (PX - 1), q = t / PX, m = q >> 3, cq = q & 7;
+        float v[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int k = 0; k < groups; k++) {
+            const f32x4 u = __builtin_bit_cast(f32x4, part[(k * p.Mt + m) * 256 + (cq >> 1) * 64 + (cq & 1) * 32 + pl]);
+#pragma unroll
+            for (int e = 0; e < 4; e++) v[e] += u[e];
+        }
+        const int o = m * 32 + cq * 4;
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            const float z = v[e] + (p.bias != nullptr ? p.bias[o + e] : 0.f);
+            v[e] = p.act == SS_ACT_GELU ? gelu_erfc(z) : floor_at(z, floor1);
+        }
+        *reinterpret_cast<uint2 *>(tile + pl * TROW + o) = make_uint2(cvt_pack2<DT>(v[0], v[1]), cvt_pack2<DT>(v[2], v[3]));
+    }
+    __syncthreads();
+    // ---- second layer
+    const float floor2 = p.act2 == SS_ACT_RELU ? 0.f : -__builtin_inff();
+    float *const slab = reinterpret_cast<float *>(smem) + wave * (PX * kFuseRow);
+    for (int mt = wave; mt < p.Mt2; mt += kPairWaves) {
+        constexpr int IT = PX * 4 / 64;                   // 16-byte runs per lane
+        u32x4 res[IT];
+#pragma unroll
+        for (int j = 0; j < IT; j++) {
+            const int it = lane + 64 * j, pg = n0 + (it >> 2);
+            res[j] = u32x4{0u, 0u, 0u, 0u};
+            if (p.res2 != nullptr && pg < p.P) res[j] = *reinterpret_cast<const u32x4 *>(p.res2 + (size_t)pg * p.Cout2 + mt * 32 + (it & 3) * 8);
+        }
+        f32x16 acc2;
+#pragma unroll
+        for (int v = 0; v < 16; v++) acc2[v] = 0.f;
+#pragma unroll
+        for (int s = 0; s < KS2; s++) {
+            if (s >= p.Ks2) break;                        // uniform
+            const uint16_t *src = tile + cc * TROW + 32 * s + 16 * g;      // 8-byte aligned
+            const uint2 u0 = *reinterpret_cast<const uint2 *>(src), u1 = *reinterpret_cast<const uint2 *>(src + 4);
+            const uint2 u2 = *reinterpret_cast<const uint2 *>(src + 8), u3 = *reinterpret_cast<const uint2 *>(src + 12);
+            B32 b;
+            b.lo = u32x4{u0.x, u0.y, u1.x, u1.y};
+            b.hi = u32x4{u2.x, u2.y, u3.x, u3.y};
+            acc2 = mma(r2.a[s], b, acc2, s);
+        }
+        if (PX == 32 || c < PX) {
+#pragma unroll
+            for (int q = 0; q < 4; q++)
+                *reinterpret_cast<float4 *>(slab + cc * kFuseRow + 8 * q + 4 * g) =
+                    make_float4(acc2[4 * q] + r2.b[q].x, acc2[4 * q + 1] + r2.b[q].y, acc2[4 * q + 2] + r2.b[q].z, acc2[4 * q + 3] + r2.b[q].w);
+        }
+        if (mt + kPairWaves < p.Mt2) load_row2(r2, mt + kPairWaves);
+        __builtin_amdgcn_wave_barrier();                  // (a wave's LDS operations execute in order: the reads below see the writes above)
+#pragma unroll
+        for (int j = 0; j < IT; j++) {
+            const int it = lane + 64 * j, px = it >> 2, run = it & 3, pg = n0 + px;
+            const float4 lo = *reinterpret_cast<const float4 *>(slab + px * kFuseRow + run * 8);
+            const float4 hi = *reinterpret_cast<const float4 *>(slab + px * kFuseRow + run * 8 + 4);
+            if (pg >= p.P) continue;
+            const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+            uint32_t w[4];
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                float x0 = v[2 * e] + widen<DT>((uint16_t)(res[j][e] & 0xFFFFu)), x1 = v[2 * e + 1] + widen<DT>((uint16_t)(res[j][e] >> 16));
+                if (p.act2 == SS_ACT_GELU) { x0 = gelu_erfc(x0); x1 = gelu_erfc(x1); }
+                else { x0 = floor_at(x0, floor2); x1 = floor_at(x1, floor2); }
+                w[e] = cvt_pack2<DT>(x0, x1);
+            }
+            *reinterpret_cast<uint4 *>(p.y2 + (size_t)pg * p.Cout2 + mt * 32 + run * 8) = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+template <int DT, bool SPARSE, int PX>
+static int launch_pair_small(const ConvParams &p, hipStream_t s)
+{
+    const size_t smem = pair_shape(PX, p.Ks / 9, p.Cout).total;
+    auto kern = pair_small_kernel<DT, SPARSE, PX>;
+    if (smem > 64 * 1024) {
+        static std::atomic<unsigned long long> done_mask{0};      // as in launch(): once per device
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess) return SS_ERR_HIP;
+        const unsigned long long bit = 1ull << (dev & 63);
+        if (dev >= 64 || !(done_mask.load(std::memory_order_acquire) & bit)) {
+            if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+                return SS_ERR_HIP;
+            if (dev < 64) done_mask.fetch_or(bit, std::memory_order_release);
+        }
+    }
+    kern<<<dim3((unsigned)(((long long)p.P + PX - 1) / PX)), dim3(kPairWaves * 64), smem, s>>>(p);
+    return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP;
+}
+
+// The fused pair on few pixels: PX = 16 or 32 as given, or chosen (px = 0) while one workgroup per compute unit holds them
+// all.  SS_ERR_INVALID_ARG where it does not fit or the tiled kernel is the better choice.
+template <int DT, bool SPARSE>
+static int pair_small(const ss_weight_desc *d1, const ConvParams &p, int px, hipStream_t s)
+{
+    if (d1->korder != SS_K_CRS || d1->kh != 3 || d1->kw != 3 || d1->cin % 32 != 0 || p.Mt > kPairWaves || p.Cout % 32 != 0) return SS_ERR_INVALID_ARG;
+    if (px == 0) {
+        const int ncu = compute_units();
+        if (ncu <= 0) return SS_ERR_HIP;
+        px = ((long long)p.P + 15) / 16 <= ncu ? 16 : (((long long)p.P + 31) / 32 <= ncu ? 32 : 0);
+    }
+    if (px == 0 || pair_shape(px, p.Ks / 9, p.Cout).total > 160 * 1024) return SS_ERR_INVALID_ARG;
+    return px == 16 ? launch_pair_small<DT, SPARSE, 16>(p, s) : launch_pair_small<DT, SPARSE, 32>(p, s);
+}
+
 }  // namespace ss
 
 #endif

@@ -91,3 +91,26 @@ def test_small_grid_choice_replays_in_a_hip_graph(ss):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(y.view(torch.int16), eager.view(torch.int16))
+
+
+@pytest.mark.parametrize("tile", [20, 21, None])
+@pytest.mark.parametrize("cin,mid,cout,s,H", [(32, 32, 32, 1, 5), (64, 64, 256, 1, 7), (96, 96, 160, 2, 9), (128, 128, 512, 1, 6), (32, 160, 64, 1, 5),
+                                              (128, 256, 288, 2, 7)])
+@pytest.mark.parametrize("sparse", [True, False])
+def test_small_fused_pair_equals_the_two_calls(ss, force_tile, cin, mid, cout, s, H, sparse, tile):
+    L1, L2 = L_(1, H, H + 2, cin, mid, 3, s=s, p=1, dtype=wl.BF16), L_(1, 1, 1, mid, cout, 1, dtype=wl.BF16, seed=22)
+    a, b = wl.make_inputs(L1), wl.make_inputs(L2)
+    d1, d2 = layer_desc(ss, L1), layer_desc(ss, L2)
+    pack = (lambda d, t: ss.ss_mask_compress(d, dev_bits(t["W"], wl.BF16), torch.from_numpy(t["M"]).cuda())) if sparse else \
+           (lambda d, t: ss.ss_dense_pack(d, dev_bits(t["W"], wl.BF16), torch.from_numpy(t["M"]).cuda()))
+    w1, w2, b1, b2 = pack(d1, a), pack(d2, b), torch.from_numpy(a["bias"]).cuda(), torch.from_numpy(b["bias"]).cuda()
+    x = dev_bits(a["x"], wl.BF16)
+    res = torch.randn((1, L1.Ho, L1.Wo, cout), device="cuda").to(torch.bfloat16)
+    force_tile(2)                                             # the two calls in tiled kernels
+    conv, conv_res = (ss.ss_conv2d_fwd, ss.ss_conv2d_res_fwd) if sparse else (ss.ss_conv2d_dense_fwd, ss.ss_conv2d_dense_res_fwd)
+    t = conv(d1, x, w1, b1, (s, s), (1, 1), wl.ACT_RELU)
+    want = conv_res(d2, t, w2, b2, res, (1, 1), (0, 0), wl.ACT_GELU)
+    force_tile(tile)
+    fused = ss.ss_conv2d_pw_fused_fwd if sparse else ss.ss_conv2d_pw_fused_dense_fwd
+    got = fused(d1, x, w1, b1, (s, s), (1, 1), wl.ACT_RELU, d2, w2, b2, res, wl.ACT_GELU)
+    assert (torch.linalg.norm(got.float() - want.float()) / torch.linalg.norm(want.float())).item() <= 2e-3
