@@ -143,9 +143,6 @@ int block_limit();
 // Test hook (ss_debug.h): workgroups per output tile forced by ss_debug_force_split, or 0 when the library decides.
 int forced_split();
 
-// Compute units of the current device (cached per device), or -1 when the runtime cannot say.
-int compute_units();
-
 // One function per operand type and operand form, each defined in its own translation unit.  conv_dispatch_* picks
 // the staging mode and tile for the problem and launches; fused_dispatch_* does so for a k x k convolution followed by
 // a 1x1 one; mlp_dispatch_* launches the 1x1 -> 1x1 kernel.  All return an SS_* status.

@@ -1,6 +1,7 @@
 // Depthwise convolution (one filter per channel), NHWC 16-bit, stride 1: the grouped convolutions that the paper
-// leaves dense (Sec. 4, "Architectures"), e.g. the 7x7 of a ConvNeXt block.  A simple dedicated kernel: it is
-// bound by vector ALU work (49 multiply-adds per output), not by a matrix unit.
+// leaves dense (Sec. 4, "Architectures"), e.g. the 7x7 of a ConvNeXt block.  Two kernels: square filters run on the matrix
+// unit (dwconv_mfma_kernel), the others on the vector ALU, whose 49 multiply-adds per output bound the 7x7 at about 50 us for the
+// 128 x 56 x 56 x 96 layer before any load or conversion (99 us measured).
 #include "ss_internal.h"
 
 namespace ss {
@@ -105,10 +106,314 @@ __global__ __launch_bounds__(256) void dwconv_kernel(const uint16_t *__restrict_
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Square filters on the matrix unit.
+//
+// For one channel and one filter row r, sixteen outputs along an image row are a banded Toeplitz matrix times the row's
+// pixels: D[m, n] += sum_k T_r[m, k] X[k, n] with T_r[m, k] = w[r][k - m] (0 <= k - m < K) and X[k, n] = pixel w0 - pad + k of
+// column n's input row.  The sixteen columns n of a V_MFMA_F32_16X16X32 are sixteen *strips* -- an image, a run of 16
+// output columns, a segment of R output rows -- that all walk down their rows in step: an input row's fragment is read from LDS once and
+// multiplied with the K matrices T_0 .. T_{K-1} into the K output rows it contributes to, whose accumulators rotate.  A fifth
+// of the products are useful (K of 32), which the matrix unit's rate pays for many times over.
+//
+// A workgroup owns 16 strips x 16 channels, two channels per wave (their K matrices stay in registers).  Per input row: the rows
+// two steps ahead are in flight to registers, the next one is transposed from channel-fastest to pixel-fastest (one
+// v_perm per two elements) into the other LDS buffer, the current one is multiplied, and the finished output row crosses LDS back to
+// channel-fastest order and is stored during the next step; one barrier per step.
+//
+// The zeros of T_r meet pixels outside an output's window, so a NaN or an infinity there reaches it as the NaN of 0 x inf: a
+// workgroup that sees a non-finite output recomputes all of its outputs on the vector ALU, each from its own window.
+// ---------------------------------------------------------------------------------------------
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+
+struct DwParams {
+    const uint16_t *x, *w;
+    const float *bias;
+    uint16_t *y;
+    int N, H, W, C, ph, pw, Ho, Wo, act;
+    int R, segs, wt, strips, groups;      // output rows per strip, segments per image, 16-wide tiles per row, strips in all, groups of 16 channels
+    unsigned x_bytes, w_bytes, y_bytes;
+};
+
+template <int DT>
+__device__ __forceinline__ f32x4 mma16(u32x4 a, u32x4 b, f32x4 c)
+{
+    if constexpr (DT == SS_F16)
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+    else
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// max(v, floor) that hands a NaN through: ReLU with floor = 0, the identity with floor = -inf.
+__device__ __forceinline__ float max_nan(float v, float floor) { return __builtin_elementwise_maximum(v, floor); }
+
+// Workgroup barrier that orders LDS traffic only: loads and output stores stay in flight across it.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+constexpr int kDwGroup = 16;              // channels of a workgroup
+constexpr int kDwIn = 16 * 16 * 32;       // 16-bit units of an input buffer: [channel][strip][32 pixels]
+constexpr int kDwPixel = 12;              // dwords per pixel of the output buffer (8 used) and
+constexpr int kDwStrip = 16 * kDwPixel + 4;      // per strip: 16-byte aligned runs whose writes spread over the banks
+
+template <int DT, int K>
+__global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t in_s[2][kDwIn];
+    __shared__ __attribute__((aligned(16))) uint32_t out_s[2][16 * kDwStrip];
+    __shared__ int odd_s;                                 // a non-finite value was met
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // neighbouring workgroups, which share halo rows and the other channel groups' cache lines, on one XCD; a workgroup keeps its
+    // channel group and takes every (gridDim / groups)-th block of 16 strips
+    const int nb = gridDim.x, xcd = blockIdx.x & 7;
+    const int lid = xcd * (nb >> 3) + min(xcd, nb & 7) + (blockIdx.x >> 3);
+    const int c0 = (lid % p.groups) * kDwGroup, first = lid / p.groups, stride = nb / p.groups;
+    const int nblocks = (p.strips + 15) >> 4;
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.x), 0, (int)p.x_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.w), 0, (int)p.w_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, (int)p.y_bytes, 0x00020000);
+    constexpr unsigned kOut = 0x80000000u;
+    constexpr uint32_t kInf = DT == SS_BF16 ? 0x7F80u : 0x7C00u;
+
+    struct Strip {
+        int img, row, col;                                // first output row and column
+        bool ok;
+    };
+    auto strip = [&](int block, int n) {
+        const int s = block * 16 + n;
+        const int rest = s / p.wt, img = rest / p.segs;
+        return Strip{img, (rest - img * p.segs) * p.R, (s - rest * p.wt) * 16, s < p.strips};
+    };
+    const int steps = p.R + K - 1;                        // input rows of a strip
+    // ---- staging: 384 threads, two neighbouring pixels x 8 channels each (the other 128 load nothing and write their zeros to
+    // the unused pixels 24 .. 31, which must be finite: no branch, so that the compiler's waits count the loads in flight exactly)
+    const bool stages = tid < 384;
+    const int so = tid & 1, sp = stages ? (tid >> 1) % 12 : 12 + ((tid >> 1) & 3), sn = stages ? tid / 24 : (tid >> 3) & 15;
+    const int sdst = (so * 8 * 16 + sn) * 16 + sp;
+    const unsigned row_bytes = (unsigned)(p.W * p.C * 2);
+    unsigned soff[2];                                     // byte offset of the thread's two pixels in the next row
+    int srow = 0, lblock = first, li = 0;                 // next row to load: block of strips, input row of the strip
+    auto aim_loads = [&]() {
+        const Strip s = strip(lblock, sn);
+        const bool ok = stages && s.ok && lblock < nblocks && c0 + so * 8 < p.C;
+        srow = s.row - p.ph;
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+            const int iw = s.col - p.pw + 2 * sp + j;
+            soff[j] = ok && (unsigned)iw < (unsigned)p.W ? (unsigned)((((s.img * p.H + srow) * p.W + iw) * p.C + c0 + so * 8) * 2) : kOut;
+        }
+    };
+    u32x4 st[K][2];                                       // input rows in flight: K, since the rotation of the accumulators unrolls the loop K times anyway
+    u16x2 top = {0, 0};                                   // largest magnitude pattern of an output
+    auto load_row = [&](u32x4 (&v)[2]) {
+        // (arithmetic only: behind a branch the waits would lose count)
+        const unsigned out = (unsigned)srow < (unsigned)p.H ? 0u : kOut;
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+            v[j] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(soff[j] | out), 0, 0);
+            soff[j] += row_bytes;                         // (an offset out of range stays so: the image is smaller than 2 GiB)
+        }
+        srow++;
+        if (++li == steps) {                              // uniform
+            li = 0;
+            lblock += stride;
+            aim_loads();
+        }
+    };
+    auto store_row = [&](int buf, const u32x4 (&v)[2]) {
+        uint32_t *dst = reinterpret_cast<uint32_t *>(in_s[buf]) + sdst;
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            dst[(2 * e) * 256] = __builtin_amdgcn_perm(v[1][e], v[0][e], 0x05040100u);
+            dst[(2 * e + 1) * 256] = __builtin_amdgcn_perm(v[1][e], v[0][e], 0x07060302u);
+        }
+    };
+    aim_loads();
+#pragma unroll
+    for (int i = 0; i < K; i++) load_row(st[i]);
+    // ---- the wave's two channels: K Toeplitz fragments each, from zero-padded rows of taps [channel pair][r][t + 15] in LDS
+    const int m = lane & 15, kg = lane >> 4, cw = c0 + wave * 2;
+    constexpr int TROW = 48;
+    static_assert(8 * K * TROW <= 2 * 16 * kDwStrip, "the taps fit the output buffers");
+    uint32_t *const taps = &out_s[0][0];
+    for (int i = tid; i < 8 * K * TROW; i += 512) {
+        const int pair = i / (K * TROW), rest = i - pair * (K * TROW), r = rest / TROW, t = rest - r * TROW - 15;
+        const bool ok = (unsigned)t < (unsigned)K && c0 + 2 * pair < p.C;
+        const uint32_t v = __builtin_amdgcn_raw_buffer_load_b32(rw, (int)(ok ? (unsigned)(((r * K + t) * p.C + c0 + 2 * pair) * 2) : kOut), 0, 0);
+        taps[i] = v;
+    }
+    if (tid == 0) odd_s = 0;
+    f32x4 b4[2];
+#pragma unroll
+    for (int j = 0; j < 2; j++) {
+        const float b = p.bias && cw + j < p.C ? p.bias[cw + j] : 0.f;
+        b4[j] = f32x4{b, b, b, b};
+    }
+    __syncthreads();
+    u32x4 a[2][K];
+#pragma unroll
+    for (int r = 0; r < K; r++) {
+        const uint32_t *src = taps + (wave * K + r) * TROW + 15 + 8 * kg - m;
+        uint32_t d[8];
+#pragma unroll
+        for (int j = 0; j < 8; j++) d[j] = src[j];
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            a[0][r][q] = __builtin_amdgcn_perm(d[2 * q + 1], d[2 * q], 0x05040100u);
+            a[1][r][q] = __builtin_amdgcn_perm(d[2 * q + 1], d[2 * q], 0x07060302u);
+        }
+    }
+    // ---- output: one 16-byte run of a pixel per thread, range-checked
+    const int oo = tid & 1, ow = (tid >> 1) & 15, on = tid >> 5;
+    const unsigned yrow = (unsigned)(p.Wo * p.C * 2);
+    int rows_left = 0, block = first;                     // output rows of this thread's strip
+    unsigned yoff = 0;
+    auto aim_stores = [&]() {
+        const Strip s = strip(block, on);
+        const bool ok = s.ok && s.col + ow < p.Wo && c0 + oo * 8 < p.C;
+        rows_left = ok ? min(p.R, p.Ho - s.row) : 0;
+        yoff = (unsigned)((((s.img * p.Ho + s.row) * p.Wo + s.col + ow) * p.C + c0 + oo * 8) * 2);
+    };
+    aim_stores();
+    const float floor = p.act == SS_ACT_RELU ? 0.f : -__builtin_inff();
+    // (The streaming cache policy, nt, would take the cold kernel alone from 65 to 51 us, but the layer behind it then reads
+    // this output from memory instead of the memory-side cache and loses more: 215 against 196 us for the ConvNeXt block.)
+    unsigned pending = kOut;                              // where the row written to LDS in the step before goes
+    auto emit = [&](int buf) {
+        const u32x4 v = *reinterpret_cast<const u32x4 *>(out_s[buf] + on * kDwStrip + ow * kDwPixel + oo * 4);
+        __builtin_amdgcn_raw_buffer_store_b128(v, ry, (int)pending, 0, 0);
+    };
+    store_row(0, st[0]);
+    load_row(st[0]);
+    __syncthreads();                                      // (the taps have been read: the output buffers are free)
+    f32x4 acc[2][K];
+#pragma unroll
+    for (int j = 0; j < 2; j++)
+#pragma unroll
+        for (int r = 0; r < K; r++) acc[j][r] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int par = 0, i = 0;
+    for (bool more = true; more;) {
+#pragma unroll
+        for (int u = 0; u < K; u++) {
+            // input row i of the block is in buffer par, the K rows after it are in or on their way to st[]
+            const u32x4 bf[2] = {*reinterpret_cast<const u32x4 *>(in_s[par] + ((wave * 2) * 16 + m) * 32 + 8 * kg),
+                                 *reinterpret_cast<const u32x4 *>(in_s[par] + ((wave * 2 + 1) * 16 + m) * 32 + 8 * kg)};
+            store_row(par ^ 1, st[(u + 1) % K]);
+            load_row(st[(u + 1) % K]);
+            emit(par ^ 1);
+#pragma unroll
+            for (int r = 0; r < K; r++)
+#pragma unroll
+                for (int j = 0; j < 2; j++)
+                    acc[j][(u + K - r) % K] = mma16<DT>(a[j][r], bf[j], r == 0 ? b4[j] : acc[j][(u + K - r) % K]);
+            {                                             // the last filter row completed output row i - (K - 1)
+                const int slot = (u + 1) % K, h = i - (K - 1);
+                uint32_t *dst = out_s[par] + m * kDwStrip + 4 * kg * kDwPixel + wave;
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    const uint32_t v = pack2<DT>(max_nan(acc[0][slot][e], floor), max_nan(acc[1][slot][e], floor));
+                    dst[e * kDwPixel] = v;
+                    top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, v & 0x7FFF7FFFu));
+                }
+                pending = (yoff + (unsigned)h * yrow) | ((unsigned)h < (unsigned)rows_left ? 0u : kOut);
+            }
+            lds_barrier();
+            par ^= 1;
+            if (++i == steps) {                           // uniform
+                i = 0;
+                block += stride;
+                if (block >= nblocks) { more = false; break; }
+                aim_stores();
+            }
+        }
+    }
+    emit(par ^ 1);
+    if (top[0] >= kInf || top[1] >= kInf) odd_s = 1;
+    __syncthreads();
+    if (odd_s == 0) return;
+    // ---- non-finite values: this workgroup's outputs again, each from its own window alone
+    for (block = first; block < nblocks; block += stride) {
+        aim_stores();
+        const Strip s = strip(block, on);
+        const int c = c0 + oo * 8, wo = s.col + ow;
+        for (int h = 0; h < rows_left; h++) {
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; e++) v[e] = p.bias ? p.bias[c + e] : 0.f;
+            for (int r = 0; r < K; r++) {
+                const int ih = s.row + h - p.ph + r;
+                if ((unsigned)ih >= (unsigned)p.H) continue;
+                for (int t = 0; t < K; t++) {
+                    const int iw = wo - p.pw + t;
+                    const unsigned off = (unsigned)iw < (unsigned)p.W ? (unsigned)((((s.img * p.H + ih) * p.W + iw) * p.C + c) * 2) : kOut;
+                    float xf[8], wf[8];
+                    widen8<DT>(__builtin_amdgcn_raw_buffer_load_b128(rx, (int)off, 0, 0), xf);
+                    widen8<DT>(*reinterpret_cast<const u32x4 *>(p.w + ((size_t)r * K + t) * p.C + c), wf);
+#pragma unroll
+                    for (int e = 0; e < 8; e++) v[e] = __builtin_fmaf(wf[e], xf[e], v[e]);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 8; e++) v[e] = max_nan(v[e], floor);
+            *reinterpret_cast<u32x4 *>(reinterpret_cast<char *>(p.y) + yoff + (size_t)h * yrow) =
+                u32x4{pack2<DT>(v[0], v[1]), pack2<DT>(v[2], v[3]), pack2<DT>(v[4], v[5]), pack2<DT>(v[6], v[7])};
+        }
+    }
+}
+
+// Segments per image: those for which the busiest workgroup walks over the fewest input rows (a strip of R output rows needs R + K - 1).
+template <int DT, int K>
+static int launch_dw_mfma(DwParams p, hipStream_t s)
+{
+    const int ncu = compute_units();
+    if (ncu <= 0) return SS_ERR_HIP;
+    p.wt = (p.Wo + 15) / 16;
+    p.groups = (p.C + kDwGroup - 1) / kDwGroup;
+    const long long per_group = ncu / p.groups > 0 ? ncu / p.groups : 1;
+    long long best = -1;
+    for (int segs = 1; segs <= p.Ho; segs++) {
+        const int R = (p.Ho + segs - 1) / segs;
+        if ((p.Ho + R - 1) / R != segs) continue;         // (no new length)
+        const long long strips = (long long)p.N * segs * p.wt, blocks = (strips + 15) / 16;
+        if (strips > 0x7FFFFFF0ll) break;
+        const long long cost = (blocks + per_group - 1) / per_group * (R + K - 1);
+        if (best < 0 || cost < best) { best = cost; p.R = R; p.segs = segs; p.strips = (int)strips; }
+    }
+    if (best < 0) return SS_ERR_UNSUPPORTED;
+    const long long blocks = (p.strips + 15ll) / 16, per = blocks < per_group ? blocks : per_group;
+    dwconv_mfma_kernel<DT, K><<<dim3((unsigned)(per * p.groups)), dim3(512), 0, s>>>(p);
+    return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP;
+}
+
 template <int DT>
 static int launch_dw(const uint16_t *x, const uint16_t *w, const float *bias, uint16_t *y, int N, int H, int W, int C, int kh,
                      int kw, int ph, int pw, int Ho, int Wo, int act, unsigned x_bytes, hipStream_t s)
 {
+    const long long ybytes = (long long)N * Ho * Wo * C * 2;
+    // The matrix kernel costs about the same for every filter width and has a longer set-up.  Measured against the vector one:
+    // 7x7 faster or equal from 1 x 7 x 7 x 96 up (128 x 56 x 56 x 96 in a chain: 99 -> 47 us); 5x5 from about 4 M outputs (32 x 56 x 56 x
+    // 96: 21.6 -> 16.9; 128 x 13 x 19 x 64: 8.5 vs 9.9); 3x3 nowhere.
+    if (kh == kw && ybytes < (1ll << 31) && (kw == 7 || (kw == 5 && ybytes >= (8ll << 20)))) {
+        DwParams p{};
+        p.x = x; p.w = w; p.bias = bias; p.y = y;
+        p.N = N; p.H = H; p.W = W; p.C = C; p.ph = ph; p.pw = pw; p.Ho = Ho; p.Wo = Wo; p.act = act;
+        p.x_bytes = x_bytes;
+        p.w_bytes = (unsigned)(kh * kw * C * 2);
+        p.y_bytes = (unsigned)ybytes;
+        switch (kw) {
+            case 5: return launch_dw_mfma<DT, 5>(p, s);
+            case 7: return launch_dw_mfma<DT, 7>(p, s);
+            default: return SS_ERR_UNSUPPORTED;
+        }
+    }
     const long long total = (long long)N * Ho * ((Wo + TW - 1) / TW) * (C / 8);
     if (total <= 0 || (total + 255) / 256 > 0x7FFFFFFFll) return SS_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)((total + 255) / 256)), block(256);

@@ -58,6 +58,9 @@ inline size_t dense_size(const TileDims &t)
     return (size_t)kHeaderBytes + (size_t)t.Mt * t.Ks * 2048;
 }
 
+// Compute units of the current device (cached per device), or -1 when the runtime cannot say.
+int compute_units();
+
 constexpr bool is_byte_type(int dtype) { return dtype == SS_I8 || dtype == SS_F8; }
 
 inline bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }

@@ -69,3 +69,31 @@ def test_dwconv_argument_errors(ss):
         ss.ss_dwconv2d_fwd(x, torch.zeros((3, 4, 16), dtype=torch.float16, device="cuda"))        # kernel width 4
     with pytest.raises(ss.SSError):
         ss.ss_dwconv2d_fwd(x, torch.zeros((3, 3, 16), dtype=torch.bfloat16, device="cuda"))       # dtype mismatch
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1, 8, 7, 3), (2, 3, 17, 40, 7, 3), (1, 20, 33, 16, 7, 0), (3, 5, 70, 24, 7, 6), (9, 17, 8, 104, 7, 3),
+                                   (70, 31, 30, 72, 5, 2)])
+def test_matrix_kernel_edges(ss, shape):
+    """Strips of 16 columns and several rows: images smaller than a strip, one column past it, channel groups half filled, more
+    strips than workgroups walk in one go; without and with a large padding."""
+    N, H, W, C, k, p = shape
+    rng = np.random.Generator(np.random.PCG64(H * W))
+    xb = wl.to_bits(rng.standard_normal((N, H, W, C), dtype=np.float32), wl.BF16)
+    wb = wl.to_bits(rng.standard_normal((k, k, C), dtype=np.float32) * np.float32((2.0 / (k * k)) ** 0.5), wl.BF16)
+    bias = (rng.standard_normal(C) * 0.1).astype(np.float32)
+    y = _run(ss, xb, wb, bias, wl.BF16, (p, p), wl.ACT_RELU)
+    check_close(y, oracle.dwconv2d(xb, wb, dtype=wl.BF16, bias=bias, pad=(p, p), act=wl.ACT_RELU), f"{shape}")
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_matrix_kernel_keeps_non_finite_values_in_their_windows(ss, value):
+    x = torch.randn((1, 20, 40, 24), device="cuda").to(torch.bfloat16)
+    w = torch.rand((7, 7, 24), device="cuda").to(torch.bfloat16) + 0.5
+    clean = ss.ss_dwconv2d_fwd(x, w, None, (3, 3))
+    x[0, 9, 14, 5] = value
+    y = ss.ss_dwconv2d_fwd(x, w, None, (3, 3))
+    hit = torch.zeros(y.shape, dtype=torch.bool, device="cuda")
+    hit[0, 6:13, 11:18, 5] = True
+    assert not torch.isfinite(y[hit].float()).any()
+    assert torch.isfinite(y[~hit].float()).all()
+    assert (y[~hit].float() - clean[~hit].float()).abs().max() <= 0.125      # (fp32 sums in another order, one rounding)
