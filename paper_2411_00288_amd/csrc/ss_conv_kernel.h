@@ -83,6 +83,15 @@ __device__ __forceinline__ Acc<DT> mma_sparse(u32x4 a, const B32 &b, Acc<DT> c, 
                                                           (int)idx, 0, 0);
 }
 
+// Workgroup barrier that orders LDS traffic only: the waves' outstanding global loads (weight ring, staging loads)
+// and stores (output tile) stay in flight across it.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Which dense FP8 kernels use the 32x32x64 instruction (the others use pairs of 32x32x16, see mma_dense): the deep
 // ones, which have the registers for its 8-register operands, and the short-chunk channels-last staging, whose shallow
 // kernels are otherwise bound by the half-rate instruction (measured: 81 vs 69 us on the N=500 benchmark layer).
@@ -148,21 +157,27 @@ __device__ __forceinline__ float widen(uint16_t bits)
         return __builtin_bit_cast(float, (uint32_t)bits << 16);
 }
 
-// GELU z * Phi(z) with the exact standard normal CDF Phi(z) = erfc(-z / sqrt 2) / 2.  erfc by the rational
-// approximation 7.1.26 of Abramowitz & Stegun (erfc(x) = t (a1 + t (a2 + ... a5 t)) exp(-x^2), t = 1 / (1 + p x),
-// x >= 0; absolute error below 1.5e-7, i.e. at fp32 round-off and three orders below the 16-bit output's), which
-// costs a third of the library erfc in an epilogue that otherwise only adds and rounds.  With h = Phi(-|z|):
-//     z >= 0:  z (1 - h) = z - |z| h        z < 0:  z h = -|z| h        i.e.  gelu(z) = max(z, 0) - |z| h,
-// which keeps the lower tail's relative accuracy (no 1 - erf cancellation) and needs no select.  The constants carry
-// the 1/sqrt 2 of the argument and the 1/2 of Phi; exp(-z^2 / 2) is one exp2.  (A NaN stays a NaN.)
-__device__ __forceinline__ float gelu_erfc(float z)
+// GELU z * Phi(z) with the exact standard normal CDF.  With a = |z| and h = Phi(-a):
+//     z >= 0:  z (1 - h) = z - a h        z < 0:  z h = -a h        i.e.  gelu(z) = max(z, 0) - a h,
+// which needs no select.  log2 Phi(-a) is smooth and close to a parabola: a polynomial of degree 8, fitted on [0, 6] for the
+// smallest largest error of Phi (iteratively reweighted least squares; relative errors below Phi = 2e-4 weighted as there),
+// and one exp2.  |error of Phi| < 1e-7, relative error 2e-7 at a = 1, 2e-5 at 3, 2e-4 at 5 and decaying to 0 beyond the fit (its leading
+// coefficient is negative): below fp32 round-off of the sum in front of it and three orders under the 16-bit output's.
+// Ten full-rate instructions and one quarter-rate one; the rational form 7.1.26 of Abramowitz & Stegun used before takes twelve and
+// two (80 against 56 clocks per wave) and is less accurate in the tail (5e-4 at 4).  (A NaN stays a NaN.)
+__device__ __forceinline__ float gelu_cdf(float z)
 {
     const float a = fabsf(z);
-    const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(0.3275911f * 0.70710678118654752f, a, 1.0f));
-    const float poly = t * (0.5f * 0.254829592f + t * (0.5f * -0.284496736f + t * (0.5f * 1.421413741f +
-                       t * (0.5f * -1.453152027f + t * (0.5f * 1.061405429f)))));
-    const float e = __builtin_amdgcn_exp2f(a * a * (-0.5f * 1.44269504088896341f));      // exp(-z^2 / 2)
-    return __builtin_fmaf(-a, poly * e, fmaxf(z, 0.f));
+    float q = -8.120558493747162e-07f;
+    q = __builtin_fmaf(q, a, 1.4290432782061204e-05f);
+    q = __builtin_fmaf(q, a, -6.487764435589362e-05f);
+    q = __builtin_fmaf(q, a, -0.0004287622419436152f);
+    q = __builtin_fmaf(q, a, 0.007434012361791795f);
+    q = __builtin_fmaf(q, a, -0.05273924310954606f);
+    q = __builtin_fmaf(q, a, -0.4591337784121185f);
+    q = __builtin_fmaf(q, a, -1.1511134917708818f);
+    q = __builtin_fmaf(q, a, -0.9999998474115108f);
+    return __builtin_fmaf(-a, __builtin_amdgcn_exp2f(q), fmaxf(z, 0.f));
 }
 
 // How the [pixels x reduction-chunk] slice of the unfolded input is built in LDS:
@@ -790,9 +805,9 @@ void conv_kernel(ConvParams p)
     const int etid = wave * 64 + (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     const float relu_floor = p.act == SS_ACT_RELU ? 0.f : -__builtin_inff();
     // ReLU when relu_floor = 0, identity when -inf (a NaN passes through); GELU = z * Phi(z) with the exact normal
-    // CDF, written with erfc so that the lower tail keeps its relative accuracy
+    // CDF (gelu_cdf)
     auto relu_or_id = [&](float v) { return floor_at(v, relu_floor); };
-    auto gelu = [](float v) { return gelu_erfc(v); };
+    auto gelu = [](float v) { return gelu_cdf(v); };
     if constexpr (CAN_SPLIT) {
         if (nsplit > 1) {
             // Every workgroup of the tile leaves its partial sums in the workspace, in register order (one 16-byte
@@ -1105,14 +1120,14 @@ void conv_kernel(ConvParams p)
 // ---------------------------------------------------------------------------------------------
 
 
-template <int DT, bool SPARSE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+template <int DT, bool SPARSE, int KS1, int TILES>      // KS1: reduction steps of the first layer; TILES: output tiles per wave
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TILES == 1 ? (SPARSE ? 4 : 3) : (SPARSE ? 3 : 2))))
 void mlp_kernel(MlpParams p)
 {
     constexpr int BN = 64, CH = 128;                      // pixels per workgroup, intermediate channels per chunk
     constexpr int CROW = CH + 4;                          // halfs per pixel row of the intermediate chunk (8-byte aligned rows)
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
-    const int XROW = p.Cin + 8;                           // halfs per pixel row of the input tile (16-byte aligned rows)
+    constexpr int XROW = KS1 * 32 + 8;                         // halfs per pixel row of the input tile (16-byte aligned rows)
     uint16_t *Xs = smem;
     uint16_t *Cs = smem + BN * XROW;
     float *b1s = reinterpret_cast<float *>(Cs + BN * CROW);       // the first layer's bias, all Cmid values
@@ -1127,18 +1142,17 @@ void mlp_kernel(MlpParams p)
     const __amdgpu_buffer_rsrc_t m2 = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.a2_meta), 0, (int)p.meta2_bytes, kRsrcFlags);
 
     struct Row1 {                                         // one 32-row tile of the first layer: all its reduction steps
-        u32x4 v[SPARSE ? 1 : 2][kMlpKs1];
-        uint32_t idx[kMlpKs1];
+        u32x4 v[SPARSE ? 1 : 2][KS1];
+        uint32_t idx[KS1];
     };
     auto load_row1 = [&](Row1 &r, int mt) {
 #pragma unroll
-        for (int s = 0; s < kMlpKs1; s++) {
-            if (s >= p.Ks1) break;                        // uniform
+        for (int s = 0; s < KS1; s++) {
             if constexpr (SPARSE) {
-                r.v[0][s] = __builtin_amdgcn_raw_buffer_load_b128(r1, (int)(((unsigned)(mt * p.Ks1 + s) * 64 + lane) * 16u), 0, 0);
+                r.v[0][s] = __builtin_amdgcn_raw_buffer_load_b128(r1, (int)(((unsigned)(mt * KS1 + s) * 64 + lane) * 16u), 0, 0);
                 r.idx[s] = __builtin_amdgcn_raw_buffer_load_b32(m1, (int)(((unsigned)(mt * p.Kp1 + (s >> 1)) * 64 + lane) * 4u), 0, 0);
             } else {
-                const unsigned off = ((unsigned)(mt * p.Ks1 + s) * 128 + lane) * 16u;
+                const unsigned off = ((unsigned)(mt * KS1 + s) * 128 + lane) * 16u;
                 r.v[0][s] = __builtin_amdgcn_raw_buffer_load_b128(r1, (int)off, 0, 0);
                 r.v[1][s] = __builtin_amdgcn_raw_buffer_load_b128(r1, (int)off, 1024, 0);
             }
@@ -1146,16 +1160,15 @@ void mlp_kernel(MlpParams p)
     };
     // the second layer's weights for this wave's output tiles and the 4 reduction steps of one chunk
     struct Row2 {
-        u32x4 v[SPARSE ? 1 : 2][kMlpTiles][4];
-        uint32_t idx[kMlpTiles][4];
+        u32x4 v[SPARSE ? 1 : 2][TILES][4];
+        uint32_t idx[TILES][4];
     };
     const int ntiles2 = p.Mt2 * 2;                        // output tiles of the second layer: (row tile, pixel half)
     auto load_row2 = [&](Row2 &r, int mc) {
 #pragma unroll
-        for (int ti = 0; ti < kMlpTiles; ti++) {
+        for (int ti = 0; ti < TILES; ti++) {
             const int t = wave + 4 * ti;
-            if (t >= ntiles2) break;                      // uniform
-            const int rt = t >> 1;
+            const int rt = min(t, ntiles2 - 1) >> 1;      // (a wave without a last tile repeats the last one's loads and drops the result)
 #pragma unroll
             for (int s = 0; s < 4; s++) {
                 const int ks = mc * 4 + s;
@@ -1174,50 +1187,64 @@ void mlp_kernel(MlpParams p)
     Row1 a1;
     Row2 a2;
     load_row1(a1, wave);
-    // ---- the input tile: 64 pixel rows of Cin channels, 16-byte vectors, zeros past the last pixel
+    // ---- the input tile: 64 pixel rows of Cin channels, 16-byte vectors, zeros past the last pixel (all loads on their way first)
     {
-        const int upr = p.Cin >> 3;                       // 16-byte units per row
-        for (int i = tid; i < BN * upr; i += 256) {
-            const int px = i / upr, u = i - px * upr;
-            const int pg = n0 + px;
-            u32x4 v = {0u, 0u, 0u, 0u};
-            if (pg < p.P) v = *reinterpret_cast<const u32x4 *>(p.x + (size_t)pg * p.Cin + u * 8);
-            *reinterpret_cast<u32x4 *>(Xs + px * XROW + u * 8) = v;
+        constexpr int UPR = KS1 * 4, IT = BN * UPR / 256; // 16-byte units per row, units per thread
+        u32x4 v[IT];
+#pragma unroll
+        for (int i = 0; i < IT; i++) {
+            const int u = tid + i * 256, pg = n0 + u / UPR;
+            v[i] = u32x4{0u, 0u, 0u, 0u};
+            if (pg < p.P) v[i] = *reinterpret_cast<const u32x4 *>(p.x + (size_t)n0 * p.Cin + u * 8);
         }
         for (int i = tid; i < p.Cmid; i += 256) b1s[i] = p.bias1 ? p.bias1[i] : 0.f;
-    }
-    // this workgroup's residual, in the output stage's thread -> (pixel, run) mapping: fetched now, used at the very end
-    u32x4 rres[kMlpTiles][2];
 #pragma unroll
-    for (int ti = 0; ti < kMlpTiles; ti++)
-#pragma unroll
-        for (int j = 0; j < 2; j++) {
-            const int t = wave + 4 * ti, it = lane + 64 * j;
-            const int pg = n0 + (t & 1) * 32 + (it >> 2);
-            rres[ti][j] = u32x4{0u, 0u, 0u, 0u};
-            if (p.res2 != nullptr && t < p.Mt2 * 2 && pg < p.P)
-                rres[ti][j] = *reinterpret_cast<const u32x4 *>(p.res2 + (size_t)pg * p.Cout2 + (t >> 1) * 32 + (it & 3) * 8);
+        for (int i = 0; i < IT; i++) {
+            const int u = tid + i * 256;
+            *reinterpret_cast<u32x4 *>(Xs + u / UPR * XROW + u % UPR * 8) = v[i];
         }
-    f32x16 acc2[kMlpTiles];
+    }
+    // the residual, in the output stage's thread -> (pixel, run) mapping: fetched during the last chunk
+    u32x4 rres[TILES][2];
+    auto load_res = [&]() {
 #pragma unroll
-    for (int ti = 0; ti < kMlpTiles; ti++)
+        for (int ti = 0; ti < TILES; ti++)
+#pragma unroll
+            for (int jj = 0; jj < 2; jj++) {
+                const int t = wave + 4 * ti, it = lane + 64 * jj;
+                const int pg = n0 + (t & 1) * 32 + (it >> 2);
+                rres[ti][jj] = u32x4{0u, 0u, 0u, 0u};
+                if (p.res2 != nullptr && t < ntiles2 && pg < p.P)
+                    rres[ti][jj] = *reinterpret_cast<const u32x4 *>(p.res2 + (size_t)pg * p.Cout2 + (t >> 1) * 32 + (it & 3) * 8);
+            }
+    };
+    f32x16 acc2[TILES];
+#pragma unroll
+    for (int ti = 0; ti < TILES; ti++)
 #pragma unroll
         for (int v = 0; v < 16; v++) acc2[ti][v] = 0.f;
     const float floor1 = p.act1 == SS_ACT_RELU ? 0.f : -__builtin_inff();
     __syncthreads();
 
     const int nchunks = p.Cmid / CH;
+    // Bound by the vector ALU: 154 M GELUs on the ConvNeXt-T stage-1 block at batch 128 are 63 us of its 120 (70 % of the SIMDs'
+    // cycles issue vector instructions).  The activation is chosen once, outside: a branch per element kept the evaluations from
+    // overlapping and cost 17 us (145 -> 128); the cheaper polynomial another 8.
+    auto chunks = [&](auto act1) {
     for (int mc = 0; mc < nchunks; mc++) {
-        load_row2(a2, mc);                                // in flight while the first contraction runs
         // ---- first contraction: rows 128*mc + 32*wave + [0,32) of the intermediate, all 64 pixels
-        f32x16 acc1[2];
+        f32x16 acc1[2];                                   // the bias starts in the accumulators
 #pragma unroll
-        for (int tn = 0; tn < 2; tn++)
+        for (int q = 0; q < 4; q++) {
+            const float4 bq1 = *reinterpret_cast<const float4 *>(b1s + (mc * 4 + wave) * 32 + 8 * q + 4 * g);
+            const float bv[4] = {bq1.x, bq1.y, bq1.z, bq1.w};
 #pragma unroll
-            for (int v = 0; v < 16; v++) acc1[tn][v] = 0.f;
+            for (int tn = 0; tn < 2; tn++)
 #pragma unroll
-        for (int s = 0; s < kMlpKs1; s++) {
-            if (s >= p.Ks1) break;                        // uniform
+                for (int e = 0; e < 4; e++) acc1[tn][4 * q + e] = bv[e];
+        }
+#pragma unroll
+        for (int s = 0; s < KS1; s++) {
 #pragma unroll
             for (int tn = 0; tn < 2; tn++) {
                 const uint16_t *src = Xs + (tn * 32 + c) * XROW + 32 * s + 16 * g;
@@ -1234,27 +1261,28 @@ void mlp_kernel(MlpParams p)
         }
 #pragma unroll
         for (int q = 0; q < 4; q++) {
-            const float4 bq1 = *reinterpret_cast<const float4 *>(b1s + (mc * 4 + wave) * 32 + 8 * q + 4 * g);
-            const float bv[4] = {bq1.x, bq1.y, bq1.z, bq1.w};
 #pragma unroll
             for (int tn = 0; tn < 2; tn++) {
                 float r[4];
 #pragma unroll
                 for (int e = 0; e < 4; e++) {
-                    const float z = acc1[tn][4 * q + e] + bv[e];
-                    r[e] = p.act1 == SS_ACT_GELU ? gelu_erfc(z) : (z < floor1 ? 0.f : z);
+                    r[e] = act1(acc1[tn][4 * q + e]);
                 }
                 *reinterpret_cast<uint2 *>(Cs + (tn * 32 + c) * CROW + wave * 32 + 8 * q + 4 * g) =
                     make_uint2(cvt_pack2<DT>(r[0], r[1]), cvt_pack2<DT>(r[2], r[3]));
             }
+            __builtin_amdgcn_sched_barrier(0);            // eight evaluations overlap; more at once cost a wave per SIMD in registers
         }
-        if (mc + 1 < nchunks) load_row1(a1, (mc + 1) * 4 + wave);       // (its registers are free) in flight while the second contraction runs
-        __syncthreads();
+        // (issued here, when the first contraction's accumulators are dead: four waves per SIMD hide the latency better than an
+        // earlier issue at three)
+        load_row2(a2, mc);
+        if (mc + 1 < nchunks) load_row1(a1, (mc + 1) * 4 + wave);       // in flight while the second contraction runs
+        else load_res();
+        lds_barrier();
         // ---- second contraction: this chunk's 128 intermediate channels into the output accumulators
 #pragma unroll
-        for (int ti = 0; ti < kMlpTiles; ti++) {
+        for (int ti = 0; ti < TILES; ti++) {
             const int t = wave + 4 * ti;
-            if (t >= ntiles2) break;                      // uniform
             const int ct = t & 1;
 #pragma unroll
             for (int s = 0; s < 4; s++) {
@@ -1272,15 +1300,19 @@ void mlp_kernel(MlpParams p)
                 }
             }
         }
-        __syncthreads();                                  // the chunk buffer is free again
+        lds_barrier();                                    // the chunk buffer is free again
     }
+    };
+    if (p.act1 == SS_ACT_GELU) chunks([](float z) { return gelu_cdf(z); });
+    else chunks([floor1](float z) { return floor_at(z, floor1); });
 
     // ---- output: bias + residual + activation in fp32, one rounding; each 32 x 32 tile crosses the wave's own LDS region
     // (the input tile and the chunk buffer are dead: the loop ended with a barrier) and leaves as 16-byte runs
     float *reg = reinterpret_cast<float *>(smem) + wave * (32 * kFuseRow);
     const float floor2 = p.act2 == SS_ACT_RELU ? 0.f : -__builtin_inff();
+    auto finish = [&](auto act2) {
 #pragma unroll
-    for (int ti = 0; ti < kMlpTiles; ti++) {
+    for (int ti = 0; ti < TILES; ti++) {
         const int t = wave + 4 * ti;
         if (t >= ntiles2) break;                          // uniform
         const int rt = t >> 1, ct = t & 1;
@@ -1310,14 +1342,14 @@ void mlp_kernel(MlpParams p)
             uint32_t w[4];
 #pragma unroll
             for (int e = 0; e < 4; e++) {
-                float a = v[2 * e], b = v[2 * e + 1];
-                if (p.act2 == SS_ACT_GELU) { a = gelu_erfc(a); b = gelu_erfc(b); }
-                else { a = a < floor2 ? 0.f : a; b = b < floor2 ? 0.f : b; }
-                w[e] = cvt_pack2<DT>(a, b);
+                w[e] = cvt_pack2<DT>(act2(v[2 * e]), act2(v[2 * e + 1]));
             }
             *reinterpret_cast<uint4 *>(p.y2 + (size_t)pg * p.Cout2 + o) = make_uint4(w[0], w[1], w[2], w[3]);
         }
     }
+    };
+    if (p.act2 == SS_ACT_GELU) finish([](float z) { return gelu_cdf(z); });
+    else finish([floor2](float z) { return floor_at(z, floor2); });
 }
 
 template <int DT, bool SPARSE>
@@ -1328,8 +1360,20 @@ static int launch_mlp(const MlpParams &p, hipStream_t s)
     size_t smem = (size_t)64 * (p.Cin + 8) * 2 + (size_t)64 * (128 + 4) * 2 + (size_t)p.Cmid * 4;
     const size_t epi = 4 * kFuseRegion;
     if (smem < epi) smem = epi;
-    mlp_kernel<DT, SPARSE><<<dim3((unsigned)blocks), dim3(256), smem, s>>>(p);
-    return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP;
+    auto go = [&](auto ks1) {
+        constexpr int KS1 = decltype(ks1)::value;
+        if (p.Mt2 <= 2) mlp_kernel<DT, SPARSE, KS1, 1><<<dim3((unsigned)blocks), dim3(256), smem, s>>>(p);
+        else mlp_kernel<DT, SPARSE, KS1, 2><<<dim3((unsigned)blocks), dim3(256), smem, s>>>(p);
+        return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP;
+    };
+    using std::integral_constant;
+    switch (p.Ks1) {
+        case 1: return go(integral_constant<int, 1>{});
+        case 2: return go(integral_constant<int, 2>{});
+        case 3: return go(integral_constant<int, 3>{});
+        case 4: return go(integral_constant<int, 4>{});
+        default: return SS_ERR_UNSUPPORTED;
+    }
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -29,15 +29,6 @@ namespace ss {
 #define SS_STREAM_PACE 0      // s_sleep argument (units of 64 clocks) between a producer thread's load / LDS-write pairs; 0 = none
 #endif
 
-// Workgroup barrier that orders LDS traffic only: the waves' outstanding global loads (weight ring, staging loads)
-// and stores (output tile) stay in flight across it.
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 template <int TN>
 struct StreamShape {
     static constexpr int TAPS = 9, KSTEPS = 9, BK = 288, ROW = 288;      // a chunk = 32 channels x 9 taps, unpadded swizzled rows
@@ -358,7 +349,7 @@ void conv3x3_stream_kernel(ConvParams p, int tiles_n, int slots_n)
             }
         }
         const int n0 = (nslot + it * slots_n) * BN;
-        if (p.act == SS_ACT_GELU) write_tile(n0, [](float v) { return gelu_erfc(v); });
+        if (p.act == SS_ACT_GELU) write_tile(n0, [](float v) { return gelu_cdf(v); });
         else write_tile(n0, [&](float v) { return floor_at(v, relu_floor); });     // ReLU, or the identity with a floor of -inf (a NaN passes)
         init_acc();
     }
