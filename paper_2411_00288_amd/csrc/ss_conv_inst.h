@@ -18,20 +18,30 @@ int SS_CAT(conv_dispatch_, SS_INST_NAME)(const ss_weight_desc *desc, const ConvP
         const int st = small_mode<SS_INST_DT, SS_INST_SPARSE>(desc, p, forced_tile() < 0 ? -1 : forced_tile() - 20, s);
         if (st != SS_ERR_INVALID_ARG) return st;
     }
-    if constexpr (!is_byte_type(SS_INST_DT)) {
+    if constexpr (!is_byte_type(SS_INST_DT) || SS_INST_SPARSE) {
         if (p.nsplit <= 1 && stream_eligible(desc, p)) {
             int ncu = compute_units();
             if (ncu <= 0) return SS_ERR_HIP;
             if (block_limit() > 0 && block_limit() < ncu) ncu = block_limit();
             const int forced = forced_tile();
-            // The resident-grid kernel pays where every compute unit gets at least two of its 256 x 128 tiles (measured:
-            // 16-20 % faster than the one-tile kernels at three tiles per compute unit, slower at one) and the 256-row
-            // tile is mostly filled.
-            const long long tiles = (long long)((p.Cout + 255) / 256) * (((long long)p.P + 127) / 128);
-            const bool pays = p.Cout % 256 == 0 || p.Cout % 256 >= 192;
-            if (forced == 10 || (forced < 0 && pays && tiles >= 2ll * ncu))
+            // Two pixel-tile widths: 128 pixels make the cheapest step, 64 waste less of the last round.  A workgroup takes
+            // its tiles one after the other, so the time goes with the rounds of the fullest compute unit; a round of the
+            // narrow tile measured 0.59 of a wide one (256 -> 256 on N 14x14 images, f16: N = 125, rounds 1 / 3, 20.4 / 24.9
+            // us; 200, 2 / 3, 37.2 / 35.8; 500, 3 / 6, 60.9 / 69.7).
+            // Against the one-tile-per-workgroup kernels: faster as soon as the narrow grid fills more than half of the
+            // compute units (256 -> 256, N = 50, 154 tiles: 12.6 against 13.0 us, fp8 N = 64: 9.4 / 9.8; N = 40, 123 tiles:
+            // 12.3 / 10.3), provided the 256-row tiles are not mostly padding: more than half filled on average with 16-bit
+            // operands (128 -> 144 on fifty 28x28: 20.1 against 24.0 us, 128 -> 288: 32.2 / 35.0; 96 -> 320: 54.6 / 66.2),
+            // three quarters with 8-bit ones, whose steps are half as long (128 -> 288, int8: 11.5 / 9.5; 256 -> 128, fp8:
+            // 69 / 54).
+            const long long rows = (p.Cout + 255) / 256, wide = ((long long)p.P + 127) / 128, narrow = ((long long)p.P + 63) / 64;
+            const long long slots = ncu > rows ? ncu / rows : 1;          // pixel tiles of one round, as the launch deals them out
+            const long long rounds_w = (wide + slots - 1) / slots, rounds_n = (narrow + slots - 1) / slots;
+            const bool filled = is_byte_type(SS_INST_DT) ? 4ll * p.Cout >= 3 * 256 * rows : 2ll * p.Cout > 256 * rows;
+            const bool pays = filled && 2 * rows * narrow > ncu;
+            if (forced == 10 || (forced < 0 && pays && 100 * rounds_w <= 59 * rounds_n))
                 return launch_stream<SS_INST_DT, SS_INST_SPARSE, 2, 4>(p, ncu, s);
-            if (forced == 11) return launch_stream<SS_INST_DT, SS_INST_SPARSE, 2, 2>(p, ncu, s);
+            if (forced == 11 || (forced < 0 && pays)) return launch_stream<SS_INST_DT, SS_INST_SPARSE, 2, 2>(p, ncu, s);
         }
     }
     if constexpr (!is_byte_type(SS_INST_DT)) {

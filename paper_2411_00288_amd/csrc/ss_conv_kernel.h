@@ -210,6 +210,41 @@ constexpr bool is_vec(int mode) { return mode == MODE_VEC || mode == MODE_VEC8; 
 constexpr bool is_taps(int mode) { return mode == MODE_TAPS || mode == MODE_TAPSR; }
 constexpr bool is_pw(int mode) { return mode == MODE_PW || mode == MODE_PW2 || mode == MODE_PWR; }
 
+// One 16-byte vector v of a tap-transposed unit: [tap][8 channels] -> [channel][tap] (8-bit operands: 16 channels), see MODE_TAPS.
+template <bool Q8, bool RAG, int TAPS>
+__device__ __forceinline__ u32x4 taps_vector(const u32x4 (&t)[TAPS], int v, bool half)
+{
+    u32x4 w;
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const int d = 4 * v + q;
+        if constexpr (Q8) {
+            uint32_t src[4], pick[4];
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const int h = 4 * d + e, c = h / TAPS, tp = h % TAPS;
+                src[e] = t[tp][c >> 2];
+                pick[e] = (uint32_t)(c & 3);
+            }
+            const uint32_t p01 = __builtin_amdgcn_perm(src[1], src[0], pick[0] | ((4u + pick[1]) << 8));
+            const uint32_t p23 = __builtin_amdgcn_perm(src[3], src[2], pick[2] | ((4u + pick[3]) << 8));
+            w[q] = __builtin_amdgcn_perm(p23, p01, 0x05040100u);
+        } else {
+            const int ha = 2 * d, hb = 2 * d + 1;
+            const int ca = ha / TAPS, ta = ha % TAPS, cb = hb / TAPS, tb = hb % TAPS;
+            uint32_t sa = t[ta][ca >> 1], sb = t[tb][cb >> 1];
+            if constexpr (RAG) {
+                sa = half ? (ca >= 4 ? 0u : t[ta][2 + (ca >> 1 & 1)]) : sa;
+                sb = half ? (cb >= 4 ? 0u : t[tb][2 + (cb >> 1 & 1)]) : sb;
+            }
+            const uint32_t sel = (uint32_t)(2 * (ca & 1)) | ((uint32_t)(2 * (ca & 1) + 1) << 8) |
+                                 ((uint32_t)(4 + 2 * (cb & 1)) << 16) | ((uint32_t)(5 + 2 * (cb & 1)) << 24);
+            w[q] = __builtin_amdgcn_perm(sb, sa, sel);
+        }
+    }
+    return w;
+}
+
 // Weight fragments of one 32-wide reduction step for the TM row tiles of a wave.
 template <bool SPARSE, int TM>
 struct AStep {
@@ -565,45 +600,7 @@ void conv_kernel(ConvParams p)
 #pragma unroll
                 for (int v = 0; v < TAPS; v++) {
                     if (v < j * TAPS / n || v >= (j + 1) * TAPS / n) continue;
-                    uint32_t o[4];
-                    if constexpr (Q8) {
-                        // bytes: [tap][16 channels] -> [channel][tap]; output byte h = c*TAPS + tap, four per dword, each
-                        // from its own tap's vector: two byte pairs are picked first, then joined
-#pragma unroll
-                        for (int q = 0; q < 4; q++) {
-                            const int d = 4 * v + q;
-                            uint32_t src[4], pick[4];
-#pragma unroll
-                            for (int e = 0; e < 4; e++) {
-                                const int h = 4 * d + e, c = h / TAPS, t = h % TAPS;
-                                src[e] = stage_t[i][t][c >> 2];
-                                pick[e] = (uint32_t)(c & 3);
-                            }
-                            const uint32_t p01 = __builtin_amdgcn_perm(src[1], src[0], pick[0] | ((4u + pick[1]) << 8));
-                            const uint32_t p23 = __builtin_amdgcn_perm(src[3], src[2], pick[2] | ((4u + pick[3]) << 8));
-                            o[q] = __builtin_amdgcn_perm(p23, p01, 0x05040100u);
-                        }
-                        u32x4 w = {o[0], o[1], o[2], o[3]};
-                        rowp[(vec0 + v) ^ swz] = w;
-                        continue;
-                    }
-#pragma unroll
-                    for (int q = 0; q < 4; q++) {
-                        const int d = 4 * v + q;
-                        const int ha = 2 * d, hb = 2 * d + 1;
-                        const int ca = ha / TAPS, ta = ha % TAPS, cb = hb / TAPS, tb = hb % TAPS;
-                        uint32_t sa = stage_t[i][ta][ca >> 1];
-                        uint32_t sb = stage_t[i][tb][cb >> 1];
-                        if constexpr (MODE == MODE_TAPSR) {
-                            sa = half_[set] ? (ca >= 4 ? 0u : stage_t[i][ta][2 + (ca >> 1 & 1)]) : sa;
-                            sb = half_[set] ? (cb >= 4 ? 0u : stage_t[i][tb][2 + (cb >> 1 & 1)]) : sb;
-                        }
-                        const uint32_t sel = (uint32_t)(2 * (ca & 1)) | ((uint32_t)(2 * (ca & 1) + 1) << 8) |
-                                             ((uint32_t)(4 + 2 * (cb & 1)) << 16) | ((uint32_t)(5 + 2 * (cb & 1)) << 24);
-                        o[q] = __builtin_amdgcn_perm(sb, sa, sel);
-                    }
-                    u32x4 w = {o[0], o[1], o[2], o[3]};
-                    rowp[(vec0 + v) ^ swz] = w;
+                    rowp[(vec0 + v) ^ swz] = taps_vector<Q8, MODE == MODE_TAPSR, TAPS>(stage_t[i], v, MODE == MODE_TAPSR && half_[set]);
                 }
             } else {
                 if (i < j * ITEMS / n || i >= (j + 1) * ITEMS / n) continue;

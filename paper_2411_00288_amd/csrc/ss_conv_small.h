@@ -21,41 +21,6 @@ namespace ss {
 enum { SMALL_PW = 0, SMALL_RSC = 1, SMALL_TAPS = 2, SMALL_TAPSR = 3 };      // (TAPSR: cin % 32 != 0, as MODE_TAPSR)
 constexpr bool small_taps(int mode) { return mode == SMALL_TAPS || mode == SMALL_TAPSR; }
 
-// One 16-byte vector v of a tap-transposed unit: [tap][8 channels] -> [channel][tap] (8-bit operands: 16 channels), see MODE_TAPS.
-template <bool Q8, bool RAG, int TAPS>
-__device__ __forceinline__ u32x4 taps_vector(const u32x4 (&t)[TAPS], int v, bool half)
-{
-    u32x4 w;
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-        const int d = 4 * v + q;
-        if constexpr (Q8) {
-            uint32_t src[4], pick[4];
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-                const int h = 4 * d + e, c = h / TAPS, tp = h % TAPS;
-                src[e] = t[tp][c >> 2];
-                pick[e] = (uint32_t)(c & 3);
-            }
-            const uint32_t p01 = __builtin_amdgcn_perm(src[1], src[0], pick[0] | ((4u + pick[1]) << 8));
-            const uint32_t p23 = __builtin_amdgcn_perm(src[3], src[2], pick[2] | ((4u + pick[3]) << 8));
-            w[q] = __builtin_amdgcn_perm(p23, p01, 0x05040100u);
-        } else {
-            const int ha = 2 * d, hb = 2 * d + 1;
-            const int ca = ha / TAPS, ta = ha % TAPS, cb = hb / TAPS, tb = hb % TAPS;
-            uint32_t sa = t[ta][ca >> 1], sb = t[tb][cb >> 1];
-            if constexpr (RAG) {
-                sa = half ? (ca >= 4 ? 0u : t[ta][2 + (ca >> 1 & 1)]) : sa;
-                sb = half ? (cb >= 4 ? 0u : t[tb][2 + (cb >> 1 & 1)]) : sb;
-            }
-            const uint32_t sel = (uint32_t)(2 * (ca & 1)) | ((uint32_t)(2 * (ca & 1) + 1) << 8) |
-                                 ((uint32_t)(4 + 2 * (cb & 1)) << 16) | ((uint32_t)(5 + 2 * (cb & 1)) << 24);
-            w[q] = __builtin_amdgcn_perm(sb, sa, sel);
-        }
-    }
-    return w;
-}
-
 // Workgroups of a problem.
 static inline long long small_blocks(const ConvParams &p, int px, int tm)
 {

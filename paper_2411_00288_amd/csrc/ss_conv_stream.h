@@ -37,10 +37,10 @@ struct StreamShape {
     static constexpr size_t stage_bytes = (size_t)2 * BN * ROW * 2;
     static constexpr size_t slab_bytes = (size_t)4 * 32 * SLAB_ROW * 2;
 };
-template <int TM, int TN>
+template <int DT, int TM, int TN>
 constexpr size_t stream_smem_bytes()
 {
-    return StreamShape<TN>::stage_bytes + StreamShape<TN>::slab_bytes + (size_t)(128 * TM) * 4;
+    return StreamShape<TN>::stage_bytes + StreamShape<TN>::slab_bytes + (size_t)(128 * TM) * (is_byte_type(DT) ? 8 : 4);      // bias, and scale
 }
 
 template <int DT, bool SPARSE, int TM, int TN>
@@ -49,16 +49,18 @@ void conv3x3_stream_kernel(ConvParams p, int tiles_n, int slots_n)
 {
     using SH = StreamShape<TN>;
     constexpr int BM = 128 * TM, BN = SH::BN, ROW = SH::ROW, TAPS = 9, KSTEPS = 9;
+    constexpr bool Q8 = is_byte_type(DT);            // 8-bit operands: chunks of 64 channels in the same bytes, full index words, scaled tail
+    static_assert(SPARSE || !Q8, "the 8-bit twins stay with the tiled kernels");
     constexpr int FR = KSTEPS * TN;                  // activation fragments per chunk
     constexpr int RB = 6, D = 4;                     // activation-fragment ring: slots, prefetch distance (fragments)
     constexpr int AF = KSTEPS * TM;                  // weight fragments per chunk
-    constexpr int RA = SPARSE ? (TM == 2 ? 9 : 3) : (TM == 2 ? 6 : 3);     // weight-fragment ring slots
+    constexpr int RA = SPARSE ? (TM == 2 ? (Q8 ? 6 : 9) : 3) : (TM == 2 ? 6 : 3);     // weight-fragment ring slots
     static_assert(FR % RB == 0 && AF % RA == 0 && D < RB && D < FR, "rings must nest with the chunk");
     static_assert(TM == 1 || TM == 2, "one or two row tiles per wave");
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
     uint16_t *const Bs0 = smem, *const Bs1 = smem + BN * ROW;
     uint16_t *slab_all = smem + 2 * BN * ROW;
-    float *bias_s = reinterpret_cast<float *>(slab_all + 4 * 32 * SH::SLAB_ROW);
+    float *bias_s = reinterpret_cast<float *>(slab_all + 4 * 32 * SH::SLAB_ROW), *scale_s = bias_s + BM;      // (scale: 8-bit operands)
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -119,23 +121,11 @@ void conv3x3_stream_kernel(ConvParams p, int tiles_n, int slots_n)
         auto load_one = [&](int set, int i, int tap) {      // set, i, tap: compile time at every call site
             st[set][i][tap] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)tapoff[i][tap], gen_c * 64, 0);
         };
-        // One transposed 16-byte vector: [tap][8 channels] -> [channel][tap], output element h = c*9 + tap, two per dword.
         auto store_one = [&](uint16_t *buf, int set, int i, int v) {
             const int pr = pr0 + i * 64;
             u32x4 *rowp = reinterpret_cast<u32x4 *>(buf + pr * ROW);
             const int vec0 = unit * TAPS, swz = (pr >> 2) & 3;
-            uint32_t o[4];
-#pragma unroll
-            for (int q = 0; q < 4; q++) {
-                const int d = 4 * v + q;
-                const int ha = 2 * d, hb = 2 * d + 1;
-                const int ca = ha / TAPS, ta = ha % TAPS, cb = hb / TAPS, tb = hb % TAPS;
-                const uint32_t sa = st[set][i][ta][ca >> 1], sb = st[set][i][tb][cb >> 1];
-                const uint32_t sel = (uint32_t)(2 * (ca & 1)) | ((uint32_t)(2 * (ca & 1) + 1) << 8) |
-                                     ((uint32_t)(4 + 2 * (cb & 1)) << 16) | ((uint32_t)(5 + 2 * (cb & 1)) << 24);
-                o[q] = __builtin_amdgcn_perm(sb, sa, sel);
-            }
-            const u32x4 w = {o[0], o[1], o[2], o[3]};
+            const u32x4 w = taps_vector<Q8, false, TAPS>(st[set][i], v, false);
             rowp[(vec0 + v) ^ swz] = w;
         };
         auto load = [&](int set) {
@@ -214,7 +204,7 @@ void conv3x3_stream_kernel(ConvParams p, int tiles_n, int slots_n)
         const int tm = j % TM;
         if constexpr (SPARSE) {
             f.v[0] = __builtin_amdgcn_raw_buffer_load_b128(ra, (int)a_lane, a_tile[tm] + ks * 1024, 0);
-            f.idx = __builtin_amdgcn_raw_buffer_load_b32(rm, (int)m_lane, m_tile[tm] + (ks >> 1) * 256, 0);
+            f.idx = __builtin_amdgcn_raw_buffer_load_b32(rm, (int)m_lane, m_tile[tm] + (Q8 ? ks : ks >> 1) * 256, 0);
         } else {
             f.v[0] = __builtin_amdgcn_raw_buffer_load_b128(ra, (int)a_lane, a_tile[tm] + ks * 2048, 0);
             f.v[1] = __builtin_amdgcn_raw_buffer_load_b128(ra, (int)a_lane, a_tile[tm] + ks * 2048 + 1024, 0);
@@ -231,12 +221,13 @@ void conv3x3_stream_kernel(ConvParams p, int tiles_n, int slots_n)
         f.hi = *reinterpret_cast<const u32x4 *>(src + frag_hi);
     };
     Acc<DT> acc[TM][TN];
-    auto init_acc = [&]() {                           // the bias goes in first: rows 8q + 4(lane / 32) + e of each row tile
+    auto init_acc = [&]() {                           // the bias goes in first (8-bit operands: with the scale at the end): rows 8q + 4(lane / 32) + e of each row tile
 #pragma unroll
         for (int tm = 0; tm < TM; tm++)
 #pragma unroll
             for (int q = 0; q < 4; q++) {
-                const float4 bq = *reinterpret_cast<const float4 *>(bias_s + (wave * TM + tm) * 32 + 8 * q + 4 * (lane >> 5));
+                float4 bq = make_float4(0.f, 0.f, 0.f, 0.f);
+                if constexpr (!Q8) bq = *reinterpret_cast<const float4 *>(bias_s + (wave * TM + tm) * 32 + 8 * q + 4 * (lane >> 5));
 #pragma unroll
                 for (int tn = 0; tn < TN; tn++) {
                     acc[tm][tn][4 * q + 0] = bq.x; acc[tm][tn][4 * q + 1] = bq.y;
@@ -246,7 +237,7 @@ void conv3x3_stream_kernel(ConvParams p, int tiles_n, int slots_n)
     };
     uint16_t *slab = slab_all + wave * 32 * SH::SLAB_ROW;
     const float relu_floor = p.act == SS_ACT_RELU ? 0.f : -__builtin_inff();
-    constexpr int ODT = DT;
+    constexpr int ODT = out_type<DT>();
     // Output: raw buffer stores whose range check does the pixel tail (a pixel past the last lies past the buffer's
     // end); rows past the last output channel get an out-of-range offset.
     const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, (int)((unsigned)p.P * (unsigned)p.Cout * 2u), kRsrcFlags);
@@ -269,8 +260,15 @@ void conv3x3_stream_kernel(ConvParams p, int tiles_n, int slots_n)
 #pragma unroll
             for (int q = 0; q < 4; q++) {
                 float r[4];
+                if constexpr (Q8) {
+                    const int row = (wave * TM + tm) * 32 + 8 * q + 4 * (lane >> 5);
+                    const f32x4 sq = *reinterpret_cast<const f32x4 *>(scale_s + row), bq = *reinterpret_cast<const f32x4 *>(bias_s + row);
 #pragma unroll
-                for (int e = 0; e < 4; e++) r[e] = actf(acc[tm][tn][4 * q + e]);
+                    for (int e = 0; e < 4; e++) r[e] = actf((float)acc[tm][tn][4 * q + e] * sq[e] + bq[e]);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; e++) r[e] = actf(acc[tm][tn][4 * q + e]);
+                }
                 *reinterpret_cast<uint2 *>(slab + (lane & 31) * SH::SLAB_ROW + 8 * q + 4 * (lane >> 5)) =
                     make_uint2(cvt_pack2<ODT>(r[0], r[1]), cvt_pack2<ODT>(r[2], r[3]));
             }
@@ -306,7 +304,10 @@ void conv3x3_stream_kernel(ConvParams p, int tiles_n, int slots_n)
         load_a(a[j], 0, j);
         __builtin_amdgcn_sched_barrier(0);
     }
-    for (int i = tid; i < BM; i += 256) bias_s[i] = (p.bias != nullptr && m0 + i < p.Cout) ? p.bias[m0 + i] : 0.f;
+    for (int i = tid; i < BM; i += 256) {
+        bias_s[i] = (p.bias != nullptr && m0 + i < p.Cout) ? p.bias[m0 + i] : 0.f;
+        if constexpr (Q8) scale_s[i] = (p.scale != nullptr && m0 + i < p.Cout) ? p.scale[m0 + i] : 1.f;
+    }
     lds_barrier();                                    // barrier 0: chunk 0 is in LDS
     init_acc();
 #pragma unroll
@@ -337,7 +338,7 @@ void conv3x3_stream_kernel(ConvParams p, int tiles_n, int slots_n)
                     for (int tm = 0; tm < TM; tm++) {
                         const AFrag &af = a[(s * TM + tm) % RA];
                         if constexpr (SPARSE) {
-                            const uint32_t idx = af.idx >> ((s & 1) ? 16 - par : par);
+                            const uint32_t idx = Q8 ? af.idx : af.idx >> ((s & 1) ? 16 - par : par);
                             acc[tm][tn] = mma_sparse<DT>(af.v[0], b[f % RB], acc[tm][tn], idx);
                         } else {
                             acc[tm][tn] = mma_dense<DT>(af.v[0], b[f % RB].lo, acc[tm][tn]);
@@ -360,7 +361,7 @@ template <int DT, bool SPARSE, int TM, int TN>
 static int launch_stream(const ConvParams &p0, int max_blocks, hipStream_t s)
 {
     constexpr int BM = 128 * TM, BN = 32 * TN;
-    constexpr size_t smem = stream_smem_bytes<TM, TN>();
+    constexpr size_t smem = stream_smem_bytes<DT, TM, TN>();
     static_assert(smem <= 160 * 1024, "LDS tile too large");
     ConvParams p = p0;
     p.tiles_m = (p.Cout + BM - 1) / BM;
@@ -384,12 +385,12 @@ static int launch_stream(const ConvParams &p0, int max_blocks, hipStream_t s)
     return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP;
 }
 
-// Can the streaming kernel take this problem?  3x3 kernel in the channel-slowest flattening, 16-bit operands, whole
-// chunks (cin % 32 == 0), 16-byte output runs (cout % 8 == 0), no residual, output below 2 GiB (32-bit store offsets,
+// Can the streaming kernel take this problem?  3x3 kernel in the channel-slowest flattening, whole chunks (cin % 32 == 0, 8-bit
+// operands cin % 64 == 0), 16-byte output runs (cout % 8 == 0), no residual, output below 2 GiB (32-bit store offsets,
 // with room for the offsets of a last tile's pixels past the end to stay below the out-of-range mark).
 static inline bool stream_eligible(const ss_weight_desc *desc, const ConvParams &p)
 {
-    return !is_byte_type(desc->dtype) && desc->korder == SS_K_CRS && desc->kh == 3 && desc->kw == 3 && desc->cin % 32 == 0 &&
+    return desc->korder == SS_K_CRS && desc->kh == 3 && desc->kw == 3 && p.Cin % 32 == 0 &&
            desc->cout % 8 == 0 && p.residual == nullptr && (long long)p.P * p.Cout * 2 < (1ll << 31) - (1ll << 27);
 }
 

@@ -7,6 +7,8 @@ import numpy as np
 import pytest
 
 from paper_2411_00288_amd import workloads as wl
+import test_gpu_f8
+import test_gpu_q8
 from helpers import check_close, oracle_ref, run_gpu
 
 pytestmark = pytest.mark.gpu
@@ -62,3 +64,24 @@ def test_stream_kernel_without_bias(ss, force_tile, limit_blocks):
     force_tile(10)
     limit_blocks(2)
     check_close(run_gpu(ss, L, d, sparse=True, bias=False), ref, "no bias")
+
+
+BYTE_SHAPES = [
+    _L(2, 15, 13, 192, 136, s=2, dtype=wl.I8, seed=1),        # 3 chunks of 64 channels, one ragged row tile, 112 pixels: a ragged tile
+    _L(3, 14, 14, 128, 264, dtype=wl.I8, seed=2),             # two row tiles (the second nearly empty), 588 pixels
+    _L(5, 9, 11, 64, 520, p=0, dtype=wl.F8, act=wl.ACT_GELU, seed=4),    # a single chunk per tile, three row tiles, no padding
+    _L(2, 14, 14, 256, 256, dtype=wl.F8, act=wl.ACT_NONE, seed=3),
+]
+
+
+@pytest.mark.parametrize("cap", [None, 3])
+@pytest.mark.parametrize("tile", STREAM_TILES)
+@pytest.mark.parametrize("L", BYTE_SHAPES, ids=lambda L: L.name)
+def test_stream_kernels_take_byte_operands(ss, force_tile, limit_blocks, L, tile, cap):
+    q8 = L.dtype == wl.I8
+    d = wl.make_inputs_q8(L) if q8 else wl.make_inputs_f8(L)
+    ref = (test_gpu_q8 if q8 else test_gpu_f8)._ref(L, d)
+    force_tile(tile)
+    limit_blocks(cap)
+    y = (test_gpu_q8 if q8 else test_gpu_f8)._run(ss, L, d, sparse=True)
+    (test_gpu_q8.check_q8 if q8 else check_close)(y, ref, f"{L.name} tile {tile} cap {cap}")
