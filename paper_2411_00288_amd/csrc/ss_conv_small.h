@@ -18,7 +18,8 @@
 
 namespace ss {
 
-enum { SMALL_PW = 0, SMALL_RSC = 1, SMALL_TAPS = 2, SMALL_TAPSR = 3 };      // (TAPSR: cin % 32 != 0, as MODE_TAPSR)
+// (RSCW: cin % 32 == 0, a reduction step lies in one tap; TAPSR: cin % 32 != 0, as MODE_TAPSR)
+enum { SMALL_PW = 0, SMALL_RSC = 1, SMALL_TAPS = 2, SMALL_TAPSR = 3, SMALL_RSCW = 4 };
 constexpr bool small_taps(int mode) { return mode == SMALL_TAPS || mode == SMALL_TAPSR; }
 
 // Workgroups of a problem.
@@ -36,14 +37,13 @@ constexpr size_t small_wave_lds()
 }
 
 // PX: pixels of a tile (32, or 16: half of the matrix instruction's columns stay empty, and twice as many workgroups share
-// the loads, which is what bounds a grid far below the chip's size).  NW: waves.
-template <int DT, bool SPARSE, int MODE, int KH, int KW, int PX, int TM, int NW>
+// the loads, which is what bounds a grid far below the chip's size).  NW: waves.  RING: reduction steps in flight per wave (direct modes).
+template <int DT, bool SPARSE, int MODE, int KH, int KW, int PX, int TM, int NW, int RING>
 __global__ __launch_bounds__(NW * 64) void conv_small_kernel(ConvParams p)
 {
     constexpr bool Q8 = is_byte_type(DT);
     constexpr int ODT = out_type<DT>();
     constexpr int TAPS = KH * KW;
-    constexpr int RING = NW > 8 ? 4 : 8;                  // direct: reduction steps in flight per wave (16 waves: 128 registers each)
     constexpr bool SWZ = TAPS == 9;                       // LDS row layout of the tap modes (see ChunkShape::SWZ; 2x2 rows are 16 vectors, XOR-ed with the whole row number)
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
     const int tid = threadIdx.x;
@@ -57,6 +57,59 @@ __global__ __launch_bounds__(NW * 64) void conv_small_kernel(ConvParams p)
     const int n0 = tile_n * PX;
     const int HoWo = p.Ho * p.Wo;
 
+    // What the finished quads need from memory, fetched ahead of everything else: behind the reduction these loads would be a second
+    // memory latency.  Consecutive threads finish the tile's channels of a pixel.
+    const float floor = p.act == SS_ACT_RELU ? 0.f : -__builtin_inff();
+    const bool four = (p.Cout & 3) == 0;
+    constexpr int QUADS = PX * 8 * TM, QIT = (QUADS + NW * 64 - 1) / (NW * 64);      // quads of channels in the tile, per thread
+    struct Tail {
+        unsigned bias[4], scale[4], res[2];
+    };
+    auto quad = [&](int t, int *pl, int *cq, int *pg, int *o) {
+        *pl = t / (8 * TM);                               // pixel, quad of channels: accumulators 4*(cq/2).. of lane group cq%2
+        *cq = t % (8 * TM);
+        *pg = n0 + *pl;
+        *o = mt * 32 + *cq * 4;
+        return (QUADS % (NW * 64) == 0 || t < QUADS) && *pg < p.P && *o < p.Cout;
+    };
+    auto vector_of = [&](const void *v, size_t bytes) {  // (an absent vector: no bytes, every load gives zero)
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(v), 0, v != nullptr ? (int)bytes : 0, kRsrcFlags);
+    };
+    Tail tail[QIT];
+    constexpr bool EARLY = !(small_taps(MODE) && TM == 2);      // (those hold 254 registers already: they fetch before the last barrier)
+    auto fetch_tail = [&]() {
+        const __amdgpu_buffer_rsrc_t rb = vector_of(p.bias, (size_t)p.Cout * 4), rs = vector_of(p.scale, (size_t)p.Cout * 4);
+        const __amdgpu_buffer_rsrc_t rr = vector_of(p.residual, (size_t)p.P * p.Cout * 2);
+#pragma unroll
+        for (int i = 0; i < QIT; i++) {
+            int pl, cq, pg, o;
+            const bool in = quad(tid + i * NW * 64, &pl, &cq, &pg, &o);
+            const unsigned vb = in ? (unsigned)o * 4u : kOutOfRange;
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                tail[i].bias[e] = __builtin_amdgcn_raw_buffer_load_b32(rb, (int)(vb + 4u * e), 0, 0);
+                if constexpr (Q8) tail[i].scale[e] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(vb + 4u * e), 0, 0);
+            }
+            if constexpr (!Q8) {
+                const unsigned vr = in ? ((unsigned)pg * p.Cout + o) * 2u : kOutOfRange;      // (the launch keeps outputs below 2 GiB)
+                tail[i].res[0] = tail[i].res[1] = 0u;
+                if (p.residual != nullptr) {              // uniform
+                    if (four) {
+                        const auto u = __builtin_amdgcn_raw_buffer_load_b64(rr, (int)vr, 0, 0);
+                        tail[i].res[0] = u[0]; tail[i].res[1] = u[1];
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; e++) {     // (past the row's end: never used)
+                            const unsigned h = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rr, (int)(vr + 2u * e), 0, 0);
+                            tail[i].res[e >> 1] |= h << (16 * (e & 1));
+                        }
+                    }
+                }
+            }
+        }
+    };
+    if constexpr (EARLY) fetch_tail();
+
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.x), 0, (int)p.x_bytes, kRsrcFlags);
     const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.a_vals), 0, (int)p.a_bytes, kRsrcFlags);
     const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.a_meta), 0, (int)p.meta_bytes, kRsrcFlags);
@@ -68,16 +121,15 @@ __global__ __launch_bounds__(NW * 64) void conv_small_kernel(ConvParams p)
         m_voff[tm] = (unsigned)(m * p.Kp * 64 + lane) * 4u;
     }
     using A = AStep<SPARSE, TM>;
-    auto load_a = [&](A &a, int ks) {                     // (steps past the last one meet all-zero activations: any weights do)
-        ks = min(ks, p.Ks - 1);
+    auto load_a = [&](A &a, int ks, unsigned out = 0u) {  // (out = bit 31: nothing is fetched, the weights are zero)
 #pragma unroll
         for (int tm = 0; tm < TM; tm++) {
             if constexpr (SPARSE) {
-                a.v[0][tm] = __builtin_amdgcn_raw_buffer_load_b128(ra, (int)a_voff[tm], ks * 1024, 0);
-                a.idx[tm] = __builtin_amdgcn_raw_buffer_load_b32(rm, (int)m_voff[tm], (Q8 ? ks : (ks >> 1)) * 256, 0);
+                a.v[0][tm] = __builtin_amdgcn_raw_buffer_load_b128(ra, (int)(a_voff[tm] | out), ks * 1024, 0);
+                a.idx[tm] = __builtin_amdgcn_raw_buffer_load_b32(rm, (int)(m_voff[tm] | out), (Q8 ? ks : (ks >> 1)) * 256, 0);
             } else {
-                a.v[0][tm] = __builtin_amdgcn_raw_buffer_load_b128(ra, (int)a_voff[tm], ks * 2048, 0);
-                a.v[1][tm] = __builtin_amdgcn_raw_buffer_load_b128(ra, (int)a_voff[tm], ks * 2048 + 1024, 0);
+                a.v[0][tm] = __builtin_amdgcn_raw_buffer_load_b128(ra, (int)(a_voff[tm] | out), ks * 2048, 0);
+                a.v[1][tm] = __builtin_amdgcn_raw_buffer_load_b128(ra, (int)(a_voff[tm] | out), ks * 2048 + 1024, 0);
             }
         }
     };
@@ -87,14 +139,12 @@ __global__ __launch_bounds__(NW * 64) void conv_small_kernel(ConvParams p)
 #pragma unroll
         for (int v = 0; v < 16; v++) acc[tm][v] = 0;
     auto multiply = [&](const A &a, const B32 &b, int ks) {
-        const int shift = Q8 ? 0 : (min(ks, p.Ks - 1) & 1) * 16;
+        const int shift = Q8 ? 0 : (ks & 1) * 16;
 #pragma unroll
         for (int tm = 0; tm < TM; tm++) {
             if constexpr (SPARSE) {
                 acc[tm] = mma_sparse<DT>(a.v[0][tm], b, acc[tm], a.idx[tm] >> shift);
-            } else if constexpr (DT == SS_F8) {
-                acc[tm] = mma_dense_f8(a.v[0][tm], a.v[1][tm], b, acc[tm]);
-            } else {
+            } else {                                      // (dense FP8: pairs of the short instruction, whose operands are not tied to 8-register tuples)
                 acc[tm] = mma_dense<DT>(a.v[0][tm], b.lo, acc[tm]);
                 acc[tm] = mma_dense<DT>(a.v[1][tm], b.hi, acc[tm]);
             }
@@ -120,39 +170,65 @@ __global__ __launch_bounds__(NW * 64) void conv_small_kernel(ConvParams p)
 
     if constexpr (!small_taps(MODE)) {
         // ------------------------------------------------------------ fragments straight from memory
-        const Pixel px = pixel(PX == 32 || c < PX ? n0 + c : p.P);
-        const bool in0 = (unsigned)px.ih < (unsigned)p.H && (unsigned)px.iw < (unsigned)p.W;
+        const int pg = PX == 32 || c < PX ? n0 + c : p.P;
+        Pixel px;
+        if (MODE == SMALL_PW && (p.sh & p.sw) == 1 && (p.ph | p.pw) == 0) {      // uniform: pixels and positions in the input are the same thing
+            px = Pixel{pg < p.P ? 0 : -(1 << 28), 0, (unsigned)pg * p.Cin * 2u};
+        } else {
+            px = pixel(pg);
+        }
         const int per = (p.Ks + NW - 1) / NW;             // steps of a wave
-        const int s0 = wave * per, s1 = min(s0 + per, p.Ks);
-        auto octet = [&](int k) -> u32x4 {                // 8 reduction indices from k
-            unsigned off = kOutOfRange;
-            if constexpr (MODE == SMALL_PW) {
-                if (in0 && k < p.K) off = px.byte + (unsigned)k * 2;
-            } else {
-                const int tap = fast_div(k, p.cin_mul, p.cin_sh);
-                const int r = fast_div(tap, p.kw_mul, p.kw_sh), t = tap - r * p.kw;
-                const bool ok = (unsigned)(px.ih + r) < (unsigned)p.H && (unsigned)(px.iw + t) < (unsigned)p.W && k < p.K;
-                if (ok) off = px.byte + (unsigned)(((r * p.W + t) * p.Cin + k - tap * p.Cin) * 2);
-            }
-            return __builtin_amdgcn_raw_buffer_load_b128(rx, (int)off, 0, 0);
+        const int s0 = min(wave * per, p.Ks), s1 = min(s0 + per, p.Ks);
+        // Byte offsets of a step's two octets of channels (bit 31: outside, reads as zero).  Steps behind a share's end
+        // fetch nothing and multiply zeros.
+        const unsigned base = px.byte + 32u * g;
+        const int rem = p.K - (p.Ks - 1) * 32;            // reduction indices of the last step
+        const bool in0 = (unsigned)px.ih < (unsigned)p.H && (unsigned)px.iw < (unsigned)p.W;
+        const unsigned pw0 = in0 ? base : kOutOfRange;
+        const unsigned pw_lo = 16 * g < rem ? pw0 : kOutOfRange, pw_hi = 16 * g + 8 < rem ? pw0 : kOutOfRange;
+        auto octet = [&](int k) -> u32x4 {                // RSC: 8 reduction indices from k
+            const int tap = fast_div(k, p.cin_mul, p.cin_sh);
+            const int r = fast_div(tap, p.kw_mul, p.kw_sh), t = tap - r * p.kw;
+            const bool ok = (unsigned)(px.ih + r) < (unsigned)p.H && (unsigned)(px.iw + t) < (unsigned)p.W && k < p.K;
+            return __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(ok ? px.byte + (unsigned)(((r * p.W + t) * p.Cin + k - tap * p.Cin) * 2) : kOutOfRange), 0, 0);
         };
         A a[RING];
         B32 b[RING];
         auto load = [&](int j, int s) {
-            load_a(a[j], s);
-            const int k = s < s1 ? s * 32 + 16 * g : 1 << 30;      // (a share's end: zeros)
-            b[j].lo = octet(k);
-            b[j].hi = octet(k + 8);
+            const unsigned out = s < s1 ? 0u : kOutOfRange;      // uniform
+            load_a(a[j], s, out);
+            if constexpr (MODE == SMALL_PW) {
+                const bool last = s == p.Ks - 1;
+                b[j].lo = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)((last ? pw_lo : pw0) | out), s * 64, 0);
+                b[j].hi = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(((last ? pw_hi : pw0) | out) + 16u), s * 64, 0);
+            } else if constexpr (MODE == SMALL_RSCW) {
+                const int k = s * 32, tap = fast_div(k, p.cin_mul, p.cin_sh);
+                const int r = fast_div(tap, p.kw_mul, p.kw_sh), t = tap - r * p.kw;
+                const bool ok = (unsigned)(px.ih + r) < (unsigned)p.H && (unsigned)(px.iw + t) < (unsigned)p.W;
+                const unsigned off = (ok ? base + (unsigned)(((r * p.W + t) * p.Cin + k - tap * p.Cin) * 2) : kOutOfRange) | out;
+                b[j].lo = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)off, 0, 0);
+                b[j].hi = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(off + 16u), 0, 0);
+            } else {
+                const int k = s < s1 ? s * 32 + 16 * g : 1 << 30;
+                b[j].lo = octet(k);
+                b[j].hi = octet(k + 8);
+            }
         };
 #pragma unroll
-        for (int j = 0; j < RING; j++) load(j, s0 + j);
-        for (int s = s0; s < s1; s += RING) {
+        for (int j = 0; j < RING; j++) {
+            load(j, s0 + j);
+            __builtin_amdgcn_sched_barrier(0);            // (in this order: the first step multiplies while the others are on their way)
+        }
+        int s = s0;
+        for (; s + RING < s1; s += RING) {
 #pragma unroll
             for (int j = 0; j < RING; j++) {
                 multiply(a[j], b[j], s + j);
-                if (s + RING < s1) load(j, s + RING + j);
+                load(j, s + RING + j);
             }
         }
+#pragma unroll
+        for (int j = 0; j < RING; j++) multiply(a[j], b[j], s + j);
     } else {
         // ------------------------------------------------------------ taps of whole channel chunks, transposed in the wave's own LDS
         constexpr int VPR = TAPS * 4;                     // 16-byte vectors per pixel row of a chunk (TAPS steps of 64 bytes)
@@ -195,7 +271,7 @@ __global__ __launch_bounds__(NW * 64) void conv_small_kernel(ConvParams p)
         if (wave < nchunks) load_x(wave);
         for (int ci = wave; ci < nchunks; ci += NW) {
 #pragma unroll
-            for (int s = 0; s < TAPS; s++) load_a(a[s], ci * TAPS + s);
+            for (int s = 0; s < TAPS; s++) load_a(a[s], min(ci * TAPS + s, p.Ks - 1));      // (a ragged chunk's missing steps: LDS holds zeros for them)
 #pragma unroll
             for (int i = 0; i < IT; i++) {
                 const int pr = (lane >> 2) + 16 * i, key = SWZ ? (pr >> 2) & 3 : pr & 15;
@@ -218,7 +294,7 @@ __global__ __launch_bounds__(NW * 64) void conv_small_kernel(ConvParams p)
 
     // ---------------------------------------------------------------- partial sums meet in LDS, in register order [wave][quad][lane]
     // (each wave's region lies inside its own staging area where there is one: no barrier before it)
-    constexpr int RSTRIDE = (int)(small_wave_lds<MODE, TAPS, PX, TM>() / 16), QUADS = PX * 8 * TM;       // 16-byte vectors from one wave's region to the next
+    constexpr int RSTRIDE = (int)(small_wave_lds<MODE, TAPS, PX, TM>() / 16);       // 16-byte vectors from one wave's region to the next
     u32x4 *const part = reinterpret_cast<u32x4 *>(smem);
 #pragma unroll
     for (int tm = 0; tm < TM; tm++)
@@ -232,49 +308,9 @@ __global__ __launch_bounds__(NW * 64) void conv_small_kernel(ConvParams p)
             }
             part[wave * RSTRIDE + (tm * 4 + q) * 64 + lane] = w;
         }
-    // (consecutive threads finish the tile's channels of a pixel)
-    const float floor = p.act == SS_ACT_RELU ? 0.f : -__builtin_inff();
-    const bool four = (p.Cout & 3) == 0;
-    struct Tail {                                         // what a finished quad needs from memory, fetched before the barrier
-        float bias[4], scale[4], res[4];
-    };
-    auto quad = [&](int t, int *pl, int *cq, int *pg, int *o) {
-        *pl = t / (8 * TM);                               // pixel, quad of channels: accumulators 4*(cq/2).. of lane group cq%2
-        *cq = t % (8 * TM);
-        *pg = n0 + *pl;
-        *o = mt * 32 + *cq * 4;
-        return *pg < p.P && *o < p.Cout;
-    };
-    auto fetch = [&](int t) {
-        Tail f;
-        int pl, cq, pg, o;
-        const bool in = t < QUADS && quad(t, &pl, &cq, &pg, &o);
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-            const bool ine = in && o + e < p.Cout;
-            f.bias[e] = ine && p.bias != nullptr ? p.bias[o + e] : 0.f;
-            f.scale[e] = Q8 && ine && p.scale != nullptr ? p.scale[o + e] : 1.f;
-            f.res[e] = 0.f;
-        }
-        if constexpr (!Q8) {
-            if (p.residual != nullptr && in) {
-                const uint16_t *r = p.residual + (size_t)pg * p.Cout + o;
-                if (four) {
-                    const uint2 u = *reinterpret_cast<const uint2 *>(r);
-                    f.res[0] = widen<ODT>((uint16_t)u.x); f.res[1] = widen<ODT>((uint16_t)(u.x >> 16));
-                    f.res[2] = widen<ODT>((uint16_t)u.y); f.res[3] = widen<ODT>((uint16_t)(u.y >> 16));
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; e++)
-                        if (o + e < p.Cout) f.res[e] = widen<ODT>(r[e]);
-                }
-            }
-        }
-        return f;
-    };
     auto finish = [&](int t, const Tail &f) {
         int pl, cq, pg, o;
-        if (t >= QUADS || !quad(t, &pl, &cq, &pg, &o)) return;
+        if (!quad(t, &pl, &cq, &pg, &o)) return;
         float v[4];
         const int from = (cq >> 1) * 64 + (cq & 1) * 32 + pl;
         if constexpr (DT == SS_I8) {
@@ -299,7 +335,8 @@ __global__ __launch_bounds__(NW * 64) void conv_small_kernel(ConvParams p)
         }
 #pragma unroll
         for (int e = 0; e < 4; e++) {
-            const float z = (Q8 ? v[e] * f.scale[e] + f.bias[e] : v[e] + f.bias[e]) + f.res[e];
+            const float bias = __builtin_bit_cast(float, f.bias[e]), scale = Q8 && p.scale != nullptr ? __builtin_bit_cast(float, f.scale[e]) : 1.f;
+            const float z = Q8 ? v[e] * scale + bias : v[e] + bias + widen<ODT>((uint16_t)(f.res[e >> 1] >> (16 * (e & 1))));
             v[e] = p.act == SS_ACT_GELU ? gelu_cdf(z) : floor_at(z, floor);
         }
         uint16_t *y = p.y + (size_t)pg * p.Cout + o;
@@ -311,13 +348,13 @@ __global__ __launch_bounds__(NW * 64) void conv_small_kernel(ConvParams p)
                 if (o + e < p.Cout) y[e] = (uint16_t)(cvt_pack2<ODT>(v[e], 0.f) & 0xFFFFu);
         }
     };
-    const Tail first = fetch(tid);
+    if constexpr (!EARLY) fetch_tail();
     __syncthreads();
-    finish(tid, first);
-    for (int t = tid + NW * 64; t < QUADS; t += NW * 64) finish(t, fetch(t));
+#pragma unroll
+    for (int i = 0; i < QIT; i++) finish(tid + i * NW * 64, tail[i]);
 }
 
-template <int DT, bool SPARSE, int MODE, int KH, int KW, int PX, int TM, int NW>
+template <int DT, bool SPARSE, int MODE, int KH, int KW, int PX, int TM, int NW, int RING = 4>
 static int launch_small_waves(ConvParams p, hipStream_t s)
 {
     constexpr size_t smem = NW * small_wave_lds<MODE, KH * KW, PX, TM>();
@@ -326,7 +363,7 @@ static int launch_small_waves(ConvParams p, hipStream_t s)
     fast_div_setup((unsigned)p.tiles_m, &p.tm_mul, &p.tm_sh);
     const long long blocks = small_blocks(p, PX, TM);
     if (blocks <= 0 || blocks > 0x7FFFFFFFll) return SS_ERR_UNSUPPORTED;
-    auto kern = conv_small_kernel<DT, SPARSE, MODE, KH, KW, PX, TM, NW>;
+    auto kern = conv_small_kernel<DT, SPARSE, MODE, KH, KW, PX, TM, NW, RING>;
     if (smem > 64 * 1024) {
         static std::atomic<unsigned long long> done_mask{0};      // as in launch(): once per device
         int dev = 0;
@@ -387,7 +424,10 @@ static int launch_small(const ConvParams &p, int variant, hipStream_t s)
         switch (small_waves(p, taps, PX == 16)) {
             case 2: return launch_small_waves<DT, SPARSE, MODE, KH, KW, PX, TM, 2>(p, s);
             case 4: return launch_small_waves<DT, SPARSE, MODE, KH, KW, PX, TM, 4>(p, s);
-            case 8: return launch_small_waves<DT, SPARSE, MODE, KH, KW, PX, TM, 8>(p, s);
+            case 8:
+                if constexpr (taps == 0)                  // shares of more than four steps
+                    if (p.Ks > 32) return launch_small_waves<DT, SPARSE, MODE, KH, KW, PX, TM, 8, 8>(p, s);
+                return launch_small_waves<DT, SPARSE, MODE, KH, KW, PX, TM, 8>(p, s);
             default: break;
         }
         if constexpr (PX == 16 && taps == 0) return launch_small_waves<DT, SPARSE, MODE, KH, KW, PX, TM, 16>(p, s);
@@ -404,7 +444,9 @@ template <int DT, bool SPARSE>
 static int small_mode(const ss_weight_desc *desc, const ConvParams &p, int variant, hipStream_t s)
 {
     const int taps = desc->kh * desc->kw;
+    if ((long long)p.P * p.Cout * 2 > 0x7FFFFFFF) return SS_ERR_INVALID_ARG;      // (32-bit offsets; such outputs are far above these kernels' range)
     if (taps == 1 && p.Cin % 8 == 0) return launch_small<DT, SPARSE, SMALL_PW, 1, 1>(p, variant, s);
+    if (desc->korder == SS_K_RSC && p.Cin % 32 == 0) return launch_small<DT, SPARSE, SMALL_RSCW, 1, 1>(p, variant, s);
     if (desc->korder == SS_K_RSC && p.Cin % 8 == 0) return launch_small<DT, SPARSE, SMALL_RSC, 1, 1>(p, variant, s);
     if (desc->korder == SS_K_CRS && p.Cin % 32 == 0) {
         if (desc->kh == 3 && desc->kw == 3) return launch_small<DT, SPARSE, SMALL_TAPS, 3, 3>(p, variant, s);
@@ -440,7 +482,7 @@ static inline __host__ __device__ PairShape pair_shape(int px, int nchunks, int 
     if (h.stage < slabs) h.stage = slabs;
     h.part = (size_t)kPairWaves * 4096;
     h.tile = (size_t)px * (cout1 + 4) * 2;
-    h.total = h.stage + h.part + h.tile;
+    h.total = h.stage + h.part + h.tile + (size_t)cout1 * 4;      // ... then the first layer's bias
     return h;
 }
 
@@ -461,6 +503,7 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
     u32x4 *const part = reinterpret_cast<u32x4 *>(reinterpret_cast<char *>(smem) + sh.stage);
     uint16_t *const tile = reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(smem) + sh.stage + sh.part);
     const int TROW = p.Cout + 4;                          // 16-bit units per pixel row of the tile
+    float *const bias1 = reinterpret_cast<float *>(reinterpret_cast<char *>(smem) + sh.stage + sh.part + sh.tile);
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.x), 0, (int)p.x_bytes, kRsrcFlags);
     const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.a_vals), 0, (int)p.a_bytes, kRsrcFlags);
     const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.a_meta), 0, (int)p.meta_bytes, kRsrcFlags);
@@ -513,6 +556,7 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
         for (int v = 0; v < TAPS; v++) stage[(ci * PX + pr) * VPR + ((unit * TAPS + v) ^ key)] = taps_vector<false, false, TAPS>(x, v, false);
     };
     const int items = nchunks * PX * 4;
+    const float bias_mine = tid < p.Cout && p.bias != nullptr ? p.bias[tid] : 0.f;      // (at most 256 channels)
     A a[RING];
     {
         u32x4 x[TAPS];
@@ -527,9 +571,19 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
         stage_item(it, x);
         store_item(it, x);
     }
+    if (tid < p.Cout) bias1[tid] = bias_mine;
     struct Row2 {
         A a[KS2];
         float4 b[4];
+    };
+    constexpr int IT = PX * 4 / 64;                       // 16-byte runs of an output row tile per lane
+    auto load_res = [&](u32x4 (&res)[IT], int mt) {
+#pragma unroll
+        for (int j = 0; j < IT; j++) {
+            const int it = lane + 64 * j, pg = n0 + (it >> 2);
+            res[j] = u32x4{0u, 0u, 0u, 0u};
+            if (p.res2 != nullptr && pg < p.P) res[j] = *reinterpret_cast<const u32x4 *>(p.res2 + (size_t)pg * p.Cout2 + mt * 32 + (it & 3) * 8);
+        }
     };
     auto load_row2 = [&](Row2 &r, int mt) {
 #pragma unroll
@@ -540,8 +594,12 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
             r.b[q] = p.bias2 ? *reinterpret_cast<const float4 *>(p.bias2 + mt * 32 + 8 * q + 4 * g) : make_float4(0.f, 0.f, 0.f, 0.f);
     };
     Row2 r2;
-    if (wave < p.Mt2) load_row2(r2, wave);                // in flight while the first layer is multiplied
-    __syncthreads();
+    u32x4 res[IT], res_next[IT];
+    if (wave < p.Mt2) {                                   // in flight while the first layer is multiplied
+        load_row2(r2, wave);
+        load_res(res_next, wave);
+    }
+    lds_barrier();
     f32x16 acc;
 #pragma unroll
     for (int v = 0; v < 16; v++) acc[v] = 0.f;
@@ -567,7 +625,7 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
         const f32x4 w = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
         part[wave * 256 + q * 64 + lane] = __builtin_bit_cast(u32x4, w);
     }
-    __syncthreads();
+    lds_barrier();
     const float floor1 = p.act == SS_ACT_RELU ? 0.f : -__builtin_inff();
     for (int t = tid; t < PX * 8 * p.Mt; t += NT) {       // quads of channels, pixel fastest: (row tile, quad, pixel)
         const int pl = t & (PX - 1), q = t / PX, m = q >> 3, cq = q & 7;
@@ -580,24 +638,18 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
         const int o = m * 32 + cq * 4;
 #pragma unroll
         for (int e = 0; e < 4; e++) {
-            const float z = v[e] + (p.bias != nullptr ? p.bias[o + e] : 0.f);
+            const float z = v[e] + bias1[o + e];
             v[e] = p.act == SS_ACT_GELU ? gelu_cdf(z) : floor_at(z, floor1);
         }
         *reinterpret_cast<uint2 *>(tile + pl * TROW + o) = make_uint2(cvt_pack2<DT>(v[0], v[1]), cvt_pack2<DT>(v[2], v[3]));
     }
-    __syncthreads();
+    lds_barrier();
     // ---- second layer
     const float floor2 = p.act2 == SS_ACT_RELU ? 0.f : -__builtin_inff();
     float *const slab = reinterpret_cast<float *>(smem) + wave * (PX * kFuseRow);
     for (int mt = wave; mt < p.Mt2; mt += kPairWaves) {
-        constexpr int IT = PX * 4 / 64;                   // 16-byte runs per lane
-        u32x4 res[IT];
 #pragma unroll
-        for (int j = 0; j < IT; j++) {
-            const int it = lane + 64 * j, pg = n0 + (it >> 2);
-            res[j] = u32x4{0u, 0u, 0u, 0u};
-            if (p.res2 != nullptr && pg < p.P) res[j] = *reinterpret_cast<const u32x4 *>(p.res2 + (size_t)pg * p.Cout2 + mt * 32 + (it & 3) * 8);
-        }
+        for (int j = 0; j < IT; j++) res[j] = res_next[j];
         f32x16 acc2;
 #pragma unroll
         for (int v = 0; v < 16; v++) acc2[v] = 0.f;
@@ -618,7 +670,10 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
                 *reinterpret_cast<float4 *>(slab + cc * kFuseRow + 8 * q + 4 * g) =
                     make_float4(acc2[4 * q] + r2.b[q].x, acc2[4 * q + 1] + r2.b[q].y, acc2[4 * q + 2] + r2.b[q].z, acc2[4 * q + 3] + r2.b[q].w);
         }
-        if (mt + kPairWaves < p.Mt2) load_row2(r2, mt + kPairWaves);
+        if (mt + kPairWaves < p.Mt2) {
+            load_row2(r2, mt + kPairWaves);
+            load_res(res_next, mt + kPairWaves);
+        }
         __builtin_amdgcn_wave_barrier();                  // (a wave's LDS operations execute in order: the reads below see the writes above)
 #pragma unroll
         for (int j = 0; j < IT; j++) {
