@@ -396,16 +396,20 @@ enum { SMALL_NONE = -1, SMALL_16 = 0, SMALL_32 = 1, SMALL_64X32 = 2 };      // 3
 //   * 32-pixel tiles under the same conditions (four waves up to eight waves per unit, 2x2 kernels two workgroups):
 //     the 256 -> 256 layer on four images 9.1 -> 5.4;
 //   * 64 x 32 tiles for long reductions while one per unit holds them: 512 -> 512 on sixteen 7x7 images 19 -> 9.6 us.  Not for the
-//     dense form of the tap modes (its fragments spill: 11.4 vs 9.8) nor for 8-bit direct loads (8.3 vs 6.6).
-//   * 1x1 reductions of one or two steps stay with the tiled kernels (3.5 vs 3.6 us).
-static inline int small_variant(const ConvParams &p, int taps, bool sparse, bool q8, int ncu)
+//     dense form of the tap modes (its fragments spill: 11.4 vs 9.8).  Direct loads from sixteen steps on (1x1 512 -> 128 on
+//     four 28x28 images 5.0 -> 4.2 us, 3x3 channels-last 128 -> 512 on one 8.3 -> 6.6, int8 1x1 1024 -> 256 on eight 14x14
+//     4.8 -> 4.1); below that the 32-pixel tiles are as good.
+//   * direct loads, 32-pixel tiles up to two per unit while the reduction is short (1x1 128 -> 512 on one 28x28 image 4.0 -> 3.3,
+//     64 -> 64 on two 56x56 3.5 -> 3.1, int8 3x3 64 -> 128 on four 28x28 4.8 -> 3.4; at 32 steps 6.7 against the tiled 6.4, and at
+//     three per unit no gain).
+static inline int small_variant(const ConvParams &p, int taps, bool sparse, int ncu)
 {
-    if (!taps && p.kh * p.kw == 1 && p.Ks <= 2) return SMALL_NONE;
     const long long b16 = small_blocks(p, 16, 1), b32 = small_blocks(p, 32, 1), b64 = small_blocks(p, 32, 2);
     const int nw = small_waves(p, taps, false);
     if (b16 <= ncu || (taps && nw == 2 && b16 * nw <= 8ll * ncu)) return SMALL_16;
     if (b32 <= ncu || (taps && nw == 4 && b32 * nw <= 8ll * ncu) || (taps == 4 && b32 <= 2ll * ncu)) return SMALL_32;
-    if (b64 <= ncu && (taps ? nw == 8 && sparse : p.Ks >= 36 && !q8)) return SMALL_64X32;
+    if (b64 <= ncu && (taps ? nw == 8 && sparse : p.Ks >= 16)) return SMALL_64X32;
+    if (!taps && p.Ks <= 20 && b32 <= 2ll * ncu) return SMALL_32;
     return SMALL_NONE;
 }
 
@@ -416,7 +420,7 @@ static int launch_small(const ConvParams &p, int variant, hipStream_t s)
     if (variant < 0) {                                    // the library decides
         const int ncu = compute_units();
         if (ncu <= 0) return SS_ERR_HIP;
-        variant = small_variant(p, taps, SPARSE, is_byte_type(DT), ncu);
+        variant = small_variant(p, taps, SPARSE, ncu);
         if (variant < 0) return SS_ERR_INVALID_ARG;
     }
     auto waves = [&](auto px, auto tm) -> int {
