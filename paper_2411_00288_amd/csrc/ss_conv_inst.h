@@ -39,9 +39,21 @@ int SS_CAT(conv_dispatch_, SS_INST_NAME)(const ss_weight_desc *desc, const ConvP
             const long long rounds_w = (wide + slots - 1) / slots, rounds_n = (narrow + slots - 1) / slots;
             const bool filled = is_byte_type(SS_INST_DT) ? 4ll * p.Cout >= 3 * 256 * rows : 2ll * p.Cout > 256 * rows;
             const bool pays = filled && 2 * rows * narrow > ncu;
-            if (forced == 10 || (forced < 0 && pays && 100 * rounds_w <= 59 * rounds_n))
-                return launch_stream<SS_INST_DT, SS_INST_SPARSE, 2, 4>(p, ncu, s);
-            if (forced == 11 || (forced < 0 && pays)) return launch_stream<SS_INST_DT, SS_INST_SPARSE, 2, 2>(p, ncu, s);
+            if (desc->kh == 2) {
+                // The same line for 2x2 kernels of 16-bit operands with at least two chunks (96 -> 192 on 128 images of 56x56: 30-35
+                // -> 25.4 us, on 32: 9.8 -> 7.7; 192 -> 384 on 64 of 28x28 12.6 -> 10.4; one chunk, 32 -> 200: 5.6 against 6.7 stays).
+                // Sparse, a narrow round is worth 0.56 of a wide one.  8-bit operands gain nothing (23.4 / 23.2, 24.1 / 23.5): not built.
+                if constexpr (!is_byte_type(SS_INST_DT)) {
+                    const bool wide_pays = 100 * rounds_w <= (SS_INST_SPARSE ? 56 : 59) * rounds_n;
+                    if (forced == 10 || (forced < 0 && pays && p.Ks > 4 && wide_pays))
+                        return launch_stream<SS_INST_DT, SS_INST_SPARSE, 2, 4, 2>(p, ncu, s);
+                    if (forced == 11 || (forced < 0 && pays && p.Ks > 4)) return launch_stream<SS_INST_DT, SS_INST_SPARSE, 2, 2, 2>(p, ncu, s);
+                }
+            } else {
+                if (forced == 10 || (forced < 0 && pays && 100 * rounds_w <= 59 * rounds_n))
+                    return launch_stream<SS_INST_DT, SS_INST_SPARSE, 2, 4, 3>(p, ncu, s);
+                if (forced == 11 || (forced < 0 && pays)) return launch_stream<SS_INST_DT, SS_INST_SPARSE, 2, 2, 3>(p, ncu, s);
+            }
         }
     }
     if constexpr (!is_byte_type(SS_INST_DT)) {

@@ -1,4 +1,4 @@
-// Resident-grid ("streaming") variant of the 3x3 convolution in the paper's channel-slowest flattening, for grids
+// Resident-grid ("streaming") variant of the 3x3 and 2x2 convolutions in the paper's channel-slowest flattening, for grids
 // of several workgroup tiles per compute unit (Sec. 3.3 Eq. 6, the same contraction as ss_conv_kernel.h).
 //
 // What differs from the one-tile-per-workgroup kernel:
@@ -29,32 +29,34 @@ namespace ss {
 #define SS_STREAM_PACE 0      // s_sleep argument (units of 64 clocks) between a producer thread's load / LDS-write pairs; 0 = none
 #endif
 
-template <int TN>
+template <int TN, int KH>
 struct StreamShape {
-    static constexpr int TAPS = 9, KSTEPS = 9, BK = 288, ROW = 288;      // a chunk = 32 channels x 9 taps, unpadded swizzled rows
+    static constexpr int TAPS = KH * KH, KSTEPS = TAPS, BK = 32 * TAPS;  // a chunk = 32 channels x all taps
+    static constexpr bool SWZ = KH == 3;                                  // rows: unpadded and swizzled, or (2x2) padded by 16 bytes, which is conflict-free there
+    static constexpr int ROW = SWZ ? BK : BK + 8;
     static constexpr int BN = 32 * TN;
     static constexpr int SLAB_ROW = 32 + 4;                               // 16-bit units per pixel row of a wave's output slab
     static constexpr size_t stage_bytes = (size_t)2 * BN * ROW * 2;
     static constexpr size_t slab_bytes = (size_t)4 * 32 * SLAB_ROW * 2;
 };
-template <int DT, int TM, int TN>
+template <int DT, int TM, int TN, int KH>
 constexpr size_t stream_smem_bytes()
 {
-    return StreamShape<TN>::stage_bytes + StreamShape<TN>::slab_bytes + (size_t)(128 * TM) * (is_byte_type(DT) ? 8 : 4);      // bias, and scale
+    return StreamShape<TN, KH>::stage_bytes + StreamShape<TN, KH>::slab_bytes + (size_t)(128 * TM) * (is_byte_type(DT) ? 8 : 4);      // bias, and scale
 }
 
-template <int DT, bool SPARSE, int TM, int TN>
+template <int DT, bool SPARSE, int TM, int TN, int KH>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void conv3x3_stream_kernel(ConvParams p, int tiles_n, int slots_n)
+void conv_stream_kernel(ConvParams p, int tiles_n, int slots_n)
 {
-    using SH = StreamShape<TN>;
-    constexpr int BM = 128 * TM, BN = SH::BN, ROW = SH::ROW, TAPS = 9, KSTEPS = 9;
+    using SH = StreamShape<TN, KH>;
+    constexpr int BM = 128 * TM, BN = SH::BN, ROW = SH::ROW, TAPS = SH::TAPS, KSTEPS = SH::KSTEPS;
     constexpr bool Q8 = is_byte_type(DT);            // 8-bit operands: chunks of 64 channels in the same bytes, full index words, scaled tail
     static_assert(SPARSE || !Q8, "the 8-bit twins stay with the tiled kernels");
     constexpr int FR = KSTEPS * TN;                  // activation fragments per chunk
-    constexpr int RB = 6, D = 4;                     // activation-fragment ring: slots, prefetch distance (fragments)
+    constexpr int RB = KH == 3 ? 6 : 4, D = KH == 3 ? 4 : 3;      // activation-fragment ring: slots, prefetch distance (fragments)
     constexpr int AF = KSTEPS * TM;                  // weight fragments per chunk
-    constexpr int RA = SPARSE ? (TM == 2 ? (Q8 ? 6 : 9) : 3) : (TM == 2 ? 6 : 3);     // weight-fragment ring slots
+    constexpr int RA = KH == 2 ? (SPARSE ? 8 : 4) : (SPARSE ? (TM == 2 ? (Q8 ? 6 : 9) : 3) : (TM == 2 ? 6 : 3));     // weight-fragment ring slots
     static_assert(FR % RB == 0 && AF % RA == 0 && D < RB && D < FR, "rings must nest with the chunk");
     static_assert(TM == 1 || TM == 2, "one or two row tiles per wave");
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
@@ -103,13 +105,16 @@ void conv3x3_stream_kernel(ConvParams p, int tiles_n, int slots_n)
                 const unsigned pixbyte = (unsigned)(((n * p.H + ih0) * p.W + iw0) * p.Cin * 2);
 #pragma unroll
                 for (int tap = 0; tap < TAPS; tap++) {
-                    const int r = tap / 3, t = tap % 3;
+                    const int r = tap / KH, t = tap % KH;
                     const bool ok = live && (unsigned)(ih0 + r) < (unsigned)p.H && (unsigned)(iw0 + t) < (unsigned)p.W;
                     tapoff[i][tap] = ok ? pixbyte + (unsigned)(((r * p.W + t) * p.Cin + unit * 8) * 2) : kOutOfRange;
                 }
             }
         };
-        u32x4 st[2][ITEMS][TAPS];
+        // Chunks in flight: the one being written to LDS and NS - 1 on their way.  A 2x2 chunk of 64 pixels is only 16 KiB, and
+        // such a layer is bound by memory (nine times fewer matrix instructions per loaded byte than a 3x3 of 256 channels).
+        constexpr int NS = KH == 2 ? 8 / TN : 2;
+        u32x4 st[NS][ITEMS][TAPS];
         int gen_it = 0, gen_c = 0;                   // the chunk the next load belongs to
         setup_tile(0);
         auto advance = [&]() {                       // (the addresses of the loads just issued are spent: overwrite them)
@@ -124,7 +129,7 @@ void conv3x3_stream_kernel(ConvParams p, int tiles_n, int slots_n)
         auto store_one = [&](uint16_t *buf, int set, int i, int v) {
             const int pr = pr0 + i * 64;
             u32x4 *rowp = reinterpret_cast<u32x4 *>(buf + pr * ROW);
-            const int vec0 = unit * TAPS, swz = (pr >> 2) & 3;
+            const int vec0 = unit * TAPS, swz = SH::SWZ ? (pr >> 2) & 3 : 0;
             const u32x4 w = taps_vector<Q8, false, TAPS>(st[set][i], v, false);
             rowp[(vec0 + v) ^ swz] = w;
         };
@@ -157,20 +162,19 @@ void conv3x3_stream_kernel(ConvParams p, int tiles_n, int slots_n)
                 }
             advance();
         };
-        // Chunk k is written to buffer k % 2 and published by barrier number k; the loads of chunk k + 1 are issued
-        // before chunk k is written (loads past the last chunk address nothing and return zeros).
-        load(0);
-        load(1);
+        // Chunk k is written to buffer k % 2 and published by barrier number k; the loads of chunk k + NS - 1 are issued
+        // while chunk k is written (loads past the last chunk address nothing and return zeros).
+#pragma unroll
+        for (int j = 0; j < NS; j++) load(j);
         store(Bs0, 0);
         lds_barrier();                                // barrier 0: chunk 0
-        for (int k = 1; k < total; k += 2) {
-            // loads of chunk k + 1 (set 0 held chunk k - 1, which is in LDS); chunk k goes to buffer 1, which held
-            // chunk k - 2, whose last read precedes barrier k - 1
-            load_store(0, Bs1, 1);
-            lds_barrier();                            // barrier k
-            if (k + 1 >= total) break;
-            load_store(1, Bs0, 0);                    // loads of chunk k + 2, LDS writes of chunk k + 1
-            lds_barrier();                            // barrier k + 1
+        for (int k = 1; k < total; k += NS) {
+#pragma unroll
+            for (int j = 0; j < NS; j++) {            // chunk k + j lies in set (1 + j) % NS; its predecessor's set is free again
+                if (k + j >= total) break;
+                load_store(j, (1 + j) & 1 ? Bs1 : Bs0, (1 + j) % NS);
+                lds_barrier();                        // barrier k + j
+            }
         }
         lds_barrier();                                // answers the multiplying waves' barrier inside the last chunk
         return;
@@ -211,7 +215,7 @@ void conv3x3_stream_kernel(ConvParams p, int tiles_n, int slots_n)
         }
     };
     // This lane's two 16-byte vectors of a fragment inside the step's aligned group of four, swizzled as the rows are.
-    const int frag_key = (lane >> 2) & 3;
+    const int frag_key = SH::SWZ ? (lane >> 2) & 3 : 0;
     const int frag_lo = ((2 * (lane >> 5)) ^ frag_key) * 8, frag_hi = ((2 * (lane >> 5) + 1) ^ frag_key) * 8;
     const int brow = (lane & 31) * ROW;
     B32 b[RB];
@@ -357,11 +361,11 @@ void conv3x3_stream_kernel(ConvParams p, int tiles_n, int slots_n)
 }
 
 // Launches the streaming kernel on a grid of at most `max_blocks` workgroups (one per compute unit).
-template <int DT, bool SPARSE, int TM, int TN>
+template <int DT, bool SPARSE, int TM, int TN, int KH>
 static int launch_stream(const ConvParams &p0, int max_blocks, hipStream_t s)
 {
     constexpr int BM = 128 * TM, BN = 32 * TN;
-    constexpr size_t smem = stream_smem_bytes<DT, TM, TN>();
+    constexpr size_t smem = stream_smem_bytes<DT, TM, TN, KH>();
     static_assert(smem <= 160 * 1024, "LDS tile too large");
     ConvParams p = p0;
     p.tiles_m = (p.Cout + BM - 1) / BM;
@@ -371,7 +375,7 @@ static int launch_stream(const ConvParams &p0, int max_blocks, hipStream_t s)
     if (slots_n < 1) slots_n = 1;
     if (slots_n > tiles_n) slots_n = tiles_n;
     const long long blocks = slots_n * p.tiles_m;
-    auto kern = conv3x3_stream_kernel<DT, SPARSE, TM, TN>;
+    auto kern = conv_stream_kernel<DT, SPARSE, TM, TN, KH>;
     static std::atomic<unsigned long long> done_mask{0};      // dynamic-LDS limit raised, per device
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return SS_ERR_HIP;
@@ -385,12 +389,12 @@ static int launch_stream(const ConvParams &p0, int max_blocks, hipStream_t s)
     return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP;
 }
 
-// Can the streaming kernel take this problem?  3x3 kernel in the channel-slowest flattening, whole chunks (cin % 32 == 0, 8-bit
+// Can the streaming kernel take this problem?  3x3 or 2x2 kernel in the channel-slowest flattening, whole chunks (cin % 32 == 0, 8-bit
 // operands cin % 64 == 0), 16-byte output runs (cout % 8 == 0), no residual, output below 2 GiB (32-bit store offsets,
 // with room for the offsets of a last tile's pixels past the end to stay below the out-of-range mark).
 static inline bool stream_eligible(const ss_weight_desc *desc, const ConvParams &p)
 {
-    return desc->korder == SS_K_CRS && desc->kh == 3 && desc->kw == 3 && p.Cin % 32 == 0 &&
+    return desc->korder == SS_K_CRS && desc->kh == desc->kw && (desc->kh == 3 || desc->kh == 2) && p.Cin % 32 == 0 &&
            desc->cout % 8 == 0 && p.residual == nullptr && (long long)p.P * p.Cout * 2 < (1ll << 31) - (1ll << 27);
 }
 

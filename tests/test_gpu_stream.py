@@ -85,3 +85,21 @@ def test_stream_kernels_take_byte_operands(ss, force_tile, limit_blocks, L, tile
     limit_blocks(cap)
     y = (test_gpu_q8 if q8 else test_gpu_f8)._run(ss, L, d, sparse=True)
     (test_gpu_q8.check_q8 if q8 else check_close)(y, ref, f"{L.name} tile {tile} cap {cap}")
+
+
+def _L2(N, H, W, cin, cout, s=2, p=0, dtype=wl.F16, act=wl.ACT_RELU, seed=0):
+    return wl.Layer(f"k2n{N}h{H}w{W}c{cin}o{cout}s{s}d{dtype}a{act}", N=N, H=H, W=W, cin=cin, cout=cout, kh=2, kw=2, stride=s, pad=p,
+                    dtype=dtype, korder=wl.K_CRS, act=act, mask="logits", seed=seed)
+
+
+@pytest.mark.parametrize("cap", [None, 1, 3])
+@pytest.mark.parametrize("tile", STREAM_TILES)
+@pytest.mark.parametrize("L", [_L2(3, 28, 27, 96, 192, dtype=wl.BF16), _L2(2, 9, 11, 32, 264, s=1, p=1, act=wl.ACT_GELU, seed=2),
+                               _L2(5, 20, 24, 160, 72, dtype=wl.BF16, seed=3)], ids=lambda L: L.name)
+def test_stream_kernels_take_2x2(ss, force_tile, limit_blocks, L, tile, cap):
+    d = wl.make_inputs(L)                 # 3, 1 and 5 chunks per tile: fewer and more than are in flight; ragged row and pixel tiles
+    ref = oracle_ref(L, d)
+    force_tile(tile)
+    limit_blocks(cap)
+    check_close(run_gpu(ss, L, d, sparse=True), ref, f"{L.name} sparse tile {tile} cap {cap}")
+    check_close(run_gpu(ss, L, d, sparse=False), ref, f"{L.name} dense tile {tile} cap {cap}")
