@@ -210,7 +210,7 @@ bool weights_fit(const ss_weight_desc &d, bool sparse, const at::Tensor *w)
 }
 
 // conv(kind, desc, x, weights, scale, bias, residual, stride, pad, act, y, workspace) -> y or None
-PyObject *conv(PyObject *, PyObject *const *a, Py_ssize_t n)
+PyObject *conv(PyObject *const *a, Py_ssize_t n)
 {
     int32_t kind, act, sp[4], nhw[3];
     ss_weight_desc d;
@@ -233,35 +233,31 @@ PyObject *conv(PyObject *, PyObject *const *a, Py_ssize_t n)
         residual = r->const_data_ptr();
     }
     at::Tensor y, ws;
-    try {
-        if (!output(a[10], *x, at::IntArrayRef(shape, 4), yt, &y)) Py_RETURN_NONE;
-        const hipStream_t s = c10::hip::getCurrentHIPStream().stream();
-        size_t need = 0, ws_bytes = 0;
-        void *wsp = nullptr;
-        if (a[11] != Py_None) {
-            const at::Tensor *t = dev_tensor(a[11]);
-            if (!t) Py_RETURN_NONE;
-            wsp = t->data_ptr();
-            ws_bytes = t->nbytes();
-        } else {
-            if (ss_conv2d_workspace_bytes(&d, nhw[0], nhw[1], nhw[2], sp[0], sp[1], sp[2], sp[3], &need) != SS_OK) Py_RETURN_NONE;
-            if (need > 0) {
-                if (!pooled_workspace(*x, s, need, &ws)) Py_RETURN_NONE;
-                wsp = ws.data_ptr();
-                ws_bytes = ws.nbytes();
-            }
+    if (!output(a[10], *x, at::IntArrayRef(shape, 4), yt, &y)) Py_RETURN_NONE;
+    const hipStream_t s = c10::hip::getCurrentHIPStream().stream();
+    size_t need = 0, ws_bytes = 0;
+    void *wsp = nullptr;
+    if (a[11] != Py_None) {
+        const at::Tensor *t = dev_tensor(a[11]);
+        if (!t) Py_RETURN_NONE;
+        wsp = t->data_ptr();
+        ws_bytes = t->nbytes();
+    } else {
+        if (ss_conv2d_workspace_bytes(&d, nhw[0], nhw[1], nhw[2], sp[0], sp[1], sp[2], sp[3], &need) != SS_OK) Py_RETURN_NONE;
+        if (need > 0) {
+            if (!pooled_workspace(*x, s, need, &ws)) Py_RETURN_NONE;
+            wsp = ws.data_ptr();
+            ws_bytes = ws.nbytes();
         }
-        if (call_conv(kind, &d, x->const_data_ptr(), nhw, w->const_data_ptr(), scale, bias, residual, sp, act, y.data_ptr(), wsp,
-                      ws_bytes, s) != SS_OK)
-            Py_RETURN_NONE;
-    } catch (const std::exception &) {      // e.g. out of memory: the caller's path meets and reports it again
-        Py_RETURN_NONE;
     }
+    if (call_conv(kind, &d, x->const_data_ptr(), nhw, w->const_data_ptr(), scale, bias, residual, sp, act, y.data_ptr(), wsp,
+                  ws_bytes, s) != SS_OK)
+        Py_RETURN_NONE;
     return give(a[10], y);
 }
 
 // fused(sparse, desc1, x, w1, bias1, stride, pad, act1, desc2, w2, bias2, residual, act2, y) -> y or None
-PyObject *fused(PyObject *, PyObject *const *a, Py_ssize_t n)
+PyObject *fused(PyObject *const *a, Py_ssize_t n)
 {
     int32_t sparse, act1, act2, sp[4], nhw[3];
     ss_weight_desc d1, d2;
@@ -282,15 +278,11 @@ PyObject *fused(PyObject *, PyObject *const *a, Py_ssize_t n)
         residual = r->const_data_ptr();
     }
     at::Tensor y;
-    try {
-        if (!output(a[13], *x, at::IntArrayRef(shape, 4), x->scalar_type(), &y)) Py_RETURN_NONE;
-        const auto fn = sparse ? ss_conv2d_pw_fused_fwd : ss_conv2d_pw_fused_dense_fwd;
-        if (fn(&d1, x->const_data_ptr(), nhw[0], nhw[1], nhw[2], w1->const_data_ptr(), b1, sp[0], sp[1], sp[2], sp[3], act1, &d2,
-               w2->const_data_ptr(), b2, residual, act2, y.data_ptr(), c10::hip::getCurrentHIPStream().stream()) != SS_OK)
-            Py_RETURN_NONE;
-    } catch (const std::exception &) {
+    if (!output(a[13], *x, at::IntArrayRef(shape, 4), x->scalar_type(), &y)) Py_RETURN_NONE;
+    const auto fn = sparse ? ss_conv2d_pw_fused_fwd : ss_conv2d_pw_fused_dense_fwd;
+    if (fn(&d1, x->const_data_ptr(), nhw[0], nhw[1], nhw[2], w1->const_data_ptr(), b1, sp[0], sp[1], sp[2], sp[3], act1, &d2,
+           w2->const_data_ptr(), b2, residual, act2, y.data_ptr(), c10::hip::getCurrentHIPStream().stream()) != SS_OK)
         Py_RETURN_NONE;
-    }
     return give(a[13], y);
 }
 
@@ -298,7 +290,7 @@ PyObject *fused(PyObject *, PyObject *const *a, Py_ssize_t n)
 // pooling and depthwise convolution
 // ---------------------------------------------------------------------------------------------
 // maxpool(x, k, stride, pad, y) -> y or None
-PyObject *maxpool(PyObject *, PyObject *const *a, Py_ssize_t n)
+PyObject *maxpool(PyObject *const *a, Py_ssize_t n)
 {
     int32_t k, s, pad;
     if (n != 5 || !read_int(a[1], &k) || !read_int(a[2], &s) || !read_int(a[3], &pad)) Py_RETURN_NONE;
@@ -309,20 +301,16 @@ PyObject *maxpool(PyObject *, PyObject *const *a, Py_ssize_t n)
     if (h < 0 || w < 0 || x->numel() == 0 || x->size(0) > INT32_MAX || x->size(1) > INT32_MAX || x->size(2) > INT32_MAX || x->size(3) > INT32_MAX)
         Py_RETURN_NONE;
     at::Tensor y;
-    try {
-        if (!output(a[4], *x, {x->size(0), h / s + 1, w / s + 1, x->size(3)}, x->scalar_type(), &y)) Py_RETURN_NONE;
-        if (ss_maxpool2d(x->const_data_ptr(), (int32_t)x->size(0), (int32_t)x->size(1), (int32_t)x->size(2), (int32_t)x->size(3),
-                         x->scalar_type() == at::kHalf ? SS_F16 : SS_BF16, k, s, pad, y.data_ptr(),
-                         c10::hip::getCurrentHIPStream().stream()) != SS_OK)
-            Py_RETURN_NONE;
-    } catch (const std::exception &) {
+    if (!output(a[4], *x, {x->size(0), h / s + 1, w / s + 1, x->size(3)}, x->scalar_type(), &y)) Py_RETURN_NONE;
+    if (ss_maxpool2d(x->const_data_ptr(), (int32_t)x->size(0), (int32_t)x->size(1), (int32_t)x->size(2), (int32_t)x->size(3),
+                     x->scalar_type() == at::kHalf ? SS_F16 : SS_BF16, k, s, pad, y.data_ptr(),
+                     c10::hip::getCurrentHIPStream().stream()) != SS_OK)
         Py_RETURN_NONE;
-    }
     return give(a[4], y);
 }
 
 // dwconv(x, w, bias, pad, act, y) -> y or None
-PyObject *dwconv(PyObject *, PyObject *const *a, Py_ssize_t n)
+PyObject *dwconv(PyObject *const *a, Py_ssize_t n)
 {
     int32_t ph, pw, act;
     if (n != 6 || !read_pair(a[3], &ph, &pw) || !read_int(a[4], &act)) Py_RETURN_NONE;
@@ -336,15 +324,11 @@ PyObject *dwconv(PyObject *, PyObject *const *a, Py_ssize_t n)
     const int64_t ho = x->size(1) + 2 * (int64_t)ph - w->size(0) + 1, wo = x->size(2) + 2 * (int64_t)pw - w->size(1) + 1;
     if (ho <= 0 || wo <= 0) Py_RETURN_NONE;
     at::Tensor y;
-    try {
-        if (!output(a[5], *x, {x->size(0), ho, wo, x->size(3)}, x->scalar_type(), &y)) Py_RETURN_NONE;
-        if (ss_dwconv2d_fwd(x->const_data_ptr(), (int32_t)x->size(0), (int32_t)x->size(1), (int32_t)x->size(2), (int32_t)x->size(3),
-                            x->scalar_type() == at::kHalf ? SS_F16 : SS_BF16, w->const_data_ptr(), bias, (int32_t)w->size(0),
-                            (int32_t)w->size(1), ph, pw, act, y.data_ptr(), c10::hip::getCurrentHIPStream().stream()) != SS_OK)
-            Py_RETURN_NONE;
-    } catch (const std::exception &) {
+    if (!output(a[5], *x, {x->size(0), ho, wo, x->size(3)}, x->scalar_type(), &y)) Py_RETURN_NONE;
+    if (ss_dwconv2d_fwd(x->const_data_ptr(), (int32_t)x->size(0), (int32_t)x->size(1), (int32_t)x->size(2), (int32_t)x->size(3),
+                        x->scalar_type() == at::kHalf ? SS_F16 : SS_BF16, w->const_data_ptr(), bias, (int32_t)w->size(0),
+                        (int32_t)w->size(1), ph, pw, act, y.data_ptr(), c10::hip::getCurrentHIPStream().stream()) != SS_OK)
         Py_RETURN_NONE;
-    }
     return give(a[5], y);
 }
 
@@ -353,7 +337,7 @@ PyObject *dwconv(PyObject *, PyObject *const *a, Py_ssize_t n)
 // ---------------------------------------------------------------------------------------------
 // pack(mode, desc, W, U, M, out) -> out, (SS_ERR_BAD_MASK, row, block), or None; mode 0: compress, 1: update and compress,
 // 2: dense (M may be None)
-PyObject *pack(PyObject *, PyObject *const *a, Py_ssize_t n)
+PyObject *pack(PyObject *const *a, Py_ssize_t n)
 {
     int32_t mode;
     ss_weight_desc d;
@@ -370,31 +354,27 @@ PyObject *pack(PyObject *, PyObject *const *a, Py_ssize_t n)
     size_t need = 0;
     if ((mode == 2 ? ss_dense_bytes(&d, &need) : ss_packed_bytes(&d, &need)) != SS_OK) Py_RETURN_NONE;
     at::Tensor out;
-    try {
-        if (a[5] == Py_None) {
-            out = at::detail::empty_cuda({(int64_t)need}, at::kByte, W->device(), c10::nullopt);
-        } else {
-            const at::Tensor *t = dev_tensor(a[5]);
-            if (!t || t->nbytes() < need) Py_RETURN_NONE;
-            out = *t;
-        }
-        const hipStream_t s = c10::hip::getCurrentHIPStream().stream();
-        const uint8_t *m = M ? static_cast<const uint8_t *>(M->const_data_ptr()) : nullptr;
-        const void *wp = W->const_data_ptr();
-        void *op = out.data_ptr();
-        int st;
-        int32_t bad[2] = {-1, -1};
-        Py_BEGIN_ALLOW_THREADS                  // the compressing calls wait for the stream
-        if (mode == 2) st = ss_dense_pack(&d, wp, m, op, s);
-        else if (mode == 1) st = ss_mask_update_compress(&d, const_cast<void *>(wp), U->const_data_ptr(), m, op, bad, s);
-        else st = ss_mask_compress(&d, wp, m, op, bad, s);
-        Py_END_ALLOW_THREADS
-        // An update that met an invalid mask has already moved the weights and must not run again: its finding is handed on.
-        if (st == SS_ERR_BAD_MASK) return Py_BuildValue("(iii)", st, bad[0], bad[1]);
-        if (st != SS_OK) Py_RETURN_NONE;
-    } catch (const std::exception &) {
-        Py_RETURN_NONE;
+    if (a[5] == Py_None) {
+        out = at::detail::empty_cuda({(int64_t)need}, at::kByte, W->device(), c10::nullopt);
+    } else {
+        const at::Tensor *t = dev_tensor(a[5]);
+        if (!t || t->nbytes() < need) Py_RETURN_NONE;
+        out = *t;
     }
+    const hipStream_t s = c10::hip::getCurrentHIPStream().stream();
+    const uint8_t *m = M ? static_cast<const uint8_t *>(M->const_data_ptr()) : nullptr;
+    const void *wp = W->const_data_ptr(), *up = U ? U->const_data_ptr() : nullptr;
+    void *op = out.data_ptr();
+    int st;
+    int32_t bad[2] = {-1, -1};
+    Py_BEGIN_ALLOW_THREADS                  // the compressing calls wait for the stream (nothing in here throws)
+    if (mode == 2) st = ss_dense_pack(&d, wp, m, op, s);
+    else if (mode == 1) st = ss_mask_update_compress(&d, const_cast<void *>(wp), up, m, op, bad, s);
+    else st = ss_mask_compress(&d, wp, m, op, bad, s);
+    Py_END_ALLOW_THREADS
+    // An update that met an invalid mask has already moved the weights and must not run again: its finding is handed on.
+    if (st == SS_ERR_BAD_MASK) return Py_BuildValue("(iii)", st, bad[0], bad[1]);
+    if (st != SS_OK) Py_RETURN_NONE;
     return give(a[5], out);
 }
 
@@ -521,12 +501,25 @@ PyObject *launch(PyObject *, PyObject *args)
     return o;
 }
 
+// Every entry point runs inside this: what torch throws (a tensor without storage under torch.func, symbolic sizes, no memory)
+// must not leave through the interpreter's C frames, where it would end the process.  The caller's path meets it again and reports it.
+template <PyObject *(*F)(PyObject *const *, Py_ssize_t)>
+PyObject *entry(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    try {
+        return F(a, n);
+    } catch (...) {
+    }
+    PyErr_Clear();                              // (torch's Python errors leave theirs set)
+    Py_RETURN_NONE;
+}
+
 PyMethodDef methods[] = {
-    {"conv", reinterpret_cast<PyCFunction>(conv), METH_FASTCALL, nullptr},
-    {"fused", reinterpret_cast<PyCFunction>(fused), METH_FASTCALL, nullptr},
-    {"maxpool", reinterpret_cast<PyCFunction>(maxpool), METH_FASTCALL, nullptr},
-    {"dwconv", reinterpret_cast<PyCFunction>(dwconv), METH_FASTCALL, nullptr},
-    {"pack", reinterpret_cast<PyCFunction>(pack), METH_FASTCALL, nullptr},
+    {"conv", reinterpret_cast<PyCFunction>(entry<conv>), METH_FASTCALL, nullptr},
+    {"fused", reinterpret_cast<PyCFunction>(entry<fused>), METH_FASTCALL, nullptr},
+    {"maxpool", reinterpret_cast<PyCFunction>(entry<maxpool>), METH_FASTCALL, nullptr},
+    {"dwconv", reinterpret_cast<PyCFunction>(entry<dwconv>), METH_FASTCALL, nullptr},
+    {"pack", reinterpret_cast<PyCFunction>(entry<pack>), METH_FASTCALL, nullptr},
     {"launch", launch, METH_VARARGS, nullptr},
     {nullptr, nullptr, 0, nullptr},
 };
