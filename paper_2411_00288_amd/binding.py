@@ -149,11 +149,9 @@ def ss_dense_bytes(desc: ss_weight_desc) -> int:
     return int(out.value)
 
 
-def _packed_or_raise(r, what):
-    """The packed buffer, or the SSError for the (status, row, block) of an invalid mask."""
-    if type(r) is tuple:
-        raise SSError(r[0], what, detail=(r[1], r[2]))
-    return r
+def _failed(r, what):
+    """Raises the SSError for the (status, row, block) of a call that the compiled path made and that failed: it is not made again."""
+    raise SSError(r[0], what, detail=(r[1], r[2]) if r[0] == SS_ERR_BAD_MASK else None)
 
 
 def ss_mask_compress(desc: ss_weight_desc, W: torch.Tensor, M: torch.Tensor, packed: torch.Tensor | None = None,
@@ -162,7 +160,7 @@ def ss_mask_compress(desc: ss_weight_desc, W: torch.Tensor, M: torch.Tensor, pac
     if stream is None:
         r = _native.pack(0, desc, W, None, M, packed)
         if r is not None:
-            return _packed_or_raise(r, "ss_mask_compress")
+            return r if type(r) is not tuple else _failed(r, "ss_mask_compress")
     K = desc.cin * desc.kh * desc.kw
     if W is not None and W.numel() != desc.cout * K or M is not None and M.numel() != desc.cout * K:
         raise SSError(SS_ERR_INVALID_ARG, "ss_mask_compress: W/M size does not match the descriptor")
@@ -184,7 +182,7 @@ def ss_mask_update_compress(desc: ss_weight_desc, W: torch.Tensor, U: torch.Tens
     if stream is None:
         r = _native.pack(1, desc, W, U, M, packed)
         if r is not None:
-            return _packed_or_raise(r, "ss_mask_update_compress")
+            return r if type(r) is not tuple else _failed(r, "ss_mask_update_compress")
     K = desc.cin * desc.kh * desc.kw
     if W is None or U is None or M is None or W.numel() != desc.cout * K or U.numel() != desc.cout * K or \
             M.numel() != desc.cout * K or U.dtype != W.dtype:
@@ -219,7 +217,7 @@ def ss_dense_pack(desc: ss_weight_desc, W: torch.Tensor, M: torch.Tensor | None,
     if stream is None:
         r = _native.pack(2, desc, W, None, M, dense)
         if r is not None:
-            return r
+            return r if type(r) is not tuple else _failed(r, "ss_dense_pack")
     K = desc.cin * desc.kh * desc.kw
     if W.numel() != desc.cout * K or (M is not None and M.numel() != desc.cout * K):
         raise SSError(SS_ERR_INVALID_ARG, "ss_dense_pack: W/M size does not match the descriptor")
@@ -378,7 +376,7 @@ def ss_conv2d_fwd(desc, x, packed, bias=None, stride=(1, 1), pad=(0, 0), act=SS_
     if stream is None:
         r = _native.conv(0, desc, x, packed, None, bias, None, stride, pad, act, y, workspace)
         if r is not None:
-            return r
+            return r if type(r) is not tuple else _failed(r, "ss_conv2d_fwd")
     return _conv(_lib.ss_conv2d_fwd, "ss_conv2d_fwd", desc, x, packed, bias, stride, pad, act, y, workspace, stream)
 
 
@@ -412,7 +410,7 @@ def ss_conv2d_dense_fwd(desc, x, dense, bias=None, stride=(1, 1), pad=(0, 0), ac
     if stream is None:
         r = _native.conv(1, desc, x, dense, None, bias, None, stride, pad, act, y, workspace)
         if r is not None:
-            return r
+            return r if type(r) is not tuple else _failed(r, "ss_conv2d_dense_fwd")
     return _conv(_lib.ss_conv2d_dense_fwd, "ss_conv2d_dense_fwd", desc, x, dense, bias, stride, pad, act, y,
                  workspace, stream)
 
@@ -423,7 +421,7 @@ def ss_conv2d_res_fwd(desc, x, packed, bias=None, residual=None, stride=(1, 1), 
     if stream is None:
         r = _native.conv(0, desc, x, packed, None, bias, residual, stride, pad, act, y, workspace)
         if r is not None:
-            return r
+            return r if type(r) is not tuple else _failed(r, "ss_conv2d_res_fwd")
     return _conv(_lib.ss_conv2d_res_fwd, "ss_conv2d_res_fwd", desc, x, packed, bias, stride, pad, act, y, workspace,
                  stream, residual, True)
 
@@ -434,7 +432,7 @@ def ss_conv2d_dense_res_fwd(desc, x, dense, bias=None, residual=None, stride=(1,
     if stream is None:
         r = _native.conv(1, desc, x, dense, None, bias, residual, stride, pad, act, y, workspace)
         if r is not None:
-            return r
+            return r if type(r) is not tuple else _failed(r, "ss_conv2d_dense_res_fwd")
     return _conv(_lib.ss_conv2d_dense_res_fwd, "ss_conv2d_dense_res_fwd", desc, x, dense, bias, stride, pad, act, y,
                  workspace, stream, residual, True)
 
@@ -481,7 +479,7 @@ def ss_conv2d_q8_fwd(desc, x, packed, scale=None, bias=None, stride=(1, 1), pad=
     if stream is None:
         r = _native.conv(2, desc, x, packed, scale, bias, None, stride, pad, act, y, workspace)
         if r is not None:
-            return r
+            return r if type(r) is not tuple else _failed(r, "ss_conv2d_q8_fwd")
     args, y, _ws = _q8_args("ss_conv2d_q8_fwd", desc, x, packed, scale, bias, stride, pad, act, y, workspace)
     st = _lib.ss_conv2d_q8_fwd(*args, _stream_ptr(stream))
     if st != SS_OK:
@@ -495,7 +493,7 @@ def ss_conv2d_q8_dense_fwd(desc, x, dense, scale=None, bias=None, stride=(1, 1),
     if stream is None:
         r = _native.conv(3, desc, x, dense, scale, bias, None, stride, pad, act, y, workspace)
         if r is not None:
-            return r
+            return r if type(r) is not tuple else _failed(r, "ss_conv2d_q8_dense_fwd")
     args, y, _ws = _q8_args("ss_conv2d_q8_dense_fwd", desc, x, dense, scale, bias, stride, pad, act, y, workspace)
     st = _lib.ss_conv2d_q8_dense_fwd(*args, _stream_ptr(stream))
     if st != SS_OK:
@@ -546,7 +544,7 @@ def ss_conv2d_pw_fused_fwd(desc1, x, packed1, bias1, stride, pad, act1, desc2, p
     """k x k masked convolution followed by a 1x1 masked convolution (+ residual), the intermediate kept on chip."""
     r = _native.fused(1, desc1, x, packed1, bias1, stride, pad, act1, desc2, packed2, bias2, residual, act2, y)
     if r is not None:
-        return r
+        return r if type(r) is not tuple else _failed(r, "ss_conv2d_pw_fused_fwd")
     launch, y = prepare_conv2d_pw_fused(desc1, x, packed1, bias1, stride, pad, act1, desc2, packed2, bias2, residual,
                                         act2, y, sparse=True)
     launch()
@@ -558,7 +556,7 @@ def ss_conv2d_pw_fused_dense_fwd(desc1, x, dense1, bias1, stride, pad, act1, des
     """The dense twin of ss_conv2d_pw_fused_fwd."""
     r = _native.fused(0, desc1, x, dense1, bias1, stride, pad, act1, desc2, dense2, bias2, residual, act2, y)
     if r is not None:
-        return r
+        return r if type(r) is not tuple else _failed(r, "ss_conv2d_pw_fused_dense_fwd")
     launch, y = prepare_conv2d_pw_fused(desc1, x, dense1, bias1, stride, pad, act1, desc2, dense2, bias2, residual,
                                         act2, y, sparse=False)
     launch()
@@ -571,7 +569,7 @@ def ss_maxpool2d(x: torch.Tensor, k: int = 3, stride: int = 2, pad: int = 1, y: 
     if stream is None:
         r = _native.maxpool(x, k, stride, pad, y)
         if r is not None:
-            return r
+            return r if type(r) is not tuple else _failed(r, "ss_maxpool2d")
     if x is None or x.dim() != 4 or x.dtype not in _T16 or stride <= 0:
         raise SSError(SS_ERR_INVALID_ARG, "ss_maxpool2d: x must be a 16-bit NHWC tensor")
     N, H, W, C = x.shape
@@ -609,7 +607,7 @@ def ss_dwconv2d_fwd(x: torch.Tensor, w: torch.Tensor, bias: torch.Tensor | None 
     if stream is None:
         r = _native.dwconv(x, w, bias, pad, act, y)
         if r is not None:
-            return r
+            return r if type(r) is not tuple else _failed(r, "ss_dwconv2d_fwd")
     if x is None or w is None or x.dim() != 4 or w.dim() != 3 or w.shape[2] != x.shape[3] or w.dtype != x.dtype or \
             x.dtype not in (torch.float16, torch.bfloat16):
         raise SSError(SS_ERR_INVALID_ARG, "ss_dwconv2d_fwd: x must be NHWC 16-bit and w [kh, kw, C] of the same dtype")

@@ -8,7 +8,9 @@
 //
 // Contract with binding.py: a function here either does the whole call and returns its result, or does nothing and
 // returns None.  None means "not the plain good case" -- a wrong type, size or device, an option that is not handled
-// here, or an error status -- and the caller then takes its own checked path, which finds and reports the reason.
+// here, or arguments that the library refuses -- and the caller then takes its own checked path, which finds and reports the
+// reason.  A call that may have enqueued its kernel and failed all the same returns (status, row, block): made again, an
+// update would move the weights twice, and a residual that is also the output would be added twice.
 #include <Python.h>
 #include <ATen/ATen.h>
 #include <ATen/hip/EmptyTensor.h>
@@ -106,13 +108,27 @@ bool output(PyObject *o, const at::Tensor &x, at::IntArrayRef shape, at::ScalarT
     return true;
 }
 
+// The result of a call that is enqueued: from here on nothing may end in None.
 PyObject *give(PyObject *o, const at::Tensor &y)
 {
     if (o != Py_None) {
         Py_INCREF(o);
         return o;
     }
-    return THPVariable_Wrap(y);
+    try {
+        return THPVariable_Wrap(y);
+    } catch (const std::exception &e) {
+        if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, e.what());
+        return nullptr;
+    }
+}
+
+// The answer for a status other than SS_OK (bad: row and block of an invalid mask, or NULL): the library checks its arguments before
+// it enqueues anything, the other two statuses come afterwards.
+PyObject *refuse(int st, const int32_t *bad = nullptr)
+{
+    if (st != SS_ERR_HIP && st != SS_ERR_BAD_MASK) Py_RETURN_NONE;
+    return Py_BuildValue("(iii)", st, bad ? bad[0] : -1, bad ? bad[1] : -1);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -209,7 +225,7 @@ bool weights_fit(const ss_weight_desc &d, bool sparse, const at::Tensor *w)
     return w && (sparse ? ss_packed_bytes(&d, &need) : ss_dense_bytes(&d, &need)) == SS_OK && w->nbytes() >= need;
 }
 
-// conv(kind, desc, x, weights, scale, bias, residual, stride, pad, act, y, workspace) -> y or None
+// conv(kind, desc, x, weights, scale, bias, residual, stride, pad, act, y, workspace) -> y, (status, row, block) or None
 PyObject *conv(PyObject *const *a, Py_ssize_t n)
 {
     int32_t kind, act, sp[4], nhw[3];
@@ -250,13 +266,12 @@ PyObject *conv(PyObject *const *a, Py_ssize_t n)
             ws_bytes = ws.nbytes();
         }
     }
-    if (call_conv(kind, &d, x->const_data_ptr(), nhw, w->const_data_ptr(), scale, bias, residual, sp, act, y.data_ptr(), wsp,
-                  ws_bytes, s) != SS_OK)
-        Py_RETURN_NONE;
-    return give(a[10], y);
+    const int st = call_conv(kind, &d, x->const_data_ptr(), nhw, w->const_data_ptr(), scale, bias, residual, sp, act, y.data_ptr(),
+                             wsp, ws_bytes, s);
+    return st == SS_OK ? give(a[10], y) : refuse(st);
 }
 
-// fused(sparse, desc1, x, w1, bias1, stride, pad, act1, desc2, w2, bias2, residual, act2, y) -> y or None
+// fused(sparse, desc1, x, w1, bias1, stride, pad, act1, desc2, w2, bias2, residual, act2, y) -> y, (status, row, block) or None
 PyObject *fused(PyObject *const *a, Py_ssize_t n)
 {
     int32_t sparse, act1, act2, sp[4], nhw[3];
@@ -280,16 +295,15 @@ PyObject *fused(PyObject *const *a, Py_ssize_t n)
     at::Tensor y;
     if (!output(a[13], *x, at::IntArrayRef(shape, 4), x->scalar_type(), &y)) Py_RETURN_NONE;
     const auto fn = sparse ? ss_conv2d_pw_fused_fwd : ss_conv2d_pw_fused_dense_fwd;
-    if (fn(&d1, x->const_data_ptr(), nhw[0], nhw[1], nhw[2], w1->const_data_ptr(), b1, sp[0], sp[1], sp[2], sp[3], act1, &d2,
-           w2->const_data_ptr(), b2, residual, act2, y.data_ptr(), c10::hip::getCurrentHIPStream().stream()) != SS_OK)
-        Py_RETURN_NONE;
-    return give(a[13], y);
+    const int st = fn(&d1, x->const_data_ptr(), nhw[0], nhw[1], nhw[2], w1->const_data_ptr(), b1, sp[0], sp[1], sp[2], sp[3], act1,
+                      &d2, w2->const_data_ptr(), b2, residual, act2, y.data_ptr(), c10::hip::getCurrentHIPStream().stream());
+    return st == SS_OK ? give(a[13], y) : refuse(st);
 }
 
 // ---------------------------------------------------------------------------------------------
 // pooling and depthwise convolution
 // ---------------------------------------------------------------------------------------------
-// maxpool(x, k, stride, pad, y) -> y or None
+// maxpool(x, k, stride, pad, y) -> y, (status, row, block) or None
 PyObject *maxpool(PyObject *const *a, Py_ssize_t n)
 {
     int32_t k, s, pad;
@@ -302,14 +316,13 @@ PyObject *maxpool(PyObject *const *a, Py_ssize_t n)
         Py_RETURN_NONE;
     at::Tensor y;
     if (!output(a[4], *x, {x->size(0), h / s + 1, w / s + 1, x->size(3)}, x->scalar_type(), &y)) Py_RETURN_NONE;
-    if (ss_maxpool2d(x->const_data_ptr(), (int32_t)x->size(0), (int32_t)x->size(1), (int32_t)x->size(2), (int32_t)x->size(3),
-                     x->scalar_type() == at::kHalf ? SS_F16 : SS_BF16, k, s, pad, y.data_ptr(),
-                     c10::hip::getCurrentHIPStream().stream()) != SS_OK)
-        Py_RETURN_NONE;
-    return give(a[4], y);
+    const int st = ss_maxpool2d(x->const_data_ptr(), (int32_t)x->size(0), (int32_t)x->size(1), (int32_t)x->size(2), (int32_t)x->size(3),
+                                x->scalar_type() == at::kHalf ? SS_F16 : SS_BF16, k, s, pad, y.data_ptr(),
+                                c10::hip::getCurrentHIPStream().stream());
+    return st == SS_OK ? give(a[4], y) : refuse(st);
 }
 
-// dwconv(x, w, bias, pad, act, y) -> y or None
+// dwconv(x, w, bias, pad, act, y) -> y, (status, row, block) or None
 PyObject *dwconv(PyObject *const *a, Py_ssize_t n)
 {
     int32_t ph, pw, act;
@@ -325,17 +338,17 @@ PyObject *dwconv(PyObject *const *a, Py_ssize_t n)
     if (ho <= 0 || wo <= 0) Py_RETURN_NONE;
     at::Tensor y;
     if (!output(a[5], *x, {x->size(0), ho, wo, x->size(3)}, x->scalar_type(), &y)) Py_RETURN_NONE;
-    if (ss_dwconv2d_fwd(x->const_data_ptr(), (int32_t)x->size(0), (int32_t)x->size(1), (int32_t)x->size(2), (int32_t)x->size(3),
-                        x->scalar_type() == at::kHalf ? SS_F16 : SS_BF16, w->const_data_ptr(), bias, (int32_t)w->size(0),
-                        (int32_t)w->size(1), ph, pw, act, y.data_ptr(), c10::hip::getCurrentHIPStream().stream()) != SS_OK)
-        Py_RETURN_NONE;
-    return give(a[5], y);
+    const int st = ss_dwconv2d_fwd(x->const_data_ptr(), (int32_t)x->size(0), (int32_t)x->size(1), (int32_t)x->size(2),
+                                   (int32_t)x->size(3), x->scalar_type() == at::kHalf ? SS_F16 : SS_BF16, w->const_data_ptr(), bias,
+                                   (int32_t)w->size(0), (int32_t)w->size(1), ph, pw, act, y.data_ptr(),
+                                   c10::hip::getCurrentHIPStream().stream());
+    return st == SS_OK ? give(a[5], y) : refuse(st);
 }
 
 // ---------------------------------------------------------------------------------------------
 // packing
 // ---------------------------------------------------------------------------------------------
-// pack(mode, desc, W, U, M, out) -> out, (SS_ERR_BAD_MASK, row, block), or None; mode 0: compress, 1: update and compress,
+// pack(mode, desc, W, U, M, out) -> out, (status, row, block) or None; mode 0: compress, 1: update and compress,
 // 2: dense (M may be None)
 PyObject *pack(PyObject *const *a, Py_ssize_t n)
 {
@@ -372,10 +385,7 @@ PyObject *pack(PyObject *const *a, Py_ssize_t n)
     else if (mode == 1) st = ss_mask_update_compress(&d, const_cast<void *>(wp), up, m, op, bad, s);
     else st = ss_mask_compress(&d, wp, m, op, bad, s);
     Py_END_ALLOW_THREADS
-    // An update that met an invalid mask has already moved the weights and must not run again: its finding is handed on.
-    if (st == SS_ERR_BAD_MASK) return Py_BuildValue("(iii)", st, bad[0], bad[1]);
-    if (st != SS_OK) Py_RETURN_NONE;
-    return give(a[5], out);
+    return st == SS_OK ? give(a[5], out) : refuse(st, bad);
 }
 
 // ---------------------------------------------------------------------------------------------

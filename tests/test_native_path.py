@@ -73,3 +73,36 @@ def test_compiled_path_declines_and_the_checked_path_gives_the_reason(fake):
     assert nat.conv(0, f["d"], f["x"]) is None and nat.pack(0) is None and nat.maxpool() is None      # wrong argument counts
     assert nat.conv(0, b"short", f["x"], f["w"], None, None, None, ONE, ONE, 0, None, None) is None
     assert nat.conv(0, f["d"], f["x"], f["w"], None, None, None, [1, 1], ONE, 0, None, None) is None  # a list as stride
+
+
+FAILS = {
+    "conv": lambda t: ss.ss_conv2d_fwd(t, t, t), "conv residual": lambda t: ss.ss_conv2d_res_fwd(t, t, t, None, t),
+    "dense": lambda t: ss.ss_conv2d_dense_fwd(t, t, t), "dense residual": lambda t: ss.ss_conv2d_dense_res_fwd(t, t, t, None, t),
+    "q8": lambda t: ss.ss_conv2d_q8_fwd(t, t, t), "q8 dense": lambda t: ss.ss_conv2d_q8_dense_fwd(t, t, t),
+    "fused": lambda t: ss.ss_conv2d_pw_fused_fwd(t, t, t, None, ONE, ONE, 0, t, t),
+    "fused dense": lambda t: ss.ss_conv2d_pw_fused_dense_fwd(t, t, t, None, ONE, ONE, 0, t, t),
+    "pool": lambda t: ss.ss_maxpool2d(t), "depthwise": lambda t: ss.ss_dwconv2d_fwd(t, t),
+    "compress": lambda t: ss.ss_mask_compress(t, t, t), "update": lambda t: ss.ss_mask_update_compress(t, t, t, t),
+    "dense pack": lambda t: ss.ss_dense_pack(t, t, t),
+}
+
+
+@pytest.mark.parametrize("which", FAILS)
+@pytest.mark.parametrize("answer", [(ss.SS_ERR_HIP, -1, -1), (ss.SS_ERR_BAD_MASK, 3, 5)])
+def test_a_call_that_failed_after_its_launch_is_not_made_again(monkeypatch, which, answer):
+    """Neither through ctypes nor at all: an update that ran twice would have moved the weights twice."""
+    made = []
+    class Native:
+        def __getattr__(self, name):
+            return lambda *a: made.append(name) or answer
+    class Library:
+        def __getattr__(self, name):
+            return made.append(name)
+        def ss_status_string(self, st):
+            return b"status"
+    monkeypatch.setattr(binding, "_native", Native())
+    monkeypatch.setattr(binding, "_lib", Library())
+    with pytest.raises(ss.SSError) as e:
+        FAILS[which](object())
+    assert (e.value.status, e.value.detail) == (answer[0], (3, 5) if answer[0] == ss.SS_ERR_BAD_MASK else None)
+    assert len(made) == 1
