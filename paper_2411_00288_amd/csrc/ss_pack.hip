@@ -369,6 +369,14 @@ static int compress_entry(const ss_weight_desc *desc, void *W, const void *U, co
     TileDims t = tile_dims(desc);
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint8_t *p = static_cast<uint8_t *>(packed);
+    // A call that waits cannot be recorded: under capture the kernel would only run at a replay, and an event that was never
+    // recorded reads as complete, so the mask would pass unseen.  Refused before anything is enqueued.
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+        (void)hipGetLastError();                          // (reported here, not by the next launch)
+        return SS_ERR_HIP;
+    }
+    if (cap != hipStreamCaptureStatusNone) return SS_ERR_HIP;
     Waiter wt;
     if (!take_waiter(&wt)) return SS_ERR_HIP;
     if (i8) st = launch_compress<SS_I8, false>(desc, t, W, nullptr, M, p, wt, s);

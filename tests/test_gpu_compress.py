@@ -186,3 +186,35 @@ def test_dense_pack_reads_rows_of_any_alignment(ss, K, offset):
     got = ss.ss_dense_pack(desc, dev_bits(W, wl.F16)[offset:], torch.from_numpy(M).cuda()[offset:]).cpu().numpy()
     Wm = np.where(M == 1, W, 0).astype(np.uint16)[offset:].reshape(cout, K)
     assert np.array_equal(got, dl.tile_dense(Wm, cin=K, kh=1, kw=1, dtype=wl.F16, korder=wl.K_CRS))
+
+
+@pytest.mark.parametrize("mode", ["global", "thread_local", "relaxed"])
+def test_packing_calls_that_wait_are_refused_under_capture(ss, mode):
+    """A recorded compression could report no mask: refused with nothing recorded, and the capture goes on."""
+    L = wl.Layer("t", N=1, H=4, W=4, cin=64, cout=64, kh=1, kw=1, dtype=wl.BF16, mask="logits", seed=3)
+    d = wl.make_inputs(L)
+    desc = layer_desc(ss, L)
+    W, M = dev_bits(d["W"], L.dtype), torch.from_numpy(d["M"]).cuda()
+    U, W_before = torch.ones_like(W), W.clone()
+    packed = ss.ss_mask_compress(desc, W, M)
+    want = packed.clone()
+    launch, y = ss.prepare_conv2d(desc, dev_bits(d["x"], L.dtype), packed, None, (1, 1), (0, 0), L.act)
+    launch()
+    torch.cuda.synchronize()
+    eager = host_bits(y).copy()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, capture_error_mode=mode):
+        launch()
+        for call in (lambda: ss.ss_mask_compress(desc, W, M, packed=packed), lambda: ss.ss_mask_update_compress(desc, W, U, M, packed=packed),
+                     lambda: ss.ss_mask_update_compress(desc, W, U, M, packed=packed, stream=torch.cuda.current_stream())):
+            with pytest.raises(ss.SSError) as e:
+                call()
+            assert e.value.status == ss.SS_ERR_HIP
+    for _ in range(3):
+        y.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(host_bits(y), eager)
+        assert torch.equal(W, W_before) and torch.equal(packed, want)
+    ss.ss_mask_update_compress(desc, W, U, M, packed=packed)                 # and the calls still work afterwards
+    assert np.array_equal(host_bits(W), oracle.update(d["W"], host_bits(U), L.dtype))
