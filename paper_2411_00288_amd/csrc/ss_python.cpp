@@ -131,6 +131,17 @@ PyObject *refuse(int st, const int32_t *bad = nullptr)
     return Py_BuildValue("(iii)", st, bad ? bad[0] : -1, bad ? bad[1] : -1);
 }
 
+// A call into the library with the interpreter lock given up, as ctypes does it: a launch blocks while the stream's queue is full,
+// and a compression waits.  The operands belong to the caller's arguments or to tensors held here; nothing in the library throws.
+template <typename F>
+int unlocked(F &&f)
+{
+    PyThreadState *const ts = PyEval_SaveThread();
+    const int st = f();
+    PyEval_RestoreThread(ts);
+    return st;
+}
+
 // ---------------------------------------------------------------------------------------------
 // Workspaces of the split reduction for callers that hand none over.  A workspace starts zero and every call hands its
 // ticket counters back at zero, so one per stream serves all calls on that stream; calls on different streams never
@@ -266,8 +277,9 @@ PyObject *conv(PyObject *const *a, Py_ssize_t n)
             ws_bytes = ws.nbytes();
         }
     }
-    const int st = call_conv(kind, &d, x->const_data_ptr(), nhw, w->const_data_ptr(), scale, bias, residual, sp, act, y.data_ptr(),
-                             wsp, ws_bytes, s);
+    const void *xp = x->const_data_ptr(), *wp = w->const_data_ptr();
+    void *yp = y.data_ptr();
+    const int st = unlocked([&] { return call_conv(kind, &d, xp, nhw, wp, scale, bias, residual, sp, act, yp, wsp, ws_bytes, s); });
     return st == SS_OK ? give(a[10], y) : refuse(st);
 }
 
@@ -295,8 +307,12 @@ PyObject *fused(PyObject *const *a, Py_ssize_t n)
     at::Tensor y;
     if (!output(a[13], *x, at::IntArrayRef(shape, 4), x->scalar_type(), &y)) Py_RETURN_NONE;
     const auto fn = sparse ? ss_conv2d_pw_fused_fwd : ss_conv2d_pw_fused_dense_fwd;
-    const int st = fn(&d1, x->const_data_ptr(), nhw[0], nhw[1], nhw[2], w1->const_data_ptr(), b1, sp[0], sp[1], sp[2], sp[3], act1,
-                      &d2, w2->const_data_ptr(), b2, residual, act2, y.data_ptr(), c10::hip::getCurrentHIPStream().stream());
+    const void *xp = x->const_data_ptr(), *w1p = w1->const_data_ptr(), *w2p = w2->const_data_ptr();
+    void *yp = y.data_ptr();
+    const hipStream_t s = c10::hip::getCurrentHIPStream().stream();
+    const int st = unlocked([&] {
+        return fn(&d1, xp, nhw[0], nhw[1], nhw[2], w1p, b1, sp[0], sp[1], sp[2], sp[3], act1, &d2, w2p, b2, residual, act2, yp, s);
+    });
     return st == SS_OK ? give(a[13], y) : refuse(st);
 }
 
@@ -316,9 +332,12 @@ PyObject *maxpool(PyObject *const *a, Py_ssize_t n)
         Py_RETURN_NONE;
     at::Tensor y;
     if (!output(a[4], *x, {x->size(0), h / s + 1, w / s + 1, x->size(3)}, x->scalar_type(), &y)) Py_RETURN_NONE;
-    const int st = ss_maxpool2d(x->const_data_ptr(), (int32_t)x->size(0), (int32_t)x->size(1), (int32_t)x->size(2), (int32_t)x->size(3),
-                                x->scalar_type() == at::kHalf ? SS_F16 : SS_BF16, k, s, pad, y.data_ptr(),
-                                c10::hip::getCurrentHIPStream().stream());
+    const int32_t d[4] = {(int32_t)x->size(0), (int32_t)x->size(1), (int32_t)x->size(2), (int32_t)x->size(3)};
+    const int32_t dtype = x->scalar_type() == at::kHalf ? SS_F16 : SS_BF16;
+    const void *xp = x->const_data_ptr();
+    void *yp = y.data_ptr();
+    const hipStream_t stream = c10::hip::getCurrentHIPStream().stream();
+    const int st = unlocked([&] { return ss_maxpool2d(xp, d[0], d[1], d[2], d[3], dtype, k, s, pad, yp, stream); });
     return st == SS_OK ? give(a[4], y) : refuse(st);
 }
 
@@ -338,10 +357,12 @@ PyObject *dwconv(PyObject *const *a, Py_ssize_t n)
     if (ho <= 0 || wo <= 0) Py_RETURN_NONE;
     at::Tensor y;
     if (!output(a[5], *x, {x->size(0), ho, wo, x->size(3)}, x->scalar_type(), &y)) Py_RETURN_NONE;
-    const int st = ss_dwconv2d_fwd(x->const_data_ptr(), (int32_t)x->size(0), (int32_t)x->size(1), (int32_t)x->size(2),
-                                   (int32_t)x->size(3), x->scalar_type() == at::kHalf ? SS_F16 : SS_BF16, w->const_data_ptr(), bias,
-                                   (int32_t)w->size(0), (int32_t)w->size(1), ph, pw, act, y.data_ptr(),
-                                   c10::hip::getCurrentHIPStream().stream());
+    const int32_t d[4] = {(int32_t)x->size(0), (int32_t)x->size(1), (int32_t)x->size(2), (int32_t)x->size(3)};
+    const int32_t dtype = x->scalar_type() == at::kHalf ? SS_F16 : SS_BF16, kh = (int32_t)w->size(0), kw = (int32_t)w->size(1);
+    const void *xp = x->const_data_ptr(), *wp = w->const_data_ptr();
+    void *yp = y.data_ptr();
+    const hipStream_t s = c10::hip::getCurrentHIPStream().stream();
+    const int st = unlocked([&] { return ss_dwconv2d_fwd(xp, d[0], d[1], d[2], d[3], dtype, wp, bias, kh, kw, ph, pw, act, yp, s); });
     return st == SS_OK ? give(a[5], y) : refuse(st);
 }
 
@@ -378,13 +399,12 @@ PyObject *pack(PyObject *const *a, Py_ssize_t n)
     const uint8_t *m = M ? static_cast<const uint8_t *>(M->const_data_ptr()) : nullptr;
     const void *wp = W->const_data_ptr(), *up = U ? U->const_data_ptr() : nullptr;
     void *op = out.data_ptr();
-    int st;
     int32_t bad[2] = {-1, -1};
-    Py_BEGIN_ALLOW_THREADS                  // the compressing calls wait for the stream (nothing in here throws)
-    if (mode == 2) st = ss_dense_pack(&d, wp, m, op, s);
-    else if (mode == 1) st = ss_mask_update_compress(&d, const_cast<void *>(wp), up, m, op, bad, s);
-    else st = ss_mask_compress(&d, wp, m, op, bad, s);
-    Py_END_ALLOW_THREADS
+    const int st = unlocked([&] {               // (the compressing calls wait for the stream)
+        if (mode == 2) return ss_dense_pack(&d, wp, m, op, s);
+        if (mode == 1) return ss_mask_update_compress(&d, const_cast<void *>(wp), up, m, op, bad, s);
+        return ss_mask_compress(&d, wp, m, op, bad, s);
+    });
     return st == SS_OK ? give(a[5], out) : refuse(st, bad);
 }
 
@@ -417,16 +437,15 @@ PyObject *launch_call(PyObject *self, PyObject *const *, size_t, PyObject *)
         PyErr_SetString(PyExc_RuntimeError, e.what());
         return nullptr;
     }
-    int st;
-    if (l->kind <= kQ8Dense) {
-        st = call_conv(l->kind, &l->d1, l->x, l->nhw, l->w1, l->scale, l->b1, l->residual, l->sp, l->act1, l->y, l->ws, l->ws_bytes, s);
-    } else if (l->kind == 6) {
-        st = ss_maxpool2d(l->x, l->nhw[0], l->nhw[1], l->nhw[2], l->pool[0], l->pool[1], l->pool[2], l->sp[0], l->sp[2], l->y, s);
-    } else {
+    const int st = unlocked([&] {
+        if (l->kind <= kQ8Dense)
+            return call_conv(l->kind, &l->d1, l->x, l->nhw, l->w1, l->scale, l->b1, l->residual, l->sp, l->act1, l->y, l->ws, l->ws_bytes, s);
+        if (l->kind == 6)
+            return ss_maxpool2d(l->x, l->nhw[0], l->nhw[1], l->nhw[2], l->pool[0], l->pool[1], l->pool[2], l->sp[0], l->sp[2], l->y, s);
         const auto fn = l->kind == 4 ? ss_conv2d_pw_fused_fwd : ss_conv2d_pw_fused_dense_fwd;
-        st = fn(&l->d1, l->x, l->nhw[0], l->nhw[1], l->nhw[2], l->w1, l->b1, l->sp[0], l->sp[1], l->sp[2], l->sp[3], l->act1, &l->d2,
-                l->w2, l->b2, l->residual, l->act2, l->y, s);
-    }
+        return fn(&l->d1, l->x, l->nhw[0], l->nhw[1], l->nhw[2], l->w1, l->b1, l->sp[0], l->sp[1], l->sp[2], l->sp[3], l->act1, &l->d2,
+                  l->w2, l->b2, l->residual, l->act2, l->y, s);
+    });
     if (st != SS_OK) return PyObject_CallFunction(l->on_error, "i", st);
     Py_RETURN_NONE;
 }
