@@ -3,7 +3,6 @@
 #include "ss_internal.h"
 #include <hip/hip_ext.h>
 #include <mutex>
-#include <vector>
 
 namespace ss {
 
@@ -285,20 +284,17 @@ extern "C" int ss_dense_bytes(const ss_weight_desc *desc, size_t *dense_bytes)
 // no copy from the device) and an event that completes with the kernel itself (given to the launch, so no marker follows
 // the kernel; polled: 9.4 us from launch to return for a small kernel, against 11.9 with hipStreamSynchronize and about 30 in
 // all with the header launch and the copy of the status word that this replaces).  Handed out one per call in flight and
-// kept for the next.
+// kept for the next, in an array: nothing here may throw through the C entry.
 namespace {
 struct Waiter {
     volatile uint32_t *bad = nullptr;
     hipEvent_t done = nullptr;
     int device = -1;
 };
-constexpr size_t kKeptWaiters = 64;
+constexpr int kKeptWaiters = 64;
 std::mutex waiter_mutex;
-std::vector<Waiter> &waiters()
-{
-    static auto *v = new std::vector<Waiter>;             // (not destroyed: no HIP calls while the process ends)
-    return *v;
-}
+Waiter kept_waiters[kKeptWaiters];
+int n_kept_waiters = 0;
 
 bool take_waiter(Waiter *w)
 {
@@ -306,11 +302,10 @@ bool take_waiter(Waiter *w)
     if (hipGetDevice(&dev) != hipSuccess) return false;
     {
         const std::lock_guard<std::mutex> lock(waiter_mutex);
-        auto &v = waiters();
-        for (size_t i = v.size(); i-- > 0;)
-            if (v[i].device == dev) {
-                *w = v[i];
-                v.erase(v.begin() + (long)i);
+        for (int i = n_kept_waiters; i-- > 0;)
+            if (kept_waiters[i].device == dev) {
+                *w = kept_waiters[i];
+                kept_waiters[i] = kept_waiters[--n_kept_waiters];
                 *w->bad = 0;
                 return true;
             }
@@ -331,8 +326,8 @@ void give_waiter(const Waiter &w)
 {
     {
         const std::lock_guard<std::mutex> lock(waiter_mutex);
-        if (waiters().size() < kKeptWaiters) {
-            waiters().push_back(w);
+        if (n_kept_waiters < kKeptWaiters) {
+            kept_waiters[n_kept_waiters++] = w;
             return;
         }
     }
