@@ -2,7 +2,9 @@
 // Integer / bit work only: no floating-point instruction touches a weight.
 #include "ss_internal.h"
 #include <hip/hip_ext.h>
+#include <chrono>
 #include <mutex>
+#include <thread>
 
 namespace ss {
 
@@ -292,6 +294,7 @@ struct Waiter {
     int device = -1;
 };
 constexpr int kKeptWaiters = 64;
+constexpr int kPollMicroseconds = 1000;
 std::mutex waiter_mutex;
 Waiter kept_waiters[kKeptWaiters];
 int n_kept_waiters = 0;
@@ -346,8 +349,14 @@ static int launch_compress(const ss_weight_desc *desc, const TileDims &t, void *
     hipExtLaunchKernelGGL((compress_kernel<DT, UPD>), dim3((unsigned)blocks), dim3(256), 0, s, nullptr, w.done, 0, W, U, M, packed,
                           desc->cout, t.K, t.Mt, t.Ks, t.Kp, pack_header(kMagicSparse, desc, t), const_cast<uint32_t *>(w.bad));
     if (hipGetLastError() != hipSuccess) return SS_ERR_HIP;
+    // Polled without a pause for as long as packing itself takes.  A longer wait is for earlier work on the stream, which may take
+    // any time: it sleeps a sixteenth of the time waited so far between two looks.  (hipEventSynchronize and hipStreamSynchronize keep
+    // the core busy throughout, with hipEventBlockingSync too: behind 300 ms of work 300 ms of processor time, 1.3 here.)
+    const auto since = std::chrono::steady_clock::now();
     hipError_t e;
     while ((e = hipEventQuery(w.done)) == hipErrorNotReady) {
+        const auto waited = std::chrono::steady_clock::now() - since;
+        if (waited > std::chrono::microseconds(kPollMicroseconds)) std::this_thread::sleep_for(waited / 16);
     }
     return e == hipSuccess ? SS_OK : SS_ERR_HIP;
 }

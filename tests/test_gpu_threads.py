@@ -71,6 +71,21 @@ def test_a_launch_into_a_full_queue_lets_other_threads_run(ss, how):
     assert other.worst < longest / 2                 # (the lock held: as long as the launch itself)
 
 
+def test_a_packing_call_that_waits_lets_other_threads_run_and_sleeps(ss):
+    L = _layer(seed=1)
+    d = wl.make_inputs(L)
+    desc, W, M = layer_desc(ss, L), dev_bits(d["W"], L.dtype), torch.from_numpy(d["M"]).cuda()
+    want = ss.ss_mask_compress(desc, W, M)
+    _sleep(0.3)
+    wall, cpu = time.perf_counter(), time.thread_time()
+    with _Ticker() as other:
+        got = ss.ss_mask_compress(desc, W, M)
+    wall, cpu = time.perf_counter() - wall, time.thread_time() - cpu
+    assert torch.equal(got, want)
+    assert wall > 0.1 and other.worst < wall / 2
+    assert cpu < wall / 2                            # (polling throughout: all of it)
+
+
 def test_concurrent_calls_on_their_own_streams(ss):
     """Packing (pinned words and events handed out per call) and a split reduction (a workspace per stream) from eight threads."""
     L = _layer(N=3, H=20, W=20, cin=512, cout=512, kh=3, kw=3, pad=1, seed=2)
