@@ -277,7 +277,7 @@ void conv_image_kernel(ConvParams p, int tiles_h, int tiles_w, int ntiles)
                 }
             }
         };
-        if (p.act == SS_ACT_GELU) write_out([](float v) { return gelu_cdf(v); });
+        if (p.act == SS_ACT_GELU) write_out([](float v) { return gelu_cdf<DT>(v); });
         else write_out([&](float v) { return floor_at(v, relu_floor); });      // ReLU, or the identity with a floor of -inf (a NaN passes)
         lds_barrier();                               // every wave is done with the patch
         if (tnext >= ntiles) break;

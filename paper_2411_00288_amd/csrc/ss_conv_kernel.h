@@ -159,24 +159,44 @@ __device__ __forceinline__ float widen(uint16_t bits)
 
 // GELU z * Phi(z) with the exact standard normal CDF.  With a = |z| and h = Phi(-a):
 //     z >= 0:  z (1 - h) = z - a h        z < 0:  z h = -a h        i.e.  gelu(z) = max(z, 0) - a h,
-// which needs no select.  log2 Phi(-a) is smooth and close to a parabola: a polynomial of degree 8, fitted on [0, 6] for the
-// smallest largest error of Phi (iteratively reweighted least squares; relative errors below Phi = 2e-4 weighted as there),
-// and one exp2.  |error of Phi| < 1e-7, relative error 2e-7 at a = 1, 2e-5 at 3, 2e-4 at 5 and decaying to 0 beyond the fit (its leading
-// coefficient is negative): below fp32 round-off of the sum in front of it and three orders under the 16-bit output's.
-// Ten full-rate instructions and one quarter-rate one; the rational form 7.1.26 of Abramowitz & Stegun used before takes twelve and
-// two (80 against 56 clocks per wave) and is less accurate in the tail (5e-4 at 4).  (A NaN stays a NaN.)
+// which needs no select.  log2 Phi(-a) is smooth and close to a parabola: a polynomial and one exp2.  Two fits, each as long as
+// the values of its output type ODT ask for (a negative leading coefficient takes either to 0 behind its range):
+//   binary16   a h rounds to 0 from a = 5.5 on: degree 8, fitted on [0, 6].  Ten full-rate instructions and one quarter-rate one
+//              (56 clocks per wave).
+//   bfloat16   holds the whole lower tail: degree 10, fitted on [0, 12.95], where Phi reaches 2^-126, the least value exp2 gives
+//              (64 clocks).
+// Fitted for the smallest largest error of Phi (|error| < 1e-7 in fp32 arithmetic), and in the tail for relative errors: 6e-7 at
+// a = 1, 2e-5 at 3, 3e-4 at 5; from there degree 8 loses the tail (6e-3 at 6.3, 8e-2 at 7, nothing is left at 10), degree 10 has
+// 1e-3 at 6, 3e-3 at 8, 2.3e-2 at 10 and 3.5e-2 at 12.9.  The rational form 7.1.26 of Abramowitz & Stegun takes twelve and two
+// instructions (80 clocks) for 2e-7 absolute and 9e-4 at 4, 5e-3 at 6, 1.2e-2 at 8, 2.2e-2 at 10, 3.6e-2 at 12.5.  (A NaN stays a NaN.)
+template <int ODT>
 __device__ __forceinline__ float gelu_cdf(float z)
 {
     const float a = fabsf(z);
-    float q = -8.120558493747162e-07f;
-    q = __builtin_fmaf(q, a, 1.4290432782061204e-05f);
-    q = __builtin_fmaf(q, a, -6.487764435589362e-05f);
-    q = __builtin_fmaf(q, a, -0.0004287622419436152f);
-    q = __builtin_fmaf(q, a, 0.007434012361791795f);
-    q = __builtin_fmaf(q, a, -0.05273924310954606f);
-    q = __builtin_fmaf(q, a, -0.4591337784121185f);
-    q = __builtin_fmaf(q, a, -1.1511134917708818f);
-    q = __builtin_fmaf(q, a, -0.9999998474115108f);
+    float q;
+    if constexpr (ODT == SS_F16) {
+        q = -8.120558493747162e-07f;
+        q = __builtin_fmaf(q, a, 1.4290432782061204e-05f);
+        q = __builtin_fmaf(q, a, -6.487764435589362e-05f);
+        q = __builtin_fmaf(q, a, -0.0004287622419436152f);
+        q = __builtin_fmaf(q, a, 0.007434012361791795f);
+        q = __builtin_fmaf(q, a, -0.05273924310954606f);
+        q = __builtin_fmaf(q, a, -0.4591337784121185f);
+        q = __builtin_fmaf(q, a, -1.1511134917708818f);
+        q = __builtin_fmaf(q, a, -0.9999998474115108f);
+    } else {
+        q = -3.325034692025497e-09f;
+        q = __builtin_fmaf(q, a, 1.58049019205464e-07f);
+        q = __builtin_fmaf(q, a, -3.0015255561011145e-06f);
+        q = __builtin_fmaf(q, a, 2.81424345303094e-05f);
+        q = __builtin_fmaf(q, a, -0.00011069921310991049f);
+        q = __builtin_fmaf(q, a, -0.00034601808874867857f);
+        q = __builtin_fmaf(q, a, 0.007352784276008606f);
+        q = __builtin_fmaf(q, a, -0.052697665989398956f);
+        q = __builtin_fmaf(q, a, -0.45914411544799805f);
+        q = __builtin_fmaf(q, a, -1.1511123180389404f);
+        q = __builtin_fmaf(q, a, -0.9999998807907104f);
+    }
     return __builtin_fmaf(-a, __builtin_amdgcn_exp2f(q), fmaxf(z, 0.f));
 }
 
@@ -804,7 +824,7 @@ void conv_kernel(ConvParams p)
     // ReLU when relu_floor = 0, identity when -inf (a NaN passes through); GELU = z * Phi(z) with the exact normal
     // CDF (gelu_cdf)
     auto relu_or_id = [&](float v) { return floor_at(v, relu_floor); };
-    auto gelu = [](float v) { return gelu_cdf(v); };
+    auto gelu = [](float v) { return gelu_cdf<ODT>(v); };
     if constexpr (CAN_SPLIT) {
         if (nsplit > 1) {
             // Every workgroup of the tile leaves its partial sums in the workspace, in register order (one 16-byte
@@ -1300,7 +1320,7 @@ void mlp_kernel(MlpParams p)
         lds_barrier();                                    // the chunk buffer is free again
     }
     };
-    if (p.act1 == SS_ACT_GELU) chunks([](float z) { return gelu_cdf(z); });
+    if (p.act1 == SS_ACT_GELU) chunks([](float z) { return gelu_cdf<DT>(z); });
     else chunks([floor1](float z) { return floor_at(z, floor1); });
 
     // ---- output: bias + residual + activation in fp32, one rounding; each 32 x 32 tile crosses the wave's own LDS region
@@ -1345,7 +1365,7 @@ void mlp_kernel(MlpParams p)
         }
     }
     };
-    if (p.act2 == SS_ACT_GELU) finish([](float z) { return gelu_cdf(z); });
+    if (p.act2 == SS_ACT_GELU) finish([](float z) { return gelu_cdf<DT>(z); });
     else finish([floor2](float z) { return floor_at(z, floor2); });
 }
 

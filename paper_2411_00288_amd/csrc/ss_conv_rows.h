@@ -237,7 +237,7 @@ void conv_pw_rows_kernel(ConvParams p, int mg, int pairs_per_group)
                 }
             }
         };
-        if (p.act == SS_ACT_GELU) write_out([](float v) { return gelu_cdf(v); });
+        if (p.act == SS_ACT_GELU) write_out([](float v) { return gelu_cdf<ODT>(v); });
         else write_out([&](float v) { return floor_at(v, relu_floor); });
     }
 }

@@ -337,7 +337,7 @@ __global__ __launch_bounds__(NW * 64) void conv_small_kernel(ConvParams p)
         for (int e = 0; e < 4; e++) {
             const float bias = __builtin_bit_cast(float, f.bias[e]), scale = Q8 && p.scale != nullptr ? __builtin_bit_cast(float, f.scale[e]) : 1.f;
             const float z = Q8 ? v[e] * scale + bias : v[e] + bias + widen<ODT>((uint16_t)(f.res[e >> 1] >> (16 * (e & 1))));
-            v[e] = p.act == SS_ACT_GELU ? gelu_cdf(z) : floor_at(z, floor);
+            v[e] = p.act == SS_ACT_GELU ? gelu_cdf<ODT>(z) : floor_at(z, floor);
         }
         uint16_t *y = p.y + (size_t)pg * p.Cout + o;
         if (four) {
@@ -643,7 +643,7 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
 #pragma unroll
         for (int e = 0; e < 4; e++) {
             const float z = v[e] + bias1[o + e];
-            v[e] = p.act == SS_ACT_GELU ? gelu_cdf(z) : floor_at(z, floor1);
+            v[e] = p.act == SS_ACT_GELU ? gelu_cdf<DT>(z) : floor_at(z, floor1);
         }
         *reinterpret_cast<uint2 *>(tile + pl * TROW + o) = make_uint2(cvt_pack2<DT>(v[0], v[1]), cvt_pack2<DT>(v[2], v[3]));
     }
@@ -690,7 +690,7 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
 #pragma unroll
             for (int e = 0; e < 4; e++) {
                 float x0 = v[2 * e] + widen<DT>((uint16_t)(res[j][e] & 0xFFFFu)), x1 = v[2 * e + 1] + widen<DT>((uint16_t)(res[j][e] >> 16));
-                if (p.act2 == SS_ACT_GELU) { x0 = gelu_cdf(x0); x1 = gelu_cdf(x1); }
+                if (p.act2 == SS_ACT_GELU) { x0 = gelu_cdf<DT>(x0); x1 = gelu_cdf<DT>(x1); }
                 else { x0 = floor_at(x0, floor2); x1 = floor_at(x1, floor2); }
                 w[e] = cvt_pack2<DT>(x0, x1);
             }

@@ -354,7 +354,7 @@ void conv_stream_kernel(ConvParams p, int tiles_n, int slots_n)
             }
         }
         const int n0 = (nslot + it * slots_n) * BN;
-        if (p.act == SS_ACT_GELU) write_tile(n0, [](float v) { return gelu_cdf(v); });
+        if (p.act == SS_ACT_GELU) write_tile(n0, [](float v) { return gelu_cdf<ODT>(v); });
         else write_tile(n0, [&](float v) { return floor_at(v, relu_floor); });     // ReLU, or the identity with a floor of -inf (a NaN passes)
         init_acc();
     }

@@ -5,6 +5,7 @@ small-integer inputs, in place (y aliasing the residual), and at full size on a 
 outputs) in the launch configuration the benchmark uses.
 """
 import dataclasses
+import math
 
 import numpy as np
 import pytest
@@ -154,3 +155,25 @@ def test_gelu_over_a_dense_grid_of_arguments(ss):
     for sparse in (True, False):
         got = _run(ss, L, d, z_bits, sparse=sparse).float().cpu().numpy().astype(np.float64)
         assert (np.abs(got - ref) <= 1e-3 * np.abs(ref) + 1e-6).all()
+
+
+def test_gelu_keeps_the_lower_tail_in_bfloat16(ss):
+    # as above with every bfloat16 value with |z| <= 12.875, where Phi(-|z|) is still a normal number.  Bounds: half a unit in
+    # the last place of the store, 2^-8 of the value, and the error of Phi as stated at gelu_cdf
+    pats = np.arange(0, 0x414E + 1, dtype=np.uint16)
+    z_bits = np.concatenate([pats, pats | 0x8000])
+    C = 64
+    n = (z_bits.size + C - 1) // C
+    z_bits = np.concatenate([z_bits, np.zeros(n * C - z_bits.size, dtype=np.uint16)]).reshape(1, n, 1, C)
+    L = wl.Layer("gelu_tail", N=1, H=n, W=1, cin=32, cout=C, kh=1, kw=1, dtype=wl.BF16, act=wl.ACT_GELU, mask="logits")
+    d = wl.make_inputs(L)
+    d["W"] = np.zeros_like(d["W"])
+    d["bias"] = np.zeros_like(d["bias"])
+    z = (z_bits.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+    ref = z * 0.5 * np.vectorize(math.erfc)(-z / math.sqrt(2.0))     # (the oracle's 1 + erf ends at -8.3)
+    tail = np.select([np.abs(z) <= 5, np.abs(z) <= 6, np.abs(z) <= 8], [3e-4, 1.1e-3, 3.1e-3], 3.6e-2)
+    bound = np.where(z >= 0, 2.0 ** -8 * np.abs(ref) + 1e-7 * np.abs(z), (2.0 ** -8 + tail) * np.abs(ref)) + 2.0 ** -134
+    for sparse in (True, False):
+        got = _run(ss, L, d, z_bits, sparse=sparse).float().cpu().numpy().astype(np.float64)
+        worst = np.argmax(np.abs(got - ref) - bound)
+        assert (np.abs(got - ref) <= bound).all(), (z.flat[worst], got.flat[worst], ref.flat[worst])
