@@ -181,8 +181,9 @@ int ss_weights_check(const ss_weight_desc *desc, const void *weights, int32_t sp
  * has so few tiles that most compute units would idle (few output pixels and a long reduction: small-batch inference,
  * the last stages of a network), the 16-bit convolutions split the reduction over several workgroups per output tile;
  * the workspace then holds their fp32 partial sums and one ticket counter per tile.  The partial sums are added in a
- * fixed order and rounded once, so the result does not depend on which workgroup finishes last.  Same value for the
- * sparse and the dense call and for the calls with a residual; 0 for the 8-bit operand types.
+ * fixed order and rounded once, so the result does not depend on which workgroup finishes last.  One value for the
+ * sparse and the dense call and for the calls with a residual (the larger of what they need: on fewer pixels still, where
+ * the reduction is split inside a workgroup, the sparse call needs none earlier than the dense one); 0 for the 8-bit operand types.
  *
  * Contract of a non-empty workspace: 256-byte aligned; zero-filled by the caller once, before the first call that
  * uses it (every call hands the ticket counters back at zero, so one clearing per allocation is enough, also under

@@ -125,10 +125,10 @@ static int conv_entry(const ss_weight_desc *desc, const void *x, int32_t N, int3
     p.meta_bytes = SPARSE ? (unsigned)((size_t)t.Mt * t.Kp * 256) : 4u;
     // Split of the reduction over several workgroups per tile (16-bit operands, grids far below the chip's size): the
     // partial sums and ticket counters live in the caller's workspace, which ss_conv2d_workspace_bytes sized from
-    // the same plan.
+    // the same plan.  The few-pixel kernels, which dispatch asks first, do not split.
     p.nsplit = 1;
     p.plan_tile = -1;
-    if (!q8) {
+    if (!q8 && !(forced_tile() < 0 && forced_split() == 0 && takes_small(desc, p, SPARSE, planning_units()))) {
         const SplitPlan pl = plan_split(desc, P, t.Ks, planning_units(), forced_tile(), forced_split());
         if (pl.nsplit > 1) {
             if (!workspace || ws_bytes < pl.ctr_bytes + pl.part_bytes) return SS_ERR_WORKSPACE;
@@ -277,8 +277,16 @@ extern "C" int ss_conv2d_workspace_bytes(const ss_weight_desc *desc, int32_t N, 
     const long long Ho = (H + 2 * pad_h - desc->kh) / stride_h + 1, Wo = (Wd + 2 * pad_w - desc->kw) / stride_w + 1;
     const long long P = (long long)N * Ho * Wo;
     if (P >= (1ll << 31) - 512) return SS_ERR_UNSUPPORTED;
-    const SplitPlan pl = plan_split(desc, P, tile_dims(desc).Ks, planning_units(), forced_tile(), forced_split());
-    if (pl.nsplit > 1) *bytes = pl.ctr_bytes + pl.part_bytes;
+    const TileDims t = tile_dims(desc);
+    const int ncu = planning_units();
+    const SplitPlan pl = plan_split(desc, P, t.Ks, ncu, forced_tile(), forced_split());
+    if (pl.nsplit <= 1) return SS_OK;
+    if (forced_tile() < 0 && forced_split() == 0) {       // as conv_entry; one answer for the sparse and the dense call
+        ConvParams p{};
+        p.Cin = desc->cin; p.Cout = desc->cout; p.P = (int)P; p.Ks = t.Ks; p.Mt = t.Mt;
+        if (takes_small(desc, p, true, ncu) && takes_small(desc, p, false, ncu)) return SS_OK;
+    }
+    *bytes = pl.ctr_bytes + pl.part_bytes;
     return SS_OK;
 }
 

@@ -84,6 +84,75 @@ static inline int choose_tile(const ConvParams &p, bool pointwise, bool bigchunk
 }
 
 
+// ---------------------------------------------------------------------------------------------
+// Few output pixels: which of the one-latency kernels (ss_conv_small.h) takes a problem.  Here and not beside them because the
+// workspace query and the entry points must know: a problem that they take never splits its reduction.
+// ---------------------------------------------------------------------------------------------
+// (RSCW: cin % 32 == 0, a reduction step lies in one tap; TAPSR: cin % 32 != 0, as MODE_TAPSR)
+enum { SMALL_PW = 0, SMALL_RSC = 1, SMALL_TAPS = 2, SMALL_TAPSR = 3, SMALL_RSCW = 4 };
+constexpr bool small_taps(int mode) { return mode == SMALL_TAPS || mode == SMALL_TAPSR; }
+
+// Workgroups of a problem.
+static inline long long small_blocks(const ConvParams &p, int px, int tm)
+{
+    return (long long)((p.Mt + tm - 1) / tm) * (((long long)p.P + px - 1) / px);
+}
+
+// How such a kernel would stage the problem, or -1 where none of them can.
+static inline int small_staging(const ss_weight_desc *d, const ConvParams &p)
+{
+    if ((long long)p.P * p.Cout * 2 > 0x7FFFFFFF) return -1;      // (32-bit offsets; such outputs are far above these kernels' range)
+    const bool square = (d->kh == 3 && d->kw == 3) || (d->kh == 2 && d->kw == 2);
+    if (d->kh * d->kw == 1 && p.Cin % 8 == 0) return SMALL_PW;
+    if (d->korder == SS_K_RSC && p.Cin % 32 == 0) return SMALL_RSCW;
+    if (d->korder == SS_K_RSC && p.Cin % 8 == 0) return SMALL_RSC;
+    if (d->korder == SS_K_CRS && square && p.Cin % 32 == 0) return SMALL_TAPS;
+    if (d->korder == SS_K_CRS && square && p.Cin % 4 == 0 && p.Cin >= 8 && !is_byte_type(d->dtype)) return SMALL_TAPSR;
+    return -1;
+}
+
+// Waves per workgroup: one per chunk of 32 channels (taps: the kernel's tap count, 0 = direct) or per four steps (direct), at most eight
+// (sixteen with the 16-pixel tiles of the direct modes, whose fragments leave the registers for it).
+static inline int small_waves(const ConvParams &p, int taps, bool tile16)
+{
+    const int shares = taps ? (p.Ks + taps - 1) / taps : (p.Ks + 3) / 4;
+    return shares <= 2 ? 2 : (shares <= 4 ? 4 : (shares <= 8 || taps || !tile16 ? 8 : 16));
+}
+
+enum { SMALL_NONE = -1, SMALL_16 = 0, SMALL_32 = 1, SMALL_64X32 = 2 };      // 32 channels x 16 / x 32 pixels, 64 x 32
+
+// Which variant pays, from a sweep of all of them and the tiled kernels over the ResNet-50 layers at batches 1 to 32, both
+// flattenings, sparse and dense, 16- and 8-bit operands (profiles/small_grids.md):
+//   * 16-pixel tiles while one per compute unit holds them all, and with two waves (short reductions) up to eight waves
+//     per compute unit: 3x3 256 -> 256 on one 14x14 image 9.0 -> 4.4 us, 64 -> 64 on one 56x56 4.9 -> 3.7;
+//   * 32-pixel tiles under the same conditions (four waves up to eight waves per unit, 2x2 kernels two workgroups):
+//     the 256 -> 256 layer on four images 9.1 -> 5.4;
+//   * 64 x 32 tiles for long reductions while one per unit holds them: 512 -> 512 on sixteen 7x7 images 19 -> 9.6 us.  Not for the
+//     dense form of the tap modes (its fragments spill: 11.4 vs 9.8).  Direct loads from sixteen steps on (1x1 512 -> 128 on
+//     four 28x28 images 5.0 -> 4.2 us, 3x3 channels-last 128 -> 512 on one 8.3 -> 6.6, int8 1x1 1024 -> 256 on eight 14x14
+//     4.8 -> 4.1); below that the 32-pixel tiles are as good.
+//   * direct loads, 32-pixel tiles up to two per unit while the reduction is short (1x1 128 -> 512 on one 28x28 image 4.0 -> 3.3,
+//     64 -> 64 on two 56x56 3.5 -> 3.1, int8 3x3 64 -> 128 on four 28x28 4.8 -> 3.4; at 32 steps 6.7 against the tiled 6.4, and at
+//     three per unit no gain).
+static inline int small_variant(const ConvParams &p, int taps, bool sparse, int ncu)
+{
+    const long long b16 = small_blocks(p, 16, 1), b32 = small_blocks(p, 32, 1), b64 = small_blocks(p, 32, 2);
+    const int nw = small_waves(p, taps, false);
+    if (b16 <= ncu || (taps && nw == 2 && b16 * nw <= 8ll * ncu)) return SMALL_16;
+    if (b32 <= ncu || (taps && nw == 4 && b32 * nw <= 8ll * ncu) || (taps == 4 && b32 <= 2ll * ncu)) return SMALL_32;
+    if (b64 <= ncu && (taps ? nw == 8 && sparse : p.Ks >= 16)) return SMALL_64X32;
+    if (!taps && p.Ks <= 20 && b32 <= 2ll * ncu) return SMALL_32;
+    return SMALL_NONE;
+}
+
+// Would the library by itself run this problem on one of them?
+static inline bool takes_small(const ss_weight_desc *d, const ConvParams &p, bool sparse, int ncu)
+{
+    const int mode = small_staging(d, p);
+    return mode >= 0 && small_variant(p, small_taps(mode) ? d->kh * d->kw : 0, sparse, ncu) != SMALL_NONE;
+}
+
+
 // Split of a convolution's reduction over several workgroups per output tile (for grids that leave most compute
 // units idle: few output pixels, long reductions -- small-batch inference and the last stages of a network).
 struct SplitPlan {

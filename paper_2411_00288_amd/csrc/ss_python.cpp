@@ -262,24 +262,27 @@ PyObject *conv(PyObject *const *a, Py_ssize_t n)
     at::Tensor y, ws;
     if (!output(a[10], *x, at::IntArrayRef(shape, 4), yt, &y)) Py_RETURN_NONE;
     const hipStream_t s = c10::hip::getCurrentHIPStream().stream();
-    size_t need = 0, ws_bytes = 0;
+    size_t ws_bytes = 0;
     void *wsp = nullptr;
     if (a[11] != Py_None) {
         const at::Tensor *t = dev_tensor(a[11]);
         if (!t) Py_RETURN_NONE;
         wsp = t->data_ptr();
         ws_bytes = t->nbytes();
-    } else {
-        if (ss_conv2d_workspace_bytes(&d, nhw[0], nhw[1], nhw[2], sp[0], sp[1], sp[2], sp[3], &need) != SS_OK) Py_RETURN_NONE;
-        if (need > 0) {
-            if (!pooled_workspace(*x, s, need, &ws)) Py_RETURN_NONE;
-            wsp = ws.data_ptr();
-            ws_bytes = ws.nbytes();
-        }
     }
     const void *xp = x->const_data_ptr(), *wp = w->const_data_ptr();
     void *yp = y.data_ptr();
-    const int st = unlocked([&] { return call_conv(kind, &d, xp, nhw, wp, scale, bias, residual, sp, act, yp, wsp, ws_bytes, s); });
+    const auto call = [&] { return call_conv(kind, &d, xp, nhw, wp, scale, bias, residual, sp, act, yp, wsp, ws_bytes, s); };
+    int st = unlocked(call);
+    if (st == SS_ERR_WORKSPACE && a[11] == Py_None) {     // (nothing is enqueued yet; few calls need one)
+        size_t need = 0;
+        if (ss_conv2d_workspace_bytes(&d, nhw[0], nhw[1], nhw[2], sp[0], sp[1], sp[2], sp[3], &need) != SS_OK ||
+            !pooled_workspace(*x, s, need, &ws))
+            Py_RETURN_NONE;
+        wsp = ws.data_ptr();
+        ws_bytes = ws.nbytes();
+        st = unlocked(call);
+    }
     return st == SS_OK ? give(a[10], y) : refuse(st);
 }
 

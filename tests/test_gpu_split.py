@@ -77,8 +77,9 @@ def test_split_with_residual_tail(ss, force_split):
 
 
 def test_library_splits_small_grids_by_itself_and_checks_the_workspace(ss):
-    # one image, 7x7, 512 -> 512 channels: four 128-row tiles for 256 compute units, 16 chunks
-    L = _L(1, 7, 7, 512, 512, 3, p=1, dtype=wl.BF16, seed=6)
+    # 24 images of 7x7, 512 -> 512 channels: 76 128-row tiles for 256 compute units, 16 chunks (up to eight images the few-pixel
+    # kernels take this layer, which need no workspace)
+    L = _L(24, 7, 7, 512, 512, 3, p=1, dtype=wl.BF16, seed=6)
     d = wl.make_inputs(L)
     ref = oracle_ref(L, d)
     desc, x, packed, bias = _operands(ss, L, d)
@@ -132,3 +133,51 @@ def test_split_under_graph_replay(ss, force_split):
         assert np.array_equal(host_bits(y), eager), f"replay {rep}"
         x2 = x * 1.0           # the program's own eager work between replays
         torch.cuda.synchronize()
+
+
+def test_few_pixel_layers_need_no_workspace(ss):
+    """What the few-pixel kernels take is not planned as a split reduction: nothing to allocate, nothing to refuse.  (At 16
+    images the sparse form is theirs and the dense one splits: one size for both, demanded of the one that uses it.)"""
+    for N, small in ((1, (True, False)), (8, (True, False)), (16, (True,)), (24, ())):
+        L = _L(N, 7, 7, 512, 512, 3, p=1, dtype=wl.BF16, seed=8)
+        d = wl.make_inputs(L)
+        desc = layer_desc(ss, L)
+        x, W, M = dev_bits(d["x"], L.dtype), dev_bits(d["W"], L.dtype), torch.from_numpy(d["M"]).cuda()
+        bias = torch.from_numpy(d["bias"]).cuda()
+        none = torch.zeros(0, dtype=torch.uint8, device="cuda")
+        assert (ss.ss_conv2d_workspace_bytes(desc, N, 7, 7, (1, 1), (1, 1)) > 0) == (len(small) < 2)
+        for sparse in (True, False):
+            w = ss.ss_mask_compress(desc, W, M) if sparse else ss.ss_dense_pack(desc, W, M)
+            call = ss.ss_conv2d_fwd if sparse else ss.ss_conv2d_dense_fwd
+            want = call(desc, x, w, bias, (1, 1), (1, 1), L.act)
+            if sparse in small:
+                assert torch.equal(call(desc, x, w, bias, (1, 1), (1, 1), L.act, workspace=none), want)
+                if N == 1:
+                    check_close(want, oracle_ref(L, d), f"{N} images")
+            else:
+                with pytest.raises(ss.SSError) as e:
+                    call(desc, x, w, bias, (1, 1), (1, 1), L.act, workspace=none)
+                assert e.value.status == ss.SS_ERR_WORKSPACE
+
+
+def test_plans_of_different_size_share_a_workspace(ss):
+    """Calls that follow each other in one workspace, never cleared in between: one's partial sums may not lie where another
+    expects its ticket counters at zero.  The same bits as from a workspace of its own, and from the pool behind the binding."""
+    layers = [_L(24, 7, 7, 512, 512, 3, p=1, dtype=wl.BF16, seed=1),       # 76 tiles of 128 x 64, three shares
+              _L(40, 7, 7, 512, 512, 3, p=1, dtype=wl.BF16, seed=2),       # 124 tiles, two
+              _L(3, 20, 20, 384, 256, 3, p=1, seed=3),                     # fewer channels, another type
+              _L(1, 60, 70, 6144, 128, 1, dtype=wl.BF16, seed=4)]          # 1x1, 66 tiles
+    calls, need = [], 0
+    for L in layers:
+        d = wl.make_inputs(L)
+        desc, x, packed, bias = _operands(ss, L, d)
+        one = ss.ss_conv2d_workspace_bytes(desc, L.N, L.H, L.W, (1, 1), (L.pad,) * 2)
+        assert one > 0, L.name
+        need = max(need, one)
+        ws = torch.zeros(one, dtype=torch.uint8, device="cuda")
+        run = lambda ws, a=(desc, x, packed, bias, (1, 1), (L.pad,) * 2, L.act): ss.ss_conv2d_fwd(*a, workspace=ws)
+        calls.append((L.name, run, run(ws)))
+    shared = torch.zeros(need, dtype=torch.uint8, device="cuda")
+    for i in (0, 1, 2, 3, 1, 3, 0, 2, 0, 3, 2, 1):
+        for ws in (shared, None):
+            assert torch.equal(calls[i][1](ws), calls[i][2]), calls[i][0]

@@ -32,12 +32,12 @@ def _both(ss, L):
 def test_static_workspace_entry_matches_the_workspace_entry_twice_in_a_row(ss):
     ss.ss_debug_force_tile(-1)
     ss.ss_debug_force_split(0)
-    # 512 -> 512 3x3 on one 7x7 image: the library splits the reduction by itself (4 tiles, 16 chunks)
-    need1, got1, ref1 = _both(ss, _L(1, 7, 7, 512, 512, 3, 1, wl.BF16, 21))
+    # 512 -> 512 3x3 on 24 7x7 images: the library splits the reduction by itself (76 tiles, 16 chunks in three shares)
+    need1, got1, ref1 = _both(ss, _L(24, 7, 7, 512, 512, 3, 1, wl.BF16, 21))
     assert need1 > 0, "the first problem must exercise the scratch array"
     assert np.array_equal(got1, ref1)
-    # a smaller input right after it, on the same array: 5x5 image, fewer channels out (two tiles), still split
-    need2, got2, ref2 = _both(ss, _L(1, 5, 5, 512, 200, 3, 1, wl.BF16, 22))
+    # fewer tiles right after it, on the same array: 5x5 images, fewer channels out (66 tiles), still split
+    need2, got2, ref2 = _both(ss, _L(83, 5, 5, 512, 256, 3, 1, wl.BF16, 22))
     assert 0 < need2 < need1
     assert np.array_equal(got2, ref2)
     # and a problem that needs no scratch at all
