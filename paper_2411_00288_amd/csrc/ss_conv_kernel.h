@@ -1491,27 +1491,18 @@ static int pick_tile(const ConvParams &p, hipStream_t s)
     return launch_tile<DT, SPARSE, MODE, KH, KW>(id, p, s);
 }
 
-// Channels-last flattening with taps: chunks of 256 reduction indices (a quarter of the barriers, four times the
-// LDS) pay with the producer-wave tiles -- few workgroups per compute unit anyway -- and cost occupancy on the large grids of
-// the shallow tiles.
-// Where the general rule takes the four-wave 256x64 tile, 16-bit operands do better with producer waves (rows filled, reductions of
-// 2048 and more: 256 -> 256 on 500 14x14 images 93 -> 84 us) or with the shallow 128x64 tile (64 -> 320 on 64 28x28 images 55.9 ->
-// 25.2, 128 -> 384 on 110 14x14 33 -> 19.5, 96 -> 320 5x5 on 128 28x28 219 -> 152); so do dense 8-bit ones with the
-// shallow tile (256 -> 512 on 128 14x14 images, int8: 40.4 -> 34.8).
+// Channels-last flattening with taps (the choice: choose_vec).
 template <int DT, bool SPARSE>
 static int pick_vec(const ConvParams &p, hipStream_t s)
 {
-    if (p.K >= 512) {
-        const int forced = forced_tile();
-        int id = forced >= 0 ? forced : choose_tile(p, false, true);
-        if (forced < 0 && id == 3 && !(is_byte_type(DT) && SPARSE)) {
-            const bool filled = p.Cout % 256 == 0 || p.Cout % 256 >= 192;
-            if (is_byte_type(DT) || !filled || p.K < 2048) return launch_tile<DT, SPARSE, MODE_VEC, 1, 1>(2, p, s);
-            return launch_tile<DT, SPARSE, MODE_VEC8, 1, 1>(5, p, s);
-        }
-        if (id == 4 || id == 5) return pick_tile<DT, SPARSE, MODE_VEC8, 1, 1>(p, s);
-    }
-    return pick_tile<DT, SPARSE, MODE_VEC, 1, 1>(p, s);
+    if (p.K < 512) return pick_tile<DT, SPARSE, MODE_VEC, 1, 1>(p, s);
+    const int forced = forced_tile();
+    if (forced >= 0) return forced == 4 || forced == 5 ? pick_tile<DT, SPARSE, MODE_VEC8, 1, 1>(p, s) : pick_tile<DT, SPARSE, MODE_VEC, 1, 1>(p, s);
+    const int ncu = compute_units();
+    if (ncu <= 0) return SS_ERR_HIP;
+    const int id = choose_vec(p, is_byte_type(DT), SPARSE, ncu);
+    if (id == 4 || id == 5) return launch_tile<DT, SPARSE, MODE_VEC8, 1, 1>(id, p, s);
+    return launch_tile<DT, SPARSE, MODE_VEC, 1, 1>(id, p, s);
 }
 
 template <int DT, bool SPARSE>

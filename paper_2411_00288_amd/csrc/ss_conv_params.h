@@ -84,6 +84,32 @@ static inline int choose_tile(const ConvParams &p, bool pointwise, bool bigchunk
 }
 
 
+// Tile id in the channels-last flattening with taps, from K = 512 on (p.K counts 2-byte units: pairs of 8-bit indices).  Ids 4 and 5
+// then stage chunks of 256 units, a quarter of the barriers and four times the LDS: right for producer waves, which run
+// few workgroups per compute unit anyway; the others stage 64.
+// choose_tile except where it takes the four-wave 256x64 tile (large grids).  From a sweep over 2566 such layers with each tile forced
+// (profiles/channels_last_large_grids.md; 256 to 1024 output channels, K 512 to 3456, five image sizes):
+//   * dense 16-bit: 128x64 where it computes fewer rows (0.60 to 0.92 of the 256x64 tile's time, mean 0.76) and below K = 1792
+//     (0.78 to 1.02, mean 0.92); with equal rows and K from there on 256x64 with producer waves (0.78 to 0.96, mean 0.87; 128x64
+//     0.98);
+//   * sparse 16-bit, half the matrix instructions per weight fetched, so that two 128-row tiles cost more than a 256-row one: by
+//     the tiles of the fullest compute unit, two 128-row tiles counted as 9/8 of a 256-row tile.  That is 128x64 where
+//     256 rows are mostly padding (288 to 384 channels: 0.72 to 0.98, mean 0.90) or leave units idle in the last round (256 channels on 64
+//     28x28 images 0.91 to 1.02), 256x64 elsewhere (with equal rows 128x64 takes up to 1.46 of its time);
+//   * dense 8-bit: 128x64 (int8 0.60 to 1.15, mean 0.84; FP8, whose general choice is producer waves, 0.58 to 1.31, mean 0.87: the
+//     losses are at 784 workgroups, two per cent more than the chip holds at once).
+// Over the sweep the choice is 1 % (dense 8-bit 1.6 %) above the best of the three in the mean, the four-wave 256x64 tile everywhere
+// would be 4 to 21 %.  Sparse 8-bit layers, whose steps are the cheapest, keep the rule for short chunks: 256x64 from 512 channels on.
+static inline int choose_vec(const ConvParams &p, bool bytes, bool sparse, int ncu)
+{
+    const int id = choose_tile(p, false, true);
+    if (id != 3) return id;
+    if (bytes) return sparse ? choose_tile(p, false, false) : 2;
+    const long long b128 = n_blocks(p, 128, 64), b256 = n_blocks(p, 256, 64);
+    if (sparse) return 9 * ((b128 + ncu - 1) / ncu) < 16 * ((b256 + ncu - 1) / ncu) ? 2 : 3;
+    return b128 == 2 * b256 && p.K >= 1792 ? 5 : 2;
+}
+
 // ---------------------------------------------------------------------------------------------
 // Few output pixels: which of the one-latency kernels (ss_conv_small.h) takes a problem.  Here and not beside them because the
 // workspace query and the entry points must know: a problem that they take never splits its reduction.
