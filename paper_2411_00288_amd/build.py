@@ -21,7 +21,7 @@ NATIVE = HERE / "_native.so"
 OBJDIR = HERE / "_build"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
-         # packed-fp32 instructions have produced silently wrong results on the test machines
+         # packed-fp32 instructions have produced silently wrong results on this hardware
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-command-line-argument"]
 
