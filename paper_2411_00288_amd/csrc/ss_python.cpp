@@ -400,12 +400,14 @@ PyObject *pack(PyObject *const *a, Py_ssize_t n)
     }
     const hipStream_t s = c10::hip::getCurrentHIPStream().stream();
     const uint8_t *m = M ? static_cast<const uint8_t *>(M->const_data_ptr()) : nullptr;
-    const void *wp = W->const_data_ptr(), *up = U ? U->const_data_ptr() : nullptr;
+    // (an update writes W: an address for writing, so that a lazy clone parts from what it shares memory with)
+    void *wp = mode == 1 ? W->mutable_data_ptr() : const_cast<void *>(W->const_data_ptr());
+    const void *up = U ? U->const_data_ptr() : nullptr;
     void *op = out.data_ptr();
     int32_t bad[2] = {-1, -1};
     const int st = unlocked([&] {               // (the compressing calls wait for the stream)
         if (mode == 2) return ss_dense_pack(&d, wp, m, op, s);
-        if (mode == 1) return ss_mask_update_compress(&d, const_cast<void *>(wp), up, m, op, bad, s);
+        if (mode == 1) return ss_mask_update_compress(&d, wp, up, m, op, bad, s);
         return ss_mask_compress(&d, wp, m, op, bad, s);
     });
     return st == SS_OK ? give(a[5], out) : refuse(st, bad);

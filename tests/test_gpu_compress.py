@@ -218,3 +218,14 @@ def test_packing_calls_that_wait_are_refused_under_capture(ss, mode):
         assert torch.equal(W, W_before) and torch.equal(packed, want)
     ss.ss_mask_update_compress(desc, W, U, M, packed=packed)                 # and the calls still work afterwards
     assert np.array_equal(host_bits(W), oracle.update(d["W"], host_bits(U), L.dtype))
+
+
+def test_update_of_a_lazy_clone_leaves_the_original_alone(ss):
+    """W is written through an address for writing: a clone that still shares its memory gets memory of its own first."""
+    L = wl.Layer("t", N=1, H=2, W=2, cin=64, cout=40, kh=1, kw=1, dtype=wl.BF16, mask="logits", seed=5)
+    d = wl.make_inputs(L)
+    W, M = dev_bits(d["W"], L.dtype), torch.from_numpy(d["M"]).cuda()
+    clone, U = torch._lazy_clone(W), torch.ones_like(W)
+    ss.ss_mask_update_compress(layer_desc(ss, L), clone, U, M)
+    assert np.array_equal(host_bits(W), d["W"])
+    assert np.array_equal(host_bits(clone), oracle.update(d["W"], host_bits(U), L.dtype))
