@@ -294,7 +294,7 @@ struct Waiter {
     int device = -1;
 };
 constexpr int kKeptWaiters = 64;
-constexpr int kPollMicroseconds = 1000;
+constexpr int kPollMicroseconds = 1000, kSleepMicroseconds = 50;
 std::mutex waiter_mutex;
 Waiter kept_waiters[kKeptWaiters];
 int n_kept_waiters = 0;
@@ -350,14 +350,14 @@ static int launch_compress(const ss_weight_desc *desc, const TileDims &t, void *
                           desc->cout, t.K, t.Mt, t.Ks, t.Kp, pack_header(kMagicSparse, desc, t), const_cast<uint32_t *>(w.bad));
     if (hipGetLastError() != hipSuccess) return SS_ERR_HIP;
     // Polled without a pause for as long as packing itself takes.  A longer wait is for earlier work on the stream, which may take
-    // any time: it sleeps a sixteenth of the time waited so far between two looks.  (hipEventSynchronize and hipStreamSynchronize keep
-    // the core busy throughout, with hipEventBlockingSync too: behind 300 ms of work 300 ms of processor time, 1.3 here.)
+    // any time: it sleeps between two looks, about 0.1 ms each with the timer's own slack, so the call returns at most that much late.
+    // (hipEventSynchronize and hipStreamSynchronize keep the core busy throughout, with hipEventBlockingSync too: behind
+    // 300 ms of work 300 ms of processor time, 8 here.)
     const auto since = std::chrono::steady_clock::now();
     hipError_t e;
-    while ((e = hipEventQuery(w.done)) == hipErrorNotReady) {
-        const auto waited = std::chrono::steady_clock::now() - since;
-        if (waited > std::chrono::microseconds(kPollMicroseconds)) std::this_thread::sleep_for(waited / 16);
-    }
+    while ((e = hipEventQuery(w.done)) == hipErrorNotReady)
+        if (std::chrono::steady_clock::now() - since > std::chrono::microseconds(kPollMicroseconds))
+            std::this_thread::sleep_for(std::chrono::microseconds(kSleepMicroseconds));
     return e == hipSuccess ? SS_OK : SS_ERR_HIP;
 }
 
