@@ -537,12 +537,14 @@ PyObject *launch(PyObject *, PyObject *args)
 
 // Every entry point runs inside this: what torch throws (a tensor without storage under torch.func, symbolic sizes, no memory)
 // must not leave through the interpreter's C frames, where it would end the process.  The caller's path meets it again and reports it.
+// (Not `catch (...)`: a daemon thread that asks for the interpreter lock while the interpreter shuts down is ended by a forced
+// unwind, which has to pass.)
 template <PyObject *(*F)(PyObject *const *, Py_ssize_t)>
 PyObject *entry(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     try {
         return F(a, n);
-    } catch (...) {
+    } catch (const std::exception &) {
     }
     PyErr_Clear();                              // (torch's Python errors leave theirs set)
     Py_RETURN_NONE;
