@@ -137,7 +137,6 @@ static int conv_entry(const ss_weight_desc *desc, const void *x, int32_t N, int3
             p.plan_tile = pl.tile;
             p.plan_bm = pl.bm;
             p.plan_bn = pl.bn;
-            p.ws_ctr = static_cast<unsigned *>(workspace);
             p.ws_part = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + pl.ctr_bytes);
         }
     }

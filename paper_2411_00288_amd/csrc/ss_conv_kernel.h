@@ -62,6 +62,37 @@ __device__ __forceinline__ int fast_div(int n, unsigned mul, unsigned sh)
     return (int)(((unsigned long long)(unsigned)n * mul) >> sh);
 }
 
+// The parameter block behind a launch's arguments (scalar arithmetic).  WINDOW: the window's size comes from the arguments, and not from KH x KW.
+// SMALL: the few-pixel kernels' reading of m_mul and extra.
+template <int DT, bool SPARSE, int KH, int KW, bool WINDOW, bool SMALL>
+__device__ __forceinline__ ConvParams unpack_args(const ConvArgs &a)
+{
+    ConvParams p;
+    p.x = a.x; p.a_vals = a.a_vals; p.bias = a.bias; p.y = a.y;
+    p.residual = is_byte_type(DT) ? nullptr : static_cast<const uint16_t *>(a.tail);
+    p.scale = is_byte_type(DT) ? static_cast<const float *>(a.tail) : nullptr;
+    p.H = a.H; p.W = a.W; p.Cin = a.Cin; p.Cout = a.Cout; p.sh = a.sh; p.sw = a.sw; p.ph = a.ph; p.pw = a.pw;
+    p.P = a.P; p.Ho = a.Ho; p.Wo = a.Wo;
+    p.howo_mul = a.howo_mul; p.wo_mul = a.wo_mul;
+    p.act = (int)(a.bits & 3u);
+    p.howo_sh = a.bits >> 2 & 63u; p.wo_sh = a.bits >> 8 & 63u;
+    (SMALL ? p.kw_mul : p.tm_mul) = a.m_mul;
+    (SMALL ? p.kw_sh : p.tm_sh) = a.bits >> 14 & 63u;
+    if constexpr (SMALL) { p.cin_mul = a.extra; p.cin_sh = a.bits >> 20 & 63u; }
+    p.K = WINDOW ? a.window.K : a.Cin * KH * KW;
+    p.kw = WINDOW ? a.window.kw : KW;
+    p.nsplit = WINDOW || SMALL ? 1 : (int)a.extra;
+    p.ws_part = WINDOW ? nullptr : a.ws_part;
+    p.Ks = (p.K + 31) / 32;                               // (as tile_dims: K counts 2-byte units, for 8-bit operands an even number to the step)
+    p.Kp = is_byte_type(DT) ? p.Ks : (p.Ks + 1) / 2;
+    p.Mt = (p.Cout + 31) / 32;
+    p.a_bytes = (unsigned)p.Mt * (unsigned)p.Ks * (SPARSE ? 1024u : 2048u);
+    p.a_meta = reinterpret_cast<const uint32_t *>(p.a_vals + (size_t)p.Mt * p.Ks * 1024);
+    p.meta_bytes = SPARSE ? (unsigned)p.Mt * (unsigned)p.Kp * 256u : 4u;
+    p.x_bytes = (unsigned)(fast_div(p.P, p.howo_mul, p.howo_sh) * p.H) * (unsigned)p.W * (unsigned)p.Cin * 2u;
+    return p;
+}
+
 constexpr unsigned kOutOfRange = 0x80000000u;   // >= any buffer size used here: the load returns 0
 constexpr int kRsrcFlags = 0x00020000;          // raw buffer, 32-bit data format (gfx9 family)
 
@@ -345,11 +376,16 @@ constexpr int min_waves_per_simd(int tm, int tn, bool big_stage)
 // 16 bit exactly as it would be stored) stays in LDS and is at once the activation operand of a following 1x1
 // convolution, whose output (+ bias + residual, activation) is what the kernel writes: the 3x3 -> 1x1 expansion of a
 // bottleneck without the intermediate tensor's round trip through memory.
+constexpr bool short_args(int mode, bool fuse) { return !fuse && mode != MODE_GATHER && mode != MODE_GATHER4; }      // (the others need more than ConvArgs holds)
+
 template <int DT, bool SPARSE, int WAVES_M, int WAVES_N, int TM, int TN, int MODE, int KH, int KW, bool DEEP, bool SPEC, bool FUSE = false>
 __global__ __launch_bounds__((WAVES_M * WAVES_N + (SPEC ? 4 : 0)) * 64)
 __attribute__((amdgpu_waves_per_eu(DEEP ? 1 : (((DT == SS_F8 || FUSE) && !SPARSE && MODE == MODE_VEC && TM * TN == 2) ? 3 : min_waves_per_simd(TM, TN, is_taps(MODE) || MODE == MODE_VEC8)))))
-void conv_kernel(ConvParams p)
+void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, ConvParams>::type args)
 {
+    ConvParams p;
+    if constexpr (short_args(MODE, FUSE)) p = unpack_args<DT, SPARSE, KH, KW, is_vec(MODE), false>(args);
+    else p = args;
     using CS = ChunkShape<MODE, KH, KW, DEEP>;
     static_assert(!SPEC || DEEP, "producer waves come with the deep variant only");
     constexpr bool Q8 = is_byte_type(DT);                 // 8-bit operands: staged as byte pairs, full index words, scaled tail
@@ -385,12 +421,14 @@ void conv_kernel(ConvParams p)
     // Workgroups are handed to the 8 XCDs round-robin, and each XCD has its own L2.  Renumber them so
     // that an XCD works on a contiguous run of tiles: both row tiles of a pixel tile, and pixel tiles
     // that share halo rows, then hit the same L2.
-    const int nb = gridDim.x, xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    constexpr bool CAN_SPLIT = !FUSE && !is_byte_type(DT);
+    const int nsplit = CAN_SPLIT ? p.nsplit : 1;
+    const int tiles_m = (p.Cout + BM - 1) / BM;
+    const int nb = tiles_m * ((p.P + BN - 1) / BN) * nsplit;      // (the grid; asking for its size would lengthen the launch's arguments)
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int lidx = xcd * (nb >> 3) + min(xcd, nb & 7) + slot;
     // Split reduction (p.nsplit > 1): nsplit workgroups share an output tile and each takes a contiguous share of the
     // reduction chunks; their fp32 partial sums meet in the workspace (see the epilogue).
-    constexpr bool CAN_SPLIT = !FUSE && !is_byte_type(DT);
-    const int nsplit = CAN_SPLIT ? p.nsplit : 1;
     // (split-major numbering: neighbouring workgroups, which land on the same XCD, work on neighbouring tiles with the
     // same share of the reduction and so share that share's weights in their L2)
     const int ntiles = nsplit > 1 ? nb / nsplit : nb;
@@ -400,7 +438,7 @@ void conv_kernel(ConvParams p)
     const int c_first = split * nchunks_all / nsplit;                  // this workgroup's chunks: [c_first, c_first + nchunks)
     const int nchunks = (split + 1) * nchunks_all / nsplit - c_first;
     const int tile_n = fast_div(lid, p.tm_mul, p.tm_sh);
-    const int tile_m = lid - tile_n * p.tiles_m;
+    const int tile_m = lid - tile_n * tiles_m;
     const int m0 = tile_m * BM;
     const int n0 = tile_n * BN;
     const int HoWo = p.Ho * p.Wo;
@@ -856,11 +894,12 @@ void conv_kernel(ConvParams p)
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wave's partial sums have been acknowledged
             __syncthreads();
             unsigned *ticket_s = reinterpret_cast<unsigned *>(smem);      // (the staging buffers are free)
-            if (etid == 0) *ticket_s = __hip_atomic_fetch_add(p.ws_ctr + lid, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            unsigned *const counter = reinterpret_cast<unsigned *>(reinterpret_cast<char *>(p.ws_part) - ticket_bytes(ntiles)) + lid;
+            if (etid == 0) *ticket_s = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __syncthreads();
             const unsigned ticket = *ticket_s;
             if (ticket != (unsigned)(nsplit - 1)) return;                 // (uniform)
-            if (etid == 0) __hip_atomic_store(p.ws_ctr + lid, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (etid == 0) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (!producer) {
 #pragma unroll
                 for (int tm = 0; tm < TM; tm++)
@@ -1415,7 +1454,7 @@ static int launch(const ConvParams &p0, hipStream_t s)
     if (FUSE || is_byte_type(DT) || p.nsplit < 1) p.nsplit = 1;
     if (p.nsplit > 1) {
         // the entry point planned the split for this very tile shape (plan_split) and sized the workspace for it
-        if (p.ws_part == nullptr || p.ws_ctr == nullptr || p.plan_bm != BM || p.plan_bn != BN) return SS_ERR_WORKSPACE;
+        if (p.ws_part == nullptr || p.plan_bm != BM || p.plan_bn != BN) return SS_ERR_WORKSPACE;
         blocks *= p.nsplit;
     }
     if (blocks <= 0 || blocks > 0x7FFFFFFFll) return SS_ERR_UNSUPPORTED;
@@ -1434,7 +1473,9 @@ static int launch(const ConvParams &p0, hipStream_t s)
             if (dev < 64) done_mask.fetch_or(bit, std::memory_order_release);
         }
     }
-    kern<<<dim3((unsigned)blocks), dim3((WAVES_M * WAVES_N + (SPEC ? 4 : 0)) * 64), smem, s>>>(p);
+    const dim3 grid((unsigned)blocks), block((WAVES_M * WAVES_N + (SPEC ? 4 : 0)) * 64);
+    if constexpr (short_args(MODE, FUSE)) kern<<<grid, block, smem, s>>>(conv_args(p, false, is_vec(MODE)));
+    else kern<<<grid, block, smem, s>>>(p);
     return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP;
 }
 

@@ -31,8 +31,55 @@ struct ConvParams {
     // counter per tile, both in the caller's workspace
     int nsplit, plan_tile, plan_bm, plan_bn;      // plan_*: the tile the split was planned (and the workspace sized) for
     float *ws_part;
-    unsigned *ws_ctr;
 };
+
+// What a launch carries to the kernels of the short calls; the rest of ConvParams follows from it (unpack_args).  A launch whose arguments
+// take more than 112 bytes costs the host 3.7 us, up to 112 bytes 2.8 (none at all: 0.8), whatever the kernel: as long as all of a
+// small layer's work on the GPU.  (ConvParams has 296 bytes, and a kernel that asks for its grid's size another 256.)
+struct ConvArgs {
+    const uint16_t *x;
+    const uint8_t *a_vals;
+    const float *bias;
+    const void *tail;         // 16-bit operands: the residual; 8-bit: the scale
+    uint16_t *y;
+    union {
+        float *ws_part;       // split reduction: partial sums (the ticket counters end where they begin)
+        struct {
+            int K, kw;        // kernels that learn the window's size from here
+        } window;
+    };
+    int H, W, Cin, Cout, sh, sw, ph, pw, P, Ho, Wo;
+    unsigned howo_mul, wo_mul;
+    unsigned m_mul;           // division by tiles_m, or (few-pixel kernels) by kw
+    unsigned extra;           // nsplit, or (few-pixel kernels) the division by Cin; activation-stationary kernel: see there
+    unsigned bits;            // act, then the shifts that go with howo_mul, wo_mul, m_mul and extra, six bits each from bit 2 on
+};
+static_assert(sizeof(ConvArgs) == 112, "a cheap launch");
+
+// small: the few-pixel kernels' reading of m_mul and extra.  window: the kernel learns the window's size from the arguments.
+static inline ConvArgs conv_args(const ConvParams &p, bool small, bool window)
+{
+    ConvArgs a;
+    a.x = p.x; a.a_vals = p.a_vals; a.bias = p.bias; a.y = p.y;
+    a.tail = p.residual != nullptr ? static_cast<const void *>(p.residual) : p.scale;      // (never both)
+    if (window) { a.window.K = p.K; a.window.kw = p.kw; }
+    else a.ws_part = p.ws_part;
+    a.H = p.H; a.W = p.W; a.Cin = p.Cin; a.Cout = p.Cout; a.sh = p.sh; a.sw = p.sw; a.ph = p.ph; a.pw = p.pw;
+    a.P = p.P; a.Ho = p.Ho; a.Wo = p.Wo;
+    a.howo_mul = p.howo_mul; a.wo_mul = p.wo_mul;
+    a.m_mul = small ? p.kw_mul : p.tm_mul;
+    a.extra = small ? p.cin_mul : (unsigned)p.nsplit;
+    a.bits = (unsigned)p.act | p.howo_sh << 2 | p.wo_sh << 8 | (small ? p.kw_sh : p.tm_sh) << 14 | (small ? p.cin_sh : 0u) << 20;
+    return a;
+}
+
+// Bytes of the ticket counters of a split reduction over so many tiles.  Every plan the library makes by itself has at most 128 tiles (half of
+// 256 compute units): their counters take the same 512 bytes, so that plans of different sizes can follow each other in one workspace
+// without one's partial sums lying where the other expects its counters at zero.
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+static inline size_t ticket_bytes(long long tiles) { return (size_t)((tiles * 4 + 511) / 512 * 512); }
 
 // floor(n / d) for 0 <= n < 2^31 as (n * mul) >> sh with s = ceil(log2 d), sh = 31 + s, mul = ceil(2^sh / d):
 // mul * d - 2^sh < d <= 2^s, so the product overshoots n / d by less than 1 / d, never reaching the next integer.
@@ -223,10 +270,7 @@ inline SplitPlan plan_split(const ss_weight_desc *d, long long P, int Ks, int nc
     if (n > nchunks) n = nchunks;
     if (n < 1) n = 1;
     pl.nsplit = n;
-    // Every plan the library makes by itself has at most 128 tiles (half of 256 compute units): their counters take the same
-    // 512 bytes, so that plans of different sizes can follow each other in one workspace without one's partial sums
-    // lying where the other expects its counters at zero.
-    pl.ctr_bytes = (size_t)((pl.tiles * 4 + 511) / 512 * 512);
+    pl.ctr_bytes = ticket_bytes(pl.tiles);
     pl.part_bytes = (size_t)pl.tiles * n * pl.bm * pl.bn * 4;
     return pl;
 }

@@ -36,8 +36,10 @@ static inline size_t rows_smem_bytes(int pairs_per_group)
 // mg workgroups share a pixel tile; each takes pairs_per_group blocks of 64 output channels.
 template <int DT, bool SPARSE, int KS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void conv_pw_rows_kernel(ConvParams p, int mg, int pairs_per_group)
+void conv_pw_rows_kernel(ConvArgs args)
 {
+    const ConvParams p = unpack_args<DT, SPARSE, 1, 1, false, true>(args);
+    const int mg = (int)args.m_mul, pairs_per_group = (int)args.extra;
     using SH = RowsShape<KS>;
     constexpr int BN = SH::BN, ROW = SH::ROW, VPP = SH::K / 8;      // 16-byte vectors per pixel
     constexpr int RMAX = SPARSE ? 8 : 4;                             // (a dense fragment is twice the registers)
@@ -293,7 +295,10 @@ static int launch_rows_ks(const ConvParams &p, int ncu, hipStream_t s)
             if (dev < 64) done_mask.fetch_or(bit, std::memory_order_release);
         }
     }
-    kern<<<dim3((unsigned)blocks), dim3(256), smem, s>>>(p, mg, ppg);
+    ConvArgs args = conv_args(p, true, false);
+    args.m_mul = (unsigned)mg;
+    args.extra = (unsigned)ppg;
+    kern<<<dim3((unsigned)blocks), dim3(256), smem, s>>>(args);
     return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP;
 }
 

@@ -29,8 +29,9 @@ constexpr size_t small_wave_lds()
 // PX: pixels of a tile (32, or 16: half of the matrix instruction's columns stay empty, and twice as many workgroups share
 // the loads, which is what bounds a grid far below the chip's size).  NW: waves.  RING: reduction steps in flight per wave (direct modes).
 template <int DT, bool SPARSE, int MODE, int KH, int KW, int PX, int TM, int NW, int RING>
-__global__ __launch_bounds__(NW * 64) void conv_small_kernel(ConvParams p)
+__global__ __launch_bounds__(NW * 64) void conv_small_kernel(ConvArgs args)
 {
+    const ConvParams p = unpack_args<DT, SPARSE, KH, KW, MODE == SMALL_RSC || MODE == SMALL_RSCW, true>(args);
     constexpr bool Q8 = is_byte_type(DT);
     constexpr int ODT = out_type<DT>();
     constexpr int TAPS = KH * KW;
@@ -42,9 +43,8 @@ __global__ __launch_bounds__(NW * 64) void conv_small_kernel(ConvParams p)
     const int g = lane >> 5, c = lane & 31;
     // Row tiles fastest: workgroups are dealt to the 8 XCDs round-robin, so with a multiple of 8 row tiles every XCD's L2
     // reads its own eighth of the weights only.
-    const int tile_n = fast_div(blockIdx.x, p.tm_mul, p.tm_sh);
-    const int mt = (blockIdx.x - tile_n * p.tiles_m) * TM;      // first row tile
-    const int n0 = tile_n * PX;
+    const int mt = blockIdx.x * TM;                       // first row tile
+    const int n0 = blockIdx.y * PX;
     const int HoWo = p.Ho * p.Wo;
 
     // What the finished quads need from memory, fetched ahead of everything else: behind the reduction these loads would be a second
@@ -345,14 +345,12 @@ __global__ __launch_bounds__(NW * 64) void conv_small_kernel(ConvParams p)
 }
 
 template <int DT, bool SPARSE, int MODE, int KH, int KW, int PX, int TM, int NW, int RING = 4>
-static int launch_small_waves(ConvParams p, hipStream_t s)
+static int launch_small_waves(const ConvParams &p, hipStream_t s)
 {
     constexpr size_t smem = NW * small_wave_lds<MODE, KH * KW, PX, TM>();
     static_assert(smem <= 160 * 1024, "LDS");
-    p.tiles_m = (p.Mt + TM - 1) / TM;
-    fast_div_setup((unsigned)p.tiles_m, &p.tm_mul, &p.tm_sh);
-    const long long blocks = small_blocks(p, PX, TM);
-    if (blocks <= 0 || blocks > 0x7FFFFFFFll) return SS_ERR_UNSUPPORTED;
+    const long long rows = (p.Mt + TM - 1) / TM, cols = ((long long)p.P + PX - 1) / PX;
+    if (rows <= 0 || cols <= 0 || cols > 65535) return SS_ERR_INVALID_ARG;      // (the grid's second dimension; only a forced variant gets here)
     auto kern = conv_small_kernel<DT, SPARSE, MODE, KH, KW, PX, TM, NW, RING>;
     if (smem > 64 * 1024) {
         static std::atomic<unsigned long long> done_mask{0};      // as in launch(): once per device
@@ -365,7 +363,7 @@ static int launch_small_waves(ConvParams p, hipStream_t s)
             if (dev < 64) done_mask.fetch_or(bit, std::memory_order_release);
         }
     }
-    kern<<<dim3((unsigned)blocks), dim3(NW * 64), smem, s>>>(p);
+    kern<<<dim3((unsigned)rows, (unsigned)cols), dim3(NW * 64), smem, s>>>(conv_args(p, true, MODE == SMALL_RSC || MODE == SMALL_RSCW));
     return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP;
 }
 

@@ -133,10 +133,12 @@ struct DwParams {
     const uint16_t *x, *w;
     const float *bias;
     uint16_t *y;
-    int N, H, W, C, ph, pw, Ho, Wo, act;
+    int H, W, C, ph, pw, Ho, Wo, act;
+    int per;                              // workgroups per group of channels (not from the grid's size: that would lengthen the launch's arguments to more than 112 bytes, which costs the host 0.9 us)
     int R, segs, wt, strips, groups;      // output rows per strip, segments per image, 16-wide tiles per row, strips in all, groups of 16 channels
     unsigned x_bytes, w_bytes, y_bytes;
 };
+static_assert(sizeof(DwParams) <= 112, "a cheap launch");
 
 template <int DT>
 __device__ __forceinline__ f32x4 mma16(u32x4 a, u32x4 b, f32x4 c)
@@ -172,10 +174,10 @@ __global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // neighbouring workgroups, which share halo rows and the other channel groups' cache lines, on one XCD; a workgroup keeps its
-    // channel group and takes every (gridDim / groups)-th block of 16 strips
-    const int nb = gridDim.x, xcd = blockIdx.x & 7;
+    // channel group and takes every per-th block of 16 strips
+    const int nb = p.per * p.groups, xcd = blockIdx.x & 7;
     const int lid = xcd * (nb >> 3) + min(xcd, nb & 7) + (blockIdx.x >> 3);
-    const int c0 = (lid % p.groups) * kDwGroup, first = lid / p.groups, stride = nb / p.groups;
+    const int c0 = (lid % p.groups) * kDwGroup, first = lid / p.groups, stride = p.per;
     const int nblocks = (p.strips + 15) >> 4;
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.x), 0, (int)p.x_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.w), 0, (int)p.w_bytes, 0x00020000);
@@ -371,7 +373,7 @@ __global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
 
 // Segments per image: those for which the busiest workgroup walks over the fewest input rows (a strip of R output rows needs R + K - 1).
 template <int DT, int K>
-static int launch_dw_mfma(DwParams p, hipStream_t s)
+static int launch_dw_mfma(DwParams p, int N, hipStream_t s)
 {
     const int ncu = compute_units();
     if (ncu <= 0) return SS_ERR_HIP;
@@ -382,14 +384,15 @@ static int launch_dw_mfma(DwParams p, hipStream_t s)
     for (int segs = 1; segs <= p.Ho; segs++) {
         const int R = (p.Ho + segs - 1) / segs;
         if ((p.Ho + R - 1) / R != segs) continue;         // (no new length)
-        const long long strips = (long long)p.N * segs * p.wt, blocks = (strips + 15) / 16;
+        const long long strips = (long long)N * segs * p.wt, blocks = (strips + 15) / 16;
         if (strips > 0x7FFFFFF0ll) break;
         const long long cost = (blocks + per_group - 1) / per_group * (R + K - 1);
         if (best < 0 || cost < best) { best = cost; p.R = R; p.segs = segs; p.strips = (int)strips; }
     }
     if (best < 0) return SS_ERR_UNSUPPORTED;
-    const long long blocks = (p.strips + 15ll) / 16, per = blocks < per_group ? blocks : per_group;
-    dwconv_mfma_kernel<DT, K><<<dim3((unsigned)(per * p.groups)), dim3(512), 0, s>>>(p);
+    const long long blocks = (p.strips + 15ll) / 16;
+    p.per = (int)(blocks < per_group ? blocks : per_group);
+    dwconv_mfma_kernel<DT, K><<<dim3((unsigned)(p.per * p.groups)), dim3(512), 0, s>>>(p);
     return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP;
 }
 
@@ -404,13 +407,13 @@ static int launch_dw(const uint16_t *x, const uint16_t *w, const float *bias, ui
     if (kh == kw && ybytes < (1ll << 31) && (kw == 7 || (kw == 5 && ybytes >= (8ll << 20)))) {
         DwParams p{};
         p.x = x; p.w = w; p.bias = bias; p.y = y;
-        p.N = N; p.H = H; p.W = W; p.C = C; p.ph = ph; p.pw = pw; p.Ho = Ho; p.Wo = Wo; p.act = act;
+        p.H = H; p.W = W; p.C = C; p.ph = ph; p.pw = pw; p.Ho = Ho; p.Wo = Wo; p.act = act;
         p.x_bytes = x_bytes;
         p.w_bytes = (unsigned)(kh * kw * C * 2);
         p.y_bytes = (unsigned)ybytes;
         switch (kw) {
-            case 5: return launch_dw_mfma<DT, 5>(p, s);
-            case 7: return launch_dw_mfma<DT, 7>(p, s);
+            case 5: return launch_dw_mfma<DT, 5>(p, N, s);
+            case 7: return launch_dw_mfma<DT, 7>(p, N, s);
             default: return SS_ERR_UNSUPPORTED;
         }
     }

@@ -31,7 +31,7 @@ __global__ __launch_bounds__(256) void maxpool_kernel(const uint16_t *__restrict
 {
     const unsigned runs = C >> 3;
     const long long total = (long long)N * Ho * Wo * runs;
-    const unsigned nb = gridDim.x, xcd = blockIdx.x & 7;
+    const unsigned nb = (unsigned)((total + 255) / 256), xcd = blockIdx.x & 7;
     const long long gid = (long long)(xcd * (nb >> 3) + min(xcd, nb & 7) + (blockIdx.x >> 3)) * 256 + threadIdx.x;
     if (gid >= total) return;
     int run, wo, ho, n;
