@@ -18,7 +18,8 @@
  *   - Unless a parameter is marked [host], every data pointer is a DEVICE pointer.  The caller
  *     owns every buffer; the library never allocates or frees device memory.  Its only state is a per-device
  *     record of which kernels have had their shared-memory limit raised (set once, at a kernel's first launch) and,
- *     for each device, a few words of pinned host memory and events with which the packing calls wait.
+ *     for each device, a few words of pinned host memory with which the packing calls wait (and
+ *     events, where more than sixteen of them wait at once).
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  The convolution
  *     calls only enqueue work on it and return; ss_mask_compress additionally waits for the
  *     stream once, because it reports the mask's validity.
@@ -127,7 +128,7 @@ int ss_dense_bytes(const ss_weight_desc *desc, size_t *dense_bytes /*[host] out*
  *   bad_row_group [host, optional] two int32: on SS_ERR_BAD_MASK receives the row and the block
  *           index of the first (row-major) invalid block.
  * Values are copied bit for bit: a kept weight that is -0, NaN or subnormal is preserved.
- * Waits for `stream`; a stream that is being captured is refused with SS_ERR_HIP and records nothing.  On SS_ERR_BAD_MASK the
+ * Waits for `stream` (on return all work up to this call is done and its results are in memory); a stream that is being captured is refused with SS_ERR_HIP and records nothing.  On SS_ERR_BAD_MASK the
  * contents of `packed` must not be used.
  */
 int ss_mask_compress(const ss_weight_desc *desc, const void *W, const uint8_t *M,

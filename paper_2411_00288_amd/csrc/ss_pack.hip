@@ -8,6 +8,8 @@
 
 namespace ss {
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
 // ---------------------------------------------------------------------------------------------
 // header: its words travel as a kernel argument and are written by the packing kernel's first workgroup
 // ---------------------------------------------------------------------------------------------
@@ -59,13 +61,37 @@ __device__ __forceinline__ bool mask_ok(uint32_t m)
     return (m & 0xFEFEFEFEu) == 0 && __popc(m) == 2;
 }
 
+// The verdict.  The call returns when everything is packed, and it learns that from the last workgroup, which says so in pinned host
+// memory: 3 us sooner than from an event that completes with the kernel (flush of the caches, completion signal, query).
+// For that, every store here is written through to memory (its acknowledgement then means that every later kernel, copy or host
+// access finds it, on whatever stream), every wave waits for its acknowledgements, and every workgroup takes a ticket.  One counter would
+// serve 10 ns a ticket (1024 workgroups: 11 us), so from kOneCounter workgroups on groups of them count by themselves, each in a cache
+// line of its own, and the last of each group counts at the root (0.7 us, the time of 64 tickets).  A counter wraps to zero with its last ticket: nothing has to be reset.
+constexpr int kSlots = 16;                        // calls in flight on a device that have counters; further ones wait for an event
+constexpr unsigned kTicketGroups = 16, kOneCounter = 64;
+struct __attribute__((aligned(128))) TicketLine {
+    unsigned n;
+};
+__device__ TicketLine ticket_lines[kSlots][kTicketGroups + 1];      // (zero when the library is loaded)
+struct Verdict {                                  // pinned host memory, zero before the call
+    uint32_t done, bad;                           // all is packed (with slot >= 0); a block's mask is invalid
+};
+
+// The workgroup's ticket, taken by one of its threads: true for the last of the `blocks` workgroups.
+__device__ __forceinline__ bool last_of_grid(int slot, unsigned blocks)
+{
+    if (blocks < kOneCounter) return atomicInc(&ticket_lines[slot][0].n, blocks - 1) == blocks - 1;
+    const unsigned grp = blockIdx.x % kTicketGroups, in_group = (blocks - grp + kTicketGroups - 1) / kTicketGroups;
+    if (atomicInc(&ticket_lines[slot][1 + grp].n, in_group - 1) != in_group - 1) return false;
+    return atomicInc(&ticket_lines[slot][0].n, kTicketGroups - 1) == kTicketGroups - 1;
+}
+
 // UPD: the weights are first moved to V = W + U (written back over W; every element belongs to exactly one
-// thread's blocks), then V is packed.  *any_bad (host memory) is set when a block's mask is invalid; its place is looked up
-// by find_bad_kernel then.
+// thread's blocks), then V is packed.  The place of an invalid block is looked up by find_bad_kernel then.
 template <int DT, bool UPD>
 __global__ __launch_bounds__(256) void compress_kernel(void *__restrict__ W, const void *__restrict__ U,
                                                        const uint8_t *__restrict__ M, uint8_t *__restrict__ packed,
-                                                       int cout, int K, int Mt, int Ks, int Kp, PackHeader hdr, uint32_t *any_bad)
+                                                       int cout, int K, int Mt, int Ks, int Kp, PackHeader hdr, Verdict *verdict, int slot)
 {
     constexpr bool BYTES = is_byte_type(DT);
     constexpr int TB = BYTES ? 16 : 8;                    // blocks per row of a tile
@@ -76,7 +102,10 @@ __global__ __launch_bounds__(256) void compress_kernel(void *__restrict__ W, con
     const int tid = threadIdx.x;
     const int G = K >> 2, gx = (Ks + TX - 1) / TX;
     const int mt = blockIdx.x / gx, ks0 = (blockIdx.x - mt * gx) * TX;
-    if (blockIdx.x == 0 && tid < 64) reinterpret_cast<uint32_t *>(packed)[tid] = tid < kHdrWords ? hdr.w[tid] : 0u;
+    // (all offsets below fit 32 bits: fewer than 2^31 elements, 1.125 bytes each)
+    constexpr int kWriteThrough = 17;                     // cache policy sc0 sc1
+    const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(packed, 0, (int)(kHeaderBytes + (unsigned)Mt * (unsigned)Ks * 1024u + (unsigned)Mt * (unsigned)Kp * 256u), 0x00020000);
+    if (blockIdx.x == 0 && tid < 64) __builtin_amdgcn_raw_buffer_store_b32(tid < kHdrWords ? hdr.w[tid] : 0u, rp, tid * 4, 0, kWriteThrough);
 
     const int col = tid & 31;                             // block of the row this thread packs
     const int g = ks0 * TB + col;
@@ -108,7 +137,7 @@ __global__ __launch_bounds__(256) void compress_kernel(void *__restrict__ W, con
             for (int e = 0; e < 4; e++)
                 v |= (uint64_t)add16<DT>((uint32_t)(w[i] >> (16 * e)) & 0xFFFFu, (uint32_t)(u[i] >> (16 * e)) & 0xFFFFu) << (16 * e);
             w[i] = v;
-            if (row < cout && g < G) static_cast<uint64_t *>(W)[(size_t)row * G + g] = v;
+            if (row < cout && g < G) __hip_atomic_store(static_cast<uint64_t *>(W) + (size_t)row * G + g, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
         const bool ok = mask_ok(m[i]);
         bad |= !ok;
@@ -126,15 +155,18 @@ __global__ __launch_bounds__(256) void compress_kernel(void *__restrict__ W, con
         }
         nibs[(t * 64 + lane) * J + j] = (uint8_t)(i0 | (i1 << 2));
     }
-    if (bad) *any_bad = 1;
+    __shared__ uint32_t bad_s[4];                         // one per wave
+    const bool wave_bad = __any(bad);
+    if ((tid & 63) == 0) bad_s[tid >> 6] = wave_bad;
     __syncthreads();
+    if (tid == 0 && (bad_s[0] | bad_s[1] | bad_s[2] | bad_s[3])) __hip_atomic_store(&verdict->bad, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     // values: one 16-byte vector per thread and 256-vector pass
 #pragma unroll
     for (int v = tid; v < TX * 64; v += 256)
         if (ks0 + (v >> 6) < Ks)
-            *reinterpret_cast<uint4 *>(packed + kHeaderBytes + (((size_t)mt * Ks + ks0) * 64 + v) * 16) = *reinterpret_cast<const uint4 *>(vals + v * 4);
+            __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4 *>(vals + v * 4), rp, (int)(kHeaderBytes + (((unsigned)mt * Ks + ks0) * 64 + v) * 16), 0, kWriteThrough);
     // indices: one word per lane and tile (8-bit) or pair of tiles (16-bit; TX is even, so pairs do not straddle workgroups)
-    uint32_t *meta = reinterpret_cast<uint32_t *>(packed + kHeaderBytes + (size_t)Mt * Ks * 1024);
+    const unsigned meta = kHeaderBytes + (unsigned)Mt * Ks * 1024;
     auto word = [&](int t, int lane) {                    // the nibbles of a lane of a tile
         uint32_t out = 0;
 #pragma unroll
@@ -147,12 +179,16 @@ __global__ __launch_bounds__(256) void compress_kernel(void *__restrict__ W, con
     if (tid < 128) {
         const int t = tid >> 6, lane = tid & 63;
         if constexpr (BYTES) {
-            if (ks0 + t < Ks) meta[((size_t)mt * Ks + ks0 + t) * 64 + lane] = word(t, lane);
+            if (ks0 + t < Ks) __builtin_amdgcn_raw_buffer_store_b32(word(t, lane), rp, (int)(meta + (((unsigned)mt * Ks + ks0 + t) * 64 + lane) * 4), 0, kWriteThrough);
         } else if ((ks0 >> 1) + t < Kp) {
             // (the upper half of an odd last pair: blocks past the row's end, i.e. padding nibbles)
-            meta[((size_t)mt * Kp + (ks0 >> 1) + t) * 64 + lane] = word(2 * t, lane) | (word(2 * t + 1, lane) << 16);
+            __builtin_amdgcn_raw_buffer_store_b32(word(2 * t, lane) | (word(2 * t + 1, lane) << 16), rp, (int)(meta + (((unsigned)mt * Kp + (ks0 >> 1) + t) * 64 + lane) * 4), 0, kWriteThrough);
         }
     }
+    if (slot < 0) return;                                 // uniform
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wave's stores are in memory
+    __syncthreads();
+    if (tid == 0 && last_of_grid(slot, (unsigned)(Mt * gx))) __hip_atomic_store(&verdict->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // The first (row-major) block with an invalid mask, into the header.  Runs only after a compression found one.
@@ -282,22 +318,28 @@ extern "C" int ss_dense_bytes(const ss_weight_desc *desc, size_t *dense_bytes)
     return SS_OK;
 }
 
-// What a compression waits with: a word of pinned host memory in which it reports an invalid mask (read after the wait, with
-// no copy from the device) and an event that completes with the kernel itself (given to the launch, so no marker follows
-// the kernel; polled: 9.4 us from launch to return for a small kernel, against 11.9 with hipStreamSynchronize and about 30 in
-// all with the header launch and the copy of the status word that this replaces).  Handed out one per call in flight and
-// kept for the next, in an array: nothing here may throw through the C entry.
+// What a compression waits with: a word of pinned host memory in which the last workgroup leaves the verdict (polled, with no copy from the
+// device) and one of the device's kSlots sets of ticket counters.  A call that finds all of those in use has an event instead, given
+// to the launch, that completes with the kernel.  Handed out one per call in flight and kept for the next, in an array: nothing here
+// may throw through the C entry.
 namespace {
 struct Waiter {
-    volatile uint32_t *bad = nullptr;
-    hipEvent_t done = nullptr;
-    int device = -1;
+    Verdict *verdict = nullptr;
+    hipEvent_t done = nullptr;        // slot < 0
+    int device = -1, slot = -1;
+    void clear() const
+    {
+        __atomic_store_n(&verdict->done, 0u, __ATOMIC_RELAXED);
+        __atomic_store_n(&verdict->bad, 0u, __ATOMIC_RELAXED);
+    }
 };
-constexpr int kKeptWaiters = 64;
-constexpr int kPollMicroseconds = 1000, kSleepMicroseconds = 50;
+constexpr int kSlotDevices = 64, kKeptOthers = 64;
+constexpr int kKeptWaiters = kSlotDevices * kSlots + kKeptOthers;      // every waiter that has counters, and some that have not
+constexpr int kPollMicroseconds = 1000, kSleepMicroseconds = 50, kSleepsPerQuery = 1000;
 std::mutex waiter_mutex;
 Waiter kept_waiters[kKeptWaiters];
-int n_kept_waiters = 0;
+int n_kept_waiters = 0, n_kept_others = 0;
+int slots_given[kSlotDevices];        // per device: sets of counters handed out for good, each to one waiter
 
 bool take_waiter(Waiter *w)
 {
@@ -305,23 +347,27 @@ bool take_waiter(Waiter *w)
     if (hipGetDevice(&dev) != hipSuccess) return false;
     {
         const std::lock_guard<std::mutex> lock(waiter_mutex);
-        for (int i = n_kept_waiters; i-- > 0;)
-            if (kept_waiters[i].device == dev) {
-                *w = kept_waiters[i];
-                kept_waiters[i] = kept_waiters[--n_kept_waiters];
-                *w->bad = 0;
-                return true;
-            }
+        int pick = -1;
+        for (int i = n_kept_waiters; i-- > 0 && (pick < 0 || kept_waiters[pick].slot < 0);)
+            if (kept_waiters[i].device == dev) pick = i;
+        if (pick >= 0) {
+            *w = kept_waiters[pick];
+            kept_waiters[pick] = kept_waiters[--n_kept_waiters];
+            if (w->slot < 0) n_kept_others--;
+            w->clear();
+            return true;
+        }
+        w->slot = dev >= 0 && dev < kSlotDevices && slots_given[dev] < kSlots ? slots_given[dev]++ : -1;
     }
     void *page = nullptr;
     if (hipHostMalloc(&page, 64, hipHostMallocDefault) != hipSuccess) return false;
-    if (hipEventCreateWithFlags(&w->done, hipEventDisableTiming) != hipSuccess) {
+    if (w->slot < 0 && hipEventCreateWithFlags(&w->done, hipEventDisableTiming) != hipSuccess) {
         (void)hipHostFree(page);
         return false;
     }
-    w->bad = static_cast<volatile uint32_t *>(page);
+    w->verdict = static_cast<Verdict *>(page);
     w->device = dev;
-    *w->bad = 0;
+    w->clear();
     return true;
 }
 
@@ -329,13 +375,14 @@ void give_waiter(const Waiter &w)
 {
     {
         const std::lock_guard<std::mutex> lock(waiter_mutex);
-        if (n_kept_waiters < kKeptWaiters) {
+        if (w.slot >= 0 || n_kept_others < kKeptOthers) {
+            if (w.slot < 0) n_kept_others++;
             kept_waiters[n_kept_waiters++] = w;
             return;
         }
     }
     (void)hipEventDestroy(w.done);
-    (void)hipHostFree(const_cast<uint32_t *>(w.bad));
+    (void)hipHostFree(w.verdict);
 }
 }  // namespace
 
@@ -346,19 +393,33 @@ static int launch_compress(const ss_weight_desc *desc, const TileDims &t, void *
     constexpr int steps = kPackBlocks / (is_byte_type(DT) ? 16 : 8);      // reduction steps per workgroup
     const long long blocks = (long long)t.Mt * ((t.Ks + steps - 1) / steps);
     if (blocks > 0x7FFFFFFFll) return SS_ERR_UNSUPPORTED;
-    hipExtLaunchKernelGGL((compress_kernel<DT, UPD>), dim3((unsigned)blocks), dim3(256), 0, s, nullptr, w.done, 0, W, U, M, packed,
-                          desc->cout, t.K, t.Mt, t.Ks, t.Kp, pack_header(kMagicSparse, desc, t), const_cast<uint32_t *>(w.bad));
+    const PackHeader hdr = pack_header(kMagicSparse, desc, t);
+    if (w.slot < 0)
+        hipExtLaunchKernelGGL((compress_kernel<DT, UPD>), dim3((unsigned)blocks), dim3(256), 0, s, nullptr, w.done, 0, W, U, M, packed,
+                              desc->cout, t.K, t.Mt, t.Ks, t.Kp, hdr, w.verdict, w.slot);
+    else
+        compress_kernel<DT, UPD><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(W, U, M, packed, desc->cout, t.K, t.Mt, t.Ks, t.Kp, hdr, w.verdict, w.slot);
     if (hipGetLastError() != hipSuccess) return SS_ERR_HIP;
     // Polled without a pause for as long as packing itself takes.  A longer wait is for earlier work on the stream, which may take
     // any time: it sleeps between two looks, about 0.1 ms each with the timer's own slack, so the call returns at most that much late.
     // (hipEventSynchronize and hipStreamSynchronize keep the core busy throughout, with hipEventBlockingSync too: behind
     // 300 ms of work 300 ms of processor time, 8 here.)
     const auto since = std::chrono::steady_clock::now();
-    hipError_t e;
-    while ((e = hipEventQuery(w.done)) == hipErrorNotReady)
-        if (std::chrono::steady_clock::now() - since > std::chrono::microseconds(kPollMicroseconds))
-            std::this_thread::sleep_for(std::chrono::microseconds(kSleepMicroseconds));
-    return e == hipSuccess ? SS_OK : SS_ERR_HIP;
+    hipError_t e = hipSuccess;
+    auto pending = [&] {
+        if (w.slot >= 0) return __atomic_load_n(&w.verdict->done, __ATOMIC_ACQUIRE) == 0;
+        return (e = hipEventQuery(w.done)) == hipErrorNotReady;
+    };
+    for (int sleeps = 0; pending();) {
+        if (std::chrono::steady_clock::now() - since <= std::chrono::microseconds(kPollMicroseconds)) continue;
+        std::this_thread::sleep_for(std::chrono::microseconds(kSleepMicroseconds));
+        // (now and then: a stream that has failed, or is done and left no verdict, will not leave one)
+        if (w.slot >= 0 && ++sleeps % kSleepsPerQuery == 0 && (e = hipStreamQuery(s)) != hipErrorNotReady) {
+            if (e == hipSuccess && !pending()) break;
+            return SS_ERR_HIP;
+        }
+    }
+    return e == hipSuccess || e == hipErrorNotReady ? SS_OK : SS_ERR_HIP;
 }
 
 static int compress_entry(const ss_weight_desc *desc, void *W, const void *U, const uint8_t *M, void *packed,
@@ -388,7 +449,7 @@ static int compress_entry(const ss_weight_desc *desc, void *W, const void *U, co
     else if (desc->dtype == SS_F16) st = launch_compress<SS_F16, true>(desc, t, W, U, M, p, wt, s);
     else st = launch_compress<SS_BF16, true>(desc, t, W, U, M, p, wt, s);
     if (st == SS_ERR_HIP) return st;                      // (the kernel may still run: the waiter is not handed out again)
-    const bool bad = *wt.bad != 0;
+    const bool bad = __atomic_load_n(&wt.verdict->bad, __ATOMIC_RELAXED) != 0;
     give_waiter(wt);
     if (st != SS_OK || !bad) return st;
     // an invalid mask: find its first block and leave it in the header

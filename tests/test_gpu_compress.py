@@ -1,4 +1,6 @@
 """GPU parity of the weight compressor / decompressor / dense packer: bit-exact against the oracle."""
+import gc
+
 import numpy as np
 import pytest
 import torch
@@ -202,6 +204,9 @@ def test_packing_calls_that_wait_are_refused_under_capture(ss, mode):
     launch()
     torch.cuda.synchronize()
     eager = host_bits(y).copy()
+    # The graph of the mode before lives in a reference cycle (exception -> traceback -> frame).  Collected during the capture, its destructor
+    # synchronizes the device, which is refused there, and an exception in a destructor ends the process.
+    gc.collect()
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g, capture_error_mode=mode):
         launch()
@@ -229,3 +234,33 @@ def test_update_of_a_lazy_clone_leaves_the_original_alone(ss):
     ss.ss_mask_update_compress(layer_desc(ss, L), clone, U, M)
     assert np.array_equal(host_bits(W), d["W"])
     assert np.array_equal(host_bits(clone), oracle.update(d["W"], host_bits(U), L.dtype))
+
+
+@pytest.mark.parametrize("rows,steps", [(1, 1), (3, 84), (4, 64), (1, 260), (9, 60)])
+def test_verdict_of_grids_of_any_size(ss, rows, steps):
+    """The verdict comes from the last of the grid's workgroups (one for 32 rows x 4 steps: 1, 63, 64, 65 and 135 of them here; from 64 on they
+    count in sixteen groups), covers every one of them, and leaves the counters ready for the next call; what was packed is there for
+    another stream as soon as the call returns."""
+    cout, K = 32 * rows - 5, 32 * steps - 8
+    rng = np.random.Generator(np.random.PCG64(steps))
+    W = rng.integers(0, 1 << 16, size=(cout, K), dtype=np.uint16)
+    M = wl.mask_from_logits(rng.standard_normal((cout, K // 4, 6)).astype(np.float32)).reshape(cout, K)
+    desc = ss.make_desc(cout, K, 1, 1, wl.F16)
+    vals, meta = oracle.compress(W, M)
+    want = dl.tile(vals, meta, cin=K, kh=1, kw=1, dtype=wl.F16, korder=wl.K_CRS)
+    Wd, Md = dev_bits(W, wl.F16), torch.from_numpy(M).cuda()
+    other = torch.cuda.Stream()
+    out = torch.empty(want.size, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    for i in range(6):
+        out.fill_(0xA5)
+        ss.ss_mask_compress(desc, Wd, Md, packed=out)
+        with torch.cuda.stream(other):
+            got = out.cpu().numpy()
+        assert np.array_equal(got, want)
+        row, block = (cout - 1, K // 4 - 1) if i % 2 else (0, 0)
+        wrong = Md.clone()
+        wrong[row, 4 * block:4 * block + 4] = 1
+        with pytest.raises(ss.SSError) as e:
+            ss.ss_mask_compress(desc, Wd, wrong)
+        assert e.value.status == ss.SS_ERR_BAD_MASK and e.value.detail == (row, block)

@@ -129,3 +129,35 @@ def test_concurrent_calls_on_their_own_streams(ss):
         assert torch.equal(packed, bytes_)
         check_close(y, ref, "concurrent call")
         assert torch.equal(y, results[0][1])         # sums in a fixed order: the same bits from every thread
+
+
+def test_more_packing_calls_at_once_than_there_are_counters(ss):
+    """Sixteen calls in flight wait for their last workgroup, further ones for an event: 24 threads, each behind work of its own."""
+    L = _layer(cin=64, cout=96, kh=3, kw=3, pad=1, seed=4)
+    d = wl.make_inputs(L)
+    desc, W, M = layer_desc(ss, L), dev_bits(d["W"], L.dtype), torch.from_numpy(d["M"]).cuda()
+    want = ss.ss_mask_compress(desc, W, M)
+    wrong = M.clone()
+    wrong[11, 8:12] = 0
+    torch.cuda.synchronize()
+    results, errors, start = [], [], threading.Barrier(24)
+
+    def work(i):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                start.wait()
+                for _ in range(3):
+                    torch.cuda._sleep(2_000_000)             # about a millisecond
+                    results.append(ss.ss_mask_compress(desc, W, M))
+                    with pytest.raises(ss.SSError) as e:
+                        ss.ss_mask_compress(desc, W, wrong)
+                    assert e.value.detail == (11, 2)
+        except BaseException as e:                   # noqa: BLE001  (reported by the main thread)
+            errors.append(e)
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(24)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    assert len(results) == 72 and all(torch.equal(r, want) for r in results)
