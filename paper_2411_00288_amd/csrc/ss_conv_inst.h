@@ -30,14 +30,14 @@ int SS_CAT(conv_dispatch_, SS_INST_NAME)(const ss_weight_desc *desc, const ConvP
             // us; 200, 2 / 3, 37.2 / 35.8; 500, 3 / 6, 60.9 / 69.7).
             // Against the one-tile-per-workgroup kernels: faster as soon as the narrow grid fills more than half of the
             // compute units (256 -> 256, N = 50, 154 tiles: 12.6 against 13.0 us, fp8 N = 64: 9.4 / 9.8; N = 40, 123 tiles:
-            // 12.3 / 10.3), provided the 256-row tiles are not mostly padding: more than half filled on average with 16-bit
-            // operands (128 -> 144 on fifty 28x28: 20.1 against 24.0 us, 128 -> 288: 32.2 / 35.0; 96 -> 320: 54.6 / 66.2),
-            // three quarters with 8-bit ones, whose steps are half as long (128 -> 288, int8: 11.5 / 9.5; 256 -> 128, fp8:
-            // 69 / 54).
+            // 12.3 / 10.3), provided the 256-row tiles are not mostly padding.  3x3: above 176 channels per 256-row tile with 16-bit
+            // operands (5 row tiles of 32: the one-tile kernels' 160-row tile takes 0.96 of this one's time, 6 to 8: 1.01 to 1.09; 9 to 11 in two: 0.91
+            // to 0.94, 12: 0.99), above 224 with 8-bit ones, whose steps are half as long (their 224-row tile 0.92, eight row tiles: 0.96 to
+            // 1.05).  2x2: above half.
             const long long rows = (p.Cout + 255) / 256, wide = ((long long)p.P + 127) / 128, narrow = ((long long)p.P + 63) / 64;
             const long long slots = ncu > rows ? ncu / rows : 1;          // pixel tiles of one round, as the launch deals them out
             const long long rounds_w = (wide + slots - 1) / slots, rounds_n = (narrow + slots - 1) / slots;
-            const bool filled = is_byte_type(SS_INST_DT) ? 4ll * p.Cout >= 3 * 256 * rows : 2ll * p.Cout > 256 * rows;
+            const bool filled = desc->kh == 2 ? 2ll * p.Cout > 256 * rows : (is_byte_type(SS_INST_DT) ? (long long)p.Cout > 224 * rows : (long long)p.Cout > 176 * rows);
             const bool pays = filled && 2 * rows * narrow > ncu;
             if (desc->kh == 2) {
                 // The same line for 2x2 kernels of 16-bit operands with at least two chunks (96 -> 192 on 128 images of 56x56: 30-35

@@ -471,13 +471,14 @@ void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, Con
     // ------------------------------------------------------------------ activation staging state
     // per pixel row and chunk: 16-byte runs (VEC: 8, TAPS: 4 channel octets) or 4-element blocks (GATHER: 16)
     constexpr int UNITS = (MODE == MODE_GATHER || MODE == MODE_GATHER4) ? 16 : (is_taps(MODE) ? 4 : (MODE == MODE_VEC8 ? 32 : (MODE == MODE_PW || MODE == MODE_PWR ? 16 : 8)));
-    constexpr int ST = SPEC ? (256 < BN * UNITS ? 256 : BN * UNITS) : (NT < BN * UNITS ? NT : BN * UNITS);     // staging threads (whole waves); the rest only multiply
+    // staging threads (whole waves); the rest only multiply
+    constexpr int ST = SPEC ? 256 : (BN * UNITS % NT == 0 ? NT : (NT > 256 ? 256 : 128));
     constexpr int ITEMS = BN * UNITS / ST;
     constexpr int NSET = SPEC ? 2 : 1;                    // producer waves hold two chunks in registers
     static_assert(BN * UNITS % ST == 0 && ST % UNITS == 0 && ST % 64 == 0 && ITEMS >= 1, "tile/threads mismatch");
     const int stid = SPEC ? tid - NMATH : tid;            // index among the staging threads
     static_assert(!SPEC || ST == 256, "every producer thread stages");
-    const bool stager = SPEC ? true : ((ST == NT) || tid < ST);     // (producer waves: only they call the staging code)
+    const bool stager = SPEC || ST == NT || wave < ST / 64;     // uniform (producer waves: only they call the staging code)
     // Thread -> (pixel row, unit): unit fastest, so consecutive lanes read consecutive 16-byte pieces of one
     // pixel (coalesced).  (Putting 16 pixel rows of one unit on consecutive lanes makes the transposed LDS
     // writes conflict-free but quadruples the cache lines per load instruction: measured 30-40 % slower.)
@@ -1479,6 +1480,9 @@ static int launch(const ConvParams &p0, hipStream_t s)
     return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP;
 }
 
+// Staging modes with tiles of 96, 160 and 224 rows (choose_height).  1x1 layers gain nothing from them (over 1000 layers: 1 %), 2x2 ones 3 %.
+constexpr bool any_height(int mode, int kh) { return (is_taps(mode) && kh == 3) || mode == MODE_VEC; }
+
 // Tile shapes (WAVES_M x WAVES_N multiplying waves, each TM x TN tiles of 32x32):
 //   id 0:  64 x  64 (2x2 waves, 1x1)
 //   id 1:  same, deep prefetch
@@ -1486,6 +1490,7 @@ static int launch(const ConvParams &p0, hipStream_t s)
 //   id 3: 256 x  64 (4x1 waves, 2x2), deep prefetch
 //   id 4: 128 x  64 (4x1 waves, 1x2), deep prefetch, plus four producer waves
 //   id 5: 256 x  64 (4x1 waves, 2x2), deep prefetch, plus four producer waves
+//   ids 6, 7, 8: 96, 160, 224 x 64 (3, 5, 7 x 1 waves, 1x2), for output channels that fill the others badly
 // Layouts with all four waves along the output channels fetch no weight tile twice inside a workgroup.
 // Measured and dropped because they won nowhere: 2x2 layouts of the larger tiles, 128x128 and 256x128 tiles,
 // deep 128x64 and shallow 256x64 without producer waves, and splitting a tile's reduction over two wave groups
@@ -1500,6 +1505,14 @@ static int launch_tile(int id, const ConvParams &p, hipStream_t s)
             case 0: return launch<DT, SPARSE, 2, 2, 1, 1, MODE, KH, KW, false>(p, s);
             case 1: return launch<DT, SPARSE, 2, 2, 1, 1, MODE, KH, KW, true>(p, s);
             case 2: return launch<DT, SPARSE, 4, 1, 1, 2, MODE, KH, KW, false>(p, s);
+            default: break;
+        }
+    }
+    if constexpr (any_height(MODE, KH)) {
+        switch (id) {
+            case 6: return launch<DT, SPARSE, 3, 1, 1, 2, MODE, KH, KW, false>(p, s);
+            case 7: return launch<DT, SPARSE, 5, 1, 1, 2, MODE, KH, KW, false>(p, s);
+            case 8: return launch<DT, SPARSE, 7, 1, 1, 2, MODE, KH, KW, false>(p, s);
             default: break;
         }
     }
@@ -1526,6 +1539,11 @@ static int pick_tile(const ConvParams &p, hipStream_t s)
     constexpr bool pointwise = is_pw(MODE);
     constexpr bool bigchunk = (is_taps(MODE) && KH * KW > 4) || MODE == MODE_VEC8;
     int id = choose_tile(p, pointwise, bigchunk);
+    if constexpr (is_taps(MODE) && KH == 3) {
+        const int ncu = compute_units();
+        if (ncu <= 0) return SS_ERR_HIP;
+        id = choose_height(p, id, true, is_byte_type(DT), SPARSE, ncu);
+    }
     // The dense FP8 instruction of the deep kernels wants its 32-byte A operand in eight consecutive registers; the
     // 256x64 four-wave tile then runs at one wave per SIMD (measured 40 % slower than with producer waves).
     if (DT == SS_F8 && !SPARSE && id == 3) id = 5;
@@ -1541,7 +1559,7 @@ static int pick_vec(const ConvParams &p, hipStream_t s)
     if (forced >= 0) return forced == 4 || forced == 5 ? pick_tile<DT, SPARSE, MODE_VEC8, 1, 1>(p, s) : pick_tile<DT, SPARSE, MODE_VEC, 1, 1>(p, s);
     const int ncu = compute_units();
     if (ncu <= 0) return SS_ERR_HIP;
-    const int id = choose_vec(p, is_byte_type(DT), SPARSE, ncu);
+    const int id = choose_height(p, choose_vec(p, is_byte_type(DT), SPARSE, ncu), false, is_byte_type(DT), SPARSE, ncu);
     if (id == 4 || id == 5) return launch_tile<DT, SPARSE, MODE_VEC8, 1, 1>(id, p, s);
     return launch_tile<DT, SPARSE, MODE_VEC, 1, 1>(id, p, s);
 }

@@ -157,6 +157,31 @@ static inline int choose_vec(const ConvParams &p, bool bytes, bool sparse, int n
     return b128 == 2 * b256 && p.K >= 1792 ? 5 : 2;
 }
 
+// Tile id of a 3x3 layer in the paper's flattening (taps), or of a channels-last layer with taps and K >= 512, on a grid of more than one
+// workgroup per compute unit, given the choice made so far.  Rows past the last output channel cost as much as any others, so
+// there are tiles of 96, 160 and 224 rows too (136 channels in one tile of 160 instead of two of 128: 12.1 -> 10.8 us on six 45x61 images,
+// 80 -> 136, sparse, with a residual).
+// By the tiles of the fullest compute unit (halfway between that and the mean, since two or three workgroups share a unit) times the time
+// of a tile, in hundredths of the 128-row one's: medians of a sweep of 6000 drawn layers with each tile forced.  The taller ones have less to
+// overlap with (two workgroups of five waves per unit, one of seven); dense 8-bit steps are bound by their registers.  Over the layers
+// that come here the choice takes 0.90 of the time of the tiles of 64, 128 and 256 rows alone (1st to 99th percentile 0.57 to 1.11) and is 4 % above
+// the best of all, half of which is noise.  In the paper's flattening the 128- and 256-row tiles are compared in the same way; the
+// channels-last choice between those (choose_vec) stands.
+static inline int choose_height(const ConvParams &p, int id, bool taps, bool bytes, bool sparse, int ncu)
+{
+    if (id != 2 && id != 3) return id;
+    const bool wide = bytes && !sparse;
+    const struct { int id, rows, cost; } tiles[] = {{2, 128, 100}, {6, 96, 92}, {7, 160, wide ? 170 : 145}, {8, 224, wide ? 180 : 162}, {3, 256, sparse ? 185 : 205}};
+    long long best = -1;
+    int pick = id;
+    for (const auto &t : tiles) {
+        if (!taps && (t.id == 2 || t.id == 3) && t.id != id) continue;
+        const long long n = n_blocks(p, t.rows, 64), cost = (n + (n + ncu - 1) / ncu * ncu) * t.cost;
+        if (best < 0 || cost < best) { best = cost; pick = t.id; }
+    }
+    return pick;
+}
+
 // ---------------------------------------------------------------------------------------------
 // Few output pixels: which of the one-latency kernels (ss_conv_small.h) takes a problem.  Here and not beside them because the
 // workspace query and the entry points must know: a problem that they take never splits its reduction.
