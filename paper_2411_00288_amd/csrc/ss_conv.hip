@@ -193,18 +193,12 @@ static int fused_entry(const ss_weight_desc *d1, const void *x, int32_t N, int32
         MlpParams m{};
         m.x = static_cast<const uint16_t *>(x);
         m.a1_vals = static_cast<const uint8_t *>(w1) + kHeaderBytes;
-        m.a1_meta = reinterpret_cast<const uint32_t *>(m.a1_vals + (size_t)t1.Mt * t1.Ks * 1024);
         m.a2_vals = static_cast<const uint8_t *>(w2) + kHeaderBytes;
-        m.a2_meta = reinterpret_cast<const uint32_t *>(m.a2_vals + (size_t)t2.Mt * t2.Ks * 1024);
         m.bias1 = bias1; m.bias2 = bias2;
         m.res2 = static_cast<const uint16_t *>(residual);
         m.y2 = static_cast<uint16_t *>(y);
         m.P = (int)P; m.Cin = d1->cin; m.Cmid = d1->cout; m.Cout2 = d2->cout;
-        m.Ks1 = t1.Ks; m.Kp1 = t1.Kp; m.Ks2 = t2.Ks; m.Kp2 = t2.Kp; m.Mt2 = t2.Mt; m.act1 = act1; m.act2 = act2;
-        m.a1_bytes = (unsigned)((size_t)t1.Mt * t1.Ks * (SPARSE ? 1024 : 2048));
-        m.meta1_bytes = SPARSE ? (unsigned)((size_t)t1.Mt * t1.Kp * 256) : 4u;
-        m.a2_bytes = (unsigned)((size_t)t2.Mt * t2.Ks * (SPARSE ? 1024 : 2048));
-        m.meta2_bytes = SPARSE ? (unsigned)((size_t)t2.Mt * t2.Kp * 256) : 4u;
+        m.act1 = act1; m.act2 = act2;
         hipStream_t ms = static_cast<hipStream_t>(stream);
         if (d1->dtype == SS_F16) return SPARSE ? mlp_dispatch_f16_sparse(m, ms) : mlp_dispatch_f16_dense(m, ms);
         return SPARSE ? mlp_dispatch_bf16_sparse(m, ms) : mlp_dispatch_bf16_dense(m, ms);

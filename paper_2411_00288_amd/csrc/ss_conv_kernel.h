@@ -228,7 +228,8 @@ __device__ __forceinline__ float gelu_cdf(float z)
         q = __builtin_fmaf(q, a, -1.1511123180389404f);
         q = __builtin_fmaf(q, a, -0.9999998807907104f);
     }
-    return __builtin_fmaf(-a, __builtin_amdgcn_exp2f(q), fmaxf(z, 0.f));
+    // (the IEEE 754-2019 maximum: fmaxf takes a second instruction, which quiets a signalling NaN first)
+    return __builtin_fmaf(-a, __builtin_amdgcn_exp2f(q), floor_at(z, 0.f));
 }
 
 // How the [pixels x reduction-chunk] slice of the unfolded input is built in LDS:
@@ -1177,14 +1178,17 @@ void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, Con
 // ---------------------------------------------------------------------------------------------
 
 
-template <int DT, bool SPARSE, int KS1, int TILES>      // KS1: reduction steps of the first layer; TILES: output tiles per wave
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TILES == 1 ? (SPARSE ? 4 : 3) : (SPARSE ? 3 : 2))))
+// KS1: reduction steps of the first layer; TILES: output tiles per wave; GELU1: the first layer's activation is GELU (not a branch inside:
+// where the two loops meet again, accumulators went through memory)
+template <int DT, bool SPARSE, int KS1, int TILES, bool GELU1>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPARSE ? 4 : (TILES == 1 ? 3 : 2))))
 void mlp_kernel(MlpParams p)
 {
     constexpr int BN = 64, CH = 128;                      // pixels per workgroup, intermediate channels per chunk
+    constexpr int CIN = KS1 * 32;
     constexpr int CROW = CH + 4;                          // halfs per pixel row of the intermediate chunk (8-byte aligned rows)
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
-    constexpr int XROW = KS1 * 32 + 8;                         // halfs per pixel row of the input tile (16-byte aligned rows)
+    constexpr int XROW = CIN + 8;                         // halfs per pixel row of the input tile (16-byte aligned rows)
     uint16_t *Xs = smem;
     uint16_t *Cs = smem + BN * XROW;
     float *b1s = reinterpret_cast<float *>(Cs + BN * CROW);       // the first layer's bias, all Cmid values
@@ -1192,11 +1196,23 @@ void mlp_kernel(MlpParams p)
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 5, c = lane & 31;
-    const int n0 = blockIdx.x * BN;
-    const __amdgpu_buffer_rsrc_t r1 = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.a1_vals), 0, (int)p.a1_bytes, kRsrcFlags);
-    const __amdgpu_buffer_rsrc_t m1 = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.a1_meta), 0, (int)p.meta1_bytes, kRsrcFlags);
-    const __amdgpu_buffer_rsrc_t r2 = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.a2_vals), 0, (int)p.a2_bytes, kRsrcFlags);
-    const __amdgpu_buffer_rsrc_t m2 = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.a2_meta), 0, (int)p.meta2_bytes, kRsrcFlags);
+    const int n0 = blockIdx.x * BN, px_here = min(BN, p.P - n0);
+    // weight tiles: values, then (sparse) index words
+    constexpr int Kp1 = (KS1 + 1) / 2;
+    const int Ks2 = p.Cmid / 32, Kp2 = (Ks2 + 1) / 2, Mt2 = p.Cout2 / 32;
+    auto buffer = [](const void *base, unsigned bytes) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, base != nullptr ? (int)bytes : 0, kRsrcFlags);
+    };
+    const __amdgpu_buffer_rsrc_t r1 = buffer(p.a1_vals, (unsigned)(Ks2 * KS1) * (SPARSE ? 1024u : 2048u));
+    const __amdgpu_buffer_rsrc_t r2 = buffer(p.a2_vals, (unsigned)(Mt2 * Ks2) * (SPARSE ? 1024u : 2048u));
+    const __amdgpu_buffer_rsrc_t m1 = buffer(p.a1_vals + (size_t)(Ks2 * KS1) * 1024, SPARSE ? (unsigned)(Ks2 * Kp1) * 256u : 4u);
+    const __amdgpu_buffer_rsrc_t m2 = buffer(p.a2_vals + (size_t)(Mt2 * Ks2) * 1024, SPARSE ? (unsigned)(Mt2 * Kp2) * 256u : 4u);
+    // input, residual and output of this workgroup's pixels: whatever lies behind the last one is out of range
+    const __amdgpu_buffer_rsrc_t rx = buffer(p.x + (size_t)n0 * CIN, (unsigned)px_here * (CIN * 2u));
+    const unsigned out_bytes = (unsigned)px_here * (unsigned)p.Cout2 * 2u;
+    const __amdgpu_buffer_rsrc_t rres = buffer(p.res2 != nullptr ? p.res2 + (size_t)n0 * p.Cout2 : nullptr, out_bytes);
+    const __amdgpu_buffer_rsrc_t ry = buffer(p.y2 + (size_t)n0 * p.Cout2, out_bytes);
+    const __amdgpu_buffer_rsrc_t rb1 = buffer(p.bias1, (unsigned)p.Cmid * 4u), rb2 = buffer(p.bias2, (unsigned)p.Cout2 * 4u);
 
     struct Row1 {                                         // one 32-row tile of the first layer: all its reduction steps
         u32x4 v[SPARSE ? 1 : 2][KS1];
@@ -1206,89 +1222,87 @@ void mlp_kernel(MlpParams p)
 #pragma unroll
         for (int s = 0; s < KS1; s++) {
             if constexpr (SPARSE) {
-                r.v[0][s] = __builtin_amdgcn_raw_buffer_load_b128(r1, (int)(((unsigned)(mt * KS1 + s) * 64 + lane) * 16u), 0, 0);
-                r.idx[s] = __builtin_amdgcn_raw_buffer_load_b32(m1, (int)(((unsigned)(mt * p.Kp1 + (s >> 1)) * 64 + lane) * 4u), 0, 0);
+                r.v[0][s] = __builtin_amdgcn_raw_buffer_load_b128(r1, lane * 16, (mt * KS1 + s) * 1024, 0);
+                r.idx[s] = __builtin_amdgcn_raw_buffer_load_b32(m1, lane * 4, (mt * Kp1 + (s >> 1)) * 256, 0);
             } else {
-                const unsigned off = ((unsigned)(mt * KS1 + s) * 128 + lane) * 16u;
-                r.v[0][s] = __builtin_amdgcn_raw_buffer_load_b128(r1, (int)off, 0, 0);
-                r.v[1][s] = __builtin_amdgcn_raw_buffer_load_b128(r1, (int)off, 1024, 0);
+                r.v[0][s] = __builtin_amdgcn_raw_buffer_load_b128(r1, lane * 16, (mt * KS1 + s) * 2048, 0);
+                r.v[1][s] = __builtin_amdgcn_raw_buffer_load_b128(r1, lane * 16, (mt * KS1 + s) * 2048 + 1024, 0);
             }
         }
     };
-    // the second layer's weights for this wave's output tiles and the 4 reduction steps of one chunk
+    // The second layer's weights for this wave's output tiles and the 4 reduction steps of one chunk.  Tile t = wave + 4 * ti is row tile t / 2
+    // on pixel half t % 2, the same half for all of a wave's tiles.  (A wave without a last tile repeats the last one's loads and drops the result.)
     struct Row2 {
         u32x4 v[SPARSE ? 1 : 2][TILES][4];
         uint32_t idx[TILES][4];
     };
-    const int ntiles2 = p.Mt2 * 2;                        // output tiles of the second layer: (row tile, pixel half)
+    const int half = wave & 1;
+    auto row_tile = [&](int ti) { return min((wave + 4 * ti) >> 1, Mt2 - 1); };
     auto load_row2 = [&](Row2 &r, int mc) {
 #pragma unroll
         for (int ti = 0; ti < TILES; ti++) {
-            const int t = wave + 4 * ti;
-            const int rt = min(t, ntiles2 - 1) >> 1;      // (a wave without a last tile repeats the last one's loads and drops the result)
+            const int rt = row_tile(ti);
 #pragma unroll
             for (int s = 0; s < 4; s++) {
                 const int ks = mc * 4 + s;
                 if constexpr (SPARSE) {
-                    r.v[0][ti][s] = __builtin_amdgcn_raw_buffer_load_b128(r2, (int)(((unsigned)(rt * p.Ks2 + ks) * 64 + lane) * 16u), 0, 0);
-                    r.idx[ti][s] = __builtin_amdgcn_raw_buffer_load_b32(m2, (int)(((unsigned)(rt * p.Kp2 + (ks >> 1)) * 64 + lane) * 4u), 0, 0);
+                    r.v[0][ti][s] = __builtin_amdgcn_raw_buffer_load_b128(r2, lane * 16, (rt * Ks2 + ks) * 1024, 0);
+                    r.idx[ti][s] = __builtin_amdgcn_raw_buffer_load_b32(m2, lane * 4, (rt * Kp2 + (ks >> 1)) * 256, 0);
                 } else {
-                    const unsigned off = ((unsigned)(rt * p.Ks2 + ks) * 128 + lane) * 16u;
-                    r.v[0][ti][s] = __builtin_amdgcn_raw_buffer_load_b128(r2, (int)off, 0, 0);
-                    r.v[1][ti][s] = __builtin_amdgcn_raw_buffer_load_b128(r2, (int)off, 1024, 0);
+                    r.v[0][ti][s] = __builtin_amdgcn_raw_buffer_load_b128(r2, lane * 16, (rt * Ks2 + ks) * 2048, 0);
+                    r.v[1][ti][s] = __builtin_amdgcn_raw_buffer_load_b128(r2, lane * 16, (rt * Ks2 + ks) * 2048 + 1024, 0);
                 }
             }
         }
     };
 
+    // ---- the input tile: 64 pixel rows of Cin channels, four threads to a row, zeros past the last pixel (all loads on their way first)
     Row1 a1;
     Row2 a2;
-    load_row1(a1, wave);
-    // ---- the input tile: 64 pixel rows of Cin channels, 16-byte vectors, zeros past the last pixel (all loads on their way first)
+    f32x16 acc2[TILES];                                   // the bias starts in the accumulators
     {
-        constexpr int UPR = KS1 * 4, IT = BN * UPR / 256; // 16-byte units per row, units per thread
-        u32x4 v[IT];
+        u32x4 v[KS1];
+        const int row = tid >> 2, q4 = tid & 3;
 #pragma unroll
-        for (int i = 0; i < IT; i++) {
-            const int u = tid + i * 256, pg = n0 + u / UPR;
-            v[i] = u32x4{0u, 0u, 0u, 0u};
-            if (pg < p.P) v[i] = *reinterpret_cast<const u32x4 *>(p.x + (size_t)n0 * p.Cin + u * 8);
-        }
-        for (int i = tid; i < p.Cmid; i += 256) b1s[i] = p.bias1 ? p.bias1[i] : 0.f;
+        for (int i = 0; i < KS1; i++) v[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, row * (CIN * 2) + q4 * 16, i * 64, 0);
+        load_row1(a1, wave);
 #pragma unroll
-        for (int i = 0; i < IT; i++) {
-            const int u = tid + i * 256;
-            *reinterpret_cast<u32x4 *>(Xs + u / UPR * XROW + u % UPR * 8) = v[i];
-        }
+        for (int ti = 0; ti < TILES; ti++)
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                const f32x4 b = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rb2, g * 16, (row_tile(ti) * 32 + 8 * q) * 4, 0));
+#pragma unroll
+                for (int e = 0; e < 4; e++) acc2[ti][4 * q + e] = b[e];
+            }
+        for (int i = tid; i < p.Cmid; i += 256) b1s[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rb1, i * 4, 0, 0));
+#pragma unroll
+        for (int i = 0; i < KS1; i++) *reinterpret_cast<u32x4 *>(Xs + row * XROW + q4 * 8 + i * 32) = v[i];
     }
-    // the residual, in the output stage's thread -> (pixel, run) mapping: fetched during the last chunk
-    u32x4 rres[TILES][2];
+    // the residual, in the output stage's lane -> (pixel, run of 8 channels) mapping
+    const int out_lane = (lane >> 2) * p.Cout2 * 2 + (lane & 3) * 16;      // byte offset of the lane's run in a 16-pixel piece
+    auto out_piece = [&](int ti, int j) { return ((half * 32 + 16 * j) * p.Cout2 + row_tile(ti) * 32) * 2; };
+    u32x4 rres2[TILES][2];
     auto load_res = [&]() {
 #pragma unroll
         for (int ti = 0; ti < TILES; ti++)
 #pragma unroll
-            for (int jj = 0; jj < 2; jj++) {
-                const int t = wave + 4 * ti, it = lane + 64 * jj;
-                const int pg = n0 + (t & 1) * 32 + (it >> 2);
-                rres[ti][jj] = u32x4{0u, 0u, 0u, 0u};
-                if (p.res2 != nullptr && t < ntiles2 && pg < p.P)
-                    rres[ti][jj] = *reinterpret_cast<const u32x4 *>(p.res2 + (size_t)pg * p.Cout2 + (t >> 1) * 32 + (it & 3) * 8);
-            }
+            for (int j = 0; j < 2; j++) rres2[ti][j] = __builtin_amdgcn_raw_buffer_load_b128(rres, out_lane, out_piece(ti, j), 0);
     };
-    f32x16 acc2[TILES];
-#pragma unroll
-    for (int ti = 0; ti < TILES; ti++)
-#pragma unroll
-        for (int v = 0; v < 16; v++) acc2[ti][v] = 0.f;
     const float floor1 = p.act1 == SS_ACT_RELU ? 0.f : -__builtin_inff();
     __syncthreads();
 
     const int nchunks = p.Cmid / CH;
-    // Bound by the vector ALU: 154 M GELUs on the ConvNeXt-T stage-1 block at batch 128 are 63 us of its 120 (70 % of the SIMDs'
-    // cycles issue vector instructions).  The activation is chosen once, outside: a branch per element kept the evaluations from
-    // overlapping and cost 17 us (145 -> 128); the cheaper polynomial another 8.
-    auto chunks = [&](auto act1) {
-    for (int mc = 0; mc < nchunks; mc++) {
+    const uint16_t *const x_frag = Xs + c * XROW + 16 * g;
+    uint16_t *const c_dst = Cs + c * CROW + wave * 32 + 4 * g;
+    int c_at = BN * XROW + (half * 32 + c) * CROW + 16 * g;
+    asm volatile("" : "+v"(c_at));                        // (an address of its own: as an offset from another one it is too large for the instruction, and an addition per read)
+    const uint16_t *const c_frag = smem + c_at;
+    // Bound by the vector ALU: 154 M GELUs on the ConvNeXt-T stage-1 block at batch 128 are 61 us of it (twelve full-rate instructions of 4
+    // clocks and one of 8 per wave).  What else the vector ALU does is kept small: the activation is chosen outside the element loop, addresses
+    // are scalar, biases start in accumulators, the residual is fetched behind the chunks (during the last one, behind a condition, its registers
+    // travelled through copies in every chunk), and four waves per SIMD (128 registers) overlap one's matrix instructions with another's
+    // GELUs: 113 -> 96 us.
+    auto chunk = [&](auto act1, int mc) {
         // ---- first contraction: rows 128*mc + 32*wave + [0,32) of the intermediate, all 64 pixels
         f32x16 acc1[2];                                   // the bias starts in the accumulators
 #pragma unroll
@@ -1304,7 +1318,7 @@ void mlp_kernel(MlpParams p)
         for (int s = 0; s < KS1; s++) {
 #pragma unroll
             for (int tn = 0; tn < 2; tn++) {
-                const uint16_t *src = Xs + (tn * 32 + c) * XROW + 32 * s + 16 * g;
+                const uint16_t *src = x_frag + tn * 32 * XROW + 32 * s;
                 B32 bf;
                 bf.lo = *reinterpret_cast<const u32x4 *>(src);
                 bf.hi = *reinterpret_cast<const u32x4 *>(src + 8);
@@ -1322,91 +1336,77 @@ void mlp_kernel(MlpParams p)
             for (int tn = 0; tn < 2; tn++) {
                 float r[4];
 #pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    r[e] = act1(acc1[tn][4 * q + e]);
-                }
-                *reinterpret_cast<uint2 *>(Cs + (tn * 32 + c) * CROW + wave * 32 + 8 * q + 4 * g) =
-                    make_uint2(cvt_pack2<DT>(r[0], r[1]), cvt_pack2<DT>(r[2], r[3]));
+                for (int e = 0; e < 4; e++) r[e] = act1(acc1[tn][4 * q + e]);
+                *reinterpret_cast<uint2 *>(c_dst + tn * 32 * CROW + 8 * q) = make_uint2(cvt_pack2<DT>(r[0], r[1]), cvt_pack2<DT>(r[2], r[3]));
             }
             __builtin_amdgcn_sched_barrier(0);            // eight evaluations overlap; more at once cost a wave per SIMD in registers
         }
         // (issued here, when the first contraction's accumulators are dead: four waves per SIMD hide the latency better than an
         // earlier issue at three)
         load_row2(a2, mc);
-        if (mc + 1 < nchunks) load_row1(a1, (mc + 1) * 4 + wave);       // in flight while the second contraction runs
-        else load_res();
+        load_row1(a1, min(mc + 1, nchunks - 1) * 4 + wave);      // in flight while the second contraction runs (behind the last chunk: not used)
         lds_barrier();
         // ---- second contraction: this chunk's 128 intermediate channels into the output accumulators
+        B32 bf[2];
+        auto load_frag = [&](B32 &f, int s) {
+            const uint16_t *src = c_frag + 32 * s;        // 8-byte aligned
+            const uint2 u0 = *reinterpret_cast<const uint2 *>(src), u1 = *reinterpret_cast<const uint2 *>(src + 4);
+            const uint2 u2 = *reinterpret_cast<const uint2 *>(src + 8), u3 = *reinterpret_cast<const uint2 *>(src + 12);
+            f.lo = u32x4{u0.x, u0.y, u1.x, u1.y};
+            f.hi = u32x4{u2.x, u2.y, u3.x, u3.y};
+        };
+        load_frag(bf[0], 0);
 #pragma unroll
-        for (int ti = 0; ti < TILES; ti++) {
-            const int t = wave + 4 * ti;
-            const int ct = t & 1;
+        for (int s = 0; s < 4; s++) {
+            if (s < 3) load_frag(bf[(s + 1) & 1], s + 1);
 #pragma unroll
-            for (int s = 0; s < 4; s++) {
-                const uint16_t *src = Cs + (ct * 32 + c) * CROW + 32 * s + 16 * g;       // 8-byte aligned
-                const uint2 u0 = *reinterpret_cast<const uint2 *>(src), u1 = *reinterpret_cast<const uint2 *>(src + 4);
-                const uint2 u2 = *reinterpret_cast<const uint2 *>(src + 8), u3 = *reinterpret_cast<const uint2 *>(src + 12);
-                B32 bf;
-                bf.lo = u32x4{u0.x, u0.y, u1.x, u1.y};
-                bf.hi = u32x4{u2.x, u2.y, u3.x, u3.y};
+            for (int ti = 0; ti < TILES; ti++) {
                 if constexpr (SPARSE) {
-                    acc2[ti] = mma_sparse<DT>(a2.v[0][ti][s], bf, acc2[ti], a2.idx[ti][s] >> ((s & 1) * 16));
+                    acc2[ti] = mma_sparse<DT>(a2.v[0][ti][s], bf[s & 1], acc2[ti], a2.idx[ti][s] >> ((s & 1) * 16));
                 } else {
-                    acc2[ti] = mma_dense<DT>(a2.v[0][ti][s], bf.lo, acc2[ti]);
-                    acc2[ti] = mma_dense<DT>(a2.v[1][ti][s], bf.hi, acc2[ti]);
+                    acc2[ti] = mma_dense<DT>(a2.v[0][ti][s], bf[s & 1].lo, acc2[ti]);
+                    acc2[ti] = mma_dense<DT>(a2.v[1][ti][s], bf[s & 1].hi, acc2[ti]);
                 }
             }
+            __builtin_amdgcn_sched_barrier(0);            // (all four steps' fragments at once would not fit the registers)
         }
         lds_barrier();                                    // the chunk buffer is free again
-    }
     };
-    if (p.act1 == SS_ACT_GELU) chunks([](float z) { return gelu_cdf<DT>(z); });
+    auto chunks = [&](auto act1) {
+        for (int mc = 0; mc < nchunks; mc++) chunk(act1, mc);
+    };
+    if constexpr (GELU1) chunks([](float z) { return gelu_cdf<DT>(z); });
     else chunks([floor1](float z) { return floor_at(z, floor1); });
+    load_res();
 
-    // ---- output: bias + residual + activation in fp32, one rounding; each 32 x 32 tile crosses the wave's own LDS region
+    // ---- output: residual + activation in fp32, one rounding; each 32 x 32 tile crosses the wave's own LDS region
     // (the input tile and the chunk buffer are dead: the loop ended with a barrier) and leaves as 16-byte runs
     float *reg = reinterpret_cast<float *>(smem) + wave * (32 * kFuseRow);
-    const float floor2 = p.act2 == SS_ACT_RELU ? 0.f : -__builtin_inff();
     auto finish = [&](auto act2) {
 #pragma unroll
-    for (int ti = 0; ti < TILES; ti++) {
-        const int t = wave + 4 * ti;
-        if (t >= ntiles2) break;                          // uniform
-        const int rt = t >> 1, ct = t & 1;
+        for (int ti = 0; ti < TILES; ti++) {
+            if (wave + 4 * ti >= Mt2 * 2) break;          // uniform
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const float4 bq = p.bias2 ? *reinterpret_cast<const float4 *>(p.bias2 + rt * 32 + 8 * q + 4 * g) : make_float4(0.f, 0.f, 0.f, 0.f);
-            *reinterpret_cast<float4 *>(reg + c * kFuseRow + 8 * q + 4 * g) =
-                make_float4(acc2[ti][4 * q + 0] + bq.x, acc2[ti][4 * q + 1] + bq.y, acc2[ti][4 * q + 2] + bq.z, acc2[ti][4 * q + 3] + bq.w);
-        }
+            for (int q = 0; q < 4; q++)
+                *reinterpret_cast<f32x4 *>(reg + c * kFuseRow + 8 * q + 4 * g) = f32x4{acc2[ti][4 * q + 0], acc2[ti][4 * q + 1], acc2[ti][4 * q + 2], acc2[ti][4 * q + 3]};
 #pragma unroll
-        for (int j = 0; j < 2; j++) {
-            const int it = lane + 64 * j;
-            const int px = it >> 2, run = it & 3;
-            const int pg = n0 + ct * 32 + px, o = rt * 32 + run * 8;
-            const float4 lo = *reinterpret_cast<const float4 *>(reg + px * kFuseRow + run * 8);
-            const float4 hi = *reinterpret_cast<const float4 *>(reg + px * kFuseRow + run * 8 + 4);
-            if (pg >= p.P) continue;
-            float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-            if (p.res2 != nullptr) {
-                const u32x4 rr = rres[ti][j];
+            for (int j = 0; j < 2; j++) {
+                const float *src = reg + ((lane >> 2) + 16 * j) * kFuseRow + (lane & 3) * 8;
+                const f32x4 lo = *reinterpret_cast<const f32x4 *>(src), hi = *reinterpret_cast<const f32x4 *>(src + 4);
+                const float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+                u32x4 w;
 #pragma unroll
                 for (int e = 0; e < 4; e++) {
-                    v[2 * e] += widen<DT>((uint16_t)(rr[e] & 0xFFFFu));
-                    v[2 * e + 1] += widen<DT>((uint16_t)(rr[e] >> 16));
+                    const uint32_t rr = rres2[ti][j][e];
+                    w[e] = cvt_pack2<DT>(act2(v[2 * e] + widen<DT>((uint16_t)(rr & 0xFFFFu))), act2(v[2 * e + 1] + widen<DT>((uint16_t)(rr >> 16))));
                 }
+                __builtin_amdgcn_raw_buffer_store_b128(w, ry, out_lane, out_piece(ti, j), 0);
             }
-            uint32_t w[4];
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-                w[e] = cvt_pack2<DT>(act2(v[2 * e]), act2(v[2 * e + 1]));
-            }
-            *reinterpret_cast<uint4 *>(p.y2 + (size_t)pg * p.Cout2 + o) = make_uint4(w[0], w[1], w[2], w[3]);
         }
-    }
     };
     if (p.act2 == SS_ACT_GELU) finish([](float z) { return gelu_cdf<DT>(z); });
-    else finish([floor2](float z) { return floor_at(z, floor2); });
+    else if (p.act2 == SS_ACT_RELU) finish([](float z) { return floor_at(z, 0.f); });
+    else finish([](float z) { return z; });
 }
 
 template <int DT, bool SPARSE>
@@ -1419,12 +1419,14 @@ static int launch_mlp(const MlpParams &p, hipStream_t s)
     if (smem < epi) smem = epi;
     auto go = [&](auto ks1) {
         constexpr int KS1 = decltype(ks1)::value;
-        if (p.Mt2 <= 2) mlp_kernel<DT, SPARSE, KS1, 1><<<dim3((unsigned)blocks), dim3(256), smem, s>>>(p);
-        else mlp_kernel<DT, SPARSE, KS1, 2><<<dim3((unsigned)blocks), dim3(256), smem, s>>>(p);
+        const bool gelu = p.act1 == SS_ACT_GELU;
+        const auto kern = p.Cout2 <= 64 ? (gelu ? mlp_kernel<DT, SPARSE, KS1, 1, true> : mlp_kernel<DT, SPARSE, KS1, 1, false>)
+                                        : (gelu ? mlp_kernel<DT, SPARSE, KS1, 2, true> : mlp_kernel<DT, SPARSE, KS1, 2, false>);
+        kern<<<dim3((unsigned)blocks), dim3(256), smem, s>>>(p);
         return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP;
     };
     using std::integral_constant;
-    switch (p.Ks1) {
+    switch (p.Cin / 32) {
         case 1: return go(integral_constant<int, 1>{});
         case 2: return go(integral_constant<int, 2>{});
         case 3: return go(integral_constant<int, 3>{});

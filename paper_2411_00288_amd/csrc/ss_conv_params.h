@@ -91,15 +91,13 @@ static inline void fast_div_setup(unsigned d, unsigned *mul, unsigned *sh)
     *mul = (unsigned)(((1ull << (31 + s)) + d - 1) / d);
 }
 
-struct MlpParams {
+struct MlpParams {            // (a cheap launch, see ConvArgs; all channel counts are multiples of 32)
     const uint16_t *x;        // [P][Cin]
     const uint8_t *a1_vals, *a2_vals;
-    const uint32_t *a1_meta, *a2_meta;
     const float *bias1, *bias2;
     const uint16_t *res2;     // [P][Cout2] or nullptr
     uint16_t *y2;             // [P][Cout2]
-    int P, Cin, Cmid, Cout2, Ks1, Kp1, Ks2, Kp2, Mt2, act1, act2;
-    unsigned a1_bytes, meta1_bytes, a2_bytes, meta2_bytes;
+    int P, Cin, Cmid, Cout2, act1, act2;
 };
 
 constexpr int kMlpKs1 = 4;        // first reduction: at most 128 input channels
