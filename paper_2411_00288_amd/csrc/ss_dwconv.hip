@@ -23,16 +23,16 @@ __device__ __forceinline__ void widen8(const u32x4 &v, float (&f)[8])
     }
 }
 
+// Two fp32 values to one dword of 16-bit floats, round to nearest even, in one instruction.
 template <int DT>
 __device__ __forceinline__ uint32_t pack2(float a, float b)
 {
-    if constexpr (DT == SS_F16) {
-        _Float16 ha = (_Float16)a, hb = (_Float16)b;
-        return (uint32_t)__builtin_bit_cast(uint16_t, ha) | ((uint32_t)__builtin_bit_cast(uint16_t, hb) << 16);
-    } else {
-        __bf16 ha = (__bf16)a, hb = (__bf16)b;
-        return (uint32_t)__builtin_bit_cast(uint16_t, ha) | ((uint32_t)__builtin_bit_cast(uint16_t, hb) << 16);
-    }
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const f32x2 v = {a, b};
+    if constexpr (DT == SS_F16) return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2));
+    else return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
 constexpr int TW = 4;      // adjacent outputs along the image row per thread: a loaded input vector serves up to KW of them
@@ -136,6 +136,8 @@ struct DwParams {
     int H, W, C, ph, pw, Ho, Wo, act;
     int per;                              // workgroups per group of channels (not from the grid's size: that would lengthen the launch's arguments to more than 112 bytes, which costs the host 0.9 us)
     int R, segs, wt, strips, groups;      // output rows per strip, segments per image, 16-wide tiles per row, strips in all, groups of 16 channels
+    int rows, more;                       // rows of the blocks of 16 strips for each workgroup of a group: `rows`, and R or 1 (whole blocks or rows are
+    int share;                            // dealt out: share) further ones for the first `more` of them
     unsigned x_bytes, w_bytes, y_bytes;
 };
 static_assert(sizeof(DwParams) <= 112, "a cheap launch");
@@ -161,7 +163,11 @@ __device__ __forceinline__ void lds_barrier()
 }
 
 constexpr int kDwGroup = 16;              // channels of a workgroup
-constexpr int kDwIn = 16 * 16 * 32;       // 16-bit units of an input buffer: [channel][strip][32 pixels]
+// 16-bit units of an input buffer: [channel][strip][32 pixels].  The four 16-byte vectors of a strip are XOR-ed with bits 2..3 of the strip's
+// number, so that a fragment read (one vector of sixteen strips) covers all banks, and the upper eight channels, which the same lanes' neighbours
+// write, lie 32 bytes further.
+constexpr int kDwIn = 16 * 16 * 32 + 16;
+__device__ __forceinline__ int dw_in_at(int channel, int strip, int vec) { return channel * 512 + (channel >> 3) * 16 + strip * 32 + ((vec ^ (strip >> 2)) & 3) * 8; }
 constexpr int kDwPixel = 12;              // dwords per pixel of the output buffer (8 used) and
 constexpr int kDwStrip = 16 * kDwPixel + 4;      // per strip: 16-byte aligned runs whose writes spread over the banks
 
@@ -174,11 +180,20 @@ __global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // neighbouring workgroups, which share halo rows and the other channel groups' cache lines, on one XCD; a workgroup keeps its
-    // channel group and takes every per-th block of 16 strips
+    // channel group
     const int nb = p.per * p.groups, xcd = blockIdx.x & 7;
     const int lid = xcd * (nb >> 3) + min(xcd, nb & 7) + (blockIdx.x >> 3);
-    const int c0 = (lid % p.groups) * kDwGroup, first = lid / p.groups, stride = p.per;
-    const int nblocks = (p.strips + 15) >> 4;
+    const int c0 = (lid % p.groups) * kDwGroup, first = lid / p.groups;
+    // This workgroup's share of the group's work, the rows of its blocks of 16 strips after each other: whole blocks, or (share = 1) rows dealt out
+    // evenly.  A run of rows inside a block costs K - 1 input rows more than it has.
+    const int lo = first * p.rows + min(first, p.more) * p.share, hi = lo + p.rows + (first < p.more ? p.share : 0);
+    struct Run {
+        int block, row, len;              // rows [row, row + len) of the block's strips
+    };
+    auto run_at = [&](int pos) {          // (behind the last row: an empty one)
+        const int block = pos / p.R, row = pos - block * p.R;
+        return Run{block, row, min(p.R - row, hi - pos)};
+    };
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.x), 0, (int)p.x_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.w), 0, (int)p.w_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, (int)p.y_bytes, 0x00020000);
@@ -194,19 +209,20 @@ __global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
         const int rest = s / p.wt, img = rest / p.segs;
         return Strip{img, (rest - img * p.segs) * p.R, (s - rest * p.wt) * 16, s < p.strips};
     };
-    const int steps = p.R + K - 1;                        // input rows of a strip
     // ---- staging: 384 threads, two neighbouring pixels x 8 channels each (the other 128 load nothing and write their zeros to
     // the unused pixels 24 .. 31, which must be finite: no branch, so that the compiler's waits count the loads in flight exactly)
     const bool stages = tid < 384;
     const int so = tid & 1, sp = stages ? (tid >> 1) % 12 : 12 + ((tid >> 1) & 3), sn = stages ? tid / 24 : (tid >> 3) & 15;
-    const int sdst = (so * 8 * 16 + sn) * 16 + sp;
+    const int sdst = dw_in_at(so * 8, sn, sp >> 2) / 2 + (sp & 3);
     const unsigned row_bytes = (unsigned)(p.W * p.C * 2);
     unsigned soff[2];                                     // byte offset of the thread's two pixels in the next row
-    int srow = 0, lblock = first, li = 0;                 // next row to load: block of strips, input row of the strip
+    int srow = 0, lpos = lo, li = 0, lsteps = 0;          // next row to load: start of the run, input row of the run, input rows it has
     auto aim_loads = [&]() {
-        const Strip s = strip(lblock, sn);
-        const bool ok = stages && s.ok && lblock < nblocks && c0 + so * 8 < p.C;
-        srow = s.row - p.ph;
+        const Run r = run_at(lpos);
+        const Strip s = strip(r.block, sn);
+        const bool ok = stages && s.ok && r.len > 0 && c0 + so * 8 < p.C;
+        srow = s.row + r.row - p.ph;
+        lsteps = max(r.len, 1) + K - 1;
 #pragma unroll
         for (int j = 0; j < 2; j++) {
             const int iw = s.col - p.pw + 2 * sp + j;
@@ -224,9 +240,9 @@ __global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
             soff[j] += row_bytes;                         // (an offset out of range stays so: the image is smaller than 2 GiB)
         }
         srow++;
-        if (++li == steps) {                              // uniform
+        if (++li == lsteps) {                             // uniform
             li = 0;
-            lblock += stride;
+            lpos = min(lpos + lsteps - (K - 1), hi);
             aim_loads();
         }
     };
@@ -243,6 +259,7 @@ __global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
     for (int i = 0; i < K; i++) load_row(st[i]);
     // ---- the wave's two channels: K Toeplitz fragments each, from zero-padded rows of taps [channel pair][r][t + 15] in LDS
     const int m = lane & 15, kg = lane >> 4, cw = c0 + wave * 2;
+    const int frag = dw_in_at(wave * 2, m, kg);           // (the pair's channels lie 512 apart)
     constexpr int TROW = 48;
     static_assert(8 * K * TROW <= 2 * 16 * kDwStrip, "the taps fit the output buffers");
     uint32_t *const taps = &out_s[0][0];
@@ -276,13 +293,15 @@ __global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
     // ---- output: one 16-byte run of a pixel per thread, range-checked
     const int oo = tid & 1, ow = (tid >> 1) & 15, on = tid >> 5;
     const unsigned yrow = (unsigned)(p.Wo * p.C * 2);
-    int rows_left = 0, block = first;                     // output rows of this thread's strip
+    int rows_left = 0, pos = lo, steps = 0;               // output rows of this thread's strip; start and input rows of the run
     unsigned yoff = 0;
     auto aim_stores = [&]() {
-        const Strip s = strip(block, on);
+        const Run r = run_at(pos);
+        const Strip s = strip(r.block, on);
         const bool ok = s.ok && s.col + ow < p.Wo && c0 + oo * 8 < p.C;
-        rows_left = ok ? min(p.R, p.Ho - s.row) : 0;
-        yoff = (unsigned)((((s.img * p.Ho + s.row) * p.Wo + s.col + ow) * p.C + c0 + oo * 8) * 2);
+        rows_left = ok ? min(r.len, p.Ho - s.row - r.row) : 0;
+        yoff = (unsigned)((((s.img * p.Ho + s.row + r.row) * p.Wo + s.col + ow) * p.C + c0 + oo * 8) * 2);
+        steps = r.len + K - 1;
     };
     aim_stores();
     const float floor = p.act == SS_ACT_RELU ? 0.f : -__builtin_inff();
@@ -306,13 +325,12 @@ __global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
 #pragma unroll
         for (int u = 0; u < K; u++) {
             // input row i of the block is in buffer par, the K rows after it are in or on their way to st[]
-            const u32x4 bf[2] = {*reinterpret_cast<const u32x4 *>(in_s[par] + ((wave * 2) * 16 + m) * 32 + 8 * kg),
-                                 *reinterpret_cast<const u32x4 *>(in_s[par] + ((wave * 2 + 1) * 16 + m) * 32 + 8 * kg)};
+            const u32x4 bf[2] = {*reinterpret_cast<const u32x4 *>(in_s[par] + frag), *reinterpret_cast<const u32x4 *>(in_s[par] + frag + 512)};
             store_row(par ^ 1, st[(u + 1) % K]);
             load_row(st[(u + 1) % K]);
             emit(par ^ 1);
 #pragma unroll
-            for (int r = 0; r < K; r++)
+            for (int r = K - 1; r >= 0; r--)              // (the filter row that completes an output row first: its rounding overlaps with the others)
 #pragma unroll
                 for (int j = 0; j < 2; j++)
                     acc[j][(u + K - r) % K] = mma16<DT>(a[j][r], bf[j], r == 0 ? b4[j] : acc[j][(u + K - r) % K]);
@@ -325,14 +343,14 @@ __global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
                     dst[e * kDwPixel] = v;
                     top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, v & 0x7FFF7FFFu));
                 }
-                pending = (yoff + (unsigned)h * yrow) | ((unsigned)h < (unsigned)rows_left ? 0u : kOut);
+                pending = (yoff + (unsigned)h * yrow) | (h >= 0 && h < rows_left ? 0u : kOut);
             }
             lds_barrier();
             par ^= 1;
             if (++i == steps) {                           // uniform
                 i = 0;
-                block += stride;
-                if (block >= nblocks) { more = false; break; }
+                pos += steps - (K - 1);
+                if (pos >= hi) { more = false; break; }
                 aim_stores();
             }
         }
@@ -342,16 +360,17 @@ __global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
     __syncthreads();
     if (odd_s == 0) return;
     // ---- non-finite values: this workgroup's outputs again, each from its own window alone
-    for (block = first; block < nblocks; block += stride) {
+    for (pos = lo; pos < hi; pos += steps - (K - 1)) {
         aim_stores();
-        const Strip s = strip(block, on);
+        const Run run = run_at(pos);
+        const Strip s = strip(run.block, on);
         const int c = c0 + oo * 8, wo = s.col + ow;
         for (int h = 0; h < rows_left; h++) {
             float v[8];
 #pragma unroll
             for (int e = 0; e < 8; e++) v[e] = p.bias ? p.bias[c + e] : 0.f;
             for (int r = 0; r < K; r++) {
-                const int ih = s.row + h - p.ph + r;
+                const int ih = s.row + run.row + h - p.ph + r;
                 if ((unsigned)ih >= (unsigned)p.H) continue;
                 for (int t = 0; t < K; t++) {
                     const int iw = wo - p.pw + t;
@@ -371,7 +390,9 @@ __global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
     }
 }
 
-// Segments per image: those for which the busiest workgroup walks over the fewest input rows (a strip of R output rows needs R + K - 1).
+// Segments per image and their shares: those for which the busiest workgroup walks over the fewest input rows (a run of R output rows needs
+// R + K - 1).  Dealt out row by row, 32 blocks of 56 rows keep 42 workgroups of a channel group busy for 43 + 2 * 6 rows instead of 32 of them for
+// 62 (128 x 56 x 56 x 96, 7x7: 46.5 -> 44.5 us); where both walk over as many rows, whole blocks have fewer seams (64 images: 29.2 against 29.7).
 template <int DT, int K>
 static int launch_dw_mfma(DwParams p, int N, hipStream_t s)
 {
@@ -387,11 +408,15 @@ static int launch_dw_mfma(DwParams p, int N, hipStream_t s)
         const long long strips = (long long)N * segs * p.wt, blocks = (strips + 15) / 16;
         if (strips > 0x7FFFFFF0ll) break;
         const long long cost = (blocks + per_group - 1) / per_group * (R + K - 1);
-        if (best < 0 || cost < best) { best = cost; p.R = R; p.segs = segs; p.strips = (int)strips; }
+        if (best < 0 || cost < best || (cost == best && p.share != p.R)) { best = cost; p.R = p.share = R; p.segs = segs; p.strips = (int)strips; }
+        const long long rows = (blocks * R + per_group - 1) / per_group, even = rows + ((rows + R - 2) / R + 1) * (K - 1);      // (the most runs that so many rows can touch)
+        if (blocks * R >= per_group && even < best) { best = even; p.R = R; p.share = 1; p.segs = segs; p.strips = (int)strips; }
     }
     if (best < 0) return SS_ERR_UNSUPPORTED;
-    const long long blocks = (p.strips + 15ll) / 16;
-    p.per = (int)(blocks < per_group ? blocks : per_group);
+    const long long units = (p.strips + 15ll) / 16 * (p.R / p.share);
+    p.per = (int)(units < per_group ? units : per_group);
+    p.rows = (int)(units / p.per) * p.share;
+    p.more = (int)(units % p.per);
     dwconv_mfma_kernel<DT, K><<<dim3((unsigned)(p.per * p.groups)), dim3(512), 0, s>>>(p);
     return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP;
 }

@@ -97,3 +97,22 @@ def test_matrix_kernel_keeps_non_finite_values_in_their_windows(ss, value):
     assert not torch.isfinite(y[hit].float()).any()
     assert torch.isfinite(y[~hit].float()).all()
     assert (y[~hit].float() - clean[~hit].float()).abs().max() <= 0.125      # (fp32 sums in another order, one rounding)
+
+
+@pytest.mark.parametrize("shape", [(58, 19, 3, 520, 7), (58, 19, 9, 520, 5)])
+def test_rows_dealt_out_evenly(ss, shape):
+    """Four blocks of 16 images on seven workgroups of a channel group: runs of 10 or 11 of a block's 19 rows, some in two blocks; then a
+    non-finite value, for which a workgroup goes through its runs again."""
+    N, H, W, C, k = shape
+    rng = np.random.Generator(np.random.PCG64(W))
+    xb = wl.to_bits(rng.standard_normal((N, H, W, C), dtype=np.float32), wl.F16)
+    wb = wl.to_bits(rng.standard_normal((k, k, C), dtype=np.float32) * np.float32((2.0 / (k * k)) ** 0.5), wl.F16)
+    bias = (rng.standard_normal(C) * 0.1).astype(np.float32)
+    y = _run(ss, xb, wb, bias, wl.F16, (k // 2, k // 2), wl.ACT_NONE)
+    check_close(y, oracle.dwconv2d(xb, wb, dtype=wl.F16, bias=bias, pad=(k // 2, k // 2), act=wl.ACT_NONE), f"{shape}")
+    xb[33, 10, 1, 77] = 0x7C00
+    z = _run(ss, xb, wb, bias, wl.F16, (k // 2, k // 2), wl.ACT_NONE)
+    hit = torch.zeros(z.shape, dtype=torch.bool, device="cuda")
+    hit[33, 10 - k // 2:11 + k // 2, :2 + k // 2, 77] = True
+    assert not torch.isfinite(z[hit].float()).any() and torch.isfinite(z[~hit].float()).all()
+    assert (z[~hit].float() - y[~hit].float()).abs().max() <= 0.0625         # (fp32 sums in another order, one rounding: values up to 8)
