@@ -83,11 +83,14 @@ __device__ __forceinline__ ConvParams unpack_args(const ConvArgs &a)
     p.kw = WINDOW ? a.window.kw : KW;
     p.nsplit = WINDOW || SMALL ? 1 : (int)a.extra;
     p.ws_part = WINDOW ? nullptr : a.ws_part;
-    p.Ks = (p.K + 31) / 32;                               // (as tile_dims: K counts 2-byte units, for 8-bit operands an even number to the step)
-    p.Kp = is_byte_type(DT) ? p.Ks : (p.Ks + 1) / 2;
-    p.Mt = (p.Cout + 31) / 32;
-    p.a_bytes = (unsigned)p.Mt * (unsigned)p.Ks * (SPARSE ? 1024u : 2048u);
-    p.a_meta = reinterpret_cast<const uint32_t *>(p.a_vals + (size_t)p.Mt * p.Ks * 1024);
+    // (unsigned throughout: a signed division by a power of two is four scalar instructions instead of one, and these stand before
+    // the first load.  Packed weights are below 4 GiB)
+    p.Ks = (int)(((unsigned)p.K + 31u) / 32u);            // (as tile_dims: K counts 2-byte units, for 8-bit operands an even number to the step)
+    p.Kp = is_byte_type(DT) ? p.Ks : (int)(((unsigned)p.Ks + 1u) / 2u);
+    p.Mt = (int)(((unsigned)p.Cout + 31u) / 32u);
+    const unsigned steps = (unsigned)p.Mt * (unsigned)p.Ks;
+    p.a_bytes = steps * (SPARSE ? 1024u : 2048u);
+    p.a_meta = reinterpret_cast<const uint32_t *>(p.a_vals + (SPARSE ? p.a_bytes : 0u));
     p.meta_bytes = SPARSE ? (unsigned)p.Mt * (unsigned)p.Kp * 256u : 4u;
     p.x_bytes = (unsigned)(fast_div(p.P, p.howo_mul, p.howo_sh) * p.H) * (unsigned)p.W * (unsigned)p.Cin * 2u;
     return p;

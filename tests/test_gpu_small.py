@@ -52,6 +52,24 @@ def test_small_grid_kernels_with_a_residual(ss, force_tile, tile, cout, act):
                                  stride=(1, 1), pad=(1, 1), act=act, residual=res), L.name)
 
 
+# Pointwise shares: exactly a ring of whole steps (256, 512: 2 and 4 waves), more than a ring from an odd step (2304 over 8 waves, 2560
+# over 16: nine and five steps each), a share that ends early (480), a last step that is not whole (504, 2568).
+@pytest.mark.parametrize("sparse", [True, False])
+@pytest.mark.parametrize("tile", [20, 21, 22])
+@pytest.mark.parametrize("cin,cout,s", [(256, 64, 1), (480, 38, 1), (504, 33, 1), (512, 68, 2), (2304, 36, 1), (2560, 40, 1), (2568, 34, 2)])
+def test_pointwise_shares_of_whole_and_ragged_steps(ss, force_tile, cin, cout, s, tile, sparse):
+    L = L_(1, 7, 9, cin, cout, 1, s=s, dtype=wl.BF16 if cin % 64 else wl.F16)
+    d = wl.make_inputs(L)
+    res = wl.to_bits(np.random.Generator(np.random.PCG64(5)).standard_normal((1, L.Ho, L.Wo, cout), dtype=np.float32), L.dtype)
+    desc = layer_desc(ss, L)
+    pack, run = (ss.ss_mask_compress, ss.ss_conv2d_res_fwd) if sparse else (ss.ss_dense_pack, ss.ss_conv2d_dense_res_fwd)
+    w = pack(desc, dev_bits(d["W"], L.dtype), torch.from_numpy(d["M"]).cuda())
+    force_tile(tile)
+    y = run(desc, dev_bits(d["x"], L.dtype), w, torch.from_numpy(d["bias"]).cuda(), dev_bits(res, L.dtype), (s, s), (0, 0), L.act)
+    check_close(y, oracle.conv2d(d["x"], d["W"], d["M"], cin=cin, kh=1, kw=1, korder=L.korder, dtype=L.dtype, bias=d["bias"],
+                                 stride=(s, s), pad=(0, 0), act=L.act, residual=res), L.name)
+
+
 @pytest.mark.parametrize("tile", [20, 21, 22])
 @pytest.mark.parametrize("f8", [False, True])
 @pytest.mark.parametrize("cin,k,korder", [(64, 3, wl.K_CRS), (320, 3, wl.K_CRS), (48, 3, wl.K_RSC), (1040, 1, wl.K_CRS), (192, 2, wl.K_CRS)])
