@@ -83,14 +83,15 @@ __device__ __forceinline__ ConvParams unpack_args(const ConvArgs &a)
     p.kw = WINDOW ? a.window.kw : KW;
     p.nsplit = WINDOW || SMALL ? 1 : (int)a.extra;
     p.ws_part = WINDOW ? nullptr : a.ws_part;
-    // (unsigned throughout: a signed division by a power of two is four scalar instructions instead of one, and these stand before
-    // the first load.  Packed weights are below 4 GiB)
-    p.Ks = (int)(((unsigned)p.K + 31u) / 32u);            // (as tile_dims: K counts 2-byte units, for 8-bit operands an even number to the step)
-    p.Kp = is_byte_type(DT) ? p.Ks : (int)(((unsigned)p.Ks + 1u) / 2u);
-    p.Mt = (int)(((unsigned)p.Cout + 31u) / 32u);
-    const unsigned steps = (unsigned)p.Mt * (unsigned)p.Ks;
-    p.a_bytes = steps * (SPARSE ? 1024u : 2048u);
-    p.a_meta = reinterpret_cast<const uint32_t *>(p.a_vals + (SPARSE ? p.a_bytes : 0u));
+    // The few-pixel kernels divide unsigned: signed, a division by a power of two is four scalar instructions instead of one, and these
+    // stand before their first load.  (In the tiled kernels, which the same gives nothing to measure, a step count known to be positive
+    // made the compiler unroll the 8-bit 2x2 loops until they spilled: 8.1 -> 12.1 us for an FP8 layer of 448 x 108 channels.)
+    using Count = typename std::conditional<SMALL, unsigned, int>::type;
+    p.Ks = (int)(((Count)p.K + 31) / 32);                 // (as tile_dims: K counts 2-byte units, for 8-bit operands an even number to the step)
+    p.Kp = is_byte_type(DT) ? p.Ks : (int)(((Count)p.Ks + 1) / 2);
+    p.Mt = (int)(((Count)p.Cout + 31) / 32);
+    p.a_bytes = (unsigned)p.Mt * (unsigned)p.Ks * (SPARSE ? 1024u : 2048u);
+    p.a_meta = reinterpret_cast<const uint32_t *>(p.a_vals + (SMALL ? (size_t)(SPARSE ? p.a_bytes : 0u) : (size_t)p.Mt * p.Ks * 1024));
     p.meta_bytes = SPARSE ? (unsigned)p.Mt * (unsigned)p.Kp * 256u : 4u;
     p.x_bytes = (unsigned)(fast_div(p.P, p.howo_mul, p.howo_sh) * p.H) * (unsigned)p.W * (unsigned)p.Cin * 2u;
     return p;
@@ -435,12 +436,17 @@ void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, Con
     // reduction chunks; their fp32 partial sums meet in the workspace (see the epilogue).
     // (split-major numbering: neighbouring workgroups, which land on the same XCD, work on neighbouring tiles with the
     // same share of the reduction and so share that share's weights in their L2)
-    const int ntiles = nsplit > 1 ? nb / nsplit : nb;
-    const int split = nsplit > 1 ? lidx / ntiles : 0;
-    const int lid = nsplit > 1 ? lidx - split * ntiles : lidx;
-    const int nchunks_all = (p.Ks + ChunkShape<MODE, KH, KW, DEEP>::KSTEPS - 1) / ChunkShape<MODE, KH, KW, DEEP>::KSTEPS;
-    const int c_first = split * nchunks_all / nsplit;                  // this workgroup's chunks: [c_first, c_first + nchunks)
-    const int nchunks = (split + 1) * nchunks_all / nsplit - c_first;
+    // (A branch around all the divisions by runtime numbers: each is some 25 instructions ahead of the first load, and in a grid one tile
+    // deep nothing hides them.  1x1 1024 -> 256 at batch 64: 10.30 -> 10.08 us, 400 layers drawn at random 0.984 of the time.)
+    int ntiles = nb, split = 0, lid = lidx, c_first = 0;               // this workgroup's chunks: [c_first, c_first + nchunks)
+    int nchunks = (p.Ks + KSTEPS - 1) / KSTEPS;
+    if (nsplit > 1) {                                                  // uniform
+        ntiles = nb / nsplit;
+        split = lidx / ntiles;
+        lid = lidx - split * ntiles;
+        c_first = split * nchunks / nsplit;
+        nchunks = (split + 1) * nchunks / nsplit - c_first;
+    }
     const int tile_n = fast_div(lid, p.tm_mul, p.tm_sh);
     const int tile_m = lid - tile_n * tiles_m;
     const int m0 = tile_m * BM;
@@ -512,10 +518,13 @@ void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, Con
     // MODE_VEC: position of this thread's 8-element run in the (tap, channel) space
     int vk = unit * 8 + c_first * ChunkShape<MODE, KH, KW, DEEP>::BK, vc = 0, vr = 0, vt = 0;
     if constexpr (is_vec(MODE)) {
-        int tap = vk / p.Cin;
-        vc = vk - tap * p.Cin;
-        vr = tap / p.kw;
-        vt = tap - vr * p.kw;
+        vc = vk;
+        if (c_first > 0 || p.Cin < UNITS * 8) {           // uniform: else the first chunk lies in the first tap
+            int tap = vk / p.Cin;
+            vc = vk - tap * p.Cin;
+            vr = tap / p.kw;
+            vt = tap - vr * p.kw;
+        }
     }
     // MODE_TAPS: per (pixel, tap) byte offsets, fixed for the whole reduction; the chunk's channel
     // offset travels in the scalar offset of the load.  Out-of-image taps are out of range for good.
