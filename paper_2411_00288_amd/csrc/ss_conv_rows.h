@@ -10,6 +10,10 @@
 // instructions), writes its 64 x 64 outputs through a private LDS slab and goes on to its next 64 rows with no
 // barrier in between.  The weight fragments travel in a register ring that runs ahead across the hand-over from one
 // row block to the next, so the only exposed memory latency is the workgroup's first.
+// (That one is single: the tile, the first bias values and the first weights are asked for together.  With the weights behind the barrier, and
+// every 16-byte run's address worked out from its pixel where the tile is one run of memory, bf16 64 -> 256 channels at 56x56 took 24.0 us
+// at batch 64 and 6.2 at batch 8 instead of 22.3 and 6.0, 512 -> 2048 at 7x7 10.8 instead of 10.1; dense layers gain 3 to 8 %, and only
+// 96 -> 384 with a residual, 620 MB of traffic, is slower: 150.9 -> 152.5.)
 // Bias, residual (added in fp32 before the activation), activation and the single rounding are those of the other
 // kernels; the bias starts in the accumulators.
 #ifndef SS_CONV_ROWS_H_
@@ -55,53 +59,18 @@ void conv_pw_rows_kernel(ConvArgs args)
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g2 = lane >> 5, c2 = lane & 31;
-    const int tile_n = blockIdx.x / mg, grp = blockIdx.x - tile_n * mg;
+    int tile_n = blockIdx.x, grp = 0;
+    if (mg > 1) {                                     // uniform (a division by a runtime number is some 25 instructions)
+        tile_n = blockIdx.x / mg;
+        grp = blockIdx.x - tile_n * mg;
+    }
     const int n0 = tile_n * BN;
     const int pairs_all = (p.Mt + 1) >> 1;
     const int rp0 = grp * pairs_per_group;
     const int rp1 = min(rp0 + pairs_per_group, pairs_all);
 
-    // ---- the activation tile: 64 pixels x K channels, 16-byte loads, one LDS row per pixel
-    {
-        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.x), 0, (int)p.x_bytes, kRsrcFlags);
-        const int HoWo = p.Ho * p.Wo;
-        u32x4 v[KS];
-#pragma unroll
-        for (int i = 0; i < KS; i++) {
-            const int idx = tid + 256 * i;
-            const int pl = idx / VPP, vec = idx % VPP;
-            const int pg = n0 + pl;
-            const bool live = pg < p.P;
-            const int n = fast_div(live ? pg : 0, p.howo_mul, p.howo_sh);
-            const int rem = (live ? pg : 0) - n * HoWo;
-            const int ho = fast_div(rem, p.wo_mul, p.wo_sh);
-            const int wo = rem - ho * p.Wo;
-            const int ih = ho * p.sh - p.ph, iw = wo * p.sw - p.pw;
-            const bool ok = live && (unsigned)ih < (unsigned)p.H && (unsigned)iw < (unsigned)p.W;
-            const unsigned off = (unsigned)(((n * p.H + ih) * p.W + iw) * p.Cin * 2) + (unsigned)vec * 16u;
-            v[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(ok ? off : kOutOfRange), 0, 0);
-        }
-        for (int i = tid; i < (rp1 - rp0) * 64; i += 256) {
-            const int o = rp0 * 64 + i;
-            bias_s[i] = (p.bias != nullptr && o < p.Cout) ? p.bias[o] : 0.f;
-        }
-#pragma unroll
-        for (int i = 0; i < KS; i++) {
-            const int idx = tid + 256 * i;
-            const int pl = idx / VPP, vec = idx % VPP;
-            *reinterpret_cast<u32x4 *>(Bs + pl * ROW + vec * 8) = v[i];
-        }
-    }
-    __syncthreads();                                  // the only barrier
-
-    int rp = rp0 + wave;                              // this wave's first block of 64 rows; the next ones follow at a stride of 4
-    if (rp >= rp1) return;
-
     const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.a_vals), 0, (int)p.a_bytes, kRsrcFlags);
     const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.a_meta), 0, (int)p.meta_bytes, kRsrcFlags);
-    const unsigned ybytes = (unsigned)p.P * (unsigned)p.Cout * 2u;
-    const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, (int)ybytes, kRsrcFlags);
-    const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.residual), 0, p.residual ? (int)ybytes : 0, kRsrcFlags);
     const unsigned a_lane = (unsigned)lane * 16u, m_lane = (unsigned)lane * 4u;
     struct AFrag {
         u32x4 v[SPARSE ? 1 : 2];
@@ -123,6 +92,62 @@ void conv_pw_rows_kernel(ConvArgs args)
             }
         }
     };
+    int rp = rp0 + wave;                              // this wave's first block of 64 rows; the next ones follow at a stride of 4
+
+    // ---- the activation tile: 64 pixels x K channels, 16-byte loads, one LDS row per pixel; behind its loads those of the first bias
+    // values and of the first weights, so that all of them are one memory latency
+    {
+        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.x), 0, (int)p.x_bytes, kRsrcFlags);
+        const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.bias), 0, p.bias != nullptr ? p.Cout * 4 : 0, kRsrcFlags);
+        u32x4 v[KS];
+        if ((p.sh & p.sw) == 1 && (p.ph | p.pw) == 0) {      // uniform: the tile is one run of memory (a pixel past the last lies past the buffer's end)
+            const unsigned off = ((unsigned)n0 * SH::K + tid * 8u) * 2u;
+#pragma unroll
+            for (int i = 0; i < KS; i++) v[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(off + 4096u * i), 0, 0);
+        } else {
+            const int HoWo = p.Ho * p.Wo;
+#pragma unroll
+            for (int i = 0; i < KS; i++) {
+                const int idx = tid + 256 * i;
+                const int pl = idx / VPP, vec = idx % VPP;
+                const int pg = n0 + pl;
+                const bool live = pg < p.P;
+                const int n = fast_div(live ? pg : 0, p.howo_mul, p.howo_sh);
+                const int rem = (live ? pg : 0) - n * HoWo;
+                const int ho = fast_div(rem, p.wo_mul, p.wo_sh);
+                const int wo = rem - ho * p.Wo;
+                const int ih = ho * p.sh - p.ph, iw = wo * p.sw - p.pw;
+                const bool ok = live && (unsigned)ih < (unsigned)p.H && (unsigned)iw < (unsigned)p.W;
+                const unsigned off = (unsigned)(((n * p.H + ih) * p.W + iw) * p.Cin * 2) + (unsigned)vec * 16u;
+                v[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(ok ? off : kOutOfRange), 0, 0);
+            }
+        }
+        // (absent, or past the last channel: zero)
+        auto bias_at = [&](int i) { return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rb, (rp0 * 64 + i) * 4, 0, 0)); };
+        const int nbias = (rp1 - rp0) * 64;
+        const float b0 = bias_at(tid), b1 = bias_at(tid + 256);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < R; s++) {                 // (also in a wave that has no rows: a branch here would make the waits below wait for them)
+            load_a(a[s], rp, s);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int i = 0; i < KS; i++) {
+            const int idx = tid + 256 * i;
+            const int pl = idx / VPP, vec = idx % VPP;
+            *reinterpret_cast<u32x4 *>(Bs + pl * ROW + vec * 8) = v[i];
+        }
+        if (tid < nbias) bias_s[tid] = b0;
+        if (tid + 256 < nbias) bias_s[tid + 256] = b1;
+        for (int i = tid + 512; i < nbias; i += 256) bias_s[i] = bias_at(i);
+    }
+    lds_barrier();                                    // the only one; the weights stay in flight across it
+    if (rp >= rp1) return;
+
+    const unsigned ybytes = (unsigned)p.P * (unsigned)p.Cout * 2u;
+    const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, (int)ybytes, kRsrcFlags);
+    const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.residual), 0, p.residual ? (int)ybytes : 0, kRsrcFlags);
     // Activation fragment of step ks for pixel subtile tn: this lane's 16 reduction indices of pixel c2
     const uint16_t *const bsrc = Bs + c2 * ROW + 16 * g2;
     B32 b[2][2];
@@ -150,11 +175,6 @@ void conv_pw_rows_kernel(ConvArgs args)
         for (int j = 0; j < 2; j++) f[j] = __builtin_amdgcn_raw_buffer_load_b128(rr, (int)out_off(rpb, t, j), 0, 0);
     };
 
-#pragma unroll
-    for (int s = 0; s < R; s++) {
-        load_a(a[s], rp, s);
-        __builtin_amdgcn_sched_barrier(0);
-    }
     load_b(b[0], 0);
 
     for (; rp < rp1; rp += 4) {
