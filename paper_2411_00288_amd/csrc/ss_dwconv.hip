@@ -171,6 +171,16 @@ __device__ __forceinline__ int dw_in_at(int channel, int strip, int vec) { retur
 constexpr int kDwPixel = 12;              // dwords per pixel of the output buffer (8 used) and
 constexpr int kDwStrip = 16 * kDwPixel + 4;      // per strip: 16-byte aligned runs whose writes spread over the banks
 
+// f(0), f(1), ... f(N - 1), each with its number as a constant
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void each_below(F &&f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        each_below<N, I + 1>(f);
+    }
+}
+
 template <int DT, int K>
 __global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
 {
@@ -190,7 +200,7 @@ __global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
     struct Run {
         int block, row, len;              // rows [row, row + len) of the block's strips
     };
-    auto run_at = [&](int pos) {          // (behind the last row: an empty one)
+    auto run_at = [&](int pos) {
         const int block = pos / p.R, row = pos - block * p.R;
         return Run{block, row, min(p.R - row, hi - pos)};
     };
@@ -220,13 +230,14 @@ __global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
     auto aim_loads = [&]() {
         const Run r = run_at(lpos);
         const Strip s = strip(r.block, sn);
-        const bool ok = stages && s.ok && r.len > 0 && c0 + so * 8 < p.C;
+        const bool ok = stages & s.ok & (c0 + so * 8 < p.C);
         srow = s.row + r.row - p.ph;
-        lsteps = max(r.len, 1) + K - 1;
+        lsteps = r.len + K - 1;
 #pragma unroll
         for (int j = 0; j < 2; j++) {
             const int iw = s.col - p.pw + 2 * sp + j;
-            soff[j] = ok && (unsigned)iw < (unsigned)p.W ? (unsigned)((((s.img * p.H + srow) * p.W + iw) * p.C + c0 + so * 8) * 2) : kOut;
+            const unsigned at = (unsigned)((((s.img * p.H + srow) * p.W + iw) * p.C + c0 + so * 8) * 2);
+            soff[j] = ok & ((unsigned)iw < (unsigned)p.W) ? at : kOut;
         }
     };
     u32x4 st[K][2];                                       // input rows in flight: K, since the rotation of the accumulators unrolls the loop K times anyway
@@ -242,8 +253,9 @@ __global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
         srow++;
         if (++li == lsteps) {                             // uniform
             li = 0;
-            lpos = min(lpos + lsteps - (K - 1), hi);
-            aim_loads();
+            lpos += lsteps - (K - 1);
+            if (lpos < hi) aim_loads();                   // (some 150 instructions)
+            else soff[0] = soff[1] = kOut;                // (nothing more to fetch: the K rows asked for behind the last one are never multiplied)
         }
     };
     auto store_row = [&](int buf, const u32x4 (&v)[2]) {
@@ -254,6 +266,12 @@ __global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
             dst[(2 * e + 1) * 256] = __builtin_amdgcn_perm(v[1][e], v[0][e], 0x07060302u);
         }
     };
+    // One tap of two channels per thread, ahead of the rows: asked for in turn, with the wait of each before the next, they were the longest part
+    // of the set-up.
+    static_assert(8 * K * K <= 512, "a thread loads at most one tap");
+    const int tpair = tid / (K * K), tr = tid % (K * K) / K, tt = tid % K;      // (K * K is a multiple of K)
+    const bool has_tap = tid < 8 * K * K;
+    const uint32_t tap = __builtin_amdgcn_raw_buffer_load_b32(rw, (int)(has_tap && c0 + 2 * tpair < p.C ? (unsigned)(((tr * K + tt) * p.C + c0 + 2 * tpair) * 2) : kOut), 0, 0);
     aim_loads();
 #pragma unroll
     for (int i = 0; i < K; i++) load_row(st[i]);
@@ -263,12 +281,12 @@ __global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
     constexpr int TROW = 48;
     static_assert(8 * K * TROW <= 2 * 16 * kDwStrip, "the taps fit the output buffers");
     uint32_t *const taps = &out_s[0][0];
-    for (int i = tid; i < 8 * K * TROW; i += 512) {
-        const int pair = i / (K * TROW), rest = i - pair * (K * TROW), r = rest / TROW, t = rest - r * TROW - 15;
-        const bool ok = (unsigned)t < (unsigned)K && c0 + 2 * pair < p.C;
-        const uint32_t v = __builtin_amdgcn_raw_buffer_load_b32(rw, (int)(ok ? (unsigned)(((r * K + t) * p.C + c0 + 2 * pair) * 2) : kOut), 0, 0);
-        taps[i] = v;
-    }
+    static_assert(8 * K * TROW % 4 == 0, "whole vectors");
+#pragma unroll
+    for (int i = 0; i < (2 * K * TROW + 511) / 512; i++)
+        if (tid + 512 * i < 2 * K * TROW) reinterpret_cast<u32x4 *>(taps)[tid + 512 * i] = u32x4{0u, 0u, 0u, 0u};
+    lds_barrier();
+    if (has_tap) taps[(tpair * K + tr) * TROW + 15 + tt] = tap;
     if (tid == 0) odd_s = 0;
     f32x4 b4[2];
 #pragma unroll
@@ -298,8 +316,9 @@ __global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
     auto aim_stores = [&]() {
         const Run r = run_at(pos);
         const Strip s = strip(r.block, on);
-        const bool ok = s.ok && s.col + ow < p.Wo && c0 + oo * 8 < p.C;
-        rows_left = ok ? min(r.len, p.Ho - s.row - r.row) : 0;
+        const bool ok = s.ok & (s.col + ow < p.Wo) & (c0 + oo * 8 < p.C);
+        const int left = min(r.len, p.Ho - s.row - r.row);
+        rows_left = ok ? left : 0;
         yoff = (unsigned)((((s.img * p.Ho + s.row + r.row) * p.Wo + s.col + ow) * p.C + c0 + oo * 8) * 2);
         steps = r.len + K - 1;
     };
@@ -321,40 +340,47 @@ __global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
 #pragma unroll
         for (int r = 0; r < K; r++) acc[j][r] = f32x4{0.f, 0.f, 0.f, 0.f};
     int par = 0, i = 0;
-    for (bool more = true; more;) {
+    auto step = [&](auto slot_of_step) {
+        constexpr int u = decltype(slot_of_step)::value;  // (the slot of the rotation: a constant)
+        // input row i of the block is in buffer par, the K rows after it are in or on their way to st[]
+        const u32x4 bf[2] = {*reinterpret_cast<const u32x4 *>(in_s[par] + frag), *reinterpret_cast<const u32x4 *>(in_s[par] + frag + 512)};
+        store_row(par ^ 1, st[(u + 1) % K]);
+        load_row(st[(u + 1) % K]);
+        emit(par ^ 1);
 #pragma unroll
-        for (int u = 0; u < K; u++) {
-            // input row i of the block is in buffer par, the K rows after it are in or on their way to st[]
-            const u32x4 bf[2] = {*reinterpret_cast<const u32x4 *>(in_s[par] + frag), *reinterpret_cast<const u32x4 *>(in_s[par] + frag + 512)};
-            store_row(par ^ 1, st[(u + 1) % K]);
-            load_row(st[(u + 1) % K]);
-            emit(par ^ 1);
+        for (int r = K - 1; r >= 0; r--)              // (the filter row that completes an output row first: its rounding overlaps with the others)
 #pragma unroll
-            for (int r = K - 1; r >= 0; r--)              // (the filter row that completes an output row first: its rounding overlaps with the others)
+            for (int j = 0; j < 2; j++)
+                acc[j][(u + K - r) % K] = mma16<DT>(a[j][r], bf[j], r == 0 ? b4[j] : acc[j][(u + K - r) % K]);
+        {                                             // the last filter row completed output row i - (K - 1)
+            const int slot = (u + 1) % K, h = i - (K - 1);
+            uint32_t *dst = out_s[par] + m * kDwStrip + 4 * kg * kDwPixel + wave;
 #pragma unroll
-                for (int j = 0; j < 2; j++)
-                    acc[j][(u + K - r) % K] = mma16<DT>(a[j][r], bf[j], r == 0 ? b4[j] : acc[j][(u + K - r) % K]);
-            {                                             // the last filter row completed output row i - (K - 1)
-                const int slot = (u + 1) % K, h = i - (K - 1);
-                uint32_t *dst = out_s[par] + m * kDwStrip + 4 * kg * kDwPixel + wave;
-#pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    const uint32_t v = pack2<DT>(max_nan(acc[0][slot][e], floor), max_nan(acc[1][slot][e], floor));
-                    dst[e * kDwPixel] = v;
-                    top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, v & 0x7FFF7FFFu));
-                }
-                pending = (yoff + (unsigned)h * yrow) | (h >= 0 && h < rows_left ? 0u : kOut);
+            for (int e = 0; e < 4; e++) {
+                const uint32_t v = pack2<DT>(max_nan(acc[0][slot][e], floor), max_nan(acc[1][slot][e], floor));
+                dst[e * kDwPixel] = v;
+                top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, v & 0x7FFF7FFFu));
             }
-            lds_barrier();
-            par ^= 1;
-            if (++i == steps) {                           // uniform
-                i = 0;
-                pos += steps - (K - 1);
-                if (pos >= hi) { more = false; break; }
-                aim_stores();
-            }
+            pending = (yoff + (unsigned)h * yrow) | (h >= 0 && h < rows_left ? 0u : kOut);
         }
-    }
+        lds_barrier();
+        par ^= 1;
+        if (++i == steps) {                               // uniform
+            i = 0;
+            pos += steps - (K - 1);
+            if (pos < hi) aim_stores();
+        }
+    };
+    // K steps at a time, and the rest after the loop: a loop that could be left from each of its K steps has those exits led through its head, where
+    // the wait for a row loaded K steps ago would become one for the row loaded last, once every K steps (with that, taps fetched in turn and both
+    // aims after the last run: 44.5 instead of 41.5 us for 128 x 56 x 56 x 96, 11.0 instead of 9.8 for 16 x 28 x 28 x 96).
+    int total = hi - lo + K - 1;                          // input rows of all runs
+    if (run_at(lo).len < hi - lo) total += ((hi - 1) / p.R - lo / p.R) * (K - 1);      // uniform: more than one
+    for (int left = total / K; left > 0; left--) each_below<K>([&](auto u) { step(u); });
+    const int rest = total % K;
+    each_below<K - 1>([&](auto u) {
+        if (decltype(u)::value < rest) step(u);           // uniform
+    });
     emit(par ^ 1);
     if (top[0] >= kInf || top[1] >= kInf) odd_s = 1;
     __syncthreads();
@@ -392,7 +418,7 @@ __global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
 
 // Segments per image and their shares: those for which the busiest workgroup walks over the fewest input rows (a run of R output rows needs
 // R + K - 1).  Dealt out row by row, 32 blocks of 56 rows keep 42 workgroups of a channel group busy for 43 + 2 * 6 rows instead of 32 of them for
-// 62 (128 x 56 x 56 x 96, 7x7: 46.5 -> 44.5 us); where both walk over as many rows, whole blocks have fewer seams (64 images: 29.2 against 29.7).
+// 62 (128 x 56 x 56 x 96, 7x7: 46.5 -> 44.5 us then); where both walk over as many rows, whole blocks have fewer seams (64 images: 29.2 against 29.7 then).
 template <int DT, int K>
 static int launch_dw_mfma(DwParams p, int N, hipStream_t s)
 {
@@ -427,7 +453,7 @@ static int launch_dw(const uint16_t *x, const uint16_t *w, const float *bias, ui
 {
     const long long ybytes = (long long)N * Ho * Wo * C * 2;
     // The matrix kernel costs about the same for every filter width and has a longer set-up.  Measured against the vector one:
-    // 7x7 faster or equal from 1 x 7 x 7 x 96 up (128 x 56 x 56 x 96 in a chain: 99 -> 47 us); 5x5 from about 4 M outputs (32 x 56 x 56 x
+    // 7x7 faster or equal from 1 x 7 x 7 x 96 up (128 x 56 x 56 x 96 in a chain: 99 -> 41.5 us); 5x5 from about 4 M outputs (32 x 56 x 56 x
     // 96: 21.6 -> 16.9; 128 x 13 x 19 x 64: 8.5 vs 9.9); 3x3 nowhere.
     if (kh == kw && ybytes < (1ll << 31) && (kw == 7 || (kw == 5 && ybytes >= (8ll << 20)))) {
         DwParams p{};

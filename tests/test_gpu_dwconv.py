@@ -116,3 +116,16 @@ def test_rows_dealt_out_evenly(ss, shape):
     hit[33, 10 - k // 2:11 + k // 2, :2 + k // 2, 77] = True
     assert not torch.isfinite(z[hit].float()).any() and torch.isfinite(z[~hit].float()).all()
     assert (z[~hit].float() - y[~hit].float()).abs().max() <= 0.0625         # (fp32 sums in another order, one rounding: values up to 8)
+
+
+@pytest.mark.parametrize("rows", [1, 2, 3, 4, 5, 6, 7, 8])
+def test_runs_of_every_length_against_the_rotation(ss, rows):
+    """One block of 16 images, six segments of `rows` rows, one workgroup each: rows + 6 input rows are 7 to 14 steps
+    of a rotation of 7, from one whole turn with no rest to two."""
+    N, H, W, C, k = 16, 6 * rows, 8, 640, 7
+    rng = np.random.Generator(np.random.PCG64(rows))
+    xb = wl.to_bits(rng.standard_normal((N, H, W, C), dtype=np.float32), wl.BF16)
+    wb = wl.to_bits(rng.standard_normal((k, k, C), dtype=np.float32) * np.float32((2.0 / (k * k)) ** 0.5), wl.BF16)
+    bias = (rng.standard_normal(C) * 0.1).astype(np.float32)
+    y = _run(ss, xb, wb, bias, wl.BF16, (k // 2, k // 2), wl.ACT_RELU)
+    check_close(y, oracle.dwconv2d(xb, wb, dtype=wl.BF16, bias=bias, pad=(k // 2, k // 2), act=wl.ACT_RELU), f"rows {rows}")
