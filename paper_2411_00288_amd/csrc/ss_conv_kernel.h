@@ -196,14 +196,14 @@ __device__ __forceinline__ float widen(uint16_t bits)
 //     z >= 0:  z (1 - h) = z - a h        z < 0:  z h = -a h        i.e.  gelu(z) = max(z, 0) - a h,
 // which needs no select.  log2 Phi(-a) is smooth and close to a parabola: a polynomial and one exp2.  Two fits, each as long as
 // the values of its output type ODT ask for (a negative leading coefficient takes either to 0 behind its range):
-//   binary16   a h rounds to 0 from a = 5.5 on: degree 8, fitted on [0, 6].  Ten full-rate instructions and one quarter-rate one
-//              (56 clocks per wave).
+//   binary16   a h rounds to 0 from a = 5.5 on: degree 8, fitted on [0, 6].  Ten full-rate instructions and one half-rate one
+//              (48 clocks per wave: measured, a fused multiply-add takes 4 and exp2 8).
 //   bfloat16   holds the whole lower tail: degree 10, fitted on [0, 12.95], where Phi reaches 2^-126, the least value exp2 gives
-//              (64 clocks).
+//              (56 clocks).
 // Fitted for the smallest largest error of Phi (|error| < 1e-7 in fp32 arithmetic), and in the tail for relative errors: 6e-7 at
 // a = 1, 2e-5 at 3, 3e-4 at 5; from there degree 8 loses the tail (6e-3 at 6.3, 8e-2 at 7, nothing is left at 10), degree 10 has
 // 1e-3 at 6, 3e-3 at 8, 2.3e-2 at 10 and 3.5e-2 at 12.9.  The rational form 7.1.26 of Abramowitz & Stegun takes twelve and two
-// instructions (80 clocks) for 2e-7 absolute and 9e-4 at 4, 5e-3 at 6, 1.2e-2 at 8, 2.2e-2 at 10, 3.6e-2 at 12.5.  (A NaN stays a NaN.)
+// instructions for 2e-7 absolute and 9e-4 at 4, 5e-3 at 6, 1.2e-2 at 8, 2.2e-2 at 10, 3.6e-2 at 12.5.  (A NaN stays a NaN.)
 template <int ODT>
 __device__ __forceinline__ float gelu_cdf(float z)
 {
