@@ -72,7 +72,8 @@ def test_pointwise_shares_of_whole_and_ragged_steps(ss, force_tile, cin, cout, s
 
 @pytest.mark.parametrize("tile", [20, 21, 22])
 @pytest.mark.parametrize("f8", [False, True])
-@pytest.mark.parametrize("cin,k,korder", [(64, 3, wl.K_CRS), (320, 3, wl.K_CRS), (48, 3, wl.K_RSC), (1040, 1, wl.K_CRS), (192, 2, wl.K_CRS)])
+@pytest.mark.parametrize("cin,k,korder", [(64, 3, wl.K_CRS), (320, 3, wl.K_CRS), (48, 3, wl.K_RSC), (1040, 1, wl.K_CRS), (192, 2, wl.K_CRS),
+                                          (1024, 1, wl.K_CRS), (4608, 1, wl.K_CRS)])
 def test_small_grid_kernels_on_8_bit_operands(ss, force_tile, cin, k, korder, f8, tile):
     L = L_(1, 6, 7, cin, 44, k, p=k // 2, dtype=wl.F8 if f8 else wl.I8, korder=korder)
     d = (wl.make_inputs_f8 if f8 else wl.make_inputs_q8)(L)
