@@ -100,7 +100,7 @@ void conv_pw_rows_kernel(ConvArgs args)
         const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.x), 0, (int)p.x_bytes, kRsrcFlags);
         const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.bias), 0, p.bias != nullptr ? p.Cout * 4 : 0, kRsrcFlags);
         u32x4 v[KS];
-        if ((p.sh & p.sw) == 1 && (p.ph | p.pw) == 0) {      // uniform: the tile is one run of memory (a pixel past the last lies past the buffer's end)
+        if (p.sh == 1 && p.sw == 1 && (p.ph | p.pw) == 0) {      // uniform: the tile is one run of memory (a pixel past the last lies past the buffer's end)
             const unsigned off = ((unsigned)n0 * SH::K + tid * 8u) * 2u;
 #pragma unroll
             for (int i = 0; i < KS; i++) v[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(off + 4096u * i), 0, 0);
