@@ -190,7 +190,7 @@ __global__ __launch_bounds__(NW * 64) void conv_small_kernel(ConvArgs args)
         __builtin_amdgcn_sched_barrier(0);
         const int pg = PX == 32 || c < PX ? n0 + c : p.P;
         Pixel px;
-        if (MODE == SMALL_PW && (p.sh & p.sw) == 1 && (p.ph | p.pw) == 0) {      // uniform: pixels and positions in the input are the same thing
+        if (MODE == SMALL_PW && p.sh == 1 && p.sw == 1 && (p.ph | p.pw) == 0) {      // uniform: pixels and positions in the input are the same thing
             px = Pixel{pg < p.P ? 0 : -(1 << 28), 0, (unsigned)pg * p.Cin * 2u};
         } else {
             px = pixel(pg);
