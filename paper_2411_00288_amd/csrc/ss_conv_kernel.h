@@ -1291,14 +1291,16 @@ void mlp_kernel(MlpParams p)
         for (int i = 0; i < KS1; i++) *reinterpret_cast<u32x4 *>(Xs + row * XROW + q4 * 8 + i * 32) = v[i];
     }
     // the residual, in the output stage's lane -> (pixel, run of 8 channels) mapping
-    const int out_lane = (lane >> 2) * p.Cout2 * 2 + (lane & 3) * 16;      // byte offset of the lane's run in a 16-pixel piece
-    auto out_piece = [&](int ti, int j) { return ((half * 32 + 16 * j) * p.Cout2 + row_tile(ti) * 32) * 2; };
+    // (The pixel is in the vector offset alone, which by itself passes the buffer's end behind the last one: that the check counts the scalar offset
+    // in is nothing the intrinsic promises.  The scalar offset stays within a pixel's row.)
+    auto out_lane = [&](int j) { return (half * 32 + 16 * j + (lane >> 2)) * p.Cout2 * 2 + (lane & 3) * 16; };
+    auto out_row = [&](int ti) { return row_tile(ti) * 64; };
     u32x4 rres2[TILES][2];
     auto load_res = [&]() {
 #pragma unroll
         for (int ti = 0; ti < TILES; ti++)
 #pragma unroll
-            for (int j = 0; j < 2; j++) rres2[ti][j] = __builtin_amdgcn_raw_buffer_load_b128(rres, out_lane, out_piece(ti, j), 0);
+            for (int j = 0; j < 2; j++) rres2[ti][j] = __builtin_amdgcn_raw_buffer_load_b128(rres, out_lane(j), out_row(ti), 0);
     };
     const float floor1 = p.act1 == SS_ACT_RELU ? 0.f : -__builtin_inff();
     __syncthreads();
@@ -1412,7 +1414,7 @@ void mlp_kernel(MlpParams p)
                     const uint32_t rr = rres2[ti][j][e];
                     w[e] = cvt_pack2<DT>(act2(v[2 * e] + widen<DT>((uint16_t)(rr & 0xFFFFu))), act2(v[2 * e + 1] + widen<DT>((uint16_t)(rr >> 16))));
                 }
-                __builtin_amdgcn_raw_buffer_store_b128(w, ry, out_lane, out_piece(ti, j), 0);
+                __builtin_amdgcn_raw_buffer_store_b128(w, ry, out_lane(j), out_row(ti), 0);
             }
         }
     };
