@@ -1,9 +1,9 @@
 // Weight compressor, decompressor and dense-twin packer (Fig. 1; Sec. 3.1 Eq. 2; Sec. 3.3 Eq. 6).
 // Integer / bit work only: no floating-point instruction touches a weight.
 #include "ss_internal.h"
+#include "ss_pack_wait.h"
 #include <hip/hip_ext.h>
 #include <chrono>
-#include <mutex>
 #include <thread>
 
 namespace ss {
@@ -67,15 +67,11 @@ __device__ __forceinline__ bool mask_ok(uint32_t m)
 // access finds it, on whatever stream), every wave waits for its acknowledgements, and every workgroup takes a ticket.  One counter would
 // serve 10 ns a ticket (1024 workgroups: 11 us), so from kOneCounter workgroups on groups of them count by themselves, each in a cache
 // line of its own, and the last of each group counts at the root (0.7 us, the time of 64 tickets).  A counter wraps to zero with its last ticket: nothing has to be reset.
-constexpr int kSlots = 16;                        // calls in flight on a device that have counters; further ones wait for an event
 constexpr unsigned kTicketGroups = 16, kOneCounter = 64;
 struct __attribute__((aligned(128))) TicketLine {
     unsigned n;
 };
 __device__ TicketLine ticket_lines[kSlots][kTicketGroups + 1];      // (zero when the library is loaded)
-struct Verdict {                                  // pinned host memory, zero before the call
-    uint32_t done, bad;                           // all is packed (with slot >= 0); a block's mask is invalid
-};
 
 // The workgroup's ticket, taken by one of its threads: true for the last of the `blocks` workgroups.
 __device__ __forceinline__ bool last_of_grid(int slot, unsigned blocks)
@@ -318,88 +314,26 @@ extern "C" int ss_dense_bytes(const ss_weight_desc *desc, size_t *dense_bytes)
     return SS_OK;
 }
 
-// What a compression waits with: a word of pinned host memory in which the last workgroup leaves the verdict (polled, with no copy from the
-// device) and one of the device's kSlots sets of ticket counters.  A call that finds all of those in use has an event instead, given
-// to the launch, that completes with the kernel.  Handed out one per call in flight and kept for the next, in an array: nothing here
-// may throw through the C entry.
-namespace {
-struct Waiter {
-    Verdict *verdict = nullptr;
-    hipEvent_t done = nullptr;        // slot < 0
-    int device = -1, slot = -1;
-    void clear() const
-    {
-        __atomic_store_n(&verdict->done, 0u, __ATOMIC_RELAXED);
-        __atomic_store_n(&verdict->bad, 0u, __ATOMIC_RELAXED);
-    }
-};
-constexpr int kSlotDevices = 64, kKeptOthers = 64;
-constexpr int kKeptWaiters = kSlotDevices * kSlots + kKeptOthers;      // every waiter that has counters, and some that have not
 constexpr int kPollMicroseconds = 1000, kSleepMicroseconds = 50, kSleepsPerQuery = 1000;
-std::mutex waiter_mutex;
-Waiter kept_waiters[kKeptWaiters];
-int n_kept_waiters = 0, n_kept_others = 0;
-int slots_given[kSlotDevices];        // per device: sets of counters handed out for good, each to one waiter
 
-bool take_waiter(Waiter *w)
-{
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return false;
-    {
-        const std::lock_guard<std::mutex> lock(waiter_mutex);
-        int pick = -1;
-        for (int i = n_kept_waiters; i-- > 0 && (pick < 0 || kept_waiters[pick].slot < 0);)
-            if (kept_waiters[i].device == dev) pick = i;
-        if (pick >= 0) {
-            *w = kept_waiters[pick];
-            kept_waiters[pick] = kept_waiters[--n_kept_waiters];
-            if (w->slot < 0) n_kept_others--;
-            w->clear();
-            return true;
-        }
-        w->slot = dev >= 0 && dev < kSlotDevices && slots_given[dev] < kSlots ? slots_given[dev]++ : -1;
-    }
-    void *page = nullptr;
-    if (hipHostMalloc(&page, 64, hipHostMallocDefault) != hipSuccess) return false;
-    if (w->slot < 0 && hipEventCreateWithFlags(&w->done, hipEventDisableTiming) != hipSuccess) {
-        (void)hipHostFree(page);
-        return false;
-    }
-    w->verdict = static_cast<Verdict *>(page);
-    w->device = dev;
-    w->clear();
-    return true;
-}
-
-void give_waiter(const Waiter &w)
-{
-    {
-        const std::lock_guard<std::mutex> lock(waiter_mutex);
-        if (w.slot >= 0 || n_kept_others < kKeptOthers) {
-            if (w.slot < 0) n_kept_others++;
-            kept_waiters[n_kept_waiters++] = w;
-            return;
-        }
-    }
-    (void)hipEventDestroy(w.done);
-    (void)hipHostFree(w.verdict);
-}
-}  // namespace
-
+// *launched: the kernel is on the stream.
 template <int DT, bool UPD>
 static int launch_compress(const ss_weight_desc *desc, const TileDims &t, void *W, const void *U, const uint8_t *M, uint8_t *packed,
-                           const Waiter &w, hipStream_t s)
+                           const Waiter &w, hipStream_t s, bool *launched)
 {
     constexpr int steps = kPackBlocks / (is_byte_type(DT) ? 16 : 8);      // reduction steps per workgroup
     const long long blocks = (long long)t.Mt * ((t.Ks + steps - 1) / steps);
     if (blocks > 0x7FFFFFFFll) return SS_ERR_UNSUPPORTED;
-    const PackHeader hdr = pack_header(kMagicSparse, desc, t);
-    if (w.slot < 0)
-        hipExtLaunchKernelGGL((compress_kernel<DT, UPD>), dim3((unsigned)blocks), dim3(256), 0, s, nullptr, w.done, 0, W, U, M, packed,
-                              desc->cout, t.K, t.Mt, t.Ks, t.Kp, hdr, w.verdict, w.slot);
-    else
-        compress_kernel<DT, UPD><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(W, U, M, packed, desc->cout, t.K, t.Mt, t.Ks, t.Kp, hdr, w.verdict, w.slot);
-    if (hipGetLastError() != hipSuccess) return SS_ERR_HIP;
+    // (launched by the calls that return their own status: what hipGetLastError says may be an earlier call's)
+    int K = t.K, Mt = t.Mt, Ks = t.Ks, Kp = t.Kp, cout = desc->cout, slot = w.slot;
+    Verdict *verdict = w.verdict;
+    PackHeader hdr = pack_header(kMagicSparse, desc, t);
+    void *args[] = {&W, &U, &M, &packed, &cout, &K, &Mt, &Ks, &Kp, &hdr, &verdict, &slot};
+    const void *const kernel = reinterpret_cast<const void *>(&compress_kernel<DT, UPD>);
+    const dim3 grid((unsigned)blocks), block(256);
+    const hipError_t sent = slot < 0 ? hipExtLaunchKernel(kernel, grid, block, args, 0, s, nullptr, w.done, 0) : hipLaunchKernel(kernel, grid, block, args, 0, s);
+    *launched = sent == hipSuccess;
+    if (hipGetLastError() != hipSuccess || sent != hipSuccess) return SS_ERR_HIP;
     // Polled without a pause for as long as packing itself takes.  A longer wait is for earlier work on the stream, which may take
     // any time: it sleeps between two looks, about 0.1 ms each with the timer's own slack, so the call returns at most that much late.
     // (hipEventSynchronize and hipStreamSynchronize keep the core busy throughout, with hipEventBlockingSync too: behind
@@ -443,12 +377,13 @@ static int compress_entry(const ss_weight_desc *desc, void *W, const void *U, co
     }
     if (cap != hipStreamCaptureStatusNone) return SS_ERR_HIP;
     Waiter wt;
+    bool launched = false;
     if (!take_waiter(&wt)) return SS_ERR_HIP;
-    if (i8) st = launch_compress<SS_I8, false>(desc, t, W, nullptr, M, p, wt, s);
-    else if (!U) st = launch_compress<SS_F16, false>(desc, t, W, nullptr, M, p, wt, s);
-    else if (desc->dtype == SS_F16) st = launch_compress<SS_F16, true>(desc, t, W, U, M, p, wt, s);
-    else st = launch_compress<SS_BF16, true>(desc, t, W, U, M, p, wt, s);
-    if (st == SS_ERR_HIP) return st;                      // (the kernel may still run: the waiter is not handed out again)
+    if (i8) st = launch_compress<SS_I8, false>(desc, t, W, nullptr, M, p, wt, s, &launched);
+    else if (!U) st = launch_compress<SS_F16, false>(desc, t, W, nullptr, M, p, wt, s, &launched);
+    else if (desc->dtype == SS_F16) st = launch_compress<SS_F16, true>(desc, t, W, U, M, p, wt, s, &launched);
+    else st = launch_compress<SS_BF16, true>(desc, t, W, U, M, p, wt, s, &launched);
+    if (st == SS_ERR_HIP && launched) return st;          // (the kernel may still run: the waiter is not handed out again)
     const bool bad = __atomic_load_n(&wt.verdict->bad, __ATOMIC_RELAXED) != 0;
     give_waiter(wt);
     if (st != SS_OK || !bad) return st;

@@ -26,6 +26,16 @@ def test_library_host_logic_under_sanitizers(tmp_path):
     assert "host checks passed" in out
 
 
+@pytest.mark.skipif(shutil.which("g++") is None, reason="no host compiler")
+def test_packing_waiters_survive_failed_allocations(tmp_path):
+    """Sixteen sets of counters per device, each in one waiter's hands, also after allocations that failed (tests/host/pack_waiters.cpp)."""
+    exe = tmp_path / "pack_waiters"
+    _run(["g++", "-std=c++17", *SAN, "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", str(ROOT / "include"),
+          str(ROOT / "tests" / "host" / "pack_waiters.cpp"), "-o", str(exe)])
+    out = _run([str(exe)], env={"ASAN_OPTIONS": "detect_leaks=0", "UBSAN_OPTIONS": "print_stacktrace=1"})
+    assert "waiter checks passed" in out
+
+
 @pytest.mark.skipif(shutil.which("gcc") is None, reason="no host compiler")
 def test_oracle_under_sanitizers(tmp_path):
     exe = tmp_path / "oracle_checks"
