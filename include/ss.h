@@ -128,8 +128,10 @@ int ss_dense_bytes(const ss_weight_desc *desc, size_t *dense_bytes /*[host] out*
  *   bad_row_group [host, optional] two int32: on SS_ERR_BAD_MASK receives the row and the block
  *           index of the first (row-major) invalid block.
  * Values are copied bit for bit: a kept weight that is -0, NaN or subnormal is preserved.
- * Waits for `stream` (on return all work up to this call is done and its results are in memory); a stream that is being captured is refused with SS_ERR_HIP and records nothing.  On SS_ERR_BAD_MASK the
- * contents of `packed` must not be used.
+ * Waits for `stream`: on return everything enqueued on it before has completed, and what this call itself wrote can be read
+ * from any stream or copied to the host.  (Earlier kernels' writes to memory that the host reads directly become visible as
+ * the runtime makes them; this call adds no synchronisation of its own to that.)  A stream that is being captured is refused
+ * with SS_ERR_HIP and records nothing.  On SS_ERR_BAD_MASK the contents of `packed` must not be used.
  */
 int ss_mask_compress(const ss_weight_desc *desc, const void *W, const uint8_t *M,
                      void *packed, int32_t *bad_row_group, void *stream);

@@ -264,3 +264,26 @@ def test_verdict_of_grids_of_any_size(ss, rows, steps):
         with pytest.raises(ss.SSError) as e:
             ss.ss_mask_compress(desc, Wd, wrong)
         assert e.value.status == ss.SS_ERR_BAD_MASK and e.value.detail == (row, block)
+
+
+@pytest.mark.parametrize("dtype", [wl.F16, wl.BF16])
+@pytest.mark.parametrize("rows,steps", [(1, 1), (9, 60)])
+def test_updated_weights_are_there_for_another_stream(ss, rows, steps, dtype):
+    """As soon as the call returns, the weights it moved are there for a copy on another stream, with what was packed from them."""
+    cout, K = 32 * rows - 5, 32 * steps - 8
+    rng = np.random.Generator(np.random.PCG64(rows))
+    W = wl.to_bits(rng.standard_normal((cout, K), dtype=np.float32), dtype)
+    U = wl.to_bits(rng.standard_normal((cout, K), dtype=np.float32) * np.float32(0.1), dtype)
+    M = wl.mask_from_logits(rng.standard_normal((cout, K // 4, 6)).astype(np.float32)).reshape(cout, K)
+    desc, Ud, Md = ss.make_desc(cout, K, 1, 1, dtype), dev_bits(U, dtype), torch.from_numpy(M).cuda()
+    other, out = torch.cuda.Stream(), torch.empty(dl.tile(*oracle.compress(W, M), cin=K, kh=1, kw=1, dtype=dtype, korder=wl.K_CRS).size,
+                                                  dtype=torch.uint8, device="cuda")
+    Wd = dev_bits(W, dtype)
+    torch.cuda.synchronize()
+    for _ in range(4):
+        W = oracle.update(W, U, dtype)
+        ss.ss_mask_update_compress(desc, Wd, Ud, Md, packed=out)
+        with torch.cuda.stream(other):
+            moved, packed = Wd.view(torch.int16).cpu().numpy().view(np.uint16), out.cpu().numpy()
+        assert np.array_equal(moved, W)
+        assert np.array_equal(packed, dl.tile(*oracle.compress(W, M), cin=K, kh=1, kw=1, dtype=dtype, korder=wl.K_CRS))
