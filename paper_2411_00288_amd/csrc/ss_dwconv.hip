@@ -237,7 +237,7 @@ __global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
         for (int j = 0; j < 2; j++) {
             const int iw = s.col - p.pw + 2 * sp + j;
             const unsigned at = (unsigned)((((s.img * p.H + srow) * p.W + iw) * p.C + c0 + so * 8) * 2);
-            soff[j] = ok & ((unsigned)iw < (unsigned)p.W) ? at : kOut;
+            soff[j] = (ok & ((unsigned)iw < (unsigned)p.W)) ? at : kOut;
         }
     };
     u32x4 st[K][2];                                       // input rows in flight: K, since the rotation of the accumulators unrolls the loop K times anyway
