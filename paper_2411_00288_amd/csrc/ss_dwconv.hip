@@ -248,7 +248,7 @@ __global__ __launch_bounds__(512) void dwconv_mfma_kernel(DwParams p)
 #pragma unroll
         for (int j = 0; j < 2; j++) {
             v[j] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(soff[j] | out), 0, 0);
-            soff[j] += row_bytes;                         // (an offset out of range stays so: the image is smaller than 2 GiB)
+            soff[j] += row_bytes;                         // (an offset out of range stays so: the launch sees to it)
         }
         srow++;
         if (++li == lsteps) {                             // uniform
@@ -455,7 +455,10 @@ static int launch_dw(const uint16_t *x, const uint16_t *w, const float *bias, ui
     // The matrix kernel costs about the same for every filter width and has a longer set-up.  Measured against the vector one:
     // 7x7 faster or equal from 1 x 7 x 7 x 96 up (128 x 56 x 56 x 96 in a chain: 99 -> 41.5 us); 5x5 from about 4 M outputs (32 x 56 x 56 x
     // 96: 21.6 -> 16.9; 128 x 13 x 19 x 64: 8.5 vs 9.9); 3x3 nowhere.
-    if (kh == kw && ybytes < (1ll << 31) && (kw == 7 || (kw == 5 && ybytes >= (8ll << 20)))) {
+    // (Its offsets outside the image start at 2 GiB and move on by a row per step, from the first padding row to the image's last: they must not
+    // come round to the image again.)
+    const bool rows_fit = ((long long)H + ph) * W * C * 2 < (1ll << 31);
+    if (kh == kw && rows_fit && ybytes < (1ll << 31) && (kw == 7 || (kw == 5 && ybytes >= (8ll << 20)))) {
         DwParams p{};
         p.x = x; p.w = w; p.bias = bias; p.y = y;
         p.H = H; p.W = W; p.C = C; p.ph = ph; p.pw = pw; p.Ho = Ho; p.Wo = Wo; p.act = act;

@@ -129,3 +129,17 @@ def test_runs_of_every_length_against_the_rotation(ss, rows):
     bias = (rng.standard_normal(C) * 0.1).astype(np.float32)
     y = _run(ss, xb, wb, bias, wl.BF16, (k // 2, k // 2), wl.ACT_RELU)
     check_close(y, oracle.dwconv2d(xb, wb, dtype=wl.BF16, bias=bias, pad=(k // 2, k // 2), act=wl.ACT_RELU), f"rows {rows}")
+
+
+@pytest.mark.parametrize("H,W,C", [(1, 54_000_000, 8), (3, 1_400_000, 160)])
+def test_few_rows_of_gigabytes(ss, H, W, C):
+    """Padding rows and the image's own together pass 2 GiB: columns outside the image stay zero on either side (ones everywhere: each output counts
+    the pixels of its window)."""
+    x, w = torch.ones((1, H, W, C), dtype=torch.float16, device="cuda"), torch.ones((7, 7, C), dtype=torch.float16, device="cuda")
+    assert x.numel() * 2 < 1 << 31 <= (H + 2) * W * C * 2
+    y = ss.ss_dwconv2d_fwd(x, w, None, (3, 3), wl.ACT_NONE)
+    for h in range(H):
+        rows = min(h + 3, H - 1) - max(h - 3, 0) + 1
+        want = rows * torch.tensor([4., 5., 6., 7., 7.], device="cuda")[:, None]
+        assert torch.equal(y[0, h, :5].float(), want.expand(5, C)) and torch.equal(y[0, h, -5:].float(), want.flip(0).expand(5, C))
+    assert bool((y[0, 0, 5:-5] == 7 * min(4, H)).all())
