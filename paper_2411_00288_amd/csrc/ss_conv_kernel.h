@@ -1498,6 +1498,7 @@ static int launch(const ConvParams &p0, hipStream_t s)
 
 // Staging modes with tiles of 96, 160 and 224 rows (choose_height).  1x1 layers gain nothing from them (over 1000 layers: 1 %), 2x2 ones 3 %.
 constexpr bool any_height(int mode, int kh) { return (is_taps(mode) && kh == 3) || mode == MODE_VEC; }
+constexpr bool dense_f8(int dt, bool sparse) { return dt == SS_F8 && !sparse; }
 
 // Tile shapes (WAVES_M x WAVES_N multiplying waves, each TM x TN tiles of 32x32):
 //   id 0:  64 x  64 (2x2 waves, 1x1)
@@ -1524,13 +1525,12 @@ static int launch_tile(int id, const ConvParams &p, hipStream_t s)
             default: break;
         }
     }
-    if constexpr (any_height(MODE, KH)) {
-        switch (id) {
-            case 6: return launch<DT, SPARSE, 3, 1, 1, 2, MODE, KH, KW, false>(p, s);
-            case 7: return launch<DT, SPARSE, 5, 1, 1, 2, MODE, KH, KW, false>(p, s);
-            case 8: return launch<DT, SPARSE, 7, 1, 1, 2, MODE, KH, KW, false>(p, s);
-            default: break;
-        }
+    if constexpr (any_height(MODE, KH) && !(dense_f8(DT, SPARSE) && is_taps(MODE))) {
+        if (id == 6) return launch<DT, SPARSE, 3, 1, 1, 2, MODE, KH, KW, false>(p, s);
+    }
+    if constexpr (any_height(MODE, KH) && !dense_f8(DT, SPARSE)) {
+        if (id == 7) return launch<DT, SPARSE, 5, 1, 1, 2, MODE, KH, KW, false>(p, s);
+        if (id == 8) return launch<DT, SPARSE, 7, 1, 1, 2, MODE, KH, KW, false>(p, s);
     }
     if constexpr (MODE != MODE_VEC8) {
         if (id == 3) return launch<DT, SPARSE, 4, 1, 2, 2, MODE, KH, KW, true>(p, s);
@@ -1558,7 +1558,7 @@ static int pick_tile(const ConvParams &p, hipStream_t s)
     if constexpr (is_taps(MODE) && KH == 3) {
         const int ncu = compute_units();
         if (ncu <= 0) return SS_ERR_HIP;
-        id = choose_height(p, id, true, is_byte_type(DT), SPARSE, ncu);
+        id = choose_height(p, id, true, is_byte_type(DT), SPARSE, ncu, DT == SS_F8);
     }
     // The dense FP8 instruction of the deep kernels wants its 32-byte A operand in eight consecutive registers; the
     // 256x64 four-wave tile then runs at one wave per SIMD (measured 40 % slower than with producer waves).
@@ -1575,7 +1575,7 @@ static int pick_vec(const ConvParams &p, hipStream_t s)
     if (forced >= 0) return forced == 4 || forced == 5 ? pick_tile<DT, SPARSE, MODE_VEC8, 1, 1>(p, s) : pick_tile<DT, SPARSE, MODE_VEC, 1, 1>(p, s);
     const int ncu = compute_units();
     if (ncu <= 0) return SS_ERR_HIP;
-    const int id = choose_height(p, choose_vec(p, is_byte_type(DT), SPARSE, ncu), false, is_byte_type(DT), SPARSE, ncu);
+    const int id = choose_height(p, choose_vec(p, is_byte_type(DT), SPARSE, ncu), false, is_byte_type(DT), SPARSE, ncu, DT == SS_F8);
     if (id == 4 || id == 5) return launch_tile<DT, SPARSE, MODE_VEC8, 1, 1>(id, p, s);
     return launch_tile<DT, SPARSE, MODE_VEC, 1, 1>(id, p, s);
 }

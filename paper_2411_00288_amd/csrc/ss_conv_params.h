@@ -160,20 +160,30 @@ static inline int choose_vec(const ConvParams &p, bool bytes, bool sparse, int n
 // there are tiles of 96, 160 and 224 rows too (136 channels in one tile of 160 instead of two of 128: 12.1 -> 10.8 us on six 45x61 images,
 // 80 -> 136, sparse, with a residual).
 // By the tiles of the fullest compute unit (halfway between that and the mean, since two or three workgroups share a unit) times the time
-// of a tile, in hundredths of the 128-row one's: medians of a sweep of 6000 drawn layers with each tile forced.  The taller ones have less to
+// of a tile, in hundredths of the 128-row one's, set by a sweep of 7000 drawn layers with each tile forced (profiles/tile_heights.md: medians by
+// staging and operands 81 to 97 for 96 rows, 132 to 156 for 160, 164 to 183 for 224, 180 up for 256).  The taller ones have less to
 // overlap with (two workgroups of five waves per unit, one of seven); dense 8-bit steps are bound by their registers.  Over the layers
 // that come here the choice takes 0.90 of the time of the tiles of 64, 128 and 256 rows alone (1st to 99th percentile 0.57 to 1.11) and is 4 % above
 // the best of all, half of which is noise.  In the paper's flattening the 128- and 256-row tiles are compared in the same way; the
-// channels-last choice between those (choose_vec) stands.
-static inline int choose_height(const ConvParams &p, int id, bool taps, bool bytes, bool sparse, int ncu)
+// channels-last choice between those (choose_vec) stands.  Dense 256 rows: twice 128 and more, so never by this rule.
+// Dense FP8 has costs of its own.  Its instruction wants eight consecutive registers per operand: tiles of 160 and 224 rows take as long as 256
+// (1.95 to 2.24) and are not built; 96 rows gain channels-last (0.84) and not in the paper's flattening (0.99, spilling), where the tile
+// with producer waves stands for 256 rows: the longer the reduction the better (2.12 at one chunk, 1.77, 1.56, 1.45 ... 1.28 at eight).  Over 2300
+// layers 0.2 % and 2 % above the best of all, 0.92 and 0.98 of the time without a choice of heights; with int8's costs it was 1.03 and 1.00 of that (1.08 to 1.13
+// in the paper's flattening at 129 to 224 channels).
+static inline int choose_height(const ConvParams &p, int id, bool taps, bool bytes, bool sparse, int ncu, bool f8 = false)
 {
     if (id != 2 && id != 3) return id;
+    struct Tile {
+        int id, rows, cost;           // (cost 0: not a choice)
+    };
     const bool wide = bytes && !sparse;
-    const struct { int id, rows, cost; } tiles[] = {{2, 128, 100}, {6, 96, 92}, {7, 160, wide ? 170 : 145}, {8, 224, wide ? 180 : 162}, {3, 256, sparse ? 185 : 205}};
+    const Tile usual[] = {{2, 128, 100}, {6, 96, 92}, {7, 160, wide ? 170 : 145}, {8, 224, wide ? 180 : 162}, {3, 256, sparse ? 185 : 205}};
+    const Tile dense_f8[] = {{2, 128, 100}, {6, 96, taps ? 0 : 88}, {7, 160, 0}, {8, 224, 0}, {3, 256, f8 && taps ? 125 + 90 * 9 / p.Ks : 0}};
     long long best = -1;
     int pick = id;
-    for (const auto &t : tiles) {
-        if (!taps && (t.id == 2 || t.id == 3) && t.id != id) continue;
+    for (const auto &t : f8 && !sparse ? dense_f8 : usual) {
+        if (t.cost == 0 || (!taps && (t.id == 2 || t.id == 3) && t.id != id)) continue;
         const long long n = n_blocks(p, t.rows, 64), cost = (n + (n + ncu - 1) / ncu * ncu) * t.cost;
         if (best < 0 || cost < best) { best = cost; pick = t.id; }
     }

@@ -45,3 +45,19 @@ def test_tiles_of_the_fullest_compute_unit_count(choose):
     assert choose(2, 128, 64 * 258, 1, S16) == 2
     for id in (0, 1, 4, 5):                          # grids of one workgroup per unit and less, and the dense channels-last rule, keep theirs
         assert choose(id, 136, LARGE, 1, S16) == id
+
+
+def test_dense_fp8_has_costs_of_its_own(tmp_path):
+    """160 and 224 rows never; 96 rows channels-last only; in the paper's flattening 256 rows (with producer waves) by the length of the reduction."""
+    if shutil.which("g++") is None:
+        pytest.skip("no host compiler")
+    exe = tmp_path / "choose_height_f8"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", str(ROOT / "include"),
+                    str(ROOT / "tests" / "host" / "choose_height_f8.cpp"), "-o", str(exe)], check=True, capture_output=True)
+    # (cout, taps, reduction steps): 9 to a chunk
+    want = {(96, 1, 72): 2, (128, 1, 9): 2, (129, 1, 9): 2, (256, 1, 9): 2, (129, 1, 18): 3, (256, 1, 18): 3, (257, 1, 27): 2, (384, 1, 27): 2, (257, 1, 36): 3,
+            (385, 1, 18): 3, (640, 1, 72): 3, (640, 1, 9): 2,
+            (96, 0, 18): 6, (97, 0, 18): 2, (128, 0, 72): 2, (129, 0, 18): 6, (192, 0, 72): 6, (193, 0, 18): 2, (256, 0, 72): 2, (288, 0, 18): 6, (289, 0, 18): 2}
+    lines = "".join(f"{2} {cout} {LARGE} {taps} {steps}\n" for cout, taps, steps in want)
+    out = subprocess.run([str(exe)], input=lines, capture_output=True, text=True, check=True).stdout.split()
+    assert [int(o) for o in out] == list(want.values())
