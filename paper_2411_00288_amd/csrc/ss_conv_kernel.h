@@ -426,7 +426,7 @@ void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, Con
     // Workgroups are handed to the 8 XCDs round-robin, and each XCD has its own L2.  Renumber them so
     // that an XCD works on a contiguous run of tiles: both row tiles of a pixel tile, and pixel tiles
     // that share halo rows, then hit the same L2.
-    constexpr bool CAN_SPLIT = !FUSE && !is_byte_type(DT);
+    constexpr bool CAN_SPLIT = !FUSE && !is_byte_type(DT) && !is_vec(MODE);
     const int nsplit = CAN_SPLIT ? p.nsplit : 1;
     const int tiles_m = (p.Cout + BM - 1) / BM;
     const int nb = tiles_m * ((p.P + BN - 1) / BN) * nsplit;      // (the grid; asking for its size would lengthen the launch's arguments)
@@ -515,11 +515,11 @@ void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, Con
         }
     }
 
-    // MODE_VEC: position of this thread's 8-element run in the (tap, channel) space
-    int vk = unit * 8 + c_first * ChunkShape<MODE, KH, KW, DEEP>::BK, vc = 0, vr = 0, vt = 0;
+    // MODE_VEC: position of this thread's 8-element run in the (tap, channel) space, from the first chunk on (these modes never split the reduction)
+    int vk = unit * 8, vc = 0, vr = 0, vt = 0;
     if constexpr (is_vec(MODE)) {
         vc = vk;
-        if (c_first > 0 || p.Cin < UNITS * 8) {           // uniform: else the first chunk lies in the first tap
+        if (p.Cin < UNITS * 8) {                          // uniform: else the first chunk lies in the first tap
             int tap = vk / p.Cin;
             vc = vk - tap * p.Cin;
             vr = tap / p.kw;
