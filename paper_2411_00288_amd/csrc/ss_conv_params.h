@@ -34,8 +34,9 @@ struct ConvParams {
 };
 
 // What a launch carries to the kernels of the short calls; the rest of ConvParams follows from it (unpack_args).  A launch whose arguments
-// take more than 112 bytes costs the host 3.7 us, up to 112 bytes 2.8 (none at all: 0.8), whatever the kernel: as long as all of a
-// small layer's work on the GPU.  (ConvParams has 296 bytes, and a kernel that asks for its grid's size another 256.)
+// take more than 112 bytes costs the host 3.65 to 3.8 us, up to 112 bytes 3.0 (none at all: 1.5), whatever the kernel: as long as all of a
+// small layer's work on the GPU (profiles/launch_and_packing_waits.md).  (ConvParams has 296 bytes, and a kernel that asks for its
+// grid's size another 256.)
 struct ConvArgs {
     const uint16_t *x;
     const uint8_t *a_vals;

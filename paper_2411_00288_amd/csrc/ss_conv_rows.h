@@ -12,8 +12,10 @@
 // row block to the next, so the only exposed memory latency is the workgroup's first.
 // (That one is single: the tile, the first bias values and the first weights are asked for together.  With the weights behind the barrier, and
 // every 16-byte run's address worked out from its pixel where the tile is one run of memory, bf16 64 -> 256 channels at 56x56 took 24.0 us
-// at batch 64 and 6.2 at batch 8 instead of 22.3 and 6.0, 512 -> 2048 at 7x7 10.8 instead of 10.1; dense layers gain 3 to 8 %, and only
-// 96 -> 384 with a residual, 620 MB of traffic, is slower: 150.9 -> 152.5.)
+// at batch 64 and 6.2 at batch 8 instead of 22.3 and 6.0, 512 -> 2048 at 7x7 10.8 instead of 10.1; dense layers gain 3 to 8 %.  With a residual the largest one,
+// 96 -> 384 on 128 56x56 images, 620 MB of traffic, is about 0.7 % slower: 151.3 and 152.0 -> 153.0 and 152.7.  It is the weights' place: asked for
+// behind the tile's arrival, 152.3, but then 256 -> 1024 at 14x14 takes 14.8 instead of 14.0 and 128 -> 512 at 28x28 25.0 instead of 24.3.  The
+// addresses and the kind of barrier make no difference.)
 // Bias, residual (added in fp32 before the activation), activation and the single rounding are those of the other
 // kernels; the bias starts in the accumulators.
 #ifndef SS_CONV_ROWS_H_

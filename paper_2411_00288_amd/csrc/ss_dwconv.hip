@@ -134,7 +134,7 @@ struct DwParams {
     const float *bias;
     uint16_t *y;
     int H, W, C, ph, pw, Ho, Wo, act;
-    int per;                              // workgroups per group of channels (not from the grid's size: that would lengthen the launch's arguments to more than 112 bytes, which costs the host 0.9 us)
+    int per;                              // workgroups per group of channels (not from the grid's size: that would lengthen the launch's arguments to more than 112 bytes, which costs the host 0.6 us)
     int R, segs, wt, strips, groups;      // output rows per strip, segments per image, 16-wide tiles per row, strips in all, groups of 16 channels
     int rows, more;                       // rows of the blocks of 16 strips for each workgroup of a group: `rows`, and R or 1 (whole blocks or rows are
     int share;                            // dealt out: share) further ones for the first `more` of them

@@ -62,10 +62,10 @@ __device__ __forceinline__ bool mask_ok(uint32_t m)
 }
 
 // The verdict.  The call returns when everything is packed, and it learns that from the last workgroup, which says so in pinned host
-// memory: 3 us sooner than from an event that completes with the kernel (flush of the caches, completion signal, query).
+// memory: 3 to 5 us sooner than from an event that completes with the kernel (flush of the caches, completion signal, query; profiles/launch_and_packing_waits.md).
 // For that, every store here is written through to memory (its acknowledgement then means that every later kernel, copy or host
 // access finds it, on whatever stream), every wave waits for its acknowledgements, and every workgroup takes a ticket.  One counter would
-// serve 10 ns a ticket (1024 workgroups: 11 us), so from kOneCounter workgroups on groups of them count by themselves, each in a cache
+// serve 12 ns a ticket (1024 workgroups: 10 us and more), so from kOneCounter workgroups on groups of them count by themselves, each in a cache
 // line of its own, and the last of each group counts at the root (0.7 us, the time of 64 tickets).  A counter wraps to zero with its last ticket: nothing has to be reset.
 constexpr unsigned kTicketGroups = 16, kOneCounter = 64;
 struct __attribute__((aligned(128))) TicketLine {

@@ -4,7 +4,7 @@
 // A call of the binding is a handful of microseconds of GPU work for the small layers of a network, so the argument
 // handling in front of it decides how fast a loop over layers runs: through ctypes (17 converted arguments, two size
 // queries, a stream object) a call took 13.4 us on the host, more than the kernel of every layer below about 10 us;
-// through this module it takes 4.1 to 4.7 (3x3 64 -> 64 on one 16x16 image, whose kernel takes 3.3).
+// through this module it takes 4.1 to 4.8 (3x3 64 -> 64 on one 16x16 image, which takes the GPU 2.8 a call).
 //
 // Contract with binding.py: a function here either does the whole call and returns its result, or does nothing and
 // returns None.  None means "not the plain good case" -- a wrong type, size or device, an option that is not handled
