@@ -16,7 +16,8 @@ extern "C" {
 /*
  * Forces the workgroup tile of the convolution entry points (ss_conv2d_*_fwd) to the kernel variant with this id
  * for all later calls of the process; a negative id returns the choice to the library.  Ids: 0-8 the one-tile-per-
- * workgroup shapes (64x64 shallow / deep, 128x64 shallow, 256x64 deep, 128x64 and 256x64 with producer waves);
+ * workgroup shapes (64x64 shallow / deep, 128x64 shallow, 256x64 deep, 128x64 and 256x64 with producer waves, and 96, 160
+ * and 224 rows x 64 for 3x3 and channels-last layers; dense FP8 has of these only the 96 rows channels-last);
  * 10 / 11 the resident-grid 3x3 kernel with 256x128 / 256x64 tiles; 12 the dense 7x7 first-layer kernel; 13 the
  * activation-stationary 1x1 kernel; 20 to 22 the kernels for few output pixels (32 channels x 16 pixels, 32 x 32,
  * 64 x 32 per workgroup).  Ids the problem has no kernel for fall back to the library's choice; with an

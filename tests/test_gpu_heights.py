@@ -1,5 +1,6 @@
 """The tiles of 96, 160 and 224 output channels (tile ids 6 to 8), whose 3, 5 or 7 waves are not a power of two: channel counts around the
-tiles' edges and several tiles high, every staging mode that has them, with and without a residual, 16- and 8-bit operands."""
+tiles' edges and several tiles high, every staging mode that has them, with and without a residual, 16- and 8-bit operands.  (Dense FP8 has the 96 rows
+channels-last only: its other combinations here run through the library's own choice.)"""
 import pytest
 
 import test_gpu_f8 as f8
