@@ -316,10 +316,10 @@ extern "C" int ss_dense_bytes(const ss_weight_desc *desc, size_t *dense_bytes)
 
 constexpr int kPollMicroseconds = 1000, kSleepMicroseconds = 50, kSleepsPerQuery = 1000;
 
-// *launched: the kernel is on the stream.
+// *running: the kernel is on the stream, and this call has not seen its end.
 template <int DT, bool UPD>
 static int launch_compress(const ss_weight_desc *desc, const TileDims &t, void *W, const void *U, const uint8_t *M, uint8_t *packed,
-                           const Waiter &w, hipStream_t s, bool *launched)
+                           const Waiter &w, hipStream_t s, bool *running)
 {
     constexpr int steps = kPackBlocks / (is_byte_type(DT) ? 16 : 8);      // reduction steps per workgroup
     const long long blocks = (long long)t.Mt * ((t.Ks + steps - 1) / steps);
@@ -332,8 +332,9 @@ static int launch_compress(const ss_weight_desc *desc, const TileDims &t, void *
     const void *const kernel = reinterpret_cast<const void *>(&compress_kernel<DT, UPD>);
     const dim3 grid((unsigned)blocks), block(256);
     const hipError_t sent = slot < 0 ? hipExtLaunchKernel(kernel, grid, block, args, 0, s, nullptr, w.done, 0) : hipLaunchKernel(kernel, grid, block, args, 0, s);
-    *launched = sent == hipSuccess;
-    if (hipGetLastError() != hipSuccess || sent != hipSuccess) return SS_ERR_HIP;
+    const bool earlier = hipGetLastError() != hipSuccess;      // an earlier call's error is reported as everywhere, but behind the wait
+    if (sent != hipSuccess) return SS_ERR_HIP;
+    *running = true;
     // Polled without a pause for as long as packing itself takes.  A longer wait is for earlier work on the stream, which may take
     // any time: it sleeps between two looks, about 0.1 ms each with the timer's own slack, so the call returns at most that much late.
     // (hipEventSynchronize and hipStreamSynchronize keep the core busy throughout, with hipEventBlockingSync too: behind
@@ -353,7 +354,9 @@ static int launch_compress(const ss_weight_desc *desc, const TileDims &t, void *
             return SS_ERR_HIP;
         }
     }
-    return e == hipSuccess || e == hipErrorNotReady ? SS_OK : SS_ERR_HIP;
+    if (e != hipSuccess && e != hipErrorNotReady) return SS_ERR_HIP;
+    *running = false;
+    return earlier ? SS_ERR_HIP : SS_OK;
 }
 
 static int compress_entry(const ss_weight_desc *desc, void *W, const void *U, const uint8_t *M, void *packed,
@@ -377,13 +380,13 @@ static int compress_entry(const ss_weight_desc *desc, void *W, const void *U, co
     }
     if (cap != hipStreamCaptureStatusNone) return SS_ERR_HIP;
     Waiter wt;
-    bool launched = false;
+    bool running = false;
     if (!take_waiter(&wt)) return SS_ERR_HIP;
-    if (i8) st = launch_compress<SS_I8, false>(desc, t, W, nullptr, M, p, wt, s, &launched);
-    else if (!U) st = launch_compress<SS_F16, false>(desc, t, W, nullptr, M, p, wt, s, &launched);
-    else if (desc->dtype == SS_F16) st = launch_compress<SS_F16, true>(desc, t, W, U, M, p, wt, s, &launched);
-    else st = launch_compress<SS_BF16, true>(desc, t, W, U, M, p, wt, s, &launched);
-    if (st == SS_ERR_HIP && launched) return st;          // (the kernel may still run: the waiter is not handed out again)
+    if (i8) st = launch_compress<SS_I8, false>(desc, t, W, nullptr, M, p, wt, s, &running);
+    else if (!U) st = launch_compress<SS_F16, false>(desc, t, W, nullptr, M, p, wt, s, &running);
+    else if (desc->dtype == SS_F16) st = launch_compress<SS_F16, true>(desc, t, W, U, M, p, wt, s, &running);
+    else st = launch_compress<SS_BF16, true>(desc, t, W, U, M, p, wt, s, &running);
+    if (st == SS_ERR_HIP && running) return st;           // (the kernel may still run: the waiter is not handed out again)
     const bool bad = __atomic_load_n(&wt.verdict->bad, __ATOMIC_RELAXED) != 0;
     give_waiter(wt);
     if (st != SS_OK || !bad) return st;

@@ -1,4 +1,5 @@
 """GPU parity of the weight compressor / decompressor / dense packer: bit-exact against the oracle."""
+import ctypes
 import gc
 
 import numpy as np
@@ -7,7 +8,7 @@ import torch
 
 import oracle
 from oracle import device_layout as dl
-from paper_2411_00288_amd import workloads as wl
+from paper_2411_00288_amd import binding, workloads as wl
 from helpers import dev_bits, host_bits, layer_desc
 
 pytestmark = pytest.mark.gpu
@@ -287,3 +288,28 @@ def test_updated_weights_are_there_for_another_stream(ss, rows, steps, dtype):
             moved, packed = Wd.view(torch.int16).cpu().numpy().view(np.uint16), out.cpu().numpy()
         assert np.array_equal(moved, W)
         assert np.array_equal(packed, dl.tile(*oracle.compress(W, M), cin=K, kh=1, kw=1, dtype=dtype, korder=wl.K_CRS))
+
+
+def test_a_call_that_reports_an_earlier_error_has_waited_for_its_kernel(ss):
+    """The runtime keeps an error of the thread until it is asked for it; a packing call that finds one reports it, but not before
+    its kernel is done: what the call waits with is free again (a device has sixteen sets of counters), and so are its buffers."""
+    L = wl.Layer("t", N=1, H=4, W=4, cin=64, cout=64, kh=1, kw=1, dtype=wl.F16, mask="logits", seed=5)
+    d, desc = wl.make_inputs(L), layer_desc(ss, L)
+    W, M = dev_bits(d["W"], L.dtype), torch.from_numpy(d["M"]).cuda()
+    want = ss.ss_mask_compress(desc, W, M)
+    packed = torch.zeros_like(want)
+    with open("/proc/self/maps") as maps:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in maps if "libamdhip64" in line))
+    stream, other, want_host = torch.cuda.current_stream(), torch.cuda.Stream(), want.cpu().numpy()
+    torch.cuda.synchronize()
+    for _ in range(20):
+        torch.cuda._sleep(2_000_000)
+        assert hip.hipSetDevice(1 << 20) != 0
+        status = binding._lib.ss_mask_compress(ctypes.byref(desc), W.data_ptr(), M.data_ptr(), packed.data_ptr(), None, stream.cuda_stream)
+        if status == ss.SS_OK:
+            pytest.skip("this runtime forgets an error with the next call that succeeds")
+        assert status == ss.SS_ERR_HIP
+        with torch.cuda.stream(other):                    # (does not wait for the call's stream)
+            assert np.array_equal(packed.cpu().numpy(), want_host)
+        packed.zero_()
+    assert torch.equal(ss.ss_mask_compress(desc, W, M), want)
