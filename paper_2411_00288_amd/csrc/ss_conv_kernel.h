@@ -1423,9 +1423,235 @@ void mlp_kernel(MlpParams p)
     else finish([](float z) { return z; });
 }
 
+// The same two layers on few pixels.  mlp_kernel's four waves take the intermediate 128 channels at a time, so that a workgroup lives for
+// four chunks of weights, matrix instructions, activations and barriers in a row, which nothing hides where there is one workgroup per
+// compute unit.  Here a workgroup owns 32 pixels and has a wave for each 32 channels of the intermediate: every wave computes
+// its row tile at once, the whole intermediate meets in LDS, and the waves share out the second layer's row tiles and its reduction;
+// the partial sums are added in the order of the reduction.  Weights, input and residual are one memory latency.  What is left is mostly the
+// activation: 32 x 384 GELUs of 56 clocks on four SIMDs are 1.1 us of the 3.9 us that 96 -> 384 -> 96 on 3136 pixels takes (7.6 -> 5.5 us with the launch).
+constexpr int kMlpWideWaves = 16;                         // at most 512 intermediate channels
+constexpr int mlp_wide_smem(int cin, int waves)
+{
+    const int tiles = 32 * (cin + 8) * 2 + 32 * (32 * waves + 8) * 2, sums = waves * (int)kFuseRegion;      // (the partial sums take the place of both tiles)
+    return tiles > sums ? tiles : sums;
+}
+
+template <int DT, bool SPARSE, int KS1, bool GELU1>
+__global__ __launch_bounds__(1024)
+void mlp_wide_kernel(MlpParams p)
+{
+    constexpr int BN = 32, CIN = KS1 * 32, XROW = CIN + 8, STEPS = 4;      // STEPS: a wave's steps of the second reduction, at most
+    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+    uint16_t *const Xs = smem, *const Ts = smem + BN * XROW;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 5, c = lane & 31;
+    const int n0 = blockIdx.x * BN, px_here = min(BN, p.P - n0);
+    constexpr int Kp1 = (KS1 + 1) / 2;
+    const unsigned Ks2 = (unsigned)p.Cmid / 32, Kp2 = (Ks2 + 1) / 2, Mt2 = (unsigned)p.Cout2 / 32, nwaves = Ks2;
+    const int TROW = p.Cmid + 8;
+    auto buffer = [](const void *base, unsigned bytes) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, base != nullptr ? (int)bytes : 0, kRsrcFlags);
+    };
+    const __amdgpu_buffer_rsrc_t r1 = buffer(p.a1_vals, Ks2 * KS1 * (SPARSE ? 1024u : 2048u));
+    const __amdgpu_buffer_rsrc_t r2 = buffer(p.a2_vals, Mt2 * Ks2 * (SPARSE ? 1024u : 2048u));
+    const __amdgpu_buffer_rsrc_t m1 = buffer(p.a1_vals + (size_t)(Ks2 * KS1) * 1024, SPARSE ? Ks2 * Kp1 * 256u : 4u);
+    const __amdgpu_buffer_rsrc_t m2 = buffer(p.a2_vals + (size_t)(Mt2 * Ks2) * 1024, SPARSE ? Mt2 * Kp2 * 256u : 4u);
+    const __amdgpu_buffer_rsrc_t rx = buffer(p.x + (size_t)n0 * CIN, (unsigned)px_here * (CIN * 2u));
+    const unsigned out_bytes = (unsigned)px_here * (unsigned)p.Cout2 * 2u;
+    const __amdgpu_buffer_rsrc_t rres = buffer(p.res2 != nullptr ? p.res2 + (size_t)n0 * p.Cout2 : nullptr, out_bytes);
+    const __amdgpu_buffer_rsrc_t ry = buffer(p.y2 + (size_t)n0 * p.Cout2, out_bytes);
+    const __amdgpu_buffer_rsrc_t rb1 = buffer(p.bias1, (unsigned)p.Cmid * 4u), rb2 = buffer(p.bias2, (unsigned)p.Cout2 * 4u);
+
+    // ---- everything that comes from memory
+    // the input tile: CIN / 8 vectors of 16 bytes per pixel, BN * CIN / 8 = 128 KS1 in all
+    u32x4 xv[2];
+    const int NT = (int)nwaves * 64;
+#pragma unroll
+    for (int i = 0; i < 2; i++) xv[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, (tid + i * NT) * 16, 0, 0);
+    u32x4 a1[SPARSE ? 1 : 2][KS1], a2[SPARSE ? 1 : 2][STEPS];
+    uint32_t i1[KS1], i2[STEPS];
+#pragma unroll
+    for (int s = 0; s < KS1; s++) {
+        if constexpr (SPARSE) {
+            a1[0][s] = __builtin_amdgcn_raw_buffer_load_b128(r1, lane * 16, (wave * KS1 + s) * 1024, 0);
+            i1[s] = __builtin_amdgcn_raw_buffer_load_b32(m1, lane * 4, (wave * Kp1 + (s >> 1)) * 256, 0);
+        } else {
+            a1[0][s] = __builtin_amdgcn_raw_buffer_load_b128(r1, lane * 16, (wave * KS1 + s) * 2048, 0);
+            a1[1][s] = __builtin_amdgcn_raw_buffer_load_b128(r1, lane * 16, (wave * KS1 + s) * 2048 + 1024, 0);
+        }
+    }
+    f32x16 acc;                                           // the bias starts in the accumulators
+    auto start = [&](const __amdgpu_buffer_rsrc_t &rb, int row) {
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const f32x4 b = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rb, g * 16, (row + 8 * q) * 4, 0));
+#pragma unroll
+            for (int e = 0; e < 4; e++) acc[4 * q + e] = b[e];
+        }
+    };
+    start(rb1, wave * 32);
+    // the second layer: row tile rt, share `split` of the reduction (a wave without one repeats the last share's loads and is told apart at the end)
+    const unsigned nsplit = nwaves / Mt2, split = (unsigned)wave / Mt2, rt = (unsigned)wave - split * Mt2;
+    const unsigned per = (Ks2 + nsplit - 1) / nsplit, k0 = split * per;
+#pragma unroll
+    for (int s = 0; s < STEPS; s++) {
+        const unsigned ks = min(k0 + s, Ks2 - 1);
+        if constexpr (SPARSE) {
+            a2[0][s] = __builtin_amdgcn_raw_buffer_load_b128(r2, lane * 16, (int)(rt * Ks2 + ks) * 1024, 0);
+            i2[s] = __builtin_amdgcn_raw_buffer_load_b32(m2, lane * 4, (int)(rt * Kp2 + (ks >> 1)) * 256, 0);
+        } else {
+            a2[0][s] = __builtin_amdgcn_raw_buffer_load_b128(r2, lane * 16, (int)(rt * Ks2 + ks) * 2048, 0);
+            a2[1][s] = __builtin_amdgcn_raw_buffer_load_b128(r2, lane * 16, (int)(rt * Ks2 + ks) * 2048 + 1024, 0);
+        }
+    }
+    // output run `it`: row tile it / 128, pixel it % 128 / 4, 8 channels
+    auto out_at = [&](int it) { return (it >> 2 & 31) * p.Cout2 * 2 + (it >> 7) * 64 + (it & 3) * 16; };
+    const int runs = (int)Mt2 * 128;
+    u32x4 res[2];
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+        const int it = tid + i * NT;
+        res[i] = __builtin_amdgcn_raw_buffer_load_b128(rres, it < runs ? out_at(it) : (int)kOutOfRange, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+        const int at = tid + i * NT;
+        if (at < 128 * KS1) *reinterpret_cast<u32x4 *>(Xs + at / (4 * KS1) * XROW + at % (4 * KS1) * 8) = xv[i];
+    }
+    lds_barrier();
+
+    // ---- first layer: rows 32 wave .. of the intermediate
+    {
+        const uint16_t *const src = Xs + c * XROW + 16 * g;
+#pragma unroll
+        for (int s = 0; s < KS1; s++) {
+            B32 bf;
+            bf.lo = *reinterpret_cast<const u32x4 *>(src + 32 * s);
+            bf.hi = *reinterpret_cast<const u32x4 *>(src + 32 * s + 8);
+            if constexpr (SPARSE) {
+                acc = mma_sparse<DT>(a1[0][s], bf, acc, i1[s] >> ((s & 1) * 16));
+            } else {
+                acc = mma_dense<DT>(a1[0][s], bf.lo, acc);
+                acc = mma_dense<DT>(a1[1][s], bf.hi, acc);
+            }
+        }
+        uint16_t *const dst = Ts + c * TROW + wave * 32 + 4 * g;
+        const float floor1 = p.act1 == SS_ACT_RELU ? 0.f : -__builtin_inff();
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            float r[4];
+#pragma unroll
+            for (int e = 0; e < 4; e++) r[e] = GELU1 ? gelu_cdf<DT>(acc[4 * q + e]) : floor_at(acc[4 * q + e], floor1);
+            *reinterpret_cast<uint2 *>(dst + 8 * q) = make_uint2(cvt_pack2<DT>(r[0], r[1]), cvt_pack2<DT>(r[2], r[3]));
+        }
+    }
+    lds_barrier();
+
+    // ---- second layer
+#pragma unroll
+    for (int e = 0; e < 16; e++) acc[e] = 0.f;
+    if (split < nsplit) {                                 // uniform
+        const uint16_t *const src = Ts + c * TROW + 16 * g;
+#pragma unroll
+        for (int s = 0; s < STEPS; s++) {
+            const unsigned ks = k0 + s;
+            if ((unsigned)s >= per || ks >= Ks2) break;   // uniform
+            B32 bf;
+            bf.lo = *reinterpret_cast<const u32x4 *>(src + 32 * ks);
+            bf.hi = *reinterpret_cast<const u32x4 *>(src + 32 * ks + 8);
+            if constexpr (SPARSE) {
+                acc = mma_sparse<DT>(a2[0][s], bf, acc, i2[s] >> ((ks & 1) * 16));
+            } else {
+                acc = mma_dense<DT>(a2[0][s], bf.lo, acc);
+                acc = mma_dense<DT>(a2[1][s], bf.hi, acc);
+            }
+        }
+    }
+    lds_barrier();                                        // the tiles are dead: the partial sums take their place
+    float *const sums = reinterpret_cast<float *>(smem);
+    if (split < nsplit) {
+        float *const dst = sums + wave * (32 * kFuseRow) + c * kFuseRow + 4 * g;
+#pragma unroll
+        for (int q = 0; q < 4; q++) *reinterpret_cast<f32x4 *>(dst + 8 * q) = f32x4{acc[4 * q + 0], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+    }
+    lds_barrier();
+
+    // ---- output: the shares in their order, bias, residual and activation in fp32, one rounding, 16-byte runs
+    auto finish = [&](auto act2) {
+#pragma unroll
+        for (int i = 0; i < 2; i++) {
+            const int it = tid + i * NT;
+            if (it >= runs) break;
+            const float *src = sums + (it >> 7) * (32 * kFuseRow) + (it >> 2 & 31) * kFuseRow + (it & 3) * 8;
+            f32x4 lo = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rb2, ((it >> 7) * 32 + (it & 3) * 8) * 4, 0, 0));
+            f32x4 hi = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rb2, ((it >> 7) * 32 + (it & 3) * 8) * 4 + 16, 0, 0));
+            for (unsigned j = 0; j < nsplit; j++) {
+                lo += *reinterpret_cast<const f32x4 *>(src + j * Mt2 * (32 * kFuseRow));
+                hi += *reinterpret_cast<const f32x4 *>(src + j * Mt2 * (32 * kFuseRow) + 4);
+            }
+            const float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            u32x4 w;
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const uint32_t rr = res[i][e];
+                w[e] = cvt_pack2<DT>(act2(v[2 * e] + widen<DT>((uint16_t)(rr & 0xFFFFu))), act2(v[2 * e + 1] + widen<DT>((uint16_t)(rr >> 16))));
+            }
+            __builtin_amdgcn_raw_buffer_store_b128(w, ry, out_at(it), 0, 0);
+        }
+    };
+    if (p.act2 == SS_ACT_GELU) finish([](float z) { return gelu_cdf<DT>(z); });
+    else if (p.act2 == SS_ACT_RELU) finish([](float z) { return floor_at(z, 0.f); });
+    else finish([](float z) { return z; });
+}
+
+template <int DT, bool SPARSE>
+static int launch_mlp_wide(const MlpParams &p, hipStream_t s)
+{
+    const int waves = p.Cmid / 32, smem = mlp_wide_smem(p.Cin, waves);
+    const long long blocks = ((long long)p.P + 31) / 32;
+    if (blocks <= 0 || blocks > 0x7FFFFFFFll || waves > kMlpWideWaves) return SS_ERR_UNSUPPORTED;
+    auto go = [&](auto ks1) {
+        constexpr int KS1 = decltype(ks1)::value;
+        const auto kern = p.act1 == SS_ACT_GELU ? mlp_wide_kernel<DT, SPARSE, KS1, true> : mlp_wide_kernel<DT, SPARSE, KS1, false>;
+        if (smem > 64 * 1024) {
+            // (once per device and kernel; two threads racing here both set it: harmless)
+            static std::atomic<unsigned long long> done_mask[2];
+            std::atomic<unsigned long long> &done = done_mask[p.act1 == SS_ACT_GELU];
+            int dev = 0;
+            if (hipGetDevice(&dev) != hipSuccess) return (int)SS_ERR_HIP;
+            const unsigned long long bit = 1ull << (dev & 63);
+            if (dev >= 64 || !(done.load(std::memory_order_acquire) & bit)) {
+                if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        mlp_wide_smem(128, kMlpWideWaves)) != hipSuccess)
+                    return (int)SS_ERR_HIP;
+                if (dev < 64) done.fetch_or(bit, std::memory_order_release);
+            }
+        }
+        kern<<<dim3((unsigned)blocks), dim3(waves * 64), smem, s>>>(p);
+        return (int)(hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP);
+    };
+    using std::integral_constant;
+    switch (p.Cin / 32) {
+        case 1: return go(integral_constant<int, 1>{});
+        case 2: return go(integral_constant<int, 2>{});
+        case 3: return go(integral_constant<int, 3>{});
+        case 4: return go(integral_constant<int, 4>{});
+        default: return SS_ERR_UNSUPPORTED;
+    }
+}
+
 template <int DT, bool SPARSE>
 static int launch_mlp(const MlpParams &p, hipStream_t s)
 {
+    const int forced = forced_tile(), ncu = compute_units();
+    if (ncu <= 0) return SS_ERR_HIP;
+    // A wave per 32 intermediate channels while its workgroups of 32 pixels all run at once, from eight waves on.  bf16 with GELU, C -> 4 C ->
+    // C, sparse / dense, mlp_kernel against this one: 3136 pixels C = 64 5.3 / 5.4 against 4.35 / 4.5 us, 96 7.6 / 8.4 against 5.5 / 5.9, 128 10.3 /
+    // 11.4 against 6.65 / 7.5; 8192 pixels, the last that fit, C = 96 7.7 / 8.6 against 5.8 / 6.3; 10000 pixels, 313 workgroups of 12 waves, 7.8 / 8.75
+    // against 9.5 / 10.9.  Four waves (C = 32) make no difference: 3.7 and 3.6.
+    const bool few = ((long long)p.P + 31) / 32 <= ncu && p.Cmid >= 256;
+    if (p.Cmid <= 32 * kMlpWideWaves && (forced == 41 || (forced != 40 && few))) return launch_mlp_wide<DT, SPARSE>(p, s);
     const long long blocks = ((long long)p.P + 63) / 64;
     if (blocks <= 0 || blocks > 0x7FFFFFFFll) return SS_ERR_UNSUPPORTED;
     size_t smem = (size_t)64 * (p.Cin + 8) * 2 + (size_t)64 * (128 + 4) * 2 + (size_t)p.Cmid * 4;
