@@ -3,6 +3,7 @@
 // unit (dwconv_mfma_kernel), the others on the vector ALU, whose 49 multiply-adds per output bound the 7x7 at about 50 us for the
 // 128 x 56 x 56 x 96 layer before any load or conversion (99 us measured).
 #include "ss_internal.h"
+#include "ss_conv_params.h"
 
 namespace ss {
 
@@ -447,18 +448,198 @@ static int launch_dw_mfma(DwParams p, int N, hipStream_t s)
     return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP;
 }
 
+// ---------------------------------------------------------------------------------------------
+// Few outputs, square filters, on the vector ALU.
+//
+// A thread owns ROWS x TWF neighbouring outputs of two channels.  All of its inputs and the filter's taps are asked for before the first
+// multiplication, so that there is one memory latency (dwconv_kernel has one per filter row, the matrix kernel a barrier per input row
+// behind a set-up of 5 us); the taps wait in LDS as fp32, the threads' positions come from multiply-and-shift divisions.  Order of the sums and
+// rounding are those of dwconv_kernel.  us, bf16, against the faster of those two before: 3x3 14 x 14 x 14 x 96 4.8 -> 3.7, 16 x 56 x 56 x 96 8.5 -> 6.3,
+// 128 x 56 x 56 x 96 40.6 -> 32.1; 5x5 14 x 14 x 14 x 96 6.9 -> 3.8, 16 x 28 x 28 x 96 7.3 -> 4.7, 12 x 56 x 56 x 96 10.1 -> 7.7; 7x7 14 x 14 x 14 x 96
+// 8.3 -> 3.9, 1 x 56 x 56 x 96 8.5 -> 4.4, 20 x 28 x 35 x 96 10.2 -> 7.6.  From there on the vector ALU bounds it: 49 multiply-adds and some 40
+// other instructions per two 7x7 outputs (four rows of a thread share their inputs' conversion, but take registers and leave half of the chip idle
+// where there are few).  Four channels per thread (twice the loads' width) are 1.1 to 1.6 times as slow, eight columns 1.0 to 1.3.
+// ---------------------------------------------------------------------------------------------
+struct DwFewParams {
+    const uint16_t *x, *w;
+    const float *bias;
+    uint16_t *y;
+    int H, W, C, ph, pw, Ho, Wo, act, total;
+    unsigned x_bytes, w_bytes;
+    unsigned run_mul, wq_mul, hq_mul, shifts;      // divisions by C / 2, ceil(Wo / TWF) and ceil(Ho / ROWS)
+};
+static_assert(sizeof(DwFewParams) <= 112, "a cheap launch");
+constexpr int kDwFewTaps = 8192;          // K K C at most: 32 KiB of LDS
+// (A column outside the image is an offset of 2 GiB, and must stay out of range on all of a thread's rows.)
+static inline bool few_fits(int W, int C, int K) { return K * K * C <= kDwFewTaps && (long long)(K + 3) * W * C * 2 < (1ll << 31); }
+
+template <int DT>
+__device__ __forceinline__ void widen2(uint32_t v, float &a, float &b)
+{
+    if constexpr (DT == SS_F16) {
+        a = (float)__builtin_bit_cast(_Float16, (uint16_t)(v & 0xFFFFu));
+        b = (float)__builtin_bit_cast(_Float16, (uint16_t)(v >> 16));
+    } else {
+        a = __builtin_bit_cast(float, v << 16);
+        b = __builtin_bit_cast(float, v & 0xFFFF0000u);
+    }
+}
+
+template <int DT, int K, int TWF, int ROWS>
+__global__ __launch_bounds__(256) void dwconv_few_kernel(DwFewParams p)
+{
+    constexpr int COLS = K + TWF - 1, INS = K + ROWS - 1;      // input columns and rows
+    extern __shared__ __attribute__((aligned(16))) float taps_s[];      // [tap][C]
+    const int tid = threadIdx.x;
+    const unsigned gid = blockIdx.x * 256u + tid;
+    const bool live = gid < (unsigned)p.total;
+    auto div = [](unsigned n, unsigned mul, unsigned sh) { return (unsigned)(((unsigned long long)n * mul) >> sh); };
+    const unsigned id = live ? gid : 0u;
+    const int runs = p.C / 2, wq = (p.Wo + TWF - 1) / TWF;
+    const unsigned r0 = div(id, p.run_mul, p.shifts & 63u), r1 = div(r0, p.wq_mul, p.shifts >> 6 & 63u), n = div(r1, p.hq_mul, p.shifts >> 12 & 63u);
+    const int c = (int)(id - r0 * runs) * 2, wo0 = (int)(r0 - r1 * wq) * TWF, ho = (int)(r1 - n * ((p.Ho + ROWS - 1) / ROWS)) * ROWS;
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.x), 0, (int)p.x_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.w), 0, (int)p.w_bytes, 0x00020000);
+
+    // ---- the filter: at most TV vectors of 8 taps per thread
+    constexpr int TV = kDwFewTaps / 2048;
+    u32x4 wv[TV];
+#pragma unroll
+    for (int i = 0; i < TV; i++) wv[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, (tid + 256 * i) * 16, 0, 0);
+    // ---- the inputs (a column outside the image is out of range; rows outside it are loaded, from wherever in the buffer, and not used)
+    unsigned off[COLS];
+    const unsigned first = (unsigned)((((int)n * p.H + ho - p.ph) * p.W + wo0 - p.pw) * p.C + c) * 2u, row_bytes = (unsigned)(p.W * p.C) * 2u;
+#pragma unroll
+    for (int j = 0; j < COLS; j++) {
+        const bool in = (unsigned)(wo0 - p.pw + j) < (unsigned)p.W;
+        off[j] = in ? first + (unsigned)(j * p.C) * 2u : 0x80000000u;
+    }
+    uint32_t xv[INS][COLS];
+#pragma unroll
+    for (int r = 0; r < INS; r++)
+#pragma unroll
+        for (int j = 0; j < COLS; j++) xv[r][j] = __builtin_amdgcn_raw_buffer_load_b32(rx, (int)(off[j] + (unsigned)r * row_bytes), 0, 0);
+    float acc[ROWS][TWF][2];
+#pragma unroll
+    for (int e = 0; e < 2; e++) {
+        const float b = p.bias ? p.bias[c + e] : 0.f;
+#pragma unroll
+        for (int o = 0; o < ROWS; o++)
+#pragma unroll
+            for (int j = 0; j < TWF; j++) acc[o][j][e] = b;
+    }
+#pragma unroll
+    for (int i = 0; i < TV; i++) {
+        const int at = (tid + 256 * i) * 8;
+        if (at < K * K * p.C) {
+            float f[8];
+            widen8<DT>(wv[i], f);
+            *reinterpret_cast<f32x4 *>(taps_s + at) = f32x4{f[0], f[1], f[2], f[3]};
+            *reinterpret_cast<f32x4 *>(taps_s + at + 4) = f32x4{f[4], f[5], f[6], f[7]};
+        }
+    }
+    lds_barrier();
+    if (!live) return;
+    const float *const taps = taps_s + c;
+#pragma unroll
+    for (int r = 0; r < INS; r++) {
+        if ((unsigned)(ho - p.ph + r) < (unsigned)p.H) {
+            float xf[COLS][2];
+#pragma unroll
+            for (int j = 0; j < COLS; j++) widen2<DT>(xv[r][j], xf[j][0], xf[j][1]);
+#pragma unroll
+            for (int o = 0; o < ROWS; o++) {              // filter row r - o, for output row ho + o
+                if (r - o < 0 || r - o >= K) continue;
+#pragma unroll
+                for (int t = 0; t < K; t++) {
+                    float wf[2];
+#pragma unroll
+                    for (int e = 0; e < 2; e++) wf[e] = taps[((r - o) * K + t) * p.C + e];
+#pragma unroll
+                    for (int j = 0; j < TWF; j++)
+#pragma unroll
+                        for (int e = 0; e < 2; e++) acc[o][j][e] = __builtin_fmaf(wf[e], xf[j + t][e], acc[o][j][e]);
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int o = 0; o < ROWS; o++) {
+        if (ho + o >= p.Ho) break;
+        uint16_t *const dst = p.y + (((size_t)n * p.Ho + ho + o) * p.Wo + wo0) * p.C + c;
+#pragma unroll
+        for (int j = 0; j < TWF; j++) {
+            if (wo0 + j >= p.Wo) break;
+            float a = acc[o][j][0], b = acc[o][j][1];
+            if (p.act == SS_ACT_RELU) { a = a < 0.f ? 0.f : a; b = b < 0.f ? 0.f : b; }
+            *reinterpret_cast<uint32_t *>(dst + (size_t)j * p.C) = pack2<DT>(a, b);
+        }
+    }
+}
+
+// floor(n / d) for 0 <= n < 2^31 as (n * mul) >> sh (as fast_div_setup of the convolutions)
+static inline unsigned div_setup(unsigned d, unsigned *mul)
+{
+    unsigned s = 0;
+    while ((1ull << s) < d) s++;
+    *mul = (unsigned)(((1ull << (31 + s)) + d - 1) / d);
+    return 31 + s;
+}
+
+template <int DT, int K, int TWF, int ROWS>
+static int launch_dw_few(const uint16_t *x, const uint16_t *w, const float *bias, uint16_t *y, int N, int H, int W, int C, int ph, int pw, int Ho, int Wo,
+                         int act, unsigned x_bytes, hipStream_t s)
+{
+    DwFewParams p{};
+    p.x = x; p.w = w; p.bias = bias; p.y = y;
+    p.H = H; p.W = W; p.C = C; p.ph = ph; p.pw = pw; p.Ho = Ho; p.Wo = Wo; p.act = act;
+    const int runs = C / 2, wq = (Wo + TWF - 1) / TWF;
+    const int hq = (Ho + ROWS - 1) / ROWS;
+    const long long total = (long long)N * hq * wq * runs;
+    if (total <= 0 || total > 0x7FFFFF00ll) return SS_ERR_UNSUPPORTED;
+    p.total = (int)total;
+    p.x_bytes = x_bytes;
+    p.w_bytes = (unsigned)(K * K * C * 2);
+    p.shifts = div_setup((unsigned)runs, &p.run_mul);
+    p.shifts |= div_setup((unsigned)wq, &p.wq_mul) << 6;
+    p.shifts |= div_setup((unsigned)hq, &p.hq_mul) << 12;
+    dwconv_few_kernel<DT, K, TWF, ROWS><<<dim3((unsigned)((total + 255) / 256)), dim3(256), (size_t)K * K * C * 4, s>>>(p);
+    return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP;
+}
+
 template <int DT>
 static int launch_dw(const uint16_t *x, const uint16_t *w, const float *bias, uint16_t *y, int N, int H, int W, int C, int kh,
                      int kw, int ph, int pw, int Ho, int Wo, int act, unsigned x_bytes, hipStream_t s)
 {
     const long long ybytes = (long long)N * Ho * Wo * C * 2;
-    // The matrix kernel costs about the same for every filter width and has a longer set-up.  Measured against the vector one:
-    // 7x7 faster or equal from 1 x 7 x 7 x 96 up (128 x 56 x 56 x 96 in a chain: 99 -> 41.5 us); 5x5 from about 4 M outputs (32 x 56 x 56 x
-    // 96: 21.6 -> 16.9; 128 x 13 x 19 x 64: 8.5 vs 9.9); 3x3 nowhere.
+    // Few outputs: the kernel for them, 3x3 always.  Against the vector one it wins everywhere (above); against the matrix one, us: 5x5 16 x 56 x 56 x 96
+    // (4.8 M outputs) 10.0 / 10.3, 64 x 28 x 28 x 128 (6.4 M) 11.9 / 11.2; 7x7 8 x 56 x 56 x 96 (2.4 M) 9.35 / 10.6, 12 x 56 x 56 x 96 (3.6 M) 11.0 / 10.95, 16 (4.8 M)
+    // 13.5 / 11.6.  Rows per thread: 3x3 at 1.9 M outputs 4.2 / 4.3 / 4.7 for one, two and four, 4.8 M 7.5 / 6.3 / 6.6, 9.6 M 14 / 11.1 / 10.2; 7x7 at
+    // 1.4 M 6.6 / 7.1 for one and two, 1.9 M 8.0 / 7.6.  7x7 in pairs of columns while that is one workgroup per compute unit: 14 x 14 x 14 x 96 4.4 -> 3.9.
+    // The matrix kernel costs about the same for every filter width and has a longer set-up.  Measured against the vector one, where the taps or
+    // the rows do not fit the kernel for few outputs: 7x7 faster or equal from 1 x 7 x 7 x 96 up, 5x5 from about 4 M outputs.
     // (Its offsets outside the image start at 2 GiB and move on by a row per step, from the first padding row to the image's last: they must not
     // come round to the image again.)
     const bool rows_fit = ((long long)H + ph) * W * C * 2 < (1ll << 31);
-    if (kh == kw && rows_fit && ybytes < (1ll << 31) && (kw == 7 || (kw == 5 && ybytes >= (8ll << 20)))) {
+    const int forced = forced_tile();                     // test hook: 60 vector kernel, 61 matrix kernel, 62 to 65 few outputs
+    if (kh == kw && few_fits(W, C, kw) && forced != 60 && forced != 61) {
+        const long long outputs = (long long)N * Ho * Wo * C;
+#define SS_DW_FEW(K, TWF, ROWS) launch_dw_few<DT, K, TWF, ROWS>(x, w, bias, y, N, H, W, C, ph, pw, Ho, Wo, act, x_bytes, s)
+        if (kw == 3) {
+            const int rows = forced == 63 ? 1 : (forced == 64 ? 2 : (forced == 65 ? 4 : (outputs < 2500000 ? 1 : (outputs < 8000000 ? 2 : 4))));
+            return rows == 1 ? SS_DW_FEW(3, 4, 1) : (rows == 2 ? SS_DW_FEW(3, 4, 2) : SS_DW_FEW(3, 4, 4));
+        }
+        if (kw == 5 && (outputs < 5000000 || forced == 63)) return SS_DW_FEW(5, 4, 1);
+        if (kw == 7 && (outputs < 3200000 || (forced >= 62 && forced <= 64))) {
+            const int ncu = compute_units();
+            if (ncu <= 0) return SS_ERR_HIP;
+            const bool narrow = (long long)N * Ho * ((Wo + 1) / 2) * (C / 2) <= 256ll * ncu;
+            if (forced == 62 || (forced < 62 && narrow)) return SS_DW_FEW(7, 2, 1);
+            return forced == 64 || (forced != 63 && outputs >= 1700000) ? SS_DW_FEW(7, 4, 2) : SS_DW_FEW(7, 4, 1);
+        }
+#undef SS_DW_FEW
+    }
+    if (kh == kw && rows_fit && ybytes < (1ll << 31) && forced != 60 && (kw == 7 || (kw == 5 && (ybytes >= (8ll << 20) || forced == 61)))) {
         DwParams p{};
         p.x = x; p.w = w; p.bias = bias; p.y = y;
         p.H = H; p.W = W; p.C = C; p.ph = ph; p.pw = pw; p.Ho = Ho; p.Wo = Wo; p.act = act;
