@@ -303,6 +303,35 @@ int ss_conv2d_pw_fused_query(const ss_weight_desc *desc1, int32_t stride_h, int3
                              const ss_weight_desc *desc2, int32_t sparse, int32_t *supported /*[host] out*/,
                              int32_t *pays /*[host] out*/);
 
+/*
+ * ss_conv2d_pw_fused_fwd and the 1x1 layer that reads its output (the channel reduction that opens the next bottleneck) in one kernel:
+ *   y2 as ss_conv2d_pw_fused_fwd writes y, and y3 = act3( conv_1x1(y2) + bias3 ), computed from y2 as it is stored, without reading it back.
+ * Both are written; up to the order of fp32 additions they equal the two calls.  First layer 3x3 in the SS_K_CRS flattening with
+ * cin % 32 == 0 and at most 128 channels, desc2->cout % 128 == 0, desc3 a 1x1 layer on desc2->cout channels with cout % 32 == 0, at most 128;
+ * anything else SS_ERR_UNSUPPORTED.  y3 [N][Ho][Wo][desc3->cout] 16-byte aligned, overlapping none of the other buffers; bias3 16-byte aligned or NULL.
+ * Everything else as for ss_conv2d_pw_fused_fwd.  The _dense_ form takes operands built by ss_dense_pack.
+ */
+int ss_conv2d_pw2_fused_fwd(const ss_weight_desc *desc1, const void *x, int32_t N, int32_t H, int32_t Wd,
+                            const void *packed1, const float *bias1,
+                            int32_t stride_h, int32_t stride_w, int32_t pad_h, int32_t pad_w, int32_t act1,
+                            const ss_weight_desc *desc2, const void *packed2, const float *bias2,
+                            const void *residual, int32_t act2, void *y2,
+                            const ss_weight_desc *desc3, const void *packed3, const float *bias3, int32_t act3, void *y3, void *stream);
+int ss_conv2d_pw2_fused_dense_fwd(const ss_weight_desc *desc1, const void *x, int32_t N, int32_t H, int32_t Wd,
+                                  const void *dense1, const float *bias1,
+                                  int32_t stride_h, int32_t stride_w, int32_t pad_h, int32_t pad_w, int32_t act1,
+                                  const ss_weight_desc *desc2, const void *dense2, const float *bias2,
+                                  const void *residual, int32_t act2, void *y2,
+                                  const ss_weight_desc *desc3, const void *dense3, const float *bias3, int32_t act3, void *y3, void *stream);
+
+/*
+ * ss_conv2d_pw_fused_query for these three layers on an input [N][H][Wd]: *pays is 1 when the library expects one kernel to beat the pair's and
+ * the third layer's (that depends on the number of pixels).
+ */
+int ss_conv2d_pw2_fused_query(const ss_weight_desc *desc1, int32_t N, int32_t H, int32_t Wd, int32_t stride_h, int32_t stride_w, int32_t pad_h,
+                              int32_t pad_w, const ss_weight_desc *desc2, const ss_weight_desc *desc3, int32_t sparse,
+                              int32_t *supported /*[host] out*/, int32_t *pays /*[host] out*/);
+
 /* The dense twin of ss_conv2d_pw_fused_fwd (operands built by ss_dense_pack). */
 int ss_conv2d_pw_fused_dense_fwd(const ss_weight_desc *desc1, const void *x, int32_t N, int32_t H, int32_t Wd,
                                  const void *dense1, const float *bias1,

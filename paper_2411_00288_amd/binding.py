@@ -29,7 +29,8 @@ EXPORTS = ["ss_status_string", "ss_packed_bytes", "ss_dense_bytes", "ss_mask_com
            "ss_dense_pack", "ss_conv2d_workspace_bytes", "ss_conv2d_fwd", "ss_conv2d_dense_fwd",
            "ss_conv2d_res_fwd", "ss_conv2d_dense_res_fwd", "ss_mask_update_compress", "ss_maxpool2d", "ss_dwconv2d_fwd",
            "ss_conv2d_q8_fwd", "ss_conv2d_q8_dense_fwd", "ss_conv2d_pw_fused_fwd", "ss_conv2d_pw_fused_dense_fwd",
-           "ss_weights_check", "ss_conv2d_fwd_static_ws", "ss_conv2d_pw_fused_query"]
+           "ss_weights_check", "ss_conv2d_fwd_static_ws", "ss_conv2d_pw_fused_query", "ss_conv2d_pw2_fused_fwd", "ss_conv2d_pw2_fused_dense_fwd",
+           "ss_conv2d_pw2_fused_query"]
 DEBUG_EXPORTS = ["ss_debug_force_tile", "ss_debug_limit_blocks", "ss_debug_force_split", "ss_debug_issue_peak", "ss_debug_lds_bandwidth"]          # include/ss_debug.h: test hooks
 
 
@@ -78,6 +79,10 @@ def _load() -> ctypes.CDLL:
     lib.ss_conv2d_pw_fused_dense_fwd.argtypes = fused_args
     lib.ss_weights_check.argtypes = [dp, vp, i32, vp]
     lib.ss_conv2d_pw_fused_query.argtypes = [dp, i32, i32, i32, i32, dp, i32, ctypes.POINTER(i32), ctypes.POINTER(i32)]
+    third_args = fused_args[:-1] + [dp, vp, vp, i32, vp, vp]
+    lib.ss_conv2d_pw2_fused_fwd.argtypes = third_args
+    lib.ss_conv2d_pw2_fused_dense_fwd.argtypes = third_args
+    lib.ss_conv2d_pw2_fused_query.argtypes = [dp, i32, i32, i32, i32, i32, i32, i32, dp, dp, i32, ctypes.POINTER(i32), ctypes.POINTER(i32)]
     lib.ss_conv2d_fwd_static_ws.argtypes = conv_args[:13] + [vp]            # no workspace pair
     lib.ss_debug_force_tile.argtypes = [i32]
     lib.ss_debug_limit_blocks.argtypes = [i32]
@@ -347,13 +352,16 @@ def _conv(fn, what, desc, x, wbuf, bias, stride, pad, act, y, workspace, stream,
     return y
 
 
-def _launch(what, kind, desc1, desc2, x, w1, w2, scale, bias1, bias2, residual, y, workspace, nhw, stride, pad, act1, act2=0, pool=None):
-    """The callable that enqueues a marshalled call on torch's current stream (arguments checked by the caller)."""
+def _launch(what, kind, desc1, desc2, x, w1, w2, scale, bias1, bias2, residual, y, workspace, nhw, stride, pad, act1, act2=0, pool=None, third=None):
+    """The callable that enqueues a marshalled call on torch's current stream (arguments checked by the caller).  third: descriptor, weights,
+    bias, activation and output of a third layer."""
     def failed(st):
         raise SSError(st, what)
     tensors = (x, w1, w2, scale, bias1, bias2, residual, y, workspace)
-    return _native.launch(kind, desc1, desc2, tuple(None if t is None else t.data_ptr() for t in tensors), _nbytes(workspace),
-                          tuple(nhw), (stride[0], stride[1], pad[0], pad[1]), int(act1), int(act2), pool, tensors, failed)
+    ptr = lambda t: None if t is None else t.data_ptr()
+    last = None if third is None else (third[0], ptr(third[1]), ptr(third[2]), int(third[3]), ptr(third[4]))
+    return _native.launch(kind, desc1, desc2, tuple(map(ptr, tensors)), _nbytes(workspace),
+                          tuple(nhw), (stride[0], stride[1], pad[0], pad[1]), int(act1), int(act2), pool, last, (tensors, third), failed)
 
 
 def prepare_conv2d(desc, x, wbuf, bias=None, stride=(1, 1), pad=(0, 0), act=SS_ACT_NONE, y=None, workspace=None,
@@ -501,10 +509,8 @@ def ss_conv2d_q8_dense_fwd(desc, x, dense, scale=None, bias=None, stride=(1, 1),
     return y
 
 
-def prepare_conv2d_pw_fused(desc1, x, w1, bias1, stride, pad, act1, desc2, w2, bias2=None, residual=None,
-                            act2=SS_ACT_NONE, y=None, sparse=True):
-    """Marshal the arguments of ss_conv2d_pw_fused_fwd / ss_conv2d_pw_fused_dense_fwd once; returns (launch, y)."""
-    what = "ss_conv2d_pw_fused_fwd" if sparse else "ss_conv2d_pw_fused_dense_fwd"
+def _prepare_fused(what, third, desc1, x, w1, bias1, stride, pad, act1, desc2, w2, bias2, residual, act2, y, sparse):
+    """Checks and marshals a fused pair, with its third layer (descriptor, weights, bias, activation, output or None) if there is one."""
     if x is None or x.dim() != 4 or x.shape[3] != desc1.cin:
         raise SSError(SS_ERR_INVALID_ARG, f"{what}: x must be NHWC with cin channels")
     N, H, W, _ = x.shape
@@ -525,8 +531,64 @@ def prepare_conv2d_pw_fused(desc1, x, w1, bias1, stride, pad, act1, desc2, w2, b
     for t, name in ((bias1, "bias1"), (bias2, "bias2")):
         _dev_ptr(t, name, (torch.float32,), allow_none=True)
     _dev_ptr(residual, "residual", allow_none=True)
-    return _launch(what, 4 if sparse else 5, desc1, desc2, x, w1, w2, None, bias1, bias2, residual, y, None, (N, H, W), stride, pad,
-                   act1, act2), y
+    if third is None:
+        return _launch(what, 4 if sparse else 5, desc1, desc2, x, w1, w2, None, bias1, bias2, residual, y, None, (N, H, W), stride, pad,
+                       act1, act2), y
+    desc3, w3, bias3, act3, y3 = third
+    _check_operands(what, desc3, w3, bias3, sparse)
+    shp3 = shp[:3] + (desc3.cout,)
+    if y3 is None:
+        y3 = torch.empty(shp3, dtype=x.dtype, device=x.device)
+    elif tuple(y3.shape) != shp3 or y3.dtype != x.dtype:
+        raise SSError(SS_ERR_INVALID_ARG, f"{what}: y3 must be {shp3} {x.dtype}")
+    _dev_ptr(w3, "weights 3")
+    _dev_ptr(y3, "y3")
+    _dev_ptr(bias3, "bias3", (torch.float32,), allow_none=True)
+    return _launch(what, 7 if sparse else 8, desc1, desc2, x, w1, w2, None, bias1, bias2, residual, y, None, (N, H, W), stride, pad,
+                   act1, act2, third=(desc3, w3, bias3, act3, y3)), y, y3
+
+
+def prepare_conv2d_pw_fused(desc1, x, w1, bias1, stride, pad, act1, desc2, w2, bias2=None, residual=None,
+                            act2=SS_ACT_NONE, y=None, sparse=True):
+    """Marshal the arguments of ss_conv2d_pw_fused_fwd / ss_conv2d_pw_fused_dense_fwd once; returns (launch, y)."""
+    what = "ss_conv2d_pw_fused_fwd" if sparse else "ss_conv2d_pw_fused_dense_fwd"
+    return _prepare_fused(what, None, desc1, x, w1, bias1, stride, pad, act1, desc2, w2, bias2, residual, act2, y, sparse)
+
+
+def prepare_conv2d_pw2_fused(desc1, x, w1, bias1, stride, pad, act1, desc2, w2, bias2, residual, act2, desc3, w3, bias3=None,
+                             act3=SS_ACT_NONE, y2=None, y3=None, sparse=True):
+    """Marshal the arguments of ss_conv2d_pw2_fused_fwd / ss_conv2d_pw2_fused_dense_fwd once; returns (launch, y2, y3)."""
+    what = "ss_conv2d_pw2_fused_fwd" if sparse else "ss_conv2d_pw2_fused_dense_fwd"
+    return _prepare_fused(what, (desc3, w3, bias3, act3, y3), desc1, x, w1, bias1, stride, pad, act1, desc2, w2, bias2, residual, act2, y2, sparse)
+
+
+def ss_conv2d_pw2_fused_query(desc1, nhw, stride, pad, desc2, desc3, sparse=True):
+    """(supported, pays): would the three layers run in one kernel, and does the library expect that, on an input of nhw = (N, H, W), to beat the
+    pair and the third call?"""
+    sup, pays = ctypes.c_int32(0), ctypes.c_int32(0)
+    st = _lib.ss_conv2d_pw2_fused_query(ctypes.byref(desc1), nhw[0], nhw[1], nhw[2], stride[0], stride[1], pad[0], pad[1], ctypes.byref(desc2), ctypes.byref(desc3),
+                                        1 if sparse else 0, ctypes.byref(sup), ctypes.byref(pays))
+    if st != SS_OK:
+        raise SSError(st, "ss_conv2d_pw2_fused_query")
+    return bool(sup.value), bool(pays.value)
+
+
+def ss_conv2d_pw2_fused_fwd(desc1, x, packed1, bias1, stride, pad, act1, desc2, packed2, bias2, residual, act2, desc3, packed3, bias3=None,
+                            act3=SS_ACT_NONE, y2=None, y3=None):
+    """ss_conv2d_pw_fused_fwd and the 1x1 masked convolution that reads its output; returns (y2, y3)."""
+    launch, y2, y3 = prepare_conv2d_pw2_fused(desc1, x, packed1, bias1, stride, pad, act1, desc2, packed2, bias2, residual, act2, desc3, packed3,
+                                              bias3, act3, y2, y3, sparse=True)
+    launch()
+    return y2, y3
+
+
+def ss_conv2d_pw2_fused_dense_fwd(desc1, x, dense1, bias1, stride, pad, act1, desc2, dense2, bias2, residual, act2, desc3, dense3, bias3=None,
+                                  act3=SS_ACT_NONE, y2=None, y3=None):
+    """The dense twin of ss_conv2d_pw2_fused_fwd."""
+    launch, y2, y3 = prepare_conv2d_pw2_fused(desc1, x, dense1, bias1, stride, pad, act1, desc2, dense2, bias2, residual, act2, desc3, dense3,
+                                              bias3, act3, y2, y3, sparse=False)
+    launch()
+    return y2, y3
 
 
 def ss_conv2d_pw_fused_query(desc1, stride, pad, desc2, sparse=True):

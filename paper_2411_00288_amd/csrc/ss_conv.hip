@@ -149,16 +149,40 @@ static int conv_entry(const ss_weight_desc *desc, const void *x, int32_t N, int3
     }
 }
 
+// The 1x1 layer that follows a fused pair (d null: none).
+struct ThirdLayer {
+    const ss_weight_desc *d;
+    const void *w;
+    const float *bias;
+    int32_t act;
+    void *y;
+};
+
+// Can a third layer follow this pair?  (the conditions of the kernels: whole tiles everywhere, 128 channels of the second output at a time)
+static bool third_fits(const ss_weight_desc *d1, const ss_weight_desc *d2, const ss_weight_desc *d3)
+{
+    return d1->korder == SS_K_CRS && d1->kh == 3 && d1->kw == 3 && d1->cin % 32 == 0 && d1->cout <= 128 && d2->cout % 128 == 0 && d3->cout % 32 == 0 && d3->cout <= 128;
+}
+
 template <bool SPARSE>
 static int fused_entry(const ss_weight_desc *d1, const void *x, int32_t N, int32_t H, int32_t Wd, const void *w1,
                        const float *bias1, int32_t sh, int32_t sw, int32_t ph, int32_t pw, int32_t act1,
                        const ss_weight_desc *d2, const void *w2, const float *bias2, const void *residual, int32_t act2,
-                       void *y, void *stream)
+                       void *y, void *stream, const ThirdLayer &third = {})
 {
     int st = check_desc(d1, SPARSE);
     if (st != SS_OK) return st;
     st = check_desc(d2, SPARSE);
     if (st != SS_OK) return st;
+    if (third.d) {
+        st = check_desc(third.d, SPARSE);
+        if (st != SS_OK) return st;
+        if (third.d->dtype != d1->dtype) return SS_ERR_UNSUPPORTED;
+        if (third.d->kh != 1 || third.d->kw != 1 || third.d->cin != d2->cout) return SS_ERR_INVALID_ARG;
+        if (!third_fits(d1, d2, third.d)) return SS_ERR_UNSUPPORTED;
+        if (!third.w || !third.y || !aligned(third.w, 16) || !aligned(third.y, 16) || (third.bias && !aligned(third.bias, 16))) return SS_ERR_INVALID_ARG;
+        if (third.act != SS_ACT_NONE && third.act != SS_ACT_RELU && third.act != SS_ACT_GELU) return SS_ERR_INVALID_ARG;
+    }
     if (is_byte_type(d1->dtype) || d2->dtype != d1->dtype) return SS_ERR_UNSUPPORTED;
     if (d2->kh != 1 || d2->kw != 1 || d2->cin != d1->cout) return SS_ERR_INVALID_ARG;
     const bool mlp = d1->kh * d1->kw == 1;        // 1x1 -> 1x1: the inverted-bottleneck kernel
@@ -231,6 +255,16 @@ static int fused_entry(const ss_weight_desc *d1, const void *x, int32_t N, int32
     p.Cout2 = d2->cout; p.Ks2 = t2.Ks; p.Kp2 = t2.Kp; p.Mt2 = t2.Mt; p.act2 = act2;
     p.a2_bytes = (unsigned)((size_t)t2.Mt * t2.Ks * (SPARSE ? 1024 : 2048));
     p.meta2_bytes = SPARSE ? (unsigned)((size_t)t2.Mt * t2.Kp * 256) : 4u;
+    if (third.d) {
+        const TileDims t3 = tile_dims(third.d);
+        p.a3_vals = static_cast<const uint8_t *>(third.w) + kHeaderBytes;
+        p.a3_meta = reinterpret_cast<const uint32_t *>(p.a3_vals + (size_t)t3.Mt * t3.Ks * 1024);
+        p.bias3 = third.bias;
+        p.y3 = static_cast<uint16_t *>(third.y);
+        p.Cout3 = third.d->cout; p.Ks3 = t3.Ks; p.Kp3 = t3.Kp; p.Mt3 = t3.Mt; p.act3 = third.act;
+        p.a3_bytes = (unsigned)((size_t)t3.Mt * t3.Ks * (SPARSE ? 1024 : 2048));
+        p.meta3_bytes = SPARSE ? (unsigned)((size_t)t3.Mt * t3.Kp * 256) : 4u;
+    }
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (d1->dtype == SS_F16) return SPARSE ? fused_dispatch_f16_sparse(d1, p, s) : fused_dispatch_f16_dense(d1, p, s);
     return SPARSE ? fused_dispatch_bf16_sparse(d1, p, s) : fused_dispatch_bf16_dense(d1, p, s);
@@ -431,4 +465,54 @@ extern "C" int ss_conv2d_pw_fused_dense_fwd(const ss_weight_desc *desc1, const v
 {
     return fused_entry<false>(desc1, x, N, H, Wd, dense1, bias1, stride_h, stride_w, pad_h, pad_w, act1, desc2, dense2,
                               bias2, residual, act2, y, stream);
+}
+
+extern "C" int ss_conv2d_pw2_fused_query(const ss_weight_desc *desc1, int32_t N, int32_t H, int32_t Wd, int32_t stride_h, int32_t stride_w,
+                                         int32_t pad_h, int32_t pad_w, const ss_weight_desc *desc2, const ss_weight_desc *desc3, int32_t sparse,
+                                         int32_t *supported, int32_t *pays)
+{
+    int st = ss_conv2d_pw_fused_query(desc1, stride_h, stride_w, pad_h, pad_w, desc2, sparse, supported, pays);
+    if (st != SS_OK || !*supported) return st;
+    if (N <= 0 || H <= 0 || Wd <= 0 || H + 2 * pad_h < desc1->kh || Wd + 2 * pad_w < desc1->kw) return SS_ERR_INVALID_ARG;
+    const int32_t pair_pays = *pays;
+    *supported = 0;
+    *pays = 0;
+    st = check_desc(desc3, sparse != 0);
+    if (st == SS_ERR_INVALID_ARG) return st;
+    if (st != SS_OK || desc3->dtype != desc1->dtype) return SS_OK;
+    if (desc3->kh != 1 || desc3->kw != 1 || desc3->cin != desc2->cout) return SS_ERR_INVALID_ARG;
+    if (!third_fits(desc1, desc2, desc3)) return SS_OK;
+    *supported = 1;
+    // The ResNet-50 trunk at 224 x 224, us, no layer joined / all that can be: batch 1 196 / 191, 4 279 / 262, 8 343 / 320, 32 726 / 677, 64 1115 / 1080.  Not
+    // where it loses: 128 channels on one workgroup per compute unit, where the pair has producer waves (batch 16, 516 without, 528 with those three, 503
+    // with the others), and, beyond the kernels for few pixels, dense layers whose third one has more than 64 channels (batch 64: 1290 / 1301; 1266 with those of 64).
+    const long long P = (long long)N * ((H + 2 * pad_h - desc1->kh) / stride_h + 1) * ((Wd + 2 * pad_w - desc1->kw) / stride_w + 1);
+    const int ncu = planning_units();
+    const bool few = (P + 31) / 32 <= ncu, one_each = desc1->cout > 64 && (P + 63) / 64 <= 256;
+    *pays = pair_pays && (few || (sparse ? !one_each : desc3->cout <= 64));
+    return SS_OK;
+}
+
+extern "C" int ss_conv2d_pw2_fused_fwd(const ss_weight_desc *desc1, const void *x, int32_t N, int32_t H, int32_t Wd,
+                                       const void *packed1, const float *bias1, int32_t stride_h, int32_t stride_w,
+                                       int32_t pad_h, int32_t pad_w, int32_t act1, const ss_weight_desc *desc2,
+                                       const void *packed2, const float *bias2, const void *residual, int32_t act2,
+                                       void *y2, const ss_weight_desc *desc3, const void *packed3, const float *bias3, int32_t act3,
+                                       void *y3, void *stream)
+{
+    if (!desc3) return SS_ERR_INVALID_ARG;
+    return fused_entry<true>(desc1, x, N, H, Wd, packed1, bias1, stride_h, stride_w, pad_h, pad_w, act1, desc2, packed2,
+                             bias2, residual, act2, y2, stream, ThirdLayer{desc3, packed3, bias3, act3, y3});
+}
+
+extern "C" int ss_conv2d_pw2_fused_dense_fwd(const ss_weight_desc *desc1, const void *x, int32_t N, int32_t H, int32_t Wd,
+                                             const void *dense1, const float *bias1, int32_t stride_h, int32_t stride_w,
+                                             int32_t pad_h, int32_t pad_w, int32_t act1, const ss_weight_desc *desc2,
+                                             const void *dense2, const float *bias2, const void *residual, int32_t act2,
+                                             void *y2, const ss_weight_desc *desc3, const void *dense3, const float *bias3, int32_t act3,
+                                             void *y3, void *stream)
+{
+    if (!desc3) return SS_ERR_INVALID_ARG;
+    return fused_entry<false>(desc1, x, N, H, Wd, dense1, bias1, stride_h, stride_w, pad_h, pad_w, act1, desc2, dense2,
+                              bias2, residual, act2, y2, stream, ThirdLayer{desc3, dense3, bias3, act3, y3});
 }

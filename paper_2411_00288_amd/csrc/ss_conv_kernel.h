@@ -349,18 +349,21 @@ constexpr int ring_size(int ksteps, int regs_per_step, int budget)
 constexpr int kFuseRow = 32 + 4;
 constexpr size_t kFuseRegion = 32 * kFuseRow * 4;
 
+// Third contraction: 128 channels of the second one's finished output, [pixel][channel].
+constexpr int kThirdRow = 128 + 8;
+
 template <int BM, int BN, int MODE, int KH, int KW, bool DEEP>
-constexpr size_t smem_body(bool with_residual, int fuse_waves = 0)
+constexpr size_t smem_body(bool with_residual, int fuse_waves = 0, bool third = false)
 {
     using CS = ChunkShape<MODE, KH, KW, DEEP>;
     size_t stage = (size_t)CS::NBUF * BN * CS::ROW * 2;
-    size_t epi = with_residual ? (size_t)BN * (BM + 4) * 4 : (size_t)BN * (BM * 2 + 8) + (size_t)fuse_waves * kFuseRegion;
+    size_t epi = with_residual ? (size_t)BN * (BM + 4) * 4 : (size_t)BN * (BM * 2 + 8) + (size_t)fuse_waves * kFuseRegion + (third ? (size_t)BN * kThirdRow * 2 : 0);
     return stage > epi ? stage : epi;
 }
 template <int BM, int BN, int MODE, int KH, int KW, bool DEEP>
-constexpr size_t smem_bytes(bool with_residual, int fuse_waves = 0)
+constexpr size_t smem_bytes(bool with_residual, int fuse_waves = 0, bool third = false)
 {
-    return smem_body<BM, BN, MODE, KH, KW, DEEP>(with_residual, fuse_waves) + (size_t)BM * 4;
+    return smem_body<BM, BN, MODE, KH, KW, DEEP>(with_residual, fuse_waves, third) + (size_t)BM * 4;
 }
 
 // Waves per SIMD the register allocator must leave room for: small wave tiles are latency-bound
@@ -381,9 +384,11 @@ constexpr int min_waves_per_simd(int tm, int tn, bool big_stage)
 // 16 bit exactly as it would be stored) stays in LDS and is at once the activation operand of a following 1x1
 // convolution, whose output (+ bias + residual, activation) is what the kernel writes: the 3x3 -> 1x1 expansion of a
 // bottleneck without the intermediate tensor's round trip through memory.
+// THIRD: that output is in turn the operand of one more 1x1 convolution, the channel reduction that opens the next bottleneck, which then
+// does not read it back from memory (the number of 32 x 32 tiles of its output per wave; 0: there is none).
 constexpr bool short_args(int mode, bool fuse) { return !fuse && mode != MODE_GATHER && mode != MODE_GATHER4; }      // (the others need more than ConvArgs holds)
 
-template <int DT, bool SPARSE, int WAVES_M, int WAVES_N, int TM, int TN, int MODE, int KH, int KW, bool DEEP, bool SPEC, bool FUSE = false>
+template <int DT, bool SPARSE, int WAVES_M, int WAVES_N, int TM, int TN, int MODE, int KH, int KW, bool DEEP, bool SPEC, bool FUSE = false, int THIRD = 0>
 __global__ __launch_bounds__((WAVES_M * WAVES_N + (SPEC ? 4 : 0)) * 64)
 __attribute__((amdgpu_waves_per_eu(DEEP ? 1 : (((DT == SS_F8 || FUSE) && !SPARSE && MODE == MODE_VEC && TM * TN == 2) ? 3 : min_waves_per_simd(TM, TN, is_taps(MODE) || MODE == MODE_VEC8)))))
 void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, ConvParams>::type args)
@@ -463,7 +468,7 @@ void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, Con
     const bool with_res = !Q8 && !FUSE && p.residual != nullptr;     // uniform (fused: the residual belongs to the second layer)
     float *bias_s = reinterpret_cast<float *>(reinterpret_cast<char *>(smem) +
                                               (with_res ? smem_body<BM, BN, MODE, KH, KW, DEEP>(true)
-                                                        : smem_body<BM, BN, MODE, KH, KW, DEEP>(false, FUSE ? NT / 64 : 0)));
+                                                        : smem_body<BM, BN, MODE, KH, KW, DEEP>(false, FUSE ? NT / 64 : 0, THIRD > 0)));
     // (Loaded after the first activation / weight loads are on their way: issued first, its latency would
     // sit in front of everything else.)
     float *scale_s = bias_s + BM;                     // (8-bit operands only)
@@ -972,6 +977,157 @@ void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, Con
             if (p.act == SS_ACT_GELU) to_lds(gelu); else to_lds(relu_or_id);
         }
         __syncthreads();
+        if constexpr (THIRD > 0) {
+            // ---- second and third contraction, 128 channels of the second one's output at a time: each wave finishes one row tile of 32
+            // (stored as in the pair below, and left in LDS), then multiplies the third one's weights with the 128 channels; its
+            // accumulators stay in registers.  The weights and the residual of the next 128 are in flight meanwhile.
+            static_assert(!SPEC && NT == 256 && BN == 64, "four waves, 64 pixels");
+            constexpr int KS2 = BM / 32, ITEMS3 = THIRD;  // steps of the second reduction at most; 32 x 32 tiles of the third output per wave
+            uint16_t *const Ts = reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(smem) + (size_t)BN * (BM * 2 + 8) + (NT / 64) * kFuseRegion);
+            float *const reg = reinterpret_cast<float *>(reinterpret_cast<char *>(smem) + (size_t)BN * (BM * 2 + 8)) + wave * (32 * kFuseRow);
+            auto buffer = [](const void *base, unsigned bytes) {
+                return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, base != nullptr ? (int)bytes : 0, kRsrcFlags);
+            };
+            const __amdgpu_buffer_rsrc_t ra2 = buffer(p.a2_vals, p.a2_bytes), rm2 = buffer(p.a2_meta, p.meta2_bytes);
+            const __amdgpu_buffer_rsrc_t ra3 = buffer(p.a3_vals, p.a3_bytes), rm3 = buffer(p.a3_meta, p.meta3_bytes);
+            const __amdgpu_buffer_rsrc_t rb2 = buffer(p.bias2, (unsigned)p.Cout2 * 4u), rb3 = buffer(p.bias3, (unsigned)p.Cout3 * 4u);
+            // outputs and residual of this workgroup's pixels: whatever lies behind the last one is out of range
+            const unsigned px_here = (unsigned)min(BN, p.P - n0), row2 = (unsigned)p.Cout2 * 2u, row3 = (unsigned)p.Cout3 * 2u;
+            const __amdgpu_buffer_rsrc_t rres = buffer(p.res2 != nullptr ? p.res2 + (size_t)n0 * p.Cout2 : nullptr, px_here * row2);
+            const __amdgpu_buffer_rsrc_t ry2 = buffer(p.y2 + (size_t)n0 * p.Cout2, px_here * row2), ry3 = buffer(p.y3 + (size_t)n0 * p.Cout3, px_here * row3);
+            const int l = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), g = l >> 5, c = l & 31;
+            struct Rows {
+                u32x4 v[SPARSE ? 1 : 2][4];
+                uint32_t idx[4];
+            };
+            auto load_steps = [&](Rows &r, const __amdgpu_buffer_rsrc_t &rv, const __amdgpu_buffer_rsrc_t &ri, int mt, int Ks, int Kp, int ks0, int n) {
+#pragma unroll
+                for (int s = 0; s < 4; s++) {
+                    if (s >= n) break;                    // uniform
+                    const int ks = ks0 + s;
+                    if constexpr (SPARSE) {
+                        r.v[0][s] = __builtin_amdgcn_raw_buffer_load_b128(rv, l * 16, (mt * Ks + ks) * 1024, 0);
+                        r.idx[s] = __builtin_amdgcn_raw_buffer_load_b32(ri, l * 4, (mt * Kp + (ks >> 1)) * 256, 0);
+                    } else {
+                        r.v[0][s] = __builtin_amdgcn_raw_buffer_load_b128(rv, l * 16, (mt * Ks + ks) * 2048, 0);
+                        r.v[1][s] = __builtin_amdgcn_raw_buffer_load_b128(rv, l * 16, (mt * Ks + ks) * 2048 + 1024, 0);
+                    }
+                }
+            };
+            auto mma = [&](const Rows &r, int s, const B32 &b, f32x16 d) {
+                if constexpr (SPARSE) return mma_sparse<DT>(r.v[0][s], b, d, r.idx[s] >> ((s & 1) * 16));
+                else return mma_dense<DT>(r.v[1][s], b.hi, mma_dense<DT>(r.v[0][s], b.lo, d));
+            };
+            auto start = [&](const __amdgpu_buffer_rsrc_t &rb, int row) {      // the bias starts in the accumulators
+                f32x16 d;
+#pragma unroll
+                for (int q = 0; q < 4; q++) {
+                    const f32x4 b = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rb, g * 16, (row + 8 * q) * 4, 0));
+#pragma unroll
+                    for (int e = 0; e < 4; e++) d[4 * q + e] = b[e];
+                }
+                return d;
+            };
+            // a lane's 16-byte run number j of a 32 x 32 tile at pixel half tn: pixel and run of 8 channels
+            auto run_px = [&](int tn, int j) { return tn * 32 + 16 * j + (l >> 2); };
+            const int half3 = wave & 1;                   // tile i of this wave: row tile (wave >> 1) + 2 i on pixel half wave & 1
+            auto row3_of = [&](int i) { return min((wave >> 1) + 2 * i, p.Mt3 - 1); };
+            f32x16 acc3[ITEMS3];
+#pragma unroll
+            for (int i = 0; i < ITEMS3; i++) acc3[i] = start(rb3, row3_of(i) * 32);
+            Rows w2, w3[ITEMS3];
+            u32x4 res[2][2];
+            load_steps(w2, ra2, rm2, wave, p.Ks2, p.Kp2, 0, p.Ks2);
+            const float floor2 = p.act2 == SS_ACT_RELU ? 0.f : -__builtin_inff(), floor3 = p.act3 == SS_ACT_RELU ? 0.f : -__builtin_inff();
+            auto put = [&](const f32x16 &d) {
+#pragma unroll
+                for (int q = 0; q < 4; q++) *reinterpret_cast<f32x4 *>(reg + c * kFuseRow + 8 * q + 4 * g) = f32x4{d[4 * q], d[4 * q + 1], d[4 * q + 2], d[4 * q + 3]};
+            };
+            auto get = [&](int j, float (&v)[8]) {        // (a wave's LDS operations execute in order: it sees what put left)
+                const float *src = reg + (16 * j + (l >> 2)) * kFuseRow + (l & 3) * 8;
+                const f32x4 lo = *reinterpret_cast<const f32x4 *>(src), hi = *reinterpret_cast<const f32x4 *>(src + 4);
+#pragma unroll
+                for (int e = 0; e < 4; e++) { v[e] = lo[e]; v[4 + e] = hi[e]; }
+            };
+            auto finish = [&](float (&v)[8], int act, float floor) {
+                if (act == SS_ACT_GELU) {
+#pragma unroll
+                    for (int e = 0; e < 8; e++) v[e] = gelu(v[e]);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; e++) v[e] = floor_at(v[e], floor);
+                }
+                return u32x4{cvt_pack2<ODT>(v[0], v[1]), cvt_pack2<ODT>(v[2], v[3]), cvt_pack2<ODT>(v[4], v[5]), cvt_pack2<ODT>(v[6], v[7])};
+            };
+            const int nparts = p.Cout2 / 128;
+            for (int part = 0; part < nparts; part++) {
+                const int mt = part * 4 + wave;
+#pragma unroll
+                for (int tn = 0; tn < 2; tn++)
+#pragma unroll
+                    for (int j = 0; j < 2; j++)
+                        res[tn][j] = __builtin_amdgcn_raw_buffer_load_b128(rres, (int)(run_px(tn, j) * row2 + (l & 3) * 16), mt * 64, 0);
+                f32x16 acc2[2];
+                acc2[0] = acc2[1] = start(rb2, mt * 32);
+#pragma unroll
+                for (int i = 0; i < ITEMS3; i++) load_steps(w3[i], ra3, rm3, row3_of(i), p.Ks3, p.Kp3, part * 4, 4);
+#pragma unroll
+                for (int s = 0; s < KS2; s++) {
+                    if (s >= p.Ks2) break;                // uniform
+#pragma unroll
+                    for (int tn = 0; tn < 2; tn++) {
+                        const uint16_t *src = Cs + (tn * 32 + c) * CROW + 32 * s + 16 * g;      // 8-byte aligned
+                        const uint2 u0 = *reinterpret_cast<const uint2 *>(src), u1 = *reinterpret_cast<const uint2 *>(src + 4);
+                        const uint2 u2 = *reinterpret_cast<const uint2 *>(src + 8), u3 = *reinterpret_cast<const uint2 *>(src + 12);
+                        B32 b;
+                        b.lo = u32x4{u0.x, u0.y, u1.x, u1.y};
+                        b.hi = u32x4{u2.x, u2.y, u3.x, u3.y};
+                        acc2[tn] = mma(w2, s, b, acc2[tn]);
+                    }
+                }
+                load_steps(w2, ra2, rm2, min(mt + 4, p.Mt2 - 1), p.Ks2, p.Kp2, 0, p.Ks2);
+#pragma unroll
+                for (int tn = 0; tn < 2; tn++) {
+                    put(acc2[tn]);
+#pragma unroll
+                    for (int j = 0; j < 2; j++) {
+                        float v[8];
+                        get(j, v);
+#pragma unroll
+                        for (int e = 0; e < 4; e++) {
+                            v[2 * e] += widen<ODT>((uint16_t)(res[tn][j][e] & 0xFFFFu));
+                            v[2 * e + 1] += widen<ODT>((uint16_t)(res[tn][j][e] >> 16));
+                        }
+                        const u32x4 w = finish(v, p.act2, floor2);
+                        *reinterpret_cast<u32x4 *>(Ts + run_px(tn, j) * kThirdRow + wave * 32 + (l & 3) * 8) = w;
+                        __builtin_amdgcn_raw_buffer_store_b128(w, ry2, (int)(run_px(tn, j) * row2 + (l & 3) * 16), mt * 64, 0);
+                    }
+                }
+                lds_barrier();
+#pragma unroll
+                for (int s = 0; s < 4; s++) {
+                    const uint16_t *src = Ts + (half3 * 32 + c) * kThirdRow + 32 * s + 16 * g;
+                    B32 b;
+                    b.lo = *reinterpret_cast<const u32x4 *>(src);
+                    b.hi = *reinterpret_cast<const u32x4 *>(src + 8);
+#pragma unroll
+                    for (int i = 0; i < ITEMS3; i++) acc3[i] = mma(w3[i], s, b, acc3[i]);
+                }
+                lds_barrier();                            // the next 128 channels may take their place
+            }
+#pragma unroll
+            for (int i = 0; i < ITEMS3; i++) {
+                if ((wave >> 1) + 2 * i >= p.Mt3) break;  // uniform
+                put(acc3[i]);
+#pragma unroll
+                for (int j = 0; j < 2; j++) {
+                    float v[8];
+                    get(j, v);
+                    __builtin_amdgcn_raw_buffer_store_b128(finish(v, p.act3, floor3), ry3, (int)(run_px(half3, j) * row3 + (l & 3) * 16), ((wave >> 1) + 2 * i) * 64, 0);
+                }
+            }
+            return;
+        }
         if constexpr (FUSE) {
             // ---- second contraction: y2[pixel, o2] = act2( sum_c A2[o2, c] * tile[pixel, c] + bias2[o2] + residual[pixel, o2] )
             // Every wave (producers included) takes row tiles of 32 output channels in turn; its weights and bias for
@@ -1678,13 +1834,13 @@ static int launch_mlp(const MlpParams &p, hipStream_t s)
 // ---------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------
-template <int DT, bool SPARSE, int WAVES_M, int WAVES_N, int TM, int TN, int MODE, int KH, int KW, bool DEEP = false, bool SPEC = false, bool FUSE = false>
+template <int DT, bool SPARSE, int WAVES_M, int WAVES_N, int TM, int TN, int MODE, int KH, int KW, bool DEEP = false, bool SPEC = false, bool FUSE = false, int THIRD = 0>
 static int launch(const ConvParams &p0, hipStream_t s)
 {
     constexpr int BM = WAVES_M * TM * 32, BN = WAVES_N * TN * 32;
     constexpr int NWAVES = WAVES_M * WAVES_N + (SPEC ? 4 : 0);
     constexpr size_t scale_bytes = is_byte_type(DT) ? (size_t)BM * 4 : 0;      // the per-channel scales sit behind the bias values
-    constexpr size_t smem_plain = smem_bytes<BM, BN, MODE, KH, KW, DEEP>(false, FUSE ? NWAVES : 0) + scale_bytes;
+    constexpr size_t smem_plain = smem_bytes<BM, BN, MODE, KH, KW, DEEP>(false, FUSE ? NWAVES : 0, THIRD > 0) + scale_bytes;
     constexpr size_t smem_res = (is_byte_type(DT) || FUSE) ? smem_plain : smem_bytes<BM, BN, MODE, KH, KW, DEEP>(true);
     static_assert(smem_plain <= 160 * 1024 && smem_res <= 160 * 1024, "LDS tile too large");
     const size_t smem = (p0.residual && !FUSE) ? smem_res : smem_plain;
@@ -1701,7 +1857,7 @@ static int launch(const ConvParams &p0, hipStream_t s)
         blocks *= p.nsplit;
     }
     if (blocks <= 0 || blocks > 0x7FFFFFFFll) return SS_ERR_UNSUPPORTED;
-    auto kern = conv_kernel<DT, SPARSE, WAVES_M, WAVES_N, TM, TN, MODE, KH, KW, DEEP, SPEC, FUSE>;
+    auto kern = conv_kernel<DT, SPARSE, WAVES_M, WAVES_N, TM, TN, MODE, KH, KW, DEEP, SPEC, FUSE, THIRD>;
     if (smem_res > 64 * 1024) {
         // Raises this kernel's dynamic-LDS limit, once per device (the attribute belongs to the device's copy of the
         // kernel).  Two threads racing here both set it: harmless.
@@ -1862,9 +2018,21 @@ static inline int choose_fused_tile(const ConvParams &p)
     return n_blocks(p, 256, 64) <= 256 ? 5 : 3;
 }
 
+// With a third contraction: the paper's flattening, tiles of 64 or 128 rows without producer waves.
+template <int DT, bool SPARSE>
+static int third_mode(const ss_weight_desc *d1, const ConvParams &p, hipStream_t s)
+{
+    if (d1->korder != SS_K_CRS || d1->kh != 3 || d1->kw != 3 || d1->cin % 32 != 0) return SS_ERR_UNSUPPORTED;
+    if (p.Cout > 128 || p.Cout3 > 128) return SS_ERR_UNSUPPORTED;
+    if (p.Cout > 64) return launch<DT, SPARSE, 4, 1, 1, 2, MODE_TAPS, 3, 3, false, false, true, 2>(p, s);
+    return p.Cout3 <= 64 ? launch<DT, SPARSE, 2, 2, 1, 1, MODE_TAPS, 3, 3, false, false, true, 1>(p, s)
+                         : launch<DT, SPARSE, 2, 2, 1, 1, MODE_TAPS, 3, 3, false, false, true, 2>(p, s);
+}
+
 template <int DT, bool SPARSE>
 static int fused_mode(const ss_weight_desc *d1, const ConvParams &p, hipStream_t s)
 {
+    if (p.Cout3 > 0) return third_mode<DT, SPARSE>(d1, p, s);
     auto run = [&](int id) {
         if (d1->korder == SS_K_CRS && d1->kh == 3 && d1->kw == 3 && d1->cin % 32 == 0)
             return launch_fused_tile<DT, SPARSE, MODE_TAPS, 3, 3>(id, p, s);

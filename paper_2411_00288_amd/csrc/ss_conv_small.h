@@ -455,24 +455,29 @@ static int small_mode(const ss_weight_desc *desc, const ConvParams &p, int varia
 // ---------------------------------------------------------------------------------------------
 constexpr int kPairWaves = 8;
 struct PairShape {                    // LDS map of a workgroup, in bytes
-    size_t stage, part, tile, total;  // [0, stage): staging, later the output slabs; then partial sums; then the 16-bit tile
-};
-static inline __host__ __device__ PairShape pair_shape(int px, int nchunks, int cout1)
+    size_t stage, part, tile, third, total;  // [0, stage): staging, later the output slabs; then partial sums; then the 16-bit tile; the second layer's
+};                                           // output where a third one follows; then the first layer's bias
+static inline __host__ __device__ PairShape pair_shape(int px, int nchunks, int cout1, int cout2)      // cout2: 0 without a third layer
 {
     PairShape h;
     h.stage = (size_t)nchunks * px * 576;
     const size_t slabs = (size_t)kPairWaves * px * kFuseRow * 4;
     if (h.stage < slabs) h.stage = slabs;
     h.part = (size_t)kPairWaves * 4096;
-    h.tile = (size_t)px * (cout1 + 4) * 2;
-    h.total = h.stage + h.part + h.tile + (size_t)cout1 * 4;      // ... then the first layer's bias
+    h.tile = (size_t)px * (cout1 + 8) * 2;
+    h.third = cout2 > 0 ? (size_t)px * (cout2 + 8) * 2 : 0;
+    h.total = h.stage + h.part + h.tile + h.third + (size_t)cout1 * 4;
     return h;
 }
 
-template <int DT, bool SPARSE, int PX>
+// THIRD: as in conv_kernel.  The second layer's output stays in LDS as well; the waves split the third one's rows and reduction as they do the first one's.
+// MT: the first layer's row tiles (2 or 4: a bottleneck of 64 or 128 channels), or 0 where they are known at run time only.  Known, the
+// waves' shares and the loops over them are constants, and every LDS read of a phase is under way before the first is needed.
+template <int DT, bool SPARSE, int PX, int MT, bool THIRD>
 __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams p)
 {
-    constexpr int TAPS = 9, VPR = 36, NT = kPairWaves * 64, RING = 9, KS2 = 8;
+    if constexpr (MT > 0) { p.Mt = p.Ks2 = MT; p.Cout = 32 * MT; }
+    constexpr int TAPS = 9, VPR = 36, NT = kPairWaves * 64, RING = 9, KS2 = MT > 0 ? MT : 8;
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -481,12 +486,14 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
     const int n0 = blockIdx.x * PX;
     const int HoWo = p.Ho * p.Wo;
     const int nchunks = (int)((unsigned)p.Ks / TAPS);     // cin % 32 == 0
-    const PairShape sh = pair_shape(PX, nchunks, p.Cout);
+    const PairShape sh = pair_shape(PX, nchunks, p.Cout, THIRD ? p.Cout2 : 0);
     u32x4 *const stage = reinterpret_cast<u32x4 *>(smem);
     u32x4 *const part = reinterpret_cast<u32x4 *>(reinterpret_cast<char *>(smem) + sh.stage);
     uint16_t *const tile = reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(smem) + sh.stage + sh.part);
-    const int TROW = p.Cout + 4;                          // 16-bit units per pixel row of the tile
-    float *const bias1 = reinterpret_cast<float *>(reinterpret_cast<char *>(smem) + sh.stage + sh.part + sh.tile);
+    const int TROW = p.Cout + 8;                          // 16-bit units per pixel row of the tile
+    uint16_t *const out2 = reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(smem) + sh.stage + sh.part + sh.tile);
+    const int T2ROW = p.Cout2 + 8;
+    float *const bias1 = reinterpret_cast<float *>(reinterpret_cast<char *>(smem) + sh.stage + sh.part + sh.tile + sh.third);
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.x), 0, (int)p.x_bytes, kRsrcFlags);
     const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.a_vals), 0, (int)p.a_bytes, kRsrcFlags);
     const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.a_meta), 0, (int)p.meta_bytes, kRsrcFlags);
@@ -496,7 +503,7 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
     // ---- first layer: this wave's row tile and share of the reduction steps
     // (a division by a runtime number is some 25 instructions ahead of the first load: 8 / Mt is a power of two, the other comes as a product)
     const int lg = p.Mt == 1 ? 3 : p.Mt == 2 ? 2 : p.Mt <= 4 ? 1 : 0, groups = 1 << lg;      // waves per row tile (Mt <= 8)
-    const int kg = fast_div(wave, p.tm_mul, p.tm_sh), rt = wave - kg * p.Mt;
+    const int kg = MT > 0 ? wave / MT : fast_div(wave, p.tm_mul, p.tm_sh), rt = wave - kg * p.Mt;
     const bool works = kg < groups;
     const int s0 = works ? kg * p.Ks >> lg : 0, s1 = works ? (kg + 1) * p.Ks >> lg : 0;
     using A = AStep<SPARSE, 1>;
@@ -614,10 +621,16 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
     for (int t = tid; t < PX * 8 * p.Mt; t += NT) {       // quads of channels, pixel fastest: (row tile, quad, pixel)
         const int pl = t & (PX - 1), q = t / PX, m = q >> 3, cq = q & 7;
         float v[4] = {0.f, 0.f, 0.f, 0.f};
-        for (int k = 0; k < groups; k++) {
+        auto add = [&](int k) {
             const f32x4 u = __builtin_bit_cast(f32x4, part[(k * p.Mt + m) * 256 + (cq >> 1) * 64 + (cq & 1) * 32 + pl]);
 #pragma unroll
             for (int e = 0; e < 4; e++) v[e] += u[e];
+        };
+        if constexpr (MT > 0) {
+#pragma unroll
+            for (int k = 0; k < kPairWaves / MT; k++) add(k);
+        } else {
+            for (int k = 0; k < groups; k++) add(k);
         }
         const int o = m * 32 + cq * 4;
 #pragma unroll
@@ -634,6 +647,36 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
         *reinterpret_cast<uint2 *>(tile + pl * TROW + o) = make_uint2(cvt_pack2<DT>(v[0], v[1]), cvt_pack2<DT>(v[2], v[3]));
     }
     lds_barrier();
+    // ---- the third layer's weights: in flight while the second one is multiplied
+    constexpr int KS3 = THIRD ? 8 : 1;
+    const int lg3 = THIRD ? (p.Mt3 == 2 ? 2 : 1) : 0;     // (2 <= Mt3 <= 4, Ks3 <= 16: eight steps per wave at most)
+    const int kg3 = THIRD ? (p.Mt3 == 2 ? wave >> 1 : p.Mt3 == 3 ? wave * 11 >> 5 : wave >> 2) : 0, rt3 = wave - kg3 * p.Mt3;
+    const bool works3 = THIRD && kg3 < 1 << lg3;
+    const int t0 = works3 ? kg3 * p.Ks3 >> lg3 : 0, t1 = works3 ? (kg3 + 1) * p.Ks3 >> lg3 : 0;
+    A a3[KS3];
+    if constexpr (THIRD) {
+        const __amdgpu_buffer_rsrc_t ra3 = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.a3_vals), 0, (int)p.a3_bytes, kRsrcFlags);
+        const __amdgpu_buffer_rsrc_t rm3 = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.a3_meta), 0, (int)p.meta3_bytes, kRsrcFlags);
+#pragma unroll
+        for (int j = 0; j < KS3; j++)
+            if (t0 + j < t1) load_w(a3[j], ra3, rm3, rt3, p.Ks3, p.Kp3, t0 + j);      // uniform
+    }
+    // ... and the bias of the quads of channels that this thread will finish
+    constexpr int Q3 = THIRD ? PX * 32 / NT : 1;          // (at most four row tiles)
+    f32x4 bias3[Q3];
+    auto quad3 = [&](int i, int *pl) {                    // quad of channels, the fastest; pixel
+        const int t = tid + i * NT, n = p.Mt3 * 8;
+        *pl = p.Mt3 == 4 ? t >> 5 : p.Mt3 == 2 ? t >> 4 : t * 2731 >> 16;      // (2731 = ceil(2^16 / 24), exact below 2^12)
+        return t - *pl * n;
+    };
+    if constexpr (THIRD) {
+        const __amdgpu_buffer_rsrc_t rb3 = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.bias3), 0, p.bias3 != nullptr ? p.Cout3 * 4 : 0, kRsrcFlags);
+#pragma unroll
+        for (int i = 0; i < Q3; i++) {
+            int pl;
+            bias3[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rb3, quad3(i, &pl) * 16, 0, 0));
+        }
+    }
     // ---- second layer
     const float floor2 = p.act2 == SS_ACT_RELU ? 0.f : -__builtin_inff();
     float *const slab = reinterpret_cast<float *>(smem) + wave * (PX * kFuseRow);
@@ -643,16 +686,22 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
         f32x16 acc2;
 #pragma unroll
         for (int v = 0; v < 16; v++) acc2[v] = 0.f;
+        auto fragment = [&](int s) {
+            const uint16_t *src = tile + cc * TROW + 32 * s + 16 * g;
+            return B32{*reinterpret_cast<const u32x4 *>(src), *reinterpret_cast<const u32x4 *>(src + 8)};
+        };
+        if constexpr (MT > 0) {
+            B32 b[KS2];
 #pragma unroll
-        for (int s = 0; s < KS2; s++) {
-            if (s >= p.Ks2) break;                        // uniform
-            const uint16_t *src = tile + cc * TROW + 32 * s + 16 * g;      // 8-byte aligned
-            const uint2 u0 = *reinterpret_cast<const uint2 *>(src), u1 = *reinterpret_cast<const uint2 *>(src + 4);
-            const uint2 u2 = *reinterpret_cast<const uint2 *>(src + 8), u3 = *reinterpret_cast<const uint2 *>(src + 12);
-            B32 b;
-            b.lo = u32x4{u0.x, u0.y, u1.x, u1.y};
-            b.hi = u32x4{u2.x, u2.y, u3.x, u3.y};
-            acc2 = mma(r2.a[s], b, acc2, s);
+            for (int s = 0; s < KS2; s++) b[s] = fragment(s);
+#pragma unroll
+            for (int s = 0; s < KS2; s++) acc2 = mma(r2.a[s], b[s], acc2, s);
+        } else {
+#pragma unroll
+            for (int s = 0; s < KS2; s++) {
+                if (s >= p.Ks2) break;                    // uniform
+                acc2 = mma(r2.a[s], fragment(s), acc2, s);
+            }
         }
         if (PX == 32 || c < PX) {
 #pragma unroll
@@ -685,17 +734,71 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
 #pragma unroll
             for (int e = 0; e < 4; e++) w[e] = cvt_pack2<DT>(v[2 * e], v[2 * e + 1]);
             *reinterpret_cast<uint4 *>(p.y2 + (size_t)pg * p.Cout2 + mt * 32 + run * 8) = make_uint4(w[0], w[1], w[2], w[3]);
+            if constexpr (THIRD) *reinterpret_cast<uint4 *>(out2 + px * T2ROW + mt * 32 + run * 8) = make_uint4(w[0], w[1], w[2], w[3]);
         }
         __builtin_amdgcn_wave_barrier();
     }
+    if constexpr (THIRD) {
+        // ---- third layer (pixels behind the last one hold whatever LDS held: their columns are not stored)
+        lds_barrier();
+        f32x16 acc3;
+#pragma unroll
+        for (int v = 0; v < 16; v++) acc3[v] = 0.f;
+        B32 b3[KS3];
+#pragma unroll
+        for (int j = 0; j < KS3; j++) {                   // (all on their way first; a step past the share's end is read and not used)
+            const uint16_t *src = out2 + cc * T2ROW + 32 * min(t0 + j, p.Ks3 - 1) + 16 * g;
+            b3[j].lo = *reinterpret_cast<const u32x4 *>(src);
+            b3[j].hi = *reinterpret_cast<const u32x4 *>(src + 8);
+        }
+#pragma unroll
+        for (int j = 0; j < KS3; j++)
+            if (t0 + j < t1) acc3 = mma(a3[j], b3[j], acc3, t0 + j);      // uniform
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const f32x4 w = {acc3[4 * q], acc3[4 * q + 1], acc3[4 * q + 2], acc3[4 * q + 3]};
+            part[wave * 256 + q * 64 + lane] = __builtin_bit_cast(u32x4, w);
+        }
+        lds_barrier();
+        const float floor3 = p.act3 == SS_ACT_RELU ? 0.f : -__builtin_inff();
+#pragma unroll
+        for (int i = 0; i < Q3; i++) {
+            int pl;
+            const int q = quad3(i, &pl), m = q >> 3, cq = q & 7, o = q * 4;
+            if (pl >= PX) break;                          // (fewer than four row tiles)
+            float v[4] = {0.f, 0.f, 0.f, 0.f};
+            auto add = [&](int k) {
+                const f32x4 u = __builtin_bit_cast(f32x4, part[(k * p.Mt3 + m) * 256 + (cq >> 1) * 64 + (cq & 1) * 32 + pl]);
+#pragma unroll
+                for (int e = 0; e < 4; e++) v[e] += u[e];
+            };
+            add(0);
+            add(1);
+            if (lg3 == 2) {                               // uniform
+                add(2);
+                add(3);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; e++) v[e] += bias3[i][e];
+            if (p.act3 == SS_ACT_GELU) {
+#pragma unroll
+                for (int e = 0; e < 4; e++) v[e] = gelu_cdf<DT>(v[e]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; e++) v[e] = floor_at(v[e], floor3);
+            }
+            if (n0 + pl < p.P)
+                *reinterpret_cast<uint2 *>(p.y3 + (size_t)(n0 + pl) * p.Cout3 + o) = make_uint2(cvt_pack2<DT>(v[0], v[1]), cvt_pack2<DT>(v[2], v[3]));
+        }
+    }
 }
 
-template <int DT, bool SPARSE, int PX>
+template <int DT, bool SPARSE, int PX, int MT, bool THIRD>
 static int launch_pair_small(ConvParams p, hipStream_t s)
 {
     fast_div_setup((unsigned)p.Mt, &p.tm_mul, &p.tm_sh);      // (the kernel deals its waves out over the row tiles)
-    const size_t smem = pair_shape(PX, p.Ks / 9, p.Cout).total;
-    auto kern = pair_small_kernel<DT, SPARSE, PX>;
+    const size_t smem = pair_shape(PX, p.Ks / 9, p.Cout, THIRD ? p.Cout2 : 0).total;
+    auto kern = pair_small_kernel<DT, SPARSE, PX, MT, THIRD>;
     if (smem > 64 * 1024) {
         static std::atomic<unsigned long long> done_mask{0};      // as in launch(): once per device
         int dev = 0;
@@ -722,8 +825,17 @@ static int pair_small(const ss_weight_desc *d1, const ConvParams &p, int px, hip
         if (ncu <= 0) return SS_ERR_HIP;
         px = ((long long)p.P + 15) / 16 <= ncu ? 16 : (((long long)p.P + 31) / 32 <= ncu ? 32 : 0);
     }
-    if (px == 0 || pair_shape(px, p.Ks / 9, p.Cout).total > 160 * 1024) return SS_ERR_INVALID_ARG;
-    return px == 16 ? launch_pair_small<DT, SPARSE, 16>(p, s) : launch_pair_small<DT, SPARSE, 32>(p, s);
+    const bool third = p.Cout3 > 0;
+    if (px == 0 || pair_shape(px, p.Ks / 9, p.Cout, third ? p.Cout2 : 0).total > 160 * 1024) return SS_ERR_INVALID_ARG;
+    if (third && (p.Mt3 < 2 || p.Mt3 > 4 || p.Ks3 > 16)) return SS_ERR_INVALID_ARG;
+    auto go = [&](auto mt) -> int {
+        constexpr int MT = decltype(mt)::value;
+        if constexpr (MT > 0)
+            if (third) return px == 16 ? launch_pair_small<DT, SPARSE, 16, MT, true>(p, s) : launch_pair_small<DT, SPARSE, 32, MT, true>(p, s);
+        return third ? (int)SS_ERR_INVALID_ARG : px == 16 ? launch_pair_small<DT, SPARSE, 16, MT, false>(p, s) : launch_pair_small<DT, SPARSE, 32, MT, false>(p, s);
+    };
+    using std::integral_constant;
+    return p.Mt == 2 ? go(integral_constant<int, 2>{}) : p.Mt == 4 ? go(integral_constant<int, 4>{}) : go(integral_constant<int, 0>{});
 }
 
 }  // namespace ss

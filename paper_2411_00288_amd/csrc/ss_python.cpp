@@ -422,8 +422,12 @@ struct Launch {
     vectorcallfunc vectorcall;
     PyObject *keep;            // everything the addresses below belong to
     PyObject *on_error;        // called with the status of a call that failed
-    int kind;                  // ConvKind, or 4 / 5: fused pair (sparse / dense), 6: max pooling
-    ss_weight_desc d1, d2;
+    int kind;                  // ConvKind, or 4 / 5: fused pair (sparse / dense), 6: max pooling, 7 / 8: fused pair and a third layer
+    ss_weight_desc d1, d2, d3;
+    const void *w3;
+    const float *b3;
+    void *y3;
+    int32_t act3;
     const void *x, *w1, *w2, *residual;
     const float *scale, *b1, *b2;
     void *y, *ws;
@@ -447,6 +451,11 @@ PyObject *launch_call(PyObject *self, PyObject *const *, size_t, PyObject *)
             return call_conv(l->kind, &l->d1, l->x, l->nhw, l->w1, l->scale, l->b1, l->residual, l->sp, l->act1, l->y, l->ws, l->ws_bytes, s);
         if (l->kind == 6)
             return ss_maxpool2d(l->x, l->nhw[0], l->nhw[1], l->nhw[2], l->pool[0], l->pool[1], l->pool[2], l->sp[0], l->sp[2], l->y, s);
+        if (l->kind >= 7) {
+            const auto fn = l->kind == 7 ? ss_conv2d_pw2_fused_fwd : ss_conv2d_pw2_fused_dense_fwd;
+            return fn(&l->d1, l->x, l->nhw[0], l->nhw[1], l->nhw[2], l->w1, l->b1, l->sp[0], l->sp[1], l->sp[2], l->sp[3], l->act1, &l->d2,
+                      l->w2, l->b2, l->residual, l->act2, l->y, &l->d3, l->w3, l->b3, l->act3, l->y3, s);
+        }
         const auto fn = l->kind == 4 ? ss_conv2d_pw_fused_fwd : ss_conv2d_pw_fused_dense_fwd;
         return fn(&l->d1, l->x, l->nhw[0], l->nhw[1], l->nhw[2], l->w1, l->b1, l->sp[0], l->sp[1], l->sp[2], l->sp[3], l->act1, &l->d2,
                   l->w2, l->b2, l->residual, l->act2, l->y, s);
@@ -489,16 +498,16 @@ bool address(PyObject *o, void **p)      // an int, or None for NULL
 }
 
 // launch(kind, desc1, desc2 | None, (x, w1, w2, scale, b1, b2, residual, y, ws) addresses, ws_bytes,
-//        (N, H, W), (sh, sw, ph, pw), act1, act2, (C, dtype, k) | None, keep, on_error) -> callable
+//        (N, H, W), (sh, sw, ph, pw), act1, act2, (C, dtype, k) | None, (desc3, w3, b3, act3, y3) | None, keep, on_error) -> callable
 PyObject *launch(PyObject *, PyObject *args)
 {
     int kind, act1, act2, nhw[3], sp[4], pool3[3] = {0, 0, 0};
-    PyObject *d1, *d2, *ptrs, *poolo, *keep, *on_error;
+    PyObject *d1, *d2, *ptrs, *poolo, *third, *keep, *on_error;
     Py_ssize_t ws_bytes;
-    if (!PyArg_ParseTuple(args, "iOOO!n(iii)(iiii)iiOOO", &kind, &d1, &d2, &PyTuple_Type, &ptrs, &ws_bytes, &nhw[0], &nhw[1], &nhw[2],
-                          &sp[0], &sp[1], &sp[2], &sp[3], &act1, &act2, &poolo, &keep, &on_error))
+    if (!PyArg_ParseTuple(args, "iOOO!n(iii)(iiii)iiOOOO", &kind, &d1, &d2, &PyTuple_Type, &ptrs, &ws_bytes, &nhw[0], &nhw[1], &nhw[2],
+                          &sp[0], &sp[1], &sp[2], &sp[3], &act1, &act2, &poolo, &third, &keep, &on_error))
         return nullptr;
-    if (kind < 0 || kind > 6 || PyTuple_GET_SIZE(ptrs) != 9) {
+    if (kind < 0 || kind > 8 || (kind >= 7) != (third != Py_None) || PyTuple_GET_SIZE(ptrs) != 9) {
         PyErr_SetString(PyExc_ValueError, "launch: bad kind or address list");
         return nullptr;
     }
@@ -511,6 +520,17 @@ PyObject *launch(PyObject *, PyObject *args)
     void *p[9];
     for (int i = 0; i < 9; i++)
         if (!address(PyTuple_GET_ITEM(ptrs, i), &p[i])) return nullptr;
+    ss_weight_desc last{};
+    void *w3 = nullptr, *b3 = nullptr, *y3 = nullptr;
+    int act3 = 0;
+    if (third != Py_None) {
+        PyObject *d3, *pw, *pb, *py;
+        if (!PyArg_ParseTuple(third, "OOOiO", &d3, &pw, &pb, &act3, &py) || !address(pw, &w3) || !address(pb, &b3) || !address(py, &y3)) return nullptr;
+        if (!read_desc(d3, &last)) {
+            PyErr_SetString(PyExc_ValueError, "launch: bad descriptor");
+            return nullptr;
+        }
+    }
     PyObject *o = LaunchType.tp_alloc(&LaunchType, 0);
     if (!o) return nullptr;
     Launch *l = reinterpret_cast<Launch *>(o);
@@ -522,6 +542,11 @@ PyObject *launch(PyObject *, PyObject *args)
     l->kind = kind;
     l->d1 = w1;
     l->d2 = w2;
+    l->d3 = last;
+    l->w3 = w3;
+    l->b3 = static_cast<const float *>(b3);
+    l->y3 = y3;
+    l->act3 = act3;
     l->x = p[0]; l->w1 = p[1]; l->w2 = p[2];
     l->scale = static_cast<const float *>(p[3]);
     l->b1 = static_cast<const float *>(p[4]);

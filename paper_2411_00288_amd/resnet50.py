@@ -75,7 +75,7 @@ class Trunk:
     def __init__(self, batch: int, image: int = 224, dtype: int = wl.BF16, sparse: bool = True, seed: int = 7000,
                  c3_scale: float = 0.25, keep_host: bool = False, image_channels: int = 4, fuse_pairs: bool = True):
         """fuse_pairs: run a block's 3x3 and the 1x1 expansion after it as one kernel where that is faster (widths up
-        to 128 on the sparse path, 64 on the dense twin); the 3x3's own output buffer is then never written."""
+        to 128 on the sparse path, 64 on the dense twin), and with it the next block's first 1x1; the 3x3's own output buffer is then never written."""
         self.ops, self.shapes = build_ops(batch, image, dtype, seed, image_channels)
         self.dtype, self.sparse = dtype, sparse
         tdt = ss.torch_dtype(dtype)
@@ -119,14 +119,37 @@ class Trunk:
                                                        desc, wbuf, bias, res, L.act, y=self.bufs[op.dst], sparse=use_sparse)
                 self.fused.append(prev.name)
                 self.launches[pos[prev.name]] = None        # the 3x3 runs inside this launch
+                pos[op.name] = len(self.launches)
                 self.launches.append(launch)
                 continue
             launch, _ = ss.prepare_conv2d(desc, self.bufs[op.src], wbuf, bias, (L.stride,) * 2, (L.pad,) * 2, L.act,
                                           y=self.bufs[op.dst], sparse=use_sparse, residual=res)
             pos[op.name] = len(self.launches)
             self.launches.append(launch)
-        self.launches = [l for l in self.launches if l is not None]
+        self._join(pos, prepared, fuse_pairs)
         torch.cuda.synchronize()
+
+    def _join(self, pos, prepared, fuse_pairs):
+        """``chain``, what ``forward`` enqueues: the launches, except that a fused pair and the 1x1 layer that opens the next block run as one
+        kernel where the library expects that to be faster (every buffer is written as before)."""
+        chain = list(self.launches)
+        ops = {op.name: op for op in self.ops}
+        for op in self.ops if fuse_pairs else ():
+            c3 = next((o for o in self.ops if o.dst == op.src), None)
+            if not op.name.endswith("_c1") or c3 is None or c3.name[:-3] + "_c2" not in self.fused:
+                continue
+            c2 = ops[c3.name[:-3] + "_c2"]
+            (d1, w1, b1, sparse), (d2, w2, b2, _), (d3, w3, b3, sparse3) = (prepared[o.name] for o in (c2, c3, op))
+            P = c2.layer
+            if sparse3 != sparse or not all(ss.ss_conv2d_pw2_fused_query(d1, (P.N, P.H, P.W), (P.stride,) * 2, (P.pad,) * 2, d2, d3, sparse)):
+                continue
+            res = None if c3.residual is None else self.bufs[c3.residual]
+            chain[pos[c3.name]], _, _ = ss.prepare_conv2d_pw2_fused(
+                d1, self.bufs[c2.src], w1, b1, (P.stride,) * 2, (P.pad,) * 2, P.act, d2, w2, b2, res, c3.layer.act, d3, w3, b3, op.layer.act,
+                y2=self.bufs[c3.dst], y3=self.bufs[op.dst], sparse=sparse)
+            chain[pos[op.name]] = None
+        self.launches = [l for l in self.launches if l is not None]
+        self.chain = [l for l in chain if l is not None]
 
     @property
     def input(self) -> torch.Tensor:
@@ -137,7 +160,7 @@ class Trunk:
         return self.bufs[self.ops[-1].dst]
 
     def forward(self):
-        for launch in self.launches:
+        for launch in self.chain:
             launch()
         return self.output
 
