@@ -30,7 +30,7 @@ EXPORTS = ["ss_status_string", "ss_packed_bytes", "ss_dense_bytes", "ss_mask_com
            "ss_conv2d_res_fwd", "ss_conv2d_dense_res_fwd", "ss_mask_update_compress", "ss_maxpool2d", "ss_dwconv2d_fwd",
            "ss_conv2d_q8_fwd", "ss_conv2d_q8_dense_fwd", "ss_conv2d_pw_fused_fwd", "ss_conv2d_pw_fused_dense_fwd",
            "ss_weights_check", "ss_conv2d_fwd_static_ws", "ss_conv2d_pw_fused_query", "ss_conv2d_pw2_fused_fwd", "ss_conv2d_pw2_fused_dense_fwd",
-           "ss_conv2d_pw2_fused_query"]
+           "ss_conv2d_pw2_fused_query", "ss_conv2d_maxpool_dense_fwd", "ss_conv2d_maxpool_dense_query"]
 DEBUG_EXPORTS = ["ss_debug_force_tile", "ss_debug_limit_blocks", "ss_debug_force_split", "ss_debug_issue_peak", "ss_debug_lds_bandwidth"]          # include/ss_debug.h: test hooks
 
 
@@ -83,6 +83,8 @@ def _load() -> ctypes.CDLL:
     lib.ss_conv2d_pw2_fused_fwd.argtypes = third_args
     lib.ss_conv2d_pw2_fused_dense_fwd.argtypes = third_args
     lib.ss_conv2d_pw2_fused_query.argtypes = [dp, i32, i32, i32, i32, i32, i32, i32, dp, dp, i32, ctypes.POINTER(i32), ctypes.POINTER(i32)]
+    lib.ss_conv2d_maxpool_dense_fwd.argtypes = conv_args[:13] + [vp, vp]    # y, pooled, stream
+    lib.ss_conv2d_maxpool_dense_query.argtypes = [dp] + [i32] * 8 + [ctypes.POINTER(i32)]
     lib.ss_conv2d_fwd_static_ws.argtypes = conv_args[:13] + [vp]            # no workspace pair
     lib.ss_debug_force_tile.argtypes = [i32]
     lib.ss_debug_limit_blocks.argtypes = [i32]
@@ -376,6 +378,36 @@ def prepare_conv2d(desc, x, wbuf, bias=None, stride=(1, 1), pad=(0, 0), act=SS_A
            ("ss_conv2d_fwd" if sparse else "ss_conv2d_dense_fwd")
     _args, y, ws = _conv_args(what, desc, x, wbuf, bias, stride, pad, act, y, workspace, None, residual, with_res)
     return _launch(what, 0 if sparse else 1, desc, None, x, wbuf, None, None, bias, None, residual, y, ws, x.shape[:3], stride, pad, act), y
+
+
+def prepare_conv2d_maxpool_dense(desc, x, dense, bias=None, stride=(1, 1), pad=(0, 0), act=SS_ACT_RELU, y=None, pooled=None):
+    """Marshal the arguments of ss_conv2d_maxpool_dense_fwd once; returns (launch, y, pooled), as prepare_conv2d does."""
+    what = "ss_conv2d_maxpool_dense_fwd"
+    _args, y, _ws = _conv_args(what, desc, x, dense, bias, stride, pad, act, y, None, None)
+    N, Ho, Wo, C = y.shape
+    shp = (N, (Ho - 1) // 2 + 1, (Wo - 1) // 2 + 1, C)
+    if pooled is None:
+        pooled = torch.empty(shp, dtype=y.dtype, device=y.device)
+    elif tuple(pooled.shape) != shp or pooled.dtype != y.dtype:
+        raise SSError(SS_ERR_INVALID_ARG, f"{what}: pooled must be {shp} {y.dtype}")
+    _dev_ptr(pooled, "pooled")
+    return _launch(what, 9, desc, None, x, dense, None, None, bias, None, None, y, pooled, x.shape[:3], stride, pad, act), y, pooled
+
+
+def ss_conv2d_maxpool_dense_query(desc, nhw, stride, pad, act=SS_ACT_RELU):
+    """Would ss_conv2d_maxpool_dense_fwd take the layer on an input of nhw = (N, H, W)?"""
+    sup = ctypes.c_int32(0)
+    st = _lib.ss_conv2d_maxpool_dense_query(ctypes.byref(desc), nhw[0], nhw[1], nhw[2], stride[0], stride[1], pad[0], pad[1], act, ctypes.byref(sup))
+    if st != SS_OK:
+        raise SSError(st, "ss_conv2d_maxpool_dense_query")
+    return bool(sup.value)
+
+
+def ss_conv2d_maxpool_dense_fwd(desc, x, dense, bias=None, stride=(1, 1), pad=(0, 0), act=SS_ACT_RELU, y=None, pooled=None):
+    """The dense first layer of an image network and the 3x3 max pooling behind it in one kernel; returns (y, pooled)."""
+    launch, y, pooled = prepare_conv2d_maxpool_dense(desc, x, dense, bias, stride, pad, act, y, pooled)
+    launch()
+    return y, pooled
 
 
 def ss_conv2d_fwd(desc, x, packed, bias=None, stride=(1, 1), pad=(0, 0), act=SS_ACT_NONE, y=None, workspace=None,

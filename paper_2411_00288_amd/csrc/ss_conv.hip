@@ -62,12 +62,12 @@ int compute_units()
 }
 
 // q8: the call came through an 8-bit entry point (then `scale` may be given and the descriptor must say SS_I8 or
-// SS_F8); the 16-bit entry points reject such descriptors.
+// SS_F8); the 16-bit entry points reject such descriptors.  pooled: where the 3x3 max pooling behind an image's first layer goes, in the same kernel.
 template <bool SPARSE>
 static int conv_entry(const ss_weight_desc *desc, const void *x, int32_t N, int32_t H, int32_t Wd, const void *wbuf,
                       const float *bias, const void *residual, int32_t sh, int32_t sw, int32_t ph, int32_t pw,
                       int32_t act, void *y, void *workspace, size_t ws_bytes, void *stream, bool q8 = false,
-                      const float *scale = nullptr)
+                      const float *scale = nullptr, void *pooled = nullptr)
 {
     int st = check_desc(desc, SPARSE);
     if (st != SS_OK) return st;
@@ -141,6 +141,11 @@ static int conv_entry(const ss_weight_desc *desc, const void *x, int32_t N, int3
         }
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (!SPARSE && pooled) {
+        p.y2 = static_cast<uint16_t *>(pooled);
+        const int pool_h = (Ho - 1) / 2 + 1, pool_w = (Wo - 1) / 2 + 1;      // window 3, stride 2, padding 1
+        return desc->dtype == SS_F16 ? pooled_dispatch_f16_dense(desc, p, pool_h, pool_w, s) : pooled_dispatch_bf16_dense(desc, p, pool_h, pool_w, s);
+    }
     switch (desc->dtype) {
         case SS_I8: return SPARSE ? conv_dispatch_i8_sparse(desc, p, s) : conv_dispatch_i8_dense(desc, p, s);
         case SS_F8: return SPARSE ? conv_dispatch_f8_sparse(desc, p, s) : conv_dispatch_f8_dense(desc, p, s);
@@ -390,6 +395,31 @@ extern "C" int ss_conv2d_dense_res_fwd(const ss_weight_desc *desc, const void *x
 {
     return conv_entry<false>(desc, x, N, H, Wd, dense, bias, residual, stride_h, stride_w, pad_h, pad_w, act, y,
                              workspace, ws_bytes, stream);
+}
+
+extern "C" int ss_conv2d_maxpool_dense_fwd(const ss_weight_desc *desc, const void *x, int32_t N, int32_t H, int32_t Wd, const void *dense, const float *bias,
+                                           int32_t stride_h, int32_t stride_w, int32_t pad_h, int32_t pad_w, int32_t act, void *y, void *pooled, void *stream)
+{
+    if (!pooled || !aligned(pooled, 16)) return SS_ERR_INVALID_ARG;
+    if (act != SS_ACT_RELU) return act == SS_ACT_NONE || act == SS_ACT_GELU ? SS_ERR_UNSUPPORTED : SS_ERR_INVALID_ARG;
+    return conv_entry<false>(desc, x, N, H, Wd, dense, bias, nullptr, stride_h, stride_w, pad_h, pad_w, act, y, nullptr, 0, stream, false, nullptr, pooled);
+}
+
+extern "C" int ss_conv2d_maxpool_dense_query(const ss_weight_desc *desc, int32_t N, int32_t H, int32_t Wd, int32_t stride_h, int32_t stride_w,
+                                             int32_t pad_h, int32_t pad_w, int32_t act, int32_t *supported)
+{
+    if (!supported) return SS_ERR_INVALID_ARG;
+    *supported = 0;
+    const int st = check_desc(desc, false);
+    if (st != SS_OK) return st == SS_ERR_INVALID_ARG ? st : (int)SS_OK;
+    if (N <= 0 || H <= 0 || Wd <= 0 || stride_h <= 0 || stride_w <= 0 || pad_h < 0 || pad_w < 0) return SS_ERR_INVALID_ARG;
+    if (H + 2 * pad_h < desc->kh || Wd + 2 * pad_w < desc->kw) return SS_ERR_INVALID_ARG;
+    const long long P = (long long)N * ((H + 2 * pad_h - desc->kh) / stride_h + 1) * ((Wd + 2 * pad_w - desc->kw) / stride_w + 1);
+    if (P >= (1ll << 31) - 512) return SS_OK;
+    ConvParams p{};
+    p.P = (int)P; p.Cout = desc->cout; p.sh = stride_h; p.sw = stride_w; p.nsplit = 1;
+    *supported = act == SS_ACT_RELU && image_eligible(desc, p);
+    return SS_OK;
 }
 
 extern "C" int ss_conv2d_q8_fwd(const ss_weight_desc *desc, const void *x, int32_t N, int32_t H, int32_t Wd,

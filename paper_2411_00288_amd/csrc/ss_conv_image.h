@@ -18,6 +18,13 @@
 //     through a wave-private LDS slab as 128-byte pixel rows (16-byte stores, 1 KiB contiguous per instruction).
 //   * The next tile's patch is fetched into registers before the current tile is multiplied.
 // Arithmetic: fp32 accumulation starting from the bias, activation, one rounding to nearest even -- as everywhere.
+//
+// POOL: the 3x3 max pooling of stride 2 and padding 1 that follows the layer, in the same kernel.  The layer's output, four times the pooled one and
+// the largest tensor of the network, is then written but not read back: a tile's 16 x 16 outputs meet in LDS and give 7 x 7
+// pooled ones, neighbouring tiles overlap by two rows and columns, 1.31 times the products.  Behind a ReLU only: outputs are then +0 or more, or
+// NaN, whose bit patterns are ordered like unsigned numbers, so that the maximum is that of the patterns and a NaN wins.  ResNet-50 stem at
+// 224 x 224, us, layer and pooling / both in one: batch 1 10.3 / 7.6, 8 20 / 11.7, 64 54 / 42.6
+// (three channels 54 / 43.0), 128 105 / 84.
 #ifndef SS_CONV_IMAGE_H_
 #define SS_CONV_IMAGE_H_
 #include "ss_conv_stream.h"
@@ -44,11 +51,14 @@ struct ImageShape {
     // at set-up: fragment-ordered weights, then the raw tiles; afterwards: patch, then the slabs
     static constexpr size_t body = a_bytes + raw_bytes > patch_bytes + slab_bytes ? a_bytes + raw_bytes : patch_bytes + slab_bytes;
     static constexpr size_t smem = body + 64 * 4;               // + the bias of the 64 channels
+    // pooled: tiles 14 outputs apart, from one row and column outside the image on; the whole tile of outputs in the slabs' place
+    static constexpr int POOLED = 7, STEP = 2 * POOLED;
+    static_assert(patch_bytes + (size_t)TH * TW * SLAB_ROW * 2 <= body, "the tile of outputs fits");
 };
 
-template <int DT, int CIN>
+template <int DT, int CIN, bool POOL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void conv_image_kernel(ConvParams p, int tiles_h, int tiles_w, int ntiles)
+void conv_image_kernel(ConvParams p, int tiles_h, int tiles_w, int ntiles, int pool_h, int pool_w)
 {
     using SH = ImageShape;
     static_assert(CIN == 3 || CIN == 4, "three or four channels");
@@ -67,6 +77,7 @@ void conv_image_kernel(ConvParams p, int tiles_h, int tiles_w, int ntiles)
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.x), 0, (int)p.x_bytes, kRsrcFlags);
     const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.a_vals), 0, (int)p.a_bytes, kRsrcFlags);
     const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, (int)((unsigned)p.P * (unsigned)p.Cout * 2u), kRsrcFlags);
+    const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(p.y2, 0, POOL ? (int)((unsigned)(p.N * pool_h * pool_w) * (unsigned)p.Cout * 2u) : 0, kRsrcFlags);
 
     // ---- weights: dense tile buffer -> LDS in fragment order [step][row tile][lane][8] -> registers
     // Element e = ((step * 2 + tm) * 64 + l) * 8 + s is the weight of output channel m0 + 32 tm + l % 32 at kernel
@@ -119,6 +130,7 @@ void conv_image_kernel(ConvParams p, int tiles_h, int tiles_w, int ntiles)
     // unconditionally.  The loaded words are kept as they arrive and only put together when they are written to LDS:
     // any arithmetic on them right after the loads would make the wave wait for them before it multiplies.
     const int per_image = tiles_h * tiles_w;
+    auto first_row = [](int tile) { return POOL ? tile * SH::STEP - 1 : tile * SH::TH; };      // (or column) of a tile's outputs
     typedef short s16x2 __attribute__((ext_vector_type(2)));
     uint32_t stage_a[SH::NLOAD];
     uint32_t stage_b[CIN == 4 ? SH::NLOAD : 1];     // four channels: second dword of a pixel
@@ -126,7 +138,7 @@ void conv_image_kernel(ConvParams p, int tiles_h, int tiles_w, int ntiles)
     auto load_patch = [&](int t) {
         const int n = t / per_image, rem = t - n * per_image;
         const int th = rem / tiles_w, tw = rem - th * tiles_w;
-        const int ih0 = th * (SH::TH * SH::S) - p.ph, iw0 = tw * (SH::TW * SH::S) - p.pw;
+        const int ih0 = first_row(th) * SH::S - p.ph, iw0 = first_row(tw) * SH::S - p.pw;
         const bool live = t < ntiles;
 #pragma unroll
         for (int i = 0; i < SH::NLOAD; i++) {
@@ -151,7 +163,7 @@ void conv_image_kernel(ConvParams p, int tiles_h, int tiles_w, int ntiles)
     auto store_patch = [&](int t) {                  // t: the tile the staged words belong to
         const int n = t / per_image, rem = t - n * per_image;
         const int th = rem / tiles_w, tw = rem - th * tiles_w;
-        const int ih0 = th * (SH::TH * SH::S) - p.ph, iw0 = tw * (SH::TW * SH::S) - p.pw;
+        const int ih0 = first_row(th) * SH::S - p.ph, iw0 = first_row(tw) * SH::S - p.pw;
 #pragma unroll
         for (int i = 0; i < SH::NLOAD; i++) {
             const int idx = tid + 256 * i;
@@ -182,7 +194,9 @@ void conv_image_kernel(ConvParams p, int tiles_h, int tiles_w, int ntiles)
     // Output slab of a wave: 32 pixel rows of 128 + 16 bytes, so that every address below is one per-lane base plus a
     // compile-time offset (an XOR swizzle would remove the slab's two-way bank conflicts, but costs twelve more
     // address registers than this kernel has: the reload of a spilled one makes the wave wait for all its stores).
-    uint16_t *const slab = slab_all + wave * 32 * SH::SLAB_ROW;
+    // (With pooling the wave keeps all of its 64 outputs, where the other waves find them.)
+    constexpr int SLAB_STEP = POOL ? 32 * SH::SLAB_ROW : 0;
+    uint16_t *const slab = slab_all + wave * (POOL ? 64 : 32) * SH::SLAB_ROW;
     const float relu_floor = p.act == SS_ACT_RELU ? 0.f : -__builtin_inff();
 
     // The wait for a prefetched patch sits at the end of the loop body, where the instructions issued since the
@@ -213,7 +227,7 @@ void conv_image_kernel(ConvParams p, int tiles_h, int tiles_w, int ntiles)
 
         const int n = t / per_image, rem = t - n * per_image;
         const int th = rem / tiles_w, tw = rem - th * tiles_w;
-        const int ho0 = th * SH::TH + 4 * wave, wo0 = tw * SH::TW;
+        const int ho0 = first_row(th) + 4 * wave, wo0 = first_row(tw);
 
         f32x16 acc[2][2];                            // [row tile][column tile]
 #pragma unroll
@@ -246,6 +260,9 @@ void conv_image_kernel(ConvParams p, int tiles_h, int tiles_w, int ntiles)
         // as soon as this one's reads are issued -- its conversion and writes then cover the slab's read latency.)
         auto write_out = [&](auto actf) {
             auto put = [&](int c) {
+                // (with pooling: zeros outside the layer's output; every window has a position inside, where nothing is less)
+                const int hp = ho0 + 2 * c + (n32 >> 4), wp = wo0 + (n32 & 15);
+                const uint32_t keep = !POOL || ((unsigned)hp < (unsigned)p.Ho && (unsigned)wp < (unsigned)p.Wo) ? 0xFFFFFFFFu : 0u;
 #pragma unroll
                 for (int tm = 0; tm < 2; tm++)
 #pragma unroll
@@ -253,8 +270,8 @@ void conv_image_kernel(ConvParams p, int tiles_h, int tiles_w, int ntiles)
                         float rr[4];
 #pragma unroll
                         for (int e = 0; e < 4; e++) rr[e] = actf(acc[tm][c][4 * j + e]);
-                        *reinterpret_cast<uint2 *>(slab + n32 * SH::SLAB_ROW + 32 * tm + 8 * j + 4 * g) =
-                            make_uint2(cvt_pack2<DT>(rr[0], rr[1]), cvt_pack2<DT>(rr[2], rr[3]));
+                        *reinterpret_cast<uint2 *>(slab + c * SLAB_STEP + n32 * SH::SLAB_ROW + 32 * tm + 8 * j + 4 * g) =
+                            make_uint2(cvt_pack2<DT>(rr[0], rr[1]) & keep, cvt_pack2<DT>(rr[2], rr[3]) & keep);
                     }
             };
             put(0);
@@ -264,19 +281,54 @@ void conv_image_kernel(ConvParams p, int tiles_h, int tiles_w, int ntiles)
 #pragma unroll
                 for (int i = 0; i < 4; i++) {
                     const int q = lane + 64 * i, px = q >> 3, run = q & 7;
-                    w[i] = *reinterpret_cast<const u32x4 *>(slab + px * SH::SLAB_ROW + run * 8);
+                    w[i] = *reinterpret_cast<const u32x4 *>(slab + c * SLAB_STEP + px * SH::SLAB_ROW + run * 8);
                 }
                 if (c == 0) put(1);
 #pragma unroll
                 for (int i = 0; i < 4; i++) {
                     const int q = lane + 64 * i, px = q >> 3, run = q & 7;
                     const int ho = ho0 + 2 * c + (px >> 4), wo = wo0 + (px & 15), o = m0 + run * 8;
-                    const bool ok = ho < p.Ho && wo < p.Wo && o < p.Cout;
+                    // (with pooling a tile's outermost outputs are its neighbours' to store)
+                    const bool own = !POOL || ((unsigned)(ho - ho0 + 4 * wave - 1) < (unsigned)SH::STEP && (unsigned)((px & 15) - 1) < (unsigned)SH::STEP);
+                    const bool ok = own && ho < p.Ho && wo < p.Wo && o < p.Cout;
                     const unsigned off = ((unsigned)((n * p.Ho + ho) * p.Wo + wo) * (unsigned)p.Cout + (unsigned)o) * 2u;
                     __builtin_amdgcn_raw_buffer_store_b128(w[i], ry, (int)(ok ? off : kOutOfRange), 0, 0);
                 }
             }
         };
+        if constexpr (POOL) {
+            write_out([](float v) { return floor_at(v, 0.f); });
+            lds_barrier();                           // the tile is whole, every wave is done with the patch
+            if (tnext < ntiles) store_patch(tnext);  // (uniform)
+            typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+            int pool_tid = tid;
+            asm volatile("" : "+v"(pool_tid));       // (its addresses are computed again for each tile: kept over the loop, they would spill)
+#pragma unroll
+            for (int i = 0; i < (SH::POOLED * SH::POOLED * 8 + 255) / 256; i++) {
+                const int item = pool_tid + 256 * i, px = item >> 3, run = item & 7; // pooled pixel, run of 8 channels
+                const int pr = px * 37 >> 8, pc = px - pr * SH::POOLED;              // (37 / 256: a seventh, exact below 64)
+                if (px >= SH::POOLED * SH::POOLED) break;
+                u32x4 v[9];
+#pragma unroll
+                for (int k = 0; k < 9; k++)
+                    v[k] = *reinterpret_cast<const u32x4 *>(slab_all + ((2 * pr + k / 3) * SH::TW + 2 * pc + k % 3) * SH::SLAB_ROW + run * 8);
+                __builtin_amdgcn_sched_barrier(0);   // (one LDS latency for the nine: the accumulators' registers are free)
+                u32x4 best = v[0];
+#pragma unroll
+                for (int k = 1; k < 9; k++)
+#pragma unroll
+                    for (int e = 0; e < 4; e++)
+                        best[e] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, (uint32_t)best[e]), __builtin_bit_cast(u16x2, (uint32_t)v[k][e])));
+                const int ho = th * SH::POOLED + pr, wo = tw * SH::POOLED + pc, o = m0 + run * 8;
+                const bool ok = ho < pool_h && wo < pool_w && o < p.Cout;
+                const unsigned off = ((unsigned)((n * pool_h + ho) * pool_w + wo) * (unsigned)p.Cout + (unsigned)o) * 2u;
+                __builtin_amdgcn_raw_buffer_store_b128(best, rp, (int)(ok ? off : kOutOfRange), 0, 0);
+            }
+            lds_barrier();                           // the next patch is in LDS, and the tile's place is free
+            if (tnext >= ntiles) break;
+            t = tnext;
+            continue;
+        }
         if (p.act == SS_ACT_GELU) write_out([](float v) { return gelu_cdf<DT>(v); });
         else write_out([&](float v) { return floor_at(v, relu_floor); });      // ReLU, or the identity with a floor of -inf (a NaN passes)
         lds_barrier();                               // every wave is done with the patch
@@ -287,23 +339,16 @@ void conv_image_kernel(ConvParams p, int tiles_h, int tiles_w, int ntiles)
     }
 }
 
-// Can the image kernel take this problem?  Dense 16-bit 7x7 kernel with stride 2 on three or four channels, 16-byte
-// output runs, no residual, output below 2 GiB (32-bit store offsets, out-of-range mark above every real one).
-static inline bool image_eligible(const ss_weight_desc *desc, const ConvParams &p)
-{
-    return !is_byte_type(desc->dtype) && desc->kh == 7 && desc->kw == 7 && (desc->cin == 3 || desc->cin == 4) && p.sh == 2 &&
-           p.sw == 2 && desc->cout % 8 == 0 && p.residual == nullptr && p.nsplit <= 1 &&
-           (long long)p.P * p.Cout * 2 < (1ll << 31) - (1ll << 27);
-}
-
 // Launches the image kernel on a resident grid: at most two workgroups per compute unit (their register budget),
 // each walking over output tiles of 16 x 16 pixels x 64 channels.
-template <int DT>
-static int launch_image(const ss_weight_desc *desc, const ConvParams &p, int ncu, hipStream_t s)
+// pool_h, pool_w: the size of the pooled output, where that is asked for.
+template <int DT, bool POOL = false>
+static int launch_image(const ss_weight_desc *desc, const ConvParams &p, int ncu, hipStream_t s, int pool_h = 0, int pool_w = 0)
 {
     using SH = ImageShape;
     static_assert(SH::smem <= 64 * 1024, "fits the default dynamic LDS limit");
-    const long long tiles_h = (p.Ho + SH::TH - 1) / SH::TH, tiles_w = (p.Wo + SH::TW - 1) / SH::TW;
+    const long long tiles_h = POOL ? (pool_h + SH::POOLED - 1) / SH::POOLED : (p.Ho + SH::TH - 1) / SH::TH;
+    const long long tiles_w = POOL ? (pool_w + SH::POOLED - 1) / SH::POOLED : (p.Wo + SH::TW - 1) / SH::TW;
     const long long ntiles = (long long)p.N * tiles_h * tiles_w;
     const int groups = (p.Cout + 63) / 64;
     if (ntiles <= 0 || ntiles > 0x7FFF0000ll || groups > 0xFFFF) return SS_ERR_UNSUPPORTED;      // (the kernel adds the grid size to a tile index)
@@ -312,9 +357,9 @@ static int launch_image(const ss_weight_desc *desc, const ConvParams &p, int ncu
     if (gx > ntiles) gx = ntiles;
     const dim3 grid((unsigned)gx, (unsigned)groups);
     if (desc->cin == 3)
-        conv_image_kernel<DT, 3><<<grid, dim3(256), SH::smem, s>>>(p, (int)tiles_h, (int)tiles_w, (int)ntiles);
+        conv_image_kernel<DT, 3, POOL><<<grid, dim3(256), SH::smem, s>>>(p, (int)tiles_h, (int)tiles_w, (int)ntiles, pool_h, pool_w);
     else
-        conv_image_kernel<DT, 4><<<grid, dim3(256), SH::smem, s>>>(p, (int)tiles_h, (int)tiles_w, (int)ntiles);
+        conv_image_kernel<DT, 4, POOL><<<grid, dim3(256), SH::smem, s>>>(p, (int)tiles_h, (int)tiles_w, (int)ntiles, pool_h, pool_w);
     return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP;
 }
 

@@ -89,6 +89,16 @@ int SS_CAT(conv_dispatch_, SS_INST_NAME)(const ss_weight_desc *desc, const ConvP
 }
 
 #if SS_INST_FUSED
+#if !SS_INST_SPARSE
+int SS_CAT(pooled_dispatch_, SS_INST_NAME)(const ss_weight_desc *desc, const ConvParams &p, int pool_h, int pool_w, hipStream_t s)
+{
+    int ncu = compute_units();
+    if (ncu <= 0) return SS_ERR_HIP;
+    if (block_limit() > 0 && block_limit() < ncu) ncu = block_limit();
+    return image_eligible(desc, p) ? launch_image<SS_INST_DT, true>(desc, p, ncu, s, pool_h, pool_w) : (int)SS_ERR_UNSUPPORTED;
+}
+#endif
+
 int SS_CAT(fused_dispatch_, SS_INST_NAME)(const ss_weight_desc *d1, const ConvParams &p, hipStream_t s)
 {
     if (forced_tile() < 0 || forced_tile() == 20 || forced_tile() == 21) {       // few output pixels

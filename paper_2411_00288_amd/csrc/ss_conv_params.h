@@ -333,6 +333,18 @@ int forced_split();
     int mlp_dispatch_##NAME(const MlpParams &p, hipStream_t s);
 SS_DECLARE_CONV(f16_sparse) SS_DECLARE_CONV(f16_dense) SS_DECLARE_CONV(bf16_sparse) SS_DECLARE_CONV(bf16_dense)
 SS_DECLARE_CONV(i8_sparse) SS_DECLARE_CONV(i8_dense) SS_DECLARE_CONV(f8_sparse) SS_DECLARE_CONV(f8_dense)
+// Can the image kernel take this problem?  Dense 16-bit 7x7 kernel with stride 2 on three or four channels, 16-byte
+// output runs, no residual, output below 2 GiB (32-bit store offsets, out-of-range mark above every real one).
+static inline bool image_eligible(const ss_weight_desc *desc, const ConvParams &p)
+{
+    return !is_byte_type(desc->dtype) && desc->kh == 7 && desc->kw == 7 && (desc->cin == 3 || desc->cin == 4) && p.sh == 2 &&
+           p.sw == 2 && desc->cout % 8 == 0 && p.residual == nullptr && p.nsplit <= 1 &&
+           (long long)p.P * p.Cout * 2 < (1ll << 31) - (1ll << 27);
+}
+
+// The first layer of an image network with the max pooling behind it (dense 16-bit operands), the pooled output at p.y2.
+int pooled_dispatch_f16_dense(const ss_weight_desc *desc, const ConvParams &p, int pool_h, int pool_w, hipStream_t s);
+int pooled_dispatch_bf16_dense(const ss_weight_desc *desc, const ConvParams &p, int pool_h, int pool_w, hipStream_t s);
 SS_DECLARE_FUSED(f16_sparse) SS_DECLARE_FUSED(f16_dense) SS_DECLARE_FUSED(bf16_sparse) SS_DECLARE_FUSED(bf16_dense)
 
 }  // namespace ss

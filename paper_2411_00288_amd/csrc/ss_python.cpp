@@ -422,7 +422,7 @@ struct Launch {
     vectorcallfunc vectorcall;
     PyObject *keep;            // everything the addresses below belong to
     PyObject *on_error;        // called with the status of a call that failed
-    int kind;                  // ConvKind, or 4 / 5: fused pair (sparse / dense), 6: max pooling, 7 / 8: fused pair and a third layer
+    int kind;                  // ConvKind, or 4 / 5: fused pair (sparse / dense), 6: max pooling, 7 / 8: fused pair and a third layer, 9: convolution and its pooling (at ws)
     ss_weight_desc d1, d2, d3;
     const void *w3;
     const float *b3;
@@ -451,6 +451,9 @@ PyObject *launch_call(PyObject *self, PyObject *const *, size_t, PyObject *)
             return call_conv(l->kind, &l->d1, l->x, l->nhw, l->w1, l->scale, l->b1, l->residual, l->sp, l->act1, l->y, l->ws, l->ws_bytes, s);
         if (l->kind == 6)
             return ss_maxpool2d(l->x, l->nhw[0], l->nhw[1], l->nhw[2], l->pool[0], l->pool[1], l->pool[2], l->sp[0], l->sp[2], l->y, s);
+        if (l->kind == 9)
+            return ss_conv2d_maxpool_dense_fwd(&l->d1, l->x, l->nhw[0], l->nhw[1], l->nhw[2], l->w1, l->b1, l->sp[0], l->sp[1], l->sp[2], l->sp[3], l->act1,
+                                               l->y, l->ws, s);
         if (l->kind >= 7) {
             const auto fn = l->kind == 7 ? ss_conv2d_pw2_fused_fwd : ss_conv2d_pw2_fused_dense_fwd;
             return fn(&l->d1, l->x, l->nhw[0], l->nhw[1], l->nhw[2], l->w1, l->b1, l->sp[0], l->sp[1], l->sp[2], l->sp[3], l->act1, &l->d2,
@@ -507,7 +510,7 @@ PyObject *launch(PyObject *, PyObject *args)
     if (!PyArg_ParseTuple(args, "iOOO!n(iii)(iiii)iiOOOO", &kind, &d1, &d2, &PyTuple_Type, &ptrs, &ws_bytes, &nhw[0], &nhw[1], &nhw[2],
                           &sp[0], &sp[1], &sp[2], &sp[3], &act1, &act2, &poolo, &third, &keep, &on_error))
         return nullptr;
-    if (kind < 0 || kind > 8 || (kind >= 7) != (third != Py_None) || PyTuple_GET_SIZE(ptrs) != 9) {
+    if (kind < 0 || kind > 9 || (kind == 7 || kind == 8) != (third != Py_None) || PyTuple_GET_SIZE(ptrs) != 9) {
         PyErr_SetString(PyExc_ValueError, "launch: bad kind or address list");
         return nullptr;
     }

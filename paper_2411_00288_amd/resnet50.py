@@ -75,7 +75,7 @@ class Trunk:
     def __init__(self, batch: int, image: int = 224, dtype: int = wl.BF16, sparse: bool = True, seed: int = 7000,
                  c3_scale: float = 0.25, keep_host: bool = False, image_channels: int = 4, fuse_pairs: bool = True):
         """fuse_pairs: run a block's 3x3 and the 1x1 expansion after it as one kernel where that is faster (widths up
-        to 128 on the sparse path, 64 on the dense twin), and with it the next block's first 1x1; the 3x3's own output buffer is then never written."""
+        to 128 on the sparse path, 64 on the dense twin), and with it the next block's first 1x1, and the pooling with the layer before it; the 3x3's own output buffer is then never written."""
         self.ops, self.shapes = build_ops(batch, image, dtype, seed, image_channels)
         self.dtype, self.sparse = dtype, sparse
         tdt = ss.torch_dtype(dtype)
@@ -130,10 +130,17 @@ class Trunk:
         torch.cuda.synchronize()
 
     def _join(self, pos, prepared, fuse_pairs):
-        """``chain``, what ``forward`` enqueues: the launches, except that a fused pair and the 1x1 layer that opens the next block run as one
+        """``chain``, what ``forward`` enqueues: the launches, except that the first layer and its pooling, and a fused pair and the 1x1 layer that opens the next block run as one
         kernel where the library expects that to be faster (every buffer is written as before)."""
         chain = list(self.launches)
         ops = {op.name: op for op in self.ops}
+        stem, pool = self.ops[0], self.ops[1]               # (the first two launches)
+        desc, wbuf, bias, _ = prepared[stem.name]
+        L = stem.layer
+        if fuse_pairs and ss.ss_conv2d_maxpool_dense_query(desc, (L.N, L.H, L.W), (L.stride,) * 2, (L.pad,) * 2, L.act):
+            chain[0], _, _ = ss.prepare_conv2d_maxpool_dense(desc, self.bufs[stem.src], wbuf, bias, (L.stride,) * 2, (L.pad,) * 2, L.act,
+                                                             y=self.bufs[stem.dst], pooled=self.bufs[pool.dst])
+            chain[1] = None
         for op in self.ops if fuse_pairs else ():
             c3 = next((o for o in self.ops if o.dst == op.src), None)
             if not op.name.endswith("_c1") or c3 is None or c3.name[:-3] + "_c2" not in self.fused:
