@@ -1059,14 +1059,22 @@ void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, Con
                 }
                 return u32x4{cvt_pack2<ODT>(v[0], v[1]), cvt_pack2<ODT>(v[2], v[3]), cvt_pack2<ODT>(v[4], v[5]), cvt_pack2<ODT>(v[6], v[7])};
             };
+            constexpr int kNonTemporal = 2;               // cache-policy bit nt of the buffer instructions
             const int nparts = p.Cout2 / 128;
+            // A residual is the block's input at its last use, y2 what the next block reads as its own.  Where both together are about as large as the 256 MB
+            // that the memory's cache holds, the residual's lines push y2 out before that: it is then read with the non-temporal hint.  ResNet-50 trunk at
+            // 224 x 224, us without and with (residual of the 56 x 56 blocks, MiB): 40 images (61) 716 / 718, 48 (73) 891 / 884, 56 (86) 950 / 933, 64 (98)
+            // 1050 / 1026 (dense 1237 / 1214), 72 (110) 1121 / 1105, 80 (122) 1187 / 1175, 88 (135) 1403 / 1401, 96 (147) 1474 / 1486.
+            const long long res_bytes = (long long)p.P * p.Cout2 * 2;
+            const bool once = res_bytes >= (72ll << 20) && res_bytes < (144ll << 20);
             for (int part = 0; part < nparts; part++) {
                 const int mt = part * 4 + wave;
 #pragma unroll
                 for (int tn = 0; tn < 2; tn++)
 #pragma unroll
                     for (int j = 0; j < 2; j++)
-                        res[tn][j] = __builtin_amdgcn_raw_buffer_load_b128(rres, (int)(run_px(tn, j) * row2 + (l & 3) * 16), mt * 64, 0);
+                        res[tn][j] = once ? __builtin_amdgcn_raw_buffer_load_b128(rres, (int)(run_px(tn, j) * row2 + (l & 3) * 16), mt * 64, kNonTemporal)
+                                          : __builtin_amdgcn_raw_buffer_load_b128(rres, (int)(run_px(tn, j) * row2 + (l & 3) * 16), mt * 64, 0);
                 f32x16 acc2[2];
                 acc2[0] = acc2[1] = start(rb2, mt * 32);
 #pragma unroll
