@@ -1587,6 +1587,217 @@ void mlp_kernel(MlpParams p)
     else finish([](float z) { return z; });
 }
 
+// The same two layers, resident: a wave takes 32 pixels through both layers at a time, the intermediate in registers.  A lane's 16 accumulators of a row
+// tile are four runs of four consecutive channels of its pixel, that is four whole 2:4 blocks of the second reduction; with the 16-bit
+// blocks 0 1 | 2 3 | 4 5 | 6 7 of the two lane halves swapped to 0 4 | 1 5 | 2 6 | 3 7 (four V_PERMLANE32_SWAP) they are the second layer's operand.
+// So the intermediate passes neither LDS nor a barrier.  The weights of both layers lie in LDS, one workgroup per compute unit walks over its pixel
+// tiles, and a wave asks for its next tile's input while it works on this one.
+// Bound by memory with ReLU (231 MB in 46 us), by the vector ALU with GELU (of 2880 vector instructions per tile of 96 -> 384 -> 96 in bf16, 2500 are
+// the GELUs).  With the weights from memory for each wave the address unit took as long as the vector ALU; with an accumulator tile more, to
+// multiply ahead of the activations, three waves per SIMD had no registers left for weights on their way, and each matrix instruction waited for LDS.
+// 401408 pixels, 96 -> 384 -> 96, bf16, mlp_kernel against this one, us: ReLU sparse 69.0 -> 46.0, dense 88.9 -> 57.7; GELU dense 116.8 -> 98.6 (f16 114.9 -> 94.0).
+// The LDS copy is in the order of use, two row tiles of the intermediate (32 channels each) after the other, so that all offsets inside a pair are constants:
+// the first layer's tiles, the second layer's steps, their index words, the first layer's bias.
+template <bool SPARSE, int TILES>
+struct MlpPair {
+    static constexpr int STEP = SPARSE ? 1024 : 2048, KP1 = (TILES + 1) / 2, W2 = 2 * TILES * STEP, I1 = 2 * W2, I2 = I1 + (SPARSE ? 2 * KP1 * 256 : 0),
+                         BIAS = I2 + (SPARSE ? TILES * 256 : 0), BYTES = BIAS + 2 * 128;
+    static constexpr size_t smem(int Cmid) { return (size_t)(Cmid / 64) * BYTES + TILES * 128; }      // (with the second layer's bias)
+};
+
+// TILES: 32-channel tiles of the input and of the output; WAVES: per workgroup.
+template <int DT, bool SPARSE, int TILES, int WAVES, bool GELU1>
+__global__ __launch_bounds__(WAVES * 64)
+void mlp_resident_kernel(MlpParams p)
+{
+    using L = MlpPair<SPARSE, TILES>;
+    constexpr int BN = 32, CIN = TILES * 32, STEP = L::STEP, NT = WAVES * 64, HALVES = SPARSE ? 1 : 2;
+    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+    uint8_t *const ws = reinterpret_cast<uint8_t *>(smem);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 5, c = lane & 31;
+    const int Ks2 = p.Cmid / 32, pairs = Ks2 / 2;         // (Cmid is a multiple of 128)
+    // a lane's 16 consecutive channels of a tile of channels, and the pixels of tile t (none behind the last): two 16-byte runs
+    const int px_at = c * (CIN * 2) + g * 32;
+    auto pixels = [&](const uint16_t *base, int t) {
+        // (clamping to a range is a vector instruction: read back, or every load would be a loop over its lanes' descriptors)
+        const int here = __builtin_amdgcn_readfirstlane(max(0, min(BN, p.P - t * BN)));
+        uint16_t *const at = reinterpret_cast<uint16_t *>(reinterpret_cast<uintptr_t>(base) + (size_t)t * (BN * CIN * 2));
+        return __builtin_amdgcn_make_buffer_rsrc(at, 0, base != nullptr ? here * (CIN * 2) : 0, kRsrcFlags);
+    };
+    auto load_runs = [&](B32 (&f)[TILES], const __amdgpu_buffer_rsrc_t &r) {
+#pragma unroll
+        for (int t = 0; t < TILES; t++) {
+            f[t].lo = __builtin_amdgcn_raw_buffer_load_b128(r, px_at, t * 64, 0);
+            f[t].hi = __builtin_amdgcn_raw_buffer_load_b128(r, px_at, t * 64 + 16, 0);
+        }
+    };
+    // (the first tiles go to all compute units before any gets a second one)
+    const int ntiles = (p.P + BN - 1) / BN, stride = p.blocks * WAVES;
+    int tile = wave * p.blocks + blockIdx.x;
+    B32 x[TILES], xn[TILES];
+    load_runs(x, pixels(p.x, tile));
+
+    // ---- weights and biases to LDS
+    {
+        // the weights: rows of 1024 bytes, one per wave at a time (all of this but the lane's place is scalar)
+        constexpr int LAYER = 2 * TILES * HALVES, AHEAD = 8;      // rows of a layer per pair; loads under way at once
+        const int rows = pairs * 2 * LAYER;
+        for (int r0 = wave; r0 < rows; r0 += WAVES * AHEAD) {
+            u32x4 v[AHEAD];
+#pragma unroll
+            for (int i = 0; i < AHEAD; i++) {
+                const int r = min(r0 + i * WAVES, rows - 1), pm = r / (2 * LAYER), k = r % (2 * LAYER), k2 = k - LAYER;
+                const uint8_t *const src = k < LAYER ? p.a1_vals + (pm * LAYER + k) * 1024
+                                                     : p.a2_vals + (k2 / (2 * HALVES) * pairs + pm) * (2 * STEP) + k2 % (2 * HALVES) * 1024;
+                v[i] = *reinterpret_cast<const u32x4 *>(src + lane * 16);
+            }
+#pragma unroll
+            for (int i = 0; i < AHEAD; i++) {
+                const int r = r0 + i * WAVES;
+                if (r < rows) *reinterpret_cast<u32x4 *>(ws + r / (2 * LAYER) * L::BYTES + r % (2 * LAYER) * 1024 + lane * 16) = v[i];
+            }
+        }
+        // the rest of each pair, 16 bytes per thread
+        constexpr int UNITS = (L::BYTES - L::I1) / 16;
+        const int vals = Ks2 * TILES * STEP;
+        for (int u = tid; u < pairs * UNITS; u += NT) {
+            const int pm = u / UNITS, at = L::I1 + u % UNITS * 16;
+            const uint8_t *src = p.bias1 != nullptr ? reinterpret_cast<const uint8_t *>(p.bias1) + pm * 256 + (at - L::BIAS) : nullptr;
+            if (at < L::I2) src = p.a1_vals + vals + pm * (2 * L::KP1 * 256) + (at - L::I1);
+            else if (at < L::BIAS) src = p.a2_vals + vals + ((at - L::I2) / 256 * pairs + pm) * 256 + (at - L::I2) % 256;
+            u32x4 v = {0, 0, 0, 0};
+            if (src != nullptr) v = *reinterpret_cast<const u32x4 *>(src);
+            *reinterpret_cast<u32x4 *>(ws + pm * L::BYTES + at) = v;
+        }
+        if (tid < CIN) reinterpret_cast<float *>(ws + pairs * L::BYTES)[tid] = p.bias2 != nullptr ? p.bias2[tid] : 0.f;
+    }
+    lds_barrier();
+    if (tile >= ntiles) return;
+    // a wave with one tile more than the others of its SIMD goes first: done last and alone, that tile would have nothing to overlap with
+    if (ntiles > stride && tile < ntiles % stride) __builtin_amdgcn_s_setprio(1);
+
+    auto start = [&](f32x16 &acc, const uint8_t *bias) {  // the bias starts in the accumulators (bias: the lane half's place)
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const f32x4 b = *reinterpret_cast<const f32x4 *>(bias + 32 * q);
+#pragma unroll
+            for (int e = 0; e < 4; e++) acc[4 * q + e] = b[e];
+        }
+    };
+    struct Weights {
+        u32x4 v[HALVES][TILES];
+        uint32_t idx[TILES];
+    };
+    auto mma = [](const Weights &w, int t, const B32 &b, f32x16 acc) {
+        if constexpr (SPARSE) {
+            return mma_sparse<DT>(w.v[0][t], b, acc, w.idx[t]);
+        } else {
+            acc = mma_dense<DT>(w.v[0][t], b.lo, acc);
+            return mma_dense<DT>(w.v[HALVES - 1][t], b.hi, acc);
+        }
+    };
+    // Runs of four channels, two dwords each: lane half g has channels 8 q + 4 g .. of the tile in run q; as 16 consecutive channels 16 g .. , and back
+    // (the swap is its own inverse).
+    auto swap_halves = [](uint32_t (&d)[4][2]) {
+#pragma unroll
+        for (int q = 0; q < 2; q++)
+#pragma unroll
+            for (int e = 0; e < 2; e++) {
+                const auto r = __builtin_amdgcn_permlane32_swap(d[q][e], d[q + 2][e], false, false);
+                d[q][e] = r[0];
+                d[q + 2][e] = r[1];
+            }
+    };
+    const float floor1 = p.act1 == SS_ACT_RELU ? 0.f : -__builtin_inff();
+    auto act1 = [floor1](float z) { return GELU1 ? gelu_cdf<DT>(z) : floor_at(z, floor1); };
+
+    f32x16 acc1, acc2[TILES];
+    Weights w;
+    const int at16 = lane * 16, at4 = lane * 4, atg = g * 16;
+    // a row tile of the first layer, and the reduction step of the second that belongs to it (index words: the half that is the step's)
+    auto request1 = [&](int pair, int odd) {
+        start(acc1, ws + atg + pair + (L::BIAS + odd * 128));
+#pragma unroll
+        for (int s = 0; s < TILES; s++) {
+#pragma unroll
+            for (int h = 0; h < HALVES; h++) w.v[h][s] = *reinterpret_cast<const u32x4 *>(ws + at16 + pair + ((odd * TILES + s) * STEP + h * 1024));
+            if (SPARSE) w.idx[s] = *reinterpret_cast<const uint16_t *>(ws + at4 + pair + (L::I1 + (odd * L::KP1 + s / 2) * 256 + s % 2 * 2));
+        }
+    };
+    auto request2 = [&](int pair, int odd) {
+#pragma unroll
+        for (int t = 0; t < TILES; t++) {
+#pragma unroll
+            for (int h = 0; h < HALVES; h++) w.v[h][t] = *reinterpret_cast<const u32x4 *>(ws + at16 + pair + (L::W2 + (2 * t + odd) * STEP + h * 1024));
+            if (SPARSE) w.idx[t] = *reinterpret_cast<const uint16_t *>(ws + at4 + pair + (L::I2 + t * 256 + odd * 2));
+        }
+    };
+    B32 res[TILES];
+    // One row tile through both layers; `next`, `next_odd`: the one behind it.
+    auto step = [&](int pair, int odd, int next, int next_odd, auto last) {
+#pragma unroll
+        for (int s = 0; s < TILES; s++) acc1 = mma(w, s, x[s], acc1);
+        if constexpr (decltype(last)::value) load_runs(res, pixels(p.res2, tile));
+        request2(pair, odd);
+        __builtin_amdgcn_sched_barrier(0);
+        uint32_t d[4][2];
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            float r[4];
+#pragma unroll
+            for (int e = 0; e < 4; e++) r[e] = act1(acc1[4 * q + e]);
+            d[q][0] = cvt_pack2<DT>(r[0], r[1]);
+            d[q][1] = cvt_pack2<DT>(r[2], r[3]);
+            if (q % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+        }
+        swap_halves(d);
+        const B32 f = {u32x4{d[0][0], d[0][1], d[2][0], d[2][1]}, u32x4{d[1][0], d[1][1], d[3][0], d[3][1]}};
+#pragma unroll
+        for (int t = 0; t < TILES; t++) acc2[t] = mma(w, t, f, acc2[t]);
+        request1(next, next_odd);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    request1(0, 0);
+    for (; tile < ntiles; tile += stride) {
+        load_runs(xn, pixels(p.x, tile + stride));
+#pragma unroll
+        for (int t = 0; t < TILES; t++) start(acc2[t], ws + atg + pairs * L::BYTES + t * 128);
+        int pair = 0;
+        for (int i = 0; i + 1 < pairs; i++, pair += L::BYTES) {
+            step(pair, 0, pair, 1, std::false_type{});
+            step(pair, 1, pair + L::BYTES, 0, std::false_type{});
+        }
+        step(pair, 0, pair, 1, std::false_type{});
+        step(pair, 1, 0, 0, std::true_type{});            // (behind the last tile: not used)
+#pragma unroll
+        for (int t = 0; t < TILES; t++) x[t] = xn[t];
+
+        // ---- output: residual and activation in fp32, one rounding
+        const __amdgpu_buffer_rsrc_t ry = pixels(p.y2, tile);
+        auto finish = [&](auto act2) {
+#pragma unroll
+            for (int t = 0; t < TILES; t++) {
+                uint32_t rr[4][2] = {{res[t].lo[0], res[t].lo[1]}, {res[t].hi[0], res[t].hi[1]}, {res[t].lo[2], res[t].lo[3]}, {res[t].hi[2], res[t].hi[3]}}, d[4][2];
+                swap_halves(rr);
+#pragma unroll
+                for (int q = 0; q < 4; q++)
+#pragma unroll
+                    for (int e = 0; e < 2; e++)
+                        d[q][e] = cvt_pack2<DT>(act2(acc2[t][4 * q + 2 * e] + widen<DT>((uint16_t)(rr[q][e] & 0xFFFFu))),
+                                                act2(acc2[t][4 * q + 2 * e + 1] + widen<DT>((uint16_t)(rr[q][e] >> 16))));
+                swap_halves(d);
+                __builtin_amdgcn_raw_buffer_store_b128(u32x4{d[0][0], d[0][1], d[2][0], d[2][1]}, ry, px_at, t * 64, 0);
+                __builtin_amdgcn_raw_buffer_store_b128(u32x4{d[1][0], d[1][1], d[3][0], d[3][1]}, ry, px_at, t * 64 + 16, 0);
+            }
+        };
+        if (p.act2 == SS_ACT_GELU) finish([](float z) { return gelu_cdf<DT>(z); });
+        else if (p.act2 == SS_ACT_RELU) finish([](float z) { return floor_at(z, 0.f); });
+        else finish([](float z) { return z; });
+    }
+}
+
 // The same two layers on few pixels.  mlp_kernel's four waves take the intermediate 128 channels at a time, so that a workgroup lives for
 // four chunks of weights, matrix instructions, activations and barriers in a row, which nothing hides where there is one workgroup per
 // compute unit.  Here a workgroup owns 32 pixels and has a wave for each 32 channels of the intermediate: every wave computes
@@ -1805,6 +2016,52 @@ static int launch_mlp_wide(const MlpParams &p, hipStream_t s)
     }
 }
 
+constexpr size_t kMlpResidentSmem = 160 * 1024;
+
+// The resident kernel on so many channels, if its weights fit the LDS.
+template <int DT, bool SPARSE, int TILES>
+static int launch_mlp_resident(const MlpParams &p0, int ncu, hipStream_t s)
+{
+    constexpr int WAVES = TILES <= 3 ? 12 : 8;            // three waves per SIMD, or the two that their registers leave room for
+    MlpParams p = p0;
+    const int tiles = (int)(((long long)p.P + 31) / 32), limit = block_limit();
+    p.blocks = tiles < ncu ? tiles : ncu;
+    if (limit > 0 && p.blocks > limit) p.blocks = limit;
+    if (p.blocks <= 0) return SS_ERR_UNSUPPORTED;
+    auto kern = mlp_resident_kernel<DT, SPARSE, TILES, WAVES, false>;
+    if constexpr (!SPARSE) kern = p.act1 == SS_ACT_GELU ? mlp_resident_kernel<DT, SPARSE, TILES, WAVES, true> : kern;
+    // (once per device and kernel; two threads racing here both set it: harmless)
+    static std::atomic<unsigned long long> done_mask[2];
+    std::atomic<unsigned long long> &done = done_mask[p.act1 == SS_ACT_GELU];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return SS_ERR_HIP;
+    const unsigned long long bit = 1ull << (dev & 63);
+    if (dev >= 64 || !(done.load(std::memory_order_acquire) & bit)) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kMlpResidentSmem) != hipSuccess)
+            return SS_ERR_HIP;
+        if (dev < 64) done.fetch_or(bit, std::memory_order_release);
+    }
+    kern<<<dim3((unsigned)p.blocks), dim3(WAVES * 64), (MlpPair<SPARSE, TILES>::smem(p.Cmid)), s>>>(p);
+    return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP;
+}
+
+// Pixel tiles per compute unit from where the resident kernel pays, or -1 where there is none.  A SIMD that gets a tile more than its neighbours keeps
+// the chip waiting for it, and the weights' way to LDS is some 3 us, so it takes a few tiles per SIMD.  Times against mlp_kernel's at 1.6, 2.4, 3.2, 4, 5.5, 7 and
+// 12.25 tiles of 32 pixels per SIMD, bf16, C -> 4 C -> C:
+//   ReLU   sparse  96   0.85 0.82 0.78 0.80 0.77 0.72 0.68      dense  96   0.79 0.82 0.73 0.72 0.73 0.69 0.62
+//          sparse 128   0.94 0.96 0.88 0.85 0.86 0.79 0.76
+//   GELU   dense   96   0.95 1.01 0.95 0.86 0.90 0.83 0.84     (in a ConvNeXt block on new inputs each time 0.95 to 0.90, 173 -> 163 us at 128 x 56 x 56)
+// Not for the sparse path with GELU, where both are bound by the vector ALU: 96 channels 0.92 to 1.05 by itself but 0.99 to 1.04 in the block, 128
+// 0.95 to 1.11 and 1.02 to 1.08; nor for 64 and 32 channels with GELU (1.0 to 1.2).  Dense 128 does not fit the LDS.
+static inline int mlp_resident_from(const MlpParams &p, bool sparse)
+{
+    if (p.Cin != p.Cout2 || (p.Cin != 96 && p.Cin != 128)) return -1;
+    const size_t smem = p.Cin == 96 ? (sparse ? MlpPair<true, 3>::smem(p.Cmid) : MlpPair<false, 3>::smem(p.Cmid))
+                                    : (sparse ? MlpPair<true, 4>::smem(p.Cmid) : MlpPair<false, 4>::smem(p.Cmid));
+    if (smem > kMlpResidentSmem) return -1;
+    return p.act1 != SS_ACT_GELU || !sparse ? 6 : -1;
+}
+
 template <int DT, bool SPARSE>
 static int launch_mlp(const MlpParams &p, hipStream_t s)
 {
@@ -1815,7 +2072,13 @@ static int launch_mlp(const MlpParams &p, hipStream_t s)
     // 11.4 against 6.65 / 7.5; 8192 pixels, the last that fit, C = 96 7.7 / 8.6 against 5.8 / 6.3; 10000 pixels, 313 workgroups of 12 waves, 7.8 / 8.75
     // against 9.5 / 10.9.  Four waves (C = 32) make no difference: 3.7 and 3.6.
     const bool few = ((long long)p.P + 31) / 32 <= ncu && p.Cmid >= 256;
-    if (p.Cmid <= 32 * kMlpWideWaves && (forced == 41 || (forced != 40 && few))) return launch_mlp_wide<DT, SPARSE>(p, s);
+    const bool free_choice = forced < 40 || forced > 42;
+    if (p.Cmid <= 32 * kMlpWideWaves && (forced == 41 || (free_choice && few))) return launch_mlp_wide<DT, SPARSE>(p, s);
+    const int from = mlp_resident_from(p, SPARSE);
+    if (from >= 0 && (forced == 42 || (free_choice && ((long long)p.P + 31) / 32 > (long long)from * ncu))) {
+        if constexpr (SPARSE) return p.Cin == 96 ? launch_mlp_resident<DT, SPARSE, 3>(p, ncu, s) : launch_mlp_resident<DT, SPARSE, 4>(p, ncu, s);
+        else if (p.Cin == 96) return launch_mlp_resident<DT, SPARSE, 3>(p, ncu, s);
+    }
     const long long blocks = ((long long)p.P + 63) / 64;
     if (blocks <= 0 || blocks > 0x7FFFFFFFll) return SS_ERR_UNSUPPORTED;
     size_t smem = (size_t)64 * (p.Cin + 8) * 2 + (size_t)64 * (128 + 4) * 2 + (size_t)p.Cmid * 4;

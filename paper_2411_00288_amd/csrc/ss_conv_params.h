@@ -106,6 +106,7 @@ struct MlpParams {            // (a cheap launch, see ConvArgs; all channel coun
     const uint16_t *res2;     // [P][Cout2] or nullptr
     uint16_t *y2;             // [P][Cout2]
     int P, Cin, Cmid, Cout2, act1, act2;
+    int blocks;               // workgroups of a resident launch
 };
 
 constexpr int kMlpKs1 = 4;        // first reduction: at most 128 input channels
