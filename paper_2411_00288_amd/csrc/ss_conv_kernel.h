@@ -2228,7 +2228,8 @@ static int pick_vec(const ConvParams &p, hipStream_t s)
     if (forced >= 0) return forced == 4 || forced == 5 ? pick_tile<DT, SPARSE, MODE_VEC8, 1, 1>(p, s) : pick_tile<DT, SPARSE, MODE_VEC, 1, 1>(p, s);
     const int ncu = compute_units();
     if (ncu <= 0) return SS_ERR_HIP;
-    const int id = choose_height(p, choose_vec(p, is_byte_type(DT), SPARSE, ncu), false, is_byte_type(DT), SPARSE, ncu, DT == SS_F8);
+    int id = choose_height(p, choose_vec(p, is_byte_type(DT), SPARSE, ncu), false, is_byte_type(DT), SPARSE, ncu, DT == SS_F8);
+    if (is_byte_type(DT) && SPARSE) id = choose_vec8_sparse(p, id, ncu);
     if (id == 4 || id == 5) return launch_tile<DT, SPARSE, MODE_VEC8, 1, 1>(id, p, s);
     return launch_tile<DT, SPARSE, MODE_VEC, 1, 1>(id, p, s);
 }

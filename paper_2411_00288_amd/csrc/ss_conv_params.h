@@ -153,7 +153,8 @@ static inline int choose_tile(const ConvParams &p, bool pointwise, bool bigchunk
 //   * dense 8-bit: 128x64 (int8 0.60 to 1.15, mean 0.84; FP8, whose general choice is producer waves, 0.58 to 1.31, mean 0.87: the
 //     losses are at 784 workgroups, two per cent more than the chip holds at once).
 // Over the sweep the choice is 1 % (dense 8-bit 1.6 %) above the best of the three in the mean, the four-wave 256x64 tile everywhere
-// would be 4 to 21 %.  Sparse 8-bit layers, whose steps are the cheapest, keep the rule for short chunks: 256x64 from 512 channels on.
+// would be 4 to 21 %.  Sparse 8-bit layers, whose steps are the cheapest, start from the rule for short chunks (256x64 from 512 channels on) and have costs
+// of their own behind it (choose_vec8_sparse).
 static inline int choose_vec(const ConvParams &p, bool bytes, bool sparse, int ncu)
 {
     const int id = choose_tile(p, false, true);
@@ -197,6 +198,32 @@ static inline int choose_height(const ConvParams &p, int id, bool taps, bool byt
         if (best < 0 || cost < best) { best = cost; pick = t.id; }
     }
     return pick;
+}
+
+// Sparse 8-bit channels-last layers with taps and K >= 512, given the choice made so far: the tile of 128 or of 256 rows where it clearly beats that,
+// by the tiles of the fullest compute unit (nearer to it than in choose_height) times the time of a tile.  Their weight fragments are half a
+// 16-bit layer's, so a tall tile, which reads an activation fragment once for more rows, gains the more the longer the reduction: 256 rows
+// take 1.75 of the 128-row tile's time at K = 640 (2-byte units), 1.63 at 1280, 1.57 at 2300; choose_vec never compares the two here, and choose_height takes K
+// not into account.  Of 12264 layers on cold inputs with each tile forced (profiles/tile_heights.md) 1643 change their tile, 0.862 of its time in the mean,
+// 99 % of them at most 1.00: 225 to 256 and 449 to 511 channels from 128 rows to 256, above those layers whose last round would be nearly empty.
+// (In calls on new inputs each time: int8 160 -> 256 on 62 28x28 images 22.65 -> 19.2 us, 144 -> 452 on fifteen 40x40 21.6 -> 18.1, 256 -> 484 on twenty 35.0 -> 33.9.)
+// The line of 0.86 is below 1 because the grid's rounding is not known better: at 0.92 2886 layers change (0.897), but 8 % of them lose.
+static inline int choose_vec8_sparse(const ConvParams &p, int id, int ncu)
+{
+    auto time = [&](int rows, int base, int start) {      // base + start / K: a tile's time in hundredths of the 128-row one's
+        const long long n = n_blocks(p, rows, 64);
+        return (3 * n + 7 * ((n + ncu - 1) / ncu * ncu)) * ((long long)base * p.K + start);
+    };
+    const long long t128 = time(128, 100, 0), t256 = time(256, 153, 11840);
+    long long now;
+    switch (id) {
+        case 2: now = t128; break;
+        case 3: now = t256; break;
+        case 7: now = time(160, 125, 7680); break;
+        case 8: now = time(224, 157, 11520); break;
+        default: return id;
+    }
+    return (t128 < t256 ? t128 : t256) / 86 < now / 100 ? (t128 < t256 ? 2 : 3) : id;
 }
 
 // ---------------------------------------------------------------------------------------------
