@@ -2223,8 +2223,10 @@ static int pick_tile(const ConvParams &p, hipStream_t s)
 template <int DT, bool SPARSE>
 static int pick_vec(const ConvParams &p, hipStream_t s)
 {
-    if (p.K < 512) return pick_tile<DT, SPARSE, MODE_VEC, 1, 1>(p, s);
     const int forced = forced_tile();
+    if (p.K < 512)
+        return forced >= 0 ? pick_tile<DT, SPARSE, MODE_VEC, 1, 1>(p, s)
+                           : launch_tile<DT, SPARSE, MODE_VEC, 1, 1>(choose_vec_short(p, is_byte_type(DT), SPARSE, DT == SS_F8), p, s);
     if (forced >= 0) return forced == 4 || forced == 5 ? pick_tile<DT, SPARSE, MODE_VEC8, 1, 1>(p, s) : pick_tile<DT, SPARSE, MODE_VEC, 1, 1>(p, s);
     const int ncu = compute_units();
     if (ncu <= 0) return SS_ERR_HIP;

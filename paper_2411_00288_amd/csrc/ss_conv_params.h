@@ -226,6 +226,19 @@ static inline int choose_vec8_sparse(const ConvParams &p, int id, int ncu)
     return (t128 < t256 ? t128 : t256) / 86 < now / 100 ? (t128 < t256 ? 2 : 3) : id;
 }
 
+// Tile id of a channels-last layer with taps and K < 512 (2-byte units), where it is not choose_tile's: one tile of 160 rows for 129 to 160 channels on the
+// sparse path instead of two of 128 (0.89 of their time in the mean over 543 layers, 0.73 to 1.00, 16- and 8-bit alike; dense 0.97, up to 1.21), and 96 rows on the dense
+// int8 one where they are no more tiles (65 to 96, 129 to 192, 257 to 288 channels: 0.915 over 560 layers, 2.7 % of them more than 1 % slower).  In calls on new inputs, us:
+// bf16 40 -> 136 on thirty 40x40 images 12.9 -> 9.65, int8 96 -> 148 on twenty 10.5 -> 9.0 (dense 11.4 -> 10.5), FP8 64 -> 132 on a hundred 28x28 16.9 -> 15.3, int8 dense 64 -> 92 13.45 -> 10.9.  Not 96 rows
+// elsewhere: dense 16-bit 0.94 but one layer in eight slower, sparse 0.98 to 0.99.  (8806 layers on cold inputs, profiles/tile_heights.md.)
+static inline int choose_vec_short(const ConvParams &p, bool bytes, bool sparse, bool f8)
+{
+    const int id = choose_tile(p, false, false);
+    if (id != 2) return id;
+    if (sparse) return p.Cout > 128 && p.Cout <= 160 ? 7 : id;
+    return bytes && !f8 && (p.Cout + 95) / 96 == (p.Cout + 127) / 128 ? 6 : id;
+}
+
 // ---------------------------------------------------------------------------------------------
 // Few output pixels: which of the one-latency kernels (ss_conv_small.h) takes a problem.  Here and not beside them because the
 // workspace query and the entry points must know: a problem that they take never splits its reduction.

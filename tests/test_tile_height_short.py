@@ -1,0 +1,51 @@
+"""The tile of channels-last layers with short reductions (choose_vec_short), on the host and on the GPU against the 128-row tile."""
+import shutil
+import subprocess
+from pathlib import Path
+
+import pytest
+import torch
+
+import test_gpu_f8 as f8
+import test_gpu_q8 as q8
+import test_gpu_tail as tail
+from helpers import run_gpu
+from paper_2411_00288_amd import workloads as wl
+
+ROOT = Path(__file__).resolve().parent.parent
+LARGE = 64 * 256 * 40
+
+
+def test_both_sides_of_the_lines(tmp_path):
+    if shutil.which("g++") is None:
+        pytest.skip("no host compiler")
+    exe = tmp_path / "choose_vec_short"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", str(ROOT / "include"),
+                    str(ROOT / "tests" / "host" / "choose_vec_short.cpp"), "-o", str(exe)], check=True, capture_output=True)
+    # (channels, pixels, bytes, sparse, f8)
+    want = {}
+    for kind in ((0, 1, 0), (1, 1, 0), (1, 1, 1)):
+        want.update({(c, LARGE) + kind: t for c, t in ((96, 2), (128, 2), (129, 7), (160, 7), (161, 2), (288, 2))})
+    want.update({(c, LARGE, 1, 0, 0): t for c, t in ((65, 6), (96, 6), (97, 2), (128, 2), (129, 6), (192, 6), (193, 2), (256, 2), (257, 6), (288, 6), (289, 2), (512, 2))})
+    want.update({(c, LARGE) + kind: 2 for c in (96, 160, 288) for kind in ((0, 0, 0), (1, 0, 1))})
+    want.update({(64, LARGE, 1, 0, 0): 0, (136, 64 * 129, 0, 1, 0): 5, (136, 64 * 128, 0, 1, 0): 4})      # the others keep theirs
+    out = subprocess.run([str(exe)], input="".join("%d %d %d %d %d\n" % k for k in want), capture_output=True, text=True, check=True).stdout.split()
+    assert [int(o) for o in out] == list(want.values())
+
+
+# a last tile of one pixel, 257 tiles of pixels; K below 512 in 2-byte units and no multiple of a step
+@pytest.mark.gpu
+@pytest.mark.parametrize("cout", [129, 160, 192, 257])
+def test_choice_against_128_rows(ss, force_tile, cout):
+    H, W = 5, 3277                                        # 16385 pixels
+    for sparse in (True, False):
+        for mod, make, cin in ((q8, wl.make_inputs_q8, 48), (f8, wl.make_inputs_f8, 48), (None, wl.make_inputs, 24)):
+            L = (mod or tail)._L(1, H, W, cin, cout, 3, p=1, korder=wl.K_RSC, seed=cout, **({} if mod else {"dtype": wl.BF16, "act": wl.ACT_RELU}))
+            d = make(L)
+            out = []
+            for tile in (None, 2):
+                force_tile(tile)
+                out.append(mod._run(ss, L, d, sparse=sparse) if mod else run_gpu(ss, L, d, sparse=sparse))
+            y, ref = (o if isinstance(o, torch.Tensor) else torch.as_tensor(o) for o in out)
+            # every height adds a row's products in the same order and has the same epilogue
+            assert torch.equal(y.contiguous().view(torch.uint8), ref.contiguous().view(torch.uint8)), f"{L.name} sparse {sparse}"
