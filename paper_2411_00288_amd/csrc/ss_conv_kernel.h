@@ -2223,13 +2223,12 @@ static int pick_tile(const ConvParams &p, hipStream_t s)
 template <int DT, bool SPARSE>
 static int pick_vec(const ConvParams &p, hipStream_t s)
 {
-    const int forced = forced_tile();
+    const int forced = forced_tile(), ncu = compute_units();
+    if (ncu <= 0) return SS_ERR_HIP;
     if (p.K < 512)
         return forced >= 0 ? pick_tile<DT, SPARSE, MODE_VEC, 1, 1>(p, s)
-                           : launch_tile<DT, SPARSE, MODE_VEC, 1, 1>(choose_vec_short(p, is_byte_type(DT), SPARSE, DT == SS_F8), p, s);
+                           : launch_tile<DT, SPARSE, MODE_VEC, 1, 1>(choose_vec_short(p, is_byte_type(DT), SPARSE, DT == SS_F8, ncu), p, s);
     if (forced >= 0) return forced == 4 || forced == 5 ? pick_tile<DT, SPARSE, MODE_VEC8, 1, 1>(p, s) : pick_tile<DT, SPARSE, MODE_VEC, 1, 1>(p, s);
-    const int ncu = compute_units();
-    if (ncu <= 0) return SS_ERR_HIP;
     int id = choose_height(p, choose_vec(p, is_byte_type(DT), SPARSE, ncu), false, is_byte_type(DT), SPARSE, ncu, DT == SS_F8);
     if (is_byte_type(DT) && SPARSE) id = choose_vec8_sparse(p, id, ncu);
     if (id == 4 || id == 5) return launch_tile<DT, SPARSE, MODE_VEC8, 1, 1>(id, p, s);

@@ -26,18 +26,23 @@ def test_both_sides_of_the_lines(tmp_path):
     want = {}
     for kind in ((0, 1, 0), (1, 1, 0), (1, 1, 1)):
         want.update({(c, LARGE) + kind: t for c, t in ((96, 2), (128, 2), (129, 7), (160, 7), (161, 2), (288, 2))})
-    want.update({(c, LARGE, 1, 0, 0): t for c, t in ((65, 6), (96, 6), (97, 2), (128, 2), (129, 6), (192, 6), (193, 2), (256, 2), (257, 6), (288, 6), (289, 2), (512, 2))})
-    want.update({(c, LARGE) + kind: 2 for c in (96, 160, 288) for kind in ((0, 0, 0), (1, 0, 1))})
+    for kind in ((0, 0, 0), (1, 0, 0)):
+        want.update({(c, LARGE) + kind: t for c, t in ((65, 6), (96, 6), (97, 2), (128, 2), (129, 6), (192, 6), (193, 2), (256, 2), (257, 6), (288, 6), (289, 2), (448, 2))})
+    want.update({(c, LARGE, 1, 0, 1): 2 for c in (96, 160, 288)})
+    # 96 rows by workgroups per compute unit (one tile of rows)
+    for kind, lo in (((0, 0, 0), 3), ((1, 0, 0), 2), ((0, 1, 0), 3), ((1, 1, 1), 3)):
+        sparse = kind[1]
+        want.update({(96, 64 * 256 * n + more) + kind: t for n, more, t in ((lo, 0, 2), (lo, 1, 6), (5, 0, 6), (5, 1, 2), (6, 0, 2), (6, 1, 2 if sparse else 6))})
     want.update({(64, LARGE, 1, 0, 0): 0, (136, 64 * 129, 0, 1, 0): 5, (136, 64 * 128, 0, 1, 0): 4})      # the others keep theirs
     out = subprocess.run([str(exe)], input="".join("%d %d %d %d %d\n" % k for k in want), capture_output=True, text=True, check=True).stdout.split()
     assert [int(o) for o in out] == list(want.values())
 
 
-# a last tile of one pixel, 257 tiles of pixels; K below 512 in 2-byte units and no multiple of a step
+# a last tile of one pixel, 257 or 307 tiles of pixels; K below 512 in 2-byte units and no multiple of a step
 @pytest.mark.gpu
-@pytest.mark.parametrize("cout", [129, 160, 192, 257])
+@pytest.mark.parametrize("cout", [129, 160, 192, 257, 280])
 def test_choice_against_128_rows(ss, force_tile, cout):
-    H, W = 5, 3277                                        # 16385 pixels
+    H, W = (5, 3277) if cout < 280 else (5, 3917)         # 16385 and 19585 pixels: two, and (280 channels) three and a half workgroups of each tile of rows per unit
     for sparse in (True, False):
         for mod, make, cin in ((q8, wl.make_inputs_q8, 48), (f8, wl.make_inputs_f8, 48), (None, wl.make_inputs, 24)):
             L = (mod or tail)._L(1, H, W, cin, cout, 3, p=1, korder=wl.K_RSC, seed=cout, **({} if mod else {"dtype": wl.BF16, "act": wl.ACT_RELU}))
