@@ -118,6 +118,15 @@ __device__ __forceinline__ Acc<DT> mma_sparse(u32x4 a, const B32 &b, Acc<DT> c, 
                                                           (int)idx, 0, 0);
 }
 
+// A 16-byte buffer store at a lane's offset plus a uniform one.  The sum is the lane's operand and not the instruction's scalar offset: without a scalar
+// offset the compiler keeps the store's data registers unwritten for two wait states behind it, with one it takes none to be needed, and a vector
+// instruction that followed at once has changed the stored words (a pixel's first dword was that instruction's result, now and then).
+template <int POLICY = 0>
+__device__ __forceinline__ void store_b128(const u32x4 &v, const __amdgpu_buffer_rsrc_t &r, int lane_off, int off)
+{
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, lane_off + off, 0, POLICY);
+}
+
 // Workgroup barrier that orders LDS traffic only: the waves' outstanding global loads (weight ring, staging loads)
 // and stores (output tile) stay in flight across it.
 __device__ __forceinline__ void lds_barrier()
@@ -907,7 +916,7 @@ void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, Con
 #pragma unroll
                         for (int q = 0; q < 4; q++) {
                             const f32x4 fw = {(float)acc[tm][tn][4 * q + 0], (float)acc[tm][tn][4 * q + 1], (float)acc[tm][tn][4 * q + 2], (float)acc[tm][tn][4 * q + 3]};
-                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, fw), rp, (((tm * TN + tn) * 4 + q) * NMATH + mtid) * 16, split * (BM * BN * 4), kDeviceScope);
+                            store_b128<kDeviceScope>(__builtin_bit_cast(u32x4, fw), rp, (((tm * TN + tn) * 4 + q) * NMATH + mtid) * 16, split * (BM * BN * 4));
                         }
             }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wave's partial sums have been acknowledged
@@ -1108,7 +1117,7 @@ void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, Con
                         }
                         const u32x4 w = finish(v, p.act2, floor2);
                         *reinterpret_cast<u32x4 *>(Ts + run_px(tn, j) * kThirdRow + wave * 32 + (l & 3) * 8) = w;
-                        __builtin_amdgcn_raw_buffer_store_b128(w, ry2, (int)(run_px(tn, j) * row2 + (l & 3) * 16), mt * 64, 0);
+                        store_b128(w, ry2, (int)(run_px(tn, j) * row2 + (l & 3) * 16), mt * 64);
                     }
                 }
                 lds_barrier();
@@ -1131,7 +1140,7 @@ void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, Con
                 for (int j = 0; j < 2; j++) {
                     float v[8];
                     get(j, v);
-                    __builtin_amdgcn_raw_buffer_store_b128(finish(v, p.act3, floor3), ry3, (int)(run_px(half3, j) * row3 + (l & 3) * 16), ((wave >> 1) + 2 * i) * 64, 0);
+                    store_b128(finish(v, p.act3, floor3), ry3, (int)(run_px(half3, j) * row3 + (l & 3) * 16), ((wave >> 1) + 2 * i) * 64);
                 }
             }
             return;
@@ -1578,7 +1587,7 @@ void mlp_kernel(MlpParams p)
                     const uint32_t rr = rres2[ti][j][e];
                     w[e] = cvt_pack2<DT>(act2(v[2 * e] + widen<DT>((uint16_t)(rr & 0xFFFFu))), act2(v[2 * e + 1] + widen<DT>((uint16_t)(rr >> 16))));
                 }
-                __builtin_amdgcn_raw_buffer_store_b128(w, ry, out_lane(j), out_row(ti), 0);
+                store_b128(w, ry, out_lane(j), out_row(ti));
             }
         }
     };
@@ -1788,8 +1797,8 @@ void mlp_resident_kernel(MlpParams p)
                         d[q][e] = cvt_pack2<DT>(act2(acc2[t][4 * q + 2 * e] + widen<DT>((uint16_t)(rr[q][e] & 0xFFFFu))),
                                                 act2(acc2[t][4 * q + 2 * e + 1] + widen<DT>((uint16_t)(rr[q][e] >> 16))));
                 swap_halves(d);
-                __builtin_amdgcn_raw_buffer_store_b128(u32x4{d[0][0], d[0][1], d[2][0], d[2][1]}, ry, px_at, t * 64, 0);
-                __builtin_amdgcn_raw_buffer_store_b128(u32x4{d[1][0], d[1][1], d[3][0], d[3][1]}, ry, px_at, t * 64 + 16, 0);
+                store_b128(u32x4{d[0][0], d[0][1], d[2][0], d[2][1]}, ry, px_at, t * 64);
+                store_b128(u32x4{d[1][0], d[1][1], d[3][0], d[3][1]}, ry, px_at, t * 64 + 16);
             }
         };
         if (p.act2 == SS_ACT_GELU) finish([](float z) { return gelu_cdf<DT>(z); });
