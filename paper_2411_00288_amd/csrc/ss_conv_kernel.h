@@ -372,7 +372,7 @@ constexpr size_t smem_body(bool with_residual, int fuse_waves = 0, bool third = 
 template <int BM, int BN, int MODE, int KH, int KW, bool DEEP>
 constexpr size_t smem_bytes(bool with_residual, int fuse_waves = 0, bool third = false)
 {
-    return smem_body<BM, BN, MODE, KH, KW, DEEP>(with_residual, fuse_waves, third) + (size_t)BM * 4;
+    return smem_body<BM, BN, MODE, KH, KW, DEEP>(with_residual, fuse_waves, third) + (size_t)(third && BM < 128 ? 128 : BM) * 4;      // (the first bias, later the third: up to 128 channels)
 }
 
 // Waves per SIMD the register allocator must leave room for: small wave tiles are latency-bound
@@ -982,11 +982,15 @@ void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, Con
                 }
             }
         };
+        float bias3 = 0.f;
+        if constexpr (THIRD > 0)
+            if (tid < p.Cout3 && p.bias3 != nullptr) bias3 = p.bias3[tid];      // (at most 128 channels)
         if (!producer) {
             if (p.act == SS_ACT_GELU) to_lds(gelu); else to_lds(relu_or_id);
         }
         __syncthreads();
         if constexpr (THIRD > 0) {
+            if (tid < p.Cout3) bias_s[tid] = bias3;       // (the first layer's is done with; read behind the barriers below)
             // ---- second and third contraction, 128 channels of the second one's output at a time: each wave finishes one row tile of 32
             // (stored as in the pair below, and left in LDS), then multiplies the third one's weights with the 128 channels; its
             // accumulators stay in registers.  The weights and the residual of the next 128 are in flight meanwhile.
@@ -999,7 +1003,7 @@ void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, Con
             };
             const __amdgpu_buffer_rsrc_t ra2 = buffer(p.a2_vals, p.a2_bytes), rm2 = buffer(p.a2_meta, p.meta2_bytes);
             const __amdgpu_buffer_rsrc_t ra3 = buffer(p.a3_vals, p.a3_bytes), rm3 = buffer(p.a3_meta, p.meta3_bytes);
-            const __amdgpu_buffer_rsrc_t rb2 = buffer(p.bias2, (unsigned)p.Cout2 * 4u), rb3 = buffer(p.bias3, (unsigned)p.Cout3 * 4u);
+            const __amdgpu_buffer_rsrc_t rb2 = buffer(p.bias2, (unsigned)p.Cout2 * 4u);
             // outputs and residual of this workgroup's pixels: whatever lies behind the last one is out of range
             const unsigned px_here = (unsigned)min(BN, p.P - n0), row2 = (unsigned)p.Cout2 * 2u, row3 = (unsigned)p.Cout3 * 2u;
             const __amdgpu_buffer_rsrc_t rres = buffer(p.res2 != nullptr ? p.res2 + (size_t)n0 * p.Cout2 : nullptr, px_here * row2);
@@ -1027,15 +1031,11 @@ void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, Con
                 if constexpr (SPARSE) return mma_sparse<DT>(r.v[0][s], b, d, r.idx[s] >> ((s & 1) * 16));
                 else return mma_dense<DT>(r.v[1][s], b.hi, mma_dense<DT>(r.v[0][s], b.lo, d));
             };
-            auto start = [&](const __amdgpu_buffer_rsrc_t &rb, int row) {      // the bias starts in the accumulators
-                f32x16 d;
+            // The sums start from zero and the bias follows them, as in the pair and in the layer's own call: the bits are the same.  The second layer's bias
+            // waits as one value per lane and crosses LDS behind the first rows of the wave's region: there are no registers for a lane's eight channels.
+            auto clear = [](f32x16 &d) {
 #pragma unroll
-                for (int q = 0; q < 4; q++) {
-                    const f32x4 b = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rb, g * 16, (row + 8 * q) * 4, 0));
-#pragma unroll
-                    for (int e = 0; e < 4; e++) d[4 * q + e] = b[e];
-                }
-                return d;
+                for (int v = 0; v < 16; v++) d[v] = 0.f;
             };
             // a lane's 16-byte run number j of a 32 x 32 tile at pixel half tn: pixel and run of 8 channels
             auto run_px = [&](int tn, int j) { return tn * 32 + 16 * j + (l >> 2); };
@@ -1043,7 +1043,7 @@ void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, Con
             auto row3_of = [&](int i) { return min((wave >> 1) + 2 * i, p.Mt3 - 1); };
             f32x16 acc3[ITEMS3];
 #pragma unroll
-            for (int i = 0; i < ITEMS3; i++) acc3[i] = start(rb3, row3_of(i) * 32);
+            for (int i = 0; i < ITEMS3; i++) clear(acc3[i]);
             Rows w2, w3[ITEMS3];
             u32x4 res[2][2];
             load_steps(w2, ra2, rm2, wave, p.Ks2, p.Kp2, 0, p.Ks2);
@@ -1052,11 +1052,12 @@ void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, Con
 #pragma unroll
                 for (int q = 0; q < 4; q++) *reinterpret_cast<f32x4 *>(reg + c * kFuseRow + 8 * q + 4 * g) = f32x4{d[4 * q], d[4 * q + 1], d[4 * q + 2], d[4 * q + 3]};
             };
-            auto get = [&](int j, float (&v)[8]) {        // (a wave's LDS operations execute in order: it sees what put left)
+            auto get = [&](int j, const float *bias, int next, float (&v)[8]) {      // (a wave's LDS operations execute in order: it sees what put left)
                 const float *src = reg + (16 * j + (l >> 2)) * kFuseRow + (l & 3) * 8;
                 const f32x4 lo = *reinterpret_cast<const f32x4 *>(src), hi = *reinterpret_cast<const f32x4 *>(src + 4);
+                const f32x4 bl = *reinterpret_cast<const f32x4 *>(bias), bh = *reinterpret_cast<const f32x4 *>(bias + next);
 #pragma unroll
-                for (int e = 0; e < 4; e++) { v[e] = lo[e]; v[4 + e] = hi[e]; }
+                for (int e = 0; e < 4; e++) { v[e] = lo[e] + bl[e]; v[4 + e] = hi[e] + bh[e]; }
             };
             auto finish = [&](float (&v)[8], int act, float floor) {
                 if (act == SS_ACT_GELU) {
@@ -1085,7 +1086,9 @@ void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, Con
                         res[tn][j] = once ? __builtin_amdgcn_raw_buffer_load_b128(rres, (int)(run_px(tn, j) * row2 + (l & 3) * 16), mt * 64, kNonTemporal)
                                           : __builtin_amdgcn_raw_buffer_load_b128(rres, (int)(run_px(tn, j) * row2 + (l & 3) * 16), mt * 64, 0);
                 f32x16 acc2[2];
-                acc2[0] = acc2[1] = start(rb2, mt * 32);
+                clear(acc2[0]);
+                clear(acc2[1]);
+                const float bias2 = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rb2, c * 4, mt * 128, 0));
 #pragma unroll
                 for (int i = 0; i < ITEMS3; i++) load_steps(w3[i], ra3, rm3, row3_of(i), p.Ks3, p.Kp3, part * 4, 4);
 #pragma unroll
@@ -1103,13 +1106,17 @@ void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, Con
                     }
                 }
                 load_steps(w2, ra2, rm2, min(mt + 4, p.Mt2 - 1), p.Ks2, p.Kp2, 0, p.Ks2);
+                int at = l;
+                asm volatile("" : "+v"(at));              // (addresses worked out in each part: kept over them, they would spill)
+                reg[(at & 31) / 4 * kFuseRow + 32 + at % 4] = bias2;
+                const float *const bias = reg + at % 4 * 2 * kFuseRow + 32;
 #pragma unroll
                 for (int tn = 0; tn < 2; tn++) {
                     put(acc2[tn]);
 #pragma unroll
                     for (int j = 0; j < 2; j++) {
                         float v[8];
-                        get(j, v);
+                        get(j, bias, kFuseRow, v);
 #pragma unroll
                         for (int e = 0; e < 4; e++) {
                             v[2 * e] += widen<ODT>((uint16_t)(res[tn][j][e] & 0xFFFFu));
@@ -1139,7 +1146,7 @@ void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, Con
 #pragma unroll
                 for (int j = 0; j < 2; j++) {
                     float v[8];
-                    get(j, v);
+                    get(j, bias_s + row3_of(i) * 32 + (l & 3) * 8, 4, v);
                     store_b128(finish(v, p.act3, floor3), ry3, (int)(run_px(half3, j) * row3 + (l & 3) * 16), ((wave >> 1) + 2 * i) * 64);
                 }
             }

@@ -34,6 +34,7 @@ struct ConvParams {
     uint16_t *y3;             // [P][Cout3]
     int Cout3, Ks3, Kp3, Mt3, act3;
     unsigned a3_bytes, meta3_bytes;
+    int shares3, per3;        // few pixels: the shares in which this reduction is added up (pw_shares), and the steps of one
     // split reduction: workgroups per output tile (1 = none), fp32 partial sums [tile][split][BM*BN] and one ticket
     // counter per tile, both in the caller's workspace
     int nsplit, plan_tile, plan_bm, plan_bn;      // plan_*: the tile the split was planned (and the workspace sized) for
@@ -305,6 +306,15 @@ static inline int small_variant(const ConvParams &p, int taps, bool sparse, int 
     if (b64 <= ncu && (taps ? nw == 8 && sparse : p.Ks >= 16)) return SMALL_64X32;
     if (!taps && p.Ks <= 20 && b32 <= 2ll * ncu) return SMALL_32;
     return SMALL_NONE;
+}
+
+// Shares of equal numbers of steps, added up in their order, in which a 1x1 layer's own call adds its reduction (1: one chain of products).
+static inline int pw_shares(int P, int Ks, int Mt, bool sparse, int ncu)
+{
+    ConvParams q{};
+    q.P = P; q.Ks = Ks; q.Mt = Mt;
+    const int variant = small_variant(q, 0, sparse, ncu);
+    return variant == SMALL_NONE ? 1 : small_waves(q, 0, variant == SMALL_16);
 }
 
 // Would the library by itself run this problem on one of them?

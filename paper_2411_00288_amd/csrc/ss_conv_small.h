@@ -470,10 +470,14 @@ static inline __host__ __device__ PairShape pair_shape(int px, int nchunks, int 
     return h;
 }
 
-// THIRD: as in conv_kernel.  The second layer's output stays in LDS as well; the waves split the third one's rows and reduction as they do the first one's.
+// THIRD: as in conv_kernel.  The second layer's output stays in LDS as well, and the waves split the third one's rows and reduction.  Its sums are those of
+// its own call, share for share (pw_shares), so that both give the same bits: a wave has one share; or two, where there are more of them than
+// waves to a row tile; or begins or ends one that is longer than the eight steps a wave holds weights for, the second taking the sums over
+// through LDS.  (A kernel each: with the three in one, decided at run time, the 64- and 128-channel ones took 0.74 and 0.96 us longer on one image.)
+enum { THIRD_NONE = 0, THIRD_SHARE = 1, THIRD_TWO = 2, THIRD_HANDED = 3 };
 // MT: the first layer's row tiles (2 or 4: a bottleneck of 64 or 128 channels), or 0 where they are known at run time only.  Known, the
 // waves' shares and the loops over them are constants, and every LDS read of a phase is under way before the first is needed.
-template <int DT, bool SPARSE, int PX, int MT, bool THIRD>
+template <int DT, bool SPARSE, int PX, int MT, int THIRD>
 __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams p)
 {
     if constexpr (MT > 0) { p.Mt = p.Ks2 = MT; p.Cout = 32 * MT; }
@@ -486,7 +490,7 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
     const int n0 = blockIdx.x * PX;
     const int HoWo = p.Ho * p.Wo;
     const int nchunks = (int)((unsigned)p.Ks / TAPS);     // cin % 32 == 0
-    const PairShape sh = pair_shape(PX, nchunks, p.Cout, THIRD ? p.Cout2 : 0);
+    const PairShape sh = pair_shape(PX, nchunks, p.Cout, THIRD != THIRD_NONE ? p.Cout2 : 0);
     u32x4 *const stage = reinterpret_cast<u32x4 *>(smem);
     u32x4 *const part = reinterpret_cast<u32x4 *>(reinterpret_cast<char *>(smem) + sh.stage);
     uint16_t *const tile = reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(smem) + sh.stage + sh.part);
@@ -649,10 +653,9 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
     lds_barrier();
     // ---- the third layer's weights: in flight while the second one is multiplied
     constexpr int KS3 = THIRD ? 8 : 1;
-    const int lg3 = THIRD ? (p.Mt3 == 2 ? 2 : 1) : 0;     // (2 <= Mt3 <= 4, Ks3 <= 16: eight steps per wave at most)
-    const int kg3 = THIRD ? (p.Mt3 == 2 ? wave >> 1 : p.Mt3 == 3 ? wave * 11 >> 5 : wave >> 2) : 0, rt3 = wave - kg3 * p.Mt3;
-    const bool works3 = THIRD && kg3 < 1 << lg3;
-    const int t0 = works3 ? kg3 * p.Ks3 >> lg3 : 0, t1 = works3 ? (kg3 + 1) * p.Ks3 >> lg3 : 0;
+    const int kg3 = THIRD ? (p.Mt3 == 2 ? wave >> 1 : p.Mt3 == 3 ? wave * 11 >> 5 : wave >> 2) : 0, rt3 = wave - kg3 * p.Mt3;      // (2 <= Mt3 <= 4)
+    const int span3 = THIRD == THIRD_SHARE ? p.per3 : THIRD == THIRD_TWO ? 2 * p.per3 : KS3;      // (a multiple of 4 steps in all, 16 at most)
+    const int t0 = THIRD ? min(kg3 * span3, p.Ks3) : 0, t1 = THIRD ? min(t0 + span3, p.Ks3) : 0;
     A a3[KS3];
     if constexpr (THIRD) {
         const __amdgpu_buffer_rsrc_t ra3 = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.a3_vals), 0, (int)p.a3_bytes, kRsrcFlags);
@@ -751,13 +754,56 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
             b3[j].lo = *reinterpret_cast<const u32x4 *>(src);
             b3[j].hi = *reinterpret_cast<const u32x4 *>(src + 8);
         }
+        // Partial sums: a row tile's pixels of one quad of channels in a row, turned by the quad's number, so that the threads below, which go over the
+        // channels first, find them in different banks (not turned, each of their reads took 0.2 us).
+        auto place = [&](int m, int cq, int pl) { return (cq >> 1) * 64 + (cq & 1) * 32 + ((pl + cq + 8 * m) & (PX - 1)); };
+        auto keep = [&](u32x4 *to, const f32x16 &sums) {
 #pragma unroll
-        for (int j = 0; j < KS3; j++)
-            if (t0 + j < t1) acc3 = mma(a3[j], b3[j], acc3, t0 + j);      // uniform
+            for (int q = 0; q < 4; q++) to[place(rt3, 2 * q + g, cc)] = __builtin_bit_cast(u32x4, f32x4{sums[4 * q], sums[4 * q + 1], sums[4 * q + 2], sums[4 * q + 3]});
+        };
+        // A wave's second share: with 16 pixels behind the first one's, from the lanes that repeat its columns; else where the staged input was.
+        u32x4 *const part2 = PX == 16 ? part + 16 : stage;
+        auto multiply = [&]() {
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const f32x4 w = {acc3[4 * q], acc3[4 * q + 1], acc3[4 * q + 2], acc3[4 * q + 3]};
-            part[wave * 256 + q * 64 + lane] = __builtin_bit_cast(u32x4, w);
+            for (int j = 0; j < KS3; j++)
+                if (t0 + j < t1) acc3 = mma(a3[j], b3[j], acc3, t0 + j);      // uniform
+            keep(part + wave * 256, acc3);
+        };
+        if constexpr (THIRD == THIRD_TWO) {
+            f32x16 second = acc3;
+            constexpr int PER = KS3 / 2;                  // steps of a share: four, or three of twelve in all
+#pragma unroll
+            for (int j = 0; j < PER; j++) {
+                if (j == PER - 1 && p.per3 < PER) break;  // uniform
+                acc3 = mma(a3[j], b3[j], acc3, t0 + j);
+            }
+            if (p.per3 < PER) second = mma(a3[PER - 1], b3[PER - 1], second, t0 + PER - 1);
+#pragma unroll
+            for (int j = PER; j < KS3; j++)
+                if (t0 + j < t1) second = mma(a3[j], b3[j], second, t0 + j);
+            // (waves without a row tile have multiplied nothing of use: their places are not read)
+            if constexpr (PX == 16) {
+#pragma unroll
+                for (int v = 0; v < 16; v++) acc3[v] = c < PX ? acc3[v] : second[v];
+                keep(part + wave * 256 + (c & 16), acc3);
+            } else {
+                keep(part + wave * 256, acc3);
+                keep(part2 + wave * 256, second);
+            }
+        } else if constexpr (THIRD == THIRD_HANDED) {
+            if (kg3 == 0) multiply();
+            lds_barrier();
+            if (kg3 == 1) {
+#pragma unroll
+                for (int q = 0; q < 4; q++) {
+                    const f32x4 u = __builtin_bit_cast(f32x4, part[rt3 * 256 + place(rt3, 2 * q + g, cc)]);
+#pragma unroll
+                    for (int e = 0; e < 4; e++) acc3[4 * q + e] = u[e];
+                }
+                multiply();
+            }
+        } else {
+            multiply();
         }
         lds_barrier();
         const float floor3 = p.act3 == SS_ACT_RELU ? 0.f : -__builtin_inff();
@@ -767,16 +813,27 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
             const int q = quad3(i, &pl), m = q >> 3, cq = q & 7, o = q * 4;
             if (pl >= PX) break;                          // (fewer than four row tiles)
             float v[4] = {0.f, 0.f, 0.f, 0.f};
-            auto add = [&](int k) {
-                const f32x4 u = __builtin_bit_cast(f32x4, part[(k * p.Mt3 + m) * 256 + (cq >> 1) * 64 + (cq & 1) * 32 + pl]);
+            const u32x4 *const from = part + m * 256 + place(m, cq, pl);
+            auto add = [&](int at) {
+                const f32x4 u = __builtin_bit_cast(f32x4, from[at]);
 #pragma unroll
                 for (int e = 0; e < 4; e++) v[e] += u[e];
             };
-            add(0);
-            add(1);
-            if (lg3 == 2) {                               // uniform
-                add(2);
-                add(3);
+            const int next = p.Mt3 * 256, other = (int)(part2 - part);      // from a row tile's wave to its next one, from a share to the wave's second
+            if constexpr (THIRD == THIRD_TWO) {
+                add(0);
+                add(other);
+                add(next);
+                add(next + other);
+            } else if constexpr (THIRD == THIRD_HANDED) {
+                add(next);
+            } else {
+                add(0);
+                if (p.shares3 > 1) add(next);             // uniform
+                if (p.shares3 > 2) {
+                    add(2 * next);
+                    add(3 * next);
+                }
             }
 #pragma unroll
             for (int e = 0; e < 4; e++) v[e] += bias3[i][e];
@@ -793,11 +850,11 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
     }
 }
 
-template <int DT, bool SPARSE, int PX, int MT, bool THIRD>
+template <int DT, bool SPARSE, int PX, int MT, int THIRD>
 static int launch_pair_small(ConvParams p, hipStream_t s)
 {
     fast_div_setup((unsigned)p.Mt, &p.tm_mul, &p.tm_sh);      // (the kernel deals its waves out over the row tiles)
-    const size_t smem = pair_shape(PX, p.Ks / 9, p.Cout, THIRD ? p.Cout2 : 0).total;
+    const size_t smem = pair_shape(PX, p.Ks / 9, p.Cout, THIRD != THIRD_NONE ? p.Cout2 : 0).total;
     auto kern = pair_small_kernel<DT, SPARSE, PX, MT, THIRD>;
     if (smem > 64 * 1024) {
         static std::atomic<unsigned long long> done_mask{0};      // as in launch(): once per device
@@ -828,11 +885,28 @@ static int pair_small(const ss_weight_desc *d1, const ConvParams &p, int px, hip
     const bool third = p.Cout3 > 0;
     if (px == 0 || pair_shape(px, p.Ks / 9, p.Cout, third ? p.Cout2 : 0).total > 160 * 1024) return SS_ERR_INVALID_ARG;
     if (third && (p.Mt3 < 2 || p.Mt3 > 4 || p.Ks3 > 16)) return SS_ERR_INVALID_ARG;
+    ConvParams q = p;
+    int plan = THIRD_NONE;
+    if (third) {
+        const int ncu = compute_units();
+        if (ncu <= 0) return SS_ERR_HIP;
+        q.shares3 = pw_shares(p.P, p.Ks3, p.Mt3, SPARSE, ncu);
+        q.per3 = p.Ks3 / q.shares3;
+        plan = q.per3 > 8 ? THIRD_HANDED : (q.shares3 > 2 && p.Mt3 > 2 ? THIRD_TWO : THIRD_SHARE);
+    }
     auto go = [&](auto mt) -> int {
         constexpr int MT = decltype(mt)::value;
-        if constexpr (MT > 0)
-            if (third) return px == 16 ? launch_pair_small<DT, SPARSE, 16, MT, true>(p, s) : launch_pair_small<DT, SPARSE, 32, MT, true>(p, s);
-        return third ? (int)SS_ERR_INVALID_ARG : px == 16 ? launch_pair_small<DT, SPARSE, 16, MT, false>(p, s) : launch_pair_small<DT, SPARSE, 32, MT, false>(p, s);
+        auto pixels = [&](auto t) -> int {
+            constexpr int THIRD = decltype(t)::value;
+            return px == 16 ? launch_pair_small<DT, SPARSE, 16, MT, THIRD>(q, s) : launch_pair_small<DT, SPARSE, 32, MT, THIRD>(q, s);
+        };
+        using std::integral_constant;
+        if constexpr (MT > 0) {
+            if (plan == THIRD_SHARE) return pixels(integral_constant<int, THIRD_SHARE>{});
+            if (plan == THIRD_TWO) return pixels(integral_constant<int, THIRD_TWO>{});
+            if (plan == THIRD_HANDED) return pixels(integral_constant<int, THIRD_HANDED>{});
+        }
+        return third ? (int)SS_ERR_INVALID_ARG : pixels(integral_constant<int, THIRD_NONE>{});
     };
     using std::integral_constant;
     return p.Mt == 2 ? go(integral_constant<int, 2>{}) : p.Mt == 4 ? go(integral_constant<int, 4>{}) : go(integral_constant<int, 0>{});

@@ -80,7 +80,7 @@ def test_refused_and_queried(ss):
 
 @pytest.mark.parametrize("batch,image,sparse,joined_layers", [(1, 64, True, 6), (1, 64, False, 3), (5, 224, True, 6), (5, 224, False, 2)])
 def test_trunk_with_joined_layers_equals_its_single_launches(ss, batch, image, sparse, joined_layers):
-    """Every buffer that the joined kernels write, against the pair's and the layer's own launches (which differ in the order of fp32 sums)."""
+    """Every buffer that the joined kernels write, against the pair's and the layer's own launches."""
     from paper_2411_00288_amd import resnet50
     t = resnet50.Trunk(batch=batch, image=image, dtype=wl.BF16, sparse=sparse)
     assert len(t.launches) - len(t.chain) == joined_layers + 1      # (and the pooling)
