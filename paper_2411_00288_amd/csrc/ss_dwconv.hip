@@ -4,6 +4,7 @@
 // 128 x 56 x 56 x 96 layer before any load or conversion (99 us measured).
 #include "ss_internal.h"
 #include "ss_conv_params.h"
+#include "ss_dwconv.h"
 
 namespace ss {
 
@@ -469,10 +470,6 @@ struct DwFewParams {
     unsigned run_mul, wq_mul, hq_mul, shifts;      // divisions by C / 2, ceil(Wo / TWF) and ceil(Ho / ROWS)
 };
 static_assert(sizeof(DwFewParams) <= 112, "a cheap launch");
-constexpr int kDwFewTaps = 8192;          // K K C at most: 32 KiB of LDS
-// (A column outside the image is an offset of 2 GiB, and must stay out of range on all of a thread's rows.)
-static inline bool few_fits(int W, int C, int K) { return K * K * C <= kDwFewTaps && (long long)(K + 3) * W * C * 2 < (1ll << 31); }
-
 template <int DT>
 __device__ __forceinline__ void widen2(uint32_t v, float &a, float &b)
 {
@@ -611,46 +608,25 @@ template <int DT>
 static int launch_dw(const uint16_t *x, const uint16_t *w, const float *bias, uint16_t *y, int N, int H, int W, int C, int kh,
                      int kw, int ph, int pw, int Ho, int Wo, int act, unsigned x_bytes, hipStream_t s)
 {
-    const long long ybytes = (long long)N * Ho * Wo * C * 2;
-    // Few outputs: the kernel for them, 3x3 always.  Against the vector one it wins everywhere (above); against the matrix one, us: 5x5 16 x 56 x 56 x 96
-    // (4.8 M outputs) 10.0 / 10.3, 64 x 28 x 28 x 128 (6.4 M) 11.9 / 11.2; 7x7 8 x 56 x 56 x 96 (2.4 M) 9.35 / 10.6, 12 x 56 x 56 x 96 (3.6 M) 11.0 / 10.95, 16 (4.8 M)
-    // 13.5 / 11.6.  Rows per thread: 3x3 at 1.9 M outputs 4.2 / 4.3 / 4.7 for one, two and four, 4.8 M 7.5 / 6.3 / 6.6, 9.6 M 14 / 11.1 / 10.2; 7x7 at
-    // 1.4 M 6.6 / 7.1 for one and two, 1.9 M 8.0 / 7.6.  7x7 in pairs of columns while that is one workgroup per compute unit: 14 x 14 x 14 x 96 4.4 -> 3.9.
-    // The matrix kernel costs about the same for every filter width and has a longer set-up.  Measured against the vector one, where the taps or
-    // the rows do not fit the kernel for few outputs: 7x7 faster or equal from 1 x 7 x 7 x 96 up, 5x5 from about 4 M outputs.
-    // (Its offsets outside the image start at 2 GiB and move on by a row per step, from the first padding row to the image's last: they must not
-    // come round to the image again.)
-    const bool rows_fit = ((long long)H + ph) * W * C * 2 < (1ll << 31);
-    const int forced = forced_tile();                     // test hook: 60 vector kernel, 61 matrix kernel, 62 to 65 few outputs
-    if (kh == kw && few_fits(W, C, kw) && forced != 60 && forced != 61) {
-        const long long outputs = (long long)N * Ho * Wo * C;
+    const DwShape shape{N, H, W, C, kh, kw, ph, Ho, Wo};
+    const int forced = forced_tile(), ncu = compute_units();      // test hook: the kernels by their ids
+    if (ncu <= 0) return SS_ERR_HIP;
+    const int id = forced >= DW_VECTOR && forced <= DW_FEW_4X4 && dw_fits(shape, forced) ? forced : choose_dw(shape, ncu);
 #define SS_DW_FEW(K, TWF, ROWS) launch_dw_few<DT, K, TWF, ROWS>(x, w, bias, y, N, H, W, C, ph, pw, Ho, Wo, act, x_bytes, s)
-        if (kw == 3) {
-            const int rows = forced == 63 ? 1 : (forced == 64 ? 2 : (forced == 65 ? 4 : (outputs < 2500000 ? 1 : (outputs < 8000000 ? 2 : 4))));
-            return rows == 1 ? SS_DW_FEW(3, 4, 1) : (rows == 2 ? SS_DW_FEW(3, 4, 2) : SS_DW_FEW(3, 4, 4));
-        }
-        if (kw == 5 && (outputs < 5000000 || forced == 63)) return SS_DW_FEW(5, 4, 1);
-        if (kw == 7 && (outputs < 3200000 || (forced >= 62 && forced <= 64))) {
-            const int ncu = compute_units();
-            if (ncu <= 0) return SS_ERR_HIP;
-            const bool narrow = (long long)N * Ho * ((Wo + 1) / 2) * (C / 2) <= 256ll * ncu;
-            if (forced == 62 || (forced < 62 && narrow)) return SS_DW_FEW(7, 2, 1);
-            return forced == 64 || (forced != 63 && outputs >= 1700000) ? SS_DW_FEW(7, 4, 2) : SS_DW_FEW(7, 4, 1);
-        }
-#undef SS_DW_FEW
+    if (id >= DW_FEW_1X2) {
+        if (kw == 3) return id == DW_FEW_1X4 ? SS_DW_FEW(3, 4, 1) : (id == DW_FEW_2X4 ? SS_DW_FEW(3, 4, 2) : SS_DW_FEW(3, 4, 4));
+        if (kw == 5) return SS_DW_FEW(5, 4, 1);
+        return id == DW_FEW_1X2 ? SS_DW_FEW(7, 2, 1) : (id == DW_FEW_2X4 ? SS_DW_FEW(7, 4, 2) : SS_DW_FEW(7, 4, 1));
     }
-    if (kh == kw && rows_fit && ybytes < (1ll << 31) && forced != 60 && (kw == 7 || (kw == 5 && (ybytes >= (8ll << 20) || forced == 61)))) {
+#undef SS_DW_FEW
+    if (id == DW_MATRIX) {
         DwParams p{};
         p.x = x; p.w = w; p.bias = bias; p.y = y;
         p.H = H; p.W = W; p.C = C; p.ph = ph; p.pw = pw; p.Ho = Ho; p.Wo = Wo; p.act = act;
         p.x_bytes = x_bytes;
         p.w_bytes = (unsigned)(kh * kw * C * 2);
-        p.y_bytes = (unsigned)ybytes;
-        switch (kw) {
-            case 5: return launch_dw_mfma<DT, 5>(p, N, s);
-            case 7: return launch_dw_mfma<DT, 7>(p, N, s);
-            default: return SS_ERR_UNSUPPORTED;
-        }
+        p.y_bytes = (unsigned)((long long)N * Ho * Wo * C * 2);
+        return kw == 5 ? launch_dw_mfma<DT, 5>(p, N, s) : launch_dw_mfma<DT, 7>(p, N, s);
     }
     const long long total = (long long)N * Ho * ((Wo + TW - 1) / TW) * (C / 8);
     if (total <= 0 || (total + 255) / 256 > 0x7FFFFFFFll) return SS_ERR_UNSUPPORTED;
