@@ -28,10 +28,14 @@ static inline bool dw_fits(const DwShape &s, int id)
     return (long long)s.N * ((s.Ho + rows - 1) / rows) * ((s.Wo + cols - 1) / cols) * (s.C / 2) <= 0x7FFFFF00ll;      // (its threads have 31-bit numbers)
 }
 
-// Few outputs: the kernel for them, 3x3 always.  Against the vector one it wins everywhere (see there); against the matrix one, us: 5x5 16 x 56 x 56 x 96
-// (4.8 M outputs) 10.0 / 10.3, 64 x 28 x 28 x 128 (6.4 M) 11.9 / 11.2; 7x7 8 x 56 x 56 x 96 (2.4 M) 9.35 / 10.6, 12 x 56 x 56 x 96 (3.6 M) 11.0 / 10.95, 16 (4.8 M)
-// 13.5 / 11.6.  Rows per thread: 3x3 at 1.9 M outputs 4.2 / 4.3 / 4.7 for one, two and four, 4.8 M 7.5 / 6.3 / 6.6, 9.6 M 14 / 11.1 / 10.2; 7x7 at
-// 1.4 M 6.6 / 7.1 for one and two, 1.9 M 8.0 / 7.6.  7x7 in pairs of columns while that is one workgroup per compute unit: 14 x 14 x 14 x 96 4.4 -> 3.9.
+// Few outputs: the kernel for them, 3x3 always.  Against the vector one it wins (see there), except on images of one row, of whose inputs it loads
+// the missing rows as well (3x3, from 2.5 M outputs on 1.1 to 2.2 of the vector kernel's time, below 0.7 to 0.9; 5x5 from 1.2 M on 1.1 to 1.45), and 5x5 on two
+// rows (from 2.5 M on 1.0 to 1.2).  Against the matrix one, us: 5x5 16 x 56 x 56 x 96
+// (4.8 M outputs) 10.0 / 10.3, 64 x 28 x 28 x 128 (6.4 M) 11.9 / 11.2; with more than 128 channels, whose taps each workgroup fetches whole, the line is the
+// vector kernel's, 11 x 47 x 63 x 152 (4.95 M) 13.7 / 10.8; 7x7 8 x 56 x 56 x 96 (2.4 M) 9.35 / 10.6, 12 x 56 x 56 x 96 (3.6 M) 11.0 / 10.95, 16 (4.8 M)
+// 13.5 / 11.6.  Rows per thread: 3x3 at 1.9 M outputs 4.2 / 4.3 / 4.7 for one, two and four, 4.8 M 7.5 / 6.3 / 6.6, 9.6 M 14 / 11.1 / 10.2 (four are 1.2 of
+// two where there are only two rows); 7x7 at 1.4 M 6.6 / 7.1 for one and two, 1.9 M 8.0 / 7.6.  7x7 in pairs of columns while that is one workgroup per
+// compute unit: 14 x 14 x 14 x 96 4.4 -> 3.9.
 // The matrix kernel costs about the same for every filter width and has a longer set-up.  Measured against the vector one, where the taps or
 // the rows do not fit the kernel for few outputs: 7x7 faster or equal from 1 x 7 x 7 x 96 up, 5x5 from about 4 M outputs.
 static inline int choose_dw(const DwShape &s, int ncu)
@@ -39,9 +43,9 @@ static inline int choose_dw(const DwShape &s, int ncu)
     const long long outputs = (long long)s.N * s.Ho * s.Wo * s.C;
     int few = -1;
     if (s.kw == 3) {
-        few = outputs < 2500000 ? DW_FEW_1X4 : (outputs < 8000000 ? DW_FEW_2X4 : DW_FEW_4X4);
+        if (s.H > 1 || outputs < 2500000) few = outputs < 2500000 ? DW_FEW_1X4 : (outputs < 8000000 || s.H == 2 ? DW_FEW_2X4 : DW_FEW_4X4);
     } else if (s.kw == 5) {
-        if (outputs < 5000000) few = DW_FEW_1X4;
+        if (outputs < (s.H == 1 ? 1200000 : (s.H == 2 ? 2500000 : (s.C > 128 ? 1 << 22 : 5000000)))) few = DW_FEW_1X4;
     } else if (outputs < 3200000) {
         const bool narrow = (long long)s.N * s.Ho * ((s.Wo + 1) / 2) * (s.C / 2) <= 256ll * ncu;
         few = narrow ? DW_FEW_1X2 : (outputs >= 1700000 ? DW_FEW_2X4 : DW_FEW_1X4);
