@@ -1612,15 +1612,6 @@ void mlp_kernel(MlpParams p)
 // the GELUs).  With the weights from memory for each wave the address unit took as long as the vector ALU; with an accumulator tile more, to
 // multiply ahead of the activations, three waves per SIMD had no registers left for weights on their way, and each matrix instruction waited for LDS.
 // 401408 pixels, 96 -> 384 -> 96, bf16, mlp_kernel against this one, us: ReLU sparse 69.0 -> 46.0, dense 88.9 -> 57.7; GELU dense 116.8 -> 98.6 (f16 114.9 -> 94.0).
-// The LDS copy is in the order of use, two row tiles of the intermediate (32 channels each) after the other, so that all offsets inside a pair are constants:
-// the first layer's tiles, the second layer's steps, their index words, the first layer's bias.
-template <bool SPARSE, int TILES>
-struct MlpPair {
-    static constexpr int STEP = SPARSE ? 1024 : 2048, KP1 = (TILES + 1) / 2, W2 = 2 * TILES * STEP, I1 = 2 * W2, I2 = I1 + (SPARSE ? 2 * KP1 * 256 : 0),
-                         BIAS = I2 + (SPARSE ? TILES * 256 : 0), BYTES = BIAS + 2 * 128;
-    static constexpr size_t smem(int Cmid) { return (size_t)(Cmid / 64) * BYTES + TILES * 128; }      // (with the second layer's bias)
-};
-
 // TILES: 32-channel tiles of the input and of the output; WAVES: per workgroup.
 template <int DT, bool SPARSE, int TILES, int WAVES, bool GELU1>
 __global__ __launch_bounds__(WAVES * 64)
@@ -1820,7 +1811,6 @@ void mlp_resident_kernel(MlpParams p)
 // its row tile at once, the whole intermediate meets in LDS, and the waves share out the second layer's row tiles and its reduction;
 // the partial sums are added in the order of the reduction.  Weights, input and residual are one memory latency.  What is left is mostly the
 // activation: 32 x 384 GELUs of 56 clocks on four SIMDs are 1.1 us of the 3.9 us that 96 -> 384 -> 96 on 3136 pixels takes (7.6 -> 5.5 us with the launch).
-constexpr int kMlpWideWaves = 16;                         // at most 512 intermediate channels
 constexpr int mlp_wide_smem(int cin, int waves)
 {
     const int tiles = 32 * (cin + 8) * 2 + 32 * (32 * waves + 8) * 2, sums = waves * (int)kFuseRegion;      // (the partial sums take the place of both tiles)
@@ -2032,8 +2022,6 @@ static int launch_mlp_wide(const MlpParams &p, hipStream_t s)
     }
 }
 
-constexpr size_t kMlpResidentSmem = 160 * 1024;
-
 // The resident kernel on so many channels, if its weights fit the LDS.
 template <int DT, bool SPARSE, int TILES>
 static int launch_mlp_resident(const MlpParams &p0, int ncu, hipStream_t s)
@@ -2061,39 +2049,16 @@ static int launch_mlp_resident(const MlpParams &p0, int ncu, hipStream_t s)
     return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP;
 }
 
-// Pixel tiles per compute unit from where the resident kernel pays, or -1 where there is none.  A SIMD that gets a tile more than its neighbours keeps
-// the chip waiting for it, and the weights' way to LDS is some 3 us, so it takes a few tiles per SIMD.  Times against mlp_kernel's at 1.6, 2.4, 3.2, 4, 5.5, 7 and
-// 12.25 tiles of 32 pixels per SIMD, bf16, C -> 4 C -> C:
-//   ReLU   sparse  96   0.85 0.82 0.78 0.80 0.77 0.72 0.68      dense  96   0.79 0.82 0.73 0.72 0.73 0.69 0.62
-//          sparse 128   0.94 0.96 0.88 0.85 0.86 0.79 0.76
-//   GELU   dense   96   0.95 1.01 0.95 0.86 0.90 0.83 0.84     (in a ConvNeXt block on new inputs each time 0.95 to 0.90, 173 -> 163 us at 128 x 56 x 56)
-// Not for the sparse path with GELU, where both are bound by the vector ALU: 96 channels 0.92 to 1.05 by itself but 0.99 to 1.04 in the block, 128
-// 0.95 to 1.11 and 1.02 to 1.08; nor for 64 and 32 channels with GELU (1.0 to 1.2).  Dense 128 does not fit the LDS.
-static inline int mlp_resident_from(const MlpParams &p, bool sparse)
-{
-    if (p.Cin != p.Cout2 || (p.Cin != 96 && p.Cin != 128)) return -1;
-    const size_t smem = p.Cin == 96 ? (sparse ? MlpPair<true, 3>::smem(p.Cmid) : MlpPair<false, 3>::smem(p.Cmid))
-                                    : (sparse ? MlpPair<true, 4>::smem(p.Cmid) : MlpPair<false, 4>::smem(p.Cmid));
-    if (smem > kMlpResidentSmem) return -1;
-    return p.act1 != SS_ACT_GELU || !sparse ? 6 : -1;
-}
-
 template <int DT, bool SPARSE>
 static int launch_mlp(const MlpParams &p, hipStream_t s)
 {
     const int forced = forced_tile(), ncu = compute_units();
     if (ncu <= 0) return SS_ERR_HIP;
-    // A wave per 32 intermediate channels while its workgroups of 32 pixels all run at once, from eight waves on.  bf16 with GELU, C -> 4 C ->
-    // C, sparse / dense, mlp_kernel against this one: 3136 pixels C = 64 5.3 / 5.4 against 4.35 / 4.5 us, 96 7.6 / 8.4 against 5.5 / 5.9, 128 10.3 /
-    // 11.4 against 6.65 / 7.5; 8192 pixels, the last that fit, C = 96 7.7 / 8.6 against 5.8 / 6.3; 10000 pixels, 313 workgroups of 12 waves, 7.8 / 8.75
-    // against 9.5 / 10.9.  Four waves (C = 32) make no difference: 3.7 and 3.6.
-    const bool few = ((long long)p.P + 31) / 32 <= ncu && p.Cmid >= 256;
-    const bool free_choice = forced < 40 || forced > 42;
-    if (p.Cmid <= 32 * kMlpWideWaves && (forced == 41 || (free_choice && few))) return launch_mlp_wide<DT, SPARSE>(p, s);
-    const int from = mlp_resident_from(p, SPARSE);
-    if (from >= 0 && (forced == 42 || (free_choice && ((long long)p.P + 31) / 32 > (long long)from * ncu))) {
+    const int id = forced >= 40 && forced <= 42 && mlp_takes(p, SPARSE, forced) ? forced : choose_mlp(p, SPARSE, ncu);
+    if (id == 41) return launch_mlp_wide<DT, SPARSE>(p, s);
+    if (id == 42) {
         if constexpr (SPARSE) return p.Cin == 96 ? launch_mlp_resident<DT, SPARSE, 3>(p, ncu, s) : launch_mlp_resident<DT, SPARSE, 4>(p, ncu, s);
-        else if (p.Cin == 96) return launch_mlp_resident<DT, SPARSE, 3>(p, ncu, s);
+        else return launch_mlp_resident<DT, SPARSE, 3>(p, ncu, s);
     }
     const long long blocks = ((long long)p.P + 63) / 64;
     if (blocks <= 0 || blocks > 0x7FFFFFFFll) return SS_ERR_UNSUPPORTED;

@@ -113,6 +113,51 @@ struct MlpParams {            // (a cheap launch, see ConvArgs; all channel coun
 constexpr int kMlpKs1 = 4;        // first reduction: at most 128 input channels
 constexpr int kMlpTiles = 2;      // 32x32 output tiles of the second layer per wave: at most 128 output channels x 64 pixels over 4 waves
 
+// The resident kernel's LDS copy of the weights is in the order of use, two row tiles of the intermediate (32 channels each) after the other, so that all
+// offsets inside a pair are constants: the first layer's tiles, the second layer's steps, their index words, the first layer's bias.
+template <bool SPARSE, int TILES>
+struct MlpPair {
+    static constexpr int STEP = SPARSE ? 1024 : 2048, KP1 = (TILES + 1) / 2, W2 = 2 * TILES * STEP, I1 = 2 * W2, I2 = I1 + (SPARSE ? 2 * KP1 * 256 : 0),
+                         BIAS = I2 + (SPARSE ? TILES * 256 : 0), BYTES = BIAS + 2 * 128;
+    static constexpr size_t smem(int Cmid) { return (size_t)(Cmid / 64) * BYTES + TILES * 128; }      // (with the second layer's bias)
+};
+constexpr size_t kMlpResidentSmem = 160 * 1024;
+constexpr int kMlpWideWaves = 16;         // wide kernel: at most 512 intermediate channels
+
+// Can the kernel of this id (ss_debug_force_tile) run the inverted bottleneck?  40 all of them; 41 the wide one; 42 the resident one: built for 96 channels
+// at both ends and sparse 128, if the weights fit the LDS (sparse 96 up to 640 intermediate channels, dense 96 up to 384, sparse 128 up to 512),
+// and not for the sparse path with GELU, where both are bound by the vector ALU (96 channels 0.92 to 1.05 of mlp_kernel's time by itself but 0.99 to 1.04
+// in a ConvNeXt block, 128 0.95 to 1.11 and 1.02 to 1.08), nor for 64 and 32 channels (with GELU 1.0 to 1.2).
+static inline bool mlp_takes(const MlpParams &p, bool sparse, int id)
+{
+    if (id == 41) return p.Cmid <= 32 * kMlpWideWaves;
+    if (id != 42) return true;
+    if (p.Cin != p.Cout2 || (p.Cin != 96 && !(sparse && p.Cin == 128)) || (sparse && p.act1 == SS_ACT_GELU)) return false;
+    return (p.Cin == 128 ? MlpPair<true, 4>::smem(p.Cmid) : (sparse ? MlpPair<true, 3>::smem(p.Cmid) : MlpPair<false, 3>::smem(p.Cmid))) <= kMlpResidentSmem;
+}
+
+// Which one pays:
+//   * the wide one, a wave per 32 intermediate channels, while its workgroups of 32 pixels all run at once, from eight waves on.  bf16 with GELU, C -> 4 C ->
+//     C, sparse / dense, mlp_kernel against it: 3136 pixels C = 64 5.3 / 5.4 against 4.35 / 4.5 us, 96 7.6 / 8.4 against 5.5 / 5.9, 128 10.3 /
+//     11.4 against 6.65 / 7.5; 8192 pixels, the last that fit, C = 96 7.7 / 8.6 against 5.8 / 6.3; 10000 pixels, 313 workgroups of 12 waves, 7.8 / 8.75
+//     against 9.5 / 10.9.  Four waves (C = 32) make no difference: 3.7 and 3.6.
+//   * the resident one from some pixel tiles per compute unit on.  A SIMD that gets a tile more than its neighbours keeps
+//     the chip waiting for it, and the weights' way to LDS is some 3 us, so it takes a few tiles per SIMD.  Times against mlp_kernel's at 1.6, 2.4, 3.2, 4, 5.5, 7 and
+//     12.25 tiles of 32 pixels per SIMD, bf16, C -> 4 C -> C:
+//       ReLU   sparse  96   0.85 0.82 0.78 0.80 0.77 0.72 0.68      dense  96   0.79 0.82 0.73 0.72 0.73 0.69 0.62
+//              sparse 128   0.94 0.96 0.88 0.85 0.86 0.79 0.76
+//       GELU   dense   96   0.95 1.01 0.95 0.86 0.90 0.83 0.84     (in a ConvNeXt block on new inputs each time 0.95 to 0.90, 173 -> 163 us at 128 x 56 x 56)
+//     With other intermediates, from 1.5 tiles per SIMD on: 96 channels and 128 between them 0.83 to 1.03, 256 0.62 to 0.90 (dense GELU 0.91 to 1.03), sparse 512
+//     and 640 0.68 to 0.86.  128 channels live less from the pixels that they save and more on the weights' way: 128 between them 1.04 to 1.11, so never;
+//     256 and 384 0.98 to 1.05 below 3 tiles per SIMD, 0.81 to 1.0 from there on.
+static inline int choose_mlp(const MlpParams &p, bool sparse, int ncu)
+{
+    const long long tiles = ((long long)p.P + 31) / 32;
+    if (tiles <= ncu && p.Cmid >= 256 && mlp_takes(p, sparse, 41)) return 41;
+    if (!mlp_takes(p, sparse, 42) || (p.Cin == 128 && p.Cmid < 256)) return 40;
+    return tiles > (p.Cin == 128 && p.Cmid < 512 ? 12ll : 6ll) * ncu ? 42 : 40;
+}
+
 static inline long long n_blocks(const ConvParams &p, int bm, int bn)
 {
     return (long long)((p.Cout + bm - 1) / bm) * (((long long)p.P + bn - 1) / bn);

@@ -25,6 +25,9 @@ def test_equals_the_one_tile_kernel(ss, force_tile, shape):
         d1, d2 = wl.make_inputs(L1), wl.make_inputs(L2)
         bits = wl.to_bits(res, dtype) if with_res else None
         for sparse in (True, False):
+            # (what the resident kernel cannot run: forced or not, the one-tile kernel does)
+            if (sparse and act1 == wl.ACT_GELU) or (not sparse and (C == 128 or cmid > 384)):
+                continue
             force_tile(40)
             expect = _run(ss, L1, L2, d1, d2, bits, sparse)[0]
             force_tile(42)
