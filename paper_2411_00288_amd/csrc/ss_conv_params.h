@@ -140,7 +140,9 @@ static inline bool mlp_takes(const MlpParams &p, bool sparse, int id)
 //   * the wide one, a wave per 32 intermediate channels, while its workgroups of 32 pixels all run at once, from eight waves on.  bf16 with GELU, C -> 4 C ->
 //     C, sparse / dense, mlp_kernel against it: 3136 pixels C = 64 5.3 / 5.4 against 4.35 / 4.5 us, 96 7.6 / 8.4 against 5.5 / 5.9, 128 10.3 /
 //     11.4 against 6.65 / 7.5; 8192 pixels, the last that fit, C = 96 7.7 / 8.6 against 5.8 / 6.3; 10000 pixels, 313 workgroups of 12 waves, 7.8 / 8.75
-//     against 9.5 / 10.9.  Four waves (C = 32) make no difference: 3.7 and 3.6.
+//     against 9.5 / 10.9.  Four waves (C = 32) make no difference: 3.7 and 3.6.  Over 588 layers of 32 to 128 channels at either end and 256 to 512 between
+//     them 0.82 of its time in the mean and with GELU always below 1; without, few channels leave it nothing to do at once: 32 and 32 1.03 to 1.11,
+//     32 and 64 0.98 to 1.07, from 128 together on 0.63 to 1.03.
 //   * the resident one from some pixel tiles per compute unit on.  A SIMD that gets a tile more than its neighbours keeps
 //     the chip waiting for it, and the weights' way to LDS is some 3 us, so it takes a few tiles per SIMD.  Times against mlp_kernel's at 1.6, 2.4, 3.2, 4, 5.5, 7 and
 //     12.25 tiles of 32 pixels per SIMD, bf16, C -> 4 C -> C:
@@ -153,7 +155,7 @@ static inline bool mlp_takes(const MlpParams &p, bool sparse, int id)
 static inline int choose_mlp(const MlpParams &p, bool sparse, int ncu)
 {
     const long long tiles = ((long long)p.P + 31) / 32;
-    if (tiles <= ncu && p.Cmid >= 256 && mlp_takes(p, sparse, 41)) return 41;
+    if (tiles <= ncu && p.Cmid >= 256 && (p.act1 == SS_ACT_GELU || p.Cin + p.Cout2 >= 128) && mlp_takes(p, sparse, 41)) return 41;
     if (!mlp_takes(p, sparse, 42) || (p.Cin == 128 && p.Cmid < 256)) return 40;
     return tiles > (p.Cin == 128 && p.Cmid < 512 ? 12ll : 6ll) * ncu ? 42 : 40;
 }

@@ -21,7 +21,7 @@ def test_both_sides_of_the_lines(tmp_path):
     for sparse in (0, 1):
         want.update({(few, 64, 256, 64, GELU, sparse): (41, 0), (few + 1, 64, 256, 64, GELU, sparse): (40, 0), (few, 32, 128, 32, GELU, sparse): (40, 0),
                      (few, 64, 512, 32, GELU, sparse): (41, 0), (few, 64, 640, 64, GELU, sparse): (40, 0), (few, 32, 256, 32, GELU, sparse): (41, 0),
-                     (few, 64, 256, 64, RELU, sparse): (41, 0),
+                     (few, 32, 256, 32, RELU, sparse): (40, 0), (few, 64, 256, 32, RELU, sparse): (40, 0), (few, 64, 256, 64, RELU, sparse): (41, 0),
                      (few, 32, 256, 96, RELU, sparse): (41, 0), (six, 96, 384, 96, RELU, sparse): (40, 1), (six + 1, 96, 384, 96, RELU, sparse): (42, 1),
                      (six + 1, 96, 384, 96, 0, sparse): (42, 1), (six + 1, 96, 384, 128, RELU, sparse): (40, 0), (six + 1, 64, 256, 64, RELU, sparse): (40, 0),
                      (six + 1, 96, 512, 96, RELU, sparse): (42 if sparse else 40, sparse), (six + 1, 96, 640, 96, RELU, sparse): (42 if sparse else 40, sparse),
