@@ -306,7 +306,8 @@ int ss_conv2d_pw_fused_query(const ss_weight_desc *desc1, int32_t stride_h, int3
 /*
  * ss_conv2d_pw_fused_fwd and the 1x1 layer that reads its output (the channel reduction that opens the next bottleneck) in one kernel:
  *   y2 as ss_conv2d_pw_fused_fwd writes y, and y3 = act3( conv_1x1(y2) + bias3 ), computed from y2 as it is stored, without reading it back.
- * Both are written; up to the order of fp32 additions they equal the two calls, and bit for bit where ss_conv2d_pw2_fused_query says that it pays.  First layer 3x3 in the SS_K_CRS flattening with
+ * Both are written; up to the order of fp32 additions they equal the two calls (bit for bit where ss_conv2d_pw2_fused_query says that it pays, the first layer
+ * has 64 or 128 channels and the third 64 or more).  First layer 3x3 in the SS_K_CRS flattening with
  * cin % 32 == 0 and at most 128 channels, desc2->cout % 128 == 0, desc3 a 1x1 layer on desc2->cout channels with cout % 32 == 0, at most 128;
  * anything else SS_ERR_UNSUPPORTED.  y3 [N][Ho][Wo][desc3->cout] 16-byte aligned, overlapping none of the other buffers; bias3 16-byte aligned or NULL.
  * Everything else as for ss_conv2d_pw_fused_fwd.  The _dense_ form takes operands built by ss_dense_pack.

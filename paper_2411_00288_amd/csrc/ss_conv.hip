@@ -513,13 +513,22 @@ extern "C" int ss_conv2d_pw2_fused_query(const ss_weight_desc *desc1, int32_t N,
     if (desc3->kh != 1 || desc3->kw != 1 || desc3->cin != desc2->cout) return SS_ERR_INVALID_ARG;
     if (!third_fits(desc1, desc2, desc3)) return SS_OK;
     *supported = 1;
-    // The ResNet-50 trunk at 224 x 224, us, no layer joined / all that can be: batch 1 196 / 191, 4 279 / 262, 8 343 / 320, 32 726 / 677, 64 1115 / 1080.  Not
+    // Few pixels: where their kernel takes all three layers, 0.61 to 0.91 of the pair's time and the third layer's.  Where it takes only the pair, the three
+    // run in the tiled kernel, 64 pixels at a time, and lose (first layers of 32 and 96 channels up to 1.9, third layers of 32 up to 1.8, second ones of 1024
+    // up to 3.2; 0.65 to 0.93 for sparse 32 -> 32 -> 128 alone).
+    // Beyond: the ResNet-50 trunk at 224 x 224, us, no layer joined / all that can be: batch 32 726 / 677, 64 1115 / 1080.  Not
     // where it loses: 128 channels on one workgroup per compute unit, where the pair has producer waves (batch 16, 516 without, 528 with those three, 503
-    // with the others), and, beyond the kernels for few pixels, dense layers whose third one has more than 64 channels (batch 64: 1290 / 1301; 1266 with those of 64).
+    // with the others), and dense layers whose third one has more than 64 channels (batch 64: 1290 / 1301; 1266 with those of 64).  Over 400 layers of 32 to 128
+    // channels by themselves 0.51 to 0.99 where it says so.
     const long long P = (long long)N * ((H + 2 * pad_h - desc1->kh) / stride_h + 1) * ((Wd + 2 * pad_w - desc1->kw) / stride_w + 1);
-    const int ncu = planning_units();
-    const bool few = (P + 31) / 32 <= ncu, one_each = desc1->cout > 64 && (P + 63) / 64 <= 256;
-    *pays = pair_pays && (few || (sparse ? !one_each : desc3->cout <= 64));
+    const int px = pair_small_pixels(P, planning_units());
+    if (px > 0) {
+        *pays = pair_pays && (pair_small_fits(desc1, px, desc2->cout, desc3->cout) || (sparse && desc1->cout == 32 && desc2->cout == 128));
+        return SS_OK;
+    }
+    ConvParams p{};
+    p.P = (int)P; p.Cout = desc1->cout;
+    *pays = pair_pays && (sparse ? choose_fused_tile(p) != 4 : desc3->cout <= 64);
     return SS_OK;
 }
 

@@ -355,7 +355,6 @@ constexpr int ring_size(int ksteps, int regs_per_step, int budget)
 // LDS of a workgroup: the staging buffers, reused by the epilogue for the output tile (16-bit, or fp32 when a
 // residual is added after it), followed by the tile's bias values (fp32).
 // Fused second contraction: every wave owns a staging region of 32 pixels x (32 + 4) floats behind the 16-bit tile.
-constexpr int kFuseRow = 32 + 4;
 constexpr size_t kFuseRegion = 32 * kFuseRow * 4;
 
 // Third contraction: 128 channels of the second one's finished output, [pixel][channel].
@@ -2261,15 +2260,6 @@ static int launch_fused_tile(int id, const ConvParams &p, hipStream_t s)
         default: break;
     }
     return SS_ERR_INVALID_ARG;
-}
-
-// The tile must hold every output channel of the first convolution: 64, 128 or 256 rows; among the tiles of that
-// height the grid size decides as in choose_tile.
-static inline int choose_fused_tile(const ConvParams &p)
-{
-    if (p.Cout <= 64) return n_blocks(p, 64, 64) <= 1024 ? 1 : 0;
-    if (p.Cout <= 128) return n_blocks(p, 128, 64) <= 256 ? 4 : 2;
-    return n_blocks(p, 256, 64) <= 256 ? 5 : 3;
 }
 
 // With a third contraction: the paper's flattening, tiles of 64 or 128 rows without producer waves.

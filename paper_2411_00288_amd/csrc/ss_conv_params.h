@@ -371,6 +371,53 @@ static inline bool takes_small(const ss_weight_desc *d, const ConvParams &p, boo
     return mode >= 0 && small_variant(p, small_taps(mode) ? d->kh * d->kw : 0, sparse, ncu) != SMALL_NONE;
 }
 
+// ---------------------------------------------------------------------------------------------
+// The fused pair and its third layer.
+// ---------------------------------------------------------------------------------------------
+constexpr int kFuseRow = 32 + 4;      // floats per pixel row of a wave's 32 x 32 result in LDS
+
+// The tile must hold every output channel of the first convolution: 64, 128 or 256 rows; among the tiles of that
+// height the grid size decides as in choose_tile.
+static inline int choose_fused_tile(const ConvParams &p)
+{
+    if (p.Cout <= 64) return n_blocks(p, 64, 64) <= 1024 ? 1 : 0;
+    if (p.Cout <= 128) return n_blocks(p, 128, 64) <= 256 ? 4 : 2;
+    return n_blocks(p, 256, 64) <= 256 ? 5 : 3;
+}
+
+// Few pixels (pair_small_kernel, ss_conv_small.h).
+constexpr int kPairWaves = 8;
+struct PairShape {                    // LDS map of a workgroup, in bytes
+    size_t stage, part, tile, third, total;  // [0, stage): staging, later the output slabs; then partial sums; then the 16-bit tile; the second layer's
+};                                           // output where a third one follows; then the first layer's bias
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+static inline PairShape pair_shape(int px, int nchunks, int cout1, int cout2)      // cout2: 0 without a third layer
+{
+    PairShape h;
+    h.stage = (size_t)nchunks * px * 576;
+    const size_t slabs = (size_t)kPairWaves * px * kFuseRow * 4;
+    if (h.stage < slabs) h.stage = slabs;
+    h.part = (size_t)kPairWaves * 4096;
+    h.tile = (size_t)px * (cout1 + 8) * 2;
+    h.third = cout2 > 0 ? (size_t)px * (cout2 + 8) * 2 : 0;
+    h.total = h.stage + h.part + h.tile + h.third + (size_t)cout1 * 4;
+    return h;
+}
+
+// Pixels per workgroup while one workgroup per compute unit holds them all, or 0.
+static inline int pair_small_pixels(long long P, int ncu) { return (P + 15) / 16 <= ncu ? 16 : ((P + 31) / 32 <= ncu ? 32 : 0); }
+
+// Does the kernel take these layers, px pixels at a time?  cout2, cout3: 0 without a third layer (with one: widths known at compile time, two waves at
+// least to a row tile, weights of at most sixteen steps).
+static inline bool pair_small_fits(const ss_weight_desc *d1, int px, int cout2, int cout3)
+{
+    if (d1->korder != SS_K_CRS || d1->kh != 3 || d1->kw != 3 || d1->cin % 32 != 0 || d1->cout % 32 != 0 || d1->cout > 32 * kPairWaves) return false;
+    if (cout2 > 0 && ((d1->cout != 64 && d1->cout != 128) || cout2 > 512 || cout3 < 64 || cout3 > 128)) return false;
+    return pair_shape(px, d1->cin / 32, d1->cout, cout2).total <= 160 * 1024;
+}
+
 
 // Split of a convolution's reduction over several workgroups per output tile (for grids that leave most compute
 // units idle: few output pixels, long reductions -- small-batch inference and the last stages of a network).

@@ -453,23 +453,6 @@ static int small_mode(const ss_weight_desc *desc, const ConvParams &p, int varia
 // 9.2 -> 5.8 us, 128 -> 128 -> 512 at 28x28 11.5 -> 8.3 (bound by the weights each workgroup fetches: a ring of 18 instead of 9
 // steps in flight measured 8.6); past one workgroup per compute unit the tiled kernel shares them over more pixels and wins.
 // ---------------------------------------------------------------------------------------------
-constexpr int kPairWaves = 8;
-struct PairShape {                    // LDS map of a workgroup, in bytes
-    size_t stage, part, tile, third, total;  // [0, stage): staging, later the output slabs; then partial sums; then the 16-bit tile; the second layer's
-};                                           // output where a third one follows; then the first layer's bias
-static inline __host__ __device__ PairShape pair_shape(int px, int nchunks, int cout1, int cout2)      // cout2: 0 without a third layer
-{
-    PairShape h;
-    h.stage = (size_t)nchunks * px * 576;
-    const size_t slabs = (size_t)kPairWaves * px * kFuseRow * 4;
-    if (h.stage < slabs) h.stage = slabs;
-    h.part = (size_t)kPairWaves * 4096;
-    h.tile = (size_t)px * (cout1 + 8) * 2;
-    h.third = cout2 > 0 ? (size_t)px * (cout2 + 8) * 2 : 0;
-    h.total = h.stage + h.part + h.tile + h.third + (size_t)cout1 * 4;
-    return h;
-}
-
 // THIRD: as in conv_kernel.  The second layer's output stays in LDS as well, and the waves split the third one's rows and reduction.  Its sums are those of
 // its own call, share for share (pw_shares), so that both give the same bits: a wave has one share; or two, where there are more of them than
 // waves to a row tile; or begins or ends one that is longer than the eight steps a wave holds weights for, the second taking the sums over
@@ -876,20 +859,14 @@ static int launch_pair_small(ConvParams p, hipStream_t s)
 template <int DT, bool SPARSE>
 static int pair_small(const ss_weight_desc *d1, const ConvParams &p, int px, hipStream_t s)
 {
-    if (d1->korder != SS_K_CRS || d1->kh != 3 || d1->kw != 3 || d1->cin % 32 != 0 || p.Mt > kPairWaves || p.Cout % 32 != 0) return SS_ERR_INVALID_ARG;
-    if (px == 0) {
-        const int ncu = compute_units();
-        if (ncu <= 0) return SS_ERR_HIP;
-        px = ((long long)p.P + 15) / 16 <= ncu ? 16 : (((long long)p.P + 31) / 32 <= ncu ? 32 : 0);
-    }
+    const int ncu = compute_units();
+    if (ncu <= 0) return SS_ERR_HIP;
     const bool third = p.Cout3 > 0;
-    if (px == 0 || pair_shape(px, p.Ks / 9, p.Cout, third ? p.Cout2 : 0).total > 160 * 1024) return SS_ERR_INVALID_ARG;
-    if (third && (p.Mt3 < 2 || p.Mt3 > 4 || p.Ks3 > 16)) return SS_ERR_INVALID_ARG;
+    if (px == 0) px = pair_small_pixels(p.P, ncu);
+    if (px == 0 || !pair_small_fits(d1, px, third ? p.Cout2 : 0, p.Cout3)) return SS_ERR_INVALID_ARG;
     ConvParams q = p;
     int plan = THIRD_NONE;
     if (third) {
-        const int ncu = compute_units();
-        if (ncu <= 0) return SS_ERR_HIP;
         q.shares3 = pw_shares(p.P, p.Ks3, p.Mt3, SPARSE, ncu);
         q.per3 = p.Ks3 / q.shares3;
         plan = q.per3 > 8 ? THIRD_HANDED : (q.shares3 > 2 && p.Mt3 > 2 ? THIRD_TWO : THIRD_SHARE);
