@@ -61,6 +61,15 @@ int compute_units()
     return n;
 }
 
+// Offsets in the kernels are 32 bits, and "out of range" must stay above every real one.  (out_channels: of the widest output; asked by the calls and
+// by their queries.)
+static bool within_limits(const ss_weight_desc *d, int32_t N, int32_t H, int32_t Wd, int32_t ph, int32_t pw, int esize, long long P, long long out_channels)
+{
+    const long long xbytes = (long long)N * H * Wd * d->cin * esize;
+    return xbytes < (1ll << 31) - (1ll << 26) && P * out_channels < (1ll << 31) && P < (1ll << 31) - 512 &&
+           (long long)(ph + d->kh + 1) * (Wd + pw + d->kw) * d->cin * esize < (1ll << 26);
+}
+
 // q8: the call came through an 8-bit entry point (then `scale` may be given and the descriptor must say SS_I8 or
 // SS_F8); the 16-bit entry points reject such descriptors.  pooled: where the 3x3 max pooling behind an image's first layer goes, in the same kernel.
 template <bool SPARSE>
@@ -94,10 +103,7 @@ static int conv_entry(const ss_weight_desc *desc, const void *x, int32_t N, int3
     if (Ho <= 0 || Wo <= 0) return SS_ERR_INVALID_ARG;
     long long P = (long long)N * Ho * Wo;
     long long xbytes = (long long)N * H * Wd * desc->cin * esize;
-    long long yelems = P * desc->cout;
-    // 32-bit byte offsets inside the kernel; "out of range" must stay above every real offset
-    if (xbytes >= (1ll << 31) - (1ll << 26) || yelems >= (1ll << 31) || P >= (1ll << 31) - 512) return SS_ERR_UNSUPPORTED;
-    if ((long long)(ph + desc->kh + 1) * (Wd + pw + desc->kw) * desc->cin * esize >= (1ll << 26)) return SS_ERR_UNSUPPORTED;
+    if (!within_limits(desc, N, H, Wd, ph, pw, esize, P, desc->cout)) return SS_ERR_UNSUPPORTED;
 
     TileDims t = tile_dims(desc);
     size_t wbytes = SPARSE ? packed_size(t) : dense_size(t);
@@ -211,8 +217,7 @@ static int fused_entry(const ss_weight_desc *d1, const void *x, int32_t N, int32
     const int Ho = (H + 2 * ph - d1->kh) / sh + 1, Wo = (Wd + 2 * pw - d1->kw) / sw + 1;
     if (Ho <= 0 || Wo <= 0) return SS_ERR_INVALID_ARG;
     const long long P = (long long)N * Ho * Wo, xbytes = (long long)N * H * Wd * d1->cin * 2;
-    if (xbytes >= (1ll << 31) - (1ll << 26) || P * d2->cout >= (1ll << 31) || P >= (1ll << 31) - 512) return SS_ERR_UNSUPPORTED;
-    if ((long long)(ph + d1->kh + 1) * (Wd + pw + d1->kw) * d1->cin * 2 >= (1ll << 26)) return SS_ERR_UNSUPPORTED;
+    if (!within_limits(d1, N, H, Wd, ph, pw, 2, P, d2->cout)) return SS_ERR_UNSUPPORTED;
     const TileDims t1 = tile_dims(d1), t2 = tile_dims(d2);
     if ((SPARSE ? packed_size(t1) : dense_size(t1)) >= (1ull << 31) || (SPARSE ? packed_size(t2) : dense_size(t2)) >= (1ull << 31))
         return SS_ERR_UNSUPPORTED;
@@ -415,7 +420,7 @@ extern "C" int ss_conv2d_maxpool_dense_query(const ss_weight_desc *desc, int32_t
     if (N <= 0 || H <= 0 || Wd <= 0 || stride_h <= 0 || stride_w <= 0 || pad_h < 0 || pad_w < 0) return SS_ERR_INVALID_ARG;
     if (H + 2 * pad_h < desc->kh || Wd + 2 * pad_w < desc->kw) return SS_ERR_INVALID_ARG;
     const long long P = (long long)N * ((H + 2 * pad_h - desc->kh) / stride_h + 1) * ((Wd + 2 * pad_w - desc->kw) / stride_w + 1);
-    if (P >= (1ll << 31) - 512) return SS_OK;
+    if (!within_limits(desc, N, H, Wd, pad_h, pad_w, 2, P, desc->cout) || dense_size(tile_dims(desc)) >= (1ull << 31)) return SS_OK;
     ConvParams p{};
     p.P = (int)P; p.Cout = desc->cout; p.sh = stride_h; p.sw = stride_w; p.nsplit = 1;
     *supported = act == SS_ACT_RELU && image_eligible(desc, p);

@@ -33,3 +33,10 @@ def test_joined_layers_on_more_pixels():
     assert [_joined(128, 512, 128, 64, N=n)[1] for n in (2, 4, 5)] == [True, False, True]
     assert [_joined(64, 1024, 64, 64, N=n)[1] for n in (2, 3)] == [False, True]
     assert [_joined(64, 256, c3, 64, False, N=4)[1] for c3 in (64, 96)] == [True, False]
+
+
+def test_pooled_layer_is_not_promised_where_the_call_refuses_it():
+    q = lambda cout, N, H, W, pad=3: ss.ss_conv2d_maxpool_dense_query(_desc(cout, 4, 7, wl.K_RSC), (N, H, W), (2, 2), (pad, pad))
+    # inputs of 2^31 - 2^26 bytes (992 images of 512 x 512) and more; padding rows of 2^26 bytes
+    assert [q(8, n, 512, 512) for n in (991, 992, 1000)] == [True, False, False]
+    assert [q(64, 1, 64, 512, p) for p in (3, 1500, 15000)] == [True, True, False]
