@@ -516,7 +516,8 @@ extern "C" int ss_conv2d_pw2_fused_query(const ss_weight_desc *desc1, int32_t N,
     if (st == SS_ERR_INVALID_ARG) return st;
     if (st != SS_OK || desc3->dtype != desc1->dtype) return SS_OK;
     if (desc3->kh != 1 || desc3->kw != 1 || desc3->cin != desc2->cout) return SS_ERR_INVALID_ARG;
-    if (!third_fits(desc1, desc2, desc3)) return SS_OK;
+    const long long P = (long long)N * ((H + 2 * pad_h - desc1->kh) / stride_h + 1) * ((Wd + 2 * pad_w - desc1->kw) / stride_w + 1);
+    if (!third_fits(desc1, desc2, desc3) || !within_limits(desc1, N, H, Wd, pad_h, pad_w, 2, P, desc2->cout)) return SS_OK;
     *supported = 1;
     // Few pixels: where their kernel takes all three layers, 0.61 to 0.91 of the pair's time and the third layer's.  Where it takes only the pair, the three
     // run in the tiled kernel, 64 pixels at a time, and lose (first layers of 32 and 96 channels up to 1.9, third layers of 32 up to 1.8, second ones of 1024
@@ -525,7 +526,6 @@ extern "C" int ss_conv2d_pw2_fused_query(const ss_weight_desc *desc1, int32_t N,
     // where it loses: 128 channels on one workgroup per compute unit, where the pair has producer waves (batch 16, 516 without, 528 with those three, 503
     // with the others), and dense layers whose third one has more than 64 channels (batch 64: 1290 / 1301; 1266 with those of 64).  Over 400 layers of 32 to 128
     // channels by themselves 0.51 to 0.99 where it says so.
-    const long long P = (long long)N * ((H + 2 * pad_h - desc1->kh) / stride_h + 1) * ((Wd + 2 * pad_w - desc1->kw) / stride_w + 1);
     const int px = pair_small_pixels(P, planning_units());
     if (px > 0) {
         *pays = pair_pays && (pair_small_fits(desc1, px, desc2->cout, desc3->cout) || (sparse && desc1->cout == 32 && desc2->cout == 128));

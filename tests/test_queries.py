@@ -40,3 +40,9 @@ def test_pooled_layer_is_not_promised_where_the_call_refuses_it():
     # inputs of 2^31 - 2^26 bytes (992 images of 512 x 512) and more; padding rows of 2^26 bytes
     assert [q(8, n, 512, 512) for n in (991, 992, 1000)] == [True, False, False]
     assert [q(64, 1, 64, 512, p) for p in (3, 1500, 15000)] == [True, True, False]
+
+
+def test_joined_layers_are_not_promised_where_the_call_refuses_them():
+    # outputs of 2^31 elements, an input of 2^31 - 2^26 bytes
+    assert [_joined(64, 256, 64, 2048, N=n)[0] for n in (1, 2)] == [True, False]
+    assert [_joined(32, 128, 32, 1024, N=n, cin=512)[0] for n in (1, 2)] == [True, False]
