@@ -277,12 +277,15 @@ static inline int choose_vec8_sparse(const ConvParams &p, int id, int ncu)
 // Tile id of a channels-last layer with taps and K < 512 (2-byte units), where it is not choose_tile's (8806 layers on cold inputs, profiles/tile_heights.md):
 //   * sparse, 129 to 160 channels: one tile of 160 rows instead of two of 128 (0.89 of their time in the mean over 543 layers, 0.73 to 1.00, 16- and 8-bit
 //     alike; dense 0.97, up to 1.21);
-//   * 96 rows where they are no more tiles (65 to 96, 129 to 192, 257 to 288 channels).  A compute unit holds four workgroups of 128 rows or five of 96, so by workgroups per unit: up to
-//     two no gain (0.99 to 1.03), two to three 0.98 for dense int8 and 1.00 for the others, three to four 0.92 dense (sparse 0.95), four to five, one round instead of
-//     two, 0.79 (0.95), five to six, two rounds on both sides, 0.98 to 1.01, above 0.89 to 0.92 (0.98, one in fifteen slower: not taken).  Not measured for dense FP8.
+//   * 96 rows where they are no more tiles (65 to 96, 129 to 192, 257 to 288 channels).  A compute unit holds four workgroups of 128 rows or five of 96
+//     (without a residual), so by workgroups per unit: up to two no gain (0.99 to 1.03), two to three 0.98 for dense int8 and 1.00 for the others, three to four
+//     0.92 dense (sparse 0.95), four to five, one round instead of two, 0.79 (0.95), five to six, two rounds on both sides, 0.98 to 1.01, above 0.89 to 0.92
+//     (0.98, one in fifteen slower: not taken).  Not measured for dense FP8.
 // In calls on new inputs, us: bf16 40 -> 136 on thirty 40x40 images 12.9 -> 9.65, int8 96 -> 148 on twenty 10.5 -> 9.0 (dense 11.4 -> 10.5), FP8 64 -> 132 on a hundred
 // 28x28 16.9 -> 15.3, int8 dense 64 -> 92 13.75 -> 11.0,
 // f16 dense 56 -> 90 on 42 40x40 19.2 -> 14.4 and 56 -> 180 27.6 -> 22.8, bf16 sparse 40 -> 92 11.45 -> 10.6.
+// With a residual, whose fp32 tile changes the LDS of a workgroup (33 KB for 128 rows, 25 for 96, 42 for 160), the layers that move gain more: 292 16-bit ones with
+// and without, strides of one and two: sparse 160 rows 0.83 of the time of 128 in the mean (0.68 to 0.98; without 0.88), sparse 96 rows 0.89 (0.95), dense 0.87 (0.89).
 static inline int choose_vec_short(const ConvParams &p, bool bytes, bool sparse, bool f8, int ncu)
 {
     const int id = choose_tile(p, false, false);
