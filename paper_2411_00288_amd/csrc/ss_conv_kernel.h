@@ -1070,10 +1070,13 @@ void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, Con
             };
             constexpr int kNonTemporal = 2;               // cache-policy bit nt of the buffer instructions
             const int nparts = p.Cout2 / 128;
-            // A residual is the block's input at its last use, y2 what the next block reads as its own.  Where both together are about as large as the 256 MB
-            // that the memory's cache holds, the residual's lines push y2 out before that: it is then read with the non-temporal hint.  ResNet-50 trunk at
-            // 224 x 224, us without and with (residual of the 56 x 56 blocks, MiB): 40 images (61) 716 / 718, 48 (73) 891 / 884, 56 (86) 950 / 933, 64 (98)
-            // 1050 / 1026 (dense 1237 / 1214), 72 (110) 1121 / 1105, 80 (122) 1187 / 1175, 88 (135) 1403 / 1401, 96 (147) 1474 / 1486.
+            // A residual is mostly the block's input at its last use, y2 what the next block reads as its own.  Where both together are about as large as the
+            // 256 MB that the memory's cache holds, the residual's lines push y2 out before that: it is then read with the non-temporal hint.  (A hint: a caller
+            // who reads the residual again finds it in memory.)  ResNet-50 trunk at 224 x 224, us without and with:
+            //   residual of the 56 x 56 blocks, 64 channels: 40 images (61 MiB) 716 / 718, 48 (73) 907 / 883, 56 (86) 960 / 931, 64 (98) 1077 / 1038 (dense 1241 / 1228),
+            //   72 (110) 1131 / 1096, 80 (122) 1215 / 1191, 88 (135) 1423 / 1412, 92 (141) 1460 / 1463; 96 (147) would be 1474 / 1486;
+            //   of the 28 x 28 blocks, 128 channels: 100 images (77 MiB) 1524 / 1493, 128 (98) 1822 / 1788, 160 (122) 2099 / 2074, 184 (141) 2520 / 2507.
+            // 200 images of 128 x 128 (100 MiB) 1089 / 1049, 48 of 256 x 256 (96) 1029 / 993, 64 (128) 1260 / 1224.
             const long long res_bytes = (long long)p.P * p.Cout2 * 2;
             const bool once = res_bytes >= (72ll << 20) && res_bytes < (144ll << 20);
             for (int part = 0; part < nparts; part++) {
