@@ -237,7 +237,7 @@ static int fused_entry(const ss_weight_desc *d1, const void *x, int32_t N, int32
         if (d1->dtype == SS_F16) return SPARSE ? mlp_dispatch_f16_sparse(m, ms) : mlp_dispatch_f16_dense(m, ms);
         return SPARSE ? mlp_dispatch_bf16_sparse(m, ms) : mlp_dispatch_bf16_dense(m, ms);
     }
-    ConvParams p{};
+    ChainParams p{};
     p.x = static_cast<const uint16_t *>(x);
     p.a_vals = static_cast<const uint8_t *>(w1) + kHeaderBytes;
     p.a_meta = reinterpret_cast<const uint32_t *>(p.a_vals + (size_t)t1.Mt * t1.Ks * 1024);

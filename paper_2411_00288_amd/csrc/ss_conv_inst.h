@@ -99,7 +99,7 @@ int SS_CAT(pooled_dispatch_, SS_INST_NAME)(const ss_weight_desc *desc, const Con
 }
 #endif
 
-int SS_CAT(fused_dispatch_, SS_INST_NAME)(const ss_weight_desc *d1, const ConvParams &p, hipStream_t s)
+int SS_CAT(fused_dispatch_, SS_INST_NAME)(const ss_weight_desc *d1, const ChainParams &p, hipStream_t s)
 {
     if (forced_tile() < 0 || forced_tile() == 20 || forced_tile() == 21) {       // few output pixels
         const int st = pair_small<SS_INST_DT, SS_INST_SPARSE>(d1, p, forced_tile() < 0 ? 0 : (forced_tile() == 20 ? 16 : 32), s);

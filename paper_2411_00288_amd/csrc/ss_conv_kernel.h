@@ -396,12 +396,15 @@ constexpr int min_waves_per_simd(int tm, int tn, bool big_stage)
 // does not read it back from memory (the number of 32 x 32 tiles of its output per wave; 0: there is none).
 constexpr bool short_args(int mode, bool fuse) { return !fuse && mode != MODE_GATHER && mode != MODE_GATHER4; }      // (the others need more than ConvArgs holds)
 
+template <int THIRD>
+using kernel_params = typename std::conditional<(THIRD > 0), ChainParams, ConvParams>::type;
+
 template <int DT, bool SPARSE, int WAVES_M, int WAVES_N, int TM, int TN, int MODE, int KH, int KW, bool DEEP, bool SPEC, bool FUSE = false, int THIRD = 0>
 __global__ __launch_bounds__((WAVES_M * WAVES_N + (SPEC ? 4 : 0)) * 64)
 __attribute__((amdgpu_waves_per_eu(DEEP ? 1 : (((DT == SS_F8 || FUSE) && !SPARSE && MODE == MODE_VEC && TM * TN == 2) ? 3 : min_waves_per_simd(TM, TN, is_taps(MODE) || MODE == MODE_VEC8)))))
-void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, ConvParams>::type args)
+void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, kernel_params<THIRD>>::type args)
 {
-    ConvParams p;
+    kernel_params<THIRD> p;
     if constexpr (short_args(MODE, FUSE)) p = unpack_args<DT, SPARSE, KH, KW, is_vec(MODE), false>(args);
     else p = args;
     using CS = ChunkShape<MODE, KH, KW, DEEP>;
@@ -2089,7 +2092,7 @@ static int launch_mlp(const MlpParams &p, hipStream_t s)
 // host side
 // ---------------------------------------------------------------------------------------------
 template <int DT, bool SPARSE, int WAVES_M, int WAVES_N, int TM, int TN, int MODE, int KH, int KW, bool DEEP = false, bool SPEC = false, bool FUSE = false, int THIRD = 0>
-static int launch(const ConvParams &p0, hipStream_t s)
+static int launch(const kernel_params<THIRD> &p0, hipStream_t s)
 {
     constexpr int BM = WAVES_M * TM * 32, BN = WAVES_N * TN * 32;
     constexpr int NWAVES = WAVES_M * WAVES_N + (SPEC ? 4 : 0);
@@ -2099,7 +2102,7 @@ static int launch(const ConvParams &p0, hipStream_t s)
     static_assert(smem_plain <= 160 * 1024 && smem_res <= 160 * 1024, "LDS tile too large");
     const size_t smem = (p0.residual && !FUSE) ? smem_res : smem_plain;
     if (FUSE && (p0.Cout > BM || p0.Cout % 32 != 0)) return SS_ERR_UNSUPPORTED;      // the whole channel range must sit in one tile
-    ConvParams p = p0;
+    kernel_params<THIRD> p = p0;
     p.tiles_m = (p.Cout + BM - 1) / BM;
     fast_div_setup((unsigned)p.tiles_m, &p.tm_mul, &p.tm_sh);
     long long tiles_n = ((long long)p.P + BN - 1) / BN;
@@ -2267,7 +2270,7 @@ static int launch_fused_tile(int id, const ConvParams &p, hipStream_t s)
 
 // With a third contraction: the paper's flattening, tiles of 64 or 128 rows without producer waves.
 template <int DT, bool SPARSE>
-static int third_mode(const ss_weight_desc *d1, const ConvParams &p, hipStream_t s)
+static int third_mode(const ss_weight_desc *d1, const ChainParams &p, hipStream_t s)
 {
     if (d1->korder != SS_K_CRS || d1->kh != 3 || d1->kw != 3 || d1->cin % 32 != 0) return SS_ERR_UNSUPPORTED;
     if (p.Cout > 128 || p.Cout3 > 128) return SS_ERR_UNSUPPORTED;
@@ -2277,7 +2280,7 @@ static int third_mode(const ss_weight_desc *d1, const ConvParams &p, hipStream_t
 }
 
 template <int DT, bool SPARSE>
-static int fused_mode(const ss_weight_desc *d1, const ConvParams &p, hipStream_t s)
+static int fused_mode(const ss_weight_desc *d1, const ChainParams &p, hipStream_t s)
 {
     if (p.Cout3 > 0) return third_mode<DT, SPARSE>(d1, p, s);
     auto run = [&](int id) {

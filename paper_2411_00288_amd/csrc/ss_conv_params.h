@@ -27,23 +27,29 @@ struct ConvParams {
     uint16_t *y2;             // [P][Cout2]
     int Cout2, Ks2, Kp2, Mt2, act2;
     unsigned a2_bytes, meta2_bytes;
-    // third contraction (a 1x1 convolution on the second one's output, which is written too): Cout3 = 0 where there is none
-    const uint8_t *a3_vals;
-    const uint32_t *a3_meta;
-    const float *bias3;
-    uint16_t *y3;             // [P][Cout3]
-    int Cout3, Ks3, Kp3, Mt3, act3;
-    unsigned a3_bytes, meta3_bytes;
-    int shares3, per3;        // few pixels: the shares in which this reduction is added up (pw_shares), and the steps of one
     // split reduction: workgroups per output tile (1 = none), fp32 partial sums [tile][split][BM*BN] and one ticket
     // counter per tile, both in the caller's workspace
     int nsplit, plan_tile, plan_bm, plan_bn;      // plan_*: the tile the split was planned (and the workspace sized) for
     float *ws_part;
 };
 
+// With a third contraction, a 1x1 convolution on the second one's output, which is written too (apart from ConvParams: every other call would clear
+// these fields, and the kernels that take all of it carry them).
+struct ThirdParams {
+    const uint8_t *a3_vals;
+    const uint32_t *a3_meta;
+    const float *bias3;
+    uint16_t *y3;             // [P][Cout3]
+    int Cout3, Ks3, Kp3, Mt3, act3;      // Cout3 = 0: there is none
+    unsigned a3_bytes, meta3_bytes;
+    int shares3, per3;        // few pixels: the shares in which this reduction is added up (pw_shares), and the steps of one
+};
+struct ChainParams : ConvParams, ThirdParams {};
+static_assert(sizeof(ConvParams) <= 288, "what every call clears");
+
 // What a launch carries to the kernels of the short calls; the rest of ConvParams follows from it (unpack_args).  A launch whose arguments
 // take more than 112 bytes costs the host 3.65 to 3.8 us, up to 112 bytes 3.0 (none at all: 1.5), whatever the kernel: as long as all of a
-// small layer's work on the GPU (profiles/launch_and_packing_waits.md).  (ConvParams has some 360 bytes, and a kernel that asks for its
+// small layer's work on the GPU (profiles/launch_and_packing_waits.md).  (ConvParams has some 300 bytes, and a kernel that asks for its
 // grid's size another 256.)
 struct ConvArgs {
     const uint16_t *x;
@@ -484,7 +490,7 @@ int forced_split();
 #define SS_DECLARE_CONV(NAME) \
     int conv_dispatch_##NAME(const ss_weight_desc *desc, const ConvParams &p, hipStream_t s);
 #define SS_DECLARE_FUSED(NAME) \
-    int fused_dispatch_##NAME(const ss_weight_desc *d1, const ConvParams &p, hipStream_t s); \
+    int fused_dispatch_##NAME(const ss_weight_desc *d1, const ChainParams &p, hipStream_t s); \
     int mlp_dispatch_##NAME(const MlpParams &p, hipStream_t s);
 SS_DECLARE_CONV(f16_sparse) SS_DECLARE_CONV(f16_dense) SS_DECLARE_CONV(bf16_sparse) SS_DECLARE_CONV(bf16_dense)
 SS_DECLARE_CONV(i8_sparse) SS_DECLARE_CONV(i8_dense) SS_DECLARE_CONV(f8_sparse) SS_DECLARE_CONV(f8_dense)

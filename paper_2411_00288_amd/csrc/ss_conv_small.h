@@ -461,8 +461,10 @@ enum { THIRD_NONE = 0, THIRD_SHARE = 1, THIRD_TWO = 2, THIRD_HANDED = 3 };
 // MT: the first layer's row tiles (2 or 4: a bottleneck of 64 or 128 channels), or 0 where they are known at run time only.  Known, the
 // waves' shares and the loops over them are constants, and every LDS read of a phase is under way before the first is needed.
 template <int DT, bool SPARSE, int PX, int MT, int THIRD>
-__global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams p)
+__global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(kernel_params<THIRD> p)
 {
+    ThirdParams p3{};
+    if constexpr (THIRD != THIRD_NONE) p3 = p;
     if constexpr (MT > 0) { p.Mt = p.Ks2 = MT; p.Cout = 32 * MT; }
     constexpr int TAPS = 9, VPR = 36, NT = kPairWaves * 64, RING = 9, KS2 = MT > 0 ? MT : 8;
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
@@ -636,27 +638,27 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
     lds_barrier();
     // ---- the third layer's weights: in flight while the second one is multiplied
     constexpr int KS3 = THIRD ? 8 : 1;
-    const int kg3 = THIRD ? (p.Mt3 == 2 ? wave >> 1 : p.Mt3 == 3 ? wave * 11 >> 5 : wave >> 2) : 0, rt3 = wave - kg3 * p.Mt3;      // (2 <= Mt3 <= 4)
-    const int span3 = THIRD == THIRD_SHARE ? p.per3 : THIRD == THIRD_TWO ? 2 * p.per3 : KS3;      // (a multiple of 4 steps in all, 16 at most)
-    const int t0 = THIRD ? min(kg3 * span3, p.Ks3) : 0, t1 = THIRD ? min(t0 + span3, p.Ks3) : 0;
+    const int kg3 = THIRD ? (p3.Mt3 == 2 ? wave >> 1 : p3.Mt3 == 3 ? wave * 11 >> 5 : wave >> 2) : 0, rt3 = wave - kg3 * p3.Mt3;      // (2 <= Mt3 <= 4)
+    const int span3 = THIRD == THIRD_SHARE ? p3.per3 : THIRD == THIRD_TWO ? 2 * p3.per3 : KS3;      // (a multiple of 4 steps in all, 16 at most)
+    const int t0 = THIRD ? min(kg3 * span3, p3.Ks3) : 0, t1 = THIRD ? min(t0 + span3, p3.Ks3) : 0;
     A a3[KS3];
     if constexpr (THIRD) {
-        const __amdgpu_buffer_rsrc_t ra3 = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.a3_vals), 0, (int)p.a3_bytes, kRsrcFlags);
-        const __amdgpu_buffer_rsrc_t rm3 = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.a3_meta), 0, (int)p.meta3_bytes, kRsrcFlags);
+        const __amdgpu_buffer_rsrc_t ra3 = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p3.a3_vals), 0, (int)p3.a3_bytes, kRsrcFlags);
+        const __amdgpu_buffer_rsrc_t rm3 = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p3.a3_meta), 0, (int)p3.meta3_bytes, kRsrcFlags);
 #pragma unroll
         for (int j = 0; j < KS3; j++)
-            if (t0 + j < t1) load_w(a3[j], ra3, rm3, rt3, p.Ks3, p.Kp3, t0 + j);      // uniform
+            if (t0 + j < t1) load_w(a3[j], ra3, rm3, rt3, p3.Ks3, p3.Kp3, t0 + j);      // uniform
     }
     // ... and the bias of the quads of channels that this thread will finish
     constexpr int Q3 = THIRD ? PX * 32 / NT : 1;          // (at most four row tiles)
     f32x4 bias3[Q3];
     auto quad3 = [&](int i, int *pl) {                    // quad of channels, the fastest; pixel
-        const int t = tid + i * NT, n = p.Mt3 * 8;
-        *pl = p.Mt3 == 4 ? t >> 5 : p.Mt3 == 2 ? t >> 4 : t * 2731 >> 16;      // (2731 = ceil(2^16 / 24), exact below 2^12)
+        const int t = tid + i * NT, n = p3.Mt3 * 8;
+        *pl = p3.Mt3 == 4 ? t >> 5 : p3.Mt3 == 2 ? t >> 4 : t * 2731 >> 16;      // (2731 = ceil(2^16 / 24), exact below 2^12)
         return t - *pl * n;
     };
     if constexpr (THIRD) {
-        const __amdgpu_buffer_rsrc_t rb3 = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.bias3), 0, p.bias3 != nullptr ? p.Cout3 * 4 : 0, kRsrcFlags);
+        const __amdgpu_buffer_rsrc_t rb3 = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p3.bias3), 0, p3.bias3 != nullptr ? p3.Cout3 * 4 : 0, kRsrcFlags);
 #pragma unroll
         for (int i = 0; i < Q3; i++) {
             int pl;
@@ -733,7 +735,7 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
         B32 b3[KS3];
 #pragma unroll
         for (int j = 0; j < KS3; j++) {                   // (all on their way first; a step past the share's end is read and not used)
-            const uint16_t *src = out2 + cc * T2ROW + 32 * min(t0 + j, p.Ks3 - 1) + 16 * g;
+            const uint16_t *src = out2 + cc * T2ROW + 32 * min(t0 + j, p3.Ks3 - 1) + 16 * g;
             b3[j].lo = *reinterpret_cast<const u32x4 *>(src);
             b3[j].hi = *reinterpret_cast<const u32x4 *>(src + 8);
         }
@@ -757,10 +759,10 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
             constexpr int PER = KS3 / 2;                  // steps of a share: four, or three of twelve in all
 #pragma unroll
             for (int j = 0; j < PER; j++) {
-                if (j == PER - 1 && p.per3 < PER) break;  // uniform
+                if (j == PER - 1 && p3.per3 < PER) break;  // uniform
                 acc3 = mma(a3[j], b3[j], acc3, t0 + j);
             }
-            if (p.per3 < PER) second = mma(a3[PER - 1], b3[PER - 1], second, t0 + PER - 1);
+            if (p3.per3 < PER) second = mma(a3[PER - 1], b3[PER - 1], second, t0 + PER - 1);
 #pragma unroll
             for (int j = PER; j < KS3; j++)
                 if (t0 + j < t1) second = mma(a3[j], b3[j], second, t0 + j);
@@ -789,7 +791,7 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
             multiply();
         }
         lds_barrier();
-        const float floor3 = p.act3 == SS_ACT_RELU ? 0.f : -__builtin_inff();
+        const float floor3 = p3.act3 == SS_ACT_RELU ? 0.f : -__builtin_inff();
 #pragma unroll
         for (int i = 0; i < Q3; i++) {
             int pl;
@@ -802,7 +804,7 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
 #pragma unroll
                 for (int e = 0; e < 4; e++) v[e] += u[e];
             };
-            const int next = p.Mt3 * 256, other = (int)(part2 - part);      // from a row tile's wave to its next one, from a share to the wave's second
+            const int next = p3.Mt3 * 256, other = (int)(part2 - part);      // from a row tile's wave to its next one, from a share to the wave's second
             if constexpr (THIRD == THIRD_TWO) {
                 add(0);
                 add(other);
@@ -812,15 +814,15 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
                 add(next);
             } else {
                 add(0);
-                if (p.shares3 > 1) add(next);             // uniform
-                if (p.shares3 > 2) {
+                if (p3.shares3 > 1) add(next);             // uniform
+                if (p3.shares3 > 2) {
                     add(2 * next);
                     add(3 * next);
                 }
             }
 #pragma unroll
             for (int e = 0; e < 4; e++) v[e] += bias3[i][e];
-            if (p.act3 == SS_ACT_GELU) {
+            if (p3.act3 == SS_ACT_GELU) {
 #pragma unroll
                 for (int e = 0; e < 4; e++) v[e] = gelu_cdf<DT>(v[e]);
             } else {
@@ -828,13 +830,13 @@ __global__ __launch_bounds__(kPairWaves * 64) void pair_small_kernel(ConvParams 
                 for (int e = 0; e < 4; e++) v[e] = floor_at(v[e], floor3);
             }
             if (n0 + pl < p.P)
-                *reinterpret_cast<uint2 *>(p.y3 + (size_t)(n0 + pl) * p.Cout3 + o) = make_uint2(cvt_pack2<DT>(v[0], v[1]), cvt_pack2<DT>(v[2], v[3]));
+                *reinterpret_cast<uint2 *>(p3.y3 + (size_t)(n0 + pl) * p3.Cout3 + o) = make_uint2(cvt_pack2<DT>(v[0], v[1]), cvt_pack2<DT>(v[2], v[3]));
         }
     }
 }
 
 template <int DT, bool SPARSE, int PX, int MT, int THIRD>
-static int launch_pair_small(ConvParams p, hipStream_t s)
+static int launch_pair_small(kernel_params<THIRD> p, hipStream_t s)
 {
     fast_div_setup((unsigned)p.Mt, &p.tm_mul, &p.tm_sh);      // (the kernel deals its waves out over the row tiles)
     const size_t smem = pair_shape(PX, p.Ks / 9, p.Cout, THIRD != THIRD_NONE ? p.Cout2 : 0).total;
@@ -857,14 +859,14 @@ static int launch_pair_small(ConvParams p, hipStream_t s)
 // The fused pair on few pixels: PX = 16 or 32 as given, or chosen (px = 0) while one workgroup per compute unit holds them
 // all.  SS_ERR_INVALID_ARG where it does not fit or the tiled kernel is the better choice.
 template <int DT, bool SPARSE>
-static int pair_small(const ss_weight_desc *d1, const ConvParams &p, int px, hipStream_t s)
+static int pair_small(const ss_weight_desc *d1, const ChainParams &p, int px, hipStream_t s)
 {
     const int ncu = compute_units();
     if (ncu <= 0) return SS_ERR_HIP;
     const bool third = p.Cout3 > 0;
     if (px == 0) px = pair_small_pixels(p.P, ncu);
     if (px == 0 || !pair_small_fits(d1, px, third ? p.Cout2 : 0, p.Cout3)) return SS_ERR_INVALID_ARG;
-    ConvParams q = p;
+    ChainParams q = p;
     int plan = THIRD_NONE;
     if (third) {
         q.shares3 = pw_shares(p.P, p.Ks3, p.Mt3, SPARSE, ncu);
