@@ -70,12 +70,17 @@ def build_ops(batch: int, image: int, dtype: int = wl.BF16, seed: int = 7000, im
 
 class Trunk:
     """Device-resident weights and activation buffers of the trunk, and a ``forward()`` that enqueues every kernel
-    on the current stream (capturable in a HIP graph)."""
+    on the current stream (capturable in a HIP graph).
+
+    ``chain`` is what ``forward`` enqueues.  ``launches`` is the same work with the first layer and its pooling, and the
+    third layer of a joined pair, in launches of their own: for timing a layer, or for comparing; both write the same
+    buffers, with the same bits."""
 
     def __init__(self, batch: int, image: int = 224, dtype: int = wl.BF16, sparse: bool = True, seed: int = 7000,
                  c3_scale: float = 0.25, keep_host: bool = False, image_channels: int = 4, fuse_pairs: bool = True):
         """fuse_pairs: run a block's 3x3 and the 1x1 expansion after it as one kernel where that is faster (widths up
-        to 128 on the sparse path, 64 on the dense twin), and with it the next block's first 1x1, and the pooling with the layer before it; the 3x3's own output buffer is then never written."""
+        to 128 on the sparse path, 64 on the dense twin; the 3x3's own output buffer is then never written), with it
+        the next block's first 1x1, and the pooling with the layer before it."""
         self.ops, self.shapes = build_ops(batch, image, dtype, seed, image_channels)
         self.dtype, self.sparse = dtype, sparse
         tdt = ss.torch_dtype(dtype)
@@ -130,8 +135,8 @@ class Trunk:
         torch.cuda.synchronize()
 
     def _join(self, pos, prepared, fuse_pairs):
-        """``chain``, what ``forward`` enqueues: the launches, except that the first layer and its pooling, and a fused pair and the 1x1 layer that opens the next block run as one
-        kernel where the library expects that to be faster (every buffer is written as before)."""
+        """``chain``: the launches, except that the first layer and its pooling, and a fused pair and the 1x1 layer that
+        opens the next block, run as one kernel where the library expects that to be faster."""
         chain = list(self.launches)
         ops = {op.name: op for op in self.ops}
         stem, pool = self.ops[0], self.ops[1]               # (the first two launches)
