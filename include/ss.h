@@ -378,16 +378,16 @@ int ss_conv2d_q8_dense_fwd(const ss_weight_desc *desc, const void *x, int32_t N,
  * The first layer of an image network and the max pooling behind it (window 3, stride 2, padding 1) in one kernel: y bit for bit as
  * ss_conv2d_dense_fwd writes it, and pooled [N][(Ho-1)/2+1][(Wo-1)/2+1][cout] as ss_maxpool2d computes it from y, without reading y back: bit
  * for bit too, except in a window with several different NaN, where it is the one with the largest bit pattern.
- * 7x7 kernel with stride 2 on three or four 16-bit channels, cout % 8 == 0, SS_ACT_RELU, y below 2^31 - 2^27 bytes; anything else SS_ERR_UNSUPPORTED.  y and pooled 16-byte
- * aligned, overlapping neither each other nor the inputs.  Needs no workspace.  Asynchronous on `stream`.
+ * 7x7 kernel with stride 2 on three or four 16-bit channels, cout % 8 == 0, SS_ACT_RELU, y below 2^31 - 2^27 bytes; anything else SS_ERR_UNSUPPORTED.  y and
+ * pooled 16-byte aligned, overlapping neither each other nor the inputs.  Needs no workspace.  Asynchronous on `stream`.
  */
 int ss_conv2d_maxpool_dense_fwd(const ss_weight_desc *desc, const void *x, int32_t N, int32_t H, int32_t Wd, const void *dense, const float *bias,
                                 int32_t stride_h, int32_t stride_w, int32_t pad_h, int32_t pad_w, int32_t act, void *y, void *pooled, void *stream);
 
 /*
- * Would ss_conv2d_maxpool_dense_fwd take this layer on an input [N][H][Wd]?  [host], touches no device.  Measured on 32 x 32 to 320 x 320 pixels, 1 to 64 images,
- * three and four channels: 0.57 to 1.01 of the two calls' time with 64, 128 and 256 output channels, up to 1.04 with 96; with 32 and 8 channels, which leave
- * half and more of its tiles' products unused, 0.69 to 1.0 while they are at most two workgroups of 14 x 14 outputs per compute unit, up to 1.4 beyond.
+ * Would ss_conv2d_maxpool_dense_fwd take this layer on an input [N][H][Wd]?  [host], touches no device.  Measured on 32 x 32 to 320 x 320 pixels, 1 to 64
+ * images, three and four channels: 0.57 to 1.01 of the two calls' time with 64, 128 and 256 output channels, up to 1.04 with 96; with 32 and 8 channels, which
+ * leave half and more of its tiles' products unused, 0.69 to 1.0 while they are at most two workgroups of 14 x 14 outputs per compute unit, up to 1.4 beyond.
  */
 int ss_conv2d_maxpool_dense_query(const ss_weight_desc *desc, int32_t N, int32_t H, int32_t Wd, int32_t stride_h, int32_t stride_w, int32_t pad_h,
                                   int32_t pad_w, int32_t act, int32_t *supported /*[host] out*/);

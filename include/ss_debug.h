@@ -21,10 +21,10 @@ extern "C" {
  * 10 / 11 the resident-grid 3x3 kernel with 256x128 / 256x64 tiles; 12 the dense 7x7 first-layer kernel; 13 the
  * activation-stationary 1x1 kernel; 20 to 22 the kernels for few output pixels (32 channels x 16 pixels, 32 x 32,
  * 64 x 32 per workgroup); 40 / 41 the inverted bottleneck of ss_conv2d_pw_fused_fwd and its twin with 64 pixels per workgroup / with 32 and
- * a wave for each 32 intermediate channels (at most 512), 42 the same resident, with both layers' weights in LDS (96 and 128 channels at both ends); 60 to 65 the depthwise convolution on the vector ALU, on the matrix unit, and for few
- * outputs with 1 x 2, 1 x 4, 2 x 4 and 4 x 4 outputs per thread.  Ids the problem has no kernel for fall back to the library's choice; with an
- * id of 10 or more no split of the reduction is planned.  Process-wide, read with a relaxed atomic load at every
- * launch; meant for single-threaded tests.  Always returns SS_OK.  [host]
+ * a wave for each 32 intermediate channels (at most 512), 42 the same resident, with both layers' weights in LDS (96 and 128 channels at both ends); 60 to 65
+ * the depthwise convolution on the vector ALU, on the matrix unit, and for few outputs with 1 x 2, 1 x 4, 2 x 4 and 4 x 4 outputs per thread.  Ids the problem
+ * has no kernel for fall back to the library's choice; with an id of 10 or more no split of the reduction is planned.  Process-wide, read with a relaxed
+ * atomic load at every launch; meant for single-threaded tests.  Always returns SS_OK.  [host]
  */
 int ss_debug_force_tile(int32_t id);
 

@@ -172,7 +172,8 @@ struct ThirdLayer {
 // Can a third layer follow this pair?  (the conditions of the kernels: whole tiles everywhere, 128 channels of the second output at a time)
 static bool third_fits(const ss_weight_desc *d1, const ss_weight_desc *d2, const ss_weight_desc *d3)
 {
-    return d1->korder == SS_K_CRS && d1->kh == 3 && d1->kw == 3 && d1->cin % 32 == 0 && d1->cout <= 128 && d2->cout % 128 == 0 && d3->cout % 32 == 0 && d3->cout <= 128;
+    return d1->korder == SS_K_CRS && d1->kh == 3 && d1->kw == 3 && d1->cin % 32 == 0 && d1->cout <= 128 && d2->cout % 128 == 0 &&
+           d3->cout % 32 == 0 && d3->cout <= 128;
 }
 
 template <bool SPARSE>
@@ -524,8 +525,8 @@ extern "C" int ss_conv2d_pw2_fused_query(const ss_weight_desc *desc1, int32_t N,
     // up to 3.2; 0.65 to 0.93 for sparse 32 -> 32 -> 128 alone).
     // Beyond: the ResNet-50 trunk at 224 x 224, us, no layer joined / all that can be: batch 32 726 / 677, 64 1115 / 1080.  Not
     // where it loses: 128 channels on one workgroup per compute unit, where the pair has producer waves (batch 16, 516 without, 528 with those three, 503
-    // with the others), and dense layers whose third one has more than 64 channels (batch 64: 1290 / 1301; 1266 with those of 64).  Over 400 layers of 32 to 128
-    // channels by themselves 0.51 to 0.99 where it says so.
+    // with the others), and dense layers whose third one has more than 64 channels (batch 64: 1290 / 1301; 1266 with those of 64).  Over 400 layers of 32 to
+    // 128 channels by themselves 0.51 to 0.99 where it says so.
     const int px = pair_small_pixels(P, planning_units());
     if (px > 0) {
         *pays = pair_pays && (pair_small_fits(desc1, px, desc2->cout, desc3->cout) || (sparse && desc1->cout == 32 && desc2->cout == 128));

@@ -24,8 +24,8 @@
 // pooled ones, neighbouring tiles overlap by two rows and columns, 1.31 times the products.  Behind a ReLU only: outputs are then +0 or more, or
 // NaN, whose bit patterns are ordered like unsigned numbers, so that the maximum is that of the patterns and a NaN wins.  ResNet-50 stem at
 // 224 x 224, us, layer and pooling / both in one: batch 1 10.3 / 7.6, 8 20 / 11.7, 64 54 / 42.6
-// (three channels 54 / 43.0), 128 105 / 84.  At 32 to 320 pixels and 1 to 64 images, also where 7 x 7 pooled outputs fill their tiles badly (64 x 64 and 128 x 128,
-// 2.25 and 1.56 times the products): 64 channels 0.58 to 0.91 of the two calls' time, 128 0.57 to 1.0, 256 0.63 to 1.01.
+// (three channels 54 / 43.0), 128 105 / 84.  At 32 to 320 pixels and 1 to 64 images, also where 7 x 7 pooled outputs fill their tiles badly (64 x 64 and 128 x
+// 128, 2.25 and 1.56 times the products): 64 channels 0.58 to 0.91 of the two calls' time, 128 0.57 to 1.0, 256 0.63 to 1.01.
 #ifndef SS_CONV_IMAGE_H_
 #define SS_CONV_IMAGE_H_
 #include "ss_conv_stream.h"

@@ -371,7 +371,8 @@ constexpr size_t smem_body(bool with_residual, int fuse_waves = 0, bool third = 
 template <int BM, int BN, int MODE, int KH, int KW, bool DEEP>
 constexpr size_t smem_bytes(bool with_residual, int fuse_waves = 0, bool third = false)
 {
-    return smem_body<BM, BN, MODE, KH, KW, DEEP>(with_residual, fuse_waves, third) + (size_t)(third && BM < 128 ? 128 : BM) * 4;      // (the first bias, later the third: up to 128 channels)
+    // (behind the body: the first layer's bias, later the third's, up to 128 channels)
+    return smem_body<BM, BN, MODE, KH, KW, DEEP>(with_residual, fuse_waves, third) + (size_t)(third && BM < 128 ? 128 : BM) * 4;
 }
 
 // Waves per SIMD the register allocator must leave room for: small wave tiles are latency-bound
@@ -1074,10 +1075,10 @@ void conv_kernel(typename std::conditional<short_args(MODE, FUSE), ConvArgs, ker
             constexpr int kNonTemporal = 2;               // cache-policy bit nt of the buffer instructions
             const int nparts = p.Cout2 / 128;
             // A residual is mostly the block's input at its last use, y2 what the next block reads as its own.  Where both together are about as large as the
-            // 256 MB that the memory's cache holds, the residual's lines push y2 out before that: it is then read with the non-temporal hint.  (A hint: a caller
-            // who reads the residual again finds it in memory.)  ResNet-50 trunk at 224 x 224, us without and with:
-            //   residual of the 56 x 56 blocks, 64 channels: 40 images (61 MiB) 716 / 718, 48 (73) 907 / 883, 56 (86) 960 / 931, 64 (98) 1077 / 1038 (dense 1241 / 1228),
-            //   72 (110) 1131 / 1096, 80 (122) 1215 / 1191, 88 (135) 1423 / 1412, 92 (141) 1460 / 1463; 96 (147) would be 1474 / 1486;
+            // 256 MB that the memory's cache holds, the residual's lines push y2 out before that: it is then read with the non-temporal hint.  (A hint: a
+            // caller who reads the residual again finds it in memory.)  ResNet-50 trunk at 224 x 224, us without and with:
+            //   residual of the 56 x 56 blocks, 64 channels: 40 images (61 MiB) 716 / 718, 48 (73) 907 / 883, 56 (86) 960 / 931, 64 (98) 1077 / 1038 (dense
+            //   1241 / 1228), 72 (110) 1131 / 1096, 80 (122) 1215 / 1191, 88 (135) 1423 / 1412, 92 (141) 1460 / 1463; 96 (147) would be 1474 / 1486;
             //   of the 28 x 28 blocks, 128 channels: 100 images (77 MiB) 1524 / 1493, 128 (98) 1822 / 1788, 160 (122) 2099 / 2074, 184 (141) 2520 / 2507.
             // 200 images of 128 x 128 (100 MiB) 1089 / 1049, 48 of 256 x 256 (96) 1029 / 993, 64 (128) 1260 / 1224.
             const long long res_bytes = (long long)p.P * p.Cout2 * 2;
@@ -1616,8 +1617,8 @@ void mlp_kernel(MlpParams p)
 // Bound by memory with ReLU (231 MB in 46 us), by the vector ALU with GELU (of 2880 vector instructions per tile of 96 -> 384 -> 96 in bf16, 2500 are
 // the GELUs).  With the weights from memory for each wave the address unit took as long as the vector ALU; with an accumulator tile more, to
 // multiply ahead of the activations, three waves per SIMD had no registers left for weights on their way, and each matrix instruction waited for LDS.
-// 401408 pixels, 96 -> 384 -> 96, bf16, mlp_kernel against this one, us: ReLU sparse 69.0 -> 46.0, dense 88.9 -> 57.7; GELU dense 116.8 -> 98.6 (f16 114.9 -> 94.0).
-// TILES: 32-channel tiles of the input and of the output; WAVES: per workgroup.
+// 401408 pixels, 96 -> 384 -> 96, bf16, mlp_kernel against this one, us: ReLU sparse 69.0 -> 46.0, dense 88.9 -> 57.7; GELU dense 116.8 -> 98.6
+// (f16 114.9 -> 94.0).  TILES: 32-channel tiles of the input and of the output; WAVES: per workgroup.
 template <int DT, bool SPARSE, int TILES, int WAVES, bool GELU1>
 __global__ __launch_bounds__(WAVES * 64)
 void mlp_resident_kernel(MlpParams p)

@@ -150,13 +150,13 @@ static inline bool mlp_takes(const MlpParams &p, bool sparse, int id)
 //     them 0.82 of its time in the mean and with GELU always below 1; without, few channels leave it nothing to do at once: 32 and 32 1.03 to 1.11,
 //     32 and 64 0.98 to 1.07, from 128 together on 0.63 to 1.03.
 //   * the resident one from some pixel tiles per compute unit on.  A SIMD that gets a tile more than its neighbours keeps
-//     the chip waiting for it, and the weights' way to LDS is some 3 us, so it takes a few tiles per SIMD.  Times against mlp_kernel's at 1.6, 2.4, 3.2, 4, 5.5, 7 and
-//     12.25 tiles of 32 pixels per SIMD, bf16, C -> 4 C -> C:
+//     the chip waiting for it, and the weights' way to LDS is some 3 us, so it takes a few tiles per SIMD.  Times against mlp_kernel's at 1.6, 2.4, 3.2, 4,
+//     5.5, 7 and 12.25 tiles of 32 pixels per SIMD, bf16, C -> 4 C -> C:
 //       ReLU   sparse  96   0.85 0.82 0.78 0.80 0.77 0.72 0.68      dense  96   0.79 0.82 0.73 0.72 0.73 0.69 0.62
 //              sparse 128   0.94 0.96 0.88 0.85 0.86 0.79 0.76
 //       GELU   dense   96   0.95 1.01 0.95 0.86 0.90 0.83 0.84     (in a ConvNeXt block on new inputs each time 0.95 to 0.90, 173 -> 163 us at 128 x 56 x 56)
-//     With other intermediates, from 1.5 tiles per SIMD on: 96 channels and 128 between them 0.83 to 1.03, 256 0.62 to 0.90 (dense GELU 0.91 to 1.03), sparse 512
-//     and 640 0.68 to 0.86.  128 channels live less from the pixels that they save and more on the weights' way: 128 between them 1.04 to 1.11, so never;
+//     With other intermediates, from 1.5 tiles per SIMD on: 96 channels and 128 between them 0.83 to 1.03, 256 0.62 to 0.90 (dense GELU 0.91 to 1.03), sparse
+//     512 and 640 0.68 to 0.86.  128 channels live less from the pixels that they save and more on the weights' way: 128 between them 1.04 to 1.11, so never;
 //     256 and 384 0.98 to 1.05 below 3 tiles per SIMD, 0.81 to 1.0 from there on.
 static inline int choose_mlp(const MlpParams &p, bool sparse, int ncu)
 {
@@ -260,8 +260,8 @@ static inline int choose_height(const ConvParams &p, int id, bool taps, bool byt
 // take 1.75 of the 128-row tile's time at K = 640 (2-byte units), 1.63 at 1280, 1.57 at 2300; choose_vec never compares the two here, and choose_height takes K
 // not into account.  Of 12264 layers on cold inputs with each tile forced (profiles/tile_heights.md) 1643 change their tile, 0.862 of its time in the mean,
 // 99 % of them at most 1.00: 225 to 256 and 449 to 511 channels from 128 rows to 256, above those layers whose last round would be nearly empty.
-// (In calls on new inputs each time: int8 160 -> 256 on 62 28x28 images 22.65 -> 19.2 us, 144 -> 452 on fifteen 40x40 21.6 -> 18.1, 256 -> 484 on twenty 35.0 -> 33.9.)
-// The line of 0.86 is below 1 because the grid's rounding is not known better: at 0.92 2886 layers change (0.897), but 8 % of them lose.
+// (In calls on new inputs each time: int8 160 -> 256 on 62 28x28 images 22.65 -> 19.2 us, 144 -> 452 on fifteen 40x40 21.6 -> 18.1, 256 -> 484 on twenty
+// 35.0 -> 33.9.)  The line of 0.86 is below 1 because the grid's rounding is not known better: at 0.92 2886 layers change (0.897), but 8 % of them lose.
 static inline int choose_vec8_sparse(const ConvParams &p, int id, int ncu)
 {
     auto time = [&](int rows, int base, int start) {      // base + start / K: a tile's time in hundredths of the 128-row one's
@@ -284,14 +284,15 @@ static inline int choose_vec8_sparse(const ConvParams &p, int id, int ncu)
 //   * sparse, 129 to 160 channels: one tile of 160 rows instead of two of 128 (0.89 of their time in the mean over 543 layers, 0.73 to 1.00, 16- and 8-bit
 //     alike; dense 0.97, up to 1.21);
 //   * 96 rows where they are no more tiles (65 to 96, 129 to 192, 257 to 288 channels).  A compute unit holds four workgroups of 128 rows or five of 96
-//     (without a residual), so by workgroups per unit: up to two no gain (0.99 to 1.03), two to three 0.98 for dense int8 and 1.00 for the others, three to four
-//     0.92 dense (sparse 0.95), four to five, one round instead of two, 0.79 (0.95), five to six, two rounds on both sides, 0.98 to 1.01, above 0.89 to 0.92
-//     (0.98, one in fifteen slower: not taken).  Not measured for dense FP8.
-// In calls on new inputs, us: bf16 40 -> 136 on thirty 40x40 images 12.9 -> 9.65, int8 96 -> 148 on twenty 10.5 -> 9.0 (dense 11.4 -> 10.5), FP8 64 -> 132 on a hundred
-// 28x28 16.9 -> 15.3, int8 dense 64 -> 92 13.75 -> 11.0,
+//     (without a residual), so by workgroups per unit: up to two no gain (0.99 to 1.03), two to three 0.98 for dense int8 and 1.00 for the others, three to
+//     four 0.92 dense (sparse 0.95), four to five, one round instead of two, 0.79 (0.95), five to six, two rounds on both sides, 0.98 to 1.01, above 0.89 to
+//     0.92 (0.98, one in fifteen slower: not taken).  Not measured for dense FP8.
+// In calls on new inputs, us: bf16 40 -> 136 on thirty 40x40 images 12.9 -> 9.65, int8 96 -> 148 on twenty 10.5 -> 9.0 (dense 11.4 -> 10.5), FP8 64 -> 132 on
+// a hundred 28x28 16.9 -> 15.3, int8 dense 64 -> 92 13.75 -> 11.0,
 // f16 dense 56 -> 90 on 42 40x40 19.2 -> 14.4 and 56 -> 180 27.6 -> 22.8, bf16 sparse 40 -> 92 11.45 -> 10.6.
-// With a residual, whose fp32 tile changes the LDS of a workgroup (33 KB for 128 rows, 25 for 96, 42 for 160), the layers that move gain more: 292 16-bit ones with
-// and without, strides of one and two: sparse 160 rows 0.83 of the time of 128 in the mean (0.68 to 0.98; without 0.88), sparse 96 rows 0.89 (0.95), dense 0.87 (0.89).
+// With a residual, whose fp32 tile changes the LDS of a workgroup (33 KB for 128 rows, 25 for 96, 42 for 160), the layers that move gain more: 292 16-bit ones
+// with and without, strides of one and two: sparse 160 rows 0.83 of the time of 128 in the mean (0.68 to 0.98; without 0.88), sparse 96 rows 0.89 (0.95),
+// dense 0.87 (0.89).
 static inline int choose_vec_short(const ConvParams &p, bool bytes, bool sparse, bool f8, int ncu)
 {
     const int id = choose_tile(p, false, false);

@@ -295,7 +295,7 @@ void conv_stream_kernel(ConvParams p, int tiles_n, int slots_n)
                 // take 1.3 % longer with the comparison.)
                 const unsigned step = (unsigned)(tn * 32 * 2) * (unsigned)p.Cout;
                 if constexpr (DT == SS_I8) {
-                    if ((lane >> 2) < p.P - n0 - 16 * j - 32 * tn) {      // (with the scalar offset: the store by itself and a wait state behind it, see store_b128)
+                    if ((lane >> 2) < p.P - n0 - 16 * j - 32 * tn) {      // (a scalar offset: the store apart, a wait state behind it, see store_b128)
                         __builtin_amdgcn_sched_barrier(0);
                         __builtin_amdgcn_raw_buffer_store_b128(w[j], ry, (int)yoff[tm][j], (int)step, 0);
                         __builtin_amdgcn_sched_barrier(0);
