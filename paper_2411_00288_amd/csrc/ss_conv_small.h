@@ -877,7 +877,9 @@ static int pair_small(const ss_weight_desc *d1, const ChainParams &p, int px, hi
         constexpr int MT = decltype(mt)::value;
         auto pixels = [&](auto t) -> int {
             constexpr int THIRD = decltype(t)::value;
-            return px == 16 ? launch_pair_small<DT, SPARSE, 16, MT, THIRD>(q, s) : launch_pair_small<DT, SPARSE, 32, MT, THIRD>(q, s);
+            // (a chain of products is the layer's own form from more pixels on than workgroups of 16 hold)
+            if constexpr (THIRD == THIRD_HANDED) return px == 16 ? (int)SS_ERR_INVALID_ARG : launch_pair_small<DT, SPARSE, 32, MT, THIRD>(q, s);
+            else return px == 16 ? launch_pair_small<DT, SPARSE, 16, MT, THIRD>(q, s) : launch_pair_small<DT, SPARSE, 32, MT, THIRD>(q, s);
         };
         using std::integral_constant;
         if constexpr (MT > 0) {
