@@ -1,7 +1,8 @@
 // Depthwise convolution (one filter per channel), NHWC 16-bit, stride 1: the grouped convolutions that the paper
-// leaves dense (Sec. 4, "Architectures"), e.g. the 7x7 of a ConvNeXt block.  Two kernels: square filters run on the matrix
-// unit (dwconv_mfma_kernel), the others on the vector ALU, whose 49 multiply-adds per output bound the 7x7 at about 50 us for the
-// 128 x 56 x 56 x 96 layer before any load or conversion (99 us measured).
+// leaves dense (Sec. 4, "Architectures"), e.g. the 7x7 of a ConvNeXt block.  Three kernels (choose_dw, ss_dwconv.h): square 5x5 and 7x7 filters
+// with many outputs run on the matrix unit (dwconv_mfma_kernel), 3x3 and few outputs in one memory latency on the vector ALU (dwconv_few_kernel), the
+// others on the vector ALU row by row, whose 49 multiply-adds per output bound the 7x7 at about 50 us for the 128 x 56 x 56 x 96 layer
+// before any load or conversion (99 us measured).
 #include "ss_internal.h"
 #include "ss_conv_params.h"
 #include "ss_dwconv.h"
